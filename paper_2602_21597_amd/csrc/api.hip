@@ -80,7 +80,8 @@ struct ngdb_ctx_s {
     DevBuf score, coef, win, mask, loss_terms, rec_coef, rec_row;
     DevBuf keys_a, keys_b, vals_a, vals_b, hist, scan_tmp, uniq, seg_off, n_uniq;
     DevBuf rank_dist;   // distances of one entity chunk in the all-entity ranking
-    DevBuf rank_thr, rank_count;   // filtered ranks: distance of every listed answer, entities closer than it
+    DevBuf rank_thr, rank_count;   // filtered ranks: distance of every listed answer, entities closer than it (total, chunk)
+    DevBuf rank_filter;            // integer rows, bounds and lists of the filtered passes
     DevBuf colsum_part; // 6 scratch areas of the bias-gradient column sums
     DevBuf gW;          // gradients of the 12 MLP tensors, packed
     // The six weight matrices of the vector family's MLPs as ready-made B operands of the contraction
@@ -1106,6 +1107,168 @@ int presize(ngdb_ctx_t* c) {
     return NGDB_OK;
 }
 
+// ---- all-entity passes: the entity rows chunk by chunk
+constexpr int RANK_CHUNK = 1 << 16;
+constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k); rows the integer grid is made from
+constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filter may leave undecided
+
+// Where a chunk of entity rows lies: in the table (or its bf16 copy), or, with text features, fused
+// into the context's chunk buffer by this call.
+struct ChunkRows { const float* rows; const uint16_t* rows16; };
+int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, hipStream_t s, ChunkRows* out) {
+    const int d = c->cfg.d;
+    *out = ChunkRows{c->prm.E.p + (size_t)e0 * d, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) + (size_t)e0 * d : nullptr};
+    if (c->cfg.d_sem == 0) return NGDB_OK;
+    SemFuseArgs fa{};
+    fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.id_base = e0;
+    fa.n_rows = cnt; fa.d = d; fa.ds = c->cfg.d_sem; fa.out = ptr<float>(c->rank_ef);
+    HIPCHK(c, launch_sem_fuse(fa, s));
+    out->rows = ptr<float>(c->rank_ef);
+    return NGDB_OK;
+}
+
+// Buffers of a filtered pass over R branch rows of B queries.
+int rank_filter_space(ngdb_ctx_t* c, int bits, int R, int B, int chunk, RankFilter* f) {
+    *f = RankFilter{};
+    f->d = c->cfg.d; f->bits = bits; f->words = rank_filter_words(f->d, bits);
+    f->ldy = (R + 127) / 128 * 128; f->lde = (chunk + 127) / 128 * 128; f->room = RANK_ROOM;
+    size_t at = 0;
+    auto place = [&](size_t words) { const size_t o = at; at += (words + 63) / 64 * 64; return o; };
+    const size_t o_part = place((size_t)32 * f->d), o_lo = place(f->d), o_grid = place(2), o_yq = place((size_t)f->words * f->ldy),
+                 o_base = place(2 * (size_t)f->ldy), o_rq = place(f->ldy), o_eq = place((size_t)f->words * f->lde),
+                 o_slack = place(f->lde), o_list = place(bits == 16 ? (size_t)B * f->room : 0),
+                 o_found = place(bits == 8 ? (size_t)f->ldy * (f->lde / 128) : 0),
+                 o_pair = place(bits == 8 ? rank_found_bytes(f->ldy, f->lde) / 4 : 0);
+    f->n_counters = B + c->cfg.n_entities / RANK_CHUNK + 32;
+    const size_t o_count = place(f->n_counters);
+    const int rc = ensure(c, c->rank_filter, at * 4, true);
+    if (rc != NGDB_OK) return rc;
+    uint32_t* p = ptr<uint32_t>(c->rank_filter);
+    f->part = reinterpret_cast<float*>(p + o_part); f->lo = reinterpret_cast<float*>(p + o_lo); f->grid = reinterpret_cast<float*>(p + o_grid);
+    f->Yq = p + o_yq; f->base = reinterpret_cast<float*>(p + o_base); f->row_q = reinterpret_cast<int32_t*>(p + o_rq);
+    f->Eq = p + o_eq; f->slack = reinterpret_cast<int32_t*>(p + o_slack);
+    f->list = reinterpret_cast<int32_t*>(p + o_list); f->found = p + o_found; f->found_pair = p + o_pair; f->count = reinterpret_cast<int32_t*>(p + o_count);
+    f->overflowed = f->count + B;
+    return NGDB_OK;
+}
+
+// The filter serves the plain distance (vector family); a table of a few thousand rows is ranked
+// in fp32 in less time than the filter's launches take.
+bool rank_filtered(const ngdb_ctx_t* c) { return c->cfg.family == NGDB_FAMILY_VEC && c->cfg.n_entities > 2 * RANK_SAMPLE; }
+
+// The grid of a filtered pass (rows spread over the table; with text features its first fused rows) and the
+// branch rows on it.
+int rank_filter_begin(ngdb_ctx_t* c, const ngdb_plan_t* pl, const RankFilter& f, const int32_t* roots, const ChunkRows& fused,
+                      int fused_rows, hipStream_t s) {
+    const int N = c->cfg.n_entities;
+    const bool sem = c->cfg.d_sem > 0;
+    HIPCHK(c, launch_rank_grid(f, sem ? fused.rows : c->prm.E.p, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr,
+                               sem ? 1 : N / RANK_SAMPLE, sem ? fused_rows : RANK_SAMPLE, s));
+    HIPCHK(c, launch_rank_rows(f, ptr<float>(c->act), roots, pl->hp.n_roots, pl->d_root_off, pl->hp.n_queries, s));
+    if (f.bits == 8) HIPCHK(c, launch_fill_zero_i32(reinterpret_cast<int32_t*>(f.found), f.ldy * (f.lde / 128), s));
+    return NGDB_OK;
+}
+
+int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int topk, int32_t* d_ids, float* d_dist, hipStream_t s) {
+    const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
+    const float* act = ptr<float>(c->act);
+    const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
+    const bool filtered = rank_filtered(c);
+    const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
+    float* dist = nullptr;
+    int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
+    if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, (size_t)chunk * d * sizeof(float), true);
+    RankFilter f{};
+    if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 8, R, B, chunk, &f);
+    if (rc != NGDB_OK) return rc;
+    dist = ptr<float>(c->rank_dist);
+    Overflowed only{f.row_q, f.count, f.room, f.overflowed};
+    Timed tm(c, NGDB_TK_SCORE, s);
+    // filtered: the sample's k-th distance lets k / sample of the first chunk pass, and chunks grow with what has
+    // been ranked (each at most 12 times that), so that a list holds 12 k entities and some that are only near it
+    const int sample = std::min(RANK_SAMPLE, std::max(512, 128 * topk));
+    int i_chunk = 0;
+    for (int e0 = 0; e0 < N; ++i_chunk) {
+        const int want = !filtered ? chunk : (e0 == 0 ? sample : (int)std::min<int64_t>(chunk, 12ll * e0));
+        const int cnt = std::min(want, N - e0);
+        ChunkRows er;
+        if ((rc = rank_chunk_rows(c, e0, cnt, s, &er)) != NGDB_OK) return rc;
+        if (!filtered || e0 == 0) {
+            HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16));
+            HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, s));
+            if (filtered && (rc = rank_filter_begin(c, pl, f, roots, er, std::min(cnt, RANK_SAMPLE), s)) != NGDB_OK) return rc;
+        } else {
+            HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
+            HIPCHK(c, launch_near_tile(f, R, cnt, d_dist, topk, s));
+            HIPCHK(c, launch_near_merge(f, i_chunk, act, roots, pl->d_root_off, B, er.rows, er.rows16, e0, cnt, topk, d_dist, d_ids, s));
+            only.any = f.overflowed + i_chunk;
+            HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16, &only));
+            HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, false, d_dist, d_ids, s, &only));
+        }
+        e0 += cnt;
+    }
+    return NGDB_OK;
+}
+
+int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, const int32_t* d_ans_off, const int32_t* d_ans, int n_ans,
+                int32_t* d_rank, float* d_ans_dist, hipStream_t s) {
+    const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
+    const float* act = ptr<float>(c->act);
+    const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
+    const bool sem = c->cfg.d_sem > 0;
+    // (with very many answers per query most entities are undecided for one of them)
+    const bool filtered = rank_filtered(c) && n_ans <= 64ll * B;
+    const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
+    int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
+    if (rc == NGDB_OK) rc = ensure(c, c->rank_count, (size_t)n_ans * 8, true);
+    if (rc == NGDB_OK && !d_ans_dist) rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, true);
+    if (rc == NGDB_OK && sem) rc = ensure(c, c->rank_ef, (size_t)std::max(chunk, std::min(n_ans, RANK_CHUNK)) * d * sizeof(float), true);
+    RankFilter f{};
+    if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 16, R, B, chunk, &f);
+    if (rc != NGDB_OK) return rc;
+    float* dist = ptr<float>(c->rank_dist);
+    float* thr = d_ans_dist ? d_ans_dist : ptr<float>(c->rank_thr);
+    int32_t* total = ptr<int32_t>(c->rank_count);
+    int32_t* in_chunk = total + n_ans;
+    Overflowed only{f.row_q, f.count, f.room, f.overflowed};
+    Timed tm(c, NGDB_TK_SCORE, s);
+    HIPCHK(c, launch_fill_zero_i32(total, 2 * n_ans, s));
+    // distance of every listed answer to its query (the arithmetic of the all-entity pass, so an answer
+    // compares equal to itself there)
+    for (int a0 = 0; a0 < n_ans; a0 += RANK_CHUNK) {
+        const int cnt = std::min(RANK_CHUNK, n_ans - a0);
+        const float* rows = c->prm.E.p;
+        if (sem) {
+            SemFuseArgs fa{};
+            fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.ids = d_ans + a0; fa.n_rows = cnt;
+            fa.d = d; fa.ds = c->cfg.d_sem; fa.out = ptr<float>(c->rank_ef);
+            HIPCHK(c, launch_sem_fuse(fa, s));
+            rows = ptr<float>(c->rank_ef);
+        }
+        HIPCHK(c, launch_answer_distance(act, box_off, c->cfg.box_alpha, roots, pl->d_root_off, d_ans_off, B, sem ? nullptr : d_ans, a0, cnt,
+                                         rows, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr, d, thr, s));
+    }
+    // entities strictly closer than each answer, chunk by chunk
+    for (int e0 = 0; e0 < N; e0 += chunk) {
+        const int cnt = std::min(chunk, N - e0);
+        ChunkRows er;
+        if ((rc = rank_chunk_rows(c, e0, cnt, s, &er)) != NGDB_OK) return rc;
+        if (filtered) {
+            if (e0 == 0 && (rc = rank_filter_begin(c, pl, f, roots, er, std::min(cnt, RANK_SAMPLE), s)) != NGDB_OK) return rc;
+            HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
+            HIPCHK(c, launch_sum_tile(f, R, cnt, reinterpret_cast<uint32_t*>(dist), ld, s));
+            HIPCHK(c, launch_count_sure(f, reinterpret_cast<const uint32_t*>(dist), ld, pl->d_root_off, d_ans_off, thr, B, cnt, in_chunk, s));
+            HIPCHK(c, launch_count_open(f, e0 / chunk, reinterpret_cast<const uint32_t*>(dist), ld, act, roots, pl->d_root_off, d_ans_off, thr, B, er.rows, er.rows16, in_chunk, total, s));
+            only.any = f.overflowed + e0 / chunk;
+        }
+        HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16, filtered ? &only : nullptr));
+        HIPCHK(c, launch_count_less(dist, ld, pl->d_root_off, d_ans_off, thr, B, cnt, total, s, filtered ? &only : nullptr));
+        if (filtered && e0 + cnt < N) HIPCHK(c, launch_fill_zero_i32(f.count, B, s));
+    }
+    HIPCHK(c, launch_finish_rank(total, thr, d_ans_off, B, n_ans, d_rank, s));
+    return NGDB_OK;
+}
+
 // Device address of the scratch array on the current GPU (looked up on first use per device).
 hipError_t noalloc_scratch(unsigned char** out) {
     int dev = -1;
@@ -1177,7 +1340,7 @@ void ngdb_destroy(ngdb_ctx_t* c) {
     DevBuf* all[] = {&c->act, &c->dact, &c->Z[0], &c->Z[1], &c->Z[2], &c->H[0], &c->H[1], &c->H[2], &c->dH[0],
                      &c->dH[1], &c->dH[2], &c->Att, &c->dAtt, &c->Dx, &c->score, &c->coef, &c->win, &c->mask,
                      &c->loss_terms, &c->rec_coef, &c->rec_row, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->hist, &c->scan_tmp,
-                     &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->colsum_part, &c->rank_dist, &c->rank_thr, &c->rank_count,
+                     &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->colsum_part, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
                      &c->Wb, &c->Ef, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
                      &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb};
     for (DevBuf* b : all) release(*b);
@@ -1481,34 +1644,8 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
         if (e == hipErrorInvalidValue) return fail(c, NGDB_ERR_UNSUPPORTED, "embedding width / union branch count too large for the scoring kernel");
         HIPCHK(c, e);
     } else {
-        // entity chunks: distances of every branch row to the chunk, then the running top-k
-        const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots;
-        const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
-        const int chunk = std::min(N, 1 << 16);
-        const int ld = (chunk + 3) & ~3;
-        rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
+        rc = rank_nearest(c, pl, roots, topk, d_topk_ids, d_topk_dist, s);
         if (rc != NGDB_OK) return rc;
-        if (sem) {
-            rc = ensure(c, c->rank_ef, (size_t)chunk * d * sizeof(float), true);
-            if (rc != NGDB_OK) return rc;
-        }
-        Timed tm(c, NGDB_TK_SCORE, s);
-        for (int e0 = 0; e0 < N; e0 += chunk) {
-            const int cnt = std::min(chunk, N - e0);
-            const float* rows = c->prm.E.p + (size_t)e0 * d;
-            if (sem) {   // the chunk's fused rows
-                SemFuseArgs fa{};
-                fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.id_base = e0;
-                fa.n_rows = cnt; fa.d = d; fa.ds = c->cfg.d_sem; fa.out = ptr<float>(c->rank_ef);
-                HIPCHK(c, launch_sem_fuse(fa, s));
-                rows = ptr<float>(c->rank_ef);
-            }
-            HIPCHK(c, launch_l1_tile(ptr<float>(c->act), box_off, c->cfg.box_alpha, roots, R, rows, nullptr, cnt, d,
-                                     ptr<float>(c->rank_dist), ld, s,
-                                     c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) + (size_t)e0 * d : nullptr));
-            HIPCHK(c, launch_topk_merge(ptr<float>(c->rank_dist), ld, pl->d_root_off, pl->hp.n_queries, e0, cnt, topk,
-                                        e0 == 0, d_topk_dist, d_topk_ids, s));
-        }
     }
     HIPCHK(c, hipEventRecord(pl->blob.last_use, s));
     return NGDB_OK;
@@ -1606,52 +1743,8 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     rc = enqueue_forward(c, pl, er, s, ctx_space(c, reclaim));
     if (rc != NGDB_OK) return rc;
     if (n_ans > 0) {
-        const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
-        const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
-        const int chunk = std::min(std::max(N, n_ans), 1 << 16);
-        const int ld = (chunk + 3) & ~3;
-        if ((rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true)) != NGDB_OK) return rc;
-        if ((rc = ensure(c, c->rank_count, (size_t)n_ans * 4, true)) != NGDB_OK) return rc;
-        if (!d_ans_dist && (rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, true)) != NGDB_OK) return rc;
-        if (sem && (rc = ensure(c, c->rank_ef, (size_t)chunk * d * sizeof(float), true)) != NGDB_OK) return rc;
-        float* thr = d_ans_dist ? d_ans_dist : ptr<float>(c->rank_thr);
-        Timed tm(c, NGDB_TK_SCORE, s);
-        HIPCHK(c, launch_fill_zero_i32(ptr<int32_t>(c->rank_count), n_ans, s));
-        SemFuseArgs fa{};
-        fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.d = d; fa.ds = c->cfg.d_sem;
-        fa.out = ptr<float>(c->rank_ef);
-        // distance of every listed answer to its query, by the kernels of the all-entity pass
-        // (the same arithmetic, so an answer compares equal to itself there)
-        for (int a0 = 0; a0 < n_ans; a0 += chunk) {
-            const int cnt = std::min(chunk, n_ans - a0);
-            const float* rows = c->prm.E.p;
-            const int32_t* ids = d_ans + a0;
-            if (sem) {
-                fa.ids = d_ans + a0; fa.id_base = 0; fa.n_rows = cnt;
-                HIPCHK(c, launch_sem_fuse(fa, s));
-                rows = ptr<float>(c->rank_ef);
-                ids = nullptr;
-            }
-            HIPCHK(c, launch_l1_tile(ptr<float>(c->act), box_off, c->cfg.box_alpha, roots, R, rows, ids, cnt, d,
-                                     ptr<float>(c->rank_dist), ld, s, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr));
-            HIPCHK(c, launch_answer_dist(ptr<float>(c->rank_dist), ld, pl->d_root_off, d_ans_off, B, a0, cnt, thr, s));
-        }
-        // entities strictly closer than each answer, chunk by chunk
-        for (int e0 = 0; e0 < N; e0 += chunk) {
-            const int cnt = std::min(chunk, N - e0);
-            const float* rows = c->prm.E.p + (size_t)e0 * d;
-            if (sem) {
-                fa.ids = nullptr; fa.id_base = e0; fa.n_rows = cnt;
-                HIPCHK(c, launch_sem_fuse(fa, s));
-                rows = ptr<float>(c->rank_ef);
-            }
-            HIPCHK(c, launch_l1_tile(ptr<float>(c->act), box_off, c->cfg.box_alpha, roots, R, rows, nullptr, cnt, d,
-                                     ptr<float>(c->rank_dist), ld, s,
-                                     c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) + (size_t)e0 * d : nullptr));
-            HIPCHK(c, launch_count_less(ptr<float>(c->rank_dist), ld, pl->d_root_off, d_ans_off, thr, B, cnt,
-                                        ptr<int32_t>(c->rank_count), s));
-        }
-        HIPCHK(c, launch_finish_rank(ptr<int32_t>(c->rank_count), thr, d_ans_off, B, n_ans, d_rank, s));
+        rc = rank_listed(c, pl, roots, d_ans_off, d_ans, n_ans, d_rank, d_ans_dist, s);
+        if (rc != NGDB_OK) return rc;
     }
     HIPCHK(c, hipEventRecord(pl->blob.last_use, s));
     return NGDB_OK;

@@ -283,19 +283,24 @@ struct ScoreArgs {
 hipError_t launch_score(const ScoreArgs& a, bool train, hipStream_t s);
 
 // ---------------------------------------------------------------- ranking (rank.hip)
-// dist[r*ld + e] = ||act[row_ids[r]] - Emat[id(e)]||_1 for r < n_rows, e < n_ent; id(e) = ent_ids[e] or e.
+// dist[r*ld + e] = ||act[row_ids[r]] - Emat[e]||_1 for r < n_rows, e < n_ent.
 // With off (box family, 0 <= alpha <= 1): the box distance of (act row, off row) to the entity row.
-// With Emat16 (bf16 bit patterns, same shape and indexing as Emat) the entity rows are read from it.
+// With Emat16 (bf16 bit patterns, same shape as Emat) the entity rows are read from it.
+// With `only` (this call completes a filtered pass): row tiles without a query whose list overflowed
+// are left out, and so are, in the two launches below, the queries whose list did not.
+struct Overflowed {
+    const int32_t* row_q;      // query of every branch row
+    int32_t* count;            // [queries] listed entities; more than room: overflowed
+    int room;
+    const int32_t* any;        // whether there is such a query
+};
 hipError_t launch_l1_tile(const float* act, const float* off, float alpha, const int32_t* row_ids, int n_rows,
-                          const float* Emat, const int32_t* ent_ids, int n_ent, int d, float* dist, int ld, hipStream_t s,
-                          const uint16_t* Emat16 = nullptr);
-// filtered ranks of listed answers (answers of query q: ans_off[q]..ans_off[q+1]-1):
-// thr[a] = distance of answer a (column a - a0 of dist) to its query, min over the query's rows
-hipError_t launch_answer_dist(const float* dist, int ld, const int32_t* root_off, const int32_t* ans_off, int n_queries,
-                              int a0, int cnt, float* thr, hipStream_t s);
+                          const float* Emat, int n_ent, int d, float* dist, int ld, hipStream_t s,
+                          const uint16_t* Emat16 = nullptr, const Overflowed* only = nullptr);
 // count[a] += #{entities e < n_ent of this chunk: min over rows dist[row, e] < thr[a]}
 hipError_t launch_count_less(const float* dist, int ld, const int32_t* root_off, const int32_t* ans_off,
-                             const float* thr, int n_queries, int n_ent, int32_t* count, hipStream_t s);
+                             const float* thr, int n_queries, int n_ent, int32_t* count, hipStream_t s,
+                             const Overflowed* only = nullptr);
 // rank[a] = 1 + count[a] - #{listed answers b of a's query: thr[b] < thr[a]}
 hipError_t launch_finish_rank(const int32_t* count, const float* thr, const int32_t* ans_off, int n_queries, int n_ans,
                               int32_t* rank, hipStream_t s);
@@ -306,7 +311,51 @@ hipError_t launch_fill_zero_i32(int32_t* p, int n, hipStream_t s);
 // per query q: entity value = min over rows root_off[q]..root_off[q+1]-1 of dist; merges the
 // k best (value, ent_base + e) of this chunk into out_dist/out_ids [n_queries, k]
 hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off, int n_queries, int ent_base, int n_ent,
-                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s);
+                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s,
+                             const Overflowed* only = nullptr);
+
+// Ranking with a filter on integer sums (rank_filter.hip): buffers of one pass.  Rows as words of 4
+// (bits = 8) or 2 (bits = 16) coordinates, word-major; leading dimensions are multiples of 128.
+struct RankFilter {
+    int d, bits, words;              // words: rank_filter_words(d, bits)
+    float *part, *lo, *grid;         // [32 * d] scratch, [d] grid origin, [2] step and its inverse
+    uint32_t* Yq; int ldy;           // branch rows [words, ldy]
+    float* base;                     // [2 * ldy] constant of every branch row in a bound from below, from above
+    int32_t* row_q;                  // [ldy] its query
+    uint32_t* Eq; int lde;           // entity rows of a chunk [words, lde]
+    int32_t* slack;                  // [lde] error of an entity row, in steps
+    // top-k: what the tiles of a chunk found, [ldy, tiles] words (zero between chunks) and rank_found_bytes(ldy, lde)
+    uint32_t *found, *found_pair;
+    // filtered ranks: per query the entities to be computed in fp32 [queries, room], their number.  Both: a
+    // number above room marks a query for the fp32 pass of the chunk
+    int32_t *list, *count; int room;
+    int32_t* overflowed;             // per chunk: a list had no room (behind count: n_counters in all, cleared with the grid)
+    int n_counters;
+};
+int rank_filter_words(int d, int bits);
+size_t rank_found_bytes(int ldy, int lde);
+// the grid of a pass from n_rows rows of a table, row_step apart
+hipError_t launch_rank_grid(const RankFilter& f, const float* E, const uint16_t* E16, int64_t row_step, int n_rows, hipStream_t s);
+hipError_t launch_rank_rows(const RankFilter& f, const float* act, const int32_t* row_ids, int n_rows, const int32_t* root_off,
+                            int n_queries, hipStream_t s);
+hipError_t launch_rank_entities(const RankFilter& f, const float* E, const uint16_t* E16, int n_ent, hipStream_t s);
+// lists the chunk's entities that may be among the k nearest (best: running [queries, k] distances), and merges them
+hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const float* best, int k, hipStream_t s);
+hipError_t launch_near_merge(const RankFilter& f, int chunk, const float* act, const int32_t* row_ids, const int32_t* root_off,
+                             int n_queries, const float* E, const uint16_t* E16, int ent_base, int n_ent, int k, float* out_dist,
+                             int32_t* out_ids, hipStream_t s);
+// sums[r * ld + e] of the chunk; chunk_count[a] = entities certainly closer than answer a, the undecided
+// ones listed; these computed, total[a] += both
+hipError_t launch_sum_tile(const RankFilter& f, int n_rows, int n_ent, uint32_t* sums, int ld, hipStream_t s);
+hipError_t launch_count_sure(const RankFilter& f, const uint32_t* sums, int ld, const int32_t* root_off, const int32_t* ans_off,
+                             const float* thr, int n_queries, int n_ent, int32_t* chunk_count, hipStream_t s);
+hipError_t launch_count_open(const RankFilter& f, int chunk, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
+                             const int32_t* ans_off, const float* thr, int n_queries, const float* E, const uint16_t* E16,
+                             int32_t* chunk_count, int32_t* total, hipStream_t s);
+// thr[a] = fp32 distance of answer a to its query, a0 <= a < a0 + cnt (row ans[a] of E, or row a - a0 where ans is null)
+hipError_t launch_answer_distance(const float* act, const float* off, float alpha, const int32_t* row_ids, const int32_t* root_off,
+                                  const int32_t* ans_off, int n_queries, const int32_t* ans, int a0, int cnt, const float* E,
+                                  const uint16_t* E16, int d, float* thr, hipStream_t s);
 
 // ---------------------------------------------------------------- index (index.hip)
 struct IndexBuffers {   // device scratch owned by the context, sized for n_keys

@@ -4,10 +4,12 @@
 //
 // The distance pass is bound by plain vector arithmetic (two VALU operations per
 // coordinate: subtract, add-absolute; an L1 distance is not a contraction, so the
-// matrix cores cannot help): a workgroup owns a 128 x 128 tile of (branch rows x
-// entities), stages both operands k-major in LDS 16 coordinates at a time, and
-// every lane accumulates an 8 x 8 block of distances in registers, so that one
-// 16-byte LDS read feeds 32 accumulations.
+// matrix cores cannot help): a workgroup owns a tile of (branch rows x entities),
+// 128 x 128 where both sides fill it, stages both operands k-major in LDS 16
+// coordinates at a time, and every lane accumulates an 8 x 8 block of distances in
+// registers, so that one 16-byte LDS read feeds 32 accumulations.  Large tables in
+// the vector family go through these kernels for a first sample only, and for what
+// the filter of rank_filter.hip cannot take.
 //
 // The selection pass keeps, per lane, the best KMAX (distance, id) pairs of the
 // entities it scanned (a union query takes the minimum over its branch rows
@@ -21,133 +23,153 @@
 namespace ngdb {
 namespace {
 
-constexpr int TQ = 128, TE = 128, DC = 16, LDT = 128 + 4;
+constexpr int DC = 16;
 
-// entity e of the tile is row ent_ids[e] of Emat if ent_ids is given, else row e.  The
-// distance of a (row, entity) pair is summed by one lane over the coordinates in ascending
-// order, so its value does not depend on where in a tile, or in which launch, the pair falls.
+// Tile of 16*RPL rows x 16*EPL entities, RPL x EPL pairs per lane (entities in groups of four, 64
+// apart, so that neighbouring lanes read adjacent 16-byte units of LDS).  The distance of a (row,
+// entity) pair is summed by one lane over the coordinates in ascending order, so its value does
+// not depend on where in a tile, or in which launch, the pair falls.
 // BOX (box family): the row side is a box, centre from act and offset from off, and a coordinate
 // contributes relu(a - o) + alpha * min(a, o) = max(alpha * a, a - (1 - alpha) * o), a = |e - c|;
 // the offsets are staged already multiplied by (1 - alpha): five VALU operations per coordinate.
 // Emat16 (if set): the entity rows are read from this bf16 copy of Emat.
-template <bool BOX>
+// count (if set): tiles without a row whose query has count > room are left out.
+template <bool BOX, int RPL, int EPL>
 __global__ __launch_bounds__(256) void l1_tile_kernel(const float* __restrict__ act, const float* __restrict__ off,
                                                       float alpha, const int32_t* __restrict__ row_ids,
                                                       int n_rows, const float* __restrict__ Emat,
-                                                      const uint16_t* __restrict__ Emat16,
-                                                      const int32_t* __restrict__ ent_ids, int n_ent, int d,
-                                                      float* __restrict__ dist, int ld) {
-    __shared__ __attribute__((aligned(16))) float Ys[2][DC][LDT];
-    __shared__ __attribute__((aligned(16))) float Es[2][DC][LDT];
-    __shared__ __attribute__((aligned(16))) float Os[BOX ? 2 : 1][BOX ? DC : 1][LDT];
+                                                      const uint16_t* __restrict__ Emat16, int n_ent, int d,
+                                                      float* __restrict__ dist, int ld, const int32_t* __restrict__ row_q,
+                                                      const int32_t* __restrict__ count, int room,
+                                                      const int32_t* __restrict__ any) {
+    if (any && *any == 0) return;                          // uniform
+    constexpr int TQ = 16 * RPL, TE = 16 * EPL, LDQ = TQ + 4, LDE = TE + 4;
+    constexpr int LQ = (TQ * 4 + 255) / 256, LE = (TE * 4 + 255) / 256;     // float4 per thread and stage
+    __shared__ __attribute__((aligned(16))) float Ys[2][DC][LDQ];
+    __shared__ __attribute__((aligned(16))) float Es[2][DC][LDE];
+    __shared__ __attribute__((aligned(16))) float Os[BOX ? 2 : 1][BOX ? DC : 1][LDQ];
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
-    const int e0 = blockIdx.x * TE, r0 = blockIdx.y * TQ;
-
-    // loader: 128 rows x 16 coordinates = 512 float4, two per thread and operand
-    const float* yrow[2];
-    const float* orow[2];
-    const float* erow[2];
-    const uint16_t* erow16[2];
-    int lrow[2], lkq[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int idx = tid + i * 256;
-        lrow[i] = idx >> 2;
-        lkq[i] = idx & 3;
-        const int r = min(r0 + lrow[i], n_rows - 1);          // clamped rows are computed and never stored
-        yrow[i] = act + (size_t)row_ids[r] * d;
-        orow[i] = BOX ? off + (size_t)row_ids[r] * d : nullptr;
-        const int ec = min(e0 + lrow[i], n_ent - 1);
-        erow[i] = Emat + (size_t)(ent_ids ? ent_ids[ec] : ec) * d;
-        erow16[i] = Emat16 ? Emat16 + (size_t)(ent_ids ? ent_ids[ec] : ec) * d : nullptr;
+    const int r0 = blockIdx.y * TQ;
+    if (count) {
+        const int r = r0 + tid;
+        if (!__syncthreads_or(tid < TQ && r < n_rows && count[row_q[r]] > room)) return;
     }
-    float4 ry[2], re[2], ro[2];
-    const float shrink = 1.f - alpha;
-    auto issue = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int kc = min(k0 + lkq[i] * 4, d - 4);
-            ry[i] = *reinterpret_cast<const float4*>(yrow[i] + kc);
-            re[i] = Emat16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(erow16[i] + kc))
-                           : *reinterpret_cast<const float4*>(erow[i] + kc);
-            if (BOX) ro[i] = *reinterpret_cast<const float4*>(orow[i] + kc);
-        }
-    };
-    auto stage = [&](int buf, int k0) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            // coordinates past d contribute |0 - 0|
-            const bool ok = k0 + lkq[i] * 4 < d;
-            const float4 y = ok ? ry[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4 e = ok ? re[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-            Ys[buf][lkq[i] * 4 + 0][lrow[i]] = y.x; Ys[buf][lkq[i] * 4 + 1][lrow[i]] = y.y;
-            Ys[buf][lkq[i] * 4 + 2][lrow[i]] = y.z; Ys[buf][lkq[i] * 4 + 3][lrow[i]] = y.w;
-            Es[buf][lkq[i] * 4 + 0][lrow[i]] = e.x; Es[buf][lkq[i] * 4 + 1][lrow[i]] = e.y;
-            Es[buf][lkq[i] * 4 + 2][lrow[i]] = e.z; Es[buf][lkq[i] * 4 + 3][lrow[i]] = e.w;
-            if (BOX) {
-                const float4 o = ok ? ro[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-                Os[buf][lkq[i] * 4 + 0][lrow[i]] = shrink * o.x; Os[buf][lkq[i] * 4 + 1][lrow[i]] = shrink * o.y;
-                Os[buf][lkq[i] * 4 + 2][lrow[i]] = shrink * o.z; Os[buf][lkq[i] * 4 + 3][lrow[i]] = shrink * o.w;
-            }
-        }
-    };
+    // (a launch that only completes a filtered pass has few workgroups, each with several entity tiles)
+    for (int e0 = blockIdx.x * TE; e0 < n_ent; e0 += gridDim.x * TE) {
 
-    float acc[8][8];
+        const float* yrow[LQ];
+        const float* orow[LQ];
+        const float* erow[LE];
+        const uint16_t* erow16[LE];
+        const int lkq = tid & 3, lrow = tid >> 2;             // row lrow + 64 * i of either side
+        const bool has_y = lrow < TQ, has_e = lrow < TE;      // (a side of 32 rows has work for half the threads)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-
-    const int nk = (d + DC - 1) / DC;
-    issue(0);
-    stage(0, 0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) issue((kt + 1) * DC);
-#pragma unroll
-        for (int k = 0; k < DC; ++k) {
-            const float4 y0 = *reinterpret_cast<const float4*>(&Ys[buf][k][ty * 8]);
-            const float4 y1 = *reinterpret_cast<const float4*>(&Ys[buf][k][ty * 8 + 4]);
-            const float4 x0 = *reinterpret_cast<const float4*>(&Es[buf][k][tx * 8]);
-            const float4 x1 = *reinterpret_cast<const float4*>(&Es[buf][k][tx * 8 + 4]);
-            const float yv[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
-            const float ev[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            if (BOX) {
-                const float4 o0 = *reinterpret_cast<const float4*>(&Os[buf][k][ty * 8]);
-                const float4 o1 = *reinterpret_cast<const float4*>(&Os[buf][k][ty * 8 + 4]);
-                const float ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const float a = fabsf(yv[i] - ev[j]);
-                        acc[i][j] += fmaxf(alpha * a, a - ov[i]);
-                    }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[i][j] += fabsf(yv[i] - ev[j]);
-            }
+        for (int i = 0; i < LQ; ++i) {
+            const int r = min(r0 + lrow + 64 * i, n_rows - 1);          // clamped rows are computed and never stored
+            yrow[i] = act + (size_t)row_ids[r] * d;
+            orow[i] = BOX ? off + (size_t)row_ids[r] * d : nullptr;
         }
-        if (kt + 1 < nk) stage(buf ^ 1, (kt + 1) * DC);
+#pragma unroll
+        for (int i = 0; i < LE; ++i) {
+            const int ec = min(e0 + lrow + 64 * i, n_ent - 1);
+            erow[i] = Emat + (Emat16 ? 0 : (size_t)ec * d);
+            erow16[i] = Emat16 ? Emat16 + (size_t)ec * d : nullptr;
+        }
+        float4 ry[LQ], re[LE], ro[LQ];
+        const float shrink = 1.f - alpha;
+        auto issue = [&](int k0) {
+            const int kc = min(k0 + lkq * 4, d - 4);
+#pragma unroll
+            for (int i = 0; i < LQ; ++i) {
+                ry[i] = *reinterpret_cast<const float4*>(yrow[i] + kc);
+                if (BOX) ro[i] = *reinterpret_cast<const float4*>(orow[i] + kc);
+            }
+#pragma unroll
+            for (int i = 0; i < LE; ++i)
+                re[i] = Emat16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(erow16[i] + kc))
+                               : *reinterpret_cast<const float4*>(erow[i] + kc);
+        };
+        auto stage = [&](int buf, int k0) {
+            const bool ok = k0 + lkq * 4 < d;                  // coordinates past d contribute |0 - 0|
+            const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int i = 0; i < LQ; ++i) {
+                if (!has_y) break;
+                const int row = lrow + 64 * i;
+                const float4 y = ok ? ry[i] : zero;
+                Ys[buf][lkq * 4 + 0][row] = y.x; Ys[buf][lkq * 4 + 1][row] = y.y;
+                Ys[buf][lkq * 4 + 2][row] = y.z; Ys[buf][lkq * 4 + 3][row] = y.w;
+                if (BOX) {
+                    const float4 o = ok ? ro[i] : zero;
+                    Os[buf][lkq * 4 + 0][row] = shrink * o.x; Os[buf][lkq * 4 + 1][row] = shrink * o.y;
+                    Os[buf][lkq * 4 + 2][row] = shrink * o.z; Os[buf][lkq * 4 + 3][row] = shrink * o.w;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < LE; ++i) {
+                if (!has_e) break;
+                const int row = lrow + 64 * i;
+                const float4 e = ok ? re[i] : zero;
+                Es[buf][lkq * 4 + 0][row] = e.x; Es[buf][lkq * 4 + 1][row] = e.y;
+                Es[buf][lkq * 4 + 2][row] = e.z; Es[buf][lkq * 4 + 3][row] = e.w;
+            }
+        };
+
+        float acc[RPL][EPL];
+#pragma unroll
+        for (int i = 0; i < RPL; ++i)
+#pragma unroll
+            for (int j = 0; j < EPL; ++j) acc[i][j] = 0.f;
+
+        const int nk = (d + DC - 1) / DC;
+        issue(0);
+        stage(0, 0);
         __syncthreads();
-    }
+        for (int kt = 0; kt < nk; ++kt) {
+            const int buf = kt & 1;
+            if (kt + 1 < nk) issue((kt + 1) * DC);
+#pragma unroll
+            for (int k = 0; k < DC; ++k) {
+                float yv[RPL], ov[RPL], ev[EPL];
+#pragma unroll
+                for (int i = 0; i < RPL; ++i) {
+                    yv[i] = Ys[buf][k][ty * RPL + i];
+                    ov[i] = BOX ? Os[BOX ? buf : 0][BOX ? k : 0][ty * RPL + i] : 0.f;
+                }
+#pragma unroll
+                for (int j = 0; j < EPL; j += 4) {
+                    const float4 x = *reinterpret_cast<const float4*>(&Es[buf][k][(j >> 2) * 64 + tx * 4]);
+                    ev[j] = x.x; ev[j + 1] = x.y; ev[j + 2] = x.z; ev[j + 3] = x.w;
+                }
+#pragma unroll
+                for (int i = 0; i < RPL; ++i)
+#pragma unroll
+                    for (int j = 0; j < EPL; ++j) {
+                        const float a = fabsf(yv[i] - ev[j]);
+                        acc[i][j] += BOX ? fmaxf(alpha * a, a - ov[i]) : a;
+                    }
+            }
+            if (kt + 1 < nk) stage(buf ^ 1, (kt + 1) * DC);
+            __syncthreads();
+        }
 
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = r0 + ty * 8 + i;
-        if (r >= n_rows) continue;
-        float* out = dist + (size_t)r * ld + e0 + tx * 8;
-        if (e0 + tx * 8 + 7 < n_ent) {
-            *reinterpret_cast<float4*>(out) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-            *reinterpret_cast<float4*>(out + 4) = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
-        } else {
+        for (int i = 0; i < RPL; ++i) {
+            const int r = r0 + ty * RPL + i;
+            if (r >= n_rows) continue;
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (e0 + tx * 8 + j < n_ent) out[j] = acc[i][j];
+            for (int j = 0; j < EPL; j += 4) {
+                const int e = e0 + (j >> 2) * 64 + tx * 4;
+                float* out = dist + (size_t)r * ld + e;
+                if (e + 3 < n_ent) {
+                    *reinterpret_cast<float4*>(out) = make_float4(acc[i][j], acc[i][j + 1], acc[i][j + 2], acc[i][j + 3]);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (e + t < n_ent) out[t] = acc[i][j + t];
+                }
+            }
         }
     }
 }
@@ -159,12 +181,14 @@ __device__ __forceinline__ bool before(float d, int i, float d2, int i2) { retur
 // one workgroup per query: merges the chunk's distances into the query's running top-k
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ dist, int ld, const int32_t* __restrict__ root_off,
                                                    int ent_base, int n_ent, int k, bool first_chunk,
-                                                   float* __restrict__ out_dist, int32_t* __restrict__ out_ids) {
+                                                   float* __restrict__ out_dist, int32_t* __restrict__ out_ids,
+                                                   int32_t* __restrict__ count, int room) {
     __shared__ float ld_[256][KMAX + 1];
     __shared__ int li_[256][KMAX + 1];
     __shared__ float wd[4];
     __shared__ int wi[4];
     const int q = blockIdx.x, t = threadIdx.x;
+    if (count && count[q] <= room) return;          // uniform: the filter has dealt with this query's chunk
     const int r0 = root_off[q], nb = root_off[q + 1] - r0;
 
     float bd[KMAX];
@@ -241,6 +265,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ dis
             out_ids[(size_t)q * k + r] = mi == INT_MAX ? -1 : mi;
         }
     }
+    if (count && t == 0) count[q] = 0;
 }
 
 // ---------------------------------------------------------------- filtered ranks of listed answers
@@ -254,19 +279,6 @@ __device__ __forceinline__ int query_of_answer(const int32_t* __restrict__ ans_o
     return lo;
 }
 
-// thr[a] = min over the branch rows of a's query of dist[row, a - a0], a0 <= a < a0 + cnt
-__global__ __launch_bounds__(256) void answer_dist_kernel(const float* __restrict__ dist, int ld,
-                                                          const int32_t* __restrict__ root_off,
-                                                          const int32_t* __restrict__ ans_off, int n_queries, int a0,
-                                                          int cnt, float* __restrict__ thr) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cnt) return;
-    const int q = query_of_answer(ans_off, n_queries, a0 + i);
-    float v = INFINITY;
-    for (int r = root_off[q]; r < root_off[q + 1]; ++r) v = fminf(v, dist[(size_t)r * ld + i]);
-    thr[a0 + i] = v;
-}
-
 constexpr int CNT_SLAB = 8192;    // entities per workgroup of the counting pass
 constexpr int CNT_TILE = 256;     // answers whose counters a workgroup holds at once
 
@@ -278,12 +290,13 @@ __global__ __launch_bounds__(256) void count_less_kernel(const float* __restrict
                                                          const int32_t* __restrict__ root_off,
                                                          const int32_t* __restrict__ ans_off,
                                                          const float* __restrict__ thr, int n_ent,
-                                                         int32_t* __restrict__ count) {
+                                                         int32_t* __restrict__ count, const int32_t* __restrict__ listed,
+                                                         int room) {
     __shared__ float s_thr[CNT_TILE];
     __shared__ int32_t s_cnt[4][CNT_TILE];
     const int q = blockIdx.y;
     const int a_lo = ans_off[q], a_hi = ans_off[q + 1];
-    if (a_lo >= a_hi) return;                                         // uniform
+    if (a_lo >= a_hi || (listed && listed[q] <= room)) return;        // uniform
     const int r_lo = root_off[q], r_hi = root_off[q + 1];
     const int e_lo = blockIdx.x * CNT_SLAB, e_hi = min(n_ent, e_lo + CNT_SLAB);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -366,34 +379,38 @@ __global__ __launch_bounds__(256) void fill_zero_i32_kernel(int32_t* p, int n) {
 }  // namespace
 
 hipError_t launch_l1_tile(const float* act, const float* off, float alpha, const int32_t* row_ids, int n_rows,
-                          const float* Emat, const int32_t* ent_ids, int n_ent, int d, float* dist, int ld, hipStream_t s,
-                          const uint16_t* Emat16) {
+                          const float* Emat, int n_ent, int d, float* dist, int ld, hipStream_t s, const uint16_t* Emat16,
+                          const Overflowed* only) {
     if (n_rows <= 0 || n_ent <= 0) return hipSuccess;
     if ((d & 3) || (ld & 3) || (off && !(alpha >= 0.f && alpha <= 1.f))) return hipErrorInvalidValue;
-    dim3 grid((n_ent + TE - 1) / TE, (n_rows + TQ - 1) / TQ);
-    if (off)
-        hipLaunchKernelGGL((l1_tile_kernel<true>), grid, dim3(256), 0, s, act, off, alpha, row_ids, n_rows, Emat, Emat16,
-                           ent_ids, n_ent, d, dist, ld);
-    else
-        hipLaunchKernelGGL((l1_tile_kernel<false>), grid, dim3(256), 0, s, act, off, alpha, row_ids, n_rows, Emat, Emat16,
-                           ent_ids, n_ent, d, dist, ld);
-    return hipGetLastError();
-}
-
-hipError_t launch_answer_dist(const float* dist, int ld, const int32_t* root_off, const int32_t* ans_off, int n_queries,
-                              int a0, int cnt, float* thr, hipStream_t s) {
-    if (cnt <= 0) return hipSuccess;
-    hipLaunchKernelGGL(answer_dist_kernel, dim3((cnt + 255) / 256), dim3(256), 0, s, dist, ld, root_off, ans_off,
-                       n_queries, a0, cnt, thr);
+    // 128 x 128 tiles where they fill the chip's 256 compute units; smaller ones for few rows (a tile's time does
+    // not depend on how many of its rows exist) and for small tables
+    const int rpl = n_rows <= 32 ? 2 : (n_rows <= 64 || (long)((n_rows + 127) / 128) * ((n_ent + 127) / 128) < 512 ? 4 : 8);
+    const int epl = (long)((n_rows + 16 * rpl - 1) / (16 * rpl)) * ((n_ent + 127) / 128) < 512 ? 4 : 8;
+    int tiles_e = (n_ent + 16 * epl - 1) / (16 * epl);
+    if (only) tiles_e = std::min(tiles_e, 64);
+    const dim3 grid(tiles_e, (n_rows + 16 * rpl - 1) / (16 * rpl)), block(256);
+#define NGDB_L1(BOX, R, C)                                                                                             \
+    hipLaunchKernelGGL((l1_tile_kernel<BOX, R, C>), grid, block, 0, s, act, off, alpha, row_ids, n_rows, Emat, Emat16,   \
+                       n_ent, d, dist, ld, only ? only->row_q : nullptr, only ? (const int32_t*)only->count : nullptr,   \
+                       only ? only->room : 0, only ? only->any : nullptr)
+#define NGDB_L1_SIZES(BOX)                                                                  \
+    if (rpl == 8) { if (epl == 8) NGDB_L1(BOX, 8, 8); else NGDB_L1(BOX, 8, 4); }             \
+    else if (rpl == 4) { if (epl == 8) NGDB_L1(BOX, 4, 8); else NGDB_L1(BOX, 4, 4); }        \
+    else { if (epl == 8) NGDB_L1(BOX, 2, 8); else NGDB_L1(BOX, 2, 4); }
+    if (off) { NGDB_L1_SIZES(true) } else { NGDB_L1_SIZES(false) }
+#undef NGDB_L1_SIZES
+#undef NGDB_L1
     return hipGetLastError();
 }
 
 hipError_t launch_count_less(const float* dist, int ld, const int32_t* root_off, const int32_t* ans_off,
-                             const float* thr, int n_queries, int n_ent, int32_t* count, hipStream_t s) {
+                             const float* thr, int n_queries, int n_ent, int32_t* count, hipStream_t s,
+                             const Overflowed* only) {
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
     if (n_queries > 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(count_less_kernel, dim3((n_ent + CNT_SLAB - 1) / CNT_SLAB, n_queries), dim3(256), 0, s, dist, ld,
-                       root_off, ans_off, thr, n_ent, count);
+                       root_off, ans_off, thr, n_ent, count, only ? (const int32_t*)only->count : nullptr, only ? only->room : 0);
     return hipGetLastError();
 }
 
@@ -418,11 +435,12 @@ hipError_t launch_fill_zero_i32(int32_t* p, int n, hipStream_t s) {
 }
 
 hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off, int n_queries, int ent_base, int n_ent,
-                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s) {
+                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s,
+                             const Overflowed* only) {
     if (n_queries <= 0) return hipSuccess;
     if (k < 1 || k > KMAX) return hipErrorInvalidValue;
     hipLaunchKernelGGL(topk_kernel, dim3(n_queries), dim3(256), 0, s, dist, ld, root_off, ent_base, n_ent, k,
-                       first_chunk, out_dist, out_ids);
+                       first_chunk, out_dist, out_ids, only ? only->count : nullptr, only ? only->room : 0);
     return hipGetLastError();
 }
 

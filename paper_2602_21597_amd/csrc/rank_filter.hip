@@ -1,0 +1,967 @@
+// Ranking with a filter (Sec. 3.2: the answers are the entities nearest to a query's embedding).
+//
+// An L1 distance costs the vector ALU two operations per coordinate, and the all-entity passes are
+// bound by nothing else.  The hardware also sums absolute differences of packed unsigned integers --
+// four 8-bit or two 16-bit coordinates in one operation -- so the entity rows and the branch
+// embeddings are rounded to integers on one common grid, the integer sums are formed for every
+// pair, and only the pairs that the integer sum leaves undecided are computed in fp32.  What a
+// rounded row is off by is summed exactly per row, so an integer sum bounds the fp32 distance
+// from both sides and the results are those of the fp32 pass: the same distances, formed in the
+// same order of summation, and the same order of ids.
+//
+// Grid: coordinate c of a row becomes round((x - lo[c]) / step), clamped to the range of the type;
+// `step` is common to all coordinates (the sums need one unit), lo[c] and step come from a sample
+// of the table.  A coordinate outside the grid is clamped.  With e' = lo + step * q(e) the entity
+// side, |e - e'| summed over the row is the entity's error (clamped outliers included); the branch
+// side splits |y - e'| into the part inside the grid and the excess |y - clamp(y)|, which adds up
+// to a constant of the row (exact for every e' on the grid), and errs by |clamp(y) - y'|.  So
+//     | dist(y, e) - (excess_y + step * SAD) | <= err_y + err_e.
+// fp32 rounding is covered by relative slacks (SLACK on a row's sums, rounding_of(d) on a distance) and by
+// half a unit in the last place of every grid point.  A row that holds an infinity or a NaN gets an
+// error that leaves every one of its pairs undecided.
+//
+// Top-k: the first rows of the table are ranked in fp32; the k-th distance so far is a bound, and the
+// 8-bit sums of the next chunk leave some tens to hundreds of entities per query that can be below it, which
+// one workgroup per query computes and merges.  Chunks grow with what has been ranked.  1024 queries
+// (1171 branch rows) x 5 M entities x 400: distance tiles 182.6 ms and merges 32.6 became integer sums 17.4 (34 T
+// operations of 4 coordinates a second; the instruction alone reaches 36), rounding 2.1 and merges 2.2.
+// Filtered ranks: the 16-bit sums decide all but about 0.1 % of the (entity, answer) comparisons: 1024
+// queries x 63 000 entities with 8 answers each, tiles 2.78 ms (0.32 of them for the answers' own
+// distances, now computed pair by pair) and counting 0.24 became 0.46 and 0.44.
+// Lists have a fixed room per query; a query whose list overflows in a chunk takes the fp32
+// pass for that chunk (launched always, its workgroups leave at once where nothing overflowed).
+#include <climits>
+
+#include "common.h"
+
+namespace ngdb {
+namespace {
+
+constexpr float SLACK = 1e-5f;       // of a row's own sums (at most 16 terms a lane, then a tree: 2e-6)
+constexpr int UNBOUNDED = INT_MAX / 4;
+// relative rounding of an fp32 distance: d additions and d subtractions in sequence
+inline float rounding_of(int d) { return (float)(d + 16) * 6e-8f; }
+constexpr int SAMPLE_SLABS = 16;
+
+// ---------------------------------------------------------------- the grid
+// per coordinate the smallest and largest value of a slab of the sampled rows; grid (d/64, slabs)
+__global__ __launch_bounds__(256) void sample_range_kernel(const float* __restrict__ E, const uint16_t* __restrict__ E16,
+                                                           int64_t row_step, int n_rows, int d, float* __restrict__ part) {
+    __shared__ float slo[4][64], shi[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = min((int)blockIdx.x * 64 + lane, d - 1);
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll 8
+    for (int i = blockIdx.y * 4 + wave; i < n_rows; i += SAMPLE_SLABS * 4) {
+        const size_t at = (size_t)i * row_step * d + c;
+        const float x = E16 ? __uint_as_float((uint32_t)E16[at] << 16) : E[at];
+        lo = fminf(lo, x);
+        hi = fmaxf(hi, x);
+    }
+    slo[wave][lane] = lo;
+    shi[wave][lane] = hi;
+    __syncthreads();
+    if (wave == 0 && (int)blockIdx.x * 64 + lane < d) {
+#pragma unroll
+        for (int w = 1; w < 4; ++w) { lo = fminf(lo, slo[w][lane]); hi = fmaxf(hi, shi[w][lane]); }
+        part[((size_t)blockIdx.y * 2 + 0) * d + c] = lo;
+        part[((size_t)blockIdx.y * 2 + 1) * d + c] = hi;
+    }
+}
+
+// One workgroup, one coordinate per thread: lo[c], and grid[0] = step, grid[1] = 1/step.  The step spans
+// the widest coordinate, but at most three times the mean width: a few wide coordinates then clamp (and
+// err) rather than coarsen the grid of all others.  The pass's counters are cleared on the way.
+__global__ __launch_bounds__(1024) void make_grid_kernel(const float* __restrict__ part, int d, int levels,
+                                                         float* __restrict__ lo_out, float* __restrict__ grid,
+                                                         int32_t* __restrict__ counters, int n_counters) {
+    __shared__ float smax[16], ssum[16];
+    const int c = threadIdx.x, lane = c & 63, wave = c >> 6;
+    for (int i = c; i < n_counters; i += 1024) counters[i] = 0;
+    float lo = INFINITY, hi = -INFINITY;
+    if (c < d) {
+#pragma unroll
+        for (int s = 0; s < SAMPLE_SLABS; ++s) {
+            lo = fminf(lo, part[((size_t)s * 2 + 0) * d + c]);
+            hi = fmaxf(hi, part[((size_t)s * 2 + 1) * d + c]);
+        }
+    }
+    const float w = c < d ? hi - lo : 0.f;
+    float wmax = w;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) wmax = fmaxf(wmax, __shfl_xor(wmax, off, 64));
+    const float wsum = wave_sum(w);
+    if (lane == 0) {
+        smax[wave] = wmax;
+        ssum[wave] = wsum;
+    }
+    __syncthreads();
+    float all_max = 0.f, all_sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        all_max = fmaxf(all_max, smax[i]);
+        all_sum += ssum[i];
+    }
+    const float width = fminf(all_max, 3.f * all_sum / (float)d);
+    // (a table of equal rows has no width: any grid serves)
+    const float step = fmaxf(width, 1e-30f) / (float)(levels - 1);
+    if (c < d) lo_out[c] = 0.5f * (lo + hi) - 0.5f * step * (float)(levels - 1);   // centred on the sampled range
+    if (c == 0) {
+        grid[0] = step;
+        grid[1] = 1.f / step;
+    }
+}
+
+// ---------------------------------------------------------------- rows -> grid
+// Q[w * ld + i]: word w of row i, 32 / BITS consecutive coordinates each, words beyond the row zero (on
+// both sides of a sum: they add nothing).  A wavefront takes 16 rows of the workgroup's 64, one after
+// the other, a float4 per lane; the words pass through LDS so that they leave 64 rows at a time.
+// ENT: slack[i] = the row's error in steps, rounded up (UNBOUNDED where it is not finite).
+// !ENT (branch rows, ids): base[i] = excess - err and base[ld + i] = excess + err (for bounds from
+// below and from above), and row_q[i] = the query the row belongs to.
+template <int BITS, bool ENT, int RW>
+__global__ __launch_bounds__(256) void quantise_kernel(const float* __restrict__ X, const uint16_t* __restrict__ X16,
+                                                       const int32_t* __restrict__ ids, int n_rows, int d, int words,
+                                                       const float* __restrict__ lo, const float* __restrict__ grid,
+                                                       uint32_t* __restrict__ Q, int ld, int32_t* __restrict__ slack,
+                                                       float* __restrict__ base, const int32_t* __restrict__ root_off,
+                                                       int n_queries, int32_t* __restrict__ row_q) {
+    constexpr int WPQ = BITS == 8 ? 1 : 2;       // words of four coordinates
+    constexpr float TOP = BITS == 8 ? 255.f : 65535.f;
+    __shared__ uint32_t tile[64 * WPQ][4 * RW + 1];      // 64 float4 columns of 4 * RW rows
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = blockIdx.x * 4 * RW;
+    const float step = grid[0], inv = grid[1];
+    float err[RW], excess[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) err[r] = excess[r] = 0.f;
+    for (int q0 = 0; q0 * WPQ < words; q0 += 64) {
+        const int q4 = q0 + lane;
+        const bool inside = q4 * 4 < d;
+        const float4 l4 = *reinterpret_cast<const float4*>(lo + (inside ? q4 * 4 : 0));
+        const float l[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const int i = min(i0 + wave * RW + r, n_rows - 1);
+            const size_t at = (size_t)(ids ? ids[i] : i) * d + (inside ? q4 * 4 : 0);
+            const float4 v4 = X16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(X16 + at)) : *reinterpret_cast<const float4*>(X + at);
+            const float v[4] = {v4.x, v4.y, v4.z, v4.w};
+            uint32_t w[2] = {0u, 0u};
+            float er = 0.f, ex = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float t = (v[j] - l[j]) * inv;
+                const float qf = fminf(fmaxf(rintf(t), 0.f), TOP);       // (a NaN becomes 0; its error stays NaN)
+                const float on = fmaf(qf, step, l[j]);                     // the grid point
+                if (ENT) {
+                    er += fabsf(v[j] - on) + fabsf(on) * 6e-8f;
+                } else {
+                    const float cl = fminf(fmaxf(v[j], l[j]), fmaf(TOP, step, l[j]));
+                    ex += fabsf(v[j] - cl);
+                    er += fabsf(cl - on) + fabsf(on) * 6e-8f + 0.f * v[j];     // (not a number where v is infinite or none)
+                }
+                const uint32_t qi = (uint32_t)qf;
+                if (BITS == 8) w[0] |= qi << (8 * j);
+                else w[j >> 1] |= qi << (16 * (j & 1));
+            }
+            if (inside) { err[r] += er; excess[r] += ex; }
+#pragma unroll
+            for (int p = 0; p < WPQ; ++p) tile[lane * WPQ + p][wave * RW + r] = inside ? w[p] : 0u;
+        }
+        __syncthreads();
+        const int n_w = min(64 * WPQ, words - q0 * WPQ);
+        for (int x = threadIdx.x; x < n_w * 4 * RW; x += 256) {
+            const int w = x / (4 * RW), i = x % (4 * RW);
+            if (i0 + i < ld) Q[(size_t)(q0 * WPQ + w) * ld + i0 + i] = tile[w][i];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const float e = wave_sum_dpp(err[r]), x = ENT ? 0.f : wave_sum_dpp(excess[r]);
+        const int i = i0 + wave * RW + r;
+        if (lane == 0 && i < n_rows) {
+            if (ENT) {
+                const float s = e * (1.f + SLACK) * inv + 2.f;
+                slack[i] = s < 1e8f ? (int32_t)s : UNBOUNDED;
+            } else {
+                base[i] = x * (1.f - SLACK) - e * (1.f + SLACK);
+                base[ld + i] = x * (1.f + SLACK) + e * (1.f + SLACK);
+                int qlo = 0, qhi = n_queries;
+                while (qhi - qlo > 1) {
+                    const int mid = (qlo + qhi) >> 1;
+                    if (root_off[mid] <= i) qlo = mid; else qhi = mid;
+                }
+                row_q[i] = qlo;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------- integer sums of a tile
+template <int BITS>
+__device__ __forceinline__ uint32_t sad(uint32_t a, uint32_t b, uint32_t c) {
+    return BITS == 8 ? __builtin_amdgcn_sad_u8(a, b, c) : __builtin_amdgcn_sad_u16(a, b, c);
+}
+
+// Tile of 16*RPL branch rows x 128 entities, RPL x 8 pairs per lane: rows ty*RPL .., entities
+// tx*4 .. +3 and 64 + tx*4 .. +3 (so that the 16-byte LDS reads of neighbouring lanes are adjacent).
+// Both operands arrive word-major, SW words are staged at a time, the next ones on their way in
+// registers meanwhile.  acc starts at the caller's values.  A launch covers its rows with tiles of 128
+// and the remainder with the smallest tile of 32, 64 or 128 rows that holds it (1171 rows: 9 x 128 + 32
+// instead of 10 x 128).
+constexpr int SW = 8;
+constexpr int TILE_LDS = 2 * SW * (128 + 128);      // words
+template <int BITS, int RPL>
+__device__ __forceinline__ void sad_tile(const uint32_t* __restrict__ Yq, int ldy, int r0, const uint32_t* __restrict__ Eq,
+                                         int lde, int e0, int words, uint32_t (&acc)[RPL][8], uint32_t* lds) {
+    constexpr int TR = 16 * RPL;
+    uint32_t* Ys = lds;                    // [2][SW][TR]
+    uint32_t* Es = lds + 2 * SW * TR;      // [2][SW][128]
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    constexpr int YQ = SW * 4 * RPL;       // 16-byte units of the row side of a stage (<= 256)
+    const int ew = tid >> 5, ec = (tid & 31) * 4;
+    const int yw = tid / (4 * RPL), yc = (tid % (4 * RPL)) * 4;
+    const bool has_y = tid < YQ;
+    // (words is a multiple of 4 and the rows of both operands are padded to whole tiles)
+    uint4 ye = make_uint4(0, 0, 0, 0), ee = make_uint4(0, 0, 0, 0);
+    auto issue = [&](int w0) {
+        if (has_y) ye = *reinterpret_cast<const uint4*>(Yq + (size_t)min(w0 + yw, words - 1) * ldy + r0 + yc);
+        ee = *reinterpret_cast<const uint4*>(Eq + (size_t)min(w0 + ew, words - 1) * lde + e0 + ec);
+    };
+    auto stage = [&](int buf) {
+        if (has_y) *reinterpret_cast<uint4*>(Ys + (buf * SW + yw) * TR + yc) = ye;
+        *reinterpret_cast<uint4*>(Es + (buf * SW + ew) * 128 + ec) = ee;
+    };
+    issue(0);
+    stage(0);
+    __syncthreads();
+    const int ns = (words + SW - 1) / SW;
+    for (int s = 0; s < ns; ++s) {
+        const int buf = s & 1;
+        if (s + 1 < ns) issue((s + 1) * SW);
+        const int nw = min(SW, words - s * SW);          // 4 or 8
+        for (int h = 0; h < nw; h += 4) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t* yrow = Ys + (buf * SW + h + k) * TR + ty * RPL;
+                const uint32_t* erow = Es + (buf * SW + h + k) * 128 + tx * 4;
+                uint32_t y[RPL], e[8];
+#pragma unroll
+                for (int i = 0; i < RPL; i += (RPL < 4 ? 2 : 4)) {
+                    if (RPL >= 4) {
+                        const uint4 v = *reinterpret_cast<const uint4*>(yrow + i);
+                        y[i] = v.x; y[i + 1] = v.y; y[(i + 2) % RPL] = v.z; y[(i + 3) % RPL] = v.w;
+                    } else {
+                        const uint2 v = *reinterpret_cast<const uint2*>(yrow + i);
+                        y[i] = v.x; y[i + 1] = v.y;
+                    }
+                }
+                const uint4 a = *reinterpret_cast<const uint4*>(erow);
+                const uint4 b = *reinterpret_cast<const uint4*>(erow + 64);
+                e[0] = a.x; e[1] = a.y; e[2] = a.z; e[3] = a.w; e[4] = b.x; e[5] = b.y; e[6] = b.z; e[7] = b.w;
+#pragma unroll
+                for (int i = 0; i < RPL; ++i)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc[i][j] = sad<BITS>(y[i], e[j], acc[i][j]);
+            }
+        }
+        if (s + 1 < ns) stage(buf ^ 1);
+        __syncthreads();
+    }
+}
+// rows of the last tile row: 128, 64 or 32
+__device__ __forceinline__ int tail_rows(int n_rows, int r0) { return n_rows - r0 > 64 ? 128 : (n_rows - r0 > 32 ? 64 : 32); }
+
+struct NearArgs {
+    const uint32_t *Yq, *Eq;
+    const float *base, *grid, *best;
+    const int32_t *row_q, *slack;
+    uint32_t *found, *found_pair;
+    int ldy, lde, n_rows, n_ent, words, k;
+    float rounding;
+};
+// Pairs that qualify are few (a per cent in the first chunk, one in 10^5 later).  They leave a tile as
+// a list of its own, grouped by row, and one word per row that has any: start << 8 | number, at
+// [row][tile column] of an array that is zero elsewhere; an entry is the entity's place in the tile (7 bits)
+// below its sum less its error (from -2^20, clamped), i.e. its lower bound.  (Appending them to a list per query takes a
+// device-wide atomic each: 140 us for the 300 000 pairs of a first chunk whose sums take 50.)  A tile
+// with more than FOUND pairs marks its rows as crowded.
+constexpr int FOUND = 2048;
+constexpr uint32_t CROWDED = 0xFFFFFFFFu;
+constexpr int32_t SUM_BIAS = 1 << 20;
+struct NearLds {
+    uint32_t tile[TILE_LDS];
+    uint32_t pair[FOUND];
+    uint8_t row[FOUND];
+    int32_t n_row[128], at_row[128];
+    int32_t n;
+};
+template <int RPL>
+__device__ __forceinline__ void near_tile(const NearArgs& g, int r0, int e0, NearLds& L) {
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4, lane = threadIdx.x & 63;
+    uint32_t acc[RPL][8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int e = e0 + (j >> 2) * 64 + tx * 4 + (j & 3);
+        // the entity's error comes off the sum here; entities past the end never qualify
+        const uint32_t start = e < g.n_ent ? (uint32_t)-g.slack[e] : (uint32_t)(INT_MAX / 2);
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) acc[i][j] = start;
+    }
+    sad_tile<8, RPL>(g.Yq, g.ldy, r0, g.Eq, g.lde, e0, g.words, acc, L.tile);
+    const float inv = g.grid[1];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        const int rl = ty * RPL + i, r = r0 + rl;
+        int32_t most = INT_MIN;
+        if (r < g.n_rows) {
+            const float t = (g.best[(size_t)g.row_q[r] * g.k + g.k - 1] * (1.f + g.rounding) - g.base[r]) * inv + 4.f;
+            most = t < 5e8f ? (int32_t)fmaxf(t, -1e9f) : INT_MAX / 2 - 1;    // (no bound yet, or not a number: everything qualifies)
+        }
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) any |= (int32_t)acc[i][j] <= most;
+        if (__ballot(any) == 0ull) continue;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool ok = (int32_t)acc[i][j] <= most;
+            const unsigned long long m = __ballot(ok);
+            if (m == 0ull) continue;
+            int at = 0;
+            if (lane == __ffsll(m) - 1) at = atomicAdd(&L.n, __popcll(m));
+            at = __builtin_amdgcn_readlane(at, __ffsll(m) - 1) + __popcll(m & ((1ull << lane) - 1ull));
+            if (ok) {
+                atomicAdd(&L.n_row[rl], 1);
+                if (at < FOUND) {
+                    L.pair[at] = (uint32_t)(max((int32_t)acc[i][j], -SUM_BIAS) + SUM_BIAS) << 7 | (uint32_t)((j >> 2) * 64 + tx * 4 + (j & 3));
+                    L.row[at] = (uint8_t)rl;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int n = L.n;
+    if (n == 0) return;                              // uniform
+    // places of the rows' groups: rows 2 * lane and 2 * lane + 1 of the scan of the first wavefront
+    if (threadIdx.x < 64) {
+        const int32_t c0 = L.n_row[2 * lane], c1 = L.n_row[2 * lane + 1];
+        int32_t inc = c0 + c1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t v = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += v;
+        }
+        L.at_row[2 * lane] = inc - c0 - c1;
+        L.at_row[2 * lane + 1] = inc - c1;
+    }
+    __syncthreads();
+    const size_t n_tx = gridDim.x;
+    if (threadIdx.x < 128 && L.n_row[threadIdx.x] > 0)
+        g.found[(r0 + threadIdx.x) * n_tx + blockIdx.x] =
+            n > FOUND ? CROWDED : (uint32_t)L.at_row[threadIdx.x] << 8 | (uint32_t)L.n_row[threadIdx.x];
+    if (n > FOUND) return;
+    __syncthreads();
+    uint32_t* out = g.found_pair + (blockIdx.y * n_tx + blockIdx.x) * FOUND;
+    for (int x = threadIdx.x; x < n; x += 256) out[atomicAdd(&L.at_row[L.row[x]], 1)] = L.pair[x];
+}
+
+// Top-k: the pairs of the chunk whose distance may be at most the k-th distance of the row's query so far.
+__global__ __launch_bounds__(256) void near_tile_kernel(const NearArgs g) {
+    __shared__ __attribute__((aligned(16))) NearLds L;
+    if (threadIdx.x < 128) L.n_row[threadIdx.x] = 0;         // (barriers in the tile loop before their use)
+    if (threadIdx.x == 0) L.n = 0;
+    const int r0 = blockIdx.y * 128, e0 = blockIdx.x * 128;
+    const int rows = tail_rows(g.n_rows, r0);
+    if (rows == 128) near_tile<8>(g, r0, e0, L);
+    else if (rows == 64) near_tile<4>(g, r0, e0, L);
+    else near_tile<2>(g, r0, e0, L);
+}
+
+// Filtered ranks: the sums themselves, sums[r * ld + e] = SAD
+template <int RPL>
+__device__ __forceinline__ void sum_tile(const uint32_t* __restrict__ Yq, int ldy, int n_rows, const uint32_t* __restrict__ Eq,
+                                         int lde, int n_ent, int words, uint32_t* __restrict__ sums, int ld, int r0, int e0,
+                                         uint32_t* lds) {
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    uint32_t acc[RPL][8];
+#pragma unroll
+    for (int i = 0; i < RPL; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = 0u;
+    sad_tile<16, RPL>(Yq, ldy, r0, Eq, lde, e0, words, acc, lds);
+#pragma unroll
+    for (int i = 0; i < RPL; ++i) {
+        const int r = r0 + ty * RPL + i;
+        if (r >= n_rows) continue;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = e0 + h * 64 + tx * 4;
+            uint32_t* out = sums + (size_t)r * ld + e;
+            if (e + 3 < n_ent) {
+                *reinterpret_cast<uint4*>(out) = make_uint4(acc[i][4 * h], acc[i][4 * h + 1], acc[i][4 * h + 2], acc[i][4 * h + 3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (e + j < n_ent) out[j] = acc[i][4 * h + j];
+            }
+        }
+    }
+}
+__global__ __launch_bounds__(256) void sum_tile_kernel(const uint32_t* __restrict__ Yq, int ldy, int n_rows,
+                                                       const uint32_t* __restrict__ Eq, int lde, int n_ent, int words,
+                                                       uint32_t* __restrict__ sums, int ld) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[TILE_LDS];
+    const int r0 = blockIdx.y * 128, e0 = blockIdx.x * 128;
+    const int rows = tail_rows(n_rows, r0);
+    if (rows == 128) sum_tile<8>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, lds);
+    else if (rows == 64) sum_tile<4>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, lds);
+    else sum_tile<2>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, lds);
+}
+
+// ---------------------------------------------------------------- fp32 distances of a list
+// min over the branch rows r_lo .. r_hi-1 of the fp32 distance to entity row e, one lane per entity,
+// coordinates in ascending order: bit for bit what a distance tile holds for the pair.  The 64 rows of
+// a wavefront come in slabs of 16 coordinates, four lanes a row, through the wavefront's own LDS (a lane
+// that read its row itself would touch a cache line for every 16 bytes), PF slabs requested ahead: a list
+// is short and the time is the latency of its rows.  The branch row's coordinates of a slab sit in the
+// lanes and are broadcast from there.
+constexpr int SLAB_C = 16, SLAB_LD = 20, PF = 3;
+template <bool B16>
+__device__ __forceinline__ float exact_distance(const float* __restrict__ act, const int32_t* __restrict__ row_ids, int r_lo,
+                                                int r_hi, const float* __restrict__ E, const uint16_t* __restrict__ E16,
+                                                int32_t e, int d, float* slab) {
+    const int lane = threadIdx.x & 63, part = (lane & 3) * 4;
+    int64_t at[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at[i] = (int64_t)__shfl(e, (lane >> 2) + 16 * i, 64) * d;
+    float4 x[PF][4];
+    float y[PF];
+    float best = INFINITY;
+    for (int r = r_lo; r < r_hi; ++r) {
+        const float* yrow = act + (size_t)row_ids[r] * d;
+        auto issue = [&](int u, int c0) {
+            const int c = min(c0 + part, d - 4);
+            y[u] = yrow[min(c0 + (lane & 15), d - 1)];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                x[u][i] = B16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(E16 + at[i] + c)) : *reinterpret_cast<const float4*>(E + at[i] + c);
+        };
+        float acc = 0.f;
+#pragma unroll
+        for (int u = 0; u < PF; ++u) issue(u, u * SLAB_C);
+        for (int c1 = 0; c1 < d; c1 += PF * SLAB_C) {
+#pragma unroll
+            for (int u = 0; u < PF; ++u) {
+                const int c0 = c1 + u * SLAB_C;
+                if (c0 >= d) break;                  // uniform
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(slab + ((lane >> 2) + 16 * i) * SLAB_LD + part) = x[u][i];
+                const float yc = y[u];
+                __builtin_amdgcn_wave_barrier();
+                if (c0 + PF * SLAB_C < d) issue(u, c0 + PF * SLAB_C);
+#pragma unroll
+                for (int c = 0; c < SLAB_C; c += 4) {
+                    if (c0 + c >= d) break;          // uniform
+                    const float4 v = *reinterpret_cast<const float4*>(slab + lane * SLAB_LD + c);
+                    acc += fabsf(lane_value(yc, c) - v.x);
+                    acc += fabsf(lane_value(yc, c + 1) - v.y);
+                    acc += fabsf(lane_value(yc, c + 2) - v.z);
+                    acc += fabsf(lane_value(yc, c + 3) - v.w);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        best = r == r_lo ? acc : fminf(best, acc);
+    }
+    return best;
+}
+
+__device__ __forceinline__ bool before(float d, int i, float d2, int i2) { return d < d2 || (d == d2 && i < i2); }
+
+struct MergeArgs {
+    const float *act, *E, *base, *grid;
+    const uint16_t* E16;
+    const int32_t *row_ids, *root_off, *slack;
+    uint32_t* found;
+    const uint32_t* found_pair;
+    int32_t *count, *overflowed;
+    float* out_dist;
+    int32_t* out_ids;
+    int n_tx, ent_base, d, k, room, ldb;
+    float rounding;
+};
+// One workgroup per query: gathers what the tiles left for the query's rows (clearing their words for
+// the next chunk) and merges the distances into the running top-k.  In a first chunk a list holds
+// hundreds of entities against a bound that the chunk itself would improve: the upper bounds of the
+// listed ones give the k-th (a histogram between the smallest and the bound so far), and only what
+// can lie below that is computed, a tenth.  Nearly all of these turn out farther than the k-th so far;
+// the few that are not are collected and inserted by the first wavefront into the list its lanes
+// hold.  A query with more than ROOM entities, or a crowded tile, is marked (count > room,
+// *overflowed) for the fp32 pass of the chunk.
+constexpr int ROOM = 4096, MERGE_T = 128, BINS = 256;
+template <bool B16>
+__global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) {
+    __shared__ __attribute__((aligned(16))) float slab[MERGE_T / 64][64 * SLAB_LD];
+    __shared__ uint16_t list[ROOM];
+    __shared__ float lower[ROOM];
+    __shared__ int32_t hist[BINS];
+    __shared__ float sd[MERGE_T], best_hi[MERGE_T / 64];
+    __shared__ int32_t si[MERGE_T];
+    __shared__ int32_t n_list, n_near, n_new, crowded;
+    __shared__ float kth_d, bound;
+    __shared__ int32_t kth_i;
+    const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6, k = g.k;
+    if (t == 0) n_list = n_near = n_new = crowded = 0;
+    __syncthreads();
+    const int r_lo = g.root_off[q], r_hi = g.root_off[q + 1];
+    const float step = g.grid[0];
+    float hi_min = INFINITY;
+    for (int r = r_lo; r < r_hi; ++r) {
+        uint32_t* words = g.found + (size_t)r * g.n_tx;
+        const uint32_t* pairs = g.found_pair + (size_t)(r >> 7) * g.n_tx * FOUND;
+        const float b_lo = g.base[r];
+        for (int x = t; x < g.n_tx; x += MERGE_T) {
+            const uint32_t w = words[x];
+            if (w == 0u) continue;
+            words[x] = 0u;
+            if (w == CROWDED) {
+                crowded = 1;
+                continue;
+            }
+            const int n = w & 0xFF, from = w >> 8, at = atomicAdd(&n_list, n);
+            for (int i = 0; i < n && at + i < ROOM; ++i) {
+                const uint32_t p = pairs[(size_t)x * FOUND + from + i];
+                list[at + i] = (uint16_t)(x * 128 + (p & 127));
+                lower[at + i] = (float)((int32_t)(p >> 7) - SUM_BIAS - 4) * step + b_lo;
+            }
+        }
+    }
+    float my_d = INFINITY;
+    int32_t my_i = INT_MAX;
+    if (wave == 0 && lane < k) {
+        const int32_t id = g.out_ids[(size_t)q * k + lane];
+        if (id >= 0) {
+            my_d = g.out_dist[(size_t)q * k + lane];
+            my_i = id;
+        }
+        if (lane == k - 1) {
+            kth_d = my_d;
+            kth_i = my_i;
+        }
+    }
+    __syncthreads();
+    int n = n_list;
+    if (n > ROOM || crowded) {                       // uniform
+        if (t == 0) {
+            *g.overflowed = 1;
+            g.count[q] = g.room + 1;
+        }
+        return;
+    }
+    if (n == 0) return;
+    if (n > MERGE_T && kth_d < INFINITY) {
+        // upper bound of a listed entity: its lower one and twice both errors (the widest branch's)
+        float both = 0.f;
+        for (int r = r_lo; r < r_hi; ++r) both = fmaxf(both, g.base[g.ldb + r] - g.base[r]);
+        auto upper = [&](int x) {
+            const int32_t sl = g.slack[list[x]];
+            return sl == UNBOUNDED ? INFINITY : (lower[x] + both + (float)(2 * sl + 8) * step) * (1.f + g.rounding);
+        };
+        for (int x = t; x < n; x += MERGE_T) hi_min = fminf(hi_min, upper(x));
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) hi_min = fminf(hi_min, __shfl_xor(hi_min, off, 64));
+        if (lane == 0) best_hi[wave] = hi_min;
+        for (int b = t; b < BINS; b += MERGE_T) hist[b] = 0;
+        __syncthreads();
+        const float top = kth_d;
+        hi_min = best_hi[0];
+#pragma unroll
+        for (int w = 1; w < MERGE_T / 64; ++w) hi_min = fminf(hi_min, best_hi[w]);
+        const float scale = (float)BINS / (top - hi_min);        // (top <= hi_min: nothing falls into a bin)
+        for (int x = t; x < n; x += MERGE_T) {
+            const float b = (upper(x) - hi_min) * scale;
+            if (b >= 0.f && b < (float)BINS) atomicAdd(&hist[(int)b], 1);
+        }
+        __syncthreads();
+        if (wave == 0) {   // the first bin that completes k entities (an entity may be listed by every branch)
+            int32_t c[BINS / 64], sum = 0;
+#pragma unroll
+            for (int i = 0; i < BINS / 64; ++i) {
+                c[i] = hist[lane * (BINS / 64) + i];
+                sum += c[i];
+            }
+            int32_t inc = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int32_t v = __shfl_up(inc, off, 64);
+                if (lane >= off) inc += v;
+            }
+            const int want = k * (r_hi - r_lo);
+            const unsigned long long m = __ballot(inc >= want);
+            if (lane == (m ? __ffsll(m) - 1 : 0)) {
+                int32_t run = inc - sum;
+                int bin = BINS;
+#pragma unroll
+                for (int i = BINS / 64 - 1; i >= 0; --i) {
+                    int32_t upto = run;
+#pragma unroll
+                    for (int i2 = 0; i2 <= i; ++i2) upto += c[i2];
+                    if (upto >= want) bin = lane * (BINS / 64) + i;
+                }
+                // (one bin of room for the rounding of the bin number)
+                bound = m && bin < BINS - 2 ? fminf(top, hi_min + (float)(bin + 2) / scale) : top;
+            }
+        }
+        __syncthreads();
+        // in place: a slot is written by the round that reads it or a later one
+        const float most = bound * (1.f + g.rounding);
+        for (int base = 0; base < n; base += MERGE_T) {
+            const int x = base + t;
+            const bool keep = x < n && !(lower[x] > most);
+            const uint16_t e = x < n ? list[x] : 0;
+            __syncthreads();
+            const unsigned long long m = __ballot(keep);
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&n_near, __popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+            if (keep) list[at] = e;
+            __syncthreads();
+        }
+        n = n_near;
+    }
+    for (int base = 0; base < n; base += MERGE_T) {
+        if (base + wave * 64 < n) {                  // uniform in the wavefront
+            const bool live = base + t < n;
+            const int32_t e = live ? list[base + t] : 0;
+            const float dv = exact_distance<B16>(g.act, g.row_ids, r_lo, r_hi, g.E, g.E16, e, g.d, slab[wave]);
+            if (live && before(dv, g.ent_base + e, kth_d, kth_i)) {
+                const int at = atomicAdd(&n_new, 1);
+                sd[at] = dv;
+                si[at] = g.ent_base + e;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const int m = n_new;
+            for (int x = 0; x < m; ++x) {
+                const float dv = sd[x];
+                const int32_t id = si[x];
+                if (__ballot(my_i == id) != 0ull) continue;      // listed by another branch already
+                const bool stays = before(my_d, my_i, dv, id);
+                const float up_d = __shfl_up(my_d, 1, 64);
+                const int32_t up_i = __shfl_up(my_i, 1, 64);
+                const bool up_stays = lane == 0 || before(up_d, up_i, dv, id);
+                if (!stays) {
+                    my_d = up_stays ? dv : up_d;
+                    my_i = up_stays ? id : up_i;
+                }
+                if (lane >= k) {
+                    my_d = INFINITY;
+                    my_i = INT_MAX;
+                }
+            }
+            if (lane == k - 1) {
+                kth_d = my_d;
+                kth_i = my_i;
+            }
+            if (lane == 0) n_new = 0;
+        }
+        __syncthreads();
+    }
+    if (wave == 0 && lane < k) {
+        g.out_dist[(size_t)q * k + lane] = my_d;
+        g.out_ids[(size_t)q * k + lane] = my_i == INT_MAX ? -1 : my_i;
+    }
+}
+
+// ---------------------------------------------------------------- filtered ranks
+// thr[a] = fp32 distance of answer a to its query, one lane per answer, summed like a distance tile.  The
+// lanes of a wavefront may belong to different queries: the branch rows are read from memory.
+template <bool BOX>
+__global__ __launch_bounds__(64) void answer_distance_kernel(const float* __restrict__ act, const float* __restrict__ off, float alpha,
+                                                             const int32_t* __restrict__ row_ids, const int32_t* __restrict__ root_off,
+                                                             const int32_t* __restrict__ ans_off, int n_queries,
+                                                             const int32_t* __restrict__ ans, int a0, int cnt,
+                                                             const float* __restrict__ E, const uint16_t* __restrict__ E16, int d,
+                                                             float* __restrict__ thr) {
+    const int i = blockIdx.x * 64 + threadIdx.x, a = a0 + i;
+    if (i >= cnt) return;
+    int lo = 0, hi = n_queries;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (ans_off[mid] <= a) lo = mid; else hi = mid;
+    }
+    const size_t e = ans ? (size_t)ans[a] : (size_t)i;
+    const float shrink = 1.f - alpha;
+    float best = INFINITY;
+    for (int r = root_off[lo]; r < root_off[lo + 1]; ++r) {
+        const size_t yrow = (size_t)row_ids[r] * d;
+        float acc = 0.f;
+        auto add = [&](float y, float x, float o) {
+#pragma clang fp contract(off)
+            const float diff = fabsf(y - x);
+            acc += BOX ? fmaxf(alpha * diff, diff - shrink * o) : diff;
+        };
+#pragma unroll 4
+        for (int c = 0; c < d; c += 4) {
+            const float4 x = E16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(E16 + e * d + c)) : *reinterpret_cast<const float4*>(E + e * d + c);
+            const float4 y = *reinterpret_cast<const float4*>(act + yrow + c);
+            const float4 o = BOX ? *reinterpret_cast<const float4*>(off + yrow + c) : x;
+            add(y.x, x.x, o.x);
+            add(y.y, x.y, o.y);
+            add(y.z, x.z, o.z);
+            add(y.w, x.w, o.w);
+        }
+        best = fminf(best, acc);
+    }
+    thr[a] = best;
+}
+
+// Bounds of the distance of a (row, entity) pair from its sum, the entity's error in steps and the row's
+// constants; every caller gets the same bits.
+struct Bounds { float lo, hi; };
+__device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step, float b_lo, float b_hi, float rounding) {
+    const float lo = fmaf((float)((int32_t)sum - sl), step, b_lo), hi = fmaf((float)((int32_t)sum + sl), step, b_hi);
+    const bool none = sl == UNBOUNDED;
+    return {none ? -INFINITY : fmaf(-rounding, fabsf(lo), lo), none ? INFINITY : fmaf(rounding, fabsf(hi), hi)};
+}
+
+// closer[a] += entities that are certainly closer than answer a; an entity that lies between its bounds from
+// some answer of the query is not decided and goes to the query's list.  Grid (parts, queries): a workgroup
+// takes every gridDim.x-th slab of 2048 entities, 8 per lane, and keeps the counters of up to 256 answers in LDS
+// between slabs (a device-wide atomic per answer and slab would cost more than the comparisons).  A comparison is one
+// vector instruction for 64 entities; counting and collecting its lanes is the scalar unit's.
+constexpr int EPT = 8, SLAB = EPT * 256, ANS_LDS = 256;
+__global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restrict__ sums, int ld, const int32_t* __restrict__ slack,
+                                                         const float* __restrict__ base, int ldb, const float* __restrict__ grid,
+                                                         const int32_t* __restrict__ root_off, const int32_t* __restrict__ ans_off,
+                                                         const float* __restrict__ thr, int n_ent, float rounding,
+                                                         int32_t* __restrict__ closer, int32_t* __restrict__ list,
+                                                         int32_t* __restrict__ count, int room) {
+    __shared__ int32_t s_cnt[ANS_LDS];
+    __shared__ uint16_t s_open[SLAB];
+    __shared__ int32_t n_open, open_at;
+    const int q = blockIdx.y;
+    const int a_lo = ans_off[q], a_hi = ans_off[q + 1];
+    if (a_lo >= a_hi) return;                                         // uniform
+    const int r_lo = root_off[q], r_hi = root_off[q + 1];
+    const float step = grid[0];
+    const int lane = threadIdx.x & 63;
+    s_cnt[threadIdx.x] = 0;
+    for (int e_lo = blockIdx.x * SLAB; e_lo < n_ent; e_lo += gridDim.x * SLAB) {
+        const int e_hi = min(n_ent, e_lo + SLAB);
+        if (threadIdx.x == 0) n_open = 0;
+        __syncthreads();
+        float vlo[EPT], vhi[EPT];
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) vlo[j] = vhi[j] = INFINITY;
+        for (int r = r_lo; r < r_hi; ++r) {
+            const float b_lo = base[r], b_hi = base[ldb + r];
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) {
+                const int e = min(e_lo + j * 256 + (int)threadIdx.x, e_hi - 1);
+                const Bounds b = bounds_of(sums[(size_t)r * ld + e], slack[e], step, b_lo, b_hi, rounding);
+                vlo[j] = fminf(vlo[j], b.lo);
+                vhi[j] = fminf(vhi[j], b.hi);
+            }
+        }
+        unsigned long long open[EPT];
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) {
+            open[j] = 0ull;
+            if (e_lo + j * 256 + (int)threadIdx.x >= e_hi) vlo[j] = vhi[j] = INFINITY;    // entities past the end are closer to nothing
+        }
+        for (int a = a_lo; a < a_hi; ++a) {
+            const float t = thr[a];
+            int c = 0;
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) {
+                const unsigned long long sure = __ballot(vhi[j] < t);
+                c += __popcll(sure);
+                open[j] |= sure ^ __ballot(vlo[j] < t);
+            }
+            if (lane == 0 && c) {
+                if (a - a_lo < ANS_LDS) atomicAdd(&s_cnt[a - a_lo], c);
+                else atomicAdd(&closer[a], c);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) {
+            if (open[j] == 0ull) continue;
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&n_open, __popcll(open[j]));
+            at = __builtin_amdgcn_readfirstlane(at) + __popcll(open[j] & ((1ull << lane) - 1ull));
+            if (open[j] >> lane & 1ull) s_open[at] = (uint16_t)(j * 256 + threadIdx.x);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && n_open) open_at = atomicAdd(&count[q], n_open);
+        __syncthreads();
+        for (int x = threadIdx.x; x < n_open; x += 256)
+            if (open_at + x < room) list[(size_t)q * room + open_at + x] = e_lo + s_open[x];
+        __syncthreads();
+    }
+    __syncthreads();
+    const int a = a_lo + threadIdx.x;
+    if (a < a_hi && s_cnt[threadIdx.x]) atomicAdd(&closer[a], s_cnt[threadIdx.x]);
+}
+
+// One workgroup per query: the undecided entities of the chunk in fp32 (for the answers that their upper bound
+// has not counted already), and the chunk's counts added to the running ones.  A query whose list
+// overflowed drops the chunk's counts (the fp32 pass of the chunk counts for it) and keeps its list count
+// as the mark for that.
+template <bool B16>
+__global__ __launch_bounds__(256) void count_open_kernel(const float* __restrict__ act, const int32_t* __restrict__ row_ids,
+                                                         const int32_t* __restrict__ root_off, const int32_t* __restrict__ ans_off,
+                                                         const float* __restrict__ thr, const float* __restrict__ E,
+                                                         const uint16_t* __restrict__ E16, int d, const uint32_t* __restrict__ sums,
+                                                         int ld, const int32_t* __restrict__ slack, const float* __restrict__ base,
+                                                         int ldb, const float* __restrict__ grid, float rounding,
+                                                         const int32_t* __restrict__ list, int32_t* __restrict__ count, int room,
+                                                         int32_t* __restrict__ overflowed, int32_t* __restrict__ chunk_count,
+                                                         int32_t* __restrict__ total) {
+    __shared__ __attribute__((aligned(16))) float slab[4][64 * SLAB_LD];
+    __shared__ int32_t s_cnt[256];
+    const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int a_lo = ans_off[q], a_hi = ans_off[q + 1];
+    const int n = count[q];
+    if (a_lo >= a_hi) return;                       // uniform
+    if (n > room) {
+        for (int a = a_lo + t; a < a_hi; a += 256) chunk_count[a] = 0;
+        if (t == 0) *overflowed = 1;
+        return;
+    }
+    const int r_lo = root_off[q], r_hi = root_off[q + 1];
+    const float step = grid[0];
+    for (int a0 = a_lo; a0 < a_hi; a0 += 256) {      // (more than 256 answers: the open entities are computed again)
+        const int na = min(256, a_hi - a0);
+        s_cnt[t] = 0;
+        __syncthreads();
+        for (int at = wave * 64; at < n; at += 256) {
+            const bool live = at + lane < n;
+            const int32_t e = live ? list[(size_t)q * room + at + lane] : 0;
+            float vhi = INFINITY;
+            for (int r = r_lo; r < r_hi; ++r)
+                vhi = fminf(vhi, bounds_of(sums[(size_t)r * ld + e], slack[e], step, base[r], base[ldb + r], rounding).hi);
+            const float v = exact_distance<B16>(act, row_ids, r_lo, r_hi, E, E16, e, d, slab[wave]);
+            for (int a = 0; a < na; ++a) {
+                const float limit = thr[a0 + a];
+                const int c = __popcll(__ballot(live && v < limit && !(vhi < limit)));
+                if (lane == 0 && c) atomicAdd(&s_cnt[a], c);
+            }
+        }
+        __syncthreads();
+        if (t < na) {
+            total[a0 + t] += chunk_count[a0 + t] + s_cnt[t];
+            chunk_count[a0 + t] = 0;
+        }
+        __syncthreads();
+    }
+    if (t == 0) count[q] = 0;
+}
+
+}  // namespace
+
+size_t rank_found_bytes(int ldy, int lde) { return (size_t)(ldy / 128) * (lde / 128) * FOUND * sizeof(uint32_t); }
+
+int rank_filter_words(int d, int bits) { return ((d / 4) * (bits / 8) + 3) / 4 * 4; }
+
+hipError_t launch_rank_grid(const RankFilter& f, const float* E, const uint16_t* E16, int64_t row_step, int n_rows, hipStream_t s) {
+    if (n_rows <= 0 || (f.bits != 8 && f.bits != 16) || (f.d & 3) || f.d > 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sample_range_kernel, dim3((f.d + 63) / 64, SAMPLE_SLABS), dim3(256), 0, s, E, E16, row_step, n_rows, f.d, f.part);
+    hipLaunchKernelGGL(make_grid_kernel, dim3(1), dim3(1024), 0, s, (const float*)f.part, f.d, 1 << f.bits, f.lo, f.grid,
+                       f.count, f.n_counters);
+    return hipGetLastError();
+}
+
+hipError_t launch_rank_rows(const RankFilter& f, const float* act, const int32_t* row_ids, int n_rows, const int32_t* root_off,
+                            int n_queries, hipStream_t s) {
+    if (n_rows <= 0) return hipSuccess;
+    // (padding rows of the last tile are copies of the last row)
+    const dim3 grid((f.ldy + 7) / 8), block(256);
+    if (f.bits == 8)
+        hipLaunchKernelGGL((quantise_kernel<8, false, 2>), grid, block, 0, s, act, (const uint16_t*)nullptr, row_ids, n_rows, f.d, f.words,
+                           f.lo, f.grid, f.Yq, f.ldy, (int32_t*)nullptr, f.base, root_off, n_queries, f.row_q);
+    else
+        hipLaunchKernelGGL((quantise_kernel<16, false, 2>), grid, block, 0, s, act, (const uint16_t*)nullptr, row_ids, n_rows, f.d, f.words,
+                           f.lo, f.grid, f.Yq, f.ldy, (int32_t*)nullptr, f.base, root_off, n_queries, f.row_q);
+    return hipGetLastError();
+}
+
+hipError_t launch_rank_entities(const RankFilter& f, const float* E, const uint16_t* E16, int n_ent, hipStream_t s) {
+    if (n_ent <= 0) return hipSuccess;
+    const dim3 grid((n_ent + 127) / 128 * 2), block(256);
+    if (f.bits == 8)
+        hipLaunchKernelGGL((quantise_kernel<8, true, 16>), grid, block, 0, s, E, E16, (const int32_t*)nullptr, n_ent, f.d, f.words, f.lo,
+                           f.grid, f.Eq, f.lde, f.slack, (float*)nullptr, (const int32_t*)nullptr, 0, (int32_t*)nullptr);
+    else
+        hipLaunchKernelGGL((quantise_kernel<16, true, 16>), grid, block, 0, s, E, E16, (const int32_t*)nullptr, n_ent, f.d, f.words, f.lo,
+                           f.grid, f.Eq, f.lde, f.slack, (float*)nullptr, (const int32_t*)nullptr, 0, (int32_t*)nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const float* best, int k, hipStream_t s) {
+    if (n_rows <= 0 || n_ent <= 0) return hipSuccess;
+    const NearArgs g{f.Yq, f.Eq, f.base, f.grid, best, f.row_q, f.slack, f.found, f.found_pair,
+                     f.ldy, f.lde, n_rows, n_ent, f.words, k, rounding_of(f.d)};
+    hipLaunchKernelGGL(near_tile_kernel, dim3((n_ent + 127) / 128, (n_rows + 127) / 128), dim3(256), 0, s, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_near_merge(const RankFilter& f, int chunk, const float* act, const int32_t* row_ids, const int32_t* root_off,
+                             int n_queries, const float* E, const uint16_t* E16, int ent_base, int n_ent, int k, float* out_dist,
+                             int32_t* out_ids, hipStream_t s) {
+    if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
+    const MergeArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, f.found, f.found_pair, f.count,
+                      f.overflowed + chunk, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, rounding_of(f.d)};
+    if (E16) hipLaunchKernelGGL((near_merge_kernel<true>), dim3(n_queries), dim3(MERGE_T), 0, s, g);
+    else hipLaunchKernelGGL((near_merge_kernel<false>), dim3(n_queries), dim3(MERGE_T), 0, s, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_tile(const RankFilter& f, int n_rows, int n_ent, uint32_t* sums, int ld, hipStream_t s) {
+    if (n_rows <= 0 || n_ent <= 0) return hipSuccess;
+    hipLaunchKernelGGL(sum_tile_kernel, dim3((n_ent + 127) / 128, (n_rows + 127) / 128), dim3(256), 0, s, (const uint32_t*)f.Yq,
+                       f.ldy, n_rows, (const uint32_t*)f.Eq, f.lde, n_ent, f.words, sums, ld);
+    return hipGetLastError();
+}
+
+hipError_t launch_answer_distance(const float* act, const float* off, float alpha, const int32_t* row_ids, const int32_t* root_off,
+                                  const int32_t* ans_off, int n_queries, const int32_t* ans, int a0, int cnt, const float* E,
+                                  const uint16_t* E16, int d, float* thr, hipStream_t s) {
+    if (cnt <= 0) return hipSuccess;
+    const dim3 grid((cnt + 63) / 64), block(64);
+    if (off)
+        hipLaunchKernelGGL((answer_distance_kernel<true>), grid, block, 0, s, act, off, alpha, row_ids, root_off, ans_off, n_queries, ans,
+                           a0, cnt, E, E16, d, thr);
+    else
+        hipLaunchKernelGGL((answer_distance_kernel<false>), grid, block, 0, s, act, off, alpha, row_ids, root_off, ans_off, n_queries, ans,
+                           a0, cnt, E, E16, d, thr);
+    return hipGetLastError();
+}
+
+hipError_t launch_count_sure(const RankFilter& f, const uint32_t* sums, int ld, const int32_t* root_off, const int32_t* ans_off,
+                             const float* thr, int n_queries, int n_ent, int32_t* chunk_count, hipStream_t s) {
+    if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
+    if (n_queries > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(count_sure_kernel, dim3(std::min((n_ent + SLAB - 1) / SLAB, std::max(1, 4096 / n_queries)), n_queries), dim3(256), 0, s, sums, ld,
+                       (const int32_t*)f.slack, (const float*)f.base, f.ldy, (const float*)f.grid, root_off, ans_off, thr, n_ent,
+                       rounding_of(f.d), chunk_count, f.list, f.count, f.room);
+    return hipGetLastError();
+}
+
+hipError_t launch_count_open(const RankFilter& f, int chunk, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
+                             const int32_t* ans_off, const float* thr, int n_queries, const float* E, const uint16_t* E16,
+                             int32_t* chunk_count, int32_t* total, hipStream_t s) {
+    if (n_queries <= 0) return hipSuccess;
+#define NGDB_OPEN(B16)                                                                                                       \
+    hipLaunchKernelGGL((count_open_kernel<B16>), dim3(n_queries), dim3(256), 0, s, act, row_ids, root_off, ans_off, thr, E, E16, f.d, \
+                       sums, ld, (const int32_t*)f.slack, (const float*)f.base, f.ldy, (const float*)f.grid, rounding_of(f.d),   \
+                       (const int32_t*)f.list, f.count, f.room, f.overflowed + chunk, chunk_count, total)
+    if (E16) NGDB_OPEN(true);
+    else NGDB_OPEN(false);
+#undef NGDB_OPEN
+    return hipGetLastError();
+}
+
+}  // namespace ngdb

@@ -1,0 +1,75 @@
+"""All-entity ranking through the filter on integer sums (tables above 4096 rows, vector family): top-k and
+filtered ranks against the oracle where a tile, a chunk, a list or the grid of the integers can go wrong."""
+import numpy as np
+import pytest
+
+from . import parity as par
+
+pytestmark = pytest.mark.gpu
+
+
+def _first_rows_far(P):
+    P["E"][:4096] *= 6.0          # the sample's bound lets every later entity through: lists overflow
+
+
+def _one_cluster(P):
+    P["E"][64:] = P["E"][64]      # equal distances everywhere: crowded tiles, ties to the lower id
+
+
+def _outliers(P):
+    P["E"][:, 3] *= 200.0         # a coordinate far wider than the grid, and a few wide rows
+    P["E"][1000:1010] *= 50.0
+
+
+def _shifted(P):
+    P["E"] += 3.0                 # large against its spread: the grid's own rounding counts
+
+
+# N just above the limit, one more tile, the ragged end of a second chunk; d of one word, of a part of a
+# stage and of several; branch rows that need tiles of 32, 64 and 128
+@pytest.mark.parametrize("N,d,h,B,edit,kw", [
+    (4097, 4, 16, 3, None, {}),
+    (4224, 36, 32, 27, None, {}),
+    (9001, 100, 72, 56, None, {}),
+    (70001, 20, 24, 40, None, {}),
+    (5000, 1024, 16, 6, None, {}),
+    (6001, 48, 32, 130, None, dict(score_bf16=True)),
+    (5003, 64, 48, 20, None, dict(d_sem=128)),
+    (20000, 32, 32, 24, _first_rows_far, {}),
+    (9000, 32, 32, 24, _one_cluster, {}),
+    (9000, 40, 32, 24, _outliers, {}),
+    (9000, 40, 32, 24, _shifted, {}),
+])
+def test_filtered_passes_match_the_oracle(N, d, h, B, edit, kw):
+    par.say("rank filter: N=%d d=%d B=%d %s %s" % (N, d, B, edit.__name__ if edit else "", kw))
+    case = par.Case(N, 12, d, h, B, 2, 8.0, seed=300 + d, T=2 * N, params_edit=edit, **kw)
+    for k in (1, 10, 16):
+        par.check_topk(case, k, 6)
+    if edit is not _one_cluster:  # (no rank is decided between thousands of equal rows)
+        par.check_filtered_ranks(case, 5)
+
+
+def test_filtered_ranks_with_many_answers_of_one_query():
+    """Hundreds of answers of one query beside a handful of the others."""
+    import torch
+    from oracle import rank as orank
+    case = par.Case(6000, 12, 32, 32, 40, 2, 8.0, seed=77, T=12000)
+    M = case.model()
+    rng = np.random.default_rng(3)
+    lists = [rng.choice(case.N, 700 if q == 5 else 2, replace=False) for q in range(case.B)]
+    off = np.concatenate([[0], np.cumsum([len(l) for l in lists])]).astype(np.int32)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.int32)).cuda()
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    ranks = eng.rank_answers(plan, dev(off), dev(np.concatenate(lists)))[0].cpu().numpy()
+    for q in (0, 5, 39):
+        want, d_ref = orank.filtered_ranks(case.qb, q, lists[q], M, case.distances_all)
+        full = case.distances_all(case.qb, q, M)
+        other = np.ones(case.N, bool)
+        other[lists[q]] = False
+        d_other = np.sort(full[other])
+        lo = 1 + np.searchsorted(d_other, d_ref * (1 - 1e-5), side="left")
+        hi = 1 + np.searchsorted(d_other, d_ref * (1 + 1e-5), side="left")
+        got = ranks[off[q]:off[q + 1]]
+        assert np.all((lo <= got) & (got <= hi)), q
+    plan.free()
