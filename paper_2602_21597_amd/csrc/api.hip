@@ -53,6 +53,8 @@ struct ngdb_plan_s {
     ngdb_ctx_t* owner = nullptr;
     PlanBlob blob;
     int32_t* d_blob = nullptr;
+    size_t blob_bytes = 0;
+    mutable bool uploaded = false;   // else the first call that uses the plan copies it on its own stream
     // device views into the blob
     const int32_t *d_in_ref = nullptr, *d_in_gslot = nullptr, *d_rel = nullptr, *d_root_off = nullptr,
                   *d_root_slot = nullptr, *d_pos = nullptr, *d_ekeys_head = nullptr, *d_r_uniq = nullptr,
@@ -237,7 +239,7 @@ int gslot_of(int t) { return t == T_PROJ ? 0 : (t == T_NEG ? 4 : 8); }
 struct FwdBytes;
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim);
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
-
+int upload_plan(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s);
 
 // bytes of the split weights: per type two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
 size_t weight_pieces_bytes(const ngdb_ctx_t* c) {
@@ -285,6 +287,7 @@ int make_weight_pieces(ngdb_ctx_t* c, hipStream_t s) {
     if (c->cfg.family != NGDB_FAMILY_VEC || c->w_pieces.cap < weight_pieces_bytes(c) || !c->w_pieces.p) return NGDB_OK;
     const int d = c->cfg.d, h = c->cfg.h;
     if ((d & 3) || (h & 3)) return NGDB_OK;   // the split reads rows as float4
+    if (d < 128 && h < 128) return NGDB_OK;   // no contraction of these widths takes the split route
     uint16_t* at = ptr<uint16_t>(c->w_pieces);
     PieceJobs J{};
     for (int t = 0; t < 3; ++t) {
@@ -879,6 +882,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         return fail(c, NGDB_ERR_ARG, "batch beyond the maxima declared at ngdb_create (b_max_queries, k_max)");
     c->have_grads = false;
     int rc = size_workspace(c, pl, K, !apply);
+    if (rc == NGDB_OK) rc = upload_plan(c, pl, stream);
     if (rc != NGDB_OK) return rc;
 
     // 1. entity gradient index (depends only on the plan and the negatives)
@@ -1064,6 +1068,20 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     gv.pair_score = ptr<float>(c->score);
     gv.loss_terms = ptr<float>(c->loss_terms);
     c->have_grads = true;
+    return NGDB_OK;
+}
+
+// A plan of ordinary size reaches the device with the first call that uses it: a small kernel on that call's
+// stream reads the staging buffer (120 KB: 5 us), which needs neither a wait on the host (10 us) nor an
+// event between streams (9 us of host time).  Large ones are copied when they are planned.
+constexpr size_t PLAN_INLINE_BYTES = 256 << 10;
+int upload_plan(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
+    if (pl->uploaded) return NGDB_OK;
+    HIPCHK(c, launch_copy(pl->blob.dev, pl->blob.pinned, pl->blob_bytes, s));
+    // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIPCHK(c, hipStreamIsCapturing(s, &st));
+    if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
     return NGDB_OK;
 }
 
@@ -1478,55 +1496,79 @@ int ngdb_plan(ngdb_ctx_t* c, const ngdb_query_batch* qb, ngdb_plan_t** out) {
         }
     }
 
-    // one upload: every device-side array, each padded to 16 bytes
-    std::vector<int32_t> blob;
-    auto put = [&](const std::vector<int32_t>& v) {
-        const size_t off = blob.size();
-        blob.insert(blob.end(), v.begin(), v.end());
-        while (blob.size() & 3) blob.push_back(0);
-        if (v.empty()) blob.resize(blob.size() + 4, 0);
+    // one upload: every device-side array, each padded to 16 bytes (at least 16)
+    size_t blob_size = 0;
+    auto place = [&](size_t n) {
+        const size_t off = blob_size;
+        blob_size += std::max<size_t>((n + 3) & ~size_t(3), 4);
         return off;
     };
-    std::vector<int32_t> r_rec(hp.r_src.size());     // relation contributions are gradient rows
-    for (size_t i = 0; i < r_rec.size(); ++i) r_rec[i] = -1 - hp.r_src[i];
-    std::vector<int32_t> ekeys = hp.anchor_ent;
-    ekeys.insert(ekeys.end(), hp.pos.begin(), hp.pos.end());
-    const size_t o_ref = put(hp.in_ref), o_gs = put(hp.in_gslot), o_rel = put(hp.rel), o_ro = put(hp.root_off),
-                 o_rs = put(hp.root_slot), o_pos = put(hp.pos), o_ek = put(ekeys), o_ru = put(hp.r_uniq),
-                 o_rso = put(hp.r_seg_off), o_rsrc = put(hp.r_src), o_rrec = put(r_rec),
-                 o_nru = put(std::vector<int32_t>{(int32_t)hp.r_uniq.size()});
-    std::vector<int32_t> f_in_ref(hp.in_ref.size()), f_root(hp.root_slot.size());
-    for (size_t i = 0; i < f_in_ref.size(); ++i) f_in_ref[i] = hp.in_ref[i] >= 0 ? hp.f_row[hp.in_ref[i]] : hp.in_ref[i];
-    for (size_t i = 0; i < f_root.size(); ++i) f_root[i] = hp.f_row[hp.root_slot[i]];
-    const size_t o_fref = put(f_in_ref), o_frow = put(hp.f_row), o_froot = put(f_root);
-    // a recycled blob (its last reader has finished) or a new one
+    const size_t n_ekeys = hp.anchor_ent.size() + hp.pos.size();
+    const size_t o_ref = place(hp.in_ref.size()), o_gs = place(hp.in_gslot.size()), o_rel = place(hp.rel.size()),
+                 o_ro = place(hp.root_off.size()), o_rs = place(hp.root_slot.size()), o_pos = place(hp.pos.size()),
+                 o_ek = place(n_ekeys), o_ru = place(hp.r_uniq.size()), o_rso = place(hp.r_seg_off.size()),
+                 o_rsrc = place(hp.r_src.size()), o_rrec = place(hp.r_src.size()), o_nru = place(1),
+                 o_fref = place(hp.in_ref.size()), o_frow = place(hp.f_row.size()), o_froot = place(hp.root_slot.size());
+    // A recycled buffer whose last reader has finished; else a new one, as long as the context has few; else the
+    // one that has been waiting longest.  (With a single buffer planning would wait for the step before.)
     PlanBlob pb;
+    bool busy = false;
     {
         std::lock_guard<std::mutex> lk(c->mu);
-        for (size_t i = 0; i < c->blob_pool.size(); ++i)
-            if (c->blob_pool[i].cap >= blob.size()) {
-                pb = c->blob_pool[i];
-                c->blob_pool.erase(c->blob_pool.begin() + i);
-                break;
-            }
+        size_t fits = c->blob_pool.size(), pick = fits;
+        for (size_t i = 0; i < c->blob_pool.size() && pick == c->blob_pool.size(); ++i) {
+            if (c->blob_pool[i].cap < blob_size) continue;
+            if (fits == c->blob_pool.size()) fits = i;
+            if (hipEventQuery(c->blob_pool[i].last_use) == hipSuccess) pick = i;
+        }
+        const bool enough = c->presized || c->blob_pool.size() + c->live_plans.size() >= 4;
+        if (pick == c->blob_pool.size() && fits < pick && enough) {
+            pick = fits;
+            busy = true;
+        }
+        if (pick < c->blob_pool.size()) {
+            pb = c->blob_pool[pick];
+            c->blob_pool.erase(c->blob_pool.begin() + pick);
+        } else {
+            // one of those that are too small makes room once there are several
+            for (size_t i = 0; enough && !c->presized && i < c->blob_pool.size(); ++i)
+                if (c->blob_pool[i].cap < blob_size) {
+                    PlanBlob& old = c->blob_pool[i];
+                    (void)hipEventSynchronize(old.last_use);
+                    (void)hipFree(old.dev);
+                    (void)hipHostFree(old.pinned);
+                    (void)hipEventDestroy(old.last_use);
+                    c->blob_pool.erase(c->blob_pool.begin() + i);
+                    break;
+                }
+            if (!new_blob(c, blob_size + blob_size / 2 + 1024, &pb)) pb = PlanBlob{};
+        }
     }
     if (!pb.dev) {
-        bool ok;
-        {
-            std::lock_guard<std::mutex> lk(c->mu);     // (the allocation counter)
-            ok = new_blob(c, blob.size() + blob.size() / 2 + 1024, &pb);
-        }
-        if (!ok) {
-            delete pl;
-            return fail(c, NGDB_ERR_OOM, "allocation for the plan failed");
-        }
-    } else if (hipEventSynchronize(pb.last_use) != hipSuccess) {
+        delete pl;
+        return fail(c, NGDB_ERR_OOM, "allocation for the plan failed");
+    }
+    if (busy && hipEventSynchronize(pb.last_use) != hipSuccess) {
         delete pl;
         return fail(c, NGDB_ERR_HIP, "waiting for a recycled plan buffer failed");
     }
-    std::memcpy(pb.pinned, blob.data(), blob.size() * 4);
-    if (hipMemcpyAsync(pb.dev, pb.pinned, blob.size() * 4, hipMemcpyHostToDevice, c->upload) != hipSuccess ||
-        hipStreamSynchronize(c->upload) != hipSuccess) {
+    {   // straight into the staging buffer
+        int32_t* at = pb.pinned;
+        auto put = [&](size_t off, const std::vector<int32_t>& v) {
+            if (!v.empty()) std::memcpy(at + off, v.data(), v.size() * sizeof(int32_t));
+        };
+        put(o_ref, hp.in_ref); put(o_gs, hp.in_gslot); put(o_rel, hp.rel); put(o_ro, hp.root_off); put(o_rs, hp.root_slot);
+        put(o_pos, hp.pos); put(o_ek, hp.anchor_ent); put(o_ek + hp.anchor_ent.size(), hp.pos); put(o_ru, hp.r_uniq);
+        put(o_rso, hp.r_seg_off); put(o_rsrc, hp.r_src); put(o_frow, hp.f_row);
+        for (size_t i = 0; i < hp.r_src.size(); ++i) at[o_rrec + i] = -1 - hp.r_src[i];   // relation contributions are gradient rows
+        at[o_nru] = (int32_t)hp.r_uniq.size();
+        for (size_t i = 0; i < hp.in_ref.size(); ++i) at[o_fref + i] = hp.in_ref[i] >= 0 ? hp.f_row[hp.in_ref[i]] : hp.in_ref[i];
+        for (size_t i = 0; i < hp.root_slot.size(); ++i) at[o_froot + i] = hp.f_row[hp.root_slot[i]];
+    }
+    pl->blob_bytes = blob_size * 4;
+    if (pl->blob_bytes > PLAN_INLINE_BYTES &&
+        (hipMemcpyAsync(pb.dev, pb.pinned, pl->blob_bytes, hipMemcpyHostToDevice, c->upload) != hipSuccess ||
+         hipStreamSynchronize(c->upload) != hipSuccess)) {
         {
             std::lock_guard<std::mutex> lk(c->mu);
             c->blob_pool.push_back(pb);
@@ -1534,6 +1576,7 @@ int ngdb_plan(ngdb_ctx_t* c, const ngdb_query_batch* qb, ngdb_plan_t** out) {
         delete pl;
         return fail(c, NGDB_ERR_HIP, "plan upload failed");
     }
+    pl->uploaded = pl->blob_bytes > PLAN_INLINE_BYTES;
     pl->owner = c;
     pl->blob = pb;
     {
@@ -1622,6 +1665,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     if (c->presized && d_cand && C > c->cfg.k_max)
         return fail(c, NGDB_ERR_ARG, "more candidates per query than the k_max declared at ngdb_create");
     int rc = reclaim ? size_forward_only(c, pl, n_tail) : size_workspace(c, pl, d_cand ? C : 0, false);
+    if (rc == NGDB_OK) rc = upload_plan(c, pl, s);
     if (rc != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, d_cand};
@@ -1701,7 +1745,8 @@ int ngdb_score_noalloc(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ca
     const uint32_t timing = c->timing_mask;     // event brackets would create events: off for this call
     c->timing_mask = 0;
     const EntRows er{c->prm.E.p, pl->d_f_in_ref, pl->d_pos, d_cand};
-    int rc = enqueue_forward(c, pl, er, s, w);
+    int rc = upload_plan(c, pl, s);
+    if (rc == NGDB_OK) rc = enqueue_forward(c, pl, er, s, w);
     if (rc == NGDB_OK) {
         ScoreArgs sa{};
         sa.act = w.act; sa.E = er.rows; sa.root_off = pl->d_root_off; sa.root_slot = pl->d_f_root;
@@ -1732,6 +1777,7 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     c->have_grads = false;
     const bool reclaim = c->cfg.family == NGDB_FAMILY_VEC;     // as in ngdb_score
     int rc = reclaim ? size_forward_only(c, pl, 0) : size_workspace(c, pl, 0, false);
+    if (rc == NGDB_OK) rc = upload_plan(c, pl, s);
     if (rc != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, nullptr};

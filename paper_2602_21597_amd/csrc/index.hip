@@ -5,6 +5,12 @@
 // touched row, in a fixed order.  Every pass is three kernels (per-tile digit
 // histogram, exclusive scan of the digit-major histogram, stable scatter); no
 // kernel contains a data-dependent wait.
+//
+// The build runs beside the forward pass and is bound by its launches, not by its bytes, until there are
+// millions of keys.  Up to SMALL_KEYS keys one workgroup sorts everything in LDS (700 keys of the
+// smallest workload: 14 launches and 32 us became one of 9 us); up to MID_TILES tiles the histogram is
+// scanned by one launch instead of three, each workgroup adding up what lies before its digit (at
+// 66 000 keys 8 launches instead of 14); beyond that this would read the histogram too often.
 #include "common.h"
 
 namespace ngdb {
@@ -19,26 +25,30 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
-// keys[i] = i < n_head ? head[i] : tail[i - n_head]; vals[i] = i
-__global__ __launch_bounds__(256) void assemble_kernel(const int32_t* __restrict__ head, int n_head,
-                                                       const int32_t* __restrict__ tail, int64_t n,
-                                                       int32_t* __restrict__ keys, int32_t* __restrict__ vals) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        keys[i] = i < n_head ? head[i] : tail[i - n_head];
-        vals[i] = (int32_t)i;
+// The keys of a pass: the sorted ones of the pass before, or (FIRST) head and tail one after the other, the
+// value then being the position.
+template <bool FIRST>
+struct KeySource {
+    const int32_t *keys, *vals;       // FIRST: head, tail
+    int n_head;
+    __device__ __forceinline__ int32_t key(int64_t i) const {
+        if (FIRST) return i < n_head ? keys[i] : vals[i - n_head];
+        return keys[i];
     }
-}
+    __device__ __forceinline__ int32_t val(int64_t i) const { return FIRST ? (int32_t)i : vals[i]; }
+};
 
 // hist[digit * n_tiles + tile] = number of keys of the tile with that digit
-__global__ __launch_bounds__(SORT_THREADS) void hist_kernel(const int32_t* __restrict__ keys, int64_t n, int shift,
-                                                            int n_tiles, int32_t* __restrict__ hist) {
+template <bool FIRST>
+__global__ __launch_bounds__(SORT_THREADS) void hist_kernel(const KeySource<FIRST> src, int64_t n, int shift, int n_tiles,
+                                                            int32_t* __restrict__ hist) {
     __shared__ int32_t h[RADIX];
     h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
     for (int r = 0; r < SORT_ITEMS; ++r) {
         const int64_t i = base + (int64_t)r * SORT_THREADS + threadIdx.x;
-        if (i < n) atomicAdd(&h[(keys[i] >> shift) & (RADIX - 1)], 1);
+        if (i < n) atomicAdd(&h[(src.key(i) >> shift) & (RADIX - 1)], 1);
     }
     __syncthreads();
     hist[(size_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
@@ -131,13 +141,64 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_apply_kernel(const int32_t*
     if (HEADS && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) seg_off[*total] = (int32_t)n;
 }
 
+// Exclusive scan of a short digit-major histogram in one launch: workgroup `digit` adds up the rows before its own
+// and scans its own (n_tiles <= MID_TILES <= SCAN_THREADS), out of place.
+constexpr int MID_TILES = 256;
+__global__ __launch_bounds__(SCAN_THREADS) void scan_rows_kernel(const int32_t* __restrict__ hist, int n_tiles,
+                                                                 int32_t* __restrict__ offs) {
+    const int digit = blockIdx.x, t = threadIdx.x;
+    int32_t before = 0;
+    for (int i = t; i < digit * n_tiles; i += SCAN_THREADS) before += hist[i];
+    int32_t base, row;
+    block_exclusive_scan(before, &base);
+    const int32_t v = t < n_tiles ? hist[(size_t)digit * n_tiles + t] : 0;
+    const int32_t ex = block_exclusive_scan(v, &row);
+    if (t < n_tiles) offs[(size_t)digit * n_tiles + t] = base + ex;
+}
+
+// Segment heads of a short sorted array in one launch after the tile sums: like scan_apply_kernel<true>, each workgroup
+// adding up the sums of the tiles before it (at most MID_TILES of them).
+__global__ __launch_bounds__(SCAN_THREADS) void heads_kernel(const int32_t* __restrict__ keys, int64_t n,
+                                                             const int32_t* __restrict__ sums, int32_t* __restrict__ uniq,
+                                                             int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) {
+    int32_t base, all, tot;
+    block_exclusive_scan((int)threadIdx.x < (int)blockIdx.x ? sums[threadIdx.x] : 0, &base);
+    const int64_t first = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
+    int32_t v[SCAN_ITEMS], s = 0;
+    for (int k = 0; k < SCAN_ITEMS; ++k) {
+        v[k] = first + k < n ? scan_input<true>(keys, first + k) : 0;
+        s += v[k];
+    }
+    int32_t run = base + block_exclusive_scan(s, &tot);
+    for (int k = 0; k < SCAN_ITEMS; ++k)
+        if (v[k]) {
+            uniq[run] = keys[first + k];
+            seg_off[run++] = (int32_t)(first + k);
+        }
+    all = base + tot;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        seg_off[all] = (int32_t)n;
+        *n_uniq = all;
+    }
+}
+
+// Lanes of the wavefront that hold a valid key with the lane's digit
+__device__ __forceinline__ unsigned long long digit_peers(bool valid, int digit) {
+    unsigned long long peers = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < RADIX_BITS; ++b) {
+        const unsigned long long bal = __ballot((digit >> b) & 1);
+        peers &= ((digit >> b) & 1) ? bal : ~bal;
+    }
+    return peers;
+}
+
 // Stable scatter of one radix pass.  The tile is walked in rounds of 256
 // consecutive keys (thread t takes key round*256 + t), so the order inside the
 // tile is (round, wavefront, lane); the rank of a key among equal digits is
 // running count of earlier rounds + counts of lower wavefronts + lower lanes.
-__global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const int32_t* __restrict__ keys_in,
-                                                               const int32_t* __restrict__ vals_in, int64_t n,
-                                                               int shift, int n_tiles,
+template <bool FIRST>
+__global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const KeySource<FIRST> src, int64_t n, int shift, int n_tiles,
                                                                const int32_t* __restrict__ offs,
                                                                int32_t* __restrict__ keys_out,
                                                                int32_t* __restrict__ vals_out) {
@@ -148,22 +209,19 @@ __global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const int32_t* __
     for (int w = 0; w < SORT_THREADS / 64; ++w) wcnt[w][threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
+    int32_t key[SORT_ITEMS], val[SORT_ITEMS];
+#pragma unroll
+    for (int r = 0; r < SORT_ITEMS; ++r) {
+        const int64_t i = base + (int64_t)r * SORT_THREADS + threadIdx.x;
+        key[r] = i < n ? src.key(i) : 0;
+        val[r] = i < n ? src.val(i) : 0;
+    }
+#pragma unroll
     for (int r = 0; r < SORT_ITEMS; ++r) {
         const int64_t i = base + (int64_t)r * SORT_THREADS + threadIdx.x;
         const bool valid = i < n;
-        int32_t key = 0, val = 0;
-        if (valid) {
-            key = keys_in[i];
-            val = vals_in[i];
-        }
-        const int digit = (key >> shift) & (RADIX - 1);
-        // lanes of this wavefront that hold a valid key with the same digit
-        unsigned long long peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < RADIX_BITS; ++b) {
-            const unsigned long long bal = __ballot((digit >> b) & 1);
-            peers &= ((digit >> b) & 1) ? bal : ~bal;
-        }
+        const int digit = (key[r] >> shift) & (RADIX - 1);
+        const unsigned long long peers = digit_peers(valid, digit);
         const unsigned long long lower = peers & ((1ull << lane) - 1ull);
         const int rank_in_wave = __popcll(lower);
         if (valid && lower == 0ull) wcnt[wave][digit] = __popcll(peers);   // one writer per digit
@@ -183,10 +241,109 @@ __global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const int32_t* __
             running[threadIdx.x] += add;
         }
         if (valid) {
-            keys_out[pos] = key;
-            vals_out[pos] = val;
+            keys_out[pos] = key[r];
+            vals_out[pos] = val[r];
         }
         __syncthreads();
+    }
+}
+
+// The whole index of at most SMALL_KEYS keys by one workgroup, keys and values in LDS: the same stable
+// radix passes (rounds of 1024 keys), then the segment heads.
+constexpr int SMALL_KEYS = 4096, SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
+__global__ __launch_bounds__(SMALL_THREADS) void small_index_kernel(const int32_t* __restrict__ head, int n_head,
+                                                                    const int32_t* __restrict__ tail, int n, int bits,
+                                                                    int32_t* __restrict__ vals_out, int32_t* __restrict__ uniq,
+                                                                    int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) {
+    __shared__ int32_t ks[2][SMALL_KEYS], vs[2][SMALL_KEYS];
+    __shared__ int32_t running[RADIX], wcnt[SMALL_WAVES][RADIX], wsum[SMALL_WAVES];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (int i = t; i < n; i += SMALL_THREADS) {
+        ks[0][i] = i < n_head ? head[i] : tail[i - n_head];
+        vs[0][i] = i;
+    }
+    int cur = 0;
+    for (int shift = 0; shift < bits; shift += RADIX_BITS) {
+        if (t < RADIX) running[t] = 0;
+        for (int i = t; i < SMALL_WAVES * RADIX; i += SMALL_THREADS) (&wcnt[0][0])[i] = 0;
+        __syncthreads();
+        for (int i = t; i < n; i += SMALL_THREADS) atomicAdd(&running[(ks[cur][i] >> shift) & (RADIX - 1)], 1);
+        __syncthreads();
+        if (wave == 0) {          // exclusive scan of the 256 counts, four per lane
+            int32_t c[4], sum = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                c[j] = running[lane * 4 + j];
+                sum += c[j];
+            }
+            int32_t inc = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int32_t v = __shfl_up(inc, off, 64);
+                if (lane >= off) inc += v;
+            }
+            int32_t run = inc - sum;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                running[lane * 4 + j] = run;
+                run += c[j];
+            }
+        }
+        __syncthreads();
+        for (int base = 0; base < n; base += SMALL_THREADS) {
+            const int i = base + t;
+            const bool valid = i < n;
+            const int32_t key = valid ? ks[cur][i] : 0, val = valid ? vs[cur][i] : 0;
+            const int digit = (key >> shift) & (RADIX - 1);
+            const unsigned long long peers = digit_peers(valid, digit);
+            const unsigned long long lower = peers & ((1ull << lane) - 1ull);
+            if (valid && lower == 0ull) wcnt[wave][digit] = __popcll(peers);
+            __syncthreads();
+            if (t < RADIX) {      // counts of a digit -> its position in every wavefront
+                int32_t run = running[t];
+                for (int w = 0; w < SMALL_WAVES; ++w) {
+                    const int32_t c = wcnt[w][t];
+                    wcnt[w][t] = run;
+                    run += c;
+                }
+                running[t] = run;
+            }
+            __syncthreads();
+            if (valid) {
+                const int pos = wcnt[wave][digit] + __popcll(lower);
+                ks[cur ^ 1][pos] = key;
+                vs[cur ^ 1][pos] = val;
+            }
+            __syncthreads();
+            for (int x = t; x < SMALL_WAVES * RADIX; x += SMALL_THREADS) (&wcnt[0][0])[x] = 0;
+            __syncthreads();
+        }
+        cur ^= 1;
+    }
+    int32_t done = 0;             // heads before the round (the same in all threads)
+    for (int base = 0; base < n; base += SMALL_THREADS) {
+        const int i = base + t;
+        const bool valid = i < n;
+        const bool is_head = valid && (i == 0 || ks[cur][i] != ks[cur][i - 1]);
+        const unsigned long long m = __ballot(is_head);
+        __syncthreads();
+        if (lane == 0) wsum[wave] = __popcll(m);
+        __syncthreads();
+        int32_t at = done + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int w = 0; w < SMALL_WAVES; ++w) {
+            at += w < wave ? wsum[w] : 0;
+            done += wsum[w];
+        }
+        if (is_head) {
+            uniq[at] = ks[cur][i];
+            seg_off[at] = i;
+        }
+        if (valid) vals_out[i] = vs[cur][i];
+    }
+    if (t == 0) {
+        seg_off[done] = n;
+        *n_uniq = done;
     }
 }
 
@@ -204,7 +361,10 @@ hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* s
 
 }  // namespace
 
-size_t index_hist_elems(int64_t n_keys) { return (size_t)RADIX * tiles_of(std::max<int64_t>(n_keys, 1), SORT_TILE); }
+size_t index_hist_elems(int64_t n_keys) {
+    const size_t tiles = tiles_of(std::max<int64_t>(n_keys, 1), SORT_TILE);
+    return (size_t)RADIX * std::max(tiles, 2 * std::min<size_t>(tiles, MID_TILES));     // (the short scan is out of place)
+}
 
 size_t index_scan_tmp_elems(int64_t n_keys) {
     const int64_t a = tiles_of((int64_t)index_hist_elems(n_keys), SCAN_TILE);
@@ -224,20 +384,37 @@ hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* t
         *src_out = buf.vals_a;
         return hipGetLastError();
     }
-    const unsigned gblocks = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
-    hipLaunchKernelGGL(assemble_kernel, dim3(gblocks), dim3(256), 0, s, head, n_head, tail, n, buf.keys_a, buf.vals_a);
-
     int bits = 1;
     while (bits < 31 && (1ll << bits) < (long long)key_bound) ++bits;
+    if (n <= SMALL_KEYS) {
+        hipLaunchKernelGGL(small_index_kernel, dim3(1), dim3(SMALL_THREADS), 0, s, head, n_head, tail, (int)n, bits, buf.vals_a,
+                           buf.uniq, buf.seg_off, buf.n_uniq);
+        *src_out = buf.vals_a;
+        return hipGetLastError();
+    }
     const int n_tiles = tiles_of(n, SORT_TILE);
+    const bool mid = n_tiles <= MID_TILES;
+    int32_t* offs = mid ? buf.hist + (size_t)RADIX * n_tiles : buf.hist;
     int32_t *kin = buf.keys_a, *kout = buf.keys_b, *vin = buf.vals_a, *vout = buf.vals_b;
     for (int shift = 0; shift < bits; shift += RADIX_BITS) {
-        hipLaunchKernelGGL(hist_kernel, dim3(n_tiles), dim3(SORT_THREADS), 0, s, (const int32_t*)kin, n, shift,
-                           n_tiles, buf.hist);
-        hipError_t e = scan_exclusive(buf.hist, buf.hist, (int64_t)RADIX * n_tiles, buf.scan_tmp, s);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(scatter_kernel, dim3(n_tiles), dim3(SORT_THREADS), 0, s, (const int32_t*)kin,
-                           (const int32_t*)vin, n, shift, n_tiles, (const int32_t*)buf.hist, kout, vout);
+        const KeySource<true> first{head, tail, n_head};
+        const KeySource<false> sorted{kin, vin, 0};
+        if (shift == 0)
+            hipLaunchKernelGGL((hist_kernel<true>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, first, n, shift, n_tiles, buf.hist);
+        else
+            hipLaunchKernelGGL((hist_kernel<false>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, sorted, n, shift, n_tiles, buf.hist);
+        if (mid) {
+            hipLaunchKernelGGL(scan_rows_kernel, dim3(RADIX), dim3(SCAN_THREADS), 0, s, (const int32_t*)buf.hist, n_tiles, offs);
+        } else {
+            hipError_t e = scan_exclusive(buf.hist, buf.hist, (int64_t)RADIX * n_tiles, buf.scan_tmp, s);
+            if (e != hipSuccess) return e;
+        }
+        if (shift == 0)
+            hipLaunchKernelGGL((scatter_kernel<true>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, first, n, shift, n_tiles,
+                               (const int32_t*)offs, kout, vout);
+        else
+            hipLaunchKernelGGL((scatter_kernel<false>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, sorted, n, shift, n_tiles,
+                               (const int32_t*)offs, kout, vout);
         std::swap(kin, kout);
         std::swap(vin, vout);
     }
@@ -245,9 +422,14 @@ hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* t
     const int nt = tiles_of(n, SCAN_TILE);
     hipLaunchKernelGGL((scan_sums_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n,
                        buf.scan_tmp);
-    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, buf.scan_tmp, nt, buf.n_uniq);
-    hipLaunchKernelGGL((scan_apply_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n,
-                       (const int32_t*)buf.scan_tmp, buf.uniq, buf.seg_off, (const int32_t*)buf.n_uniq);
+    if (nt <= MID_TILES) {
+        hipLaunchKernelGGL(heads_kernel, dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n, (const int32_t*)buf.scan_tmp,
+                           buf.uniq, buf.seg_off, buf.n_uniq);
+    } else {
+        hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, buf.scan_tmp, nt, buf.n_uniq);
+        hipLaunchKernelGGL((scan_apply_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n,
+                           (const int32_t*)buf.scan_tmp, buf.uniq, buf.seg_off, (const int32_t*)buf.n_uniq);
+    }
     *src_out = vin;
     return hipGetLastError();
 }

@@ -11,8 +11,6 @@
 #include "planner.h"
 
 #include <algorithm>
-#include <functional>
-#include <queue>
 #include <climits>
 #include <numeric>
 
@@ -95,6 +93,7 @@ struct Expander {
 
 struct Flat {   // all nodes of the batch after DNF, by global id
     std::vector<int32_t> type, arg, level, in_off, in;
+    int32_t size() const { return (int32_t)type.size(); }
     int32_t add(int32_t t, int32_t a, int32_t lvl, const int32_t* ins, int32_t n_ins) {
         type.push_back(t);
         arg.push_back(a);
@@ -115,6 +114,47 @@ int32_t number_postorder(const std::vector<Tree>& pool, int32_t t, Flat& flat) {
         lvl = std::max(lvl, flat.level[ins[k]] + 1);
     }
     return flat.add(node.type, node.arg, lvl, ins, node.n_kids);
+}
+
+// A union-free query whose nodes already stand in depth-first post-order, every node used once (what
+// samplers write): its nodes are appended as they are.  Returns the root, or -1 (nothing appended) for any
+// other query.  The nodes not yet consumed form a stack; a node's inputs must be its topmost entries in order.
+int32_t append_in_order(const ngdb_query_batch& qb, int32_t lo, int32_t hi, Flat& flat) {
+    constexpr int32_t DEEP = 64;
+    int32_t stack[DEEP];
+    int32_t top = 0;
+    for (int32_t n = lo; n < hi; ++n) {
+        if (qb.op[n] == NGDB_OP_UNION) return -1;
+        const int32_t a = qb.in_off[n], m = qb.in_off[n + 1] - a;
+        if (m > top) return -1;
+        top -= m;
+        for (int32_t k = 0; k < m; ++k)
+            if (qb.in_idx[a + k] != stack[top + k]) return -1;
+        if (top == DEEP) return -1;
+        stack[top++] = n - lo;
+    }
+    if (top != 1) return -1;
+    const int32_t base = flat.size(), shift = base - lo, in_lo = qb.in_off[lo], in_shift = (int32_t)flat.in.size() - in_lo;
+    const size_t n_new = (size_t)(hi - lo), n_in = (size_t)(qb.in_off[hi] - in_lo);
+    flat.type.resize(base + n_new);
+    flat.arg.resize(base + n_new);
+    flat.level.resize(base + n_new);
+    flat.in_off.resize(base + n_new + 1);
+    flat.in.resize(flat.in.size() + n_in);
+    for (int32_t n = lo; n < hi; ++n) {
+        const int32_t g = n + shift, op = qb.op[n];
+        flat.type[g] = op;
+        flat.arg[g] = op == NGDB_OP_ANCHOR || op == NGDB_OP_PROJ ? qb.arg[n] : 0;
+        int32_t lvl = 0;
+        for (int32_t k = qb.in_off[n]; k < qb.in_off[n + 1]; ++k) {
+            const int32_t kid = qb.in_idx[k] + base;
+            flat.in[k + in_shift] = kid;
+            lvl = std::max(lvl, flat.level[kid] + 1);
+        }
+        flat.level[g] = lvl;
+        flat.in_off[g + 1] = qb.in_off[n + 1] + in_shift;
+    }
+    return base + (hi - lo) - 1;
 }
 
 // Max-Fillness schedule (Alg. 1 without the gradient nodes, which mirror it): returns the step
@@ -273,31 +313,47 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
 
     // 1. DNF + global numbering
     Flat flat;
+    const size_t n_given = B > 0 ? (size_t)qb.node_off[B] : 0, guess = n_given + n_given / 4 + 16;
+    flat.type.reserve(guess);
+    flat.arg.reserve(guess);
+    flat.level.reserve(guess);
+    flat.in_off.reserve(guess + 1);
+    flat.in.reserve(guess);
     flat.in_off.push_back(0);
-    std::vector<std::vector<int32_t>> roots(B);
+    std::vector<int32_t> root_node;          // roots of all queries, P.root_off delimits them
+    root_node.reserve((size_t)B + B / 4 + 16);
+    P.root_off.reserve((size_t)B + 1);
+    P.root_off.push_back(0);
     std::vector<Tree> pool;
     std::vector<int32_t> branches;
     for (int32_t q = 0; q < B; ++q) {
-        pool.clear();
-        Expander ex{qb, qb.node_off[q], qb.node_off[q + 1] - qb.node_off[q], pool, err};
-        branches.clear();
-        ex.expand(ex.n_local - 1, 0, branches);
-        if (ex.code != NGDB_OK) return ex.code;
-        for (int32_t b : branches) {
-            if (pool[b].type == NGDB_OP_ANCHOR) {
+        const int32_t lo = qb.node_off[q], hi = qb.node_off[q + 1];
+        int32_t g = append_in_order(qb, lo, hi, flat);
+        const bool in_order = g >= 0;
+        if (!in_order) {
+            pool.clear();
+            Expander ex{qb, lo, hi - lo, pool, err};
+            branches.clear();
+            ex.expand(ex.n_local - 1, 0, branches);
+            if (ex.code != NGDB_OK) return ex.code;
+        }
+        const size_t n_branch = in_order ? 1 : branches.size();
+        for (size_t b = 0; b < n_branch; ++b) {
+            if ((in_order ? flat.type[g] : pool[branches[b]].type) == NGDB_OP_ANCHOR) {
                 err = "a query must contain at least one operator";
                 return NGDB_ERR_UNSUPPORTED;
             }
-            int32_t g = number_postorder(pool, b, flat);
+            if (!in_order) g = number_postorder(pool, branches[b], flat);
             if (flat.level[g] > NGDB_MAX_LEVELS) {
                 err = "query deeper than NGDB_MAX_LEVELS";
                 return NGDB_ERR_UNSUPPORTED;
             }
-            roots[q].push_back(g);
+            root_node.push_back(g);
         }
-        P.max_branch = std::max<int32_t>(P.max_branch, (int32_t)branches.size());
+        P.root_off.push_back((int32_t)root_node.size());
+        P.max_branch = std::max<int32_t>(P.max_branch, (int32_t)n_branch);
     }
-    const int32_t n_nodes = (int32_t)flat.type.size();
+    const int32_t n_nodes = flat.size();
 
     // 1b. execution step of every operator: its depth, or its Max-Fillness step.  From here
     // on "level" means execution step.  The eager-reclamation peak of the level-synchronous
@@ -324,97 +380,102 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
         }
     }
 
-    // 2. anchors and operator nodes
-    std::vector<int32_t> ops, anchor_idx(n_nodes, -1);
-    for (int32_t g = 0; g < n_nodes; ++g) {
-        if (flat.type[g] == NGDB_OP_ANCHOR) {
-            anchor_idx[g] = (int32_t)P.anchor_ent.size();
-            P.anchor_ent.push_back(flat.arg[g]);
-        } else {
-            ops.push_back(g);
-        }
-    }
-    P.n_anchor = (int32_t)P.anchor_ent.size();
-    P.n_slots = (int32_t)ops.size();
-
-    // 3. slots: type-major, then level, input count, node id
+    // 2. anchors, and the class (type, level, input count) of every operator: a counting sort by class
+    // gives the slots (type-major, then level, input count, node id)
     auto type_rank = [](int32_t t) { return t == NGDB_OP_PROJ ? 0 : (t == NGDB_OP_INTER ? 1 : 2); };
-    int32_t top_level = 0;
-    for (int32_t g : ops) top_level = std::max(top_level, flat.level[g]);
+    int32_t top_level = 0, n_anchor = 0;
+    for (int32_t g = 0; g < n_nodes; ++g) {
+        top_level = std::max(top_level, flat.level[g]);
+        n_anchor += flat.type[g] == NGDB_OP_ANCHOR ? 1 : 0;
+    }
+    P.n_anchor = n_anchor;
+    P.n_slots = n_nodes - n_anchor;
     const int64_t n_lvl = (int64_t)top_level + 1, n_card = NGDB_MAX_CARD + 1;
-    std::vector<int32_t> key(ops.size()), order;
-    std::vector<int32_t> by_slot(ops.size());
-    if (3 * n_lvl * n_card > INT32_MAX) {
+    const int64_t n_class = 3 * n_lvl * n_card;
+    if (n_class > INT32_MAX) {
         err = "too many execution steps";
         return NGDB_ERR_UNSUPPORTED;
     }
-    for (size_t i = 0; i < ops.size(); ++i)
-        key[i] = (int32_t)((type_rank(flat.type[ops[i]]) * n_lvl + flat.level[ops[i]]) * n_card + flat.nin(ops[i]));
-    stable_order_by_key(key, 3 * n_lvl * n_card, order);
-    for (size_t i = 0; i < ops.size(); ++i) by_slot[i] = ops[order[i]];
-    std::vector<int32_t> slot(n_nodes, -1);
-    for (int32_t s = 0; s < P.n_slots; ++s) {
-        slot[by_slot[s]] = s;
-        const int32_t t = flat.type[by_slot[s]];
-        if (t == NGDB_OP_PROJ) ++P.n_proj;
-        else if (t == NGDB_OP_INTER) ++P.n_inter;
-        else ++P.n_neg;
+    std::vector<int32_t> place(n_nodes);     // anchors: their number; operators: first their class, then their slot
+    std::vector<int32_t> start((size_t)n_class + 1, 0);
+    P.anchor_ent.resize(n_anchor);
+    int32_t at_anchor = 0;
+    for (int32_t g = 0; g < n_nodes; ++g) {
+        const int32_t t = flat.type[g];
+        if (t == NGDB_OP_ANCHOR) {
+            P.anchor_ent[at_anchor] = flat.arg[g];
+            place[g] = at_anchor++;
+        } else {
+            const int32_t c = (int32_t)((type_rank(t) * n_lvl + flat.level[g]) * n_card + flat.nin(g));
+            place[g] = c;
+            ++start[c + 1];
+        }
+    }
+    for (int64_t c = 0; c < n_class; ++c) start[c + 1] += start[c];
+    P.n_proj = start[n_lvl * n_card];
+    P.n_inter = start[2 * n_lvl * n_card] - P.n_proj;
+    P.n_neg = P.n_slots - P.n_proj - P.n_inter;
+    std::vector<int32_t> by_slot(P.n_slots);
+    {
+        std::vector<int32_t> next(start.begin(), start.end() - 1);
+        for (int32_t g = 0; g < n_nodes; ++g)
+            if (flat.type[g] != NGDB_OP_ANCHOR) {
+                const int32_t sl = next[place[g]]++;
+                by_slot[sl] = g;
+                place[g] = sl;
+            }
     }
     const int32_t type_base[3] = {0, P.n_proj, P.n_proj + P.n_inter};
-    auto grad_row = [&](int32_t g) { return slot[g] >= 0 ? slot[g] : P.n_slots + anchor_idx[g]; };
+    auto is_anchor = [&](int32_t g) { return flat.type[g] == NGDB_OP_ANCHOR; };
+    auto grad_row = [&](int32_t g) { return is_anchor(g) ? P.n_slots + place[g] : place[g]; };
 
-    // 4. groups: level, type, input count; members in node order
-    std::vector<int32_t> by_group(ops.size());
-    for (size_t i = 0; i < ops.size(); ++i)
-        key[i] = (int32_t)((flat.level[ops[i]] * 3 + type_rank(flat.type[ops[i]])) * n_card + flat.nin(ops[i]));
-    stable_order_by_key(key, 3 * n_lvl * n_card, order);
-    for (size_t i = 0; i < ops.size(); ++i) by_group[i] = ops[order[i]];
-    size_t i = 0;
-    while (i < by_group.size()) {
-        const int32_t g0 = by_group[i];
-        size_t j = i;
-        while (j < by_group.size() && flat.level[by_group[j]] == flat.level[g0] &&
-               flat.type[by_group[j]] == flat.type[g0] && flat.nin(by_group[j]) == flat.nin(g0))
-            ++j;
-        const int32_t n = (int32_t)(j - i), nin = flat.nin(g0), t = flat.type[g0];
-        P.g_level.push_back(flat.level[g0]);
-        P.g_type.push_back(t);
-        P.g_nin.push_back(nin);
-        P.g_n.push_back(n);
-        P.g_out_base.push_back(slot[g0]);
-        P.g_ref_off.push_back((int32_t)P.in_ref.size());
-        if (t == NGDB_OP_INTER) {
-            P.g_mlp_base.push_back(P.n_int_rows);
-            P.n_int_rows += n * nin;
-        } else {
-            P.g_mlp_base.push_back(slot[g0] - type_base[type_rank(t)]);
-        }
-        P.g_rel_off.push_back(t == NGDB_OP_PROJ ? (int32_t)P.rel.size() : -1);
-        for (int32_t k = 0; k < nin; ++k)
-            for (size_t m = i; m < j; ++m) {
-                const int32_t c = flat.in[flat.in_off[by_group[m]] + k];
-                P.in_ref.push_back(slot[c] >= 0 ? slot[c] : -1 - flat.arg[c]);
-                P.in_gslot.push_back(grad_row(c));
+    // 3. groups: the classes that have members, by level, type, input count; members are a class's slots
+    P.in_ref.reserve(flat.in.size());
+    P.in_gslot.reserve(flat.in.size());
+    P.rel.reserve(P.n_proj);
+    for (int64_t l = 1; l < n_lvl; ++l)
+        for (int32_t tr = 0; tr < 3; ++tr)
+            for (int32_t nin = 1; nin < n_card; ++nin) {
+                const int64_t c = (tr * n_lvl + l) * n_card + nin;
+                const int32_t s0 = start[c], n = start[c + 1] - s0;
+                if (n == 0) continue;
+                const int32_t t = tr == 0 ? NGDB_OP_PROJ : (tr == 1 ? NGDB_OP_INTER : NGDB_OP_NEG);
+                P.g_level.push_back((int32_t)l);
+                P.g_type.push_back(t);
+                P.g_nin.push_back(nin);
+                P.g_n.push_back(n);
+                P.g_out_base.push_back(s0);
+                P.g_ref_off.push_back((int32_t)P.in_ref.size());
+                if (t == NGDB_OP_INTER) {
+                    P.g_mlp_base.push_back(P.n_int_rows);
+                    P.n_int_rows += n * nin;
+                } else {
+                    P.g_mlp_base.push_back(s0 - type_base[tr]);
+                }
+                P.g_rel_off.push_back(t == NGDB_OP_PROJ ? (int32_t)P.rel.size() : -1);
+                for (int32_t k = 0; k < nin; ++k)
+                    for (int32_t m = s0; m < s0 + n; ++m) {
+                        const int32_t kid = flat.in[flat.in_off[by_slot[m]] + k];
+                        const bool leaf = is_anchor(kid);
+                        P.in_ref.push_back(leaf ? -1 - flat.arg[kid] : place[kid]);
+                        P.in_gslot.push_back(leaf ? P.n_slots + place[kid] : place[kid]);
+                    }
+                if (t == NGDB_OP_PROJ)
+                    for (int32_t m = s0; m < s0 + n; ++m) P.rel.push_back(flat.arg[by_slot[m]]);
             }
-        if (t == NGDB_OP_PROJ)
-            for (size_t m = i; m < j; ++m) P.rel.push_back(flat.arg[by_group[m]]);
-        i = j;
-    }
     P.n_groups = (int32_t)P.g_level.size();
     P.n_levels = P.n_groups ? P.g_level.back() : 0;
     P.lvl_off.assign(P.n_levels + 2, 0);
     for (int32_t l : P.g_level) P.lvl_off[l + 1] += 1;
     for (size_t l = 1; l < P.lvl_off.size(); ++l) P.lvl_off[l] += P.lvl_off[l - 1];
 
-    // 5. roots
-    P.root_off.push_back(0);
-    for (int32_t q = 0; q < B; ++q) {
-        for (int32_t g : roots[q]) P.root_slot.push_back(slot[g]);
-        P.root_off.push_back((int32_t)P.root_slot.size());
-    }
-    P.n_roots = (int32_t)P.root_slot.size();
+    // 4. roots
+    P.n_roots = (int32_t)root_node.size();
+    P.root_slot.resize(P.n_roots);
+    for (int32_t i = 0; i < P.n_roots; ++i) P.root_slot[i] = place[root_node[i]];
 
-    // 6. relation gradient index over the projections in slot order
+    // 5. relation gradient index over the projections in slot order
+    std::vector<int32_t> order;
     std::vector<int32_t> rkeys(P.n_proj), rsrc(P.n_proj);
     for (int32_t s = 0; s < P.n_proj; ++s) {
         const int32_t g = by_slot[s];
@@ -425,24 +486,28 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
     P.r_src.resize(P.n_proj);
     for (int32_t s = 0; s < P.n_proj; ++s) P.r_src[s] = rsrc[order[s]];
 
-    // 7. rows of a forward-only pass under eager reference counting (Sec. 4.3, Reclaim(T); Alg. 1,
+    // 6. rows of a forward-only pass under eager reference counting (Sec. 4.3, Reclaim(T); Alg. 1,
     // DecrementRefCounts): the steps in order; every output of a step takes, in group and member
     // order, the lowest free row (a new one if none is free); when the step has run, the rows of
     // the outputs it consumed are free again.  Every output has one consumer (queries are trees);
-    // roots have none and keep their rows.
-    P.f_row.assign(P.n_slots, -1);
-    std::priority_queue<int32_t, std::vector<int32_t>, std::greater<int32_t>> free_rows;
+    // roots have none and keep their rows.  Free rows are bits; the search for the lowest goes on from
+    // where the last one was found, and starts over when rows were freed.
+    P.f_row.resize(P.n_slots);
+    std::vector<uint64_t> free_bits((size_t)P.n_slots / 64 + 1, 0);
+    size_t n_free = 0, word = 0;
     P.n_f_rows = 0;
     for (int32_t l = 1; l <= P.n_levels; ++l) {
         int32_t rows_now[3] = {0, 0, 0};
         for (int32_t g = P.lvl_off[l]; g < P.lvl_off[l + 1]; ++g) {
             const int32_t t = P.g_type[g];
-            rows_now[t == NGDB_OP_PROJ ? 0 : (t == NGDB_OP_INTER ? 1 : 2)] += P.g_n[g] * (t == NGDB_OP_INTER ? P.g_nin[g] : 1);
+            rows_now[type_rank(t)] += P.g_n[g] * (t == NGDB_OP_INTER ? P.g_nin[g] : 1);
             for (int32_t m = 0; m < P.g_n[g]; ++m) {
                 int32_t row;
-                if (!free_rows.empty()) {
-                    row = free_rows.top();
-                    free_rows.pop();
+                if (n_free > 0) {
+                    while (free_bits[word] == 0) ++word;
+                    row = (int32_t)(word * 64 + __builtin_ctzll(free_bits[word]));
+                    free_bits[word] &= free_bits[word] - 1;
+                    --n_free;
                 } else {
                     row = P.n_f_rows++;
                 }
@@ -453,9 +518,13 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
             const int32_t n_ref = P.g_n[g] * P.g_nin[g];
             for (int32_t k = 0; k < n_ref; ++k) {
                 const int32_t ref = P.in_ref[P.g_ref_off[g] + k];
-                if (ref >= 0) free_rows.push(P.f_row[ref]);
+                if (ref < 0) continue;
+                const int32_t row = P.f_row[ref];
+                free_bits[row >> 6] |= 1ull << (row & 63);
+                ++n_free;
             }
         }
+        word = 0;
         for (int k = 0; k < 3; ++k) P.f_step_rows[k] = std::max(P.f_step_rows[k], rows_now[k]);
     }
     return NGDB_OK;
