@@ -624,7 +624,11 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
 int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hipStream_t s, const FwdSpace& w) {
     if (c->cfg.family == NGDB_FAMILY_BOX) return enqueue_forward_box(c, pl, s);   // (always on the context's buffers)
     const int d = c->cfg.d, h = c->cfg.h;
-    {
+    c->have_pieces = false;
+    bool narrow = true;      // every launch of the pass has a few rows only
+    for (const std::vector<Segment>& segs : pl->levels)
+        for (const Segment& sg : segs) narrow = narrow && gemm_takes_rows(sg.rows, std::max(d, h));
+    if (!narrow) {
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
         int rc_p = make_weight_pieces(c, s);
         if (rc_p != NGDB_OK) return rc_p;

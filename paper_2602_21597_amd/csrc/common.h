@@ -143,6 +143,8 @@ struct GemmGroup {
 // given) whether the launch wrote c_pieces (only the kernels that read their B operand as pieces do,
 // in launches of at most 256 small tiles, and only if every problem of the group asks for it).
 hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route = nullptr, bool* emitted = nullptr);
+// Whether a forward layer of M rows is computed row by row (and has no use for split weights).
+bool gemm_takes_rows(int M, int K);
 
 // A row-major matrix W [R][C] as B operand of the bf16 MFMA block in both forms, each value split
 // into three bf16 pieces, stored tile by tile (32 n x 16 k) in lane order and zero beyond the

@@ -70,6 +70,10 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     const int nb = a.root_off[i + 1] - r0;
     const int has_pos = a.pos ? 1 : 0;
     const int CT = a.C + has_pos;
+    // (forward only: the list may be shared by gridDim.y workgroups, equal slices of it each)
+    const int slice = TRAIN ? CT : (CT + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int c_lo = TRAIN ? 0 : (int)blockIdx.y * slice, c_hi = TRAIN ? CT : min(CT, c_lo + slice);
+    if (!TRAIN && c_lo >= c_hi) return;
 
     constexpr int PARTS = BOX ? 2 : 1;                               // centre (and offset) per branch
     float4* ybr = reinterpret_cast<float4*>(lds);                    // [PARTS][nb][d4]
@@ -77,8 +81,8 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     constexpr bool SEQ = NW <= 4;                                    // how branch 0 is summed over the wavefronts
     float4* stage = accs + (TRAIN ? (size_t)NW * PARTS * (a.max_branch - 1) * d4 : 0);   // [NW][PARTS][d4]  (!SEQ)
     float* lossp = reinterpret_cast<float*>(stage + (TRAIN && !SEQ ? (size_t)NW * PARTS * d4 : 0));
-    float* out_s = lossp + 16;                                       // [CT] scores          (STASH)
-    float* out_c = out_s + CT;                                       // [CT] dL/ds           (STASH, TRAIN)
+    float* out_s = lossp + 16;                                       // [slice] scores       (STASH)
+    float* out_c = out_s + slice;                                    // [CT] dL/ds           (STASH, TRAIN)
     int* out_b = reinterpret_cast<int*>(out_c + CT);                 // [CT] winning branch  (STASH, TRAIN, no MASK)
     const float4* obr = ybr + (size_t)nb * d4;                       // offsets (BOX)
 
@@ -111,12 +115,12 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     // on short ones).  Requests past the end repeat the last candidate (clamped, no branches
     // around loads).
     float4 cur[NCH], nxt[NCH];
-    int c = wave;
-    int32_t e_nxt = cand_id(a, i, has_pos, min(c + NW, CT - 1));
-    if (c < CT) load_row<NCH, B16>(a, cand_id(a, i, has_pos, c), lane, d4, cur);
-    for (; c < CT; c += NW) {
+    int c = c_lo + wave;
+    int32_t e_nxt = cand_id(a, i, has_pos, min(c + NW, c_hi - 1));
+    if (c < c_hi) load_row<NCH, B16>(a, cand_id(a, i, has_pos, c), lane, d4, cur);
+    for (; c < c_hi; c += NW) {
         load_row<NCH, B16>(a, e_nxt, lane, d4, nxt);
-        e_nxt = cand_id(a, i, has_pos, min(c + 2 * NW, CT - 1));
+        e_nxt = cand_id(a, i, has_pos, min(c + 2 * NW, c_hi - 1));
         float best = INFINITY;
         int bw = 0;
         for (int b = 0; b < nb; ++b) {
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
         }
         const float s = a.gamma - best;
         const size_t pair = (size_t)i * CT + c;
-        if (STASH) out_s[c] = s;                 // (every lane the same value to the same word)
+        if (STASH) out_s[c - c_lo] = s;          // (every lane the same value to the same word)
         else if (lane == 0) a.score[pair] = s;
         if (TRAIN) {
             const bool is_pos = (c == 0);
@@ -226,8 +230,8 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
 
     if (STASH) {
         __syncthreads();
-        for (int idx = tid; idx < CT; idx += NW * 64) {
-            const size_t pair = (size_t)i * CT + idx;
+        for (int idx = tid; idx < c_hi - c_lo; idx += NW * 64) {
+            const size_t pair = (size_t)i * CT + c_lo + idx;
             a.score[pair] = out_s[idx];
             if (TRAIN) {
                 a.coef[pair] = out_c[idx];
@@ -314,20 +318,24 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
 
 constexpr int STASH_MAX_PAIRS = 4096;     // pairs per query whose results fit the LDS stash (48 KB)
 template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16, bool STASH>
-hipError_t launch_stash(const ScoreArgs& a, size_t lds, hipStream_t s) {
+hipError_t launch_stash(const ScoreArgs& a, size_t lds, int parts, hipStream_t s) {
     if (lds > 64 * 1024)
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH>), dim3(a.B), dim3(NW * 64), lds, s, a);
+    hipLaunchKernelGGL((score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH>), dim3(a.B, parts), dim3(NW * 64), lds, s, a);
     return hipGetLastError();
 }
 template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16 = false>
 hipError_t launch_variant(const ScoreArgs& a, size_t lds, hipStream_t s) {
     const int CT = a.C + (a.pos ? 1 : 0);
-    const size_t stash = (size_t)CT * (TRAIN ? 3 : 1) * sizeof(float);
-    if (CT <= STASH_MAX_PAIRS && lds + stash <= 150 * 1024)
-        return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, true>(a, lds + stash, s);
-    return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, false>(a, lds, s);
+    // forward only: few queries share their lists over enough workgroups of 4 wavefronts to cover the chip, at least
+    // four candidates a wavefront (one query with 1000 candidates: 24 us in one workgroup, 6 in 63)
+    const int parts = TRAIN ? 1 : std::max(1, std::min((2048 + a.B - 1) / a.B, (CT + 4 * NW - 1) / (4 * NW)));
+    const int slice = (CT + parts - 1) / parts;
+    const size_t stash = (size_t)slice * (TRAIN ? 3 : 1) * sizeof(float);
+    if (slice <= STASH_MAX_PAIRS && lds + stash <= 150 * 1024)
+        return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, true>(a, lds + stash, parts, s);
+    return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, false>(a, lds, parts, s);
 }
 
 template <int NCH, int NW>
@@ -343,8 +351,8 @@ hipError_t launch_nw(const ScoreArgs& a, bool train, size_t lds, hipStream_t s) 
 
 template <int NCH>
 hipError_t launch_nch(const ScoreArgs& a, bool train, hipStream_t s) {
-    // enough wavefronts to cover the chip even for small batches
-    const int nw = a.B >= 2048 ? 4 : (a.B >= 1024 ? 8 : 16);
+    // enough wavefronts to cover the chip even for small batches (forward only: shared lists do that)
+    const int nw = !train || a.B >= 2048 ? 4 : (a.B >= 1024 ? 8 : 16);
     auto lds_for = [&](int w) {
         const int per_wave = a.max_branch - 1 + (w <= 4 ? 0 : 1);   // union accumulators (+ staging)
         return ((size_t)(a.off ? 2 : 1) * a.d * (a.max_branch + (train ? w * per_wave : 0)) + 16) * sizeof(float);
