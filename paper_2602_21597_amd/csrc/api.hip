@@ -84,7 +84,6 @@ struct ngdb_ctx_s {
     DevBuf rank_dist;   // distances of one entity chunk in the all-entity ranking
     DevBuf rank_thr, rank_count;   // filtered ranks: distance of every listed answer, entities closer than it (total, chunk)
     DevBuf rank_filter;            // integer rows, bounds and lists of the filtered passes
-    DevBuf colsum_part; // 6 scratch areas of the bias-gradient column sums
     DevBuf gW;          // gradients of the 12 MLP tensors, packed
     // The six weight matrices of the vector family's MLPs as ready-made B operands of the contraction
     // kernel (bf16 pieces in MFMA lane order), in both orientations: rebuilt at the start of every
@@ -358,7 +357,6 @@ int size_workspace(ngdb_ctx_t* c, const ngdb_plan_t* pl, int K, bool want_table_
     ENS(c->hist, index_hist_elems(nk) * 4);
     ENS(c->scan_tmp, index_scan_tmp_elems(nk) * 4);
     ENS(c->n_uniq, 256);
-    ENS(c->colsum_part, 6 * (size_t)COLSUM_MAX_CHUNKS * std::max(d, h) * f);
     if (!c->gW.p) {
         size_t off = 0;
         for (int t = 0; t < 3; ++t) {
@@ -703,43 +701,22 @@ struct WgradJob {   // what enqueue_weight_grads needs after a backward chain
 };
 
 // Gradients of the MLP tensors of the given types (their Z / H / dH buffers, dY = gradient of
-// the second layer's output): both weight matrices of every type in one grouped launch, the
-// biases as column sums.
-// With `open` the bias gradients are left as partial column sums (described in *open) for the
-// dense Adam launch to add up: one launch less on the step's tail.
-int enqueue_weight_grads(ngdb_ctx_t* c, const WgradJob& wj, hipStream_t s, ColsumJobs* open = nullptr) {
+// the second layer's output): weights and biases of both layers of every type in one launch.
+int enqueue_weight_grads(ngdb_ctx_t* c, const WgradJob& wj, hipStream_t s, bool aside) {
     const int d = c->cfg.d, h = c->cfg.h, nt = wj.nt;
-    const int* types = wj.types;
-    const size_t* rows = wj.rows;
-    const float* const* dY = wj.dY;
     float* gW = ptr<float>(c->gW);
     Timed tm(c, NGDB_TK_WGRAD, s);
-    GemmArgs w[6];
-    ColsumJobs cs{};
+    WgradArgs w[6];
+    double flop = 0.0;
     for (int i = 0; i < nt; ++i) {
-        const int t = types[i], gs = gslot_of(t), r = (int)rows[i];
-        GemmArgs& wa = w[2 * i];       // dWa[h,d] = dH^T Z
-        wa.A = ptr<float>(c->dH[t]); wa.lda = h; wa.a_kcontig = false;
-        wa.B = ptr<float>(c->Z[t]); wa.ldb = d; wa.b_kcontig = false;
-        wa.C = gW + c->gw_off[gs + 0]; wa.ldc = d; wa.M = h; wa.N = d; wa.K = r;
-        GemmArgs& wb = w[2 * i + 1];   // dWb[d,h] = dY^T H
-        wb.A = dY[i]; wb.lda = d; wb.a_kcontig = false;
-        wb.B = ptr<float>(c->H[t]); wb.ldb = h; wb.b_kcontig = false;
-        wb.C = gW + c->gw_off[gs + 2]; wb.ldc = h; wb.M = d; wb.N = h; wb.K = r;
-        float* part = ptr<float>(c->colsum_part) + (size_t)(2 * i) * COLSUM_MAX_CHUNKS * std::max(d, h);
-        cs.job[cs.count++] = ColsumJob{ptr<float>(c->dH[t]), gW + c->gw_off[gs + 1], part, r, h, h, 0, 0};
-        cs.job[cs.count++] = ColsumJob{dY[i], gW + c->gw_off[gs + 3], part + (size_t)COLSUM_MAX_CHUNKS * std::max(d, h),
-                                       r, d, d, 0, 0};
+        const int t = wj.types[i], gs = gslot_of(t), r = (int)wj.rows[i];
+        // dWa[h,d] = dH^T Z, dba = column sums of dH; dWb[d,h] = dY^T H, dbb = column sums of dY
+        w[2 * i] = WgradArgs{ptr<float>(c->dH[t]), ptr<float>(c->Z[t]), gW + c->gw_off[gs + 0], gW + c->gw_off[gs + 1], h, d, r, h, d, d};
+        w[2 * i + 1] = WgradArgs{wj.dY[i], ptr<float>(c->H[t]), gW + c->gw_off[gs + 2], gW + c->gw_off[gs + 3], d, h, r, d, h, h};
+        flop += 4.0 * h * d * r;
     }
-    {
-        int route = GEMM_FP32;
-        HIPCHK(c, launch_gemm_group(w, 2 * nt, s, &route));
-        double flop = 0.0;
-        for (int i = 0; i < 2 * nt; ++i) flop += 2.0 * w[i].M * w[i].N * w[i].K;
-        tm.work(route, flop);
-    }
-    HIPCHK(c, launch_colsums(cs, s, open == nullptr));
-    if (open) *open = cs;
+    HIPCHK(c, launch_wgrad_group(w, 2 * nt, s, aside));
+    tm.work(GEMM_SPLIT, flop);
     return NGDB_OK;
 }
 
@@ -999,8 +976,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
             HIPCHK(c, launch_table_update(small[k], ah, s_tab));
         }
     }
-    ColsumJobs open_sums{};
-    rc = enqueue_weight_grads(c, wj, stream, apply ? &open_sums : nullptr);
+    rc = enqueue_weight_grads(c, wj, stream, aside && !small_step);
     if (rc != NGDB_OK) return rc;
     if (apply) {
         DenseAdamJob job{};
@@ -1013,12 +989,6 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
             job.p[k] = ts[i]->p; job.m[k] = ts[i]->m; job.v[k] = ts[i]->v;
             job.g[k] = ptr<float>(c->gW) + c->gw_off[i];
             job.n[k] = sz[i % 4];
-            for (int q = 0; q < open_sums.count; ++q)     // a bias: its gradient is still in chunks
-                if (open_sums.job[q].out == job.g[k]) {
-                    job.gsum[k] = open_sums.job[q].out;
-                    job.g[k] = open_sums.job[q].part;
-                    job.chunks[k] = open_sums.job[q].chunks;
-                }
         }
         Timed tm(c, NGDB_TK_ADAM, stream);
         HIPCHK(c, launch_dense_adam(job, ah, stream));
@@ -1362,7 +1332,7 @@ void ngdb_destroy(ngdb_ctx_t* c) {
     DevBuf* all[] = {&c->act, &c->dact, &c->Z[0], &c->Z[1], &c->Z[2], &c->H[0], &c->H[1], &c->H[2], &c->dH[0],
                      &c->dH[1], &c->dH[2], &c->Att, &c->dAtt, &c->Dx, &c->score, &c->coef, &c->win, &c->mask,
                      &c->loss_terms, &c->rec_coef, &c->rec_row, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->hist, &c->scan_tmp,
-                     &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->colsum_part, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
+                     &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
                      &c->Wb, &c->Ef, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
                      &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb};
     for (DevBuf* b : all) release(*b);
@@ -1818,7 +1788,11 @@ int ngdb_debug_gemm(const float* A, const float* B, float* C, int32_t M, int32_t
     g.a_kcontig = a_kcontig != 0; g.b_kcontig = b_kcontig != 0; g.bias = bias; g.relu = relu != 0;
     g.mask = mask; g.ldmask = ldmask; g.addend = addend; g.ldadd = ldadd; g.dst_row = dst_row;
     g.arith = arith;
-    const hipError_t e = launch_gemm(g, static_cast<hipStream_t>(stream));
+    // (as the step chooses: weight gradients have a kernel of their own)
+    const bool wgrad = arith == 0 && !g.a_kcontig && !g.b_kcontig && !bias && !relu && !mask && !addend && !dst_row &&
+                       ((M | N | lda | ldb | ldc) & 3) == 0 && (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) == 0;
+    const WgradArgs w{A, B, C, nullptr, M, N, K, lda, ldb, ldc};
+    const hipError_t e = wgrad ? launch_wgrad_group(&w, 1, static_cast<hipStream_t>(stream)) : launch_gemm(g, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? NGDB_OK : (e == hipErrorInvalidValue ? NGDB_ERR_ARG : NGDB_ERR_HIP);
 }
 

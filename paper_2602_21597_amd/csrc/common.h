@@ -58,6 +58,27 @@ __device__ __forceinline__ int32_t lane_value(int32_t v, int l) {
 __device__ __forceinline__ float lane_value(float v, int l) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), __builtin_amdgcn_readfirstlane(l)));
 }
+// A direct load from global memory into LDS (gfx950): lane l's 16 (4) bytes land at lds_base + l * 16 (4), whatever
+// global address the lane gives; lds_base is wave-uniform (it travels in M0).  The loads are
+// issued from inline assembly and waited for by hand (s_waitcnt vmcnt): left to the compiler,
+// every LDS read after such a load would wait for all of them, also those of the stages ahead.
+__device__ __forceinline__ void lds_load16(const void* gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
+}
+__device__ __forceinline__ void lds_load4(const void* gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
+}
+// at most n vector-memory operations of this wavefront still in flight (they complete in order)
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+    static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+// all LDS operations of this wavefront done
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4)); }
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
 // Hardware transcendental approximations (about 1 ulp each; the results they feed are held to 1e-4).
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
@@ -143,6 +164,16 @@ struct GemmGroup {
 // given) whether the launch wrote c_pieces (only the kernels that read their B operand as pieces do,
 // in launches of at most 256 small tiles, and only if every problem of the group asks for it).
 hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route = nullptr, bool* emitted = nullptr);
+// Weight gradients: C[M,N] = A^T B over the K rows of A [K][lda] and B [K][ldb] (the rows of an operator type),
+// and colsum[m] = sum of column m of A (the gradient of the layer's bias).  M, N and the leading
+// dimensions multiples of 4; K >= 0.  Up to GEMM_MAX_GROUP of them in one launch.
+struct WgradArgs {
+    const float *A, *B;
+    float *C, *colsum;
+    int M, N, K, lda, ldb, ldc;
+};
+hipError_t launch_wgrad_group(const WgradArgs* problems, int count, hipStream_t s, bool aside = false);
+
 // Whether a forward layer of M rows is computed row by row (and has no use for split weights).
 bool gemm_takes_rows(int M, int K);
 
@@ -210,24 +241,6 @@ struct BoxPoolJobs {
     BoxProjArgs proj;
 };
 hipError_t launch_box_pool(const BoxPoolJobs& jobs, bool backward, hipStream_t s);
-// out[c] = sum_m X[m*ld + c], c < cols, for several matrices in one launch pair (fixed
-// summation order); `part` is scratch of COLSUM_MAX_CHUNKS * cols floats per matrix
-constexpr int COLSUM_MAX_CHUNKS = 128;
-constexpr int COLSUM_MAX_JOBS = 6;
-struct ColsumJob {
-    const float* X;
-    float* out;
-    float* part;
-    int rows, cols, ld;
-    int chunk_rows, chunks;   // filled by launch_colsums
-};
-struct ColsumJobs {
-    int count;
-    ColsumJob job[COLSUM_MAX_JOBS];
-};
-// finish == false: only the partial sums (part[chunk * cols + c], chunks filled in); whoever
-// consumes them adds the chunks up in colsum_final_kernel's order.
-hipError_t launch_colsums(ColsumJobs& jobs, hipStream_t s, bool finish = true);
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // calibration access patterns (ngdb_debug_stream)
@@ -244,10 +257,6 @@ struct DenseAdamJob {
     float* v[13];
     const float* g[13];
     int64_t n[13];
-    // chunks[t] > 0: g[t] holds that many partial column sums of n[t] columns each (launch_colsums
-    // without its last step); they are added up here, the sum also stored in gsum[t]
-    int chunks[13];
-    float* gsum[13];
     int count;
 };
 hipError_t launch_dense_adam(const DenseAdamJob& job, const AdamHyper& hp, hipStream_t s);

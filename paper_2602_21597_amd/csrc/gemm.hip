@@ -644,6 +644,174 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
     }
 }
 
+// Weight gradients.  Both operands have k (the rows) as the slow index.  A wavefront owns a 64 x 64 tile of the
+// output over every fourth block of 16 rows and needs nobody: the blocks of both operands travel from global memory
+// straight into its own LDS (256 bytes of a row by 16 lanes), are read as the 8 rows x 32 columns a lane group of
+// the 32x32x16 MFMA wants, split into pieces in registers, and multiplied: 24 MFMAs (768 cycles) beside 176 vector
+// operations (704) and 8 KB of operands a block, every split value feeding two MFMA blocks.  A block's
+// buffer is requested again as soon as its values are in registers, so that two blocks are on the way during
+// the arithmetic at 64 KB of LDS per workgroup, two workgroups per compute unit.  (Staged through registers
+// and LDS as pieces, with one block ahead, a block took 4500 cycles: 51 us for the six contractions of 512
+// queries at d=400, h=800 (1356, 730 and 182 rows) and 5 us for the bias gradients, against 29 us here; 88 and
+// 53 us against 48 for 1024.)  The column sums of A that the bias gradients are fall out of the values read.
+constexpr int WG_T = 64, WG_LD = WG_T + 1;
+struct WgradGroup {
+    int count;
+    int tile_start[GEMM_MAX_GROUP + 1];
+    WgradArgs p[GEMM_MAX_GROUP];
+};
+__global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradGroup g) {
+    constexpr int BUF = 16 * WG_T * 4;                      // bytes of 16 rows of one operand
+    constexpr int WAVE_LDS = WG_T * WG_LD * 4;              // >= two buffers of both operands; the partial tile at the end
+    static_assert(WAVE_LDS >= 4 * BUF, "staging fits the reduction area");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * WAVE_LDS];
+    __shared__ float cs[4][WG_T];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int p = 0;
+#pragma unroll
+    for (int i = 1; i < GEMM_MAX_GROUP; ++i)
+        if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) p = i;
+    const WgradArgs& a = g.p[p];
+    // (tiles to dies as in gemm_kernel)
+    const int local = (int)blockIdx.x - g.tile_start[p], per_die = (g.tile_start[p + 1] - g.tile_start[p]) >> 3;
+    const int tile = (local & 7) * per_die + (local >> 3);
+    const int tiles_m = (a.M + WG_T - 1) / WG_T, tiles_n = (a.N + WG_T - 1) / WG_T;
+    if (tile >= tiles_m * tiles_n) return;
+    const bool m_major = a.M >= a.N;
+    const int m0 = (m_major ? tile / tiles_n : tile % tiles_m) * WG_T;
+    const int n0 = (m_major ? tile % tiles_n : tile / tiles_m) * WG_T;
+
+    const int nk = (a.K + 15) / 16;
+    const int rounds = nk > wave ? (nk - wave + 3) / 4 : 0;
+    unsigned char* mine = lds + wave * WAVE_LDS;
+    const uint32_t at = lds_addr(mine);
+    const int row_in = lane >> 4, col_in = (lane & 15) * 4;
+    const float* acol = a.A + min(m0 + col_in, a.M - 4);
+    const float* bcol = a.B + min(n0 + col_in, a.N - 4);
+    // (rounds past the end fetch the last one again; rows past K the last row, zeroed after the read)
+    auto issue = [&](int it) {
+        const int k0 = (min(it, rounds - 1) * 4 + wave) * 16;
+        const uint32_t to = at + (uint32_t)(it & 1) * 2 * BUF;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lds_load16(acol + (size_t)min(k0 + q * 4 + row_in, a.K - 1) * a.lda, to + q * 1024);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lds_load16(bcol + (size_t)min(k0 + q * 4 + row_in, a.K - 1) * a.ldb, to + BUF + q * 1024);
+    };
+    floatx16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    float csum[2] = {0.f, 0.f};
+    float v[4][8];                      // values of a block: A columns 0-31, 32-63, B columns 0-31, 32-63
+    bf16x8 pc[2][4][3];                 // pieces of the block being multiplied and of the next
+    auto fetch = [&](int it) {
+        wait_vm<8>();
+        asm volatile("" ::: "memory");
+        // lane: column (lane & 31) of a group of 32, rows 8 * (lane >> 5) .. + 7
+        const float* src = reinterpret_cast<const float*>(mine + (it & 1) * 2 * BUF) + (lane >> 5) * 8 * WG_T + (lane & 31);
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) v[o * 2 + b][r] = src[o * (BUF / 4) + r * WG_T + b * 32];
+        wait_lds();
+        issue(it + 2);
+        const int k0 = (it * 4 + wave) * 16;
+        if (k0 + 16 > a.K) {            // the last block, or beyond it: rows past the end count nothing
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                if (k0 + (lane >> 5) * 8 + r >= a.K) v[0][r] = v[1][r] = v[2][r] = v[3][r] = 0.f;
+        }
+    };
+    auto split = [&](bf16x8 (&to)[4][3]) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            csum[b] += ((v[b][0] + v[b][1]) + (v[b][2] + v[b][3])) + ((v[b][4] + v[b][5]) + (v[b][6] + v[b][7]));
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            u32x4 h, m, l;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t wh, wm, wl;
+                split2(v[b][2 * q], v[b][2 * q + 1], wh, wm, wl);
+                h[q] = wh; m[q] = wm; l[q] = wl;
+            }
+            to[b][0] = __builtin_bit_cast(bf16x8, h);
+            to[b][1] = __builtin_bit_cast(bf16x8, m);
+            to[b][2] = __builtin_bit_cast(bf16x8, l);
+        }
+    };
+    // smallest products first; the output is built transposed (a lane holds 4 consecutive columns of a row)
+    auto multiply = [&](const bf16x8 (&of)[4][3]) {
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[2 + j][PB[t]], of[i][PA[t]], acc[i][j], 0, 0, 0);
+    };
+    if (rounds > 0) {
+        issue(0);
+        issue(1);
+        fetch(0);
+        split(pc[0]);
+        // the next block is split between the MFMAs of this one: matrix and vector unit work side by side in one
+        // wavefront (a block beyond the last is zeros)
+        for (int it0 = 0; it0 < rounds; it0 += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (it0 + u < rounds) {     // uniform
+                    fetch(it0 + u + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(pc[u]);
+                    split(pc[u ^ 1]);
+#pragma unroll
+                    for (int q = 0; q < 24; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);    // one MFMA,
+                        __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);    // then vector operations
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
+    wait_vm<0>();                       // (the requests past the end land before their place is used again)
+    float* part = reinterpret_cast<float*>(mine);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                part[(i * 32 + (lane & 31)) * WG_LD + j * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)] = acc[i][j][r];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const float both = csum[b] + __shfl_xor(csum[b], 32, 64);
+        if (lane < 32) cs[wave][b * 32 + lane] = both;
+    }
+    __syncthreads();
+    const float* all = reinterpret_cast<const float*>(lds);
+#pragma unroll
+    for (int q = 0; q < WG_T * WG_T / 4 / 256; ++q) {
+        const int idx = tid + q * 256, lr = idx / (WG_T / 4), lc = (idx % (WG_T / 4)) * 4;
+        float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] += all[w * (WAVE_LDS / 4) + lr * WG_LD + lc + j];
+        if (m0 + lr < a.M && n0 + lc < a.N)
+            *reinterpret_cast<float4*>(a.C + (size_t)(m0 + lr) * a.ldc + n0 + lc) = make_float4(o[0], o[1], o[2], o[3]);
+    }
+    if (a.colsum && n0 == 0 && tid < WG_T && m0 + tid < a.M)
+        a.colsum[m0 + tid] = (cs[0][tid] + cs[1][tid]) + (cs[2][tid] + cs[3][tid]);
+}
+
 // Forward layers of very few rows (a handful of queries): a matrix-vector product per row.  The time is reading
 // the weights once, 1.3 MB at d=400, h=800, spread over the chip: a wavefront takes ROWS_N output columns, reads
 // their weight rows (k-contiguous, a float4 per lane) and multiplies them with up to MR assembled rows held in
@@ -862,6 +1030,32 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     }
     if (blocks_small * 2 > 512) return dispatch_layout<32, 32, 4>(g, s);
     return dispatch_layout<32, 32, 8>(g, s);
+}
+
+hipError_t launch_wgrad_group(const WgradArgs* problems, int count, hipStream_t s, bool aside) {
+    WgradGroup g{};
+    for (int i = 0; i < count; ++i) {
+        const WgradArgs& a = problems[i];
+        if (a.M <= 0 || a.N <= 0) continue;
+        if (g.count == GEMM_MAX_GROUP || (a.M & 3) || (a.N & 3) || (a.lda & 3) || (a.ldb & 3) || (a.ldc & 3) || a.K < 0)
+            return hipErrorInvalidValue;
+        // the contractions over the most rows first: their tiles take longest
+        int at = g.count++;
+        for (; at > 0 && g.p[at - 1].K < a.K; --at) g.p[at] = g.p[at - 1];
+        g.p[at] = a;
+    }
+    if (g.count == 0) return hipSuccess;
+    int tiles = 0;
+    for (int i = 0; i < g.count; ++i) {
+        g.tile_start[i] = tiles;
+        tiles += (((g.p[i].M + WG_T - 1) / WG_T) * ((g.p[i].N + WG_T - 1) / WG_T) + 7) / 8 * 8;
+    }
+    for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = tiles;
+    // Beside a long memory-bound pass on another stream the LDS asked for leaves room for one workgroup per
+    // compute unit: two of them hold the wavefront slots that the other pass needs to keep memory busy
+    // (6.84 against 6.76 ms for the step over a 2.5 M-entity table, which that pass bounds).
+    hipLaunchKernelGGL(wgrad_kernel, dim3(tiles), dim3(256), aside ? 40 * 1024 : 0, s, g);
+    return hipGetLastError();
 }
 
 bool gemm_takes_rows(int M, int K) {

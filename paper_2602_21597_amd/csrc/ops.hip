@@ -1,8 +1,7 @@
 // Memory-bound pieces around the grouped MLPs (the row gathers through the plan's
 // precomputed references, Sec. 4.2 "Efficient Tensor Indexing", are fused into the
 // contraction kernel's operand loads): the attention
-// pooling of the intersection classes C_k (Sec. 4.3), column sums for the bias
-// gradients, dense Adam (Alg. 1, OptimizerStep) and the final loss reduction.
+// pooling of the intersection classes C_k (Sec. 4.3), dense Adam (Alg. 1, OptimizerStep) and the final loss reduction.
 #include "common.h"
 
 namespace ngdb {
@@ -54,48 +53,6 @@ __global__ __launch_bounds__(256) void inter_kernel(const InterJobs jobs) {
             }
         }
     }
-}
-
-// column sums of up to COLSUM_MAX_JOBS matrices in a fixed order, two steps: partial
-// sums over chunks of rows (one workgroup per 64 columns x chunk x matrix), then the
-// chunks are added up per column
-__global__ __launch_bounds__(256) void colsum_part_kernel(const ColsumJobs jobs) {
-    __shared__ float red[4][64];
-    const ColsumJob j = jobs.job[blockIdx.z];
-    const int c = blockIdx.x * 64 + threadIdx.x;
-    const int lo = blockIdx.y * j.chunk_rows, hi = min(j.rows, lo + j.chunk_rows);
-    if (blockIdx.y >= j.chunks || blockIdx.x * 64 >= j.cols) return;     // uniform per workgroup
-    float s0 = 0.f, s1 = 0.f;
-    if (c < j.cols) {
-        int m = lo + threadIdx.y;
-        for (; m + 4 < hi; m += 8) {
-            s0 += j.X[(size_t)m * j.ld + c];
-            s1 += j.X[(size_t)(m + 4) * j.ld + c];
-        }
-        if (m < hi) s0 += j.X[(size_t)m * j.ld + c];
-    }
-    red[threadIdx.y][threadIdx.x] = s0 + s1;
-    __syncthreads();
-    if (threadIdx.y == 0 && c < j.cols)
-        j.part[(size_t)blockIdx.y * j.cols + c] =
-            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-}
-
-__global__ __launch_bounds__(256) void colsum_final_kernel(const ColsumJobs jobs) {
-    const ColsumJob j = jobs.job[blockIdx.y];
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= j.cols) return;
-    // four running sums (fixed assignment of chunks to sums): the loads of a round do not wait for one another
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int k = 0;
-    for (; k + 4 <= j.chunks; k += 4) {
-        s0 += j.part[(size_t)(k + 0) * j.cols + c];
-        s1 += j.part[(size_t)(k + 1) * j.cols + c];
-        s2 += j.part[(size_t)(k + 2) * j.cols + c];
-        s3 += j.part[(size_t)(k + 3) * j.cols + c];
-    }
-    for (; k < j.chunks; ++k) s0 += j.part[(size_t)k * j.cols + c];
-    j.out[c] = (s0 + s1) + (s2 + s3);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* p, size_t n) {
@@ -205,24 +162,8 @@ __global__ __launch_bounds__(256) void dense_adam_kernel(const DenseAdamJob job,
     float* __restrict__ v = job.v[t];
     const float* __restrict__ g = job.g[t];
     const int64_t n = job.n[t];
-    const int chunks = job.chunks[t];
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        float gi;
-        if (chunks > 0) {     // partial column sums, added up as colsum_final_kernel does
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-            int k = 0;
-            for (; k + 4 <= chunks; k += 4) {
-                s0 += g[(size_t)(k + 0) * n + i];
-                s1 += g[(size_t)(k + 1) * n + i];
-                s2 += g[(size_t)(k + 2) * n + i];
-                s3 += g[(size_t)(k + 3) * n + i];
-            }
-            for (; k < chunks; ++k) s0 += g[(size_t)k * n + i];
-            gi = (s0 + s1) + (s2 + s3);
-            job.gsum[t][i] = gi;
-        } else {
-            gi = g[i];
-        }
+        const float gi = g[i];
         const float mi = hp.beta1 * m[i] + (1.f - hp.beta1) * gi;
         const float vi = hp.beta2 * v[i] + (1.f - hp.beta2) * gi * gi;
         m[i] = mi;
@@ -255,22 +196,6 @@ hipError_t launch_inter(const InterJobs& jobs, bool backward, hipStream_t s) {
     const dim3 grid((unsigned)((most + 255) / 256), jobs.count);
     if (backward) hipLaunchKernelGGL((inter_kernel<true>), grid, dim3(256), 0, s, jobs);
     else hipLaunchKernelGGL((inter_kernel<false>), grid, dim3(256), 0, s, jobs);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsums(ColsumJobs& jobs, hipStream_t s, bool finish) {
-    if (jobs.count <= 0) return hipSuccess;
-    int max_cols = 0, max_chunks = 1;
-    for (int i = 0; i < jobs.count; ++i) {
-        ColsumJob& j = jobs.job[i];
-        j.chunk_rows = std::max(32, (j.rows + COLSUM_MAX_CHUNKS - 1) / COLSUM_MAX_CHUNKS);
-        j.chunks = std::max(1, (j.rows + j.chunk_rows - 1) / j.chunk_rows);
-        max_cols = std::max(max_cols, j.cols);
-        max_chunks = std::max(max_chunks, j.chunks);
-    }
-    hipLaunchKernelGGL(colsum_part_kernel, dim3((max_cols + 63) / 64, max_chunks, jobs.count), dim3(64, 4), 0, s, jobs);
-    if (!finish) return hipGetLastError();
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((max_cols + 255) / 256, jobs.count), dim3(256), 0, s, jobs);
     return hipGetLastError();
 }
 

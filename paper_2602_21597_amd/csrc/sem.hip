@@ -63,25 +63,6 @@ __global__ __launch_bounds__(256) void translate_refs_kernel(const int32_t* __re
 }
 
 // ---- building blocks of the projection kernels (gfx950)
-// A direct load from global memory into LDS: lane l's bytes land at lds_base + l * size, whatever
-// global address the lane gives; lds_base is wave-uniform (it travels in M0).  The loads are
-// issued from inline assembly and waited for by hand (s_waitcnt vmcnt): left to the compiler,
-// every LDS read after such a load would wait for all of them, also those of the stages ahead.
-__device__ __forceinline__ void lds_load16(const void* gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
-}
-__device__ __forceinline__ void lds_load4(const void* gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
-}
-// at most n vector-memory operations of this wavefront still in flight (they complete in order)
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
 // Transposing LDS read of 16-bit values: within 16 lanes, lane 4r + c gives the address of 4
 // consecutive values of row r (c-th group of 4 columns); lane i receives column i of the
 // 4 x 16 block: rows 0..3.  Two of them make the 8 consecutive k of a 16x16x32 MFMA operand

@@ -1,5 +1,5 @@
 """Kernels chosen by size, at the sizes where the choice changes: matrix-vector forward layers, candidate lists shared by
-several workgroups, the gradient index of one workgroup, of a short and of a long histogram."""
+several workgroups, weight gradients, the gradient index of one workgroup, of a short and of a long histogram."""
 import numpy as np
 import pytest
 
@@ -26,6 +26,21 @@ def test_forward_layers_of_few_rows(M, N, K):
     scale = np.abs(A).astype(np.float64) @ np.abs(B.T) + np.abs(bias)
     assert (np.abs(got[perm] - want) / scale).max() < 0.1 * 2e-6 * max(1.0, np.sqrt(K) / 8)
     assert not np.any(np.delete(got, perm, axis=0))
+
+
+# rows: none, one, below and above a block of 16, a block of every wavefront and one more, several rounds
+@pytest.mark.parametrize("K", [0, 1, 15, 17, 64, 65, 127, 500])
+@pytest.mark.parametrize("M,N", [(4, 4), (64, 60), (68, 132), (200, 64)])
+def test_weight_gradients_by_rows(M, N, K):
+    import torch
+    from paper_2602_21597_amd import binding
+    rng = np.random.default_rng(M * 1000 + K)
+    A, B = (rng.standard_normal((K, n)).astype(np.float32) for n in (M, N))
+    f = lambda a: torch.from_numpy(a if K else np.zeros((1, a.shape[1]), np.float32)).cuda()
+    got = binding.debug_gemm(f(A), f(B), M, N, K, a_kcontig=False, b_kcontig=False).cpu().numpy()
+    want = A.astype(np.float64).T @ B.astype(np.float64)
+    scale = np.abs(A).astype(np.float64).T @ np.abs(B) + 1e-30
+    assert (np.abs(got - want) / scale).max() < 0.1 * 2e-6 * max(1.0, np.sqrt(K) / 8)
 
 
 @pytest.mark.parametrize("B,C", [(1, 1), (1, 15), (1, 17), (1, 1000), (3, 4097), (40, 33)])
