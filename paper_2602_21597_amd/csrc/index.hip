@@ -147,8 +147,18 @@ constexpr int MID_TILES = 256;
 __global__ __launch_bounds__(SCAN_THREADS) void scan_rows_kernel(const int32_t* __restrict__ hist, int n_tiles,
                                                                  int32_t* __restrict__ offs) {
     const int digit = blockIdx.x, t = threadIdx.x;
+    // 16 bytes a lane, eight loads on the way (one 4-byte load after the other: 18 us at 66 tiles, 33 at 128)
     int32_t before = 0;
-    for (int i = t; i < digit * n_tiles; i += SCAN_THREADS) before += hist[i];
+    const int n_before = digit * n_tiles, n4 = n_before >> 2;
+    const int4* h4 = reinterpret_cast<const int4*>(hist);
+    for (int i = t; i < n4; i += 8 * SCAN_THREADS) {
+        int4 x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = h4[min(i + j * SCAN_THREADS, n4 - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) before += i + j * SCAN_THREADS < n4 ? (x[j].x + x[j].y) + (x[j].z + x[j].w) : 0;
+    }
+    if (t < (n_before & 3)) before += hist[n4 * 4 + t];
     int32_t base, row;
     block_exclusive_scan(before, &base);
     const int32_t v = t < n_tiles ? hist[(size_t)digit * n_tiles + t] : 0;
