@@ -100,6 +100,7 @@ struct ngdb_ctx_s {
     // contribution's entity in that list, operator references redirected to it, bf16 row gradients,
     // split-wise partial sums and the gradient of Wp, fused rows of one ranking chunk
     DevBuf Wb, Ef, inv, refs_sem, g_bf16, wp_partial, gWp, rank_ef;
+    DevBuf later;       // touched entity rows that wait for the backward pass (positions in uniq)
     // box family: offsets and their gradients by slot (act / dact hold the centres), per-input
     // outputs of the offset MLP with their gradients, direct gradient of the inputs' offsets,
     // compact gradient of Ro.  The offset MLP (V1 c1 V2 c2) uses the Z/H/dH buffers of index T_NEG.
@@ -238,8 +239,6 @@ int gslot_of(int t) { return t == T_PROJ ? 0 : (t == T_NEG ? 4 : 8); }
 struct FwdBytes;
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim);
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
-int upload_plan(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s);
-
 // bytes of the split weights: per type two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
 size_t weight_pieces_bytes(const ngdb_ctx_t* c) {
     if (c->cfg.family != NGDB_FAMILY_VEC) return 0;
@@ -279,31 +278,58 @@ void take_hidden_pieces(const HiddenPieces& hpc, GemmArgs* second, int n) {
     for (int i = 0; i < n; ++i) { second[i].a_pieces = hpc.at[i]; second[i].a_kt = hpc.kt; }
 }
 
-// Splits the weights of the three MLPs for this pass (one launch).  Without the buffer (a context
+// Splits the weights of the three MLPs for a pass.  Without the buffer (a context
 // that never sized a workspace) the contractions split their B operands themselves.
-int make_weight_pieces(ngdb_ctx_t* c, hipStream_t s) {
+void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, PieceJobs* J) {
     c->have_pieces = false;
-    if (c->cfg.family != NGDB_FAMILY_VEC || c->w_pieces.cap < weight_pieces_bytes(c) || !c->w_pieces.p) return NGDB_OK;
+    if (c->cfg.family != NGDB_FAMILY_VEC || c->w_pieces.cap < weight_pieces_bytes(c) || !c->w_pieces.p) return;
     const int d = c->cfg.d, h = c->cfg.h;
-    if ((d & 3) || (h & 3)) return NGDB_OK;   // the split reads rows as float4
-    if (d < 128 && h < 128) return NGDB_OK;   // no contraction of these widths takes the split route
+    if ((d & 3) || (h & 3)) return;   // the split reads rows as float4
+    if (d < 128 && h < 128) return;   // no contraction of these widths takes the split route
+    bool narrow = true;      // every launch of the pass has a few rows only
+    for (const std::vector<Segment>& segs : pl->levels)
+        for (const Segment& sg : segs) narrow = narrow && gemm_takes_rows(sg.rows, std::max(d, h));
+    if (narrow) return;
     uint16_t* at = ptr<uint16_t>(c->w_pieces);
-    PieceJobs J{};
     for (int t = 0; t < 3; ++t) {
         const MlpRefs W = mlp_of(c->prm, t);
         // Wa [h][d]: rows as n = forward operand of H = X Wa^T; columns as n = backward operand of dZ = dH Wa
-        PieceJob& ja = J.job[J.count++];
+        PieceJob& ja = J->job[J->count++];
         ja.W = W.Wa; ja.R = h; ja.C = d;
         c->wp[t][0] = ja.out_rk = at; at += pieces_elems(h, d);
         c->wp[t][3] = ja.out_ck = at; at += pieces_elems(d, h);
         // Wb [d][h]: rows as n = forward operand of Y = H Wb^T; columns as n = backward operand of dH = dY Wb
-        PieceJob& jw = J.job[J.count++];
+        PieceJob& jw = J->job[J->count++];
         jw.W = W.Wb; jw.R = d; jw.C = h;
         c->wp[t][1] = jw.out_rk = at; at += pieces_elems(d, h);
         c->wp[t][2] = jw.out_ck = at; at += pieces_elems(h, d);
     }
-    HIPCHK(c, launch_weight_pieces(J, s));
     c->have_pieces = true;
+}
+
+// The first launch of a pass: the plan to the device and the weights as pieces.
+// A plan of ordinary size reaches the device with the first call that uses it: workgroups of this launch
+// read the staging buffer (120 KB: 5 us as a launch of its own), which needs neither a wait on the host (10 us) nor an
+// event between streams (9 us of host time).  Large ones are copied when they are planned.
+constexpr size_t PLAN_INLINE_BYTES = 256 << 10;
+int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
+    PieceJobs J{};
+    if (!pl->uploaded) {
+        J.copy_dst = reinterpret_cast<float4*>(pl->blob.dev);
+        J.copy_src = reinterpret_cast<const float4*>(pl->blob.pinned);
+        J.copy_n = (int)(pl->blob_bytes / 16);
+    }
+    add_weight_pieces(c, pl, &J);
+    {
+        Timed tm(c, NGDB_TK_GEMM_FWD, s);
+        HIPCHK(c, launch_weight_pieces(J, s));
+    }
+    if (!pl->uploaded) {
+        // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        HIPCHK(c, hipStreamIsCapturing(s, &st));
+        if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
+    }
     return NGDB_OK;
 }
 
@@ -356,7 +382,8 @@ int size_workspace(ngdb_ctx_t* c, const ngdb_plan_t* pl, int K, bool want_table_
     ENS(c->seg_off, ((size_t)nk + 1) * 4);
     ENS(c->hist, index_hist_elems(nk) * 4);
     ENS(c->scan_tmp, index_scan_tmp_elems(nk) * 4);
-    ENS(c->n_uniq, 256);
+    ENS(c->n_uniq, 256);       // count, and the number of rows in `later`
+    ENS(c->later, (size_t)hp.n_anchor * 4);
     if (!c->gW.p) {
         size_t off = 0;
         for (int t = 0; t < 3; ++t) {
@@ -622,15 +649,6 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
 int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hipStream_t s, const FwdSpace& w) {
     if (c->cfg.family == NGDB_FAMILY_BOX) return enqueue_forward_box(c, pl, s);   // (always on the context's buffers)
     const int d = c->cfg.d, h = c->cfg.h;
-    c->have_pieces = false;
-    bool narrow = true;      // every launch of the pass has a few rows only
-    for (const std::vector<Segment>& segs : pl->levels)
-        for (const Segment& sg : segs) narrow = narrow && gemm_takes_rows(sg.rows, std::max(d, h));
-    if (!narrow) {
-        Timed tm(c, NGDB_TK_GEMM_FWD, s);
-        int rc_p = make_weight_pieces(c, s);
-        if (rc_p != NGDB_OK) return rc_p;
-    }
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         GemmArgs g1[3], g2[3];
@@ -863,7 +881,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         return fail(c, NGDB_ERR_ARG, "batch beyond the maxima declared at ngdb_create (b_max_queries, k_max)");
     c->have_grads = false;
     int rc = size_workspace(c, pl, K, !apply);
-    if (rc == NGDB_OK) rc = upload_plan(c, pl, stream);
+    if (rc == NGDB_OK) rc = begin_pass(c, pl, stream);
     if (rc != NGDB_OK) return rc;
 
     // 1. entity gradient index (depends only on the plan and the negatives)
@@ -903,42 +921,22 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         HIPCHK(c, e);
     }
 
-    // The records of the table pass (and the sum of the loss terms, in the same launch) depend on
-    // the scoring pass only.  In a large step, where the table pass on the library stream ends the
-    // step, they are resolved beside the backward pass; in a small step the extra fork costs more
-    // than the launch it hides.
+    // 4. entity rows whose contributions are (query, candidate) pairs only need nothing of the backward pass: with a
+    // library stream they are updated beside it, and only the rows that anchors refer to are left to the end of the
+    // step.  (All rows after the backward pass, beside the weight gradients: 307 against 290 us a step at 512 queries over
+    // 15 000 entities, 507 against 457 at 1024 over 63 000, 6.64 against 6.46 ms at 4096 over 2.5 million.)
     hipStream_t s_tab = aside ? c->side[0] : stream;     // after the index on the same stream
     const int64_t n_contrib = (int64_t)hp.n_anchor + B + (int64_t)B * K;
-    const bool small_step = std::min<int64_t>(n_contrib, c->cfg.n_entities) <= 65536;
-    const bool resolve_early = aside && !small_step;
-    auto resolve_records = [&]() -> int {
-        HIPCHK(c, launch_resolve(e_src, n_contrib, hp.n_anchor, hp.n_slots, B, K, ptr<float>(c->coef),
-                                 sem ? nullptr : ptr<int32_t>(c->win), ptr<float>(c->rec_coef), ptr<int32_t>(c->rec_row),
-                                 ptr<float>(c->loss_terms), B > 0 ? 1.f / (2.f * B) : 0.f, d_loss, s_tab));
-        return NGDB_OK;
-    };
-    if (resolve_early) {
-        HIPCHK(c, hipEventRecord(c->ev_fork, stream));
-        HIPCHK(c, hipStreamWaitEvent(s_tab, c->ev_fork, 0));
-        if ((rc = resolve_records()) != NGDB_OK) return rc;
-    }
-
-    // 4. reversed frontiers
-    WgradJob wj;
-    rc = enqueue_backward(c, pl, stream, &wj);
-    if (rc != NGDB_OK) return rc;
-
-    // 5. table gradients (+ Adam), dense Adam
+    const int64_t max_rows = std::min<int64_t>(n_contrib, c->cfg.n_entities);
+    // A pass that ends before the backward pass does even on few wavefronts is kept to few of them: at full width it
+    // takes the compute units and caches from the launches that the step waits for.  Estimates in us: three rows read
+    // and written at 2.7 TB/s by one workgroup per compute unit, against a chain of launches and its contractions.
+    const double mlp_rows = (double)hp.n_proj + (box ? 2.0 : 1.0) * hp.n_int_rows + hp.n_neg;
+    const bool short_pass = aside ? 24.0 * max_rows * d / 2.7e6 <= 100.0 + 12.0 * c->cfg.h * d * mlp_rows / 1e8 : max_rows <= 65536;
     const int64_t t = c->step + 1;
-    AdamHyper ah{c->cfg.lr, c->cfg.beta1, c->cfg.beta2, c->cfg.eps,
-                 (float)(1.0 - std::pow((double)c->cfg.beta1, (double)t)),
-                 (float)(1.0 - std::pow((double)c->cfg.beta2, (double)t))};
-    if (aside) {
-        HIPCHK(c, hipEventRecord(c->ev_fork, stream));
-        HIPCHK(c, hipStreamWaitEvent(s_tab, c->ev_fork, 0));
-    }
-    // (the sum of the loss terms is off the critical path there, in the launch that resolves the records)
-    if (!resolve_early && (rc = resolve_records()) != NGDB_OK) return rc;
+    const AdamHyper ah{c->cfg.lr, c->cfg.beta1, c->cfg.beta2, c->cfg.eps,
+                       (float)(1.0 - std::pow((double)c->cfg.beta1, (double)t)),
+                       (float)(1.0 - std::pow((double)c->cfg.beta2, (double)t))};
     TableArgs te{};
     te.P = c->prm.E.p; te.Mo = c->prm.E.m; te.Vo = c->prm.E.v;
     te.uniq = ptr<int32_t>(c->uniq); te.seg_off = ptr<int32_t>(c->seg_off);
@@ -947,39 +945,55 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     te.dact = ptr<float>(c->dact); te.act = ptr<float>(c->act); te.g_out = apply ? nullptr : ptr<float>(c->gE);
     if (sem) { te.mask = c->mask.p; te.g_bf16 = ptr<uint16_t>(c->g_bf16); }
     TableArgs tr = te;
-    // parameters + two moments beyond what the 256 MB last-level cache could keep between steps
-    te.streaming = (size_t)c->cfg.n_entities * d * 3 * sizeof(float) > ((size_t)512 << 20);
+    // parameters + two moments beyond what the 256 MB last-level cache could keep between steps (300 MB of them: 489
+    // against 463 us a step; 72 MB: 304 with the hint against 296)
+    te.streaming = (size_t)c->cfg.n_entities * d * 3 * sizeof(float) > ((size_t)256 << 20);
     if (c->cfg.score_bf16) te.shadow = ptr<uint16_t>(c->Eb);   // signs against the rounded rows; written only when updating
     if (box) { te.off = ptr<float>(c->off); te.alpha = c->cfg.box_alpha; }
+    // the sum of the loss terms rides in the launch that resolves the records
+    auto resolve_records = [&]() -> int {
+        HIPCHK(c, launch_resolve(e_src, n_contrib, hp.n_anchor, hp.n_slots, B, K, ptr<float>(c->coef),
+                                 sem ? nullptr : ptr<int32_t>(c->win), ptr<float>(c->rec_coef), ptr<int32_t>(c->rec_row),
+                                 ptr<float>(c->loss_terms), B > 0 ? 1.f / (2.f * B) : 0.f, d_loss, s_tab));
+        return NGDB_OK;
+    };
+    if (aside) {
+        HIPCHK(c, hipEventRecord(c->ev_fork, stream));
+        HIPCHK(c, hipStreamWaitEvent(s_tab, c->ev_fork, 0));
+        if ((rc = resolve_records()) != NGDB_OK) return rc;
+        te.later = ptr<int32_t>(c->later); te.n_later = ptr<int32_t>(c->n_uniq) + 1;
+        {
+            Timed tm(c, NGDB_TK_TABLE_E, s_tab);
+            HIPCHK(c, launch_table_update(te, ah, short_pass, s_tab));
+        }
+        HIPCHK(c, hipEventRecord(c->ev_join, s_tab));
+        te.pick = te.later; te.n_uniq_dev = te.n_later;
+        te.later = te.n_later = nullptr;
+    }
+
+    // 5. reversed frontiers, weight gradients
+    WgradJob wj;
+    rc = enqueue_backward(c, pl, stream, &wj);
+    if (rc != NGDB_OK) return rc;
+
+    rc = enqueue_weight_grads(c, wj, stream, aside && !short_pass);
+    if (rc != NGDB_OK) return rc;
+
+    // 6. the other table rows, relation tables, dense Adam
+    if (!aside && (rc = resolve_records()) != NGDB_OK) return rc;
     tr.g_bf16 = nullptr; tr.mask = nullptr;
     tr.P = c->prm.R.p; tr.Mo = c->prm.R.m; tr.Vo = c->prm.R.v;
     tr.uniq = pl->d_r_uniq; tr.seg_off = pl->d_r_seg_off; tr.n_uniq_dev = pl->d_n_r_uniq;
     tr.rec_coef = nullptr; tr.rec_row = pl->d_r_rec; tr.g_out = apply ? nullptr : ptr<float>(c->gR);
-    // in a small step the relation tables ride in the entity table's launch (a launch of their own
-    // each would add its latency to the tail of the step)
     TableArgs small[2] = {tr, tr};
     int n_small = 1;
-    small[0].shadow = nullptr; small[0].off = nullptr;
     if (box) {   // relation offsets: the same segments over the offset gradients, gated by relu
         TableArgs& to = small[n_small++];
-        to = small[0];
         to.P = c->prm.Ro.p; to.Mo = c->prm.Ro.m; to.Vo = c->prm.Ro.v;
         to.dact = ptr<float>(c->doff); to.relu_gate = true; to.g_out = apply ? nullptr : ptr<float>(c->gRo);
     }
-    if (small_step) {   // one launch for all tables
-        Timed tm(c, NGDB_TK_TABLE_E, s_tab);
-        HIPCHK(c, launch_table_update(te, ah, s_tab, small, n_small, c->cfg.n_relations));
-    } else {
-        { Timed tm(c, NGDB_TK_TABLE_E, s_tab); HIPCHK(c, launch_table_update(te, ah, s_tab)); }
-        for (int k = 0; k < n_small; ++k) {
-            Timed tm(c, NGDB_TK_TABLE_R, s_tab);
-            HIPCHK(c, launch_table_update(small[k], ah, s_tab));
-        }
-    }
-    rc = enqueue_weight_grads(c, wj, stream, aside && !small_step);
-    if (rc != NGDB_OK) return rc;
+    DenseAdamJob job{};
     if (apply) {
-        DenseAdamJob job{};
         const ngdb_tensor* ts[12] = {&c->prm.W1, &c->prm.b1, &c->prm.W2, &c->prm.b2, &c->prm.V1, &c->prm.c1,
                                      &c->prm.V2, &c->prm.c2, &c->prm.U1, &c->prm.u1, &c->prm.U2, &c->prm.u2};
         const int64_t hd = (int64_t)c->cfg.h * d;
@@ -990,12 +1004,21 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
             job.g[k] = ptr<float>(c->gW) + c->gw_off[i];
             job.n[k] = sz[i % 4];
         }
+    }
+    if (!short_pass) {    // the passes that run long on their own: not in the launch that ends the step
+        if (!aside) {
+            Timed tm(c, NGDB_TK_TABLE_E, stream);
+            HIPCHK(c, launch_table_update(te, ah, false, stream));
+        }
         Timed tm(c, NGDB_TK_ADAM, stream);
         HIPCHK(c, launch_dense_adam(job, ah, stream));
+        job.count = 0;
     }
-    if (aside) {
-        HIPCHK(c, hipEventRecord(c->ev_join, s_tab));
-        HIPCHK(c, hipStreamWaitEvent(stream, c->ev_join, 0));
+    if (aside) HIPCHK(c, hipStreamWaitEvent(stream, c->ev_join, 0));
+    {
+        Timed tm(c, short_pass ? NGDB_TK_ADAM : NGDB_TK_TABLE_R, stream);
+        const int64_t left = aside ? std::min<int64_t>(hp.n_anchor, max_rows) : (short_pass ? max_rows : 0);
+        HIPCHK(c, launch_step_tail(te, left, small, n_small, c->cfg.n_relations, job, ah, stream));
     }
     if (sem) {
         // gradient of the text projection over the touched rows, then its Adam step
@@ -1042,20 +1065,6 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     gv.pair_score = ptr<float>(c->score);
     gv.loss_terms = ptr<float>(c->loss_terms);
     c->have_grads = true;
-    return NGDB_OK;
-}
-
-// A plan of ordinary size reaches the device with the first call that uses it: a small kernel on that call's
-// stream reads the staging buffer (120 KB: 5 us), which needs neither a wait on the host (10 us) nor an
-// event between streams (9 us of host time).  Large ones are copied when they are planned.
-constexpr size_t PLAN_INLINE_BYTES = 256 << 10;
-int upload_plan(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
-    if (pl->uploaded) return NGDB_OK;
-    HIPCHK(c, launch_copy(pl->blob.dev, pl->blob.pinned, pl->blob_bytes, s));
-    // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    HIPCHK(c, hipStreamIsCapturing(s, &st));
-    if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
     return NGDB_OK;
 }
 
@@ -1306,8 +1315,10 @@ int ngdb_create(const ngdb_config* cfg, ngdb_ctx_t** out) {
     c->n_side = cfg->num_streams > 1 ? 1 : 0;
     bool ok = true;
     if (c->n_side) ok = hipStreamCreateWithFlags(&c->side[0], hipStreamNonBlocking) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess;
+    // (they order work of this GPU only: no fence towards the host, 2 us of a launch queue and of host time each)
+    const unsigned ev_flags = hipEventDisableTiming | hipEventDisableSystemFence;
+    ok = ok && hipEventCreateWithFlags(&c->ev_join, ev_flags) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&c->ev_fork, ev_flags) == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->upload, hipStreamNonBlocking) == hipSuccess;
     unsigned char* sp = nullptr;
     ok = ok && noalloc_scratch(&sp) == hipSuccess;     // address of the static scratch on this GPU
@@ -1334,7 +1345,7 @@ void ngdb_destroy(ngdb_ctx_t* c) {
                      &c->loss_terms, &c->rec_coef, &c->rec_row, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->hist, &c->scan_tmp,
                      &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
                      &c->Wb, &c->Ef, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
-                     &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb};
+                     &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb, &c->later};
     for (DevBuf* b : all) release(*b);
     if (c->side[0]) (void)hipStreamDestroy(c->side[0]);
     if (c->ev_join) (void)hipEventDestroy(c->ev_join);
@@ -1639,7 +1650,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     if (c->presized && d_cand && C > c->cfg.k_max)
         return fail(c, NGDB_ERR_ARG, "more candidates per query than the k_max declared at ngdb_create");
     int rc = reclaim ? size_forward_only(c, pl, n_tail) : size_workspace(c, pl, d_cand ? C : 0, false);
-    if (rc == NGDB_OK) rc = upload_plan(c, pl, s);
+    if (rc == NGDB_OK) rc = begin_pass(c, pl, s);
     if (rc != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, d_cand};
@@ -1719,7 +1730,7 @@ int ngdb_score_noalloc(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ca
     const uint32_t timing = c->timing_mask;     // event brackets would create events: off for this call
     c->timing_mask = 0;
     const EntRows er{c->prm.E.p, pl->d_f_in_ref, pl->d_pos, d_cand};
-    int rc = upload_plan(c, pl, s);
+    int rc = begin_pass(c, pl, s);
     if (rc == NGDB_OK) rc = enqueue_forward(c, pl, er, s, w);
     if (rc == NGDB_OK) {
         ScoreArgs sa{};
@@ -1751,7 +1762,7 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     c->have_grads = false;
     const bool reclaim = c->cfg.family == NGDB_FAMILY_VEC;     // as in ngdb_score
     int rc = reclaim ? size_forward_only(c, pl, 0) : size_workspace(c, pl, 0, false);
-    if (rc == NGDB_OK) rc = upload_plan(c, pl, s);
+    if (rc == NGDB_OK) rc = begin_pass(c, pl, s);
     if (rc != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, nullptr};

@@ -191,6 +191,10 @@ struct PieceJobs {
     int count;
     PieceJob job[PIECE_MAX_JOBS];
     int block0[PIECE_MAX_JOBS + 1];
+    // and copy_n x 16 bytes from copy_src to copy_dst (a plan, from host memory) by the first copy_blocks workgroups
+    float4* copy_dst;
+    const float4* copy_src;
+    int copy_n, copy_blocks;
 };
 inline size_t pieces_elems(int N, int K) { return (size_t)((N + 31) / 32) * ((K + 15) / 16) * 1536; }
 hipError_t launch_weight_pieces(PieceJobs& jobs, hipStream_t s);
@@ -259,6 +263,24 @@ struct DenseAdamJob {
     int64_t n[13];
     int count;
 };
+#ifdef __HIPCC__
+// one tensor by the threads start, start + stride, ...
+__device__ __forceinline__ void dense_adam(const DenseAdamJob& job, int t, const AdamHyper& hp, int64_t start, int64_t stride) {
+    float* __restrict__ p = job.p[t];
+    float* __restrict__ m = job.m[t];
+    float* __restrict__ v = job.v[t];
+    const float* __restrict__ g = job.g[t];
+    const int64_t n = job.n[t];
+    for (int64_t i = start; i < n; i += stride) {
+        const float gi = g[i];
+        const float mi = hp.beta1 * m[i] + (1.f - hp.beta1) * gi;
+        const float vi = hp.beta2 * v[i] + (1.f - hp.beta2) * gi * gi;
+        m[i] = mi;
+        v[i] = vi;
+        p[i] -= hp.lr * (mi / hp.bc1) / (sqrtf(vi / hp.bc2) + hp.eps);
+    }
+}
+#endif
 hipError_t launch_dense_adam(const DenseAdamJob& job, const AdamHyper& hp, hipStream_t s);
 // loss[0] = scale * sum_i terms[i]
 hipError_t launch_loss_reduce(const float* terms, int n, float scale, float* loss, hipStream_t s);
@@ -413,6 +435,12 @@ struct TableArgs {
     float alpha = 0.f;
     // the row's gradient is multiplied by [table row > 0] (a table that is used through relu)
     bool relu_gate = false;
+    // A pass over the rows that do not wait for the backward pass (`later` set): rows whose first record is a gradient
+    // row are left out, their positions in uniq appended to later (*n_later of them, zero before).  The pass over
+    // those (`pick` set): the positions pick[0..*n_uniq_dev).
+    int32_t* later = nullptr;
+    int32_t* n_later = nullptr;
+    const int32_t* pick = nullptr;
     // bf16 copy of the table [rows, d] that the scoring pass reads: pair signs are taken against
     // the rounded row, and the updated row is rounded into the copy
     uint16_t* shadow = nullptr;
@@ -427,16 +455,19 @@ struct TableArgs {
 hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_base, int B, int K, const float* coef,
                           const int32_t* win, float* rec_coef, int32_t* rec_row, const float* loss_terms,
                           float loss_scale, float* loss, hipStream_t s);
-// Up to two small plain tables of the same width (no text features, box weights or bf16 copy: the
-// relation tables), updated by extra workgroups of the main table's launch (meant for small steps).
+// few: by one workgroup per compute unit (a pass that has time and should leave the chip to others)
+hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, hipStream_t s);
+// The end of a step in one launch: the main table (at most max_rows touched rows; 0: not part of it), up to two small
+// plain tables of the same width (no text features, box weights or bf16 copy: the relation tables, each of at most
+// small_rows touched rows), and the dense tensors.
 struct TableTail {
-    int main_blocks;
+    int main_blocks, dense_blocks;     // dense_blocks: of every tensor
     int blocks[2];
     TableArgs job[2];
+    DenseAdamJob dense;
 };
-// small[0..n_small): such tables, each of at most small_rows touched rows.
-hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, hipStream_t s, const TableArgs* small = nullptr,
-                               int n_small = 0, int small_rows = 0);
+hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArgs* small, int n_small, int small_rows,
+                            const DenseAdamJob& dense, const AdamHyper& hp, hipStream_t s);
 
 // ---------------------------------------------------------------- text-feature fusion (sem.hip)
 hipError_t launch_cast_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t s);

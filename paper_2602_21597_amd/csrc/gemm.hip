@@ -238,15 +238,20 @@ constexpr int WTILE = 3 * 512;            // bf16 values of one tile
 // (four tiles along k) and B[n = column][k = row] (two tile rows x two k-tiles).
 __global__ __launch_bounds__(256) void weight_pieces_kernel(const PieceJobs J) {
     __shared__ float blk[32][65];
+    if ((int)blockIdx.x < J.copy_blocks) {
+        for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < J.copy_n; i += J.copy_blocks * 256) J.copy_dst[i] = J.copy_src[i];
+        return;
+    }
+    const int block = (int)blockIdx.x - J.copy_blocks;
     int j = 0;
 #pragma unroll
     for (int i = 1; i < PIECE_MAX_JOBS; ++i)
-        if (i < J.count && (int)blockIdx.x >= J.block0[i]) j = i;
+        if (i < J.count && block >= J.block0[i]) j = i;
     PieceJob jb = J.job[0];
 #pragma unroll
     for (int i = 1; i < PIECE_MAX_JOBS; ++i)
         if (i == j) jb = J.job[i];
-    const int b = (int)blockIdx.x - J.block0[j];
+    const int b = block - J.block0[j];
     const int cblocks = (jb.C + 63) / 64;
     const int r0 = (b / cblocks) * 32, c0 = (b % cblocks) * 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1067,8 +1072,8 @@ bool gemm_takes_rows(int M, int K) {
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) { return launch_gemm_group(&a, 1, s, nullptr); }
 
 hipError_t launch_weight_pieces(PieceJobs& J, hipStream_t s) {
-    if (J.count <= 0) return hipSuccess;
-    if (J.count > PIECE_MAX_JOBS) return hipErrorInvalidValue;
+    if (J.count <= 0 && J.copy_n <= 0) return hipSuccess;
+    if (J.count > PIECE_MAX_JOBS || J.copy_n < 0) return hipErrorInvalidValue;
     int blocks = 0;
     for (int i = 0; i < J.count; ++i) {
         if ((J.job[i].C & 3) || J.job[i].R <= 0 || J.job[i].C <= 0) return hipErrorInvalidValue;
@@ -1076,7 +1081,8 @@ hipError_t launch_weight_pieces(PieceJobs& J, hipStream_t s) {
         blocks += ((J.job[i].R + 31) / 32) * ((J.job[i].C + 63) / 64);
     }
     J.block0[J.count] = blocks;
-    hipLaunchKernelGGL(weight_pieces_kernel, dim3(blocks), dim3(256), 0, s, J);
+    J.copy_blocks = std::min((J.copy_n + 255) / 256, 256);
+    hipLaunchKernelGGL(weight_pieces_kernel, dim3(blocks + J.copy_blocks), dim3(256), 0, s, J);
     return hipGetLastError();
 }
 

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_top_kernel(int32_t* __restr
         if (i < m) sums[i] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0 && total) *total = carry;
+    if (threadIdx.x == 0 && total) total[0] = carry, total[1] = 0;
 }
 
 // HEADS=false: out[i] = exclusive prefix.  HEADS=true: for every head position i
@@ -188,7 +188,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void heads_kernel(const int32_t* __re
     all = base + tot;
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         seg_off[all] = (int32_t)n;
-        *n_uniq = all;
+        n_uniq[0] = all;
+        n_uniq[1] = 0;
     }
 }
 
@@ -353,7 +354,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_index_kernel(const int32_
     }
     if (t == 0) {
         seg_off[done] = n;
-        *n_uniq = done;
+        n_uniq[0] = done;
+        n_uniq[1] = 0;
     }
 }
 

@@ -156,20 +156,7 @@ __global__ __launch_bounds__(256) void update_rows_kernel(float* __restrict__ ta
 }
 
 __global__ __launch_bounds__(256) void dense_adam_kernel(const DenseAdamJob job, const AdamHyper hp) {
-    const int t = blockIdx.y;
-    float* __restrict__ p = job.p[t];
-    float* __restrict__ m = job.m[t];
-    float* __restrict__ v = job.v[t];
-    const float* __restrict__ g = job.g[t];
-    const int64_t n = job.n[t];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = hp.beta1 * m[i] + (1.f - hp.beta1) * gi;
-        const float vi = hp.beta2 * v[i] + (1.f - hp.beta2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        p[i] -= hp.lr * (mi / hp.bc1) / (sqrtf(vi / hp.bc2) + hp.eps);
-    }
+    dense_adam(job, blockIdx.y, hp, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 __global__ __launch_bounds__(256) void loss_reduce_kernel(const float* __restrict__ terms, int n, float scale,

@@ -108,7 +108,8 @@ __device__ __forceinline__ void row_store(float4* p, float4 v) {
 // UPD: the pass applies Adam (known when the kernel is chosen; otherwise a.g_out decides at run time).
 // With the choice open, the stores of either path count as "maybe issued" for the compiler, and the
 // wait for the next row's parameter rows, requested before them, also waits for the stores.
-template <int NCH, bool SEM, bool BOX, bool SH, bool NT = false, bool UPD = false>
+// PICK: a.pick may choose the rows; otherwise a.later may leave some out.
+template <int NCH, bool SEM, bool BOX, bool SH, bool NT = false, bool UPD = false, bool PICK = false>
 __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& hp, int wave_global, int n_waves) {
     const int lane = threadIdx.x & 63;
     const int d4 = a.d >> 2;
@@ -116,6 +117,14 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
     const bool update = UPD || a.g_out == nullptr;
     const float step1 = hp.lr / hp.bc1, ibc2 = 1.f / hp.bc2;   // lr / (1 - beta1^t), 1 / (1 - beta2^t): once per wavefront
+    // Stores without a lane condition (plain rows of tables that stay in the caches): the lanes
+    // past the end of the row hold, through their clamped loads, the values of its last four
+    // coordinates and write those once more.  Under a condition the stores may or may not be
+    // issued as far as the compiler can tell, and the next row's wait for its parameter rows,
+    // requested before them, becomes a wait for the stores too.  (With text features the sign
+    // codes of those lanes are not the last column's; tables streamed from HBM are faster with
+    // that wait: 4.32 against 4.49 ms at 2 M touched rows.)
+    constexpr bool ALL_LANES = !SEM && !NT;
     bool col_ok[NCH];
     int colc[NCH];
 #pragma unroll
@@ -128,17 +137,19 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
     // during the walk over the current segment, its parameter and moment rows before the update
     // arithmetic and the stores of the current row (the registers of the segment walk are free
     // then).  Past the last row the requests repeat it and are not used.
-    int32_t row_n = 0;
-    int t0_n = 0, t1_n = 0;
+    int32_t row_n = 0, first_n = 0;
+    int t0_n = 0, t1_n = 0, u_n = 0;
     float4 p_n[NCH], m_n[NCH], v_n[NCH];
 #define NGDB_FETCH_INDEX(uu)                                   \
     do {                                                       \
-        const int uc = min((uu), n_uniq - 1);                  \
-        row_n = a.uniq[uc];                                    \
-        t0_n = a.seg_off[uc];                                  \
-        t1_n = a.seg_off[uc + 1];                              \
+        u_n = min((uu), n_uniq - 1);                           \
+        if (PICK && a.pick) u_n = a.pick[u_n];                 \
+        row_n = a.uniq[u_n];                                   \
+        t0_n = a.seg_off[u_n];                                 \
+        t1_n = a.seg_off[u_n + 1];                             \
     } while (0)
 #define NGDB_FETCH_ROWS()                                                                                      \
+    if (!PICK && a.later) first_n = a.rec_row[t0_n];                                                           \
     _Pragma("unroll") for (int ch = 0; ch < NCH; ++ch) {                                                      \
         if (update || !SEM) p_n[ch] = row_load<NT>(reinterpret_cast<const float4*>(a.P + (size_t)row_n * a.d) + colc[ch]); \
         if (update) {                                                                                          \
@@ -150,9 +161,17 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
         NGDB_FETCH_INDEX(wave_global);
         NGDB_FETCH_ROWS()
     }
-    for (int u = wave_global; u < n_uniq; u += n_waves) {
+    for (int i = wave_global; i < n_uniq; i += n_waves) {
+        const int u = u_n;
+        const bool skip = !PICK && __builtin_amdgcn_readfirstlane(first_n) < 0;     // its gradient rows are not there yet
+        if (skip && lane == 0) a.later[atomicAdd(a.n_later, 1)] = u;
+        if (ALL_LANES && skip) {
+            NGDB_FETCH_INDEX(i + n_waves);
+            NGDB_FETCH_ROWS()
+            continue;
+        }
         const int32_t row = row_n;
-        const int t0 = t0_n, t1 = t1_n;
+        const int t0 = t0_n, t1 = skip ? t0_n : t1_n;
         float4* prow = reinterpret_cast<float4*>(a.P + (size_t)row * a.d);
         float4* mrow = reinterpret_cast<float4*>(a.Mo + (size_t)row * a.d);
         float4* vrow = reinterpret_cast<float4*>(a.Vo + (size_t)row * a.d);
@@ -166,7 +185,7 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
             }
             g[ch] = zero4;
         }
-        NGDB_FETCH_INDEX(u + n_waves);
+        NGDB_FETCH_INDEX(i + n_waves);
         // SH: the row as the scoring pass read it (rounded to bf16)
         float4 psr[SH ? NCH : 1];
         if (SH) {
@@ -273,7 +292,7 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
             uint2* brow = reinterpret_cast<uint2*>(a.g_bf16 + (size_t)u * a.d);
 #pragma unroll
             for (int ch = 0; ch < NCH; ++ch)
-                if (col_ok[ch])
+                if (col_ok[ch] && !skip)
                     brow[ch * 64 + lane] = make_uint2(bf16_bits(g[ch].x) | (bf16_bits(g[ch].y) << 16),
                                                       bf16_bits(g[ch].z) | (bf16_bits(g[ch].w) << 16));
         }
@@ -286,27 +305,19 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
                 g[ch].w = p[ch].w > 0.f ? g[ch].w : 0.f;
             }
         }
-        // Stores without a lane condition (plain rows of tables that stay in the caches): the lanes
-        // past the end of the row hold, through their clamped loads, the values of its last four
-        // coordinates and write those once more.  Under a condition the stores may or may not be
-        // issued as far as the compiler can tell, and the next row's wait for its parameter rows,
-        // requested before them, becomes a wait for the stores too.  (With text features the sign
-        // codes of those lanes are not the last column's; tables streamed from HBM are faster with
-        // that wait: 4.32 against 4.49 ms at 2 M touched rows.)
-        constexpr bool ALL_LANES = !SEM && !NT;
         if (!update) {
             float4* orow = reinterpret_cast<float4*>(a.g_out + (size_t)u * a.d);
 #pragma unroll
             for (int ch = 0; ch < NCH; ++ch) {
                 if (ALL_LANES) orow[colc[ch]] = g[ch];
-                else if (col_ok[ch]) orow[ch * 64 + lane] = g[ch];
+                else if (col_ok[ch] && !skip) orow[ch * 64 + lane] = g[ch];
             }
             continue;
         }
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
             const int at = ALL_LANES ? colc[ch] : ch * 64 + lane;
-            if (ALL_LANES || col_ok[ch]) {
+            if (ALL_LANES || (col_ok[ch] && !skip)) {
                 // (reciprocal and square root by the hardware approximations, about 1 ulp each: the
                 // correctly rounded forms cost some sixty instructions per coordinate, which made
                 // this memory-bound kernel wait for its own arithmetic)
@@ -333,38 +344,41 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
 #undef NGDB_FETCH_INDEX
 #undef NGDB_FETCH_ROWS
 
-// Small steps (the launch, not the bytes, is what a table update costs there): the last
-// main_blocks workgroups walk the rows of the main table; the ones before them those of up to two
-// small plain tables of the same width (the relation tables, whose launches of their own would
-// each add their latency to the step's tail).  Large tables keep table_kernel: there this
-// kernel measured 3 % slower on the entity table than the launches it saves are worth.
 // one table per launch
+// (box family at d <= 512, in the caches: every pair re-reads two cached rows, and a fourth wavefront per SIMD
+// costs more in cache misses than it hides: held at three, here and at the end of the step)
 template <int NCH, bool SEM, bool BOX, bool SH, bool NT, bool UPD>
-__global__ __launch_bounds__(256) void table_kernel(const TableArgs a, const AdamHyper hp) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (BOX && NCH == 2 && !NT) ? 3 : 8))) void table_kernel(const TableArgs a, const AdamHyper hp) {
     table_rows<NCH, SEM, BOX, SH, NT, UPD>(a, hp, (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6),
                                   (int)((gridDim.x * blockDim.x) >> 6));
 }
 
-// (box family at d <= 512: every pair re-reads two cached rows, and a fourth wavefront per SIMD
-// costs more in cache misses than it hides: held at three)
+// The end of a step: the first workgroups walk up to two small plain tables of the same width (the relation tables), the
+// next ones the rows of the main table that are left (in a small step without a second stream: all of them), the last
+// the dense tensors.  As launches of their own each of these would add its latency to the end of the step.
 template <int NCH, bool SEM, bool BOX, bool SH, bool UPD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (BOX && NCH == 2) ? 3 : 8)))
-void table_group_kernel(const TableArgs a, const TableTail tail, const AdamHyper hp) {
+void step_tail_kernel(const TableArgs a, const TableTail tail, const AdamHyper hp) {
     const int b = (int)blockIdx.x;
     const int mb = b - tail.blocks[0] - tail.blocks[1];
+    if (mb >= tail.main_blocks) {
+        const int db = mb - tail.main_blocks;
+        dense_adam(tail.dense, db / tail.dense_blocks, hp, (int64_t)(db % tail.dense_blocks) * 256 + threadIdx.x,
+                   (int64_t)tail.dense_blocks * 256);
+        return;
+    }
     if (mb >= 0) {
         // (the wavefront's number is the same in all its lanes: kept in a scalar register)
-        table_rows<NCH, SEM, BOX, SH, false, UPD>(a, hp, __builtin_amdgcn_readfirstlane((int)((mb * blockDim.x + threadIdx.x) >> 6)),
-                                                  tail.main_blocks * 4);
+        table_rows<NCH, SEM, BOX, SH, false, UPD, true>(a, hp, __builtin_amdgcn_readfirstlane((int)((mb * blockDim.x + threadIdx.x) >> 6)),
+                                                        tail.main_blocks * 4);
         return;
     }
     const int k = b < tail.blocks[0] ? 0 : 1;
     const int lb = k ? b - tail.blocks[0] : b;
-    table_rows<NCH, false, false, false, false, UPD>(tail.job[k], hp,
-                                                     __builtin_amdgcn_readfirstlane((int)((lb * blockDim.x + threadIdx.x) >> 6)),
-                                                     tail.blocks[k] * 4);
+    table_rows<NCH, false, false, false, false, UPD, true>(tail.job[k], hp,
+                                                           __builtin_amdgcn_readfirstlane((int)((lb * blockDim.x + threadIdx.x) >> 6)),
+                                                           tail.blocks[k] * 4);
 }
-
 
 }  // namespace
 
@@ -378,49 +392,75 @@ hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_b
     return hipGetLastError();
 }
 
-hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, hipStream_t s, const TableArgs* small,
-                               int n_small, int small_rows) {
-    // the number of touched rows is only known on the device: a fixed grid walks them
+namespace {
+// The number of touched rows is only known on the device: a fixed grid walks them.  Four times as many workgroups as
+// fit at once, so that the launches of the other stream get their turn (6.42, 6.46 and 6.48 ms with 16, 4 and 2 times as
+// many for the step over 2.5 M entities, 15.9 and 16.4 ms with 8 and 2 with text features).
+constexpr int TABLE_BLOCKS = 256 * 16;
+
+bool table_args_ok(const TableArgs& a) {
+    const bool sem = a.g_bf16 != nullptr, box = a.off != nullptr;
+    return a.d <= 1024 && sem == (a.mask != nullptr) && !(sem && (box || a.relu_gate)) && !(a.shadow && (sem || box));
+}
+
+// CALL(NCH, SEM, BOX, SH) for the kind of table
+#define NGDB_TABLE_KIND(CALL, NCH)                                         \
+    do {                                                                   \
+        if (a.g_bf16) CALL(NCH, true, false, false);                       \
+        else if (a.off) CALL(NCH, false, true, false);                     \
+        else if (a.shadow) CALL(NCH, false, false, true);                  \
+        else CALL(NCH, false, false, false);                               \
+    } while (0)
+#define NGDB_TABLE(CALL)                                                   \
+    do {                                                                   \
+        if (a.d <= 256) NGDB_TABLE_KIND(CALL, 1);                          \
+        else if (a.d <= 512) NGDB_TABLE_KIND(CALL, 2);                     \
+        else NGDB_TABLE_KIND(CALL, 4);                                     \
+    } while (0)
+}  // namespace
+
+hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, hipStream_t s) {
+    if (!table_args_ok(a)) return hipErrorInvalidValue;
+    const int blocks = few ? 256 : TABLE_BLOCKS;
+#define NGDB_WALK(NCH, SEM_, BOX_, SH_)                                                                                                   \
+    do {                                                                                                                                  \
+        if (a.streaming) hipLaunchKernelGGL((table_kernel<NCH, SEM_, BOX_, SH_, true, false>), dim3(blocks), dim3(256), 0, s, a, hp);    \
+        else if (a.g_out) hipLaunchKernelGGL((table_kernel<NCH, SEM_, BOX_, SH_, false, false>), dim3(blocks), dim3(256), 0, s, a, hp);  \
+        else hipLaunchKernelGGL((table_kernel<NCH, SEM_, BOX_, SH_, false, true>), dim3(blocks), dim3(256), 0, s, a, hp);                \
+    } while (0)
+    NGDB_TABLE(NGDB_WALK);
+#undef NGDB_WALK
+    return hipGetLastError();
+}
+
+hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArgs* small, int n_small, int small_rows,
+                            const DenseAdamJob& dense, const AdamHyper& hp, hipStream_t s) {
+    if (!table_args_ok(a) || n_small < 0 || n_small > 2 || (n_small > 0 && !small)) return hipErrorInvalidValue;
     TableTail tail{};
-    tail.main_blocks = 256 * 8;
-    if (n_small < 0 || n_small > 2 || (n_small > 0 && !small)) return hipErrorInvalidValue;
+    tail.main_blocks = (int)std::min<int64_t>(TABLE_BLOCKS, (max_rows + 3) / 4);
+    bool upd = a.g_out == nullptr;        // every table of the launch is updated in place
     for (int k = 0; k < n_small; ++k) {
         const TableArgs& t = small[k];
         if (t.d != a.d || t.g_bf16 || t.mask || t.off || t.shadow) return hipErrorInvalidValue;   // plain tables only
         tail.job[k] = t;
         tail.blocks[k] = std::max(1, std::min(256, (small_rows + 3) / 4));
+        upd = upd && t.g_out == nullptr;
     }
-    const int blocks = tail.main_blocks + tail.blocks[0] + tail.blocks[1];
-    if (a.d > 1024 || (a.g_bf16 != nullptr) != (a.mask != nullptr)) return hipErrorInvalidValue;
-    const bool sem = a.g_bf16 != nullptr, box = a.off != nullptr;
-    if (sem && (box || a.relu_gate)) return hipErrorInvalidValue;
-    if (a.shadow && (sem || box)) return hipErrorInvalidValue;
-    bool upd = a.g_out == nullptr;        // every table of the launch is updated in place
-    for (int k = 0; k < n_small; ++k) upd = upd && small[k].g_out == nullptr;
-#define NGDB_TABLE_U(NCH, SEM_, BOX_, SH_, UPD_)                                                              \
-    do {                                                                                                      \
-        if (n_small) hipLaunchKernelGGL((table_group_kernel<NCH, SEM_, BOX_, SH_, UPD_>), dim3(blocks), dim3(256), 0, s, a, tail, hp); \
-        else if (a.streaming) hipLaunchKernelGGL((table_kernel<NCH, SEM_, BOX_, SH_, true, false>), dim3(tail.main_blocks), dim3(256), 0, s, a, hp); \
-        else hipLaunchKernelGGL((table_kernel<NCH, SEM_, BOX_, SH_, false, UPD_>), dim3(tail.main_blocks), dim3(256), 0, s, a, hp); \
+    tail.dense = dense;
+    int64_t longest = 0;
+    for (int t = 0; t < dense.count; ++t) longest = std::max(longest, dense.n[t]);
+    tail.dense_blocks = (int)std::max<int64_t>(1, std::min<int64_t>((longest + 255) / 256, 512));
+    const int blocks = tail.blocks[0] + tail.blocks[1] + tail.main_blocks + dense.count * tail.dense_blocks;
+    if (blocks == 0) return hipSuccess;
+#define NGDB_TAIL(NCH, SEM_, BOX_, SH_)                                                                                          \
+    do {                                                                                                                         \
+        if (upd) hipLaunchKernelGGL((step_tail_kernel<NCH, SEM_, BOX_, SH_, true>), dim3(blocks), dim3(256), 0, s, a, tail, hp); \
+        else hipLaunchKernelGGL((step_tail_kernel<NCH, SEM_, BOX_, SH_, false>), dim3(blocks), dim3(256), 0, s, a, tail, hp);    \
     } while (0)
-#define NGDB_TABLE_V(NCH, SEM_, BOX_, SH_)                                                                     \
-    do {                                                                                                      \
-        if (upd) NGDB_TABLE_U(NCH, SEM_, BOX_, SH_, true);                                                    \
-        else NGDB_TABLE_U(NCH, SEM_, BOX_, SH_, false);                                                       \
-    } while (0)
-#define NGDB_TABLE(NCH)                                   \
-    do {                                                  \
-        if (sem) NGDB_TABLE_V(NCH, true, false, false);   \
-        else if (box) NGDB_TABLE_V(NCH, false, true, false); \
-        else if (a.shadow) NGDB_TABLE_V(NCH, false, false, true); \
-        else NGDB_TABLE_V(NCH, false, false, false);      \
-    } while (0)
-    if (a.d <= 256) NGDB_TABLE(1);
-    else if (a.d <= 512) NGDB_TABLE(2);
-    else NGDB_TABLE(4);
+    NGDB_TABLE(NGDB_TAIL);
+#undef NGDB_TAIL
 #undef NGDB_TABLE
-#undef NGDB_TABLE_V
-#undef NGDB_TABLE_U
+#undef NGDB_TABLE_KIND
     return hipGetLastError();
 }
 

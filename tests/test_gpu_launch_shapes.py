@@ -76,3 +76,31 @@ def test_gradient_index_by_size(N, B, n_keys):
     for name, want in (("e_uniq", u), ("e_seg_off", off), ("e_src", src)):
         assert np.array_equal(g[name], want), name
     plan.free()
+
+
+# table rows beside the backward pass, rows of anchors after it: every row an anchor's, nearly none, a pass kept to few
+# wavefronts, one at full width over a table beyond the caches, text features, a bf16 copy of the table
+@pytest.mark.parametrize("N,d,B,K,d_sem,bf16", [(20, 32, 60, 3, 0, False), (9000, 64, 3, 50, 0, False), (9000, 260, 40, 200, 0, False),
+                                                (60000, 400, 60, 1000, 0, False), (3000, 40, 50, 90, 64, False),
+                                                (60000, 520, 60, 1000, 64, False), (3000, 40, 50, 90, 0, True)])
+def test_tables_beside_the_backward_pass(N, d, B, K, d_sem, bf16):
+    import torch
+    from paper_2602_21597_amd import Engine
+    qb = wl.make_batch(wl.make_kg(N, 7, 5 * N, 2.1, 1), B, {n: 1.0 for n in wl.configs.ALL14}, 2)
+    params = wl.make_params(N, 7, d, 32, 3, d_sem=d_sem)
+    sem = wl.make_sem_features(N, d_sem, 4) if d_sem else None
+    negs = torch.from_numpy(wl.make_negatives(N, B, K, 5)).cuda()
+    out = []
+    for streams in (1, 2):
+        eng = Engine(N, 7, d, 32, 12.0, num_streams=streams, d_sem=d_sem, score_bf16=bf16)
+        eng.bind_numpy(params, sem_bits=sem)
+        plan = eng.plan(qb)
+        eng.forward_backward(plan, negs)
+        grads = {k: np.copy(v) for k, v in eng.grads().items()}
+        losses = [float(eng.train_step(plan, negs)) for _ in range(3)]
+        out.append((grads, losses, [t for name in eng.tensor_names() for t in eng.tensors[name]]))
+        plan.free()
+    for name, want in out[0][0].items():
+        assert np.array_equal(out[1][0][name], want), name
+    assert out[0][1] == out[1][1]
+    assert all(torch.equal(a, b) for a, b in zip(out[0][2], out[1][2]))
