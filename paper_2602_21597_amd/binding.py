@@ -277,18 +277,23 @@ class SampledBatch:
 
     def __init__(self, c, neg_ptr, tmpl_ptr, K, names):
         B = int(c.n_queries)
-        take = lambda ptr, n, dt: (np.ctypeslib.as_array(C.cast(ptr, C.POINTER(dt)), shape=(n,)).copy() if n
-                                   else np.zeros(0, dt))
+
+        def take(ptr, shape, dt):
+            a = np.empty(shape, dt)
+            if a.size:      # (a plain memory copy: a tenth of what numpy's view of a ctypes pointer costs)
+                C.memmove(a.__array_interface__["data"][0], ptr, a.nbytes)
+            return a
+
         self.B = B
-        self.node_off = take(c.node_off, B + 1, C.c_int32)
+        self.node_off = take(c.node_off, B + 1, np.int32)
         n_nodes = int(self.node_off[-1]) if B else 0
-        self.op = take(c.op, n_nodes, C.c_uint8)
-        self.arg = take(c.arg, n_nodes, C.c_int32)
-        self.in_off = take(c.in_off, n_nodes + 1, C.c_int32)
-        self.in_idx = take(c.in_idx, int(self.in_off[-1]), C.c_int32)
-        self.pos = take(c.pos, B, C.c_int32)
-        self.negs = take(neg_ptr, B * K, C.c_int32).reshape(B, K)
-        self.names = [names[int(t)] for t in take(tmpl_ptr, B, C.c_uint8)]
+        self.op = take(c.op, n_nodes, np.uint8)
+        self.arg = take(c.arg, n_nodes, np.int32)
+        self.in_off = take(c.in_off, n_nodes + 1, np.int32)
+        self.in_idx = take(c.in_idx, int(self.in_off[-1]), np.int32)
+        self.pos = take(c.pos, B, np.int32)
+        self.negs = take(neg_ptr, (B, K), np.int32)
+        self.names = list(map(names.__getitem__, take(tmpl_ptr, B, np.uint8).tobytes()))
 
     def query_nodes(self, i):
         """Nodes of query i as a list of (op, arg, [local input indices]), root last."""

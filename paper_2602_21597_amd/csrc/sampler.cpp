@@ -12,13 +12,11 @@
 // from its own counter-based random stream (seed, batch number, query number),
 // so a batch does not depend on the number of threads.
 #include <algorithm>
+#include <atomic>
 #include <condition_variable>
 #include <cstring>
-#include <functional>
 #include <mutex>
 #include <new>
-#include <numeric>
-#include <memory>
 #include <string>
 #include <thread>
 #include <vector>
@@ -41,19 +39,19 @@ struct Rng {   // splitmix64 over a per-query counter
         z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
         return z ^ (z >> 31);
     }
-    // uniform in [0, n), n > 0 (multiply-shift with rejection of the biased tail)
+    // uniform in [0, n), n > 0 (multiply-shift with rejection of the biased tail, which is shorter than n: the
+    // division is left to the draws that might lie in it)
     uint64_t below(uint64_t n) {
         for (;;) {
             const uint64_t x = next();
             const unsigned __int128 m = (unsigned __int128)x * n;
-            if ((uint64_t)m >= (uint64_t)(-n) % n) return (uint64_t)(m >> 64);
+            if ((uint64_t)m >= n || (uint64_t)m >= (uint64_t)(-n) % n) return (uint64_t)(m >> 64);
         }
     }
     double unit() { return (double)(next() >> 11) * (1.0 / 9007199254740992.0); }
     // two uniform draws in [0, n), n < 2^31, from one 64-bit word (each half: multiply-shift,
-    // redrawn together if either falls into the biased tail)
-    void below32x2(uint32_t n, int32_t* out) {
-        const uint32_t tail = (uint32_t)(-n) % n;
+    // redrawn together if either falls into the biased tail = 2^32 mod n)
+    void below32x2(uint32_t n, uint32_t tail, int32_t* out) {
         for (;;) {
             const uint64_t x = next();
             const uint64_t a = (uint64_t)(uint32_t)x * n, b = (x >> 32) * n;
@@ -66,82 +64,27 @@ struct Rng {   // splitmix64 over a per-query counter
     }
 };
 
-// Worker threads that live as long as the sampler: a call hands them a function of the
-// worker number and waits for all of them.
-class Workers {
-public:
-    explicit Workers(int n) {
-        for (int i = 0; i < n; ++i) threads_.emplace_back([this, i] { loop(i); });
-    }
-    ~Workers() {
-        {
-            std::lock_guard<std::mutex> lk(mu_);
-            stop_ = true;
-            ++round_;
-        }
-        cv_.notify_all();
-        for (std::thread& t : threads_) t.join();
-    }
-    int size() const { return (int)threads_.size(); }
-    // fn must stay alive until wait() has returned
-    void start(const std::function<void(int)>& fn) {
-        {
-            std::lock_guard<std::mutex> lk(mu_);
-            fn_ = &fn;
-            pending_ = (int)threads_.size();
-            ++round_;
-        }
-        cv_.notify_all();
-    }
-    void wait() {
-        std::unique_lock<std::mutex> lk(mu_);
-        done_.wait(lk, [this] { return pending_ == 0; });
-    }
-
-private:
-    void loop(int i) {
-        uint64_t seen = 0;
-        for (;;) {
-            const std::function<void(int)>* fn;
-            {
-                std::unique_lock<std::mutex> lk(mu_);
-                cv_.wait(lk, [&] { return round_ != seen; });
-                seen = round_;
-                if (stop_) return;
-                fn = fn_;
-            }
-            (*fn)(i);
-            {
-                std::lock_guard<std::mutex> lk(mu_);
-                if (--pending_ == 0) done_.notify_one();
-            }
-        }
-    }
-    std::vector<std::thread> threads_;
-    std::mutex mu_;
-    std::condition_variable cv_, done_;
-    const std::function<void(int)>* fn_ = nullptr;
-    uint64_t round_ = 0;
-    int pending_ = 0;
-    bool stop_ = false;
-};
-
 // ---------------------------------------------------------------- graph
 struct Graph {
     int32_t N = 0, R = 0;
     int64_t T = 0;
     std::vector<int64_t> in_off, out_off;          // [N+1]
-    std::vector<int32_t> in_head, in_rel;          // in-edges of every entity, any fixed order
-    std::vector<int32_t> out_rel, out_tail;        // out-edges sorted by (relation, tail)
+    struct InEdge { int32_t head, rel; };
+    struct OutEdge { int32_t rel, tail; };
+    std::vector<InEdge> in_edge;                   // in-edges of every entity, any fixed order
+    struct RelEdge { int32_t rel, at, head; };
+    std::vector<RelEdge> rel_edge;                 // the same sorted by relation; at: place among the entity's in-edges
+    std::vector<OutEdge> out_edge;                 // out-edges sorted by (relation, tail)
     std::vector<int32_t> tails;                    // tail of every triple (answers are drawn from it)
 
     bool has_triple(int32_t h, int32_t r, int32_t t) const {
         int64_t lo = out_off[h], hi = out_off[h + 1];
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
-            if (out_rel[mid] < r || (out_rel[mid] == r && out_tail[mid] < t)) lo = mid + 1; else hi = mid;
+            const OutEdge e = out_edge[mid];
+            if (e.rel < r || (e.rel == r && e.tail < t)) lo = mid + 1; else hi = mid;
         }
-        return lo < out_off[h + 1] && out_rel[lo] == r && out_tail[lo] == t;
+        return lo < out_off[h + 1] && out_edge[lo].rel == r && out_edge[lo].tail == t;
     }
 };
 
@@ -184,23 +127,20 @@ const char* shape_of(const std::string& name) {
 }
 
 // ---------------------------------------------------------------- one query
+constexpr int MAX_NODES = 16;   // of a query, and inputs of all its nodes: more than any template has
 struct Query {           // nodes in post-order, root last
-    std::vector<uint8_t> op;
-    std::vector<int32_t> arg, in_off, in_idx;
-    void clear() { op.clear(); arg.clear(); in_idx.clear(); in_off.assign(1, 0); }
-    int add(uint8_t o, int32_t a, const int* ins, int n) {
-        op.push_back(o);
-        arg.push_back(a);
-        in_idx.insert(in_idx.end(), ins, ins + n);
-        in_off.push_back((int32_t)in_idx.size());
-        return (int)op.size() - 1;
+    int n = 0;
+    uint8_t op[MAX_NODES];
+    int32_t arg[MAX_NODES], in_off[MAX_NODES + 1] = {0}, in_idx[MAX_NODES];
+    void clear() { n = 0; }
+    int add(uint8_t o, int32_t a, const int* ins, int n_in) {
+        op[n] = o;
+        arg[n] = a;
+        for (int k = 0; k < n_in; ++k) in_idx[in_off[n] + k] = ins[k];
+        in_off[n + 1] = in_off[n] + n_in;
+        return n++;
     }
-    void truncate(size_t n_nodes) {
-        op.resize(n_nodes);
-        arg.resize(n_nodes);
-        in_off.resize(n_nodes + 1);
-        in_idx.resize(in_off.back());
-    }
+    void truncate(int n_nodes) { n = n_nodes; }
 };
 
 struct Builder {
@@ -214,7 +154,7 @@ struct Builder {
     // up (treated as "cannot tell") when the budget runs out.
     int contains(int n, int32_t v) {
         const uint8_t o = q.op[n];
-        const int32_t* ins = q.in_idx.data() + q.in_off[n];
+        const int32_t* ins = q.in_idx + q.in_off[n];
         const int nin = q.in_off[n + 1] - q.in_off[n];
         if (o == NGDB_OP_ANCHOR) return q.arg[n] == v;
         if (o == NGDB_OP_NEG) {
@@ -233,23 +173,32 @@ struct Builder {
         // projection by relation r: some m with (m, r, v) in the graph and m an answer of the input
         const int32_t r = q.arg[n];
         if (q.op[ins[0]] == NGDB_OP_ANCHOR) return g.has_triple(q.arg[ins[0]], r, v);
-        for (int64_t j = g.in_off[v]; j < g.in_off[v + 1]; ++j) {
-            if (--budget < 0) return -1;
-            if (g.in_rel[j] != r) continue;
-            const int c = contains(ins[0], g.in_head[j]);
+        // The budget counts in-edges in their fixed order, whatever their relation; those of relation r are looked up
+        // (entities that answers are drawn at have thousands of in-edges, few of them of one relation).
+        const Graph::RelEdge *e = g.rel_edge.data() + g.in_off[v], *end = g.rel_edge.data() + g.in_off[v + 1];
+        const long degree = (long)(end - e);
+        e = std::lower_bound(e, end, r, [](const Graph::RelEdge& x, int32_t rel) { return x.rel < rel; });
+        long seen = 0;
+        for (; e < end && e->rel == r; ++e) {
+            budget -= e->at + 1 - seen;
+            seen = e->at + 1;
+            if (budget < 0) return -1;
+            const int c = contains(ins[0], e->head);
             if (c) return c;
         }
+        budget -= degree - seen;
+        if (budget < 0) return -1;
         return 0;
     }
 
-    bool same_subtree(size_t a0, size_t a1, size_t b0, size_t b1) const {
+    bool same_subtree(int a0, int a1, int b0, int b1) const {
         if (a1 - a0 != b1 - b0) return false;
-        for (size_t i = 0; i < a1 - a0; ++i) {
+        for (int i = 0; i < a1 - a0; ++i) {
             if (q.op[a0 + i] != q.op[b0 + i] || q.arg[a0 + i] != q.arg[b0 + i]) return false;
             const int na = q.in_off[a0 + i + 1] - q.in_off[a0 + i], nb = q.in_off[b0 + i + 1] - q.in_off[b0 + i];
             if (na != nb) return false;
             for (int k = 0; k < na; ++k)
-                if (q.in_idx[q.in_off[a0 + i] + k] - (int32_t)a0 != q.in_idx[q.in_off[b0 + i] + k] - (int32_t)b0)
+                if (q.in_idx[q.in_off[a0 + i] + k] - a0 != q.in_idx[q.in_off[b0 + i] + k] - b0)
                     return false;
         }
         return true;
@@ -267,9 +216,10 @@ struct Builder {
                 const int64_t lo = g.in_off[v], hi = g.in_off[v + 1];
                 if (hi == lo) return -1;
                 const int64_t j = lo + (int64_t)rng.below((uint64_t)(hi - lo));
-                const int c = grow(node.kids[0], g.in_head[j]);
+                const Graph::InEdge e = g.in_edge[j];
+                const int c = grow(node.kids[0], e.head);
                 if (c < 0) return -1;
-                return q.add(NGDB_OP_PROJ, g.in_rel[j], &c, 1);
+                return q.add(NGDB_OP_PROJ, e.rel, &c, 1);
             }
             case 'n': {
                 const int c = grow(node.kids[0], random_tail());
@@ -277,36 +227,35 @@ struct Builder {
                 return q.add(NGDB_OP_NEG, 0, &c, 1);
             }
             case 'i': {
-                std::vector<int> kids;
-                std::vector<std::pair<size_t, size_t>> span;
+                int kids[MAX_NODES], span[MAX_NODES], n = 0;      // roots and first nodes of the children
                 for (int kt : node.kids) {
                     int c = -1;
                     for (int attempt = 0; attempt < 8; ++attempt) {
-                        const size_t start = q.op.size();
+                        const int start = q.n;
                         c = grow(kt, v);
                         if (c < 0) return -1;
                         bool dup = false;
-                        for (const auto& sp : span) dup = dup || same_subtree(sp.first, sp.second, start, q.op.size());
+                        for (int k = 0; k < n; ++k) dup = dup || same_subtree(span[k], kids[k] + 1, start, q.n);
                         if (!dup) {
-                            span.emplace_back(start, q.op.size());
+                            span[n] = start;
                             break;
                         }
                         q.truncate(start);
                         c = -1;
                     }
                     if (c < 0) return -1;
-                    kids.push_back(c);
+                    kids[n++] = c;
                 }
-                return q.add(NGDB_OP_INTER, 0, kids.data(), (int)kids.size());
+                return q.add(NGDB_OP_INTER, 0, kids, n);
             }
             case 'u': {
-                std::vector<int> kids;
-                for (size_t k = 0; k < node.kids.size(); ++k) {
-                    const int c = grow(node.kids[k], k == 0 ? v : random_tail());
+                int kids[MAX_NODES], n = 0;
+                for (int kt : node.kids) {
+                    const int c = grow(kt, n == 0 ? v : random_tail());
                     if (c < 0) return -1;
-                    kids.push_back(c);
+                    kids[n++] = c;
                 }
-                return q.add(NGDB_OP_UNION, 0, kids.data(), (int)kids.size());
+                return q.add(NGDB_OP_UNION, 0, kids, n);
             }
         }
         return -1;
@@ -315,9 +264,22 @@ struct Builder {
 
 }  // namespace
 
+// A batch is drawn in chunks of 32 queries, which the threads take in turn; each chunk leaves its queries one after
+// the other in arrays of its own, and whoever ends the last one strings them together.  (Equal shares per thread, queries
+// in vectors strung together by one thread, in-edges of hubs scanned for a relation: 107 us a batch of 512 queries with
+// 128 negatives over 310 000 triples on four threads, 57 now; one thread alone 235, now 169.)
+constexpr int CHUNK = 32;
+struct Chunk {
+    int n_nodes, n_idx, failed;           // failed: first query that could not be drawn, or -1
+    int32_t node_end[CHUNK];
+    uint8_t op[CHUNK * MAX_NODES];
+    int32_t arg[CHUNK * MAX_NODES], in_end[CHUNK * MAX_NODES], in_idx[CHUNK * MAX_NODES];
+};
+
 struct BatchArrays {   // what ngdb_sampler_next hands out
     std::vector<int32_t> node_off, arg, in_off, in_idx, pos, neg;
     std::vector<uint8_t> op, tmpl;
+    std::vector<Chunk> chunk;
 };
 
 struct ngdb_sampler_s {
@@ -325,56 +287,174 @@ struct ngdb_sampler_s {
     std::vector<Template> templates;
     std::vector<double> cdf;
     uint64_t seed = 0, batch_no = 0;
-    int n_threads = 1;
-    std::unique_ptr<Workers> workers;   // n_threads - 1 helpers; the caller's thread works too
-    std::vector<Query> queries;         // per query scratch, reused
     BatchArrays out[3];                 // three sets taking turns: a batch stays valid over the next call
                                         // while the one after it is already being drawn
     std::string err;
-    // Read-ahead: after a call has returned batch t, a coordinator thread draws batch t+1 (same
-    // sizes) with the helpers, so that the next call usually finds its batch ready.  The batches
+    // The batch being drawn.  Read-ahead: after a call has returned batch t, the threads draw batch t+1 (same
+    // sizes), so that the next call usually finds its batch ready.  The batches
     // are functions of (seed, batch number, query number): reading ahead changes nothing in them.
-    std::thread coordinator;
-    std::mutex pm;
-    std::condition_variable pcv;
-    bool pf_requested = false, pf_done = false, pf_stop = false;   // guarded by pm
-    uint64_t pf_no = 0;
-    int pf_B = 0, pf_K = 0, pf_rc = NGDB_OK;
+    std::vector<std::thread> threads;
+    std::mutex mu;
+    std::condition_variable work, done;
+    bool stop = false, posted = false, ahead = false;       // from here on guarded by mu (ahead: batch `no` is the next call's)
+    uint64_t no = 0;
+    int B = 0, K = 0, n_chunks = 0, next = 0, ended = 0, rc = NGDB_OK;
+    std::string draw_err;
+    std::atomic<uint64_t> posts{0}, finished{0};            // batches posted / complete so far (also read without mu)
 
     ~ngdb_sampler_s() {
-        if (coordinator.joinable()) {
-            {
-                std::lock_guard<std::mutex> lk(pm);
-                pf_stop = true;
-            }
-            pcv.notify_all();
-            coordinator.join();
+        {
+            std::lock_guard<std::mutex> lk(mu);
+            stop = true;
         }
+        work.notify_all();
+        for (std::thread& t : threads) t.join();
     }
 };
 
 namespace {
-int fill_batch(ngdb_sampler_s* s, uint64_t batch_no, int32_t B, int32_t K, BatchArrays& o);
 
-void coordinator_loop(ngdb_sampler_s* s) {
-    for (;;) {
-        uint64_t no;
-        int B, K;
-        {
-            std::unique_lock<std::mutex> lk(s->pm);
-            s->pcv.wait(lk, [&] { return s->pf_stop || (s->pf_requested && !s->pf_done); });
-            if (s->pf_stop) return;
-            no = s->pf_no; B = s->pf_B; K = s->pf_K;
+void draw_chunk(const ngdb_sampler_s& s, uint64_t batch_no, int lo, int hi, int K, BatchArrays& o, Chunk& c) {
+    c.n_nodes = c.n_idx = 0;
+    c.failed = -1;
+    const uint32_t n = (uint32_t)s.g.N, tail = (uint32_t)(-n) % n;
+    Query q;
+    for (int i = lo; i < hi; ++i) {
+        Rng rng(s.seed, batch_no, (uint64_t)i);
+        const double u = rng.unit();
+        size_t t = 0;
+        while (t + 1 < s.cdf.size() && u >= s.cdf[t]) ++t;
+        o.tmpl[i] = (uint8_t)t;
+        const Template& tp = s.templates[t];
+        bool ok = false;
+        int32_t v = 0;
+        for (int attempt = 0; attempt < 1000 && !ok; ++attempt) {
+            q.clear();
+            v = s.g.tails[rng.below((uint64_t)s.g.T)];
+            Builder b{s.g, tp, rng, q};
+            if (b.grow((int)tp.nodes.size() - 1, v) < 0) continue;
+            b.budget = 20000;
+            ok = b.contains(q.n - 1, v) == 1;   // (not if e.g. the end point lies in a negated branch)
         }
-        const int rc = fill_batch(s, no, B, K, s->out[no % 3]);
-        {
-            std::lock_guard<std::mutex> lk(s->pm);
-            s->pf_rc = rc;
-            s->pf_done = true;
+        o.pos[i] = ok ? v : 0;
+        if (!ok && c.failed < 0) c.failed = i;
+        for (int k = 0; k < q.n; ++k) {
+            c.op[c.n_nodes + k] = q.op[k];
+            c.arg[c.n_nodes + k] = q.arg[k];
+            c.in_end[c.n_nodes + k] = c.n_idx + q.in_off[k + 1];
         }
-        s->pcv.notify_all();
+        for (int k = 0; k < q.in_off[q.n]; ++k) c.in_idx[c.n_idx + k] = q.in_idx[k];
+        c.n_nodes += q.n;
+        c.n_idx += q.in_off[q.n];
+        c.node_end[i - lo] = c.n_nodes;
+        int32_t* nrow = o.neg.data() + (size_t)i * K;
+        int k = 0;
+        for (; k + 2 <= K; k += 2) rng.below32x2(n, tail, nrow + k);
+        if (k < K) nrow[k] = (int32_t)rng.below((uint64_t)s.g.N);
     }
 }
+
+// the chunks of a batch one after the other
+int join_chunks(const ngdb_sampler_s& s, int B, int n_chunks, BatchArrays& o, std::string* err) {
+    size_t nodes = 0, idx = 0;
+    for (int c = 0; c < n_chunks; ++c) {
+        if (o.chunk[c].failed >= 0) {
+            *err = "query instantiation kept failing for template " + s.templates[o.tmpl[o.chunk[c].failed]].name;
+            return NGDB_ERR_UNSUPPORTED;
+        }
+        nodes += o.chunk[c].n_nodes;
+        idx += o.chunk[c].n_idx;
+    }
+    auto room = [](auto& v, size_t n) { if (v.size() < n) v.resize(n + n / 8); };
+    try {
+        room(o.node_off, (size_t)B + 1);
+        room(o.op, nodes); room(o.arg, nodes); room(o.in_off, nodes + 1); room(o.in_idx, idx);
+    } catch (const std::bad_alloc&) {
+        return NGDB_ERR_OOM;
+    }
+    int32_t nb = 0, ib = 0, q = 0;
+    o.node_off[0] = o.in_off[0] = 0;
+    for (int c = 0; c < n_chunks; ++c) {
+        const Chunk& ch = o.chunk[c];
+        memcpy(o.op.data() + nb, ch.op, ch.n_nodes);
+        memcpy(o.arg.data() + nb, ch.arg, (size_t)ch.n_nodes * 4);
+        memcpy(o.in_idx.data() + ib, ch.in_idx, (size_t)ch.n_idx * 4);
+        int32_t* off = o.in_off.data() + nb + 1;
+        for (int k = 0; k < ch.n_nodes; ++k) off[k] = ib + ch.in_end[k];
+        const int nq = std::min(CHUNK, B - q);
+        for (int k = 0; k < nq; ++k) o.node_off[q + 1 + k] = nb + ch.node_end[k];
+        nb += ch.n_nodes;
+        ib += ch.n_idx;
+        q += nq;
+    }
+    return NGDB_OK;
+}
+
+inline void relax() {
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+}
+constexpr int SPINS = 1000;      // about 20 us: a thread that has just drawn (or a caller that finds its batch
+                                 // under way) is not put to sleep and woken for a wait shorter than that
+
+// Draws chunks of the posted batch until none is left to take; mu is held on entry and on return.
+void help(ngdb_sampler_s* s, std::unique_lock<std::mutex>& lk) {
+    while (!s->stop && s->posted && s->next < s->n_chunks) {
+        const int c = s->next++, B = s->B, K = s->K, n_chunks = s->n_chunks;
+        const uint64_t no = s->no;
+        BatchArrays& o = s->out[no % 3];
+        lk.unlock();
+        draw_chunk(*s, no, c * CHUNK, std::min(B, (c + 1) * CHUNK), K, o, o.chunk[c]);
+        lk.lock();
+        if (++s->ended < n_chunks) continue;      // (the batch stays posted until its last chunk has ended)
+        lk.unlock();
+        std::string err;
+        const int rc = join_chunks(*s, B, n_chunks, o, &err);
+        lk.lock();
+        s->rc = rc;
+        s->draw_err = err;
+        s->posted = false;
+        s->finished.fetch_add(1);
+        s->done.notify_all();
+    }
+}
+
+void thread_loop(ngdb_sampler_s* s) {
+    std::unique_lock<std::mutex> lk(s->mu);
+    for (;;) {
+        help(s, lk);
+        if (s->stop) return;
+        const uint64_t seen = s->posts.load();
+        lk.unlock();
+        for (int i = 0; i < SPINS && s->posts.load(std::memory_order_relaxed) == seen; ++i) relax();
+        lk.lock();
+        s->work.wait(lk, [&] { return s->stop || s->posts.load() != seen || (s->posted && s->next < s->n_chunks); });
+        if (s->stop) return;
+    }
+}
+
+// hands batch number no to the threads; mu held, nothing posted
+int post(ngdb_sampler_s* s, uint64_t no, int B, int K) {
+    BatchArrays& o = s->out[no % 3];
+    s->n_chunks = (B + CHUNK - 1) / CHUNK;
+    try {
+        if (o.pos.size() < (size_t)B) { o.pos.resize(B); o.tmpl.resize(B); }
+        if (o.neg.size() < (size_t)B * K) o.neg.resize((size_t)B * K);
+        if (o.chunk.size() < (size_t)s->n_chunks) o.chunk.resize(s->n_chunks);
+        if (B == 0) { o.node_off.assign(1, 0); o.in_off.assign(1, 0); }
+    } catch (const std::bad_alloc&) {
+        return NGDB_ERR_OOM;
+    }
+    s->no = no; s->B = B; s->K = K;
+    s->next = s->ended = 0;
+    s->rc = NGDB_OK;
+    s->posted = s->n_chunks > 0;
+    s->posts.fetch_add(1);
+    if (!s->posted) s->finished.fetch_add(1);
+    return NGDB_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -402,7 +482,7 @@ int ngdb_sampler_create(int32_t N, int32_t R, int64_t T, const int32_t* head, co
             if (!shape) { delete s; return NGDB_ERR_ARG; }
             Template tp;
             tp.name = cur;
-            parse(shape, tp.nodes);
+            parse(shape, tp.nodes);          // (at most 9 nodes with 8 inputs: MAX_NODES)
             s->templates.push_back(std::move(tp));
             cur.clear();
         }
@@ -424,30 +504,39 @@ int ngdb_sampler_create(int32_t N, int32_t R, int64_t T, const int32_t* head, co
         g.out_off.assign((size_t)N + 1, 0);
         for (int64_t i = 0; i < T; ++i) { ++g.in_off[tail[i] + 1]; ++g.out_off[head[i] + 1]; }
         for (int32_t v = 0; v < N; ++v) { g.in_off[v + 1] += g.in_off[v]; g.out_off[v + 1] += g.out_off[v]; }
-        g.in_head.resize(T); g.in_rel.resize(T); g.out_rel.resize(T); g.out_tail.resize(T);
+        g.in_edge.resize(T); g.out_edge.resize(T);
         std::vector<int64_t> in_fill(g.in_off.begin(), g.in_off.end() - 1), out_fill(g.out_off.begin(), g.out_off.end() - 1);
         for (int64_t i = 0; i < T; ++i) {
             const int64_t a = in_fill[tail[i]]++, b = out_fill[head[i]]++;
-            g.in_head[a] = head[i]; g.in_rel[a] = rel[i];
-            g.out_rel[b] = rel[i]; g.out_tail[b] = tail[i];
+            g.in_edge[a] = {head[i], rel[i]};
+            g.out_edge[b] = {rel[i], tail[i]};
         }
-        std::vector<std::pair<int32_t, int32_t>> tmp;
-        for (int32_t v = 0; v < N; ++v) {
-            const int64_t lo = g.out_off[v], hi = g.out_off[v + 1];
-            tmp.resize((size_t)(hi - lo));
-            for (int64_t j = lo; j < hi; ++j) tmp[(size_t)(j - lo)] = {g.out_rel[j], g.out_tail[j]};
-            std::sort(tmp.begin(), tmp.end());
-            for (int64_t j = lo; j < hi; ++j) { g.out_rel[j] = tmp[(size_t)(j - lo)].first; g.out_tail[j] = tmp[(size_t)(j - lo)].second; }
+        // (relations in ascending order: every entity's list fills up sorted)
+        std::vector<int64_t> rel_off((size_t)R + 1, 0), by_rel(T);
+        for (int64_t j = 0; j < T; ++j) ++rel_off[g.in_edge[j].rel + 1];
+        for (int32_t r = 0; r < R; ++r) rel_off[r + 1] += rel_off[r];
+        std::vector<int32_t> tail_of(T);
+        for (int32_t v = 0; v < N; ++v)
+            for (int64_t j = g.in_off[v]; j < g.in_off[v + 1]; ++j) {
+                tail_of[j] = v;
+                by_rel[rel_off[g.in_edge[j].rel]++] = j;
+            }
+        g.rel_edge.resize(T);
+        in_fill.assign(g.in_off.begin(), g.in_off.end() - 1);
+        for (const int64_t j : by_rel) {
+            const int32_t v = tail_of[j];
+            g.rel_edge[in_fill[v]++] = {g.in_edge[j].rel, (int32_t)(j - g.in_off[v]), g.in_edge[j].head};
         }
+        for (int32_t v = 0; v < N; ++v)
+            std::sort(g.out_edge.begin() + g.out_off[v], g.out_edge.begin() + g.out_off[v + 1],
+                      [](const Graph::OutEdge& x, const Graph::OutEdge& y) { return x.rel != y.rel ? x.rel < y.rel : x.tail < y.tail; });
     } catch (const std::bad_alloc&) {
         delete s;
         return NGDB_ERR_OOM;
     }
     s->seed = seed;
-    s->n_threads = n_threads;
     try {
-        if (n_threads > 1) s->workers.reset(new Workers(n_threads - 1));
-        s->coordinator = std::thread(coordinator_loop, s);
+        for (int i = 0; i < n_threads; ++i) s->threads.emplace_back(thread_loop, s);
     } catch (...) {
         delete s;
         return NGDB_ERR_OOM;
@@ -458,119 +547,37 @@ int ngdb_sampler_create(int32_t N, int32_t R, int64_t T, const int32_t* head, co
 
 void ngdb_sampler_destroy(ngdb_sampler_t* s) { delete s; }
 
-extern "C++" {
-namespace {
-// draws batch number batch_no into o (the calling thread works beside the helpers)
-int fill_batch(ngdb_sampler_s* s, uint64_t batch_no, int32_t B, int32_t K, BatchArrays& o) {
-    std::vector<int> failed;
-    try {
-        if ((int)s->queries.size() < B) s->queries.resize((size_t)B);
-        failed.assign((size_t)B, 0);
-        o.pos.assign((size_t)B, 0);
-        o.tmpl.assign((size_t)B, 0);
-        o.neg.resize((size_t)B * K);
-    } catch (const std::bad_alloc&) {
-        return NGDB_ERR_OOM;
-    }
-    std::vector<Query>& queries = s->queries;
-    auto work = [&](int lo, int hi) {
-        for (int i = lo; i < hi; ++i) {
-            Rng rng(s->seed, batch_no, (uint64_t)i);
-            const double u = rng.unit();
-            size_t t = 0;
-            while (t + 1 < s->cdf.size() && u >= s->cdf[t]) ++t;
-            o.tmpl[i] = (uint8_t)t;
-            const Template& tp = s->templates[t];
-            Query& q = queries[i];
-            bool ok = false;
-            for (int attempt = 0; attempt < 1000 && !ok; ++attempt) {
-                q.clear();
-                const int32_t v = s->g.tails[rng.below((uint64_t)s->g.T)];
-                Builder b{s->g, tp, rng, q};
-                if (b.grow((int)tp.nodes.size() - 1, v) < 0) continue;
-                b.budget = 20000;
-                if (b.contains((int)q.op.size() - 1, v) != 1) continue;   // e.g. the end point lies in a negated branch
-                o.pos[i] = v;
-                ok = true;
-            }
-            failed[i] = !ok;
-            int32_t* nrow = o.neg.data() + (size_t)i * K;
-            int k = 0;
-            for (; k + 2 <= K; k += 2) rng.below32x2((uint32_t)s->g.N, nrow + k);
-            if (k < K) nrow[k] = (int32_t)rng.below((uint64_t)s->g.N);
-        }
-    };
-    const int parts = s->workers ? std::max(1, std::min(s->workers->size() + 1, B / 32 + 1)) : 1;
-    if (parts == 1) {
-        work(0, B);
-    } else {
-        const std::function<void(int)> fn = [&](int w) {      // helper w takes part w + 1
-            if (w + 1 < parts) work((int)((int64_t)B * (w + 1) / parts), (int)((int64_t)B * (w + 2) / parts));
-        };
-        // the helpers run their parts while this thread does part 0
-        s->workers->start(fn);
-        bool oom = false;
-        try {
-            work(0, (int)((int64_t)B / parts));
-        } catch (const std::bad_alloc&) {
-            oom = true;
-        }
-        s->workers->wait();
-        if (oom) return NGDB_ERR_OOM;
-    }
-    for (int i = 0; i < B; ++i)
-        if (failed[i]) {
-            s->err = "query instantiation kept failing for template " + s->templates[o.tmpl[i]].name;
-            return NGDB_ERR_UNSUPPORTED;
-        }
-    // concatenate
-    try {
-        o.node_off.assign(1, 0);
-        o.op.clear(); o.arg.clear(); o.in_idx.clear();
-        o.in_off.assign(1, 0);
-        for (int i = 0; i < B; ++i) {
-            const Query& q = queries[i];
-            o.op.insert(o.op.end(), q.op.begin(), q.op.end());
-            o.arg.insert(o.arg.end(), q.arg.begin(), q.arg.end());
-            const int32_t base = (int32_t)o.in_idx.size();
-            o.in_idx.insert(o.in_idx.end(), q.in_idx.begin(), q.in_idx.end());
-            for (size_t n = 1; n < q.in_off.size(); ++n) o.in_off.push_back(base + q.in_off[n]);
-            o.node_off.push_back((int32_t)o.op.size());
-        }
-    } catch (const std::bad_alloc&) {
-        return NGDB_ERR_OOM;
-    }
-    return NGDB_OK;
-}
-}  // namespace
-}  // extern "C++"
-
 int ngdb_sampler_next(ngdb_sampler_t* s, int32_t B, int32_t K, ngdb_query_batch* batch, const int32_t** neg,
                       const uint8_t** template_id) {
     if (!s || !batch || B < 0 || K < 0 || (K > 0 && !neg)) return NGDB_ERR_ARG;
     const uint64_t batch_no = s->batch_no++;
     BatchArrays& o = s->out[batch_no % 3];
-    int rc;
-    bool ready = false;
-    {   // a batch read ahead by the coordinator?
-        std::unique_lock<std::mutex> lk(s->pm);
-        if (s->pf_requested) {
-            s->pcv.wait(lk, [&] { return s->pf_done; });
-            ready = s->pf_no == batch_no && s->pf_B == B && s->pf_K == K;
-            rc = s->pf_rc;
-            s->pf_requested = s->pf_done = false;
+    {
+        std::unique_lock<std::mutex> lk(s->mu);
+        auto wait = [&] {          // for the batch posted last
+            const uint64_t want = s->posts.load();
+            lk.unlock();
+            for (int i = 0; i < SPINS && s->finished.load(std::memory_order_relaxed) < want; ++i) relax();
+            lk.lock();
+            s->done.wait(lk, [&] { return s->finished.load() >= want; });
+        };
+        if (s->posted) wait();
+        if (!s->ahead || s->no != batch_no || s->B != B || s->K != K) {     // first call, or other sizes than read ahead
+            const int rc = post(s, batch_no, B, K);
+            if (rc != NGDB_OK) return rc;
+            s->work.notify_all();
+            help(s, lk);
+            if (s->posted) wait();
         }
-    }
-    if (!ready) rc = fill_batch(s, batch_no, B, K, o);     // first call, or other sizes than read ahead
-    if (rc != NGDB_OK) return rc;
-    if (s->coordinator.joinable()) {   // read ahead: the next batch with the same sizes
-        {
-            std::lock_guard<std::mutex> lk(s->pm);
-            s->pf_no = batch_no + 1; s->pf_B = B; s->pf_K = K;
-            s->pf_requested = true; s->pf_done = false;
+        s->ahead = false;
+        if (s->rc != NGDB_OK) {
+            s->err = s->draw_err;
+            return s->rc;
         }
-        s->pcv.notify_all();
+        // read ahead: the next batch with the same sizes (left to the next call if there is no memory for it)
+        s->ahead = post(s, batch_no + 1, B, K) == NGDB_OK;
     }
+    s->work.notify_all();
     batch->n_queries = B;
     batch->node_off = o.node_off.data();
     batch->op = o.op.data();
