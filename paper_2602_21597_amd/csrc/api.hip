@@ -278,6 +278,34 @@ void take_hidden_pieces(const HiddenPieces& hpc, GemmArgs* second, int n) {
     for (int i = 0; i < n; ++i) { second[i].a_pieces = hpc.at[i]; second[i].a_kt = hpc.kt; }
 }
 
+double level_flop(const ngdb_ctx_t* c, const std::vector<Segment>& segs) {
+    double rows = 0.0;
+    for (const Segment& sg : segs) rows += sg.rows;
+    return 4.0 * c->cfg.d * c->cfg.h * rows;
+}
+
+// The operators of one depth as problems of one launch (level.hip), where the MLPs are small and the depth does not have
+// very many rows. 
+bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, LevelArgs* a) {
+    if (c->cfg.family != NGDB_FAMILY_VEC || !level_fits(c->cfg.d, c->cfg.h)) return false;
+    const HostPlan& hp = pl->hp;
+    *a = LevelArgs{};
+    a->d = c->cfg.d; a->h = c->cfg.h;
+    for (const Segment& sg : segs) {
+        if (sg.type != T_INTER) {
+            if (!level_add(*a, sg.type, 0, sg.rows, 1, sg.ref_off, sg.rel_off, sg.mlp_base, sg.out_base)) return false;
+            continue;
+        }
+        for (int g = sg.g_lo; g < sg.g_hi; ++g)
+            if (!level_add(*a, sg.type, 1, hp.g_n[g], hp.g_nin[g], sg.ref_off + hp.g_mlp_base[g] - sg.mlp_base, -1, hp.g_mlp_base[g], hp.g_out_base[g])) return false;
+    }
+    for (int t = 0; t < 3; ++t) {
+        const MlpRefs W = mlp_of(c->prm, t);
+        a->mlp[t] = LevelMlp{W.Wa, W.ba, W.Wb, W.bb, ptr<float>(c->Z[t]), ptr<float>(c->H[t]), ptr<float>(c->dH[t])};
+    }
+    return true;
+}
+
 // Splits the weights of the three MLPs for a pass.  Without the buffer (a context
 // that never sized a workspace) the contractions split their B operands themselves.
 void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, PieceJobs* J) {
@@ -286,9 +314,12 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, PieceJobs* J) {
     const int d = c->cfg.d, h = c->cfg.h;
     if ((d & 3) || (h & 3)) return;   // the split reads rows as float4
     if (d < 128 && h < 128) return;   // no contraction of these widths takes the split route
-    bool narrow = true;      // every launch of the pass has a few rows only
-    for (const std::vector<Segment>& segs : pl->levels)
+    bool narrow = true;      // every launch of the pass has a few rows only, or takes whole operators
+    LevelArgs la;
+    for (const std::vector<Segment>& segs : pl->levels) {
+        if (level_problems(c, pl, segs, &la)) continue;
         for (const Segment& sg : segs) narrow = narrow && gemm_takes_rows(sg.rows, std::max(d, h));
+    }
     if (narrow) return;
     uint16_t* at = ptr<uint16_t>(c->w_pieces);
     for (int t = 0; t < 3; ++t) {
@@ -651,6 +682,16 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
     const int d = c->cfg.d, h = c->cfg.h;
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        LevelArgs la;
+        if (level_problems(c, pl, segs, &la)) {
+            la.refs = er.refs; la.rel = pl->d_rel; la.E = er.rows; la.R = c->prm.R.p;
+            la.act = w.act; la.Att = w.Att; la.out_row = w.reclaim ? pl->d_f_row : nullptr;
+            la.keep = !w.reclaim;
+            Timed tm(c, NGDB_TK_GEMM_FWD, s);
+            HIPCHK(c, launch_level(la, false, s));
+            tm.work(GEMM_FP32, level_flop(c, segs));
+            continue;
+        }
         GemmArgs g1[3], g2[3];
         int n = 0;
         for (const Segment& sg : segs) {
@@ -747,6 +788,14 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     float* dact = ptr<float>(c->dact);
     for (int l = hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        LevelArgs la;
+        if (level_problems(c, pl, segs, &la)) {
+            la.dst_row = pl->d_in_gslot; la.Att = ptr<float>(c->Att); la.dact = dact; la.dAtt = ptr<float>(c->dAtt);
+            Timed tm(c, NGDB_TK_GEMM_BWD, s);
+            HIPCHK(c, launch_level(la, true, s));
+            tm.work(GEMM_FP32, level_flop(c, segs));
+            continue;
+        }
         GemmArgs b2[3], b1[3];
         int n = 0;
         for (const Segment& sg : segs) {

@@ -285,6 +285,32 @@ hipError_t launch_dense_adam(const DenseAdamJob& job, const AdamHyper& hp, hipSt
 // loss[0] = scale * sum_i terms[i]
 hipError_t launch_loss_reduce(const float* terms, int n, float scale, float* loss, hipStream_t s);
 
+// ---------------------------------------------------------------- small models (level.hip)
+// The operators of one depth in one launch.  A problem is a projection or negation group (k = 1, pool = 0) or one class of
+// intersections (k inputs each, pool = 1): MLP rows row0 + j * n + i of type's buffers, references ref_off + j * n + i
+// (and relations rel_off + ..., -1: none), outputs out0 + i.
+// Taken up to LEVEL_WEIGHTS weights a layer (at 128 x 256 the separate launches take as long on the device and two thirds more
+// host time; beyond, the weights read by every row block cost more than the launches), and up to LEVEL_WORK = row blocks
+// x weights of a depth (512 blocks there: from 4096 queries on the separate launches are as fast, 386 against 395 us).
+constexpr int LEVEL_MAX = 10, LEVEL_WEIGHTS = 32768;
+constexpr long LEVEL_WORK = 512l * LEVEL_WEIGHTS;
+struct LevelProblem { int type, pool, n, k, ref_off, rel_off, row0, out0; };
+struct LevelMlp { const float *Wa, *ba, *Wb, *bb; float *Z, *H, *dH; };
+struct LevelArgs {
+    int count, d, h;
+    bool keep;                      // forward: inputs, hidden rows and logits are kept for a backward pass
+    int tile_start[LEVEL_MAX + 1];
+    LevelProblem p[LEVEL_MAX];
+    LevelMlp mlp[3];
+    const int32_t *refs, *rel, *out_row, *dst_row;   // out_row: row of act per output (null: itself); dst_row: of dact per reference
+    const float *E, *R;
+    float *act, *Att, *dact, *dAtt;
+};
+bool level_fits(int d, int h);
+// adds a problem; false if the launch has no room for it
+bool level_add(LevelArgs& a, int type, int pool, int n, int k, int ref_off, int rel_off, int row0, int out0);
+hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s);
+
 // ---------------------------------------------------------------- scoring (score.hip)
 struct ScoreArgs {
     const float* act;          // [n_slots, d]

@@ -1,0 +1,288 @@
+// The operators of one depth in one launch, for models whose MLPs are small: assembly of the input rows, both layers
+// and the intersection's pooling, or the reverse of it in the backward pass.
+//
+// At small widths a step is bound by its launches, not by their work: three a depth in either direction, 3 to 5 us each
+// for contractions of a few MFLOP.  A workgroup takes 16 rows (of an intersection: all inputs of 16 / k members, so
+// that the pooling needs nobody else), keeps their inputs and hidden rows in LDS and reads the weights of both
+// layers from the L2, 16 output columns at a time per wavefront, eight k-steps ahead (sixteen wavefronts: with eight and
+// six steps ahead 112 against 101 us for a forward pass at d = h = 256).  What it costs over the
+// separate launches is that every 16 rows read all weights again and that a row block's matrix work stays on one
+// compute unit.  Measured, device time of a forward pass with scoring of 256 queries (two launches a depth less, 41 -> 25 us of
+// host time) and of a training step, separate -> here: d = 32, h = 64: 60 -> 36 and 191 -> 130 us; 64, 128: 66 -> 42, 195 -> 134;
+// 100, 200: 71 -> 54, 193 -> 151; 128, 256: 70 -> 68, 204 -> 171; 200, 200: 74 -> 75, 199 -> 198; 256, 256: 75 -> 102, 192 -> 243.
+#include <algorithm>
+#include "common.h"
+
+namespace ngdb {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int LV_ROWS = 16, LV_WAVES = 16, LV_T = LV_WAVES * 64;
+constexpr int LV_AHEAD = 8;      // k-steps of 16 on the way per wavefront
+
+__host__ __device__ constexpr int lv_pitch(int n) { return (n + 15) / 16 * 16 + 4; }
+
+// One layer, out = A * W^T (BT: A * W) for the 16 rows of A in LDS; wavefront w computes the column blocks w, w + 16, ...  start()
+// requests the first weights (long before A is there), run() hands a lane's four values (rows 4 (lane / 16) .. +3 of
+// column n) to done.  Within a k-step lane group g holds k = 4g .. 4g+3 of both operands, one of them per matrix instruction.
+template <bool BT>
+struct Layer {
+    const float* W;
+    int ldw, K, N, steps, col, kg, lb, ls;
+    float4 w[LV_AHEAD];
+    __device__ __forceinline__ float4 fetch() {       // (past the last block: clamped, never used)
+        const int n = min(lb * 16 + col, N - 1), k = ls * 16 + kg, kc = min(k, K - 4);
+        float4 v;
+        if (!BT) {
+            v = *reinterpret_cast<const float4*>(W + (size_t)n * ldw + kc);
+        } else {
+            const float* p = W + (size_t)kc * ldw + n;
+            v = make_float4(p[0], p[ldw], p[2 * ldw], p[3 * ldw]);
+        }
+        if (k >= K) v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (++ls == steps) {
+            ls = 0;
+            lb += LV_WAVES;
+        }
+        return v;
+    }
+    __device__ __forceinline__ void start(const float* W_, int ldw_, int K_, int N_) {
+        W = W_; ldw = ldw_; K = K_; N = N_;
+        steps = (K + 15) / 16;
+        col = threadIdx.x & 15;
+        kg = ((threadIdx.x & 63) >> 4) * 4;
+        lb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        ls = 0;
+#pragma unroll
+        for (int q = 0; q < LV_AHEAD; ++q) w[q] = fetch();
+    }
+    template <class Done>
+    __device__ __forceinline__ void run(const float* As, int ap, Done done) {
+        int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), s = 0;
+        const int blocks = (N + 15) / 16;
+        const int total = b < blocks ? ((blocks - b + LV_WAVES - 1) / LV_WAVES) * steps : 0;
+        floatx4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+        const float* arow = As + col * ap + kg;
+        for (int t0 = 0; t0 < total; t0 += LV_AHEAD) {
+#pragma unroll
+            for (int q = 0; q < LV_AHEAD; ++q) {
+                if (t0 + q < total) {
+                    const float4 x = *reinterpret_cast<const float4*>(arow + s * 16);
+                    a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w[q].x, a0, 0, 0, 0);
+                    a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w[q].y, a1, 0, 0, 0);
+                    a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, w[q].z, a0, 0, 0, 0);
+                    a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, w[q].w, a1, 0, 0, 0);
+                    if (t0 + q + LV_AHEAD < total) w[q] = fetch();
+                    if (++s == steps) {
+                        done(b * 16 + col, a0 + a1);
+                        a0 = a1 = floatx4{0.f, 0.f, 0.f, 0.f};
+                        s = 0;
+                        b += LV_WAVES;
+                    }
+                }
+            }
+        }
+    }
+};
+
+template <bool BWD>
+__global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ int row_of[LV_ROWS], out_of[LV_ROWS], in_of[LV_ROWS];     // MLP row / output row / input reference of a tile row
+    int q = 0;
+    for (int i = 1; i < a.count; ++i)
+        if ((int)blockIdx.x >= a.tile_start[i]) q = i;
+    const LevelProblem p = a.p[q];
+    const LevelMlp w = a.mlp[p.type];
+    const int d = a.d, h = a.h, xp = lv_pitch(d), hp = lv_pitch(h), d4 = d >> 2, h4 = h >> 2;
+    float *Xs = lds, *Ls = Xs + LV_ROWS * xp, *Hs = Ls + LV_ROWS * xp, *bias = Hs + LV_ROWS * hp;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int m = LV_ROWS / p.k, i0 = ((int)blockIdx.x - a.tile_start[q]) * m;
+    const bool inter = p.pool != 0;
+    Layer<BWD> first, second;
+    if (BWD) first.start(w.Wb, h, d, h);
+    else first.start(w.Wa, d, d, h);
+    if (tid < LV_ROWS) {
+        const int j = tid / m, i = i0 + tid - j * m;
+        const bool ok = j < p.k && i < p.n;
+        const int r = j * p.n + i;
+        row_of[tid] = ok ? p.row0 + r : -1;
+        if (BWD) {
+            in_of[tid] = ok ? a.dst_row[p.ref_off + r] : 0;
+            out_of[tid] = p.out0 + min(i, p.n - 1);
+        } else {
+            const int o = p.out0 + min(i, p.n - 1);
+            out_of[tid] = a.out_row ? a.out_row[o] : o;
+        }
+    }
+    if (!BWD)
+        for (int i = tid; i < h + d; i += LV_T) bias[i] = i < h ? w.ba[i] : w.bb[i - h];
+    // rows of the tile that are no rows, and the columns that fill up the last k-step, count as zeros
+    if (!BWD) {
+        const int c4 = (xp - 4) >> 2;
+        for (int idx = tid; idx < LV_ROWS * c4; idx += LV_T) {
+            const int lr = idx / c4, c = (idx - lr * c4) * 4;
+            const int j = lr / m, i = i0 + lr - j * m;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j < p.k && i < p.n && c < d) {
+                const int r = j * p.n + i;
+                const int32_t ref = a.refs[p.ref_off + r];
+                v = *reinterpret_cast<const float4*>((ref >= 0 ? a.act + (size_t)ref * d : a.E + (size_t)(-1 - ref) * d) + c);
+                if (p.rel_off >= 0) {
+                    const float4 t = *reinterpret_cast<const float4*>(a.R + (size_t)a.rel[p.rel_off + r] * d + c);
+                    v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+                }
+                if (a.keep) *reinterpret_cast<float4*>(w.Z + (size_t)(p.row0 + r) * d + c) = v;
+            }
+            *reinterpret_cast<float4*>(Xs + lr * xp + c) = v;
+        }
+        __syncthreads();
+        first.run(Xs, xp, [&](int n, floatx4 v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int lr = (lane >> 4) * 4 + e;
+                const float y = n < h ? fmaxf(v[e] + bias[min(n, h - 1)], 0.f) : 0.f;
+                Hs[lr * hp + n] = y;
+                const int r = row_of[lr];
+                if (a.keep && r >= 0 && n < h) w.H[(size_t)r * h + n] = y;
+            }
+        });
+        second.start(w.Wb, h, h, d);
+        __syncthreads();
+        second.run(Hs, hp, [&](int n, floatx4 v) {
+            if (n >= d) return;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int lr = (lane >> 4) * 4 + e, r = row_of[lr];
+                const float y = v[e] + bias[h + n];
+                if (inter) {
+                    Ls[lr * xp + n] = y;
+                    if (a.keep && r >= 0) a.Att[(size_t)r * d + n] = y;
+                } else if (r >= 0) {
+                    a.act[(size_t)out_of[lr] * d + n] = y;
+                }
+            }
+        });
+        if (!inter) return;
+        __syncthreads();
+        for (int idx = tid; idx < m * d; idx += LV_T) {
+            const int ii = idx / d, c = idx - ii * d;
+            if (i0 + ii >= p.n) break;
+            float e[NGDB_MAX_CARD], mx = -INFINITY, den = 0.f, y = 0.f;
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                e[j] = Ls[(min(j, p.k - 1) * m + ii) * xp + c];
+                if (j < p.k) mx = fmaxf(mx, e[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                e[j] = j < p.k ? expf(e[j] - mx) : 0.f;
+                den += e[j];
+            }
+            const float inv = 1.f / den;
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) y += e[j] * inv * Xs[(min(j, p.k - 1) * m + ii) * xp + c];
+            a.act[(size_t)out_of[ii] * d + c] = y;
+        }
+        return;
+    }
+    // ---- backward: gradients of the second layer's outputs in Xs, the hidden rows (for the sign) in Hs, the direct
+    // gradient of an intersection's inputs in Ls
+    {
+        const int c4 = (xp - 4) >> 2, e4 = (hp - 4) >> 2;
+        for (int idx = tid; idx < LV_ROWS * c4; idx += LV_T) {
+            const int lr = idx / c4, c = (idx - lr * c4) * 4;
+            const int j = lr / m, i = i0 + lr - j * m;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!inter && j < p.k && i < p.n && c < d) v = *reinterpret_cast<const float4*>(a.dact + (size_t)(p.out0 + i) * d + c);
+            *reinterpret_cast<float4*>(Xs + lr * xp + c) = v;
+        }
+        for (int idx = tid; idx < LV_ROWS * e4; idx += LV_T) {
+            const int lr = idx / e4, c = (idx - lr * e4) * 4;
+            const int j = lr / m, i = i0 + lr - j * m;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j < p.k && i < p.n && c < h) v = *reinterpret_cast<const float4*>(w.H + (size_t)(p.row0 + j * p.n + i) * h + c);
+            *reinterpret_cast<float4*>(Hs + lr * hp + c) = v;
+        }
+        __syncthreads();
+        if (inter) {
+            for (int idx = tid; idx < m * d; idx += LV_T) {
+                const int ii = idx / d, c = idx - ii * d;
+                if (i0 + ii >= p.n) break;
+                float e[NGDB_MAX_CARD], x[NGDB_MAX_CARD], mx = -INFINITY, den = 0.f, tall = 0.f;
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                    const size_t at = (size_t)(p.row0 + min(j, p.k - 1) * p.n + i0 + ii) * d + c;
+                    e[j] = a.Att[at];
+                    x[j] = w.Z[at];
+                    if (j < p.k) mx = fmaxf(mx, e[j]);
+                }
+                const float dy = a.dact[(size_t)(p.out0 + i0 + ii) * d + c];
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                    e[j] = j < p.k ? expf(e[j] - mx) : 0.f;
+                    den += e[j];
+                }
+                const float inv = 1.f / den;
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j) tall += e[j] * inv * x[j] * dy;
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                    if (j < p.k) {
+                        const float wj = e[j] * inv, g = wj * (dy * x[j] - tall);
+                        Xs[(j * m + ii) * xp + c] = g;
+                        Ls[(j * m + ii) * xp + c] = wj * dy;
+                        a.dAtt[(size_t)(p.row0 + j * p.n + i0 + ii) * d + c] = g;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        first.run(Xs, xp, [&](int n, floatx4 v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int lr = (lane >> 4) * 4 + e, r = row_of[lr];
+                const float y = Hs[lr * hp + n] > 0.f ? v[e] : 0.f;       // (zero beyond h)
+                Hs[lr * hp + n] = y;
+                if (r >= 0 && n < h) w.dH[(size_t)r * h + n] = y;
+            }
+        });
+        second.start(w.Wa, d, h, d);
+        __syncthreads();
+        second.run(Hs, hp, [&](int n, floatx4 v) {
+            if (n >= d) return;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int lr = (lane >> 4) * 4 + e;
+                if (row_of[lr] >= 0) a.dact[(size_t)in_of[lr] * d + n] = v[e] + (inter ? Ls[lr * xp + n] : 0.f);
+            }
+        });
+    }
+}
+
+size_t lv_lds(int d, int h) { return ((size_t)LV_ROWS * (2 * lv_pitch(d) + lv_pitch(h)) + d + h) * sizeof(float); }
+
+}  // namespace
+
+bool level_add(LevelArgs& a, int type, int pool, int n, int k, int ref_off, int rel_off, int row0, int out0) {
+    if (n <= 0) return true;
+    if (a.count == LEVEL_MAX || k < 1 || k > NGDB_MAX_CARD) return false;
+    a.p[a.count] = LevelProblem{type, pool, n, k, ref_off, rel_off, row0, out0};
+    const int m = LV_ROWS / k;
+    a.tile_start[a.count + 1] = a.tile_start[a.count] + (n + m - 1) / m;
+    return (long)a.tile_start[++a.count] * a.d * a.h <= LEVEL_WORK;
+}
+
+bool level_fits(int d, int h) { return d <= 256 && h <= 512 && d * h <= LEVEL_WEIGHTS; }
+
+hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
+    if (a.count == 0) return hipSuccess;
+    if (!level_fits(a.d, a.h) || (a.d & 3) || (a.h & 3)) return hipErrorInvalidValue;
+    const dim3 grid(a.tile_start[a.count]);
+    if (backward) hipLaunchKernelGGL((level_kernel<true>), grid, dim3(LV_T), lv_lds(a.d, a.h), s, a);
+    else hipLaunchKernelGGL((level_kernel<false>), grid, dim3(LV_T), lv_lds(a.d, a.h), s, a);
+    return hipGetLastError();
+}
+
+}  // namespace ngdb

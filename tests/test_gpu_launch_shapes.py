@@ -104,3 +104,26 @@ def test_tables_beside_the_backward_pass(N, d, B, K, d_sem, bf16):
         assert np.array_equal(out[1][0][name], want), name
     assert out[0][1] == out[1][1]
     assert all(torch.equal(a, b) for a, b in zip(out[0][2], out[1][2]))
+
+
+# operators of a depth in one launch: widths that fill no tile, the widest hidden layer, the limit of weights a layer and
+# beyond it; one query, row blocks that are nearly empty, intersections of two to eight inputs
+@pytest.mark.parametrize("d,h,B", [(4, 4, 5), (20, 36, 1), (36, 100, 30), (64, 512, 40), (128, 256, 90), (132, 256, 40), (256, 128, 17)])
+def test_operators_of_a_depth_in_one_launch(d, h, B):
+    rng = np.random.default_rng(d)
+    N, R = 300, 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    trees = []
+    for i in range(2 * B):
+        k = 2 + i % 7
+        trees.append([proj(), proj(proj()), proj(("i",) + tuple(proj() for _ in range(k))),
+                      ("i", proj(), ("n", proj(proj()))), ("u", proj(), proj())][(i // 2) % 5])
+    case = par.Case(N, R, d, h, B, 7, 6.0, seed=d + h, trees=trees, pos=[int(x) for x in rng.integers(0, N, len(trees))])
+    par.check_forward_backward(case)
+    import torch
+    cand = rng.integers(0, N, (case.B, 9)).astype(np.int32)
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    par.assert_close(eng.score(plan, torch.from_numpy(cand).cuda()).cpu().numpy(),
+                     orank.score_candidates(case.qb, cand, om.Model(case.params, case.gamma)), "scores d=%d h=%d" % (d, h))
+    plan.free()
