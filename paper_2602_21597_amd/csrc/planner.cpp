@@ -18,7 +18,7 @@ namespace ngdb {
 namespace {
 
 struct Tree {          // node of a union-free branch (no heap: at most NGDB_MAX_CARD inputs)
-    int32_t type, arg, n_kids;
+    int32_t type, arg, n_kids;   // arg: the node of the query whose argument it takes (-1: none)
     int32_t kids[NGDB_MAX_CARD];
 };
 
@@ -52,13 +52,13 @@ struct Expander {
         const size_t first = out.size();
         switch (op) {
             case NGDB_OP_ANCHOR:
-                out.push_back(make(NGDB_OP_ANCHOR, qb.arg[n], nullptr, 0));
+                out.push_back(make(NGDB_OP_ANCHOR, j, nullptr, 0));
                 break;
             case NGDB_OP_PROJ: {
                 expand(qb.in_idx[lo], depth + 1, out);          // one projection on top of every branch of the input
                 for (size_t i = first; i < out.size() && code == NGDB_OK; ++i) {
                     const int32_t kid = out[i];
-                    out[i] = make(NGDB_OP_PROJ, qb.arg[n], &kid, 1);
+                    out[i] = make(NGDB_OP_PROJ, j, &kid, 1);
                 }
                 break;
             }
@@ -81,7 +81,7 @@ struct Expander {
                     kids[n_kids++] = out.back();                // validate() bounds the input count
                     out.pop_back();
                 }
-                out.push_back(make(op, 0, kids, n_kids));
+                out.push_back(make(op, -1, kids, n_kids));
             }
         }
         if (out.size() - first > (size_t)NGDB_MAX_BRANCH && code == NGDB_OK) {
@@ -91,7 +91,7 @@ struct Expander {
     }
 };
 
-struct Flat {   // all nodes of the batch after DNF, by global id
+struct Flat {   // nodes after DNF, numbered in post-order
     std::vector<int32_t> type, arg, level, in_off, in;
     int32_t size() const { return (int32_t)type.size(); }
     int32_t add(int32_t t, int32_t a, int32_t lvl, const int32_t* ins, int32_t n_ins) {
@@ -114,47 +114,6 @@ int32_t number_postorder(const std::vector<Tree>& pool, int32_t t, Flat& flat) {
         lvl = std::max(lvl, flat.level[ins[k]] + 1);
     }
     return flat.add(node.type, node.arg, lvl, ins, node.n_kids);
-}
-
-// A union-free query whose nodes already stand in depth-first post-order, every node used once (what
-// samplers write): its nodes are appended as they are.  Returns the root, or -1 (nothing appended) for any
-// other query.  The nodes not yet consumed form a stack; a node's inputs must be its topmost entries in order.
-int32_t append_in_order(const ngdb_query_batch& qb, int32_t lo, int32_t hi, Flat& flat) {
-    constexpr int32_t DEEP = 64;
-    int32_t stack[DEEP];
-    int32_t top = 0;
-    for (int32_t n = lo; n < hi; ++n) {
-        if (qb.op[n] == NGDB_OP_UNION) return -1;
-        const int32_t a = qb.in_off[n], m = qb.in_off[n + 1] - a;
-        if (m > top) return -1;
-        top -= m;
-        for (int32_t k = 0; k < m; ++k)
-            if (qb.in_idx[a + k] != stack[top + k]) return -1;
-        if (top == DEEP) return -1;
-        stack[top++] = n - lo;
-    }
-    if (top != 1) return -1;
-    const int32_t base = flat.size(), shift = base - lo, in_lo = qb.in_off[lo], in_shift = (int32_t)flat.in.size() - in_lo;
-    const size_t n_new = (size_t)(hi - lo), n_in = (size_t)(qb.in_off[hi] - in_lo);
-    flat.type.resize(base + n_new);
-    flat.arg.resize(base + n_new);
-    flat.level.resize(base + n_new);
-    flat.in_off.resize(base + n_new + 1);
-    flat.in.resize(flat.in.size() + n_in);
-    for (int32_t n = lo; n < hi; ++n) {
-        const int32_t g = n + shift, op = qb.op[n];
-        flat.type[g] = op;
-        flat.arg[g] = op == NGDB_OP_ANCHOR || op == NGDB_OP_PROJ ? qb.arg[n] : 0;
-        int32_t lvl = 0;
-        for (int32_t k = qb.in_off[n]; k < qb.in_off[n + 1]; ++k) {
-            const int32_t kid = qb.in_idx[k] + base;
-            flat.in[k + in_shift] = kid;
-            lvl = std::max(lvl, flat.level[kid] + 1);
-        }
-        flat.level[g] = lvl;
-        flat.in_off[g + 1] = qb.in_off[n + 1] + in_shift;
-    }
-    return base + (hi - lo) - 1;
 }
 
 // Max-Fillness schedule (Alg. 1 without the gradient nodes, which mirror it): returns the step
@@ -215,7 +174,8 @@ void max_fillness_steps(const Flat& flat, int32_t b_max, std::vector<int32_t>& s
     }
 }
 
-int validate(const ngdb_query_batch& qb, int32_t N, int32_t R, std::string& err) {
+// Checks the queries q_lo .. q_hi - 1 (and the batch as a whole).
+int validate(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t q_lo, int32_t q_hi, std::string& err) {
     if (qb.n_queries < 0) { err = "n_queries < 0"; return NGDB_ERR_ARG; }
     if (qb.n_queries == 0) return NGDB_OK;
     if (!qb.node_off || !qb.op || !qb.arg || !qb.in_off || !qb.pos) {
@@ -223,7 +183,7 @@ int validate(const ngdb_query_batch& qb, int32_t N, int32_t R, std::string& err)
         return NGDB_ERR_ARG;
     }
     if (qb.node_off[0] != 0 || qb.in_off[0] != 0) { err = "offsets must start at 0"; return NGDB_ERR_ARG; }
-    for (int32_t q = 0; q < qb.n_queries; ++q) {
+    for (int32_t q = q_lo; q < q_hi; ++q) {
         const int32_t lo = qb.node_off[q], hi = qb.node_off[q + 1];
         if (hi <= lo) { err = "query without nodes"; return NGDB_ERR_ARG; }
         if (qb.pos[q] < 0 || qb.pos[q] >= N) { err = "positive entity id out of range"; return NGDB_ERR_RANGE; }
@@ -265,36 +225,178 @@ int validate(const ngdb_query_batch& qb, int32_t N, int32_t R, std::string& err)
     return NGDB_OK;
 }
 
-// order = positions 0..n-1 sorted stably by key[position], keys in [0, key_bound): a counting
-// sort where the key range allows it (the keys here are small composites), else a merge sort.
-void stable_order_by_key(const std::vector<int32_t>& key, int64_t key_bound, std::vector<int32_t>& order) {
+// Stable grouping of values by key (keys in [0, key_bound)): the keys that occur in ascending order, segment offsets, and
+// the values segment by segment in input order.  A counting sort where the key range allows it, else a merge sort.
+void group_by_key(const std::vector<int32_t>& key, int32_t key_bound, const std::vector<int32_t>& value, std::vector<int32_t>& uniq,
+                  std::vector<int32_t>& seg_off, std::vector<int32_t>& grouped) {
     const size_t n = key.size();
-    order.resize(n);
-    if (key_bound <= (int64_t)(4 * n + 1024)) {
-        std::vector<int32_t> start((size_t)key_bound + 1, 0);
-        for (size_t i = 0; i < n; ++i) ++start[key[i] + 1];
-        for (int64_t k = 0; k < key_bound; ++k) start[k + 1] += start[k];
-        for (size_t i = 0; i < n; ++i) order[start[key[i]]++] = (int32_t)i;
-        return;
-    }
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return key[a] < key[b]; });
-}
-
-// Stable grouping of `keys` (values < n_keys): unique keys ascending, segment
-// offsets, and the permutation that lists each segment's members in input order.
-void segment_index(const std::vector<int32_t>& keys, int32_t n_keys, std::vector<int32_t>& uniq,
-                   std::vector<int32_t>& seg_off, std::vector<int32_t>& order) {
-    stable_order_by_key(keys, n_keys, order);
     uniq.clear();
     seg_off.clear();
-    for (size_t i = 0; i < order.size(); ++i)
-        if (i == 0 || keys[order[i]] != keys[order[i - 1]]) {
-            uniq.push_back(keys[order[i]]);
-            seg_off.push_back((int32_t)i);
+    grouped.resize(n);
+    if (key_bound <= (int64_t)(4 * n + 1024)) {
+        std::vector<int32_t> at((size_t)key_bound, 0);
+        for (size_t i = 0; i < n; ++i) ++at[key[i]];
+        int32_t sum = 0;
+        for (int32_t k = 0; k < key_bound; ++k) {
+            const int32_t c = at[k];
+            at[k] = sum;
+            if (c == 0) continue;
+            uniq.push_back(k);
+            seg_off.push_back(sum);
+            sum += c;
         }
-    seg_off.push_back((int32_t)order.size());
+        for (size_t i = 0; i < n; ++i) grouped[at[key[i]]++] = value[i];
+    } else {
+        std::vector<int32_t> order(n);
+        std::iota(order.begin(), order.end(), 0);
+        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return key[a] < key[b]; });
+        for (size_t i = 0; i < n; ++i) {
+            if (i == 0 || key[order[i]] != key[order[i - 1]]) {
+                uniq.push_back(key[order[i]]);
+                seg_off.push_back((int32_t)i);
+            }
+            grouped[i] = value[order[i]];
+        }
+    }
+    seg_off.push_back((int32_t)n);
 }
+
+// A structure of queries: everything the plan needs to know of a query but its arguments.  A batch has thousands of
+// queries and few structures, so each is checked, expanded (DNF) and numbered once and the queries only look up theirs:
+// expanding and checking every query by itself was more than half of the planner's time, most of it mispredicted branches
+// (450 us for 4096 queries of 14 structures, 50 for 512; 170 and 30 now).
+struct Shape {
+    uint64_t ops, n_ins;                 // four bits a node: operator, input count
+    int32_t n, m, in0;                   // nodes and inputs as given; its inputs in given_in
+    int32_t count;                       // queries
+    // ranges of the table's arrays
+    struct Range { int32_t at, n; } node, op, ref, anchor, root, ent, rel;
+};
+
+// The structures of a batch and their nodes (numbered from 0 in each structure).
+struct ShapeTable {
+    static constexpr int SLOTS = 256;
+    static constexpr int32_t NODES = 16, INPUTS = 32;      // of the queries that are looked up; larger ones get a structure each
+    struct Op { int32_t node, cls, rel; };            // an operator, its class; rel: node of the query that names the relation (-1: none)
+    struct Ref { int32_t op, k, kid; };               // input k of the op-th operator is node kid
+    std::vector<Shape> shapes;
+    Flat flat;                           // arg: node of the query; in: numbered over all structures
+    std::vector<Op> op;
+    std::vector<Ref> ref;
+    std::vector<int32_t> anchor, root, ent, rel, given_in;  // ent, rel: nodes of the query whose arguments are entities, relations
+    std::vector<Tree> pool;              // scratch
+    std::vector<int32_t> branches;
+    int16_t slot[SLOTS];
+
+    ShapeTable() {
+        std::fill(slot, slot + SLOTS, (int16_t)-1);
+        shapes.reserve(32);
+        flat.type.reserve(256); flat.arg.reserve(256); flat.level.reserve(256); flat.in_off.reserve(257); flat.in.reserve(256);
+        flat.in_off.push_back(0);
+        op.reserve(256); ref.reserve(256);
+        anchor.reserve(128); root.reserve(64); ent.reserve(128); rel.reserve(128); given_in.reserve(256);
+        pool.reserve(32); branches.reserve(16);
+    }
+    int32_t level(const Shape& sh, const Op& o) const { return flat.level[sh.node.at + o.node]; }
+    int32_t type(const Shape& sh, int32_t node) const { return flat.type[sh.node.at + node]; }
+    int32_t nin(const Shape& sh, const Op& o) const { return flat.nin(sh.node.at + o.node); }
+
+    // The structure of query q, or -1 if it is new: key then holds what it looks like and *at its free place among
+    // the slots, or -1 if it is not to be looked up.  A query that is found passes every check but those of its arguments and
+    // its positive.
+    int32_t find(const ngdb_query_batch& qb, int32_t q, Shape& key, int32_t* at) const {
+        const int32_t lo = qb.node_off[q], n = qb.node_off[q + 1] - lo;
+        *at = -1;
+        if (n < 1 || n > NODES) return -1;
+        uint64_t ops = 0, n_ins = 0;
+        uint32_t large = 0;
+        const int32_t in_lo = qb.in_off[lo];
+        int32_t before = in_lo;
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t next = qb.in_off[lo + i + 1];
+            const uint32_t o = qb.op[lo + i], e = (uint32_t)next - (uint32_t)before;
+            before = next;
+            large |= o | e;
+            ops |= (uint64_t)(o & 15u) << (4 * i);
+            n_ins |= (uint64_t)(e & 15u) << (4 * i);
+        }
+        if (large > 15u) return -1;
+        const int32_t m = before - in_lo;
+        if (m > INPUTS || (m > 0 && !qb.in_idx)) return -1;
+        const int32_t* in = qb.in_idx + in_lo;
+        int32_t h = (int32_t)((ops * 0x9E3779B97F4A7C15ull ^ n_ins * 0xC2B2AE3D27D4EB4Full) >> 56);
+        for (int probe = 0; probe < 8; ++probe, h = (h + 1) & (SLOTS - 1)) {
+            const int32_t s = slot[h];
+            if (s < 0) {
+                *at = h;
+                key.ops = ops; key.n_ins = n_ins; key.n = n; key.m = m;
+                return -1;
+            }
+            const Shape& c = shapes[s];
+            if (c.ops != ops || c.n_ins != n_ins || c.n != n) continue;
+            const int32_t* want = given_in.data() + c.in0;
+            int32_t differ = 0;
+            for (int32_t k = 0; k < m; ++k) differ |= want[k] ^ in[k];
+            if (differ == 0) return s;
+        }
+        return -1;
+    }
+
+    // Adds the structure of query q, which has been validated; its number in *s.
+    int add(const ngdb_query_batch& qb, int32_t q, Shape sh, int32_t at, int32_t* s, std::string& err) {
+        const int32_t lo = qb.node_off[q], hi = qb.node_off[q + 1];
+        pool.clear();
+        branches.clear();
+        Expander ex{qb, lo, hi - lo, pool, err};
+        ex.expand(ex.n_local - 1, 0, branches);
+        if (ex.code != NGDB_OK) return ex.code;
+        sh.count = 0;
+        sh.in0 = (int32_t)given_in.size();
+        given_in.insert(given_in.end(), qb.in_idx + qb.in_off[lo], qb.in_idx + qb.in_off[hi]);
+        const int32_t base = flat.size();
+        auto open = [](const auto& v) { return Shape::Range{(int32_t)v.size(), 0}; };
+        auto close = [](Shape::Range& r, const auto& v) { r.n = (int32_t)v.size() - r.at; };
+        sh.root = open(root); sh.op = open(op); sh.ref = open(ref); sh.anchor = open(anchor); sh.ent = open(ent); sh.rel = open(rel);
+        for (const int32_t b : branches) {
+            if (pool[b].type == NGDB_OP_ANCHOR) {
+                err = "a query must contain at least one operator";
+                return NGDB_ERR_UNSUPPORTED;
+            }
+            const int32_t g = number_postorder(pool, b, flat);
+            if (flat.level[g] > NGDB_MAX_LEVELS) {
+                err = "query deeper than NGDB_MAX_LEVELS";
+                return NGDB_ERR_UNSUPPORTED;
+            }
+            root.push_back(g - base);
+        }
+        for (int32_t g = base; g < flat.size(); ++g) {
+            if (flat.type[g] == NGDB_OP_ANCHOR) {
+                anchor.push_back(g - base);
+                continue;
+            }
+            const int32_t i = (int32_t)op.size() - sh.op.at;
+            for (int32_t k = 0; k < flat.nin(g); ++k) ref.push_back({i, k, flat.in[flat.in_off[g] + k] - base});
+            op.push_back({g - base, 0, flat.type[g] == NGDB_OP_PROJ ? flat.arg[g] : -1});
+        }
+        for (int32_t n = lo; n < hi; ++n) {
+            if (qb.op[n] == NGDB_OP_ANCHOR) ent.push_back(n - lo);
+            if (qb.op[n] == NGDB_OP_PROJ) rel.push_back(n - lo);
+        }
+        sh.node = {base, flat.size() - base};
+        close(sh.root, root); close(sh.op, op); close(sh.ref, ref); close(sh.anchor, anchor); close(sh.ent, ent); close(sh.rel, rel);
+        *s = (int32_t)shapes.size();
+        shapes.push_back(sh);
+        if (at >= 0 && *s <= INT16_MAX) slot[at] = (int16_t)*s;
+        return NGDB_OK;
+    }
+};
+template <class V>
+struct Span {            // a range of one of the table's arrays
+    const V *b, *e;
+    Span(const std::vector<V>& v, Shape::Range r) : b(v.data() + r.at), e(b + r.n) {}
+    const V* begin() const { return b; }
+    const V* end() const { return e; }
+};
 
 }  // namespace
 
@@ -304,73 +406,81 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
         err = "unknown schedule or negative b_max";
         return NGDB_ERR_ARG;
     }
-    int rc = validate(qb, N, R, err);
+    int rc = validate(qb, N, R, 0, 0, err);
     if (rc != NGDB_OK) return rc;
     P = HostPlan{};
     const int32_t B = qb.n_queries;
     P.n_queries = B;
-    P.pos.assign(qb.pos, qb.pos + B);
 
-    // 1. DNF + global numbering
-    Flat flat;
-    const size_t n_given = B > 0 ? (size_t)qb.node_off[B] : 0, guess = n_given + n_given / 4 + 16;
-    flat.type.reserve(guess);
-    flat.arg.reserve(guess);
-    flat.level.reserve(guess);
-    flat.in_off.reserve(guess + 1);
-    flat.in.reserve(guess);
-    flat.in_off.push_back(0);
-    std::vector<int32_t> root_node;          // roots of all queries, P.root_off delimits them
-    root_node.reserve((size_t)B + B / 4 + 16);
-    P.root_off.reserve((size_t)B + 1);
-    P.root_off.push_back(0);
-    std::vector<Tree> pool;
-    std::vector<int32_t> branches;
+    // 1. the structure of every query (DNF + numbering), its arguments checked
+    ShapeTable tab;
+    std::vector<int32_t> shape_of(B);
+    P.root_off.resize((size_t)B + 1);
+    P.root_off[0] = 0;
     for (int32_t q = 0; q < B; ++q) {
-        const int32_t lo = qb.node_off[q], hi = qb.node_off[q + 1];
-        int32_t g = append_in_order(qb, lo, hi, flat);
-        const bool in_order = g >= 0;
-        if (!in_order) {
-            pool.clear();
-            Expander ex{qb, lo, hi - lo, pool, err};
-            branches.clear();
-            ex.expand(ex.n_local - 1, 0, branches);
-            if (ex.code != NGDB_OK) return ex.code;
-        }
-        const size_t n_branch = in_order ? 1 : branches.size();
-        for (size_t b = 0; b < n_branch; ++b) {
-            if ((in_order ? flat.type[g] : pool[branches[b]].type) == NGDB_OP_ANCHOR) {
-                err = "a query must contain at least one operator";
-                return NGDB_ERR_UNSUPPORTED;
+        Shape key;
+        int32_t at, s = tab.find(qb, q, key, &at);
+        bool bad = (uint32_t)qb.pos[q] >= (uint32_t)N;
+        if (s < 0) {
+            std::string why;
+            int code = validate(qb, N, R, q, q + 1, why);
+            if (code == NGDB_OK) code = tab.add(qb, q, key, at, &s, why);
+            if (code != NGDB_OK) {           // what is wrong with any query outranks what is not supported
+                rc = validate(qb, N, R, 0, B, err);
+                if (rc != NGDB_OK) return rc;
+                err = why;
+                return code;
             }
-            if (!in_order) g = number_postorder(pool, branches[b], flat);
-            if (flat.level[g] > NGDB_MAX_LEVELS) {
-                err = "query deeper than NGDB_MAX_LEVELS";
-                return NGDB_ERR_UNSUPPORTED;
-            }
-            root_node.push_back(g);
+        } else {
+            const int32_t* arg = qb.arg + qb.node_off[q];
+            for (const int32_t n : Span(tab.ent, tab.shapes[s].ent)) bad |= (uint32_t)arg[n] >= (uint32_t)N;
+            for (const int32_t n : Span(tab.rel, tab.shapes[s].rel)) bad |= (uint32_t)arg[n] >= (uint32_t)R;
         }
-        P.root_off.push_back((int32_t)root_node.size());
-        P.max_branch = std::max<int32_t>(P.max_branch, (int32_t)n_branch);
+        if (bad) return validate(qb, N, R, 0, B, err);
+        Shape& sh = tab.shapes[s];
+        ++sh.count;
+        shape_of[q] = s;
+        P.root_off[q + 1] = P.root_off[q] + sh.root.n;
     }
-    const int32_t n_nodes = flat.size();
+    P.pos.assign(qb.pos, qb.pos + B);
+    int32_t n_nodes = 0, n_anchor = 0, n_ref = 0, max_level = 0;
+    for (const Shape& sh : tab.shapes) {
+        n_nodes += sh.count * sh.node.n;
+        n_anchor += sh.count * sh.anchor.n;
+        n_ref += sh.count * sh.ref.n;
+        for (const ShapeTable::Op& o : Span(tab.op, sh.op)) max_level = std::max(max_level, tab.level(sh, o));
+        P.max_branch = std::max(P.max_branch, sh.root.n);
+    }
+    P.n_anchor = n_anchor;
+    P.n_slots = n_nodes - n_anchor;
+    P.n_roots = P.root_off[B];
 
     // 1b. execution step of every operator: its depth, or its Max-Fillness step.  From here
     // on "level" means execution step.  The eager-reclamation peak of the level-synchronous
     // order is computed the same way: outputs of a step appear, then their inputs die.
+    std::vector<int32_t> step;               // Max-Fillness: of every node
+    int32_t top_level = max_level;
     if (schedule == NGDB_SCHED_MAX_FILL) {
-        std::vector<int32_t> step;
-        max_fillness_steps(flat, b_max, step, P.peak_live);
-        flat.level = step;
+        Flat all;
+        all.type.reserve(n_nodes); all.in.reserve(n_ref); all.in_off.reserve(n_nodes + 1);
+        all.in_off.push_back(0);
+        for (int32_t q = 0; q < B; ++q) {
+            const Shape& sh = tab.shapes[shape_of[q]];
+            const int32_t base = all.size();
+            for (int32_t g = sh.node.at; g < sh.node.at + sh.node.n; ++g) {
+                all.type.push_back(tab.flat.type[g]);
+                for (int32_t k = tab.flat.in_off[g]; k < tab.flat.in_off[g + 1]; ++k) all.in.push_back(tab.flat.in[k] - sh.node.at + base);
+                all.in_off.push_back((int32_t)all.in.size());
+            }
+        }
+        max_fillness_steps(all, b_max, step, P.peak_live);
+        for (const int32_t l : step) top_level = std::max(top_level, l);
     } else {
-        int32_t max_level = 0;
-        for (int32_t g = 0; g < n_nodes; ++g) max_level = std::max(max_level, flat.level[g]);
         std::vector<int32_t> born(max_level + 2, 0), dead(max_level + 2, 0);
-        for (int32_t g = 0; g < n_nodes; ++g) {
-            if (flat.type[g] == NGDB_OP_ANCHOR) continue;
-            ++born[flat.level[g]];
-            for (int32_t k = flat.in_off[g]; k < flat.in_off[g + 1]; ++k)
-                if (flat.type[flat.in[k]] != NGDB_OP_ANCHOR) ++dead[flat.level[g]];
+        for (const Shape& sh : tab.shapes) {
+            for (const ShapeTable::Op& o : Span(tab.op, sh.op)) born[tab.level(sh, o)] += sh.count;
+            for (const ShapeTable::Ref& r : Span(tab.ref, sh.ref))
+                if (tab.type(sh, r.kid) != NGDB_OP_ANCHOR) dead[tab.level(sh, tab.op[sh.op.at + r.op])] += sh.count;
         }
         int32_t live = 0;
         for (int32_t l = 1; l <= max_level; ++l) {
@@ -380,59 +490,46 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
         }
     }
 
-    // 2. anchors, and the class (type, level, input count) of every operator: a counting sort by class
-    // gives the slots (type-major, then level, input count, node id)
+    // 2. the class (type, level, input count) of every operator; the classes in order (type-major, then level, input
+    // count) give the slots, a class's in node order
     auto type_rank = [](int32_t t) { return t == NGDB_OP_PROJ ? 0 : (t == NGDB_OP_INTER ? 1 : 2); };
-    int32_t top_level = 0, n_anchor = 0;
-    for (int32_t g = 0; g < n_nodes; ++g) {
-        top_level = std::max(top_level, flat.level[g]);
-        n_anchor += flat.type[g] == NGDB_OP_ANCHOR ? 1 : 0;
-    }
-    P.n_anchor = n_anchor;
-    P.n_slots = n_nodes - n_anchor;
     const int64_t n_lvl = (int64_t)top_level + 1, n_card = NGDB_MAX_CARD + 1;
     const int64_t n_class = 3 * n_lvl * n_card;
     if (n_class > INT32_MAX) {
         err = "too many execution steps";
         return NGDB_ERR_UNSUPPORTED;
     }
-    std::vector<int32_t> place(n_nodes);     // anchors: their number; operators: first their class, then their slot
+    auto class_of = [&](int32_t t, int32_t level, int32_t nin) { return (int32_t)((type_rank(t) * n_lvl + level) * n_card + nin); };
     std::vector<int32_t> start((size_t)n_class + 1, 0);
-    P.anchor_ent.resize(n_anchor);
-    int32_t at_anchor = 0;
-    for (int32_t g = 0; g < n_nodes; ++g) {
-        const int32_t t = flat.type[g];
-        if (t == NGDB_OP_ANCHOR) {
-            P.anchor_ent[at_anchor] = flat.arg[g];
-            place[g] = at_anchor++;
-        } else {
-            const int32_t c = (int32_t)((type_rank(t) * n_lvl + flat.level[g]) * n_card + flat.nin(g));
-            place[g] = c;
-            ++start[c + 1];
+    for (const Shape& sh : tab.shapes)
+        for (int32_t i = sh.op.at; i < sh.op.at + sh.op.n; ++i) {
+            ShapeTable::Op& o = tab.op[i];
+            o.cls = class_of(tab.type(sh, o.node), tab.level(sh, o), tab.nin(sh, o));
+            if (step.empty()) start[o.cls + 1] += sh.count;
+        }
+    std::vector<int32_t> cls;                // Max-Fillness: of every operator, in node order
+    if (!step.empty()) {
+        cls.reserve(P.n_slots);
+        int32_t base = 0;
+        for (int32_t q = 0; q < B; ++q) {
+            const Shape& sh = tab.shapes[shape_of[q]];
+            for (const ShapeTable::Op& o : Span(tab.op, sh.op)) {
+                cls.push_back(class_of(tab.type(sh, o.node), step[base + o.node], tab.nin(sh, o)));
+                ++start[cls.back() + 1];
+            }
+            base += sh.node.n;
         }
     }
     for (int64_t c = 0; c < n_class; ++c) start[c + 1] += start[c];
     P.n_proj = start[n_lvl * n_card];
     P.n_inter = start[2 * n_lvl * n_card] - P.n_proj;
     P.n_neg = P.n_slots - P.n_proj - P.n_inter;
-    std::vector<int32_t> by_slot(P.n_slots);
-    {
-        std::vector<int32_t> next(start.begin(), start.end() - 1);
-        for (int32_t g = 0; g < n_nodes; ++g)
-            if (flat.type[g] != NGDB_OP_ANCHOR) {
-                const int32_t sl = next[place[g]]++;
-                by_slot[sl] = g;
-                place[g] = sl;
-            }
-    }
     const int32_t type_base[3] = {0, P.n_proj, P.n_proj + P.n_inter};
-    auto is_anchor = [&](int32_t g) { return flat.type[g] == NGDB_OP_ANCHOR; };
-    auto grad_row = [&](int32_t g) { return is_anchor(g) ? P.n_slots + place[g] : place[g]; };
 
     // 3. groups: the classes that have members, by level, type, input count; members are a class's slots
-    P.in_ref.reserve(flat.in.size());
-    P.in_gslot.reserve(flat.in.size());
-    P.rel.reserve(P.n_proj);
+    struct Class { int32_t next, ref0, n; };             // next slot; reference k of slot s is at ref0 + k * n + s
+    std::vector<Class> at_class(n_class);
+    int32_t ref_off = 0;
     for (int64_t l = 1; l < n_lvl; ++l)
         for (int32_t tr = 0; tr < 3; ++tr)
             for (int32_t nin = 1; nin < n_card; ++nin) {
@@ -445,48 +542,72 @@ int build_plan(const ngdb_query_batch& qb, int32_t N, int32_t R, int32_t schedul
                 P.g_nin.push_back(nin);
                 P.g_n.push_back(n);
                 P.g_out_base.push_back(s0);
-                P.g_ref_off.push_back((int32_t)P.in_ref.size());
+                P.g_ref_off.push_back(ref_off);
                 if (t == NGDB_OP_INTER) {
                     P.g_mlp_base.push_back(P.n_int_rows);
                     P.n_int_rows += n * nin;
                 } else {
                     P.g_mlp_base.push_back(s0 - type_base[tr]);
                 }
-                P.g_rel_off.push_back(t == NGDB_OP_PROJ ? (int32_t)P.rel.size() : -1);
-                for (int32_t k = 0; k < nin; ++k)
-                    for (int32_t m = s0; m < s0 + n; ++m) {
-                        const int32_t kid = flat.in[flat.in_off[by_slot[m]] + k];
-                        const bool leaf = is_anchor(kid);
-                        P.in_ref.push_back(leaf ? -1 - flat.arg[kid] : place[kid]);
-                        P.in_gslot.push_back(leaf ? P.n_slots + place[kid] : place[kid]);
-                    }
-                if (t == NGDB_OP_PROJ)
-                    for (int32_t m = s0; m < s0 + n; ++m) P.rel.push_back(flat.arg[by_slot[m]]);
+                P.g_rel_off.push_back(t == NGDB_OP_PROJ ? s0 : -1);      // (projections have the first slots)
+                at_class[c] = Class{s0, ref_off - s0, n};
+                ref_off += n * nin;
             }
+    P.in_ref.resize(n_ref);
+    P.in_gslot.resize(n_ref);
+    P.rel.resize(P.n_proj);
+    P.anchor_ent.resize(n_anchor);
+    P.root_slot.resize(P.n_roots);
+    {
+        int32_t widest = 1;
+        for (const Shape& sh : tab.shapes) widest = std::max(widest, sh.node.n);
+        struct Place { int32_t ref, grad; };             // how operators refer to a node, and its gradient row
+        std::vector<Place> place(widest);
+        struct Out { int32_t at, stride; };
+        std::vector<Out> out(widest);                    // where an operator's references go
+        int32_t a = 0, r = 0;
+        const int32_t* own = cls.data();
+        for (int32_t q = 0; q < B; ++q) {
+            const Shape& sh = tab.shapes[shape_of[q]];
+            const int32_t* arg = qb.arg + qb.node_off[q];
+            const int32_t* src = tab.flat.arg.data() + sh.node.at;
+            for (const int32_t g : Span(tab.anchor, sh.anchor)) {
+                const int32_t e = arg[src[g]];
+                P.anchor_ent[a] = e;
+                place[g] = Place{-1 - e, P.n_slots + a++};
+            }
+            const ShapeTable::Op* op = tab.op.data() + sh.op.at;
+            for (int32_t i = 0; i < sh.op.n; ++i) {
+                const ShapeTable::Op& o = op[i];
+                Class& c = at_class[step.empty() ? o.cls : own[i]];
+                const int32_t s = c.next++;
+                place[o.node] = Place{s, s};
+                out[i] = Out{c.ref0 + s, c.n};
+                if (o.rel >= 0) P.rel[s] = arg[o.rel];
+            }
+            for (const ShapeTable::Ref& x : Span(tab.ref, sh.ref)) {
+                const int32_t at = out[x.op].at + x.k * out[x.op].stride;
+                P.in_ref[at] = place[x.kid].ref;
+                P.in_gslot[at] = place[x.kid].grad;
+            }
+            for (const int32_t g : Span(tab.root, sh.root)) P.root_slot[r++] = place[g].ref;
+            if (!step.empty()) own += sh.op.n;
+        }
+    }
     P.n_groups = (int32_t)P.g_level.size();
     P.n_levels = P.n_groups ? P.g_level.back() : 0;
     P.lvl_off.assign(P.n_levels + 2, 0);
     for (int32_t l : P.g_level) P.lvl_off[l + 1] += 1;
     for (size_t l = 1; l < P.lvl_off.size(); ++l) P.lvl_off[l] += P.lvl_off[l - 1];
 
-    // 4. roots
-    P.n_roots = (int32_t)root_node.size();
-    P.root_slot.resize(P.n_roots);
-    for (int32_t i = 0; i < P.n_roots; ++i) P.root_slot[i] = place[root_node[i]];
+    // 4. relation gradient index over the projections in slot order
+    std::vector<int32_t> rsrc(P.n_proj);
+    for (int32_t g = 0; g < P.n_groups; ++g)
+        if (P.g_type[g] == NGDB_OP_PROJ)
+            std::copy_n(P.in_gslot.begin() + P.g_ref_off[g], P.g_n[g], rsrc.begin() + P.g_out_base[g]);
+    group_by_key(P.rel, R, rsrc, P.r_uniq, P.r_seg_off, P.r_src);
 
-    // 5. relation gradient index over the projections in slot order
-    std::vector<int32_t> order;
-    std::vector<int32_t> rkeys(P.n_proj), rsrc(P.n_proj);
-    for (int32_t s = 0; s < P.n_proj; ++s) {
-        const int32_t g = by_slot[s];
-        rkeys[s] = flat.arg[g];
-        rsrc[s] = grad_row(flat.in[flat.in_off[g]]);
-    }
-    segment_index(rkeys, R, P.r_uniq, P.r_seg_off, order);
-    P.r_src.resize(P.n_proj);
-    for (int32_t s = 0; s < P.n_proj; ++s) P.r_src[s] = rsrc[order[s]];
-
-    // 6. rows of a forward-only pass under eager reference counting (Sec. 4.3, Reclaim(T); Alg. 1,
+    // 5. rows of a forward-only pass under eager reference counting (Sec. 4.3, Reclaim(T); Alg. 1,
     // DecrementRefCounts): the steps in order; every output of a step takes, in group and member
     // order, the lowest free row (a new one if none is free); when the step has run, the rows of
     // the outputs it consumed are free again.  Every output has one consumer (queries are trees);
