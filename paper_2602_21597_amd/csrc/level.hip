@@ -103,6 +103,8 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
     Layer<BWD> first, second;
     if (BWD) first.start(w.Wb, h, d, h);
     else first.start(w.Wa, d, d, h);
+    if (BWD) second.start(w.Wa, d, h, d);
+    else second.start(w.Wb, h, h, d);
     if (tid < LV_ROWS) {
         const int j = tid / m, i = i0 + tid - j * m;
         const bool ok = j < p.k && i < p.n;
@@ -148,7 +150,6 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                 if (a.keep && r >= 0 && n < h) w.H[(size_t)r * h + n] = y;
             }
         });
-        second.start(w.Wb, h, h, d);
         __syncthreads();
         second.run(Hs, hp, [&](int n, floatx4 v) {
             if (n >= d) return;
@@ -248,7 +249,6 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                 if (r >= 0 && n < h) w.dH[(size_t)r * h + n] = y;
             }
         });
-        second.start(w.Wa, d, h, d);
         __syncthreads();
         second.run(Hs, hp, [&](int n, floatx4 v) {
             if (n >= d) return;
