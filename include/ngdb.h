@@ -492,6 +492,10 @@ int ngdb_copy_to_host(void* h_dst, const void* d_src, size_t bytes);
  * declared maxima of ngdb_config.                                                              */
 int64_t ngdb_debug_alloc_count(const ngdb_ctx_t* ctx);
 
+/* From how many coordinate differences (branch rows x entities x d) on the rankings of this context go through the
+ * integer filter; negative: the library's own choice.  For tests of the filter at sizes below that.   */
+int ngdb_debug_rank_filter_from(ngdb_ctx_t* ctx, int64_t work);
+
 int64_t ngdb_step_count(const ngdb_ctx_t* ctx);
 const char* ngdb_strerror(int code);
 const char* ngdb_last_error(const ngdb_ctx_t* ctx);   /* text of the last failure on ctx */

@@ -118,6 +118,7 @@ def load_library(path=LIB_PATH):
         "ngdb_copy_to_host": (C.c_int, [vp, vp, C.c_size_t]),
         "ngdb_step_count": (i64, [vp]),
         "ngdb_debug_alloc_count": (i64, [vp]),
+        "ngdb_debug_rank_filter_from": (C.c_int, [vp, i64]),
         "ngdb_strerror": (C.c_char_p, [C.c_int]),
         "ngdb_last_error": (C.c_char_p, [vp]),
     }
@@ -142,13 +143,18 @@ def _i32(a):
     return np.ascontiguousarray(a, np.int32)
 
 
+def _address(a):
+    """Address of an array's data (a third of what a.ctypes costs, where the array can be written)."""
+    return C.addressof(C.c_char.from_buffer(a)) if a.flags.writeable else a.ctypes.data
+
+
 class _BatchArrays:
     """Keeps the numpy arrays alive while the C struct points at them."""
 
     def __init__(self, qb):
         self.keep = [_i32(qb.node_off), np.ascontiguousarray(qb.op, np.uint8), _i32(qb.arg), _i32(qb.in_off),
                      _i32(qb.in_idx), _i32(qb.pos)]
-        p = [a.ctypes.data if a.size else None for a in self.keep]
+        p = [_address(a) if a.size else None for a in self.keep]
         self.c = QueryBatchC(int(qb.B), p[0], p[1], p[2], p[3], p[4], p[5])
 
 
@@ -156,6 +162,11 @@ class Plan:
     def __init__(self, handle, owner=None):
         self.handle = handle
         self.owner = owner      # keeps the engine (the plan's context) alive as long as the plan
+
+    def n_queries(self):
+        v = PlanView()
+        _check(lib().ngdb_plan_export(self.handle, C.byref(v)), None)
+        return int(v.n_queries)
 
     def export(self):
         """All plan arrays as a dict of numpy int32 copies / ints."""
@@ -281,7 +292,7 @@ class SampledBatch:
         def take(ptr, shape, dt):
             a = np.empty(shape, dt)
             if a.size:      # (a plain memory copy: a tenth of what numpy's view of a ctypes pointer costs)
-                C.memmove(a.__array_interface__["data"][0], ptr, a.nbytes)
+                C.memmove(_address(a), ptr, a.nbytes)
             return a
 
         self.B = B
@@ -537,7 +548,7 @@ class Engine:
     def rank_all(self, plan, k, stream=None):
         """All-entity ranking: ([B, k] int32 ids, [B, k] float32 L1 distances), ascending, device tensors."""
         t = self.torch
-        B = plan.export()["n_queries"]
+        B = plan.n_queries()
         ids = t.empty((B, k), dtype=t.int32, device=self.device)
         dist = t.empty((B, k), dtype=t.float32, device=self.device)
         _check(lib().ngdb_score(self.ctx, plan.handle, None, 0, int(k), None, ids.data_ptr(), dist.data_ptr(),

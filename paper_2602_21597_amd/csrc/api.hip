@@ -91,6 +91,7 @@ struct ngdb_ctx_s {
     DevBuf w_pieces;
     const uint16_t* wp[3][4]{};     // per type: Wa forward, Wb forward, Wb backward (dH = dY Wb), Wa backward (dZ = dH Wa)
     bool have_pieces = false;
+    int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
     // The hidden activations of one depth (forward) or their gradients (backward) once more as bf16
     // pieces in tile order: written by the first launch of a layer pair, read as A operand by the
     // second, then free again.  Only steps whose launches use the small tile get that far.
@@ -1202,9 +1203,18 @@ int rank_filter_space(ngdb_ctx_t* c, int bits, int R, int B, int chunk, RankFilt
     return NGDB_OK;
 }
 
-// The filter serves the plain distance (vector family); a table of a few thousand rows is ranked
-// in fp32 in less time than the filter's launches take.
-bool rank_filtered(const ngdb_ctx_t* c) { return c->cfg.family == NGDB_FAMILY_VEC && c->cfg.n_entities > 2 * RANK_SAMPLE; }
+// The filter serves the plain distance (vector family).  It replaces two operations per coordinate by a quarter (top-k) or a
+// half of one, for launches and lists of its own: below `from` coordinate differences the fp32 pass is through first.  Top-k:
+// 226 us in fp32 and 252 with the filter at 15 000 entities x 585 rows x 256 coordinates (2.2e9), 442 and 415 at 200 000 x 114 x
+// 256 (5.8e9), 413 and 313 at 50 000 x 585 x 256 (7.5e9).
+// Answers: the filter's counting takes as long per pair as 64 coordinates save, and each chunk has launches of its own:
+// 502 us in fp32 and 602 with the filter at 200 000 x 585 x 64, 250 and 230 at 15 000 x 585 x 256, 439 and 586 at 200 000 x 114 x
+// 256 (four chunks), 1357 and 1180 at 200 000 x 585 x 256.
+bool rank_filtered(const ngdb_ctx_t* c, int n_rows, int coords, double from) {
+    if (c->cfg.family != NGDB_FAMILY_VEC || c->cfg.n_entities <= 2 * RANK_SAMPLE) return false;
+    if (c->rank_filter_from >= 0) return (double)n_rows * c->cfg.n_entities * c->cfg.d >= (double)c->rank_filter_from;
+    return (double)n_rows * c->cfg.n_entities * coords >= from;
+}
 
 // The grid of a filtered pass (rows spread over the table; with text features its first fused rows) and the
 // branch rows on it.
@@ -1223,7 +1233,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
     const float* act = ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
-    const bool filtered = rank_filtered(c);
+    const bool filtered = rank_filtered(c, R, d, 3.5e9);
     const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
     float* dist = nullptr;
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
@@ -1267,8 +1277,8 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
     const bool sem = c->cfg.d_sem > 0;
     // (with very many answers per query most entities are undecided for one of them)
-    const bool filtered = rank_filtered(c) && n_ans <= 64ll * B;
     const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
+    const bool filtered = rank_filtered(c, R, d - 64, 1.4e9 + 3.7e9 * ((N - 1) / chunk)) && n_ans <= 64ll * B;
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
     if (rc == NGDB_OK) rc = ensure(c, c->rank_count, (size_t)n_ans * 8, true);
     if (rc == NGDB_OK && !d_ans_dist) rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, true);
@@ -1947,6 +1957,12 @@ int ngdb_copy_to_host(void* h_dst, const void* d_src, size_t bytes) {
 }
 
 int64_t ngdb_debug_alloc_count(const ngdb_ctx_t* c) { return c ? c->n_alloc : -1; }
+
+int ngdb_debug_rank_filter_from(ngdb_ctx_t* c, int64_t work) {
+    if (!c) return NGDB_ERR_ARG;
+    c->rank_filter_from = work;
+    return NGDB_OK;
+}
 
 int64_t ngdb_step_count(const ngdb_ctx_t* c) { return c ? c->step : -1; }
 

@@ -11,11 +11,8 @@
 // the vector family go through these kernels for a first sample only, and for what
 // the filter of rank_filter.hip cannot take.
 //
-// The selection pass keeps, per lane, the best KMAX (distance, id) pairs of the
-// entities it scanned (a union query takes the minimum over its branch rows
-// first), then merges the 256 sorted lists of the workgroup and the running
-// result of earlier chunks by repeated workgroup-wide minimum.  Order is
-// (distance, entity id), so equal distances rank the lower id first.
+// The selection pass looks for a bound, lists what is within it and places that with the running result of
+// earlier chunks.  Order is (distance, entity id), so equal distances rank the lower id first.
 #include <climits>
 
 #include "common.h"
@@ -34,8 +31,11 @@ constexpr int DC = 16;
 // the offsets are staged already multiplied by (1 - alpha): five VALU operations per coordinate.
 // Emat16 (if set): the entity rows are read from this bf16 copy of Emat.
 // count (if set): tiles without a row whose query has count > room are left out.
+// Three wavefronts per SIMD and two coordinates unrolled: left to itself the compiler unrolled all sixteen, fetched them
+// ahead into 512 registers and ran one wavefront per SIMD, waiting for LDS and copying between register files.  At 603 boxes
+// (737 rows) x 300 000 entities x 316 coordinates 14.4 -> 6.4 ms, at 512 vectors x 200 000 x 256 2.56 -> 1.52 ms.
 template <bool BOX, int RPL, int EPL>
-__global__ __launch_bounds__(256) void l1_tile_kernel(const float* __restrict__ act, const float* __restrict__ off,
+__global__ __launch_bounds__(256, 3) void l1_tile_kernel(const float* __restrict__ act, const float* __restrict__ off,
                                                       float alpha, const int32_t* __restrict__ row_ids,
                                                       int n_rows, const float* __restrict__ Emat,
                                                       const uint16_t* __restrict__ Emat16, int n_ent, int d,
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256) void l1_tile_kernel(const float* __restrict__ 
         for (int kt = 0; kt < nk; ++kt) {
             const int buf = kt & 1;
             if (kt + 1 < nk) issue((kt + 1) * DC);
-#pragma unroll
+#pragma unroll 2
             for (int k = 0; k < DC; ++k) {
                 float yv[RPL], ov[RPL], ev[EPL];
 #pragma unroll
@@ -178,91 +178,133 @@ constexpr int KMAX = NGDB_MAX_TOPK;
 
 __device__ __forceinline__ bool before(float d, int i, float d2, int i2) { return d < d2 || (d == d2 && i < i2); }
 
-// one workgroup per query: merges the chunk's distances into the query's running top-k
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ dist, int ld, const int32_t* __restrict__ root_off,
-                                                   int ent_base, int n_ent, int k, bool first_chunk,
-                                                   float* __restrict__ out_dist, int32_t* __restrict__ out_ids,
-                                                   int32_t* __restrict__ count, int room) {
-    __shared__ float ld_[256][KMAX + 1];
-    __shared__ int li_[256][KMAX + 1];
-    __shared__ float wd[4];
-    __shared__ int wi[4];
-    const int q = blockIdx.x, t = threadIdx.x;
+// One workgroup per query: merges the chunk's distances into the query's running top-k.  Two looks at the distances (a
+// union query takes the minimum over its branch rows): the first finds every lane's smallest, and the k-th smallest of
+// these in a wavefront is a bound that k entities keep; the second lists what is within the least of these bounds,
+// some ten times k entities, whose places are counted directly.  (Sorted lists of KMAX per lane, merged: 78 us more at
+// 15 000 entities, 290 at 50 000.)  Should the list be too short for ties, the k best are found one after the other.
+constexpr int TOPK_T = 1024, TOPK_LIST = 2048;
+__global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ dist, int ld, const int32_t* __restrict__ root_off,
+                                                      int ent_base, int n_ent, int k, bool first_chunk,
+                                                      float* __restrict__ out_dist, int32_t* __restrict__ out_ids,
+                                                      int32_t* __restrict__ count, int room) {
+    __shared__ float s_d[TOPK_LIST], s_bound[TOPK_T / 64], s_run[KMAX];
+    __shared__ int s_i[TOPK_LIST], s_run_i[KMAX], s_n;
+    const int q = blockIdx.x, t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
     if (count && count[q] <= room) return;          // uniform: the filter has dealt with this query's chunk
     const int r0 = root_off[q], nb = root_off[q + 1] - r0;
-
-    float bd[KMAX];
-    int bi[KMAX];
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-        bd[j] = INFINITY;
-        bi[j] = INT_MAX;
-    }
-    auto insert = [&](float dv, int id) {
-        if (!before(dv, id, bd[KMAX - 1], bi[KMAX - 1])) return;
-#pragma unroll
-        for (int j = KMAX - 1; j >= 1; --j) {
-            const bool shift = before(dv, id, bd[j - 1], bi[j - 1]);
-            const bool here = !shift && before(dv, id, bd[j], bi[j]);
-            const float nd = shift ? bd[j - 1] : (here ? dv : bd[j]);
-            const int ni = shift ? bi[j - 1] : (here ? id : bi[j]);
-            bd[j] = nd;
-            bi[j] = ni;
+    const float* row = dist + (size_t)r0 * ld;
+    auto four = [&](int e) {                         // entities e .. e + 3, those past the end not a number
+        float4 v = *reinterpret_cast<const float4*>(row + e);
+        for (int b = 1; b < nb; ++b) {
+            const float4 w = *reinterpret_cast<const float4*>(row + (size_t)b * ld + e);
+            v.x = fminf(v.x, w.x); v.y = fminf(v.y, w.y); v.z = fminf(v.z, w.z); v.w = fminf(v.w, w.w);
         }
-        if (before(dv, id, bd[0], bi[0])) {
-            bd[0] = dv;
-            bi[0] = id;
+        if (e + 1 >= n_ent) v.y = NAN;
+        if (e + 2 >= n_ent) v.z = NAN;
+        if (e + 3 >= n_ent) v.w = NAN;
+        return v;
+    };
+    if (t == 0) s_n = 0;
+    if (t < KMAX) {
+        const bool have = !first_chunk && t < k;
+        s_run[t] = have ? out_dist[(size_t)q * k + t] : INFINITY;
+        s_run_i[t] = have ? out_ids[(size_t)q * k + t] : -1;
+    }
+    float least = INFINITY;
+#pragma unroll 4
+    for (int e = 4 * t; e < n_ent; e += 4 * T) {
+        const float4 v = four(e);
+        least = fminf(least, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
+    }
+    int smaller = 0;                                 // lanes before this one
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+        const float o = lane_value(least, j);
+        smaller += (o < least || (o == least && j < lane)) ? 1 : 0;
+    }
+    const float bound_w = lane_value(least, __ffsll(__ballot(smaller == k - 1)) - 1);
+    if (lane == 0) s_bound[wave] = bound_w;
+    __syncthreads();
+    float bound = INFINITY;
+    for (int w = 0; w < T / 64; ++w) bound = fminf(bound, s_bound[w]);
+    if (s_run_i[k - 1] >= 0) bound = fminf(bound, s_run[k - 1]);
+    auto list = [&](float d, int id) {
+        const int at = atomicAdd(&s_n, 1);
+        if (at < TOPK_LIST) {
+            s_d[at] = d;
+            s_i[at] = id;
         }
     };
-    if (!first_chunk && t < k) {
-        const int id = out_ids[(size_t)q * k + t];
-        if (id >= 0) insert(out_dist[(size_t)q * k + t], id);
+    if (t < k && s_run_i[t] >= 0) list(s_run[t], s_run_i[t]);
+#pragma unroll 4
+    for (int e = 4 * t; e < n_ent; e += 4 * T) {
+        const float4 v = four(e);
+        if (v.x <= bound) list(v.x, ent_base + e);
+        if (v.y <= bound) list(v.y, ent_base + e + 1);
+        if (v.z <= bound) list(v.z, ent_base + e + 2);
+        if (v.w <= bound) list(v.w, ent_base + e + 3);
     }
-    for (int e = t; e < n_ent; e += 256) {
-        float dv = dist[(size_t)r0 * ld + e];
-        for (int b = 1; b < nb; ++b) dv = fminf(dv, dist[(size_t)(r0 + b) * ld + e]);
-        insert(dv, ent_base + e);
-    }
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-        ld_[t][j] = bd[j];
-        li_[t][j] = bi[j];
-    }
-    ld_[t][KMAX] = INFINITY;
-    li_[t][KMAX] = INT_MAX;
-    int head = 0;
-    for (int r = 0; r < k; ++r) {
-        float cd = ld_[t][head];
-        int ci = li_[t][head];
-        float md = cd;
-        int mi = ci;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const float od = __shfl_xor(md, off, 64);
-            const int oi = __shfl_xor(mi, off, 64);
-            if (before(od, oi, md, mi)) {
-                md = od;
-                mi = oi;
+    __syncthreads();
+    const int n = s_n;
+    if (n <= TOPK_LIST) {
+        for (int x = t; x < n; x += T) {
+            const float d = s_d[x];
+            const int id = s_i[x];
+            int place = 0;
+            for (int j = 0; j < n; ++j) place += before(s_d[j], s_i[j], d, id) ? 1 : 0;
+            if (place < k) {
+                out_dist[(size_t)q * k + place] = d;
+                out_ids[(size_t)q * k + place] = id;
             }
         }
-        __syncthreads();                 // wd / wi of the previous round have been read
-        if ((t & 63) == 0) {
-            wd[t >> 6] = md;
-            wi[t >> 6] = mi;
+        if (t >= n && t < k) {
+            out_dist[(size_t)q * k + t] = INFINITY;
+            out_ids[(size_t)q * k + t] = -1;
         }
-        __syncthreads();
-        md = wd[0];
-        mi = wi[0];
-#pragma unroll
-        for (int w = 1; w < 4; ++w)
-            if (before(wd[w], wi[w], md, mi)) {
-                md = wd[w];
-                mi = wi[w];
+    } else {
+        float pd = -INFINITY;
+        int pi = -1;
+        for (int r = 0; r < k; ++r) {                // the first one after (pd, pi)
+            float md = INFINITY;
+            int mi = INT_MAX;
+            auto look = [&](float d, int id) {
+                if (before(pd, pi, d, id) && before(d, id, md, mi)) {
+                    md = d;
+                    mi = id;
+                }
+            };
+            if (t < k && s_run_i[t] >= 0) look(s_run[t], s_run_i[t]);
+            for (int e = 4 * t; e < n_ent; e += 4 * T) {
+                const float4 v = four(e);
+                look(v.x, ent_base + e); look(v.y, ent_base + e + 1); look(v.z, ent_base + e + 2); look(v.w, ent_base + e + 3);
             }
-        if (ci == mi && cd == md && mi != INT_MAX) ++head;     // ids are unique: exactly one list advances
-        if (t == 0) {
-            out_dist[(size_t)q * k + r] = md;
-            out_ids[(size_t)q * k + r] = mi == INT_MAX ? -1 : mi;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const float od = __shfl_xor(md, off, 64);
+                const int oi = __shfl_xor(mi, off, 64);
+                if (before(od, oi, md, mi)) {
+                    md = od;
+                    mi = oi;
+                }
+            }
+            __syncthreads();                         // s_d / s_i of the round before have been read
+            if (lane == 0) {
+                s_d[wave] = md;
+                s_i[wave] = mi;
+            }
+            __syncthreads();
+            for (int w = 0; w < T / 64; ++w)
+                if (before(s_d[w], s_i[w], md, mi)) {
+                    md = s_d[w];
+                    mi = s_i[w];
+                }
+            pd = md;
+            pi = mi;
+            if (t == 0) {
+                out_dist[(size_t)q * k + r] = md;
+                out_ids[(size_t)q * k + r] = mi == INT_MAX ? -1 : mi;
+            }
         }
     }
     if (count && t == 0) count[q] = 0;
@@ -280,45 +322,61 @@ __device__ __forceinline__ int query_of_answer(const int32_t* __restrict__ ans_o
 }
 
 constexpr int CNT_SLAB = 8192;    // entities per workgroup of the counting pass
-constexpr int CNT_TILE = 256;     // answers whose counters a workgroup holds at once
+constexpr int CNT_AT_ONCE = 8;    // answers a lane counts for in one look at its distances
 
 // count[a] += number of entities of the slab strictly closer to a's query than thr[a].
-// Grid (slabs, queries).  A wavefront compares 64 entities with one threshold at a time and
-// counts by ballot; the per-wavefront counters live in LDS, one integer atomic per answer and
-// workgroup reaches global memory (integer sums do not depend on the order).
+// Grid (slabs, queries).  Counters in registers, summed over the workgroup at the end; one integer atomic per answer and
+// workgroup reaches global memory (integer sums do not depend on the order).  (A ballot and an LDS counter per answer
+// and 64 entities took 44 us more for 100 queries of six answers over 50 000 entities.)
 __global__ __launch_bounds__(256) void count_less_kernel(const float* __restrict__ dist, int ld,
                                                          const int32_t* __restrict__ root_off,
                                                          const int32_t* __restrict__ ans_off,
                                                          const float* __restrict__ thr, int n_ent,
                                                          int32_t* __restrict__ count, const int32_t* __restrict__ listed,
                                                          int room) {
-    __shared__ float s_thr[CNT_TILE];
-    __shared__ int32_t s_cnt[4][CNT_TILE];
+    __shared__ int32_t s_cnt[4][CNT_AT_ONCE];
     const int q = blockIdx.y;
     const int a_lo = ans_off[q], a_hi = ans_off[q + 1];
     if (a_lo >= a_hi || (listed && listed[q] <= room)) return;        // uniform
-    const int r_lo = root_off[q], r_hi = root_off[q + 1];
+    const int r_lo = root_off[q], nb = root_off[q + 1] - r_lo;
+    const float* row = dist + (size_t)r_lo * ld;
     const int e_lo = blockIdx.x * CNT_SLAB, e_hi = min(n_ent, e_lo + CNT_SLAB);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int t0 = a_lo; t0 < a_hi; t0 += CNT_TILE) {
-        const int nt = min(CNT_TILE, a_hi - t0);
-        __syncthreads();
-        for (int j = threadIdx.x; j < nt; j += 256) s_thr[j] = thr[t0 + j];
-        for (int j = lane; j < nt; j += 64) s_cnt[wave][j] = 0;
-        __syncthreads();
-        for (int e = e_lo + threadIdx.x; e - (int)threadIdx.x < e_hi; e += 256) {   // whole wavefronts iterate together
-            float v = INFINITY;                                       // entities past the end are closer to nothing
-            if (e < e_hi)
-                for (int r = r_lo; r < r_hi; ++r) v = fminf(v, dist[(size_t)r * ld + e]);
-            for (int j = 0; j < nt; ++j) {
-                const int c = __popcll(__ballot(v < s_thr[j]));
-                if (lane == 0) s_cnt[wave][j] += c;
-            }
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (int t0 = a_lo; t0 < a_hi; t0 += CNT_AT_ONCE) {
+        float th[CNT_AT_ONCE];
+        int cnt[CNT_AT_ONCE];
+#pragma unroll
+        for (int j = 0; j < CNT_AT_ONCE; ++j) {
+            th[j] = t0 + j < a_hi ? thr[t0 + j] : -INFINITY;          // (nothing is closer)
+            cnt[j] = 0;
         }
+#pragma unroll 2
+        for (int e = e_lo + 4 * t; e < e_hi; e += 4 * 256) {
+            float4 v = *reinterpret_cast<const float4*>(row + e);
+            for (int b = 1; b < nb; ++b) {
+                const float4 w = *reinterpret_cast<const float4*>(row + (size_t)b * ld + e);
+                v.x = fminf(v.x, w.x); v.y = fminf(v.y, w.y); v.z = fminf(v.z, w.z); v.w = fminf(v.w, w.w);
+            }
+            if (e + 1 >= e_hi) v.y = INFINITY;                        // entities past the end are closer to nothing
+            if (e + 2 >= e_hi) v.z = INFINITY;
+            if (e + 3 >= e_hi) v.w = INFINITY;
+#pragma unroll
+            for (int j = 0; j < CNT_AT_ONCE; ++j)
+                cnt[j] += (v.x < th[j] ? 1 : 0) + (v.y < th[j] ? 1 : 0) + (v.z < th[j] ? 1 : 0) + (v.w < th[j] ? 1 : 0);
+        }
+#pragma unroll
+        for (int j = 0; j < CNT_AT_ONCE; ++j) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) cnt[j] += __shfl_xor(cnt[j], off, 64);
+        }
+        __syncthreads();                                              // the counters of the round before have been read
+        if (lane == 0)
+#pragma unroll
+            for (int j = 0; j < CNT_AT_ONCE; ++j) s_cnt[wave][j] = cnt[j];
         __syncthreads();
-        for (int j = threadIdx.x; j < nt; j += 256) {
-            const int c = (s_cnt[0][j] + s_cnt[1][j]) + (s_cnt[2][j] + s_cnt[3][j]);
-            if (c) atomicAdd(&count[t0 + j], c);
+        if (t < CNT_AT_ONCE && t0 + t < a_hi) {
+            const int c = (s_cnt[0][t] + s_cnt[1][t]) + (s_cnt[2][t] + s_cnt[3][t]);
+            if (c) atomicAdd(&count[t0 + t], c);
         }
     }
 }
@@ -439,7 +497,8 @@ hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off,
                              const Overflowed* only) {
     if (n_queries <= 0) return hipSuccess;
     if (k < 1 || k > KMAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(topk_kernel, dim3(n_queries), dim3(256), 0, s, dist, ld, root_off, ent_base, n_ent, k,
+    if (ld & 3) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(topk_kernel, dim3(n_queries), dim3(n_ent > 4096 ? TOPK_T : 256), 0, s, dist, ld, root_off, ent_base, n_ent, k,
                        first_chunk, out_dist, out_ids, only ? only->count : nullptr, only ? only->room : 0);
     return hipGetLastError();
 }

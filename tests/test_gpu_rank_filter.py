@@ -8,6 +8,20 @@ from . import parity as par
 pytestmark = pytest.mark.gpu
 
 
+def _filtered(case):
+    """The case with engines that take the filter whatever the size of the pass."""
+    from paper_2602_21597_amd import binding
+    plain = case.engine
+
+    def engine(*args, **kw):
+        eng = plain(*args, **kw)
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, 0) == 0
+        return eng
+
+    case.engine = engine
+    return case
+
+
 def _first_rows_far(P):
     P["E"][:4096] *= 6.0          # the sample's bound lets every later entity through: lists overflow
 
@@ -42,7 +56,7 @@ def _shifted(P):
 ])
 def test_filtered_passes_match_the_oracle(N, d, h, B, edit, kw):
     par.say("rank filter: N=%d d=%d B=%d %s %s" % (N, d, B, edit.__name__ if edit else "", kw))
-    case = par.Case(N, 12, d, h, B, 2, 8.0, seed=300 + d, T=2 * N, params_edit=edit, **kw)
+    case = _filtered(par.Case(N, 12, d, h, B, 2, 8.0, seed=300 + d, T=2 * N, params_edit=edit, **kw))
     for k in (1, 10, 16):
         par.check_topk(case, k, 6)
     if edit is not _one_cluster:  # (no rank is decided between thousands of equal rows)
@@ -53,7 +67,7 @@ def test_filtered_ranks_with_many_answers_of_one_query():
     """Hundreds of answers of one query beside a handful of the others."""
     import torch
     from oracle import rank as orank
-    case = par.Case(6000, 12, 32, 32, 40, 2, 8.0, seed=77, T=12000)
+    case = _filtered(par.Case(6000, 12, 32, 32, 40, 2, 8.0, seed=77, T=12000))
     M = case.model()
     rng = np.random.default_rng(3)
     lists = [rng.choice(case.N, 700 if q == 5 else 2, replace=False) for q in range(case.B)]
@@ -73,3 +87,16 @@ def test_filtered_ranks_with_many_answers_of_one_query():
         got = ranks[off[q]:off[q + 1]]
         assert np.all((lo <= got) & (got <= hi)), q
     plan.free()
+
+
+# the fp32 pass: fewer entities than k, one lane's four, a group of lanes, more than a workgroup's lanes; equal distances
+# beyond the list's room; a second chunk
+@pytest.mark.parametrize("N,d,B,edit", [(5, 8, 9, None), (14, 8, 9, None), (1030, 20, 20, None), (4099, 12, 9, None),
+                                        (9000, 32, 12, _one_cluster), (65700, 8, 5, None)])
+def test_unfiltered_passes_match_the_oracle(N, d, B, edit):
+    case = par.Case(N, 5, d, 16, B, 2, 8.0, seed=40 + d, T=6 * N, params_edit=edit)
+    for k in (1, 10, 16):
+        if k <= N:
+            par.check_topk(case, k, 4)
+    if edit is None and N > 100:
+        par.check_filtered_ranks(case, 5)
