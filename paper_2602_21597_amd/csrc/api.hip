@@ -100,7 +100,7 @@ struct ngdb_ctx_s {
     // text-feature fusion: bf16 copy of Wp, fused rows of the touched entities, position of every
     // contribution's entity in that list, operator references redirected to it, bf16 row gradients,
     // split-wise partial sums and the gradient of Wp, fused rows of one ranking chunk
-    DevBuf Wb, Ef, inv, refs_sem, g_bf16, wp_partial, gWp, rank_ef;
+    DevBuf Wb, Ef, Ea, inv, refs_sem, g_bf16, wp_partial, gWp, rank_ef;
     DevBuf later;       // touched entity rows that wait for the backward pass (positions in uniq)
     // box family: offsets and their gradients by slot (act / dact hold the centres), per-input
     // outputs of the offset MLP with their gradients, direct gradient of the inputs' offsets,
@@ -435,6 +435,7 @@ int size_workspace(ngdb_ctx_t* c, const ngdb_plan_t* pl, int K, bool want_table_
         ENS(c->Ef, urows * d * f);
         ENS(c->inv, (size_t)nk * 4);
         ENS(c->refs_sem, hp.in_ref.size() * 4);
+        ENS(c->Ea, (size_t)hp.n_anchor * d * sizeof(float));
         ENS(c->g_bf16, urows * d * sizeof(uint16_t));
         ENS(c->wp_partial, (size_t)sem_wgrad_splits((int64_t)urows, (int)d, (int)ds) * d * ds * f);
         ENS(c->gWp, d * ds * f);
@@ -458,40 +459,69 @@ struct EntRows {
     const int32_t* cand;   // [B, C] rows of the candidates
 };
 
-// Builds the index over [anchors | positives | tail] and, with text features, the fused rows
-// of its distinct entities and the references into them.  The index is left in the context's
-// buffers; *e_src receives the sorted contribution numbers.
-int prepare_entities(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_tail, int64_t n_tail, hipStream_t s_idx,
-                     hipStream_t stream, int32_t** e_src, EntRows* er, bool reclaim = false) {
-    const HostPlan& hp = pl->hp;
-    const int B = hp.n_queries, d = c->cfg.d, ds = c->cfg.d_sem;
-    IndexBuffers ib{ptr<int32_t>(c->keys_a), ptr<int32_t>(c->keys_b), ptr<int32_t>(c->vals_a),
-                    ptr<int32_t>(c->vals_b), ptr<int32_t>(c->hist),   ptr<int32_t>(c->scan_tmp),
-                    ptr<int32_t>(c->uniq),   ptr<int32_t>(c->seg_off), ptr<int32_t>(c->n_uniq)};
-    {
-        Timed tm(c, NGDB_TK_INDEX, s_idx);
-        HIPCHK(c, build_segment_index(pl->d_ekeys_head, hp.n_anchor + B, d_tail, n_tail, c->cfg.n_entities, ib, e_src,
-                                      s_idx));
-    }
-    if (ds == 0) {
-        *er = EntRows{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, d_tail};
-        return NGDB_OK;
-    }
-    // s_idx == stream in this mode: everything below needs the index
-    const int64_t n_contrib = (int64_t)hp.n_anchor + B + n_tail;
-    Timed tm(c, NGDB_TK_SEM, stream);
-    HIPCHK(c, launch_cast_bf16(c->prm.Wp.p, ptr<uint16_t>(c->Wb), (int64_t)d * ds, stream));
-    HIPCHK(c, launch_inverse_index(*e_src, ptr<int32_t>(c->seg_off), ptr<int32_t>(c->n_uniq), n_contrib,
-                                   ptr<int32_t>(c->inv), stream));
+IndexBuffers index_buffers(ngdb_ctx_t* c) {
+    return IndexBuffers{ptr<int32_t>(c->keys_a), ptr<int32_t>(c->keys_b), ptr<int32_t>(c->vals_a), ptr<int32_t>(c->vals_b), ptr<int32_t>(c->hist),
+                        ptr<int32_t>(c->scan_tmp), ptr<int32_t>(c->uniq), ptr<int32_t>(c->seg_off), ptr<int32_t>(c->n_uniq)};
+}
+
+// Index over [anchors | positives | tail], left in the context's buffers; *e_src receives the sorted contribution numbers.
+int build_index(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_tail, int64_t n_tail, hipStream_t s, int32_t** e_src) {
+    Timed tm(c, NGDB_TK_INDEX, s);
+    HIPCHK(c, build_segment_index(pl->d_ekeys_head, pl->hp.n_anchor + pl->hp.n_queries, d_tail, n_tail, c->cfg.n_entities, index_buffers(c), e_src, s));
+    return NGDB_OK;
+}
+
+// ---- text features: Wp as bf16, the fused rows of the anchors (one per anchor) or of the index's distinct
+// entities, and the references to them
+int cast_projection(ngdb_ctx_t* c, hipStream_t s) {
+    Timed tm(c, NGDB_TK_SEM, s);
+    HIPCHK(c, launch_cast_bf16(c->prm.Wp.p, ptr<uint16_t>(c->Wb), (int64_t)c->cfg.d * c->cfg.d_sem, s));
+    return NGDB_OK;
+}
+SemFuseArgs fuse_args(const ngdb_ctx_t* c) {
     SemFuseArgs fa{};
-    fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.ids = ptr<int32_t>(c->uniq);
-    fa.n_rows_dev = ptr<int32_t>(c->n_uniq); fa.n_rows = (int)std::min<int64_t>(n_contrib, c->cfg.n_entities);
-    fa.d = d; fa.ds = ds; fa.out = ptr<float>(c->Ef);
-    HIPCHK(c, launch_sem_fuse(fa, stream));
-    HIPCHK(c, launch_translate_refs(reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_in_gslot, (int)hp.in_ref.size(), hp.n_slots,
-                                    ptr<int32_t>(c->inv), ptr<int32_t>(c->refs_sem), stream));
-    *er = EntRows{ptr<float>(c->Ef), ptr<int32_t>(c->refs_sem), ptr<int32_t>(c->inv) + hp.n_anchor,
-                  ptr<int32_t>(c->inv) + hp.n_anchor + B};
+    fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.d = c->cfg.d; fa.ds = c->cfg.d_sem;
+    return fa;
+}
+int fuse_anchors(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, EntRows* er, bool reclaim) {
+    const HostPlan& hp = pl->hp;
+    Timed tm(c, NGDB_TK_SEM, s);
+    SemFuseArgs fa = fuse_args(c);
+    fa.ids = pl->d_ekeys_head; fa.n_rows = hp.n_anchor; fa.out = ptr<float>(c->Ea);
+    HIPCHK(c, launch_sem_fuse(fa, s));
+    HIPCHK(c, launch_translate_refs(reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_in_gslot, (int)hp.in_ref.size(), hp.n_slots, nullptr,
+                                    ptr<int32_t>(c->refs_sem), s));
+    *er = EntRows{ptr<float>(c->Ea), ptr<int32_t>(c->refs_sem), nullptr, nullptr};
+    return NGDB_OK;
+}
+int fuse_indexed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* e_src, int64_t n_tail, hipStream_t s, EntRows* er) {
+    const int n_anchor = pl->hp.n_anchor, B = pl->hp.n_queries;
+    const int64_t n_contrib = (int64_t)n_anchor + B + n_tail;
+    Timed tm(c, NGDB_TK_SEM, s);
+    HIPCHK(c, launch_inverse_index(e_src, ptr<int32_t>(c->seg_off), ptr<int32_t>(c->n_uniq), n_contrib, ptr<int32_t>(c->inv), s));
+    SemFuseArgs fa = fuse_args(c);
+    fa.ids = ptr<int32_t>(c->uniq); fa.n_rows_dev = ptr<int32_t>(c->n_uniq); fa.n_rows = (int)std::min<int64_t>(n_contrib, c->cfg.n_entities);
+    fa.out = ptr<float>(c->Ef);
+    HIPCHK(c, launch_sem_fuse(fa, s));
+    er->rows = ptr<float>(c->Ef);
+    er->pos = ptr<int32_t>(c->inv) + n_anchor;
+    er->cand = ptr<int32_t>(c->inv) + n_anchor + B;
+    return NGDB_OK;
+}
+// What a forward-only pass reads: with text features the fused rows of the anchors and, if there are candidates,
+// of the distinct entities among them.
+int prepare_entities(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_tail, int64_t n_tail, hipStream_t s, EntRows* er, bool reclaim) {
+    const HostPlan& hp = pl->hp;
+    *er = EntRows{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, d_tail};
+    if (c->cfg.d_sem == 0) return NGDB_OK;
+    int rc = cast_projection(c, s);
+    if (rc != NGDB_OK || n_tail == 0) return rc != NGDB_OK ? rc : fuse_anchors(c, pl, s, er, reclaim);
+    int32_t* e_src = nullptr;
+    if ((rc = build_index(c, pl, d_tail, n_tail, s, &e_src)) != NGDB_OK) return rc;
+    if ((rc = fuse_indexed(c, pl, e_src, n_tail, s, er)) != NGDB_OK) return rc;
+    Timed tm(c, NGDB_TK_SEM, s);
+    HIPCHK(c, launch_translate_refs(er->refs, pl->d_in_gslot, (int)hp.in_ref.size(), hp.n_slots, ptr<int32_t>(c->inv), ptr<int32_t>(c->refs_sem), s));
+    er->refs = ptr<int32_t>(c->refs_sem);
     return NGDB_OK;
 }
 
@@ -671,6 +701,7 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
         ENS(c->Ef, urows * d * sizeof(float));
         ENS(c->inv, (size_t)nk * 4);
         ENS(c->refs_sem, hp.in_ref.size() * 4);
+        ENS(c->Ea, (size_t)hp.n_anchor * d * sizeof(float));
     }
 #undef ENS
     return NGDB_OK;
@@ -934,31 +965,34 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     if (rc == NGDB_OK) rc = begin_pass(c, pl, stream);
     if (rc != NGDB_OK) return rc;
 
-    // 1. entity gradient index (depends only on the plan and the negatives)
+    // 1. entity gradient index (depends only on the plan and the negatives).  With a library stream the index build, and with
+    // text features the fusion of all rows that are scored, run beside the forward pass, which needs the anchors' rows only.
     int32_t* e_src = nullptr;
-    // With a library stream two independent pieces leave the caller's stream: the index build runs
-    // beside the forward pass (without text features, where nothing before the tables needs it), and
-    // the table updates run beside the weight gradients and the dense Adam step.
     const bool sem = c->cfg.d_sem > 0;
     const bool aside = c->n_side > 0;
-    const bool idx_aside = aside && !sem;
-    hipStream_t s_idx = idx_aside ? c->side[0] : stream;
-    if (idx_aside) {
+    hipStream_t s_idx = aside ? c->side[0] : stream;
+    if (sem && (rc = cast_projection(c, stream)) != NGDB_OK) return rc;
+    if (aside) {
         HIPCHK(c, hipEventRecord(c->ev_fork, stream));
         HIPCHK(c, hipStreamWaitEvent(s_idx, c->ev_fork, 0));
     }
-    EntRows er{};
-    rc = prepare_entities(c, pl, d_neg, (int64_t)B * K, s_idx, stream, &e_src, &er);
-    if (rc != NGDB_OK) return rc;
+    EntRows er{c->prm.E.p, pl->d_in_ref, pl->d_pos, d_neg}, scored = er;
+    if ((rc = build_index(c, pl, d_neg, (int64_t)B * K, s_idx, &e_src)) != NGDB_OK) return rc;
+    if (sem) {
+        if ((rc = fuse_indexed(c, pl, e_src, (int64_t)B * K, s_idx, &scored)) != NGDB_OK) return rc;
+        if (aside) HIPCHK(c, hipEventRecord(c->ev_join, s_idx));
+        if ((rc = fuse_anchors(c, pl, stream, &er, false)) != NGDB_OK) return rc;
+    }
 
     // 2. forward frontiers
     rc = enqueue_forward(c, pl, er, stream, ctx_space(c));
     if (rc != NGDB_OK) return rc;
 
     // 3. scores, loss terms, dL/ds, gradients of the branch embeddings
+    if (sem && aside) HIPCHK(c, hipStreamWaitEvent(stream, c->ev_join, 0));
     ScoreArgs sa{};
-    sa.act = ptr<float>(c->act); sa.E = er.rows; sa.root_off = pl->d_root_off; sa.root_slot = pl->d_root_slot;
-    sa.pos = er.pos; sa.cand = er.cand; sa.B = B; sa.C = K; sa.d = d; sa.max_branch = std::max(1, hp.max_branch);
+    sa.act = ptr<float>(c->act); sa.E = scored.rows; sa.root_off = pl->d_root_off; sa.root_slot = pl->d_root_slot;
+    sa.pos = scored.pos; sa.cand = scored.cand; sa.B = B; sa.C = K; sa.d = d; sa.max_branch = std::max(1, hp.max_branch);
     sa.gamma = c->cfg.gamma; sa.score = ptr<float>(c->score); sa.coef = ptr<float>(c->coef);
     sa.win = sem ? nullptr : ptr<int32_t>(c->win); sa.mask = sem ? c->mask.p : nullptr; sa.dact = ptr<float>(c->dact); sa.loss_terms = ptr<float>(c->loss_terms);
     const bool box = c->cfg.family == NGDB_FAMILY_BOX;
@@ -1403,7 +1437,7 @@ void ngdb_destroy(ngdb_ctx_t* c) {
                      &c->dH[1], &c->dH[2], &c->Att, &c->dAtt, &c->Dx, &c->score, &c->coef, &c->win, &c->mask,
                      &c->loss_terms, &c->rec_coef, &c->rec_row, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->hist, &c->scan_tmp,
                      &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
-                     &c->Wb, &c->Ef, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
+                     &c->Wb, &c->Ef, &c->Ea, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
                      &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb, &c->later};
     for (DevBuf* b : all) release(*b);
     if (c->side[0]) (void)hipStreamDestroy(c->side[0]);
@@ -1701,7 +1735,6 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
         return fail(c, NGDB_ERR_ARG, "all-entity mode needs 1 <= topk <= NGDB_MAX_TOPK and both output arrays");
     }
     c->have_grads = false;
-    const bool sem = c->cfg.d_sem > 0;
     // forward only: an operator output is reclaimed as soon as its consumer has run (Sec. 4.3);
     // the box family keeps one row per output
     const bool reclaim = c->cfg.family == NGDB_FAMILY_VEC;
@@ -1712,12 +1745,9 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     if (rc == NGDB_OK) rc = begin_pass(c, pl, s);
     if (rc != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
-    EntRows er{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, d_cand};
-    if (sem) {   // fused rows of the anchors (and candidates) first
-        int32_t* e_src = nullptr;
-        rc = prepare_entities(c, pl, d_cand, n_tail, s, s, &e_src, &er, reclaim);
-        if (rc != NGDB_OK) return rc;
-    }
+    EntRows er{};
+    rc = prepare_entities(c, pl, d_cand, n_tail, s, &er, reclaim);
+    if (rc != NGDB_OK) return rc;
     rc = enqueue_forward(c, pl, er, s, ctx_space(c, reclaim));
     if (rc != NGDB_OK) return rc;
     if (d_cand) {
@@ -1817,19 +1847,15 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
         return fail(c, NGDB_ERR_ARG, "answer lists / rank output missing");
     if (pl->hp.n_queries > 65535) return fail(c, NGDB_ERR_UNSUPPORTED, "more than 65535 queries in one ranking call");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool sem = c->cfg.d_sem > 0;
     c->have_grads = false;
     const bool reclaim = c->cfg.family == NGDB_FAMILY_VEC;     // as in ngdb_score
     int rc = reclaim ? size_forward_only(c, pl, 0) : size_workspace(c, pl, 0, false);
     if (rc == NGDB_OK) rc = begin_pass(c, pl, s);
     if (rc != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
-    EntRows er{c->prm.E.p, reclaim ? pl->d_f_in_ref : pl->d_in_ref, pl->d_pos, nullptr};
-    if (sem) {
-        int32_t* e_src = nullptr;
-        rc = prepare_entities(c, pl, nullptr, 0, s, s, &e_src, &er, reclaim);
-        if (rc != NGDB_OK) return rc;
-    }
+    EntRows er{};
+    rc = prepare_entities(c, pl, nullptr, 0, s, &er, reclaim);
+    if (rc != NGDB_OK) return rc;
     rc = enqueue_forward(c, pl, er, s, ctx_space(c, reclaim));
     if (rc != NGDB_OK) return rc;
     if (n_ans > 0) {

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
         if ((int)blockIdx.x >= a.tile_start[i]) q = i;
     const LevelProblem p = a.p[q];
     const LevelMlp w = a.mlp[p.type];
-    const int d = a.d, h = a.h, xp = lv_pitch(d), hp = lv_pitch(h), d4 = d >> 2, h4 = h >> 2;
+    const int d = a.d, h = a.h, xp = lv_pitch(d), hp = lv_pitch(h);
     float *Xs = lds, *Ls = Xs + LV_ROWS * xp, *Hs = Ls + LV_ROWS * xp, *bias = Hs + LV_ROWS * hp;
     const int tid = threadIdx.x, lane = tid & 63;
     const int m = LV_ROWS / p.k, i0 = ((int)blockIdx.x - a.tile_start[q]) * m;

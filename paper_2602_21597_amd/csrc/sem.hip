@@ -52,14 +52,19 @@ __global__ __launch_bounds__(256) void inverse_index_kernel(const int32_t* __res
     }
 }
 
-// operator input references with anchors redirected to their fused row
+// operator input references with anchors redirected to their fused row: inv[anchor], or the anchor's number
 __global__ __launch_bounds__(256) void translate_refs_kernel(const int32_t* __restrict__ in_ref,
                                                              const int32_t* __restrict__ in_gslot, int n, int n_slots,
                                                              const int32_t* __restrict__ inv, int32_t* __restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t r = in_ref[i];
-    out[i] = r >= 0 ? r : -1 - inv[in_gslot[i] - n_slots];
+    if (r >= 0) {
+        out[i] = r;
+        return;
+    }
+    const int32_t anchor = in_gslot[i] - n_slots;
+    out[i] = -1 - (inv ? inv[anchor] : anchor);
 }
 
 // ---- building blocks of the projection kernels (gfx950)
@@ -350,21 +355,34 @@ __global__ __launch_bounds__(256) void sem_wgrad_kernel(const SemWgradArgs a) {
     }
 }
 
-__global__ __launch_bounds__(64) void sem_wgrad_reduce_kernel(const float* __restrict__ partial, int n_splits,
-                                                               int64_t n4, float* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n4) return;
-    // (eight loads on the way: one after the other the sums of a small step, on few wavefronts, took 25 us)
+// A workgroup sums 64 groups of four coefficients, each of its eight wavefronts an eighth of the splits, eight loads
+// on the way.  (One thread per group and one load after the other: 25 us for 26 splits at d = 128 and 512 features.)
+constexpr int RED_PARTS = 8;
+__global__ __launch_bounds__(64 * RED_PARTS) void sem_wgrad_reduce_kernel(const float* __restrict__ partial, int n_splits,
+                                                                          int64_t n4, float* __restrict__ out) {
+    __shared__ float4 part[RED_PARTS][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t at = i < n4 ? i : n4 - 1;
+    const int per = (n_splits + RED_PARTS - 1) / RED_PARTS, lo = wave * per, hi = min(n_splits, lo + per);
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k0 = 0; k0 < n_splits; k0 += 8) {
+    for (int k0 = lo; k0 < hi; k0 += 8) {
         float4 v[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const float4*>(partial)[(size_t)min(k0 + q, n_splits - 1) * n4 + i];
+        for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const float4*>(partial)[(size_t)min(k0 + q, hi - 1) * n4 + at];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            if (k0 + q >= n_splits) break;
+            if (k0 + q >= hi) break;
             s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w;
         }
+    }
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || i >= n4) return;
+#pragma unroll
+    for (int w = 1; w < RED_PARTS; ++w) {
+        const float4 v = part[w][lane];
+        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
     reinterpret_cast<float4*>(out)[i] = s;
 }
@@ -421,7 +439,7 @@ hipError_t launch_sem_wgrad(const SemWgradArgs& a, float* out, hipStream_t s) {
     const int blocks = ((a.n_splits + 7) / 8) * 8 * tiles;
     hipLaunchKernelGGL(sem_wgrad_kernel, dim3(blocks), dim3(256), 0, s, a);
     const int64_t n4 = (int64_t)a.d * a.ds / 4;
-    hipLaunchKernelGGL(sem_wgrad_reduce_kernel, dim3((unsigned)((n4 + 63) / 64)), dim3(64), 0, s,
+    hipLaunchKernelGGL(sem_wgrad_reduce_kernel, dim3((unsigned)((n4 + 63) / 64)), dim3(64 * RED_PARTS), 0, s,
                        (const float*)a.partial, a.n_splits, n4, out);
     return hipGetLastError();
 }
