@@ -281,24 +281,39 @@ void take_hidden_pieces(const HiddenPieces& hpc, GemmArgs* second, int n) {
 
 double level_flop(const ngdb_ctx_t* c, const std::vector<Segment>& segs) {
     double rows = 0.0;
-    for (const Segment& sg : segs) rows += sg.rows;
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    for (const Segment& sg : segs) rows += box ? (sg.type == T_INTER ? 2.0 * sg.rows : 0.0) : sg.rows;
     return 4.0 * c->cfg.d * c->cfg.h * rows;
 }
 
 // The operators of one depth as problems of one launch (level.hip), where the MLPs are small and the depth does not have
 // very many rows. 
 bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, LevelArgs* a) {
-    if (c->cfg.family != NGDB_FAMILY_VEC || !level_fits(c->cfg.d, c->cfg.h)) return false;
+    if (!level_fits(c->cfg.d, c->cfg.h)) return false;
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
     const HostPlan& hp = pl->hp;
     *a = LevelArgs{};
     a->d = c->cfg.d; a->h = c->cfg.h;
     for (const Segment& sg : segs) {
+        if (box && sg.type != T_INTER) {
+            if (sg.type != T_PROJ || !level_add(*a, sg.type, LEVEL_PROJECTION, sg.rows, 1, sg.ref_off, sg.rel_off, 0, sg.out_base)) return false;
+            continue;
+        }
         if (sg.type != T_INTER) {
             if (!level_add(*a, sg.type, 0, sg.rows, 1, sg.ref_off, sg.rel_off, sg.mlp_base, sg.out_base)) return false;
             continue;
         }
         for (int g = sg.g_lo; g < sg.g_hi; ++g)
             if (!level_add(*a, sg.type, 1, hp.g_n[g], hp.g_nin[g], sg.ref_off + hp.g_mlp_base[g] - sg.mlp_base, -1, hp.g_mlp_base[g], hp.g_out_base[g])) return false;
+        for (int g = sg.g_lo; box && g < sg.g_hi; ++g)      // the offsets of the same inputs through the second MLP
+            if (!level_add(*a, T_NEG, LEVEL_GATE, hp.g_n[g], hp.g_nin[g], sg.ref_off + hp.g_mlp_base[g] - sg.mlp_base, -1, hp.g_mlp_base[g], hp.g_out_base[g])) return false;
+    }
+    if (box) {
+        a->act = ptr<float>(c->act); a->off = ptr<float>(c->off); a->dact = ptr<float>(c->dact); a->doff = ptr<float>(c->doff);
+        a->Att = ptr<float>(c->Att); a->Gate = ptr<float>(c->Gate); a->dAtt = ptr<float>(c->dAtt); a->dGate = ptr<float>(c->dGate);
+        a->refs = pl->d_in_ref; a->rel = pl->d_rel; a->dst_row = pl->d_in_gslot;
+        a->E = c->prm.E.p; a->R = c->prm.R.p; a->Ro = c->prm.Ro.p;
+        a->keep = true;
     }
     for (int t = 0; t < 3; ++t) {
         const MlpRefs W = mlp_of(c->prm, t);
@@ -584,6 +599,13 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     const int d = c->cfg.d, h = c->cfg.h;
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        LevelArgs la;
+        if (level_problems(c, pl, segs, &la)) {
+            Timed tm(c, NGDB_TK_GEMM_FWD, s);
+            HIPCHK(c, launch_level(la, false, s));
+            tm.work(GEMM_FP32, level_flop(c, segs));
+            continue;
+        }
         GemmArgs g1[GEMM_MAX_GROUP], g2[GEMM_MAX_GROUP];
         int n = 0;
         const Segment* ride = riding_projection(segs);
@@ -892,6 +914,13 @@ int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, Wg
     const HostPlan& hp = pl->hp;
     for (int l = hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        LevelArgs la;
+        if (level_problems(c, pl, segs, &la)) {
+            Timed tm(c, NGDB_TK_GEMM_BWD, s);
+            HIPCHK(c, launch_level(la, true, s));
+            tm.work(GEMM_FP32, level_flop(c, segs));
+            continue;
+        }
         GemmArgs b2[GEMM_MAX_GROUP], b1[GEMM_MAX_GROUP];
         int n = 0;
         const Segment* ride = riding_projection(segs);

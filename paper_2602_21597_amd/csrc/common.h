@@ -294,6 +294,7 @@ hipError_t launch_loss_reduce(const float* terms, int n, float scale, float* los
 // x weights of a depth (512 blocks there: from 4096 queries on the separate launches are as fast, 386 against 395 us).
 constexpr int LEVEL_MAX = 10, LEVEL_WEIGHTS = 32768;
 constexpr long LEVEL_WORK = 512l * LEVEL_WEIGHTS;
+constexpr int LEVEL_GATE = 2, LEVEL_PROJECTION = 3;      // box family (off set): pooling of offsets, projection without MLP
 struct LevelProblem { int type, pool, n, k, ref_off, rel_off, row0, out0; };
 struct LevelMlp { const float *Wa, *ba, *Wb, *bb; float *Z, *H, *dH; };
 struct LevelArgs {
@@ -305,6 +306,8 @@ struct LevelArgs {
     const int32_t *refs, *rel, *out_row, *dst_row;   // out_row: row of act per output (null: itself); dst_row: of dact per reference
     const float *E, *R;
     float *act, *Att, *dact, *dAtt;
+    const float* Ro;
+    float *off, *Gate, *doff, *dGate;
 };
 bool level_fits(int d, int h);
 // adds a problem; false if the launch has no room for it

@@ -86,7 +86,39 @@ struct Layer {
     }
 };
 
+// Box family: projections have no MLP (16 members a workgroup: centre plus, offset plus relu of the relation's rows); the
+// offset side of an intersection pools by the least input times the gate of the mean logit.
 template <bool BWD>
+__device__ __forceinline__ void box_projection(const LevelArgs& a, const LevelProblem& p, int i0) {
+    const int d4 = a.d >> 2;
+    const int n = min(LV_ROWS, p.n - i0) * d4;
+    for (int idx = threadIdx.x; idx < n; idx += LV_T) {
+        const int i = i0 + idx / d4, c = (idx % d4) * 4;
+        const size_t out = (size_t)(p.out0 + i) * a.d + c;
+        if (BWD) {
+            const size_t in = (size_t)a.dst_row[p.ref_off + i] * a.d + c;
+            *reinterpret_cast<float4*>(a.dact + in) = *reinterpret_cast<const float4*>(a.dact + out);
+            *reinterpret_cast<float4*>(a.doff + in) = *reinterpret_cast<const float4*>(a.doff + out);
+            continue;
+        }
+        const int32_t ref = a.refs[p.ref_off + i];
+        const size_t r = (size_t)a.rel[p.rel_off + i] * a.d + c;
+        float4 x, o = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ref >= 0) {
+            x = *reinterpret_cast<const float4*>(a.act + (size_t)ref * a.d + c);
+            o = *reinterpret_cast<const float4*>(a.off + (size_t)ref * a.d + c);
+        } else {
+            x = *reinterpret_cast<const float4*>(a.E + (size_t)(-1 - ref) * a.d + c);
+        }
+        const float4 rc = *reinterpret_cast<const float4*>(a.R + r), ro = *reinterpret_cast<const float4*>(a.Ro + r);
+        x.x += rc.x; x.y += rc.y; x.z += rc.z; x.w += rc.w;
+        o.x += fmaxf(ro.x, 0.f); o.y += fmaxf(ro.y, 0.f); o.z += fmaxf(ro.z, 0.f); o.w += fmaxf(ro.w, 0.f);
+        *reinterpret_cast<float4*>(a.act + out) = x;
+        *reinterpret_cast<float4*>(a.off + out) = o;
+    }
+}
+
+template <bool BWD, bool BOX>
 __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ int row_of[LV_ROWS], out_of[LV_ROWS], in_of[LV_ROWS];     // MLP row / output row / input reference of a tile row
@@ -100,6 +132,15 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int m = LV_ROWS / p.k, i0 = ((int)blockIdx.x - a.tile_start[q]) * m;
     const bool inter = p.pool != 0;
+    if (BOX && p.pool == LEVEL_PROJECTION) {
+        box_projection<BWD>(a, p, i0);
+        return;
+    }
+    const bool gate = BOX && p.pool == LEVEL_GATE;
+    float* const act = gate ? a.off : a.act;
+    float* const dact = gate ? a.doff : a.dact;
+    float* const Att = gate ? a.Gate : a.Att;
+    float* const dAtt = gate ? a.dGate : a.dAtt;
     Layer<BWD> first, second;
     if (BWD) first.start(w.Wb, h, d, h);
     else first.start(w.Wa, d, d, h);
@@ -130,7 +171,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
             if (j < p.k && i < p.n && c < d) {
                 const int r = j * p.n + i;
                 const int32_t ref = a.refs[p.ref_off + r];
-                v = *reinterpret_cast<const float4*>((ref >= 0 ? a.act + (size_t)ref * d : a.E + (size_t)(-1 - ref) * d) + c);
+                v = *reinterpret_cast<const float4*>((ref >= 0 ? act + (size_t)ref * d : a.E + (size_t)(-1 - ref) * d) + c);
                 if (p.rel_off >= 0) {
                     const float4 t = *reinterpret_cast<const float4*>(a.R + (size_t)a.rel[p.rel_off + r] * d + c);
                     v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
@@ -159,9 +200,9 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                 const float y = v[e] + bias[h + n];
                 if (inter) {
                     Ls[lr * xp + n] = y;
-                    if (a.keep && r >= 0) a.Att[(size_t)r * d + n] = y;
+                    if (a.keep && r >= 0) Att[(size_t)r * d + n] = y;
                 } else if (r >= 0) {
-                    a.act[(size_t)out_of[lr] * d + n] = y;
+                    act[(size_t)out_of[lr] * d + n] = y;
                 }
             }
         });
@@ -170,6 +211,15 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
         for (int idx = tid; idx < m * d; idx += LV_T) {
             const int ii = idx / d, c = idx - ii * d;
             if (i0 + ii >= p.n) break;
+            if (gate) {
+                float mean = 0.f, mn = INFINITY;
+                for (int j = 0; j < p.k; ++j) {
+                    mean += Ls[(j * m + ii) * xp + c];
+                    mn = fminf(mn, Xs[(j * m + ii) * xp + c]);
+                }
+                act[(size_t)out_of[ii] * d + c] = mn * sigmoid_f(mean / (float)p.k);
+                continue;
+            }
             float e[NGDB_MAX_CARD], mx = -INFINITY, den = 0.f, y = 0.f;
 #pragma unroll
             for (int j = 0; j < NGDB_MAX_CARD; ++j) {
@@ -184,7 +234,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
             const float inv = 1.f / den;
 #pragma unroll
             for (int j = 0; j < NGDB_MAX_CARD; ++j) y += e[j] * inv * Xs[(min(j, p.k - 1) * m + ii) * xp + c];
-            a.act[(size_t)out_of[ii] * d + c] = y;
+            act[(size_t)out_of[ii] * d + c] = y;
         }
         return;
     }
@@ -196,7 +246,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
             const int lr = idx / c4, c = (idx - lr * c4) * 4;
             const int j = lr / m, i = i0 + lr - j * m;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!inter && j < p.k && i < p.n && c < d) v = *reinterpret_cast<const float4*>(a.dact + (size_t)(p.out0 + i) * d + c);
+            if (!inter && j < p.k && i < p.n && c < d) v = *reinterpret_cast<const float4*>(dact + (size_t)(p.out0 + i) * d + c);
             *reinterpret_cast<float4*>(Xs + lr * xp + c) = v;
         }
         for (int idx = tid; idx < LV_ROWS * e4; idx += LV_T) {
@@ -215,11 +265,32 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
 #pragma unroll
                 for (int j = 0; j < NGDB_MAX_CARD; ++j) {
                     const size_t at = (size_t)(p.row0 + min(j, p.k - 1) * p.n + i0 + ii) * d + c;
-                    e[j] = a.Att[at];
+                    e[j] = Att[at];
                     x[j] = w.Z[at];
                     if (j < p.k) mx = fmaxf(mx, e[j]);
                 }
-                const float dy = a.dact[(size_t)(p.out0 + i0 + ii) * d + c];
+                const float dy = dact[(size_t)(p.out0 + i0 + ii) * d + c];
+                if (gate) {
+                    float mean = 0.f, mn = INFINITY;
+                    int arg = 0;
+#pragma unroll
+                    for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                        if (j < p.k) {
+                            mean += e[j];
+                            if (x[j] < mn) {       // strict: equal offsets keep the lower input
+                                mn = x[j];
+                                arg = j;
+                            }
+                        }
+                    }
+                    const float g = sigmoid_f(mean / (float)p.k), dpre = dy * mn * g * (1.f - g) / (float)p.k;
+                    for (int j = 0; j < p.k; ++j) {
+                        Xs[(j * m + ii) * xp + c] = dpre;
+                        Ls[(j * m + ii) * xp + c] = j == arg ? dy * g : 0.f;
+                        dAtt[(size_t)(p.row0 + j * p.n + i0 + ii) * d + c] = dpre;
+                    }
+                    continue;
+                }
 #pragma unroll
                 for (int j = 0; j < NGDB_MAX_CARD; ++j) {
                     e[j] = j < p.k ? expf(e[j] - mx) : 0.f;
@@ -234,7 +305,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                         const float wj = e[j] * inv, g = wj * (dy * x[j] - tall);
                         Xs[(j * m + ii) * xp + c] = g;
                         Ls[(j * m + ii) * xp + c] = wj * dy;
-                        a.dAtt[(size_t)(p.row0 + j * p.n + i0 + ii) * d + c] = g;
+                        dAtt[(size_t)(p.row0 + j * p.n + i0 + ii) * d + c] = g;
                     }
                 }
             }
@@ -255,7 +326,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int lr = (lane >> 4) * 4 + e;
-                if (row_of[lr] >= 0) a.dact[(size_t)in_of[lr] * d + n] = v[e] + (inter ? Ls[lr * xp + n] : 0.f);
+                if (row_of[lr] >= 0) dact[(size_t)in_of[lr] * d + n] = v[e] + (inter ? Ls[lr * xp + n] : 0.f);
             }
         });
     }
@@ -280,8 +351,11 @@ hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
     if (a.count == 0) return hipSuccess;
     if (!level_fits(a.d, a.h) || (a.d & 3) || (a.h & 3)) return hipErrorInvalidValue;
     const dim3 grid(a.tile_start[a.count]);
-    if (backward) hipLaunchKernelGGL((level_kernel<true>), grid, dim3(LV_T), lv_lds(a.d, a.h), s, a);
-    else hipLaunchKernelGGL((level_kernel<false>), grid, dim3(LV_T), lv_lds(a.d, a.h), s, a);
+    const size_t lds = lv_lds(a.d, a.h);
+    if (a.off && backward) hipLaunchKernelGGL((level_kernel<true, true>), grid, dim3(LV_T), lds, s, a);
+    else if (a.off) hipLaunchKernelGGL((level_kernel<false, true>), grid, dim3(LV_T), lds, s, a);
+    else if (backward) hipLaunchKernelGGL((level_kernel<true, false>), grid, dim3(LV_T), lds, s, a);
+    else hipLaunchKernelGGL((level_kernel<false, false>), grid, dim3(LV_T), lds, s, a);
     return hipGetLastError();
 }
 

@@ -127,3 +127,9 @@ def test_operators_of_a_depth_in_one_launch(d, h, B):
     par.assert_close(eng.score(plan, torch.from_numpy(cand).cuda()).cpu().numpy(),
                      orank.score_candidates(case.qb, cand, om.Model(case.params, case.gamma)), "scores d=%d h=%d" % (d, h))
     plan.free()
+
+
+@pytest.mark.parametrize("d,h,B", [(8, 12, 20), (36, 100, 40), (64, 512, 40), (128, 256, 60), (132, 256, 30)])
+def test_box_operators_of_a_depth_in_one_launch(d, h, B):
+    from . import parity_box as pb
+    pb.check_forward_backward(pb.BoxCase(500, 9, d, h, B, 6, 4.0, alpha=0.2, seed=d + h))
