@@ -998,7 +998,15 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     // text features the fusion of all rows that are scored, run beside the forward pass, which needs the anchors' rows only.
     int32_t* e_src = nullptr;
     const bool sem = c->cfg.d_sem > 0;
-    const bool aside = c->n_side > 0;
+    const int64_t n_contrib = (int64_t)hp.n_anchor + B + (int64_t)B * K, max_rows = std::min<int64_t>(n_contrib, c->cfg.n_entities);
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    // The three waits between streams cost the host some 30 us a step.  Steps that are bound by the host either way stay on
+    // the caller's stream: an index of one launch, or small MLPs with few rows to update (64 queries x 32 negatives 119
+    // against 133 us at d = 64 and 211 against 220 at d = 400; 256 x 64 at d = 64 145 against 175, 1024 x 64 187 against 202, but
+    // 1024 x 256 237 against 222; at d = 128, h = 256 256 x 64 196 against 184, as boxes, with fewer depths, 141 against 167).
+    const bool host_bound = !sem && (n_contrib <= 4096 || (level_fits(d, c->cfg.h) && (box || d * c->cfg.h <= 16384) &&
+                                                          n_contrib <= 70000 && max_rows * d <= 2000000));
+    const bool aside = c->n_side > 0 && !host_bound;
     hipStream_t s_idx = aside ? c->side[0] : stream;
     if (sem && (rc = cast_projection(c, stream)) != NGDB_OK) return rc;
     if (aside) {
@@ -1024,7 +1032,6 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     sa.pos = scored.pos; sa.cand = scored.cand; sa.B = B; sa.C = K; sa.d = d; sa.max_branch = std::max(1, hp.max_branch);
     sa.gamma = c->cfg.gamma; sa.score = ptr<float>(c->score); sa.coef = ptr<float>(c->coef);
     sa.win = sem ? nullptr : ptr<int32_t>(c->win); sa.mask = sem ? c->mask.p : nullptr; sa.dact = ptr<float>(c->dact); sa.loss_terms = ptr<float>(c->loss_terms);
-    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
     if (box) { sa.off = ptr<float>(c->off); sa.doff = ptr<float>(c->doff); sa.alpha = c->cfg.box_alpha; }
     if (c->cfg.score_bf16) sa.E16 = ptr<uint16_t>(c->Eb);
     {
@@ -1039,8 +1046,6 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     // step.  (All rows after the backward pass, beside the weight gradients: 307 against 290 us a step at 512 queries over
     // 15 000 entities, 507 against 457 at 1024 over 63 000, 6.64 against 6.46 ms at 4096 over 2.5 million.)
     hipStream_t s_tab = aside ? c->side[0] : stream;     // after the index on the same stream
-    const int64_t n_contrib = (int64_t)hp.n_anchor + B + (int64_t)B * K;
-    const int64_t max_rows = std::min<int64_t>(n_contrib, c->cfg.n_entities);
     // A pass that ends before the backward pass does even on few wavefronts is kept to few of them: at full width it
     // takes the compute units and caches from the launches that the step waits for.  Estimates in us: three rows read
     // and written at 2.7 TB/s by one workgroup per compute unit, against a chain of launches and its contractions.

@@ -79,20 +79,21 @@ def test_gradient_index_by_size(N, B, n_keys):
 
 
 # table rows beside the backward pass, rows of anchors after it: every row an anchor's, nearly none, a pass kept to few
-# wavefronts, one at full width over a table beyond the caches, text features, a bf16 copy of the table
-@pytest.mark.parametrize("N,d,B,K,d_sem,bf16", [(20, 32, 60, 3, 0, False), (9000, 64, 3, 50, 0, False), (9000, 260, 40, 200, 0, False),
+# wavefronts, one at full width over a table beyond the caches, text features, a bf16 copy of the table (hidden layers wide
+# enough, and contributions many enough, that the second stream is used)
+@pytest.mark.parametrize("N,d,B,K,d_sem,bf16", [(20, 32, 60, 80, 0, False), (9000, 64, 3, 1500, 0, False), (9000, 260, 40, 200, 0, False),
                                                 (60000, 400, 60, 1000, 0, False), (3000, 40, 50, 90, 64, False),
                                                 (60000, 520, 60, 1000, 64, False), (3000, 40, 50, 90, 0, True)])
 def test_tables_beside_the_backward_pass(N, d, B, K, d_sem, bf16):
     import torch
     from paper_2602_21597_amd import Engine
     qb = wl.make_batch(wl.make_kg(N, 7, 5 * N, 2.1, 1), B, {n: 1.0 for n in wl.configs.ALL14}, 2)
-    params = wl.make_params(N, 7, d, 32, 3, d_sem=d_sem)
+    params = wl.make_params(N, 7, d, 520, 3, d_sem=d_sem)
     sem = wl.make_sem_features(N, d_sem, 4) if d_sem else None
     negs = torch.from_numpy(wl.make_negatives(N, B, K, 5)).cuda()
     out = []
     for streams in (1, 2):
-        eng = Engine(N, 7, d, 32, 12.0, num_streams=streams, d_sem=d_sem, score_bf16=bf16)
+        eng = Engine(N, 7, d, 520, 12.0, num_streams=streams, d_sem=d_sem, score_bf16=bf16)
         eng.bind_numpy(params, sem_bits=sem)
         plan = eng.plan(qb)
         eng.forward_backward(plan, negs)
