@@ -8,7 +8,9 @@
 //
 // The build runs beside the forward pass and is bound by its launches, not by its bytes, until there are
 // millions of keys.  Up to SMALL_KEYS keys one workgroup sorts everything in LDS (700 keys of the
-// smallest workload: 14 launches and 32 us became one of 9 us); up to MID_TILES tiles the histogram is
+// smallest workload: 14 launches and 32 us became one of 9 us); up to OWN_TILES tiles every workgroup of the
+// scatter adds up the histogram for itself, and up to OWN_KEYS keys the segment heads before it too (five launches
+// for two passes); up to MID_TILES tiles the histogram is
 // scanned by one launch instead of three, each workgroup adding up what lies before its digit (at
 // 66 000 keys 8 launches instead of 14); beyond that this would read the histogram too often.
 #include "common.h"
@@ -168,11 +170,36 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_rows_kernel(const int32_t* 
 
 // Segment heads of a short sorted array in one launch after the tile sums: like scan_apply_kernel<true>, each workgroup
 // adding up the sums of the tiles before it (at most MID_TILES of them).
+// OWN: without sums, each counting the heads before it (at most OWN_KEYS keys).
+constexpr int OWN_KEYS = 16384;
+template <bool OWN>
 __global__ __launch_bounds__(SCAN_THREADS) void heads_kernel(const int32_t* __restrict__ keys, int64_t n,
                                                              const int32_t* __restrict__ sums, int32_t* __restrict__ uniq,
                                                              int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) {
     int32_t base, all, tot;
-    block_exclusive_scan((int)threadIdx.x < (int)blockIdx.x ? sums[threadIdx.x] : 0, &base);
+    int32_t mine = 0;
+    if (OWN) {
+        const int n4 = (int)blockIdx.x * (SCAN_TILE / 4);
+        for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * SCAN_THREADS) {
+            int4 k[4];
+            int32_t last[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = min(i0 + j * SCAN_THREADS, n4 - 1);
+                k[j] = reinterpret_cast<const int4*>(keys)[i];
+                last[j] = keys[max(4 * i - 1, 0)];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = i0 + j * SCAN_THREADS;
+                if (i >= n4) break;
+                mine += (i == 0 || k[j].x != last[j] ? 1 : 0) + (k[j].y != k[j].x ? 1 : 0) + (k[j].z != k[j].y ? 1 : 0) + (k[j].w != k[j].z ? 1 : 0);
+            }
+        }
+    } else {
+        mine = (int)threadIdx.x < (int)blockIdx.x ? sums[threadIdx.x] : 0;
+    }
+    block_exclusive_scan(mine, &base);
     const int64_t first = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
     int32_t v[SCAN_ITEMS], s = 0;
     for (int k = 0; k < SCAN_ITEMS; ++k) {
@@ -208,7 +235,9 @@ __device__ __forceinline__ unsigned long long digit_peers(bool valid, int digit)
 // consecutive keys (thread t takes key round*256 + t), so the order inside the
 // tile is (round, wavefront, lane); the rank of a key among equal digits is
 // running count of earlier rounds + counts of lower wavefronts + lower lanes.
-template <bool FIRST>
+// OWN: offs is the histogram itself (at most OWN_TILES tiles), scanned by every workgroup.
+constexpr int OWN_TILES = 32;
+template <bool FIRST, bool OWN>
 __global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const KeySource<FIRST> src, int64_t n, int shift, int n_tiles,
                                                                const int32_t* __restrict__ offs,
                                                                int32_t* __restrict__ keys_out,
@@ -216,7 +245,24 @@ __global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const KeySource<F
     __shared__ int32_t running[RADIX];                    // global position of the next key per digit
     __shared__ int32_t wcnt[SORT_THREADS / 64][RADIX];    // per wavefront counts of the current round
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    running[threadIdx.x] = offs[(size_t)threadIdx.x * n_tiles + blockIdx.x];
+    if (OWN) {
+        int32_t before = 0, total = 0, all;
+#pragma unroll
+        for (int i0 = 0; i0 < OWN_TILES; i0 += 8) {
+            if (i0 >= n_tiles) break;
+            int32_t x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = offs[threadIdx.x * n_tiles + min(i0 + i, n_tiles - 1)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                before += i0 + i < (int)blockIdx.x ? x[i] : 0;
+                total += i0 + i < n_tiles ? x[i] : 0;
+            }
+        }
+        running[threadIdx.x] = block_exclusive_scan(total, &all) + before;
+    } else {
+        running[threadIdx.x] = offs[(size_t)threadIdx.x * n_tiles + blockIdx.x];
+    }
     for (int w = 0; w < SORT_THREADS / 64; ++w) wcnt[w][threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
@@ -405,7 +451,7 @@ hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* t
         return hipGetLastError();
     }
     const int n_tiles = tiles_of(n, SORT_TILE);
-    const bool mid = n_tiles <= MID_TILES;
+    const bool own = n_tiles <= OWN_TILES, mid = !own && n_tiles <= MID_TILES;
     int32_t* offs = mid ? buf.hist + (size_t)RADIX * n_tiles : buf.hist;
     int32_t *kin = buf.keys_a, *kout = buf.keys_b, *vin = buf.vals_a, *vout = buf.vals_b;
     for (int shift = 0; shift < bits; shift += RADIX_BITS) {
@@ -415,27 +461,35 @@ hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* t
             hipLaunchKernelGGL((hist_kernel<true>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, first, n, shift, n_tiles, buf.hist);
         else
             hipLaunchKernelGGL((hist_kernel<false>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, sorted, n, shift, n_tiles, buf.hist);
-        if (mid) {
+        if (own) {
+        } else if (mid) {
             hipLaunchKernelGGL(scan_rows_kernel, dim3(RADIX), dim3(SCAN_THREADS), 0, s, (const int32_t*)buf.hist, n_tiles, offs);
         } else {
             hipError_t e = scan_exclusive(buf.hist, buf.hist, (int64_t)RADIX * n_tiles, buf.scan_tmp, s);
             if (e != hipSuccess) return e;
         }
-        if (shift == 0)
-            hipLaunchKernelGGL((scatter_kernel<true>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, first, n, shift, n_tiles,
-                               (const int32_t*)offs, kout, vout);
-        else
-            hipLaunchKernelGGL((scatter_kernel<false>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, sorted, n, shift, n_tiles,
-                               (const int32_t*)offs, kout, vout);
+#define NGDB_SCATTER(FIRST, OWN, SRC)                                                                                                  \
+    hipLaunchKernelGGL((scatter_kernel<FIRST, OWN>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, SRC, n, shift, n_tiles, (const int32_t*)offs, kout, vout)
+        if (shift == 0 && own) NGDB_SCATTER(true, true, first);
+        else if (shift == 0) NGDB_SCATTER(true, false, first);
+        else if (own) NGDB_SCATTER(false, true, sorted);
+        else NGDB_SCATTER(false, false, sorted);
+#undef NGDB_SCATTER
         std::swap(kin, kout);
         std::swap(vin, vout);
     }
     // segment heads over the sorted keys
     const int nt = tiles_of(n, SCAN_TILE);
+    if (n <= OWN_KEYS) {
+        hipLaunchKernelGGL((heads_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n, (const int32_t*)nullptr, buf.uniq,
+                           buf.seg_off, buf.n_uniq);
+        *src_out = vin;
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((scan_sums_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n,
                        buf.scan_tmp);
     if (nt <= MID_TILES) {
-        hipLaunchKernelGGL(heads_kernel, dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n, (const int32_t*)buf.scan_tmp,
+        hipLaunchKernelGGL((heads_kernel<false>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n, (const int32_t*)buf.scan_tmp,
                            buf.uniq, buf.seg_off, buf.n_uniq);
     } else {
         hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, buf.scan_tmp, nt, buf.n_uniq);

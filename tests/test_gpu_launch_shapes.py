@@ -55,9 +55,10 @@ def test_candidate_lists_shared_by_workgroups(B, C):
     plan.free()
 
 
-# keys: one; 4096 and one more (one workgroup / tiles); 262 144 and more (short / long histogram); a bound of one digit, of
-# two and of three
-@pytest.mark.parametrize("N,B,n_keys", [(50, 1, 3), (200, 8, 4096), (200, 8, 4104), (70000, 64, 4096), (70000, 64, 262144),
+# keys: one; 4096 and more (one workgroup / tiles); 16 384 and more (heads counted by every workgroup / scanned); 32 768 and more
+# (histogram scanned by every workgroup / once); 262 144 and more (short / long histogram); a bound of one digit, of two and of three
+@pytest.mark.parametrize("N,B,n_keys", [(50, 1, 3), (200, 8, 4096), (200, 8, 4104), (200, 8, 16384), (70000, 8, 16392),
+                                        (70000, 8, 32768), (3000, 8, 32776), (70000, 64, 4096), (70000, 64, 262144),
                                         (300, 64, 262208), (1000, 700, 300000)])
 def test_gradient_index_by_size(N, B, n_keys):
     import torch
