@@ -1047,10 +1047,12 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     // 15 000 entities, 507 against 457 at 1024 over 63 000, 6.64 against 6.46 ms at 4096 over 2.5 million.)
     hipStream_t s_tab = aside ? c->side[0] : stream;     // after the index on the same stream
     // A pass that ends before the backward pass does even on few wavefronts is kept to few of them: at full width it
-    // takes the compute units and caches from the launches that the step waits for.  Estimates in us: three rows read
-    // and written at 2.7 TB/s by one workgroup per compute unit, against a chain of launches and its contractions.
+    // takes the compute units and caches from the launches that the step waits for.  Estimates in us: by 1024 wavefronts three
+    // rows read and written at 2.7 TB/s, but 2 us a row, and 0.2 us a contribution; a chain of launches and its contractions.
     const double mlp_rows = (double)hp.n_proj + (box ? 2.0 : 1.0) * hp.n_int_rows + hp.n_neg;
-    const bool short_pass = aside ? 24.0 * max_rows * d / 2.7e6 <= 100.0 + 12.0 * c->cfg.h * d * mlp_rows / 1e8 : max_rows <= 65536;
+    const double pass_us = std::max(24.0 * max_rows * d / 2.7e6, 2.0 * max_rows / 1024.0) + 0.2 * n_contrib / 1024.0;
+    const double chain_us = level_fits(d, c->cfg.h) ? 25.0 + 18.0 * hp.n_levels : 100.0 + 12.0 * c->cfg.h * d * mlp_rows / 1e8;
+    const bool short_pass = aside ? pass_us <= chain_us : max_rows <= 65536;
     const int64_t t = c->step + 1;
     const AdamHyper ah{c->cfg.lr, c->cfg.beta1, c->cfg.beta2, c->cfg.eps,
                        (float)(1.0 - std::pow((double)c->cfg.beta1, (double)t)),
@@ -1098,7 +1100,15 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     if (rc != NGDB_OK) return rc;
 
     // 6. the other table rows, relation tables, dense Adam
-    if (!aside && (rc = resolve_records()) != NGDB_OK) return rc;
+    const bool unresolved = !aside && short_pass;       // the launch that ends the step resolves for itself
+    LossSum loss_sum{};
+    if (unresolved) {
+        te.src = e_src; te.pair_coef = ptr<float>(c->coef); te.pair_win = sem ? nullptr : ptr<int32_t>(c->win);
+        te.n_rowsrc = hp.n_anchor; te.row_base = hp.n_slots; te.B = B; te.K = K;
+        loss_sum = LossSum{ptr<float>(c->loss_terms), B, B > 0 ? 1.f / (2.f * B) : 0.f, d_loss};
+    } else if (!aside && (rc = resolve_records()) != NGDB_OK) {
+        return rc;
+    }
     tr.g_bf16 = nullptr; tr.mask = nullptr;
     tr.P = c->prm.R.p; tr.Mo = c->prm.R.m; tr.Vo = c->prm.R.v;
     tr.uniq = pl->d_r_uniq; tr.seg_off = pl->d_r_seg_off; tr.n_uniq_dev = pl->d_n_r_uniq;
@@ -1136,7 +1146,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     {
         Timed tm(c, short_pass ? NGDB_TK_ADAM : NGDB_TK_TABLE_R, stream);
         const int64_t left = aside ? std::min<int64_t>(hp.n_anchor, max_rows) : (short_pass ? max_rows : 0);
-        HIPCHK(c, launch_step_tail(te, left, small, n_small, c->cfg.n_relations, job, ah, stream));
+        HIPCHK(c, launch_step_tail(te, left, small, n_small, c->cfg.n_relations, job, loss_sum, ah, stream));
     }
     if (sem) {
         // gradient of the text projection over the touched rows, then its Adam step

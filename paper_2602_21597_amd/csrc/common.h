@@ -451,6 +451,12 @@ struct TableArgs {
     // ScoreArgs::mask).  rec_coef may be null if all records are gradient rows.
     const float* rec_coef;
     const int32_t* rec_row;
+    // the records unresolved (at the end of a step only): contribution numbers in segment order and what
+    // launch_resolve makes records of; rec_coef and rec_row are not read then
+    const int32_t* src = nullptr;
+    const float* pair_coef = nullptr;
+    const int32_t* pair_win = nullptr;
+    int n_rowsrc = 0, row_base = 0, B = 0, K = 1;
     const float* dact;
     const float* act;
     const void* mask;              // set together with g_bf16
@@ -494,9 +500,15 @@ struct TableTail {
     int blocks[2];
     TableArgs job[2];
     DenseAdamJob dense;
+    // one more workgroup: loss[0] = loss_scale * sum of the loss terms (null: not here)
+    const float* loss_terms;
+    int n_loss;
+    float loss_scale;
+    float* loss;
 };
+struct LossSum { const float* terms; int n; float scale; float* loss; };
 hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArgs* small, int n_small, int small_rows,
-                            const DenseAdamJob& dense, const AdamHyper& hp, hipStream_t s);
+                            const DenseAdamJob& dense, const LossSum& loss, const AdamHyper& hp, hipStream_t s);
 
 // ---------------------------------------------------------------- text-feature fusion (sem.hip)
 hipError_t launch_cast_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t s);

@@ -26,6 +26,33 @@
 namespace ngdb {
 namespace {
 
+struct Record { float coef; int32_t row; };
+// of contribution c: the first n_rowsrc are gradient rows, then the positives and the negatives
+__device__ __forceinline__ Record record_of(int32_t c, int n_rowsrc, int row_base, int B, int K, const float* __restrict__ coef,
+                                            const int32_t* __restrict__ win) {
+    if (c < n_rowsrc) return {0.f, -1 - (row_base + c)};
+    const int r = c - n_rowsrc;
+    int pair;
+    if (r < B) {
+        pair = r * (K + 1);                       // the query's positive
+    } else {
+        const int q = (r - B) / K;
+        pair = q * (K + 1) + 1 + ((r - B) - q * K);
+    }
+    return {coef[pair], win ? win[pair] : pair};
+}
+
+// one workgroup of 256 threads
+__device__ __forceinline__ void sum_loss(const float* __restrict__ terms, int n, float scale, float* __restrict__ loss) {
+    __shared__ float part[4];
+    float s = 0.f;
+    for (int i = threadIdx.x; i < n; i += 256) s += terms[i];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) loss[0] = scale * ((part[0] + part[1]) + (part[2] + part[3]));
+}
+
 // rec_row[t] >= 0: pair contribution (rec_coef[t] = dL/ds): the row of act of the pair's
 // winning branch if win is given, else the pair number; rec_row[t] < 0: row -1-rec_row[t]
 // of dact (gradient row, added as is).  With loss_terms, one more workgroup (the last) sums the
@@ -38,32 +65,13 @@ __global__ __launch_bounds__(256) void resolve_kernel(const int32_t* __restrict_
                                                       float* __restrict__ loss) {
     const int walkers = (int)gridDim.x - (loss_terms ? 1 : 0);
     if ((int)blockIdx.x == walkers) {      // (only with loss_terms)
-        __shared__ float part[4];
-        float s = 0.f;
-        for (int i = threadIdx.x; i < B; i += 256) s += loss_terms[i];
-        s = wave_sum(s);
-        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) loss[0] = loss_scale * ((part[0] + part[1]) + (part[2] + part[3]));
+        sum_loss(loss_terms, B, loss_scale, loss);
         return;
     }
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)walkers * blockDim.x) {
-        const int32_t c = src[t];
-        if (c < n_rowsrc) {
-            rec_coef[t] = 0.f;
-            rec_row[t] = -1 - (row_base + c);
-        } else {
-            const int r = c - n_rowsrc;
-            int pair;
-            if (r < B) {
-                pair = r * (K + 1);                       // the query's positive
-            } else {
-                const int q = (r - B) / K;
-                pair = q * (K + 1) + 1 + ((r - B) - q * K);
-            }
-            rec_coef[t] = coef[pair];
-            rec_row[t] = win ? win[pair] : pair;
-        }
+        const Record r = record_of(src[t], n_rowsrc, row_base, B, K, coef, win);
+        rec_coef[t] = r.coef;
+        rec_row[t] = r.row;
     }
 }
 
@@ -199,8 +207,16 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
         for (int base = t0; base < t1; base += 64) {
             const int n = min(64, t1 - base);
             const int tl = base + min(lane, n - 1);
-            const int32_t my_row = a.rec_row[tl];
-            const float my_coef = a.rec_coef ? a.rec_coef[tl] : 0.f;
+            int32_t my_row;
+            float my_coef = 0.f;
+            if (PICK && a.src) {
+                const Record r = record_of(a.src[tl], a.n_rowsrc, a.row_base, a.B, a.K, a.pair_coef, a.pair_win);
+                my_row = r.row;
+                my_coef = r.coef;
+            } else {
+                my_row = a.rec_row[tl];
+                if (a.rec_coef) my_coef = a.rec_coef[tl];
+            }
             // gradient rows come first in a segment
             const int n_rows = __popcll(__ballot(my_row < 0 && lane < n));
             for (int j0 = 0; j0 < n_rows; j0 += G) {
@@ -353,6 +369,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (BOX && 
                                   (int)((gridDim.x * blockDim.x) >> 6));
 }
 
+// (its records may come unresolved: one launch less where everything waits for the backward pass anyway)
 // The end of a step: the first workgroups walk up to two small plain tables of the same width (the relation tables), the
 // next ones the rows of the main table that are left (in a small step without a second stream: all of them), the last
 // the dense tensors.  As launches of their own each of these would add its latency to the end of the step.
@@ -363,6 +380,10 @@ void step_tail_kernel(const TableArgs a, const TableTail tail, const AdamHyper h
     const int mb = b - tail.blocks[0] - tail.blocks[1];
     if (mb >= tail.main_blocks) {
         const int db = mb - tail.main_blocks;
+        if (db == tail.dense.count * tail.dense_blocks) {
+            sum_loss(tail.loss_terms, tail.n_loss, tail.loss_scale, tail.loss);
+            return;
+        }
         dense_adam(tail.dense, db / tail.dense_blocks, hp, (int64_t)(db % tail.dense_blocks) * 256 + threadIdx.x,
                    (int64_t)tail.dense_blocks * 256);
         return;
@@ -434,7 +455,7 @@ hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few
 }
 
 hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArgs* small, int n_small, int small_rows,
-                            const DenseAdamJob& dense, const AdamHyper& hp, hipStream_t s) {
+                            const DenseAdamJob& dense, const LossSum& loss, const AdamHyper& hp, hipStream_t s) {
     if (!table_args_ok(a) || n_small < 0 || n_small > 2 || (n_small > 0 && !small)) return hipErrorInvalidValue;
     TableTail tail{};
     tail.main_blocks = (int)std::min<int64_t>(TABLE_BLOCKS, (max_rows + 3) / 4);
@@ -450,7 +471,8 @@ hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArg
     int64_t longest = 0;
     for (int t = 0; t < dense.count; ++t) longest = std::max(longest, dense.n[t]);
     tail.dense_blocks = (int)std::max<int64_t>(1, std::min<int64_t>((longest + 255) / 256, 512));
-    const int blocks = tail.blocks[0] + tail.blocks[1] + tail.main_blocks + dense.count * tail.dense_blocks;
+    tail.loss_terms = loss.terms; tail.n_loss = loss.n; tail.loss_scale = loss.scale; tail.loss = loss.loss;
+    const int blocks = tail.blocks[0] + tail.blocks[1] + tail.main_blocks + dense.count * tail.dense_blocks + (loss.terms ? 1 : 0);
     if (blocks == 0) return hipSuccess;
 #define NGDB_TAIL(NCH, SEM_, BOX_, SH_)                                                                                          \
     do {                                                                                                                         \
