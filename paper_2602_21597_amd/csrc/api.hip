@@ -781,6 +781,39 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
         bool emitted = false;
         if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_FWD, g1, n, s, &emitted)) != NGDB_OK) return rc_g;
         if (emitted) take_hidden_pieces(hpc, g2, n);
+        // second layer with the pooling in its epilogue: the intersections class by class
+        GemmArgs gp[GEMM_MAX_GROUP];
+        int np = 0;
+        bool pooled = false;
+        for (int i = 0; i < n && np <= GEMM_MAX_GROUP; ++i) {
+            const Segment& sg = segs[i];
+            const int classes = sg.type == T_INTER ? sg.g_hi - sg.g_lo : 1;
+            pooled = pooled || sg.type == T_INTER;
+            for (int k = 0; k < classes; ++k, ++np) {
+                if (np == GEMM_MAX_GROUP) { np = GEMM_MAX_GROUP + 1; break; }
+                GemmArgs& b = gp[np] = g2[i];
+                if (sg.type != T_INTER) continue;
+                const int g = sg.g_lo + k, r0 = pl->hp.g_mlp_base[g] - sg.mlp_base, out0 = pl->hp.g_out_base[g];
+                b.A += (size_t)r0 * h; b.a_row0 = r0; b.M = pl->hp.g_n[g] * pl->hp.g_nin[g];
+                b.C = w.reclaim ? nullptr : b.C + (size_t)r0 * d;      // (the backward pass reads the logits)
+                b.pool_k = pl->hp.g_nin[g];
+                b.pool_X = w.Z[T_INTER] + ((w.reclaim ? 0 : (size_t)sg.mlp_base) + r0) * d;
+                b.pool_out = w.reclaim ? w.act : w.act + (size_t)out0 * d;
+                b.pool_row = w.reclaim ? pl->d_f_row + out0 : nullptr;
+            }
+        }
+        if (pooled && np <= GEMM_MAX_GROUP) {
+            Timed tm(c, NGDB_TK_GEMM_FWD, s);
+            int route = GEMM_FP32;
+            const hipError_t e = launch_gemm_group(gp, np, s, &route);
+            if (e == hipSuccess) {
+                double flop = 0.0;
+                for (int i = 0; i < np; ++i) flop += 2.0 * gp[i].M * gp[i].N * gp[i].K;
+                tm.work(route, flop);
+                continue;
+            }
+            if (e != hipErrorNotSupported) HIPCHK(c, e);
+        }
         if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_FWD, g2, n, s)) != NGDB_OK) return rc_g;
         for (const Segment& sg : segs) {
             if (sg.type != T_INTER) continue;

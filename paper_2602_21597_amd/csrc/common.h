@@ -145,6 +145,14 @@ struct GemmArgs {
     int a_kt = 0;
     uint16_t* c_pieces = nullptr;
     int c_kt = 0;
+    int a_row0 = 0;                // row 0 of A is row a_row0 of a_pieces (with pool_k only)
+    // The output rows are the logits of intersections of pool_k inputs (row j * n + i: input j of member i, M = n * pool_k):
+    // row i of pool_out, or row pool_row[i], receives sum_j softmax_j(C[j * n + i]) * pool_X[j * n + i] (leading dimension ldc).
+    // C may be null then.  Only launches of split weights in small tiles do this; others return hipErrorNotSupported.
+    int pool_k = 0;
+    const float* pool_X = nullptr;
+    float* pool_out = nullptr;
+    const int32_t* pool_row = nullptr;
 };
 // GEMM_FP32: fp32 MFMA.  GEMM_SPLIT: every fp32 operand value as the exact sum of three bf16
 // values, the six largest of the nine partial products on the bf16 MFMA with fp32 accumulation

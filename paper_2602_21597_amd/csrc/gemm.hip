@@ -299,7 +299,9 @@ __device__ __forceinline__ bf16x8 piece_at(const uint16_t* at, int q) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + q * 512));
 }
 
-template <int BM, int BN, int NW, bool AK, bool BKC, bool SPLIT = false, int PF = 1, bool BP = false, bool AP = false>
+// POOL: problems with pool_k set take whole intersections: a tile is all inputs of 32 / pool_k members, and the pooling
+// is the end of the epilogue (a launch of its own cost 3 to 5 us at each depth).
+template <int BM, int BN, int NW, bool AK, bool BKC, bool SPLIT = false, int PF = 1, bool BP = false, bool AP = false, bool POOL = false>
 __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
     static_assert(!BP || (SPLIT && AK), "B operand from split pieces: split route with k-contiguous A only");
     static_assert(!AP || (BP && BM == 32), "A operand from split pieces: with B from pieces, one block of rows");
@@ -325,10 +327,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
     const int local = (int)blockIdx.x - first;
     const int per_die = (last - first) >> 3;
     const int tile = (local & 7) * per_die + (local >> 3);
-    const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+    const int cls = POOL && a.pool_k ? a.pool_k : 1, mem = BM / cls, n_mem = a.M / cls;     // POOL: inputs, members per tile and in all
+    const int tiles_m = POOL ? (n_mem + mem - 1) / mem : (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     if (tile >= tiles_m * tiles_n) return;
     const bool m_major = a.M >= a.N;
-    const int m0 = (m_major ? tile / tiles_n : tile % tiles_m) * BM;
+    const int mt = m_major ? tile / tiles_n : tile % tiles_m;
+    const int m0 = mt * BM;
+    auto pool_row_of = [&](int lr, bool* ok) {          // POOL: row of A and C that row lr of the tile is
+        const int j = lr / mem, i = mt * mem + lr - j * mem;
+        *ok = j < cls && i < n_mem;
+        return *ok ? j * n_mem + i : a.M - 1;
+    };
     const int n0 = (m_major ? tile % tiles_n : tile / tiles_m) * BN;
     const bool first_n_tile = n0 == 0;
     constexpr int TM = BM / 32, TN = BN / 32;
@@ -366,7 +375,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
         if (AK && !AP) {
             const int gm = m0 + (lane + i * 64) / (BK / 4);
             avalid[i] = gm < a.M;
-            const int gmc = min(gm, a.M - 1);
+            int gmc = min(gm, a.M - 1);
+            if (POOL) gmc = pool_row_of((lane + i * 64) / (BK / 4), &avalid[i]);
             if (a.a_ref) {
                 const int32_t r = a.a_ref[gmc];
                 arow[i] = r >= 0 ? a.a_base0 + (size_t)r * a.lda : a.a_base1 + (size_t)(-1 - r) * a.lda;
@@ -374,6 +384,18 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
             } else {
                 arow[i] = a.A + (size_t)gmc * a.lda;
             }
+        }
+    }
+
+    // AP: this lane's place in the first k-tile of the A pieces
+    size_t a_lane = 0;
+    if (AP) {
+        if (POOL) {
+            bool ok;
+            const int r = pool_row_of(lane & 31, &ok) + a.a_row0;
+            a_lane = (size_t)(r >> 5) * a.a_kt * WTILE + ((lane >> 5) * 32 + (r & 31)) * 8;
+        } else {
+            a_lane = (size_t)(m0 / 32) * a.a_kt * WTILE + lane * 8;
         }
     }
 
@@ -392,7 +414,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
     _Pragma("unroll") for (int q = 0; q < EPT; ++q) {                                      \
         const int e = tid + q * NW * 64;                                                    \
         const int lr = e / BN, lc = e % BN;                                                 \
-        const int row = min(m0 + lr, a.M - 1), col = min(n0 + lc, a.N - 1);                 \
+        bool row_ok;                                                                        \
+        const int row = POOL ? pool_row_of(lr, &row_ok) : min(m0 + lr, a.M - 1), col = min(n0 + lc, a.N - 1); \
         e_bias[q] = has_bias ? a.bias[col] : 0.f;                                           \
         e_mask[q] = has_mask ? a.mask[(size_t)row * a.ldmask + col] : 1.f;                  \
         e_add[q] = has_addend ? a.addend[(size_t)row * a.ldadd + col] : 0.f;                \
@@ -423,7 +446,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
     }
 #define NGDB_ISSUE_PIECES(u, kc, live)                                                       \
     if (AP) {                                                                                \
-        const uint16_t* at = (live) ? a.a_pieces + ((size_t)(m0 / 32) * a.a_kt + (kc) / BK) * WTILE + lane * 8 : a.a_pieces; \
+        const uint16_t* at = (live) ? a.a_pieces + (size_t)((kc) / BK) * WTILE + a_lane : a.a_pieces; \
         _Pragma("unroll") for (int q = 0; q < 3; ++q) aq[u][q] = piece_at(at, q);           \
     }                                                                                        \
     if (BP) {                                                                                \
@@ -576,6 +599,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
       }
     }
     if (!EARLY_EPILOGUE) { NGDB_LOAD_EPILOGUE() }   // in flight during the reduction
+    constexpr int PQ = POOL ? std::max(1, BM / 2 * BN / (NW * 64)) : 1;      // pooled values of a thread (at most 16 members a tile)
+    float px[PQ][NGDB_MAX_CARD];
+    if (POOL && a.pool_k) {
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) {
+            const int e = tid + q * NW * 64, i = min(mt * mem + e / BN, n_mem - 1), col = min(n0 + e % BN, a.N - 1);
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) px[q][j] = a.pool_X[(size_t)(min(j, cls - 1) * n_mem + i) * a.ldc + col];
+        }
+    }
 #undef NGDB_LOAD_EPILOGUE
 #undef NGDB_ISSUE_VALUES
 #undef NGDB_ISSUE_PIECES
@@ -625,10 +658,38 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
         if (a.relu) v = fmaxf(v, 0.f);
         v = e_mask[q] > 0.f ? v : 0.f;
         v += e_add[q];
-        const bool inside = m0 + lr < a.M && n0 + lc < a.N;
-        if (inside) a.C[(size_t)e_orow[q] * a.ldc + n0 + lc] = v;
+        bool inside = m0 + lr < a.M && n0 + lc < a.N;
+        if (POOL) {
+            (void)pool_row_of(lr, &inside);
+            inside = inside && n0 + lc < a.N;
+            if (a.pool_k) smem[lr * (BN + 1) + lc] = v;      // (read by the thread that owns the element only, as below)
+        }
+        if (inside && (!POOL || a.C)) a.C[(size_t)e_orow[q] * a.ldc + n0 + lc] = v;
         // (a slot of the first partial tile is read by the thread that owns the element only)
         if (BM == 32 && BN == 32 && SPLIT && emit) smem[lr * (BN + 1) + lc] = inside ? v : 0.f;
+    }
+    if (POOL && a.pool_k) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PQ; ++q) {
+            const int e = tid + q * NW * 64, ii = e / BN, lc = e % BN, i = mt * mem + ii;
+            if (ii >= mem || i >= n_mem || n0 + lc >= a.N) continue;
+            float z[NGDB_MAX_CARD], mx = -INFINITY, den = 0.f, y = 0.f;
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                z[j] = smem[(min(j, cls - 1) * mem + ii) * (BN + 1) + lc];
+                if (j < cls) mx = fmaxf(mx, z[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) {
+                z[j] = j < cls ? expf(z[j] - mx) : 0.f;
+                den += z[j];
+            }
+            const float inv = 1.f / den;
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j) y += z[j] * inv * px[q][j];
+            a.pool_out[(size_t)(a.pool_row ? a.pool_row[i] : i) * a.ldc + n0 + lc] = y;
+        }
     }
     // The output once more as bf16 pieces in tile order (zero beyond the matrix), for the launch that
     // takes it as its A operand: block row m0/32, k-tiles n0/16 and n0/16 + 1; a lane of the first
@@ -940,15 +1001,17 @@ hipError_t dispatch_layout(GemmGroup& g, hipStream_t s) {
 }
 
 template <int NW, bool AP, int PF>
-hipError_t dispatch_pieces(GemmGroup& g, hipStream_t s) {
+hipError_t dispatch_pieces(GemmGroup& g, bool pool, hipStream_t s) {
     constexpr int BM = 32, BN = 32;
     int tiles = 0;
     for (int i = 0; i < g.count; ++i) {
         g.tile_start[i] = tiles;
-        tiles += (((g.p[i].M + BM - 1) / BM) * ((g.p[i].N + BN - 1) / BN) + 7) / 8 * 8;
+        const int k = g.p[i].pool_k ? g.p[i].pool_k : 1, rows = BM / k, n = g.p[i].M / k;
+        tiles += (((n + rows - 1) / rows) * ((g.p[i].N + BN - 1) / BN) + 7) / 8 * 8;
     }
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = tiles;
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP>), dim3(tiles), dim3(NW * 64), 0, s, g);
+    if (pool) hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP, true>), dim3(tiles), dim3(NW * 64), 0, s, g);
+    else hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP>), dim3(tiles), dim3(NW * 64), 0, s, g);
     return hipGetLastError();
 }
 
@@ -980,9 +1043,11 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
         max_k = std::max(max_k, a.K);
     }
     if (g.count == 0) return hipSuccess;
+    bool pool = false;
+    for (int i = 0; i < g.count; ++i) pool = pool || g.p[i].pool_k > 0;
     bool few_rows = true;
     for (int i = 0; i < g.count; ++i) few_rows = few_rows && takes_rows_kernel(g.p[i]);
-    if (few_rows) return dispatch_rows(g, s);
+    if (few_rows) return pool ? hipErrorNotSupported : dispatch_rows(g, s);
     const int arith = g.p[0].arith;
     const bool auto_split = arith == GEMM_AUTO && g.p[0].a_kcontig && max_k >= 128;
     // weight gradients (k = all rows of an operator type) of a mid-size step: the large tile with
@@ -993,6 +1058,9 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     bool b_ready = g.p[0].a_kcontig;
     for (int i = 0; i < g.count; ++i) b_ready = b_ready && g.p[i].b_pieces != nullptr && g.p[i].b_kt >= (g.p[i].K + 15) / 16;
     const long big_at = b_ready && auto_split ? 4096 : 2048;
+    if (pool && (!b_ready || !auto_split || blocks_small >= big_at)) return hipErrorNotSupported;
+    for (int i = 0; pool && i < g.count; ++i)
+        if (g.p[i].pool_k == 1 || g.p[i].pool_k > NGDB_MAX_CARD || (g.p[i].pool_k > 0 && g.p[i].M % g.p[i].pool_k)) return hipErrorInvalidValue;
     if ((blocks_small >= big_at || wgrad_big_tile) && arith != GEMM_SPLIT) {
         // (in the large tile every staged value feeds two MFMA blocks: there the split pays for
         // the weight gradients too)
@@ -1027,8 +1095,8 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
                 for (int i = 0; i < g.count; ++i)
                     if (*emitted) g.p[i].c_pieces = c_pieces[i];
             }
-            if (blocks_small * 2 > 512) return a_too ? dispatch_pieces<4, true, 2>(g, s) : dispatch_pieces<4, false, 1>(g, s);
-            return a_too ? dispatch_pieces<8, true, 2>(g, s) : dispatch_pieces<8, false, 1>(g, s);
+            if (blocks_small * 2 > 512) return a_too ? dispatch_pieces<4, true, 2>(g, pool, s) : dispatch_pieces<4, false, 1>(g, pool, s);
+            return a_too ? dispatch_pieces<8, true, 2>(g, pool, s) : dispatch_pieces<8, false, 1>(g, pool, s);
         }
         if (blocks_small * 2 > 512) return dispatch_layout<32, 32, 4, true>(g, s);
         return dispatch_layout<32, 32, 8, true>(g, s);

@@ -131,6 +131,29 @@ def test_operators_of_a_depth_in_one_launch(d, h, B):
     plan.free()
 
 
+# the pooling in the second layer's launch: widths that fill no tile, one member a tile and sixteen, rows of both layers
+# few and many, more classes than a launch takes
+@pytest.mark.parametrize("d,h,B,cards", [(132, 256, 40, (2, 3, 5, 8)), (400, 100, 150, (2, 3)), (200, 200, 12, (8,)), (260, 132, 90, (2, 3, 4, 5, 6, 7, 8)),
+                                         (256, 800, 400, (3,))])
+def test_pooling_in_the_second_layer(d, h, B, cards):
+    import torch
+    rng = np.random.default_rng(d + B)
+    N, R = 300, 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    trees = []
+    for i in range(2 * B):
+        both = ("i",) + tuple(proj() for _ in range(cards[i % len(cards)]))
+        trees.append([both, proj(both), ("i", proj(), ("n", proj(proj())))][(i // len(cards)) % 3 if 2 in cards else (i // len(cards)) % 2])
+    case = par.Case(N, R, d, h, B, 5, 6.0, seed=d + h, trees=trees, pos=[int(x) for x in rng.integers(0, N, len(trees))])
+    par.check_forward_backward(case)
+    cand = rng.integers(0, N, (case.B, 9)).astype(np.int32)
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    par.assert_close(eng.score(plan, torch.from_numpy(cand).cuda()).cpu().numpy(),
+                     orank.score_candidates(case.qb, cand, om.Model(case.params, case.gamma)), "scores d=%d h=%d" % (d, h))
+    plan.free()
+
+
 @pytest.mark.parametrize("d,h,B", [(8, 12, 20), (36, 100, 40), (64, 512, 40), (128, 256, 60), (132, 256, 30)])
 def test_box_operators_of_a_depth_in_one_launch(d, h, B):
     from . import parity_box as pb
