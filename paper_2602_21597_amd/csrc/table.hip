@@ -416,8 +416,11 @@ hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_b
 namespace {
 // The number of touched rows is only known on the device: a fixed grid walks them.  Four times as many workgroups as
 // fit at once, so that the launches of the other stream get their turn (6.42, 6.46 and 6.48 ms with 16, 4 and 2 times as
-// many for the step over 2.5 M entities, 15.9 and 16.4 ms with 8 and 2 with text features).
+// many for the step over 2.5 M entities, 15.9 and 16.4 ms with 8 and 2 with text features).  Rows with text features carry
+// twice the traffic: sixteen times as many as fit keep the last round of workgroups short (15.6 ms; 15.8 with 4096 or
+// 8192, 15.7 with 12 288, 15.6 with 32 768; plain rows 6.45 with 4096, 6.48 with 16 384, 6.51 with 32 768).
 constexpr int TABLE_BLOCKS = 256 * 16;
+constexpr int TABLE_BLOCKS_SEM = 4 * TABLE_BLOCKS;
 
 bool table_args_ok(const TableArgs& a) {
     const bool sem = a.g_bf16 != nullptr, box = a.off != nullptr;
@@ -442,7 +445,7 @@ bool table_args_ok(const TableArgs& a) {
 
 hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, hipStream_t s) {
     if (!table_args_ok(a)) return hipErrorInvalidValue;
-    const int blocks = few ? 256 : TABLE_BLOCKS;
+    const int blocks = few ? 256 : a.g_bf16 ? TABLE_BLOCKS_SEM : TABLE_BLOCKS;
 #define NGDB_WALK(NCH, SEM_, BOX_, SH_)                                                                                                   \
     do {                                                                                                                                  \
         if (a.streaming) hipLaunchKernelGGL((table_kernel<NCH, SEM_, BOX_, SH_, true, false>), dim3(blocks), dim3(256), 0, s, a, hp);    \
