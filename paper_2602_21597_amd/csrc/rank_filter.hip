@@ -284,7 +284,8 @@ struct NearArgs {
 // Pairs that qualify are few (a per cent in the first chunk, one in 10^5 later).  They leave a tile as
 // a list of its own, grouped by row, and one word per row that has any: start << 8 | number, at
 // [row][tile column] of an array that is zero elsewhere; an entry is the entity's place in the tile (7 bits)
-// below its sum less its error (from -2^20, clamped), i.e. its lower bound.  (Appending them to a list per query takes a
+// below its sum less its error (counted from -2^20; 0: below that, where the error of a row far outside the grid may
+// lie), i.e. its lower bound.  (Appending them to a list per query takes a
 // device-wide atomic each: 140 us for the 300 000 pairs of a first chunk whose sums take 50.)  A tile
 // with more than FOUND pairs marks its rows as crowded.
 constexpr int FOUND = 2048;
@@ -533,7 +534,8 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
             for (int i = 0; i < n && at + i < ROOM; ++i) {
                 const uint32_t p = pairs[(size_t)x * FOUND + from + i];
                 list[at + i] = (uint16_t)(x * 128 + (p & 127));
-                lower[at + i] = (float)((int32_t)(p >> 7) - SUM_BIAS - 4) * step + b_lo;
+                // (a sum that did not fit its bits bounds nothing)
+                lower[at + i] = p >> 7 ? (float)((int32_t)(p >> 7) - SUM_BIAS - 4) * step + b_lo : -INFINITY;
             }
         }
     }
@@ -566,7 +568,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         for (int r = r_lo; r < r_hi; ++r) both = fmaxf(both, g.base[g.ldb + r] - g.base[r]);
         auto upper = [&](int x) {
             const int32_t sl = g.slack[list[x]];
-            return sl == UNBOUNDED ? INFINITY : (lower[x] + both + (float)(2 * sl + 8) * step) * (1.f + g.rounding);
+            return sl == UNBOUNDED || lower[x] == -INFINITY ? INFINITY : (lower[x] + both + (float)(2 * sl + 8) * step) * (1.f + g.rounding);
         };
         for (int x = t; x < n; x += MERGE_T) hi_min = fminf(hi_min, upper(x));
 #pragma unroll

@@ -39,6 +39,18 @@ def _shifted(P):
     P["E"] += 3.0                 # large against its spread: the grid's own rounding counts
 
 
+def _far_group(shift):
+    """A group of rows that the grid's sample (every fourth row) does not hold, far outside the grid and with queries in its
+    midst: their sums less their errors lie far below zero, and only the group's own distances decide."""
+    def edit(P):
+        group = np.arange(1000, 2600)
+        P["E"][group[group % 4 != 0]] += shift
+        P["b2"] += shift
+        P["c2"] += shift
+    edit.__name__ = "_far_group(%g)" % shift
+    return edit
+
+
 # N just above the limit, one more tile, the ragged end of a second chunk; d of one word, of a part of a
 # stage and of several; branch rows that need tiles of 32, 64 and 128
 @pytest.mark.parametrize("N,d,h,B,edit,kw", [
@@ -61,6 +73,16 @@ def test_filtered_passes_match_the_oracle(N, d, h, B, edit, kw):
         par.check_topk(case, k, 6)
     if edit is not _one_cluster:  # (no rank is decided between thousands of equal rows)
         par.check_filtered_ranks(case, 5)
+
+
+# (operators of one depth, so that every query ends up among the group; few queries, so that no tile is crowded)
+@pytest.mark.parametrize("d,shift", [(400, 4.0)])
+def test_queries_and_entities_far_outside_the_grid(d, shift):
+    par.say("rank filter: group %g outside the grid, d=%d" % (shift, d))
+    case = _filtered(par.Case(9001, 12, d, 32, 10, 2, 8.0, mix={"1p": 0.5, "2i": 0.3, "2u": 0.2}, seed=300 + d, T=2 * 9001,
+                              params_edit=_far_group(shift)))
+    for k in (1, 10, 16):
+        par.check_topk(case, k, 10)
 
 
 def test_filtered_ranks_with_many_answers_of_one_query():
