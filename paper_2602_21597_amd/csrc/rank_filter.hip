@@ -318,7 +318,8 @@ __device__ __forceinline__ void near_tile(const NearArgs& g, int r0, int e0, Nea
         int32_t most = INT_MIN;
         if (r < g.n_rows) {
             const float t = (g.best[(size_t)g.row_q[r] * g.k + g.k - 1] * (1.f + g.rounding) - g.base[r]) * inv + 4.f;
-            most = t < 5e8f ? (int32_t)fmaxf(t, -1e9f) : INT_MAX / 2 - 1;    // (no bound yet, or not a number: everything qualifies)
+            // (no bound yet, or not a number: everything qualifies; rows of unbounded error always do)
+            most = t < 5e8f ? (int32_t)fmaxf(t, -(float)(UNBOUNDED - SUM_BIAS)) : INT_MAX / 2 - 1;
         }
         bool any = false;
 #pragma unroll

@@ -75,8 +75,9 @@ def test_filtered_passes_match_the_oracle(N, d, h, B, edit, kw):
         par.check_filtered_ranks(case, 5)
 
 
+# the error of the group's rows above 2^20 steps, above 10^8 (unbounded)
 # (operators of one depth, so that every query ends up among the group; few queries, so that no tile is crowded)
-@pytest.mark.parametrize("d,shift", [(400, 4.0)])
+@pytest.mark.parametrize("d,shift", [(400, 4.0), (1024, 700.0)])
 def test_queries_and_entities_far_outside_the_grid(d, shift):
     par.say("rank filter: group %g outside the grid, d=%d" % (shift, d))
     case = _filtered(par.Case(9001, 12, d, 32, 10, 2, 8.0, mix={"1p": 0.5, "2i": 0.3, "2u": 0.2}, seed=300 + d, T=2 * 9001,
