@@ -495,6 +495,9 @@ int64_t ngdb_debug_alloc_count(const ngdb_ctx_t* ctx);
 /* From how many coordinate differences (branch rows x entities x d) on the rankings of this context go through the
  * integer filter; negative: the library's own choice.  For tests of the filter at sizes below that.   */
 int ngdb_debug_rank_filter_from(ngdb_ctx_t* ctx, int64_t work);
+/* Chunks of entity rows that the last ranking of this context computed in fp32 for some query although it went through
+ * the filter (a list had no room); negative on failure.  Waits for the device.                          */
+int ngdb_debug_rank_overflows(ngdb_ctx_t* ctx);
 
 int64_t ngdb_step_count(const ngdb_ctx_t* ctx);
 const char* ngdb_strerror(int code);

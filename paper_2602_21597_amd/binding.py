@@ -119,6 +119,7 @@ def load_library(path=LIB_PATH):
         "ngdb_step_count": (i64, [vp]),
         "ngdb_debug_alloc_count": (i64, [vp]),
         "ngdb_debug_rank_filter_from": (C.c_int, [vp, i64]),
+        "ngdb_debug_rank_overflows": (C.c_int, [vp]),
         "ngdb_strerror": (C.c_char_p, [C.c_int]),
         "ngdb_last_error": (C.c_char_p, [vp]),
     }

@@ -92,6 +92,8 @@ struct ngdb_ctx_s {
     const uint16_t* wp[3][4]{};     // per type: Wa forward, Wb forward, Wb backward (dH = dY Wb), Wa backward (dZ = dH Wa)
     bool have_pieces = false;
     int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
+    const int32_t* rank_overflowed = nullptr;    // the last ranking's marks per chunk (null: no filter)
+    int rank_chunks = 0;
     // The hidden activations of one depth (forward) or their gradients (backward) once more as bf16
     // pieces in tile order: written by the first launch of a layer pair, read as A operand by the
     // second, then free again.  Only steps whose launches use the small tile get that far.
@@ -1275,15 +1277,19 @@ constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k)
 constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filter may leave undecided
 
 // Where a chunk of entity rows lies: in the table (or its bf16 copy), or, with text features, fused
-// into the context's chunk buffer by this call.
-struct ChunkRows { const float* rows; const uint16_t* rows16; };
-int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, hipStream_t s, ChunkRows* out) {
+// into the context's chunk buffer by this call.  sample: there, too, RANK_SAMPLE rows spread over the table (a launch
+// of its own for so few workgroups takes 100 us).
+struct ChunkRows { const float* rows; const uint16_t* rows16; const float* sample; };
+int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, bool sample, hipStream_t s, ChunkRows* out) {
     const int d = c->cfg.d;
-    *out = ChunkRows{c->prm.E.p + (size_t)e0 * d, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) + (size_t)e0 * d : nullptr};
+    *out = ChunkRows{c->prm.E.p + (size_t)e0 * d, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) + (size_t)e0 * d : nullptr, nullptr};
     if (c->cfg.d_sem == 0) return NGDB_OK;
-    SemFuseArgs fa{};
-    fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.id_base = e0;
-    fa.n_rows = cnt; fa.d = d; fa.ds = c->cfg.d_sem; fa.out = ptr<float>(c->rank_ef);
+    SemFuseArgs fa = fuse_args(c);
+    fa.id_base = e0; fa.n_rows = cnt; fa.out = ptr<float>(c->rank_ef);
+    if (sample) {
+        fa.n_seq = cnt; fa.n_rows += RANK_SAMPLE; fa.spread = c->cfg.n_entities / RANK_SAMPLE;
+        out->sample = fa.out + (size_t)cnt * d;
+    }
     HIPCHK(c, launch_sem_fuse(fa, s));
     out->rows = ptr<float>(c->rank_ef);
     return NGDB_OK;
@@ -1327,14 +1333,12 @@ bool rank_filtered(const ngdb_ctx_t* c, int n_rows, int coords, double from) {
     return (double)n_rows * c->cfg.n_entities * coords >= from;
 }
 
-// The grid of a filtered pass (rows spread over the table; with text features its first fused rows) and the
-// branch rows on it.
-int rank_filter_begin(ngdb_ctx_t* c, const ngdb_plan_t* pl, const RankFilter& f, const int32_t* roots, const ChunkRows& fused,
-                      int fused_rows, hipStream_t s) {
-    const int N = c->cfg.n_entities;
-    const bool sem = c->cfg.d_sem > 0;
-    HIPCHK(c, launch_rank_grid(f, sem ? fused.rows : c->prm.E.p, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr,
-                               sem ? 1 : N / RANK_SAMPLE, sem ? fused_rows : RANK_SAMPLE, s));
+// The grid of a filtered pass, from rows spread over the table (the first rows alone would leave a table that is ordered
+// by kind with most of its rows off the grid, every list overflowing and every chunk paid twice), and the branch rows on it.
+int rank_filter_begin(ngdb_ctx_t* c, const ngdb_plan_t* pl, const RankFilter& f, const int32_t* roots, const float* fused_sample,
+                      hipStream_t s) {
+    HIPCHK(c, launch_rank_grid(f, fused_sample ? fused_sample : c->prm.E.p, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr,
+                               fused_sample ? 1 : c->cfg.n_entities / RANK_SAMPLE, RANK_SAMPLE, s));
     HIPCHK(c, launch_rank_rows(f, ptr<float>(c->act), roots, pl->hp.n_roots, pl->d_root_off, pl->hp.n_queries, s));
     if (f.bits == 8) HIPCHK(c, launch_fill_zero_i32(reinterpret_cast<int32_t*>(f.found), f.ldy * (f.lde / 128), s));
     return NGDB_OK;
@@ -1348,9 +1352,10 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
     float* dist = nullptr;
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
-    if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, (size_t)chunk * d * sizeof(float), true);
+    if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, ((size_t)chunk + RANK_SAMPLE) * d * sizeof(float), true);
     RankFilter f{};
     if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 8, R, B, chunk, &f);
+    c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
     if (rc != NGDB_OK) return rc;
     dist = ptr<float>(c->rank_dist);
     Overflowed only{f.row_q, f.count, f.room, f.overflowed};
@@ -1363,11 +1368,11 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         const int want = !filtered ? chunk : (e0 == 0 ? sample : (int)std::min<int64_t>(chunk, 12ll * e0));
         const int cnt = std::min(want, N - e0);
         ChunkRows er;
-        if ((rc = rank_chunk_rows(c, e0, cnt, s, &er)) != NGDB_OK) return rc;
+        if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, s, &er)) != NGDB_OK) return rc;
         if (!filtered || e0 == 0) {
             HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16));
             HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, s));
-            if (filtered && (rc = rank_filter_begin(c, pl, f, roots, er, std::min(cnt, RANK_SAMPLE), s)) != NGDB_OK) return rc;
+            if (filtered && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
         } else {
             HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_near_tile(f, R, cnt, d_dist, topk, s));
@@ -1378,6 +1383,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         }
         e0 += cnt;
     }
+    c->rank_chunks = i_chunk;
     return NGDB_OK;
 }
 
@@ -1393,9 +1399,11 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
     if (rc == NGDB_OK) rc = ensure(c, c->rank_count, (size_t)n_ans * 8, true);
     if (rc == NGDB_OK && !d_ans_dist) rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, true);
-    if (rc == NGDB_OK && sem) rc = ensure(c, c->rank_ef, (size_t)std::max(chunk, std::min(n_ans, RANK_CHUNK)) * d * sizeof(float), true);
+    if (rc == NGDB_OK && sem) rc = ensure(c, c->rank_ef, ((size_t)std::max(chunk, std::min(n_ans, RANK_CHUNK)) + RANK_SAMPLE) * d * sizeof(float), true);
     RankFilter f{};
     if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 16, R, B, chunk, &f);
+    c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
+    c->rank_chunks = (N + chunk - 1) / chunk;
     if (rc != NGDB_OK) return rc;
     float* dist = ptr<float>(c->rank_dist);
     float* thr = d_ans_dist ? d_ans_dist : ptr<float>(c->rank_thr);
@@ -1423,9 +1431,9 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     for (int e0 = 0; e0 < N; e0 += chunk) {
         const int cnt = std::min(chunk, N - e0);
         ChunkRows er;
-        if ((rc = rank_chunk_rows(c, e0, cnt, s, &er)) != NGDB_OK) return rc;
+        if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, s, &er)) != NGDB_OK) return rc;
         if (filtered) {
-            if (e0 == 0 && (rc = rank_filter_begin(c, pl, f, roots, er, std::min(cnt, RANK_SAMPLE), s)) != NGDB_OK) return rc;
+            if (e0 == 0 && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
             HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_sum_tile(f, R, cnt, reinterpret_cast<uint32_t*>(dist), ld, s));
             HIPCHK(c, launch_count_sure(f, reinterpret_cast<const uint32_t*>(dist), ld, pl->d_root_off, d_ans_off, thr, B, cnt, in_chunk, s));
@@ -2065,6 +2073,18 @@ int ngdb_debug_rank_filter_from(ngdb_ctx_t* c, int64_t work) {
     if (!c) return NGDB_ERR_ARG;
     c->rank_filter_from = work;
     return NGDB_OK;
+}
+
+int ngdb_debug_rank_overflows(ngdb_ctx_t* c) {
+    if (!c) return -1;
+    if (!c->rank_overflowed) return 0;
+    int n = 0;
+    for (int i = 0; i < c->rank_chunks; ++i) {
+        int32_t mark = 0;
+        if (hipMemcpy(&mark, c->rank_overflowed + i, sizeof(mark), hipMemcpyDeviceToHost) != hipSuccess) return -1;
+        n += mark != 0;
+    }
+    return n;
 }
 
 int64_t ngdb_step_count(const ngdb_ctx_t* c) { return c ? c->step : -1; }

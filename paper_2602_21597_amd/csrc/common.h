@@ -526,13 +526,15 @@ hipError_t launch_inverse_index(const int32_t* src, const int32_t* seg_off, cons
 // out[i] = in_ref[i] if it is a slot, else -1 - inv[in_gslot[i] - n_slots] (anchor -> its touched-row position)
 hipError_t launch_translate_refs(const int32_t* in_ref, const int32_t* in_gslot, int n, int n_slots,
                                  const int32_t* inv, int32_t* out, hipStream_t s);
-// out[u, :] = E[id(u), :] + Wb * H[id(u), :] for u < n_rows; id(u) = ids[u] or id_base + u
+// out[u, :] = E[id(u), :] + Wb * H[id(u), :] for u < n_rows; id(u) = ids[u], or id_base + u for u < n_seq and
+// (u - n_seq) * spread from there on
 struct SemFuseArgs {
     const uint16_t* H;          // [N, ds] bf16
     const uint16_t* Wb;         // [d, ds] bf16
     const float* E;             // [N, d]
     const int32_t* ids;         // [n_rows] or null
     int64_t id_base;
+    int n_seq = INT32_MAX, spread = 0;
     const int32_t* n_rows_dev;  // device scalar (then n_rows is an upper bound) or null
     int n_rows;
     int d, ds;                  // ds a multiple of 64

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(SF_NW * 64) void sem_fuse_kernel(const SemFuseArgs 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     // entity of a row of the tile (rows past the end: the last row's); the row numbers are read
-    // unconditionally (from a valid address when the rows are consecutive entities)
+    // unconditionally (from a valid address when the rows are no list)
     const bool listed = a.ids != nullptr;
     const int32_t* id_src = listed ? a.ids : reinterpret_cast<const int32_t*>(a.E);
     constexpr int HQ = SF_HL / SF_NW, WQ = SF_WL / SF_NW;     // loads per wavefront: 4 + 4
@@ -124,7 +124,8 @@ __global__ __launch_bounds__(SF_NW * 64) void sem_fuse_kernel(const SemFuseArgs 
     for (int q = 0; q < HQ + 2; ++q) listed_id[q] = id_src[listed ? urow[q] : 0];
     int64_t ent[HQ + 2];
 #pragma unroll
-    for (int q = 0; q < HQ + 2; ++q) ent[q] = listed ? (int64_t)listed_id[q] : a.id_base + urow[q];
+    for (int q = 0; q < HQ + 2; ++q)
+        ent[q] = listed ? (int64_t)listed_id[q] : urow[q] < a.n_seq ? a.id_base + urow[q] : (int64_t)(urow[q] - a.n_seq) * a.spread;
     // sources of this lane's loads at k = 0 (row r of the area = 8 * load + lane / 8, stored column lane % 8)
     const uint16_t* src[SF_PER_WAVE];
 #pragma unroll

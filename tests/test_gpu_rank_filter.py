@@ -9,13 +9,14 @@ pytestmark = pytest.mark.gpu
 
 
 def _filtered(case):
-    """The case with engines that take the filter whatever the size of the pass."""
+    """The case with engines that take the filter whatever the size of the pass (the last one is case.last_engine)."""
     from paper_2602_21597_amd import binding
     plain = case.engine
 
     def engine(*args, **kw):
         eng = plain(*args, **kw)
         assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, 0) == 0
+        case.last_engine = eng
         return eng
 
     case.engine = engine
@@ -84,6 +85,23 @@ def test_queries_and_entities_far_outside_the_grid(d, shift):
                               params_edit=_far_group(shift)))
     for k in (1, 10, 16):
         par.check_topk(case, k, 10)
+
+
+def _ordered_by_kind(P):
+    P["Wp"] *= 0.05
+    P["E"][:2048] *= 0.2          # a narrow kind of entities first, the others five times as wide
+
+
+def test_grid_of_a_table_with_text_features_that_is_ordered_by_kind():
+    """The grid covers all kinds: no list overflows (from the first rows alone every later one errs by more than the
+    distances differ, and both passes go to fp32 entirely)."""
+    from paper_2602_21597_amd import binding
+    case = _filtered(par.Case(20000, 12, 64, 32, 24, 2, 8.0, seed=301, T=40000, d_sem=64, params_edit=_ordered_by_kind))
+    for k in (1, 10, 16):
+        par.check_topk(case, k, 6)
+        assert binding.lib().ngdb_debug_rank_overflows(case.last_engine.ctx) == 0
+    par.check_filtered_ranks(case, 5)
+    assert binding.lib().ngdb_debug_rank_overflows(case.last_engine.ctx) == 0
 
 
 def test_filtered_ranks_with_many_answers_of_one_query():
