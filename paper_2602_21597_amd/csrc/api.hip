@@ -1321,16 +1321,25 @@ int rank_filter_space(ngdb_ctx_t* c, int bits, int R, int B, int chunk, RankFilt
 }
 
 // The filter serves the plain distance (vector family).  It replaces two operations per coordinate by a quarter (top-k) or a
-// half of one, for launches and lists of its own: below `from` coordinate differences the fp32 pass is through first.  Top-k:
-// 226 us in fp32 and 252 with the filter at 15 000 entities x 585 rows x 256 coordinates (2.2e9), 442 and 415 at 200 000 x 114 x
-// 256 (5.8e9), 413 and 313 at 50 000 x 585 x 256 (7.5e9).
+// half of one, for launches and lists of its own and for rounding the entity rows: below `from` the fp32 pass is through first.
+// Top-k: the fp32 tiles take 32, 64 or 128 rows at a time, filled or not, and rounding the table costs about as much as 48
+// rows.  (These rows - 48) x entities x coordinates in 1e9, then us in fp32 and with the filter: 15 000 entities x 584 rows
+// x 256 coordinates (2.3) 228 and 220, 60 000 x 228 x 256 (3.2) 253 and 269, 15 000 x 584 x 400 (3.6) 322 and 284,
+// 30 000 x 292 x 400 (4.0) 305 and 315, 100 000 x 114 x 400 (3.2) 364 and 428, 200 000 x 114 x 256 (4.1) 434 and 415,
+// 300 000 x 114 x 400 (9.6) 801 and 767; 500 000 x 56 x 400 (3.2) 817 and 909, 500 000 x 72 x 400 (16) 1201 and 1026;
+// with 8 to 18 rows (below 0) the filter was 6 to 25 % slower from 500 000 to 2.5 million entities.
 // Answers: the filter's counting takes as long per pair as 64 coordinates save, and each chunk has launches of its own:
 // 502 us in fp32 and 602 with the filter at 200 000 x 585 x 64, 250 and 230 at 15 000 x 585 x 256, 439 and 586 at 200 000 x 114 x
 // 256 (four chunks), 1357 and 1180 at 200 000 x 585 x 256.
-bool rank_filtered(const ngdb_ctx_t* c, int n_rows, int coords, double from) {
+constexpr double NEAR_FROM = 3.3e9;
+double near_work(const ngdb_ctx_t* c, int n_rows) {
+    const int tile_rows = n_rows <= 32 ? 32 : (n_rows <= 64 ? 64 : (n_rows + 127) / 128 * 128);
+    return (double)(tile_rows - 48) * c->cfg.n_entities * c->cfg.d;
+}
+bool rank_filtered(const ngdb_ctx_t* c, int n_rows, double work, double from) {
     if (c->cfg.family != NGDB_FAMILY_VEC || c->cfg.n_entities <= 2 * RANK_SAMPLE) return false;
     if (c->rank_filter_from >= 0) return (double)n_rows * c->cfg.n_entities * c->cfg.d >= (double)c->rank_filter_from;
-    return (double)n_rows * c->cfg.n_entities * coords >= from;
+    return work >= from;
 }
 
 // The grid of a filtered pass, from rows spread over the table (the first rows alone would leave a table that is ordered
@@ -1348,7 +1357,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
     const float* act = ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
-    const bool filtered = rank_filtered(c, R, d, 3.5e9);
+    const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
     const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
     float* dist = nullptr;
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
@@ -1395,7 +1404,7 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     const bool sem = c->cfg.d_sem > 0;
     // (with very many answers per query most entities are undecided for one of them)
     const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
-    const bool filtered = rank_filtered(c, R, d - 64, 1.4e9 + 3.7e9 * ((N - 1) / chunk)) && n_ans <= 64ll * B;
+    const bool filtered = rank_filtered(c, R, (double)R * N * (d - 64), 1.4e9 + 3.7e9 * ((N - 1) / chunk)) && n_ans <= 64ll * B;
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
     if (rc == NGDB_OK) rc = ensure(c, c->rank_count, (size_t)n_ans * 8, true);
     if (rc == NGDB_OK && !d_ans_dist) rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, true);
