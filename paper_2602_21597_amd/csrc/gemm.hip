@@ -720,6 +720,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
 // and LDS as pieces, with one block ahead, a block took 4500 cycles: 51 us for the six contractions of 512
 // queries at d=400, h=800 (1356, 730 and 182 rows) and 5 us for the bias gradients, against 29 us here; 88 and
 // 53 us against 48 for 1024.)  The column sums of A that the bias gradients are fall out of the values read.
+// Six bf16 products stand for an fp32 one, whatever the size of the step.  The five small ones have accumulators of their own,
+// so that the large sums are rounded once a block: against fp64 the error is 0.4 to 0.9 of that of fp32 matrix instructions on
+// eight partial sums (16 to 5000 rows; gradients with rows of one size or many, hidden rows of one sign or both).  All six
+// in one accumulator were up to 1.9 times as far off as those, from 130 rows on.  185 -> 249 registers, still two
+// wavefronts per SIMD and the same time.
 constexpr int WG_T = 64, WG_LD = WG_T + 1;
 struct WgradGroup {
     int count;
@@ -763,13 +768,13 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradGroup g) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) lds_load16(bcol + (size_t)min(k0 + q * 4 + row_in, a.K - 1) * a.ldb, to + BUF + q * 1024);
     };
-    floatx16 acc[2][2];
+    floatx16 acc[2][2], low[2][2];      // products of the first pieces; the other five of the six
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
     float csum[2] = {0.f, 0.f};
     float v[4][8];                      // values of a block: A columns 0-31, 32-63, B columns 0-31, 32-63
     bf16x8 pc[2][4][3];                 // pieces of the block being multiplied and of the next
@@ -819,8 +824,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradGroup g) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[2 + j][PB[t]], of[i][PA[t]], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < 2; ++j) {
+                    floatx16& to = t < 5 ? low[i][j] : acc[i][j];
+                    to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(of[2 + j][PB[t]], of[i][PA[t]], to, 0, 0, 0);
+                }
     };
     if (rounds > 0) {
         issue(0);
@@ -855,7 +862,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradGroup g) {
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                part[(i * 32 + (lane & 31)) * WG_LD + j * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)] = acc[i][j][r];
+                part[(i * 32 + (lane & 31)) * WG_LD + j * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)] = acc[i][j][r] + low[i][j][r];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
         const float both = csum[b] + __shfl_xor(csum[b], 32, 64);
