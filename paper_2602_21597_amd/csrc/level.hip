@@ -26,6 +26,11 @@ __host__ __device__ constexpr int lv_pitch(int n) { return (n + 15) / 16 * 16 + 
 // One layer, out = A * W^T (BT: A * W) for the 16 rows of A in LDS; wavefront w computes the column blocks w, w + 16, ...  start()
 // requests the first weights (long before A is there), run() hands a lane's four values (rows 4 (lane / 16) .. +3 of
 // column n) to done.  Within a k-step lane group g holds k = 4g .. 4g+3 of both operands, one of them per matrix instruction.
+// These add product after product to an fp32 sum, so k goes through sums of at most 16 products, four at a time, which are
+// then added: the error against fp64 stays at that of the separate launches, which split k over eight wavefronts.  (Two sums
+// over all of k: outputs at d = 128, h = 256 off by 2.2e-7 instead of 1.3e-7, at 256, 128 2.4e-7 instead of 1.3e-7; a step
+// 167.9 -> 174.5 us at 100, 200, 186.5 -> 193.4 at 128, 256, 134.4 -> 136.7 at 64, 128.  Eight sums folded half as often
+// spill, and k split over wavefronts waits longer at the barrier than it saves.)
 template <bool BT>
 struct Layer {
     const float* W;
@@ -62,24 +67,29 @@ struct Layer {
         int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), s = 0;
         const int blocks = (N + 15) / 16;
         const int total = b < blocks ? ((blocks - b + LV_WAVES - 1) / LV_WAVES) * steps : 0;
-        floatx4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+        floatx4 sum[4] = {zero, zero, zero, zero}, all = zero;
         const float* arow = As + col * ap + kg;
         for (int t0 = 0; t0 < total; t0 += LV_AHEAD) {
 #pragma unroll
             for (int q = 0; q < LV_AHEAD; ++q) {
-                if (t0 + q < total) {
-                    const float4 x = *reinterpret_cast<const float4*>(arow + s * 16);
-                    a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w[q].x, a0, 0, 0, 0);
-                    a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w[q].y, a1, 0, 0, 0);
-                    a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, w[q].z, a0, 0, 0, 0);
-                    a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, w[q].w, a1, 0, 0, 0);
-                    if (t0 + q + LV_AHEAD < total) w[q] = fetch();
-                    if (++s == steps) {
-                        done(b * 16 + col, a0 + a1);
-                        a0 = a1 = floatx4{0.f, 0.f, 0.f, 0.f};
-                        s = 0;
-                        b += LV_WAVES;
-                    }
+                if (t0 + q >= total) return;
+                const float4 x = *reinterpret_cast<const float4*>(arow + s * 16);
+                sum[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w[q].x, sum[0], 0, 0, 0);
+                sum[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w[q].y, sum[1], 0, 0, 0);
+                sum[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, w[q].z, sum[2], 0, 0, 0);
+                sum[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, w[q].w, sum[3], 0, 0, 0);
+                if (t0 + q + LV_AHEAD < total) w[q] = fetch();
+                const bool last = ++s == steps;      // uniform
+                if (q % 4 == 3 || last) {
+                    all += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+                    sum[0] = sum[1] = sum[2] = sum[3] = zero;
+                }
+                if (last) {
+                    done(b * 16 + col, all);
+                    all = zero;
+                    s = 0;
+                    b += LV_WAVES;
                 }
             }
         }

@@ -153,6 +153,26 @@ def test_operators_of_a_depth_in_one_launch(d, h, B):
     plan.free()
 
 
+# Rounding errors of a layer over k: chains of 16 products, four of them as a tree, these sums one after the other.  In units of
+# the variance of one relative rounding (at most 2^-48 / 3), for products of random sign: 8.5 + 2 + (k / 64 + 1) / 2.  (Two
+# chains over all of k have k / 4.)  The errors of both layers add up in quadrature.
+@pytest.mark.parametrize("d,h", [(64, 512), (128, 256), (256, 128)])
+def test_rounding_of_operators_of_a_depth_in_one_launch(d, h):
+    def live(P):                     # rows keep their size through a layer
+        for a, b in (("W1", "W2"), ("V1", "V2"), ("U1", "U2")):
+            P[a] *= np.float32(np.sqrt(6.0 / d) / 0.1)
+            P[b] *= np.float32(np.sqrt(3.0 / h) / 0.1)
+    case = par.Case(2000, 20, d, h, 100, 4, 12.0, mix={"1p": 1.0}, seed=d + h, params_edit=live)
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    eng.forward_backward(plan, case.neg_dev())
+    slots, act, M = plan.export()["root_slot"], eng.grads()["act"], case.model()
+    want = np.stack([orank.query_embeddings(case.qb, q, M)[0] for q in range(case.B)])
+    err = np.linalg.norm(act[slots] - want) / np.linalg.norm(want)
+    assert err <= np.sqrt(sum(10.5 + (k / 64 + 1) / 2 for k in (d, h)) / 3) * 2.0 ** -24, err
+    plan.free()
+
+
 # the pooling in the second layer's launch: widths that fill no tile, one member a tile and sixteen, rows of both layers
 # few and many, more classes than a launch takes
 @pytest.mark.parametrize("d,h,B,cards", [(132, 256, 40, (2, 3, 5, 8)), (400, 100, 150, (2, 3)), (200, 200, 12, (8,)), (260, 132, 90, (2, 3, 4, 5, 6, 7, 8)),
