@@ -291,8 +291,8 @@ double level_flop(const ngdb_ctx_t* c, const std::vector<Segment>& segs) {
 // The operators of one depth as problems of one launch (level.hip), where the MLPs are small and the depth does not have
 // very many rows. 
 bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, LevelArgs* a) {
-    if (!level_fits(c->cfg.d, c->cfg.h)) return false;
     const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    if (!level_fits(c->cfg.d, c->cfg.h, true)) return false;
     const HostPlan& hp = pl->hp;
     *a = LevelArgs{};
     a->d = c->cfg.d; a->h = c->cfg.h;
@@ -310,6 +310,7 @@ bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vecto
         for (int g = sg.g_lo; box && g < sg.g_hi; ++g)      // the offsets of the same inputs through the second MLP
             if (!level_add(*a, T_NEG, LEVEL_GATE, hp.g_n[g], hp.g_nin[g], sg.ref_off + hp.g_mlp_base[g] - sg.mlp_base, -1, hp.g_mlp_base[g], hp.g_out_base[g])) return false;
     }
+    if (!level_fits(c->cfg.d, c->cfg.h, box) && a->tile_start[a->count] > LEVEL_FEW) return false;
     if (box) {
         a->act = ptr<float>(c->act); a->off = ptr<float>(c->off); a->dact = ptr<float>(c->dact); a->doff = ptr<float>(c->doff);
         a->Att = ptr<float>(c->Att); a->Gate = ptr<float>(c->Gate); a->dAtt = ptr<float>(c->dAtt); a->dGate = ptr<float>(c->dGate);
@@ -1039,7 +1040,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     // the caller's stream: an index of one launch, or small MLPs with few rows to update (64 queries x 32 negatives 119
     // against 133 us at d = 64 and 211 against 220 at d = 400; 256 x 64 at d = 64 145 against 175, 1024 x 64 187 against 202, but
     // 1024 x 256 237 against 222; at d = 128, h = 256 256 x 64 196 against 184, as boxes, with fewer depths, 141 against 167).
-    const bool host_bound = !sem && (n_contrib <= 4096 || (level_fits(d, c->cfg.h) && (box || d * c->cfg.h <= 16384) &&
+    const bool host_bound = !sem && (n_contrib <= 4096 || (level_fits(d, c->cfg.h, box) && (box || d * c->cfg.h <= 16384) &&
                                                           n_contrib <= 70000 && max_rows * d <= 2000000));
     const bool aside = c->n_side > 0 && !host_bound;
     hipStream_t s_idx = aside ? c->side[0] : stream;
@@ -1086,7 +1087,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     // rows read and written at 2.7 TB/s, but 2 us a row, and 0.2 us a contribution; a chain of launches and its contractions.
     const double mlp_rows = (double)hp.n_proj + (box ? 2.0 : 1.0) * hp.n_int_rows + hp.n_neg;
     const double pass_us = std::max(24.0 * max_rows * d / 2.7e6, 2.0 * max_rows / 1024.0) + 0.2 * n_contrib / 1024.0;
-    const double chain_us = level_fits(d, c->cfg.h) ? 25.0 + 18.0 * hp.n_levels : 100.0 + 12.0 * c->cfg.h * d * mlp_rows / 1e8;
+    const double chain_us = level_fits(d, c->cfg.h, box) ? 25.0 + 18.0 * hp.n_levels : 100.0 + 12.0 * c->cfg.h * d * mlp_rows / 1e8;
     const bool short_pass = aside ? pass_us <= chain_us : max_rows <= 65536;
     const int64_t t = c->step + 1;
     const AdamHyper ah{c->cfg.lr, c->cfg.beta1, c->cfg.beta2, c->cfg.eps,

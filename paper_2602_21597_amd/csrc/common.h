@@ -297,11 +297,15 @@ hipError_t launch_loss_reduce(const float* terms, int n, float scale, float* los
 // The operators of one depth in one launch.  A problem is a projection or negation group (k = 1, pool = 0) or one class of
 // intersections (k inputs each, pool = 1): MLP rows row0 + j * n + i of type's buffers, references ref_off + j * n + i
 // (and relations rel_off + ..., -1: none), outputs out0 + i.
-// Taken up to LEVEL_WEIGHTS weights a layer (at 128 x 256 the separate launches take as long on the device and two thirds more
-// host time; beyond, the weights read by every row block cost more than the launches), and up to LEVEL_WORK = row blocks
-// x weights of a depth (512 blocks there: from 4096 queries on the separate launches are as fast, 386 against 395 us).
-constexpr int LEVEL_MAX = 10, LEVEL_WEIGHTS = 32768;
-constexpr long LEVEL_WORK = 512l * LEVEL_WEIGHTS;
+// Taken up to LEVEL_WEIGHTS weights a layer (a step of 64, 256 and 1024 queries at 100 x 200, separate launches against this one,
+// planning included: 157 and 147, 172 and 169, 211 and 212 us; at 128 x 256 152 and 163, 168 and 188, 210 and 230; beyond, the
+// weights read by every row block cost more than the launches).  Up to LEVEL_WEIGHTS_BOX by boxes, whose separate launches
+// are more (at 128 x 256 122 and 111, 129 and 131, 157 and 158), and by depths of at most LEVEL_FEW row blocks (at 128 x 256,
+// separate, all depths here and these depths here: 16 queries 159, 149 and 149, 32 queries 162, 155 and 149, 64 queries 152,
+// 163 and 139, 512 queries 182, 200 and 170).  Never above LEVEL_WORK = row blocks x weights of a depth (from 4096 queries
+// on the separate launches are as fast, 386 against 395 us).
+constexpr int LEVEL_MAX = 10, LEVEL_WEIGHTS = 20480, LEVEL_WEIGHTS_BOX = 32768, LEVEL_FEW = 4;
+constexpr long LEVEL_WORK = 512l * LEVEL_WEIGHTS_BOX;
 constexpr int LEVEL_GATE = 2, LEVEL_PROJECTION = 3;      // box family (off set): pooling of offsets, projection without MLP
 struct LevelProblem { int type, pool, n, k, ref_off, rel_off, row0, out0; };
 struct LevelMlp { const float *Wa, *ba, *Wb, *bb; float *Z, *H, *dH; };
@@ -317,7 +321,7 @@ struct LevelArgs {
     const float* Ro;
     float *off, *Gate, *doff, *dGate;
 };
-bool level_fits(int d, int h);
+bool level_fits(int d, int h, bool box);
 // adds a problem; false if the launch has no room for it
 bool level_add(LevelArgs& a, int type, int pool, int n, int k, int ref_off, int rel_off, int row0, int out0);
 hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s);

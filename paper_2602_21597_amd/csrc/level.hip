@@ -8,8 +8,10 @@
 // six steps ahead 112 against 101 us for a forward pass at d = h = 256).  What it costs over the
 // separate launches is that every 16 rows read all weights again and that a row block's matrix work stays on one
 // compute unit.  Measured, device time of a forward pass with scoring of 256 queries (two launches a depth less, 41 -> 25 us of
-// host time) and of a training step, separate -> here: d = 32, h = 64: 60 -> 36 and 191 -> 130 us; 64, 128: 66 -> 42, 195 -> 134;
-// 100, 200: 71 -> 54, 193 -> 151; 128, 256: 70 -> 68, 204 -> 171; 200, 200: 74 -> 75, 199 -> 198; 256, 256: 75 -> 102, 192 -> 243.
+// host time) and of a training step with 32 negatives, separate -> here: d = 64, h = 128: 59 -> 45 and 149 -> 128 us;
+// 128, 128: 62 -> 56, 157 -> 148; 100, 200: 65 -> 59, 163 -> 165; 32, 512: 66 -> 67, 165 -> 182; 128, 256: 62 -> 72, 160 -> 184.
+// Boxes (more launches apart): 128, 128: 46 -> 39, 112 -> 106; 128, 256: 48 -> 46, 116 -> 123; 64, 512: 49 -> 49, 117 -> 132,
+// and with 16 queries 56 -> 47 and 100 -> 104.
 #include <algorithm>
 #include "common.h"
 
@@ -355,11 +357,11 @@ bool level_add(LevelArgs& a, int type, int pool, int n, int k, int ref_off, int 
     return (long)a.tile_start[++a.count] * a.d * a.h <= LEVEL_WORK;
 }
 
-bool level_fits(int d, int h) { return d <= 256 && h <= 512 && d * h <= LEVEL_WEIGHTS; }
+bool level_fits(int d, int h, bool box) { return d <= 256 && h <= 512 && d * h <= (box ? LEVEL_WEIGHTS_BOX : LEVEL_WEIGHTS); }
 
 hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
     if (a.count == 0) return hipSuccess;
-    if (!level_fits(a.d, a.h) || (a.d & 3) || (a.h & 3)) return hipErrorInvalidValue;
+    if (!level_fits(a.d, a.h, true) || (a.d & 3) || (a.h & 3)) return hipErrorInvalidValue;
     const dim3 grid(a.tile_start[a.count]);
     const size_t lds = lv_lds(a.d, a.h);
     if (a.off && backward) hipLaunchKernelGGL((level_kernel<true, true>), grid, dim3(LV_T), lds, s, a);

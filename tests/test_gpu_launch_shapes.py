@@ -156,7 +156,7 @@ def test_operators_of_a_depth_in_one_launch(d, h, B):
 # Rounding errors of a layer over k: chains of 16 products, four of them as a tree, these sums one after the other.  In units of
 # the variance of one relative rounding (at most 2^-48 / 3), for products of random sign: 8.5 + 2 + (k / 64 + 1) / 2.  (Two
 # chains over all of k have k / 4.)  The errors of both layers add up in quadrature.
-@pytest.mark.parametrize("d,h", [(64, 512), (128, 256), (256, 128)])
+@pytest.mark.parametrize("d,h", [(40, 512), (128, 160), (256, 80)])
 def test_rounding_of_operators_of_a_depth_in_one_launch(d, h):
     def live(P):                     # rows keep their size through a layer
         for a, b in (("W1", "W2"), ("V1", "V2"), ("U1", "U2")):
