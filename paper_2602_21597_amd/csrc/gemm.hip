@@ -1,5 +1,5 @@
-// fp32 MFMA GEMM for the grouped operator MLPs (forward, data-gradient and
-// weight-gradient contractions of Sec. 4.1's batched kernels).
+// Contractions of the grouped operator MLPs (Sec. 4.1's batched kernels): gemm_kernel forward and
+// for data gradients, rows_kernel forward over few rows, wgrad_kernel for weight gradients.
 //
 // The groups of one batch are small next to the chip (a few hundred to a few
 // thousand rows against 256 compute units), so a contraction is latency bound,
@@ -1000,8 +1000,8 @@ hipError_t dispatch_layout(GemmGroup& g, hipStream_t s) {
         hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, SPLIT>), grid, block, 0, s, g);
     else if (a.a_kcontig && !a.b_kcontig)
         hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, false, SPLIT>), grid, block, 0, s, g);
-    else if (!a.a_kcontig && !a.b_kcontig)
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, false, false, SPLIT>), grid, block, 0, s, g);
+    else if (!a.a_kcontig && !a.b_kcontig && (!SPLIT || BM == 32))     // (the large tile: fp32 only)
+        hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, false, false, SPLIT && BM == 32>), grid, block, 0, s, g);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -1057,9 +1057,6 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     if (few_rows) return pool ? hipErrorNotSupported : dispatch_rows(g, s);
     const int arith = g.p[0].arith;
     const bool auto_split = arith == GEMM_AUTO && g.p[0].a_kcontig && max_k >= 128;
-    // weight gradients (k = all rows of an operator type) of a mid-size step: the large tile with
-    // the split route beats the small tile with fp32 MFMAs although it leaves compute units idle
-    const bool wgrad_big_tile = arith == GEMM_AUTO && !g.p[0].a_kcontig && max_k >= 512 && blocks_small >= 512;
     // (with the B operands ready-made the small tile holds its own up to twice the size: 0.516 + 0.388
     // against 0.537 + 0.416 ms for the forward and backward launches of 4096 queries at h = 800)
     bool b_ready = g.p[0].a_kcontig;
@@ -1068,20 +1065,17 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     if (pool && (!b_ready || !auto_split || blocks_small >= big_at)) return hipErrorNotSupported;
     for (int i = 0; pool && i < g.count; ++i)
         if (g.p[i].pool_k == 1 || g.p[i].pool_k > NGDB_MAX_CARD || (g.p[i].pool_k > 0 && g.p[i].M % g.p[i].pool_k)) return hipErrorInvalidValue;
-    if ((blocks_small >= big_at || wgrad_big_tile) && arith != GEMM_SPLIT) {
-        // (in the large tile every staged value feeds two MFMA blocks: there the split pays for
-        // the weight gradients too)
-        const bool big_split = arith == GEMM_AUTO && max_k >= 128;
-        if (route && big_split) *route = GEMM_SPLIT;
-        return big_split ? dispatch_layout<64, 64, 4, true>(g, s) : dispatch_layout<64, 64, 4>(g, s);
+    if (blocks_small >= big_at && arith != GEMM_SPLIT) {
+        if (route && auto_split) *route = GEMM_SPLIT;
+        return auto_split ? dispatch_layout<64, 64, 4, true>(g, s) : dispatch_layout<64, 64, 4>(g, s);
     }
     // below that the launches of a step do not fill the chip: the smallest tile the MFMA block
     // allows spreads a launch over the most compute units (a tile's MFMA work runs on one)
     // (more than two such tiles per compute unit: 4 wavefronts per tile keep them all resident)
     // fp32 operands as three bf16 pieces each (six bf16 MFMAs per k-tile instead of eight fp32
     // ones that take twice as long each): launches whose A operand is k-contiguous, i.e. the
-    // forward and data-gradient contractions.  With k as the slow index of both operands (weight
-    // gradients) splitting and transposing the pieces costs more than the matrix unit saves.
+    // forward and data-gradient contractions.  (With k as the slow index of both operands, which a step leaves to
+    // wgrad_kernel, these kernels serve ngdb_debug_gemm: products of fp32 matrix instructions to measure that one against.)
     // (with a k extent below 128 the matrix unit is idle either way and the splitting only adds work)
     if (arith == GEMM_SPLIT || auto_split) {
         if (route) *route = GEMM_SPLIT;
