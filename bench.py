@@ -590,7 +590,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": res["workload"],
                    "contractions": "fp32 results; operands split exactly into three bf16 pieces, six partial products on "
-                                   "the bf16 MFMA with fp32 accumulation (fp32 MFMA for small weight-gradient tiles)",
+                                   "the bf16 MFMA with fp32 accumulation (fp32 MFMA for small MLPs and widths below 128)",
                    "streams": res["streams"],
                    "schedule": args.schedule if args.schedule == "level" else "max_fill, B_max=%s" % (args.bmax or "inf"),
                    "steps_per_batch": res["steps_per_batch"], "peak_live_outputs": res["peak_live_outputs"],

@@ -285,9 +285,12 @@ void ngdb_destroy(ngdb_ctx_t* ctx);
 int ngdb_bind_params(ngdb_ctx_t* ctx, const ngdb_params* params);
 
 /* Queries -> operator-level frontiers and index arrays (Alg. 1, graph construction and
- * the pools of Sec. 4.1, resolved ahead of time level by level).  Host work
- * plus one upload; deterministic.  Ids are range-checked here (NGDB_ERR_RANGE).
- * The plan may be used for any number of steps on this context.                  */
+ * the pools of Sec. 4.1, resolved ahead of time level by level).  Host work;
+ * deterministic.  Ids are range-checked here (NGDB_ERR_RANGE).  Arrays above 256 KB
+ * are copied to the device here; smaller ones by the first call that uses the plan,
+ * on that call's stream.  The plan may be used for any number of steps on this
+ * context (calls on different streams are the caller's to order: they share the
+ * context's workspace).                                                          */
 int ngdb_plan(ngdb_ctx_t* ctx, const ngdb_query_batch* batch, ngdb_plan_t** out);
 /* The host half of ngdb_plan alone (no context, no device, nothing uploaded):
  * the result can be exported and freed, not executed.                            */

@@ -369,9 +369,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (BOX && 
                                   (int)((gridDim.x * blockDim.x) >> 6));
 }
 
-// (its records may come unresolved: one launch less where everything waits for the backward pass anyway)
 // The end of a step: the first workgroups walk up to two small plain tables of the same width (the relation tables), the
-// next ones the rows of the main table that are left (in a small step without a second stream: all of them), the last
+// next ones the rows of the main table that are left (in a small step without a second stream: all of them, their records
+// unresolved, a launch less where everything waits for the backward pass anyway), the last
 // the dense tensors.  As launches of their own each of these would add its latency to the end of the step.
 template <int NCH, bool SEM, bool BOX, bool SH, bool UPD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (BOX && NCH == 2) ? 3 : 8)))
@@ -418,7 +418,9 @@ namespace {
 // fit at once, so that the launches of the other stream get their turn (6.42, 6.46 and 6.48 ms with 16, 4 and 2 times as
 // many for the step over 2.5 M entities, 15.9 and 16.4 ms with 8 and 2 with text features).  Rows with text features carry
 // twice the traffic: sixteen times as many as fit keep the last round of workgroups short (15.6 ms; 15.8 with 4096 or
-// 8192, 15.7 with 12 288, 15.6 with 32 768; plain rows 6.45 with 4096, 6.48 with 16 384, 6.51 with 32 768).
+// 8192, 15.7 with 12 288, 15.6 with 32 768; plain rows 6.45 with 4096, 6.48 with 16 384, 6.51 with 32 768).  Smaller tables
+// with text features, 4 and 16 times: one million entities, 4096 x 1024 at d = 512 8.08 and 7.85 ms, 2048 x 1024 at 200 2.74 and
+// 2.72, 2048 x 512 at 400 3.93 and 3.89; from 500 000 entities down no difference beyond 1 %.
 constexpr int TABLE_BLOCKS = 256 * 16;
 constexpr int TABLE_BLOCKS_SEM = 4 * TABLE_BLOCKS;
 
