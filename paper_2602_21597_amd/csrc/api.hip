@@ -383,6 +383,24 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     return NGDB_OK;
 }
 
+// The end of a pass, also of one that is refused or fails half way: what it enqueued still reads the plan, whose buffer
+// goes to another plan once last_use has passed, and, on the library stream, the caller's tensors, which the caller's
+// stream must wait for.
+struct PassEnd {
+    ngdb_ctx_t* c;
+    const ngdb_plan_t* pl;
+    hipStream_t s;
+    bool forked = false, closed = false;      // forked: the library stream has work that s does not wait for yet
+    hipError_t close() {
+        closed = true;
+        return hipEventRecord(pl->blob.last_use, s);
+    }
+    ~PassEnd() {
+        if (forked && hipEventRecord(c->ev_join, c->side[0]) == hipSuccess) (void)hipStreamWaitEvent(s, c->ev_join, 0);
+        if (!closed) (void)close();
+    }
+};
+
 int size_workspace(ngdb_ctx_t* c, const ngdb_plan_t* pl, int K, bool want_table_grads) {
     const HostPlan& hp = pl->hp;
     const size_t d = c->cfg.d, h = c->cfg.h, f = sizeof(float);
@@ -1027,8 +1045,9 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         return fail(c, NGDB_ERR_ARG, "batch beyond the maxima declared at ngdb_create (b_max_queries, k_max)");
     c->have_grads = false;
     int rc = size_workspace(c, pl, K, !apply);
-    if (rc == NGDB_OK) rc = begin_pass(c, pl, stream);
     if (rc != NGDB_OK) return rc;
+    PassEnd end{c, pl, stream};
+    if ((rc = begin_pass(c, pl, stream)) != NGDB_OK) return rc;
 
     // 1. entity gradient index (depends only on the plan and the negatives).  With a library stream the index build, and with
     // text features the fusion of all rows that are scored, run beside the forward pass, which needs the anchors' rows only.
@@ -1048,6 +1067,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     if (aside) {
         HIPCHK(c, hipEventRecord(c->ev_fork, stream));
         HIPCHK(c, hipStreamWaitEvent(s_idx, c->ev_fork, 0));
+        end.forked = true;
     }
     EntRows er{c->prm.E.p, pl->d_in_ref, pl->d_pos, d_neg}, scored = er;
     if ((rc = build_index(c, pl, d_neg, (int64_t)B * K, s_idx, &e_src)) != NGDB_OK) return rc;
@@ -1178,7 +1198,10 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         HIPCHK(c, launch_dense_adam(job, ah, stream));
         job.count = 0;
     }
-    if (aside) HIPCHK(c, hipStreamWaitEvent(stream, c->ev_join, 0));
+    if (aside) {
+        HIPCHK(c, hipStreamWaitEvent(stream, c->ev_join, 0));
+        end.forked = false;
+    }
     {
         Timed tm(c, short_pass ? NGDB_TK_ADAM : NGDB_TK_TABLE_R, stream);
         const int64_t left = aside ? std::min<int64_t>(hp.n_anchor, max_rows) : (short_pass ? max_rows : 0);
@@ -1201,7 +1224,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         }
     }
 
-    HIPCHK(c, hipEventRecord(pl->blob.last_use, stream));
+    HIPCHK(c, end.close());
     if (apply) c->step = t;
     // describe the results
     ngdb_grad_view& gv = c->gv;
@@ -1837,8 +1860,9 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     if (c->presized && d_cand && C > c->cfg.k_max)
         return fail(c, NGDB_ERR_ARG, "more candidates per query than the k_max declared at ngdb_create");
     int rc = reclaim ? size_forward_only(c, pl, n_tail) : size_workspace(c, pl, d_cand ? C : 0, false);
-    if (rc == NGDB_OK) rc = begin_pass(c, pl, s);
     if (rc != NGDB_OK) return rc;
+    PassEnd end{c, pl, s};
+    if ((rc = begin_pass(c, pl, s)) != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, d_cand, n_tail, s, &er, reclaim);
@@ -1860,7 +1884,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
         rc = rank_nearest(c, pl, roots, topk, d_topk_ids, d_topk_dist, s);
         if (rc != NGDB_OK) return rc;
     }
-    HIPCHK(c, hipEventRecord(pl->blob.last_use, s));
+    HIPCHK(c, end.close());
     return NGDB_OK;
 }
 
@@ -1914,6 +1938,7 @@ int ngdb_score_noalloc(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ca
     const uint32_t timing = c->timing_mask;     // event brackets would create events: off for this call
     c->timing_mask = 0;
     const EntRows er{c->prm.E.p, pl->d_f_in_ref, pl->d_pos, d_cand};
+    PassEnd end{c, pl, s};
     int rc = begin_pass(c, pl, s);
     if (rc == NGDB_OK) rc = enqueue_forward(c, pl, er, s, w);
     if (rc == NGDB_OK) {
@@ -1928,7 +1953,7 @@ int ngdb_score_noalloc(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ca
     }
     c->timing_mask = timing;
     if (rc != NGDB_OK) return rc;
-    HIPCHK(c, hipEventRecord(pl->blob.last_use, s));
+    HIPCHK(c, end.close());
     return NGDB_OK;
 }
 
@@ -1945,8 +1970,9 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     c->have_grads = false;
     const bool reclaim = c->cfg.family == NGDB_FAMILY_VEC;     // as in ngdb_score
     int rc = reclaim ? size_forward_only(c, pl, 0) : size_workspace(c, pl, 0, false);
-    if (rc == NGDB_OK) rc = begin_pass(c, pl, s);
     if (rc != NGDB_OK) return rc;
+    PassEnd end{c, pl, s};
+    if ((rc = begin_pass(c, pl, s)) != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, nullptr, 0, s, &er, reclaim);
@@ -1957,7 +1983,7 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
         rc = rank_listed(c, pl, roots, d_ans_off, d_ans, n_ans, d_rank, d_ans_dist, s);
         if (rc != NGDB_OK) return rc;
     }
-    HIPCHK(c, hipEventRecord(pl->blob.last_use, s));
+    HIPCHK(c, end.close());
     return NGDB_OK;
 }
 

@@ -140,3 +140,32 @@ def test_box_errors():
             setattr(P, name, binding.Tensor(p.data_ptr(), m.data_ptr(), v.data_ptr()))
     import ctypes as C
     assert L.ngdb_bind_params(fresh.ctx, C.byref(P)) == binding.ERR_ARG
+
+
+def test_a_step_that_is_refused_half_way_is_waited_for():
+    """Too many union branches for the scoring kernel is found after the forward pass and the index (on the library stream) have
+    been enqueued: the plan's buffer may go to another plan only behind them, and the caller's stream waits for them."""
+    import torch
+    from paper_2602_21597_amd import NgdbError, binding
+    N, R, d, h, B, K = 3000, 5, 1024, 64, 40, 120
+    rng = np.random.default_rng(3)
+    p = lambda: ("p", int(rng.integers(R)), ("e", int(rng.integers(N))))
+    wide = wl.batch_from_trees([("u",) + tuple(p() for _ in range(6)) for _ in range(B)], list(range(B)))
+    plain = wl.batch_from_trees([("u", p(), ("p", 1, p())) for _ in range(B)], list(range(B)))
+    params, negs = wl.make_box_params(N, R, d, h, 5), torch.from_numpy(wl.make_negatives(N, B, K, 6)).cuda()
+    out = []
+    for refused in (0, 3):
+        eng = binding.Engine(N, R, d, h, 12.0, num_streams=2, family=binding.FAMILY_BOX)
+        eng.bind_numpy(params)
+        for _ in range(4):
+            for _ in range(refused):
+                plan = eng.plan(wide)
+                with pytest.raises(NgdbError) as e:
+                    eng.train_step(plan, negs)
+                assert e.value.code == binding.ERR_UNSUPPORTED
+                plan.free()
+            plan = eng.plan(plain)
+            eng.train_step(plan, negs)
+            plan.free()
+        out.append([t for name in eng.tensor_names() for t in eng.tensors[name]])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
