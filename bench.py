@@ -114,10 +114,12 @@ def say(msg):
     print("[bench] " + msg, file=sys.stderr, flush=True)
 
 
-def kernel_models(cfg, pexp, touched, box=False, score_bf16=False):
+def kernel_models(cfg, pexp, touched, box=False, score_bf16=False, streams=1):
     """Algorithmic work of one step per kernel class: what the method itself has to move or
     multiply, whatever the kernels do.  Returns {class: (bound, amount, peak, unit)} with
     amounts in bytes (hbm) or flops (mfma)."""
+    # with a library stream the rows that anchors refer to are left to the launch that ends the step
+    left = np.unique(pexp["anchor_ent"]).size if streams > 1 else 0
     row = 4 * cfg.d
     pairs = cfg.B * (cfg.K + 1)
     n_contrib = pexp["n_anchor"] + cfg.B + cfg.B * cfg.K
@@ -128,12 +130,13 @@ def kernel_models(cfg, pexp, touched, box=False, score_bf16=False):
     score_bytes = pairs * (row + 4 + 12) + pexp["n_roots"] * 2 * row
     # every touched row: p, m, v read and written; every contribution: 12 bytes of record; anchor
     # gradient rows read; with text features also the fused row read and the bf16 gradient written
-    table_bytes = touched * 6 * row + n_contrib * 12 + pexp["n_anchor"] * row
+    table_rows = touched - left
+    table_bytes = table_rows * 6 * row + n_contrib * 12 + (0 if left else pexp["n_anchor"] * row)
     if sem:
-        table_bytes += touched * (row + 2 * cfg.d)
+        table_bytes += table_rows * (row + 2 * cfg.d)
     if score_bf16:   # candidate rows at 2 bytes per coordinate; the copy's row written with every touched row
         score_bytes -= pairs * (row // 2)
-        table_bytes += touched * (row // 2)
+        table_bytes += table_rows * (row // 2)
     if box:   # boxes at the roots are two rows wide; two MLPs over the inputs of the intersections, none elsewhere
         score_bytes += pexp["n_roots"] * 2 * row
         mlp_rows = 2 * pexp["n_int_rows"]
@@ -205,8 +208,10 @@ def rank_bench(args, cfg, kg, params, sem_bits, box=False):
         run()
     ms, n = eng.get_timing(reset=True)["score"]
     # subtract and |.|-accumulate per coordinate, branch row and entity (box distance: subtract,
-    # scale, subtract the shrunk offset, maximum, accumulate)
-    ops = (5.0 if box else 2.0) * rows * cfg.N * cfg.d
+    # scale, subtract the shrunk offset, maximum, accumulate); vectors over more than 4096 entities go through the
+    # integer filter, which sums four packed differences per operation (filtered ranks: two)
+    per_coord = 5.0 if box else (2.0 if cfg.N <= 4096 else (0.25 if args.answers <= 0 else 0.5))
+    ops = per_coord * rows * cfg.N * cfg.d
     ach = ops / (ms / n * 1e-3) / 1e12
     what = "top-%d" % k if args.answers <= 0 else "filtered ranks of %d answers per query, MRR, Hit@k" % args.answers
     out = {"metric": "all-entity ranking queries/sec (forward + L1 distance to every entity + %s)" % what,
@@ -216,7 +221,8 @@ def rank_bench(args, cfg, kg, params, sem_bits, box=False):
            "config": {"workload": "configs[%d] %s ranking pass: %d queries (%d branch rows) x N=%d entities, d=%d%s, top-%d"
                       % (cfg.index, cfg.name + (" (box family, alpha=%g)" % args.box_alpha if box else ""), Q, rows,
                          cfg.N, cfg.d, " d_sem=%d" % cfg.d_sem if cfg.d_sem else "", k), "evaluation": what},
-           "roofline": {"bound": "alu", "kernel": "rank (distance tiles + %s%s)" % (
+           "roofline": {"bound": "alu", "kernel": "rank (%s + %s%s)" % (
+                            "distance tiles" if box or cfg.N <= 4096 else "integer filter",
                             "top-k merge" if args.answers <= 0 else "closer-entity counts",
                             " + projection of every entity chunk" if cfg.d_sem else ""),
                         "achieved": ach, "peak": VALU_PEAK_TOPS, "unit": "Tlane-op/s", "frac": ach / VALU_PEAK_TOPS,
@@ -402,7 +408,7 @@ def measure_workload(cfg, args, kg, steps, warmup, box=False, streams=None):
     # against the fp32 matrix peak; the ones on split operands execute six bf16 products per fp32
     # product and are priced with those executed flops against the bf16 matrix peak (their
     # algorithmic rate is a sixth of that).
-    models = kernel_models(cfg, pexp, touched, box, args.score_bf16)
+    models = kernel_models(cfg, pexp, touched, box, args.score_bf16, streams)
     kern = {}
     for name, (bound, amount, peak, unit) in models.items():
         ms, n = timing[name]
