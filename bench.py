@@ -153,8 +153,8 @@ def kernel_models(cfg, pexp, touched, box=False, score_bf16=False, streams=1):
     return models
 
 
-VALU_PEAK_TOPS = 39.3     # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one fp32 op per lane and clock
-                          # (packed forms are switched off in this build)
+VALU_PEAK_TOPS = 78.6     # fp32 vector operations: the published 157.3 TFLOP/s, two flops an operation
+SAD_PEAK_TOPS = 39.3      # sums of packed integer differences: 256 CUs x 64 lanes x 2.4 GHz
 
 
 def rank_bench(args, cfg, kg, params, sem_bits, box=False):
@@ -210,7 +210,9 @@ def rank_bench(args, cfg, kg, params, sem_bits, box=False):
     # subtract and |.|-accumulate per coordinate, branch row and entity (box distance: subtract,
     # scale, subtract the shrunk offset, maximum, accumulate); vectors over more than 4096 entities go through the
     # integer filter, which sums four packed differences per operation (filtered ranks: two)
-    per_coord = 5.0 if box else (2.0 if cfg.N <= 4096 else (0.25 if args.answers <= 0 else 0.5))
+    fp32 = box or cfg.N <= 4096
+    per_coord = 5.0 if box else (2.0 if fp32 else (0.25 if args.answers <= 0 else 0.5))
+    peak = VALU_PEAK_TOPS if fp32 else SAD_PEAK_TOPS
     ops = per_coord * rows * cfg.N * cfg.d
     ach = ops / (ms / n * 1e-3) / 1e12
     what = "top-%d" % k if args.answers <= 0 else "filtered ranks of %d answers per query, MRR, Hit@k" % args.answers
@@ -222,10 +224,10 @@ def rank_bench(args, cfg, kg, params, sem_bits, box=False):
                       % (cfg.index, cfg.name + (" (box family, alpha=%g)" % args.box_alpha if box else ""), Q, rows,
                          cfg.N, cfg.d, " d_sem=%d" % cfg.d_sem if cfg.d_sem else "", k), "evaluation": what},
            "roofline": {"bound": "alu", "kernel": "rank (%s + %s%s)" % (
-                            "distance tiles" if box or cfg.N <= 4096 else "integer filter",
+                            "distance tiles" if fp32 else "integer filter",
                             "top-k merge" if args.answers <= 0 else "closer-entity counts",
                             " + projection of every entity chunk" if cfg.d_sem else ""),
-                        "achieved": ach, "peak": VALU_PEAK_TOPS, "unit": "Tlane-op/s", "frac": ach / VALU_PEAK_TOPS,
+                        "achieved": ach, "peak": peak, "unit": "Tlane-op/s", "frac": ach / peak,
                         "traffic": None, "avg_us": 1e3 * ms / n,
                         "algorithmic_work_per_launch": ops},
            "cpu_baseline": cpu}
