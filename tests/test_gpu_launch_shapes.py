@@ -130,9 +130,10 @@ def test_tables_beside_the_backward_pass(N, d, B, K, d_sem, bf16):
     assert all(torch.equal(a, b) for a, b in zip(out[0][2], out[1][2]))
 
 
-# operators of a depth in one launch: widths that fill no tile, the widest hidden layer, the limit of weights a layer and
-# beyond it; one query, row blocks that are nearly empty, intersections of two to eight inputs
-@pytest.mark.parametrize("d,h,B", [(4, 4, 5), (20, 36, 1), (36, 100, 30), (64, 512, 40), (128, 256, 90), (132, 256, 40), (256, 128, 17)])
+# operators of a depth in one launch: widths that fill no tile, the widest hidden layer, the limit of weights a layer (for any
+# depth, for depths of few row blocks) and beyond it; one query, row blocks that are nearly empty, intersections of two to eight inputs
+@pytest.mark.parametrize("d,h,B", [(4, 4, 5), (20, 36, 1), (36, 100, 30), (64, 512, 40), (128, 256, 90), (132, 256, 40), (256, 128, 17),
+                                   (40, 512, 60), (128, 160, 40), (128, 164, 3), (128, 164, 14), (128, 256, 4)])
 def test_operators_of_a_depth_in_one_launch(d, h, B):
     rng = np.random.default_rng(d)
     N, R = 300, 9
