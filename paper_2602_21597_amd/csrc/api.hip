@@ -776,10 +776,12 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
             float* Z = w.Z[sg.type] + row0 * d;
             float* Hh = w.H[sg.type] + row0 * h;
             GemmArgs& a = g1[n];
-            // first layer reads its rows through the plan's references and leaves a copy in Z
+            // first layer reads its rows through the plan's references and leaves a copy in Z for who reads them again: the weight
+            // gradients, and the pooling of intersections
             a.a_ref = er.refs + sg.ref_off; a.a_base0 = w.act; a.a_base1 = er.rows;
             if (sg.rel_off >= 0) { a.a_add_idx = pl->d_rel + sg.rel_off; a.a_add = c->prm.R.p; }
-            a.a_copy = Z; a.lda = d; a.B = W.Wa; a.ldb = d; a.C = Hh; a.ldc = h;
+            a.a_copy = w.reclaim && sg.type != T_INTER ? nullptr : Z;
+            a.lda = d; a.B = W.Wa; a.ldb = d; a.C = Hh; a.ldc = h;
             a.M = sg.rows; a.N = h; a.K = d; a.bias = W.ba; a.relu = true;
             GemmArgs& b = g2[n];
             b.A = Hh; b.lda = h; b.B = W.Wb; b.ldb = h; b.M = sg.rows; b.N = d; b.K = h; b.bias = W.bb; b.ldc = d;

@@ -65,6 +65,10 @@ __device__ __forceinline__ float lane_value(float v, int l) {
 __device__ __forceinline__ void lds_load16(const void* gptr, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
 }
+// the same from a wave-uniform address and a lane's byte offset
+__device__ __forceinline__ void lds_load16_at(const void* base, uint32_t offset, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(offset), "s"(base) : "memory");
+}
 __device__ __forceinline__ void lds_load4(const void* gptr, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
 }
@@ -148,7 +152,7 @@ struct GemmArgs {
     int a_row0 = 0;                // row 0 of A is row a_row0 of a_pieces (with pool_k only)
     // The output rows are the logits of intersections of pool_k inputs (row j * n + i: input j of member i, M = n * pool_k):
     // row i of pool_out, or row pool_row[i], receives sum_j softmax_j(C[j * n + i]) * pool_X[j * n + i] (leading dimension ldc).
-    // C may be null then.  Only launches of split weights in small tiles do this; others return hipErrorNotSupported.
+    // C may be null then.  Only launches of split weights do this; others return hipErrorNotSupported.
     int pool_k = 0;
     const float* pool_X = nullptr;
     float* pool_out = nullptr;
@@ -169,8 +173,8 @@ struct GemmGroup {
     GemmArgs p[GEMM_MAX_GROUP];
 };
 // *route (if given) receives the arithmetic the launch used: GEMM_FP32 or GEMM_SPLIT; *emitted (if
-// given) whether the launch wrote c_pieces (only the kernels that read their B operand as pieces do,
-// in launches of at most 256 small tiles, and only if every problem of the group asks for it).
+// given) whether the launch wrote c_pieces (only gemm_kernel does where it reads its B operand as pieces,
+// in launches of few tiles, and only if every problem of the group asks for it).
 hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route = nullptr, bool* emitted = nullptr);
 // Weight gradients: C[M,N] = A^T B over the K rows of A [K][lda] and B [K][ldb] (the rows of an operator type),
 // and colsum[m] = sum of column m of A (the gradient of the layer's bias).  M, N and the leading

@@ -1,5 +1,6 @@
 // Contractions of the grouped operator MLPs (Sec. 4.1's batched kernels): gemm_kernel forward and
-// for data gradients, rows_kernel forward over few rows, wgrad_kernel for weight gradients.
+// for data gradients, product_kernel the same over many rows, rows_kernel forward over few rows, wgrad_kernel for
+// weight gradients.
 //
 // The groups of one batch are small next to the chip (a few hundred to a few
 // thousand rows against 256 compute units), so a contraction is latency bound,
@@ -885,6 +886,325 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradGroup g) {
         a.colsum[m0 + tid] = (cs[0][tid] + cs[1][tid]) + (cs[2][tid] + cs[3][tid]);
 }
 
+// Forward layers and data gradients over many rows, weights from pieces.  A tile of 32 WM rows x 64 columns belongs to
+// WM x WK wavefronts: one takes 32 rows x 64 columns over every WK-th block of 16 k.  Rows (fp32) and pieces travel from global
+// memory straight into LDS: a wavefront's own rows, and for the WM of a block the pieces together.  A wavefront reads both as
+// MFMA operands, splits the rows on the way (44 vector operations a block) and multiplies (12 MFMAs, 384 cycles); a block's
+// requests are on their way for one turn.  Every operand reaches a compute unit once a tile instead of once a wavefront, and a
+// row is split once per 64 columns: gemm_kernel's 32 x 32 tiles fetch 5 KB a block of 6 MFMAs, which at 2000 rows is 190 MB
+// through the L1s.  What is left is bound by LDS (8 KB read and 5 KB written a block and wavefront) and by issue; it takes four
+// wavefronts a SIMD to hide that (128 registers), and 64 x 64 accumulators on two, or three stages in LDS, were slower.
+// us a launch at d = 400, h = 800 (first layer with relations and copy, second layer, their gradients), against gemm_kernel:
+// 480 rows 7.8 7.9 7.8 6.6 (8.8 8.2 8.2 7.9), 1000 rows 11.0 8.3 8.2 8.4 (14.9 10.8 10.8 12.1), 2000 rows 17.3 11.7 11.7 13.7
+// (22.5 18.9 19.1 19.7), 7900 rows 57 40 40 44 (76 59 60 64).  The whole forward pass of 1024 queries (launches and their gaps included)
+// 136 -> 121 us, of 4096 314 -> 261.
+// 64 bytes of a row and block land per row; 16-byte unit c of row r is stored at c ^ tile_swizzle(r), which spreads the reads
+// of 16 rows over all banks.
+// ADD: problems may add a second gathered row (the relation's) to every row of A; it is staged likewise.
+// POOL: as in gemm_kernel, 32 WM / pool_k members to a tile.
+// The sums are formed as in gemm_kernel (WK partial sums of blocks, six products each, smallest first).
+constexpr int FIRST = 3;      // products ahead of the wait for a block's reads
+constexpr int PN = 64, PN_LD = PN + 4;      // columns of a tile
+__device__ __forceinline__ int tile_swizzle(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
+template <int WM, int WK, bool ADD, bool POOL>
+__global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(const GemmGroup g) {
+    constexpr int NW = WM * WK, BM = 32 * WM;
+    constexpr int AB = 2048, BB = 2 * WTILE * 2;             // bytes of 32 rows of a block, of two tiles of pieces
+    constexpr int ROWS = (ADD ? 2 : 1) * AB, GROUP = 2 * BB + WM * ROWS;
+    // partial sums of a group of wavefronts: where one wavefront alone staged (its own requests are in), else behind a barrier
+    constexpr int PART = WM == 1 ? GROUP : BM * PN_LD * 4;
+    static_assert(PART >= BM * PN_LD * 4, "a partial tile fits its place");
+    constexpr int BL = (6 + WM - 1) / WM;                    // loads of pieces per wavefront and stage
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[WK * (GROUP > PART ? GROUP : PART)];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave / WM, wm = wave % WM;      // (in scalar registers)
+    int p = 0;
+#pragma unroll
+    for (int i = 1; i < GEMM_MAX_GROUP; ++i)
+        if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) p = i;
+    const GemmArgs& a = g.p[p];
+    // (all of the arguments that are used late are requested here: one by one each costs a round trip to the argument segment)
+    const float *bias = a.bias, *mask = a.mask, *addend = a.addend, *X = a.pool_X;
+    const int32_t *dst_row = a.dst_row, *pool_row = a.pool_row;
+    float *C = a.C, *a_copy = a.a_copy, *pool_out = a.pool_out;
+    const int ldc = a.ldc, ldmask = a.ldmask, ldadd = a.ldadd, relu = a.relu;
+    asm volatile("" ::"s"(bias), "s"(mask), "s"(addend), "s"(dst_row), "s"(C), "s"(a_copy), "s"(ldc), "s"(ldmask), "s"(ldadd), "s"(relu));
+    if (POOL) asm volatile("" ::"s"(X), "s"(pool_row), "s"(pool_out));
+    // (tiles to dies as in gemm_kernel)
+    const int local = (int)blockIdx.x - g.tile_start[p], per_die = (g.tile_start[p + 1] - g.tile_start[p]) >> 3;
+    const int tile = (local & 7) * per_die + (local >> 3);
+    const int cls = POOL && a.pool_k ? a.pool_k : 1, mem = BM / cls, n_mem = a.M / cls;
+    const int tiles_m = (n_mem + mem - 1) / mem, tiles_n = (a.N + PN - 1) / PN;
+    if (tile >= tiles_m * tiles_n) return;
+    const bool m_major = a.M >= a.N;
+    const int mt = m_major ? tile / tiles_n : tile % tiles_m;
+    const int nt = m_major ? tile % tiles_n : tile / tiles_m, n0 = nt * PN;
+    auto row_of = [&](int lr, bool* ok) {          // row of A and C that row lr of the tile is (past the end: the last one)
+        const int j = POOL ? lr / mem : 0, i = mt * mem + lr - j * mem;
+        *ok = j < cls && i < n_mem;
+        return *ok ? j * n_mem + i : a.M - 1;
+    };
+
+    const int nk = (a.K + 15) / 16, stages = (nk + WK - 1) / WK, k_last = a.K - 4;
+    const uint32_t at = lds_addr(lds) + kg * GROUP, at_a = at + 2 * BB + wm * ROWS;
+    const bool has_add = ADD && a.a_add_idx != nullptr;      // uniform
+    // (the second tile of a last column block that has one only: the first once more, its columns are not stored)
+    const uint16_t* btile = a.b_pieces + (size_t)(n0 / 32) * a.b_kt * WTILE;
+    const uint32_t b_next = n0 + 32 < a.N ? (uint32_t)a.b_kt * WTILE : 0u;
+    uint32_t b_at[BL];                  // this wavefront's pieces of a stage: i % 3 of tile i / 3
+#pragma unroll
+    for (int q = 0; q < BL; ++q) {
+        const int i = min(wm * BL + q, 5);
+        b_at[q] = i >= 3 ? b_next + (i - 3) * 512 : i * 512;
+    }
+    // (stages past the end fetch the last block again; k past the end the last four, which meet zeros in the pieces)
+    auto issue_b = [&](int s, int half) {
+        const uint16_t* b = btile + (uint32_t)min(s * WK + kg, nk - 1) * WTILE;
+#pragma unroll
+        for (int q = 0; q < BL; ++q) lds_load16_at(b + b_at[q], lane * 16, at + half * BB + min(wm * BL + q, 5) * 1024);
+    };
+    issue_b(0, 0);                      // on their way while the rows are looked up
+    issue_b(1, 1);
+    const int unit = ((lane & 3) ^ tile_swizzle(lane >> 2)) * 4;                // k of the 16 bytes this lane fetches
+    const float *arow[2], *radd[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        bool ok;
+        const int m = row_of(wm * 32 + q * 16 + (lane >> 2), &ok);
+        if (a.a_ref) {
+            const int32_t r = a.a_ref[m];
+            arow[q] = r >= 0 ? a.a_base0 + (size_t)r * a.lda : a.a_base1 + (size_t)(-1 - r) * a.lda;
+        } else {
+            arow[q] = a.A + (size_t)m * a.lda;
+        }
+        if (ADD) radd[q] = has_add ? a.a_add + (size_t)a.a_add_idx[m] * a.lda : arow[q];
+    }
+    auto issue_a = [&](int s, auto added) {
+        const uint32_t k = (uint32_t)min(min(s * WK + kg, nk - 1) * 16 + unit, k_last);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) lds_load16(arow[q] + k, at_a + q * 1024);
+        if (decltype(added)::value) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) lds_load16(radd[q] + k, at_a + AB + q * 1024);
+        }
+    };
+    floatx16 acc[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    float v[8];                         // values of a block of A
+    bf16x8 pa[2][3], pb[2][2][3];       // pieces of the block being multiplied and of the next
+    // lane: row (lane & 31) of 32, k = 8 * (lane >> 5) .. + 7 = units 2 * (lane >> 5) and the next
+    const int f = tile_swizzle(lane & 15), u0 = (lane >> 5) * 2;
+    const unsigned char* rows = lds + kg * GROUP + 2 * BB + wm * ROWS + (lane & 31) * 64;
+    const unsigned char* pieces = lds + kg * GROUP + lane * 16;
+    auto fetch = [&](int half, bf16x8 (&b)[2][3], auto added) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int off = ((u0 + h) ^ f) * 16;
+            float4 x = *reinterpret_cast<const float4*>(rows + off);
+            if (decltype(added)::value) {
+                const float4 y = *reinterpret_cast<const float4*>(rows + AB + off);
+                x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
+            }
+            v[h * 4] = x.x; v[h * 4 + 1] = x.y; v[h * 4 + 2] = x.z; v[h * 4 + 3] = x.w;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) b[j][q] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(pieces + half * BB + (j * 3 + q) * 1024));
+    };
+    auto split = [&](bf16x8 (&to)[3]) {
+        u32x4 h, m, l;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t wh, wm_, wl;
+            split2(v[2 * q], v[2 * q + 1], wh, wm_, wl);
+            h[q] = wh; m[q] = wm_; l[q] = wl;
+        }
+        to[0] = __builtin_bit_cast(bf16x8, h);
+        to[1] = __builtin_bit_cast(bf16x8, m);
+        to[2] = __builtin_bit_cast(bf16x8, l);
+    };
+    // smallest products first; the output is built transposed (a lane holds 4 consecutive columns of a row)
+    auto multiply = [&](const bf16x8 (&fa)[3], const bf16x8 (&fb)[2][3], auto from, auto to) {
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int t = decltype(from)::value; t < decltype(to)::value; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j][PB[t]], fa[PA[t]], acc[j], 0, 0, 0);
+    };
+    using N0 = std::integral_constant<int, 0>;
+    using N1 = std::integral_constant<int, 1>;
+    using NF = std::integral_constant<int, FIRST>;
+    using N6 = std::integral_constant<int, 6>;
+    auto walk = [&](auto added) {
+        // what was asked for has landed, everybody's, and everybody has read what it fetched
+        auto arrive = [&]() {
+            asm volatile("" ::: "memory");
+            wait_lds();
+            wait_vm<0>();
+            if (WM > 1) __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        auto turn = [&](int s, auto half) {
+            constexpr int u = decltype(half)::value;
+            arrive();
+            fetch(u ^ 1, pb[u ^ 1], added);
+            issue_b(s + 2, u);
+            multiply(pa[u], pb[u], N0(), NF());         // (while the reads are on their way)
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+            wait_lds();
+            issue_a(s + 2, added);                      // the rows' place is this wavefront's own
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(pa[u], pb[u], NF(), N6());
+            split(pa[u ^ 1]);
+#pragma unroll
+            for (int q = 0; q < 12 - 2 * FIRST; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);    // one MFMA,
+                __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);    // then vector operations
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        issue_a(0, added);
+        arrive();
+        fetch(0, pb[0], added);
+        wait_lds();
+        issue_a(1, added);
+        split(pa[0]);
+        // (in the last stage not every group of wavefronts has a block)
+        const bool last = (stages - 1) * WK + kg < nk;
+        int s = 0;
+        for (; s + 2 < stages; s += 2) {
+            turn(s, N0());
+            turn(s + 1, N1());
+        }
+        if (s + 1 < stages) {
+            turn(s, N0());
+            if (last) multiply(pa[1], pb[1], N0(), N6());
+        } else if (last) {
+            multiply(pa[0], pb[0], N0(), N6());
+        }
+    };
+    if (has_add) walk(std::true_type());
+    else walk(std::false_type());
+    wait_vm<0>();                       // (the requests past the end land before their place is used again)
+    if (WM > 1) __syncthreads();
+    // The rows as gathered, for who reads them later: every tile copies its share of their columns, a wavefront its rows and its
+    // share of these (requested here, stored last).
+    const bool copies = !POOL && a_copy != nullptr;
+    const int k4 = a.K >> 2, per = (k4 + tiles_n - 1) / tiles_n, c_end = min(k4, (nt + 1) * per);
+    int c = nt * per + kg * 4;
+    float4 cy[2], cz[2];
+    auto copy_load = [&]() {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int k = min(c + (lane & 3), k4 - 1) * 4;
+            cy[q] = load_global4(arow[q] + k);
+            if (has_add) cz[q] = load_global4(radd[q] + k);
+        }
+    };
+    auto copy_store = [&]() {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int m = mt * BM + wm * 32 + q * 16 + (lane >> 2), k = c + (lane & 3);
+            if (has_add) { cy[q].x += cz[q].x; cy[q].y += cz[q].y; cy[q].z += cz[q].z; cy[q].w += cz[q].w; }
+            if (m < a.M && k < c_end) *reinterpret_cast<float4*>(a_copy + (size_t)m * a.lda + k * 4) = cy[q];
+        }
+    };
+    if (copies) copy_load();
+    // operands of the epilogue: four consecutive columns of ER rows per thread, in flight during the reduction
+    constexpr int ER = BM * PN / 4 / (NW * 64), RS = NW * 4;      // rows of a thread, RS apart
+    const int lc = (tid & 15) * 4, col = min(n0 + lc, a.N - 4);
+    float4 e_mask[ER], e_add[ER];
+    float e_bias[4];
+    int row[ER], orow[ER];
+    bool inside[ER];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e_bias[j] = bias ? bias[col + j] : 0.f;
+#pragma unroll
+    for (int q = 0; q < ER; ++q) {
+        row[q] = row_of((tid >> 4) + q * RS, &inside[q]);
+        e_mask[q] = mask ? load_global4(mask + (size_t)row[q] * ldmask + col) : make_float4(1.f, 1.f, 1.f, 1.f);
+        e_add[q] = addend ? load_global4(addend + (size_t)row[q] * ldadd + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+        inside[q] = inside[q] && n0 + lc < a.N;
+    }
+#pragma unroll
+    for (int q = 0; q < ER; ++q) orow[q] = dst_row ? dst_row[row[q]] : row[q];
+    float* part = reinterpret_cast<float*>(lds + kg * PART) + (wm * 32 + (lane & 31)) * PN_LD;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<float4*>(part + j * 32 + r * 8 + (lane >> 5) * 4) =
+                make_float4(acc[j][r * 4], acc[j][r * 4 + 1], acc[j][r * 4 + 2], acc[j][r * 4 + 3]);
+    __syncthreads();
+    float* all = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int q = 0; q < ER; ++q) {
+        float* mine4 = all + ((tid >> 4) + q * RS) * PN_LD + lc;
+        float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WK; ++w) {
+            const float4 x = *reinterpret_cast<const float4*>(mine4 + w * (PART / 4));
+            o[0] += x.x; o[1] += x.y; o[2] += x.z; o[3] += x.w;
+        }
+        const float mk[4] = {e_mask[q].x, e_mask[q].y, e_mask[q].z, e_mask[q].w}, ad[4] = {e_add[q].x, e_add[q].y, e_add[q].z, e_add[q].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[j] += e_bias[j];
+            if (relu) o[j] = fmaxf(o[j], 0.f);
+            o[j] = mk[j] > 0.f ? o[j] : 0.f;
+            o[j] += ad[j];
+        }
+        const float4 out = make_float4(o[0], o[1], o[2], o[3]);
+        if (inside[q] && (!POOL || C)) *reinterpret_cast<float4*>(C + (size_t)orow[q] * ldc + n0 + lc) = out;
+        if (POOL && a.pool_k) *reinterpret_cast<float4*>(mine4) = out;      // (read before by this thread only)
+    }
+    if (copies) {
+        copy_store();
+        for (c += 4 * WK; c < c_end; c += 4 * WK) {
+            copy_load();
+            copy_store();
+        }
+    }
+    if (POOL && a.pool_k) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < (ER + 1) / 2; ++q) {                 // (at most BM / 2 members a tile)
+            const int ii = (tid >> 4) + q * RS, i = mt * mem + ii;
+            if (ii >= mem || i >= n_mem || n0 + lc >= a.N) continue;
+            float4 z[NGDB_MAX_CARD], x[NGDB_MAX_CARD];
+#pragma unroll
+            for (int j = 0; j < NGDB_MAX_CARD; ++j)
+                if (j < cls) {
+                    x[j] = load_global4(X + (size_t)(j * n_mem + i) * ldc + n0 + lc);
+                    z[j] = *reinterpret_cast<const float4*>(all + (j * mem + ii) * PN_LD + lc);
+                }
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                auto of = [&](const float4& f4) { return e == 0 ? f4.x : (e == 1 ? f4.y : (e == 2 ? f4.z : f4.w)); };
+                float mx = -INFINITY, den = 0.f, w[NGDB_MAX_CARD];
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j)
+                    if (j < cls) mx = fmaxf(mx, of(z[j]));
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j)
+                    if (j < cls) { w[j] = expf(of(z[j]) - mx); den += w[j]; }
+                const float inv = 1.f / den;
+                y[e] = 0.f;
+#pragma unroll
+                for (int j = 0; j < NGDB_MAX_CARD; ++j)
+                    if (j < cls) y[e] += w[j] * inv * of(x[j]);
+            }
+            *reinterpret_cast<float4*>(pool_out + (size_t)(pool_row ? pool_row[i] : i) * ldc + n0 + lc) = make_float4(y[0], y[1], y[2], y[3]);
+        }
+    }
+}
+
 // Forward layers of very few rows (a handful of queries): a matrix-vector product per row.  The time is reading
 // the weights once, 1.3 MB at d=400, h=800, spread over the chip: a wavefront takes ROWS_N output columns, reads
 // their weight rows (k-contiguous, a float4 per lane) and multiplies them with up to MR assembled rows held in
@@ -965,6 +1285,16 @@ __global__ __launch_bounds__(256) void rows_kernel(const GemmGroup g) {
     }
 }
 
+// Launches of more than this many tiles of 32 x 64 take product_kernel; below, half of them would leave compute units idle, and
+// gemm_kernel's smaller tiles are through first.  At d = 400, h = 800, first layer, gemm_kernel against this one: 130 tiles 6.9 and 7.4 us,
+// 169 tiles 9.0 and 7.7; second layer 112 tiles 7.9 and 7.8, 154 tiles 10.7 and 8.1; at d = 256, h = 512 104 tiles 5.7 and 6.7, 176
+// tiles 7.6 and 6.9.  Short k needs more tiles: k = 128 with 188 tiles 5.8 and 6.1, with 376 tiles 8.5 and 7.6; k = 184 with 188 tiles 6.7
+// and 7.0; k = 152 with 282 tiles 9.3 and 8.0.  Up to 256 tiles, one to a compute unit, k is split over all eight wavefronts of one; beyond,
+// pairs of them share the pieces (1000 rows at d = 400, h = 800: second layer 224 tiles 8.3 against 10.6 us, first layer 416 tiles
+// 13.5 against 11.0).
+constexpr long PRODUCT_ONE_EACH = 256;
+long product_from(int max_k) { return max_k < 256 ? PRODUCT_ONE_EACH : 140; }
+
 bool takes_rows_kernel(const GemmArgs& a) {
     return a.arith == GEMM_AUTO && a.a_kcontig && a.b_kcontig && a.M <= ROWS_MAX && (long)a.M * a.K <= ROWS_LDS && !a.mask &&
            !a.addend && !a.a_pieces;
@@ -1007,9 +1337,28 @@ hipError_t dispatch_layout(GemmGroup& g, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int NW, bool AP, int PF>
+template <int WM, int WK>
+hipError_t dispatch_product(GemmGroup& g, bool pool, hipStream_t s) {
+    int tiles = 0;
+    bool add = false;
+    for (int i = 0; i < g.count; ++i) {
+        g.tile_start[i] = tiles;
+        const int k = g.p[i].pool_k ? g.p[i].pool_k : 1, rows = WM * 32 / k, n = g.p[i].M / k;
+        tiles += (((n + rows - 1) / rows) * ((g.p[i].N + PN - 1) / PN) + 7) / 8 * 8;
+        add = add || g.p[i].a_add_idx != nullptr;
+    }
+    for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = tiles;
+    const dim3 grid(tiles), block(WM * WK * 64);
+    if (pool && add) return hipErrorInvalidValue;
+    if (pool) hipLaunchKernelGGL((product_kernel<WM, WK, false, true>), grid, block, 0, s, g);
+    else if (add) hipLaunchKernelGGL((product_kernel<WM, WK, true, false>), grid, block, 0, s, g);
+    else hipLaunchKernelGGL((product_kernel<WM, WK, false, false>), grid, block, 0, s, g);
+    return hipGetLastError();
+}
+
+template <bool AP, int PF>
 hipError_t dispatch_pieces(GemmGroup& g, bool pool, hipStream_t s) {
-    constexpr int BM = 32, BN = 32;
+    constexpr int BM = 32, BN = 32, NW = 8;
     int tiles = 0;
     for (int i = 0; i < g.count; ++i) {
         g.tile_start[i] = tiles;
@@ -1057,15 +1406,22 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     if (few_rows) return pool ? hipErrorNotSupported : dispatch_rows(g, s);
     const int arith = g.p[0].arith;
     const bool auto_split = arith == GEMM_AUTO && g.p[0].a_kcontig && max_k >= 128;
-    // (with the B operands ready-made the small tile holds its own up to twice the size: 0.516 + 0.388
-    // against 0.537 + 0.416 ms for the forward and backward launches of 4096 queries at h = 800)
+    // every B operand comes ready-made (weights split once per pass), and rows of four columns can be stored at once
     bool b_ready = g.p[0].a_kcontig;
-    for (int i = 0; i < g.count; ++i) b_ready = b_ready && g.p[i].b_pieces != nullptr && g.p[i].b_kt >= (g.p[i].K + 15) / 16;
-    const long big_at = b_ready && auto_split ? 4096 : 2048;
-    if (pool && (!b_ready || !auto_split || blocks_small >= big_at)) return hipErrorNotSupported;
+    for (int i = 0; i < g.count; ++i) {
+        const GemmArgs& a = g.p[i];
+        b_ready = b_ready && a.b_pieces != nullptr && a.b_kt >= (a.K + 15) / 16 && ((a.N | a.ldc) & 3) == 0 && (!a.mask || (a.ldmask & 3) == 0) &&
+                  (!a.addend || (a.ldadd & 3) == 0) &&
+                  (((uintptr_t)a.C | (uintptr_t)a.mask | (uintptr_t)a.addend | (uintptr_t)a.pool_X | (uintptr_t)a.pool_out | (uintptr_t)a.a_copy) & 15) == 0;
+    }
+    if (pool && (!b_ready || !auto_split)) return hipErrorNotSupported;
     for (int i = 0; pool && i < g.count; ++i)
         if (g.p[i].pool_k == 1 || g.p[i].pool_k > NGDB_MAX_CARD || (g.p[i].pool_k > 0 && g.p[i].M % g.p[i].pool_k)) return hipErrorInvalidValue;
-    if (blocks_small >= big_at && arith != GEMM_SPLIT) {
+    if (b_ready && (auto_split || arith == GEMM_SPLIT) && blocks_small > product_from(max_k)) {
+        if (route) *route = GEMM_SPLIT;
+        return blocks_small <= PRODUCT_ONE_EACH ? dispatch_product<1, 8>(g, pool, s) : dispatch_product<2, 4>(g, pool, s);
+    }
+    if (blocks_small >= 2048 && arith != GEMM_SPLIT) {
         if (route && auto_split) *route = GEMM_SPLIT;
         return auto_split ? dispatch_layout<64, 64, 4, true>(g, s) : dispatch_layout<64, 64, 4>(g, s);
     }
@@ -1079,25 +1435,19 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     // (with a k extent below 128 the matrix unit is idle either way and the splitting only adds work)
     if (arith == GEMM_SPLIT || auto_split) {
         if (route) *route = GEMM_SPLIT;
-        // every B operand comes ready-made (weights split once per pass): no staging of B at all
-        bool all_pieces = g.p[0].a_kcontig;
-        for (int i = 0; i < g.count; ++i) all_pieces = all_pieces && g.p[i].b_pieces != nullptr && g.p[i].b_kt >= (g.p[i].K + 15) / 16;
-        if (all_pieces) {
+        if (b_ready) {      // no staging of B at all
             // ... and the A operand too where the launch before left its output as pieces
             bool a_too = true;
             for (int i = 0; i < g.count; ++i)
                 a_too = a_too && g.p[i].a_pieces != nullptr && !g.p[i].a_ref && !g.p[i].a_copy && g.p[i].a_kt >= (g.p[i].K + 15) / 16;
-            // (only from launches that leave compute units idle: in a larger one the extra stores cost
-            // more than the launch after it saves)
-            if (emitted && blocks_small * 2 <= 512) {
+            if (emitted) {
                 *emitted = true;
                 for (int i = 0; i < g.count; ++i)
                     *emitted = *emitted && c_pieces[i] != nullptr && !g.p[i].dst_row && g.p[i].c_kt >= 2 * ((g.p[i].N + 31) / 32);
                 for (int i = 0; i < g.count; ++i)
                     if (*emitted) g.p[i].c_pieces = c_pieces[i];
             }
-            if (blocks_small * 2 > 512) return a_too ? dispatch_pieces<4, true, 2>(g, pool, s) : dispatch_pieces<4, false, 1>(g, pool, s);
-            return a_too ? dispatch_pieces<8, true, 2>(g, pool, s) : dispatch_pieces<8, false, 1>(g, pool, s);
+            return a_too ? dispatch_pieces<true, 2>(g, pool, s) : dispatch_pieces<false, 1>(g, pool, s);
         }
         if (blocks_small * 2 > 512) return dispatch_layout<32, 32, 4, true>(g, s);
         return dispatch_layout<32, 32, 8, true>(g, s);

@@ -201,3 +201,47 @@ def test_pooling_in_the_second_layer(d, h, B, cards):
 def test_box_operators_of_a_depth_in_one_launch(d, h, B):
     from . import parity_box as pb
     pb.check_forward_backward(pb.BoxCase(500, 9, d, h, B, 6, 4.0, alpha=0.2, seed=d + h))
+
+
+# both layers over many rows, one tile more than the two lines of the rule, widths that fill no tile and k that fills no block,
+# fewer blocks of k than groups of wavefronts
+@pytest.mark.parametrize("M,d,h", [(897, 132, 260), (1633, 132, 260), (4100, 148, 68), (4513, 36, 68)])
+def test_layers_of_many_rows(M, d, h):
+    import torch
+    from paper_2602_21597_amd import binding
+    rng = np.random.default_rng(M)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)
+    X, W1, W2, b1, b2, mask = f(M, d), f(h, d), f(d, h), f(h), f(d), f(M, h)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W1, b1, W2, b2)]
+    bar = lambda k: 0.1 * 2e-6 * max(1.0, np.sqrt(k) / 8)
+    for backward in (False, True):
+        H, Y, _ = binding.debug_mlp(*dev, mask=torch.from_numpy(mask).cuda(), backward=backward)
+        H, Y = (t.cpu().numpy().astype(np.float64) for t in (H, Y))
+        A, B = (W2, W1) if backward else (W1.T, W2.T)
+        pre = X.astype(np.float64) @ A + (0 if backward else b1)
+        scale = np.abs(X).astype(np.float64) @ np.abs(A) + (0 if backward else np.abs(b1))
+        want = np.where(mask > 0, pre, 0) if backward else np.maximum(pre, 0)
+        assert (np.abs(H - want) / scale).max() < bar(d)
+        add = 0 if backward else b2
+        assert (np.abs(Y - (H @ B + add)) / (np.abs(H) @ np.abs(B) + np.abs(add) + 1e-30)).max() < bar(h)
+
+
+# gathered rows with and without relations, rows kept, pooling and scattered gradients in launches of many rows
+@pytest.mark.parametrize("d,h,B", [(132, 260, 300), (260, 516, 400)])
+def test_operators_over_many_rows(d, h, B):
+    import torch
+    rng = np.random.default_rng(d + B)
+    N, R = 300, 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    trees = []
+    for i in range(2 * B):
+        both = ("i",) + tuple(proj() for _ in range(2 + i % 2))
+        trees.append([both, proj(both), ("i", proj(), ("n", proj(proj())))][i % 3])
+    case = par.Case(N, R, d, h, B, 5, 6.0, seed=d + h, trees=trees, pos=[int(x) for x in rng.integers(0, N, len(trees))])
+    par.check_forward_backward(case)
+    cand = rng.integers(0, N, (case.B, 9)).astype(np.int32)
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    par.assert_close(eng.score(plan, torch.from_numpy(cand).cuda()).cpu().numpy(),
+                     orank.score_candidates(case.qb, cand, om.Model(case.params, case.gamma)), "scores d=%d h=%d" % (d, h))
+    plan.free()
