@@ -130,6 +130,30 @@ def test_filtered_ranks_with_many_answers_of_one_query():
     plan.free()
 
 
+# answers of a query at the edges of a thread's own histogram, of the workgroup's and beyond, an answer listed twice, a table of more than
+# a workgroup's room for undecided entities and a second chunk: the counts of the fp32 pass
+@pytest.mark.parametrize("N,d,edit", [(6001, 32, None), (20002, 8, _outliers), (70001, 4, None)])
+def test_filtered_ranks_by_answers_per_query(N, d, edit):
+    import torch
+    from paper_2602_21597_amd import binding
+    case = par.Case(N, 12, d, 32, 60, 2, 8.0, seed=78, T=2 * N, params_edit=edit)
+    rng = np.random.default_rng(4)
+    lists = [rng.integers(0, N, n) for n in [1, 2, 3, 14, 15, 16, 17, 31, 32, 33, 254, 255, 256, 257, 300] + [5] * 45]
+    for l in lists[1:]:
+        l[-1] = l[0]
+    off = np.concatenate([[0], np.cumsum([len(l) for l in lists])]).astype(np.int32)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.int32)).cuda()
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb)
+        got.append([x.cpu().numpy() for x in eng.rank_answers(plan, dev(off), dev(np.concatenate(lists)))])
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # the fp32 pass: fewer entities than k, one lane's four, a group of lanes, more than a workgroup's lanes; equal distances
 # beyond the list's room; a second chunk
 @pytest.mark.parametrize("N,d,B,edit", [(5, 8, 9, None), (14, 8, 9, None), (1030, 20, 20, None), (4099, 12, 9, None),
