@@ -1304,9 +1304,9 @@ constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the 
 
 // Where a chunk of entity rows lies: in the table (or its bf16 copy), or, with text features, fused
 // into the context's chunk buffer by this call.  sample: there, too, RANK_SAMPLE rows spread over the table (a launch
-// of its own for so few workgroups takes 100 us).
+// of its own for so few workgroups takes 100 us).  grid: rows fused here are also put on it.
 struct ChunkRows { const float* rows; const uint16_t* rows16; const float* sample; };
-int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, bool sample, hipStream_t s, ChunkRows* out) {
+int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, bool sample, const RankFilter* grid, hipStream_t s, ChunkRows* out) {
     const int d = c->cfg.d;
     *out = ChunkRows{c->prm.E.p + (size_t)e0 * d, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) + (size_t)e0 * d : nullptr, nullptr};
     if (c->cfg.d_sem == 0) return NGDB_OK;
@@ -1316,6 +1316,7 @@ int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, bool sample, hipStream_t s, 
         fa.n_seq = cnt; fa.n_rows += RANK_SAMPLE; fa.spread = c->cfg.n_entities / RANK_SAMPLE;
         out->sample = fa.out + (size_t)cnt * d;
     }
+    if (grid) { fa.bits = grid->bits; fa.ldq = grid->lde; fa.words = grid->words; fa.lo = grid->lo; fa.grid = grid->grid; fa.Q = grid->Eq; fa.err = grid->slack; }
     HIPCHK(c, launch_sem_fuse(fa, s));
     out->rows = ptr<float>(c->rank_ef);
     return NGDB_OK;
@@ -1326,11 +1327,12 @@ int rank_filter_space(ngdb_ctx_t* c, int bits, int R, int B, int chunk, RankFilt
     *f = RankFilter{};
     f->d = c->cfg.d; f->bits = bits; f->words = rank_filter_words(f->d, bits);
     f->ldy = (R + 127) / 128 * 128; f->lde = (chunk + 127) / 128 * 128; f->room = RANK_ROOM;
+    f->parts = c->cfg.d_sem > 0 ? sem_fuse_parts(f->d) : 1;
     size_t at = 0;
     auto place = [&](size_t words) { const size_t o = at; at += (words + 63) / 64 * 64; return o; };
     const size_t o_part = place((size_t)32 * f->d), o_lo = place(f->d), o_grid = place(2), o_yq = place((size_t)f->words * f->ldy),
                  o_base = place(2 * (size_t)f->ldy), o_rq = place(f->ldy), o_eq = place((size_t)f->words * f->lde),
-                 o_slack = place(f->lde), o_list = place(bits == 16 ? (size_t)B * f->room : 0),
+                 o_slack = place((size_t)f->parts * f->lde), o_list = place(bits == 16 ? (size_t)B * f->room : 0),
                  o_found = place(bits == 8 ? (size_t)f->ldy * (f->lde / 128) : 0),
                  o_pair = place(bits == 8 ? rank_found_bytes(f->ldy, f->lde) / 4 : 0);
     f->n_counters = B + c->cfg.n_entities / RANK_CHUNK + 32;
@@ -1403,13 +1405,14 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         const int want = !filtered ? chunk : (e0 == 0 ? sample : (int)std::min<int64_t>(chunk, 12ll * e0));
         const int cnt = std::min(want, N - e0);
         ChunkRows er;
-        if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, s, &er)) != NGDB_OK) return rc;
-        if (!filtered || e0 == 0) {
+        const bool rounded = filtered && e0 > 0;
+        if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, rounded ? &f : nullptr, s, &er)) != NGDB_OK) return rc;
+        if (!rounded) {
             HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16));
             HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, s));
             if (filtered && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
         } else {
-            HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
+            if (c->cfg.d_sem == 0) HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_near_tile(f, R, cnt, d_dist, topk, s));
             HIPCHK(c, launch_near_merge(f, i_chunk, act, roots, pl->d_root_off, B, er.rows, er.rows16, e0, cnt, topk, d_dist, d_ids, s));
             only.any = f.overflowed + i_chunk;
@@ -1466,10 +1469,12 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     for (int e0 = 0; e0 < N; e0 += chunk) {
         const int cnt = std::min(chunk, N - e0);
         ChunkRows er;
-        if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, s, &er)) != NGDB_OK) return rc;
+        const bool rounded = filtered && sem && e0 > 0;      // (the first chunk's rows hold the sample that the grid comes from)
+        if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, rounded ? &f : nullptr, s, &er)) != NGDB_OK) return rc;
         if (filtered) {
             if (e0 == 0 && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
-            HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
+            f.parts = rounded ? sem_fuse_parts(d) : 1;
+            if (!rounded) HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_sum_tile(f, R, cnt, reinterpret_cast<uint32_t*>(dist), ld, s));
             HIPCHK(c, launch_count_sure(f, reinterpret_cast<const uint32_t*>(dist), ld, pl->d_root_off, d_ans_off, thr, B, cnt, in_chunk, s));
             HIPCHK(c, launch_count_open(f, e0 / chunk, reinterpret_cast<const uint32_t*>(dist), ld, act, roots, pl->d_root_off, d_ans_off, thr, B, er.rows, er.rows16, in_chunk, total, s));

@@ -101,6 +101,20 @@ __device__ __forceinline__ float sign_unit(float x) {
     return __builtin_amdgcn_fmed3f(__builtin_ldexpf(x, 252), -1.f, 1.f);
 }
 __device__ __forceinline__ float signed_by(float c, float x) { return c * sign_unit(x); }
+// ---- the integer grid of a filtered ranking (rank_filter.hip): a coordinate becomes q = round((x - lo) * inv) within [0, top], the
+// grid point lo + step * q; what the row errs by is summed exactly.
+constexpr float SLACK = 1e-5f;       // of a row's own sums (at most 16 terms a lane, then a tree: 2e-6)
+constexpr int32_t SLACK_CAP = 100000000;      // an error of this or more bounds nothing (a row's parts are added, each capped)
+__device__ __forceinline__ float to_grid(float x, float lo, float step, float inv, float top, float* err) {
+    const float qf = fminf(fmaxf(rintf((x - lo) * inv), 0.f), top);           // (a NaN becomes 0; its error stays NaN)
+    const float on = fmaf(qf, step, lo);                                       // the grid point, itself rounded
+    *err += fabsf(x - on) + fabsf(on) * 6e-8f;
+    return qf;
+}
+__device__ __forceinline__ int32_t slack_steps(float err, float inv) {         // in steps, rounded up
+    const float s = err * (1.f + SLACK) * inv + 2.f;
+    return s < (float)SLACK_CAP ? (int32_t)s : SLACK_CAP;
+}
 // log(1+exp(x)) and 1/(1+exp(-x)) without overflow
 __device__ __forceinline__ float softplus_f(float x) { return fmaxf(x, 0.f) + log1pf(expf(-fabsf(x))); }
 __device__ __forceinline__ float sigmoid_f(float x) {
@@ -401,7 +415,7 @@ struct RankFilter {
     float* base;                     // [2 * ldy] constant of every branch row in a bound from below, from above
     int32_t* row_q;                  // [ldy] its query
     uint32_t* Eq; int lde;           // entity rows of a chunk [words, lde]
-    int32_t* slack;                  // [lde] error of an entity row, in steps
+    int32_t* slack; int parts;       // [parts, lde] error of an entity row, in steps: the sum over the parts
     // top-k: what the tiles of a chunk found, [ldy, tiles] words (zero between chunks) and rank_found_bytes(ldy, lde)
     uint32_t *found, *found_pair;
     // filtered ranks: per query the entities to be computed in fp32 [queries, room], their number.  Both: a
@@ -547,7 +561,14 @@ struct SemFuseArgs {
     int n_rows;
     int d, ds;                  // ds a multiple of 64
     float* out;                 // [n_rows, d]
+    // the rows on the integer grid of a ranking as well (bits: 8, 16, or 0 for not): words of row u at Q[w * ldq + u], the error that
+    // column part c of the row adds at err[c * ldq + u] (sem_fuse_parts(d) parts)
+    int bits = 0, ldq = 0, words = 0;
+    const float *lo = nullptr, *grid = nullptr;
+    uint32_t* Q = nullptr;
+    int32_t* err = nullptr;
 };
+int sem_fuse_parts(int d);
 hipError_t launch_sem_fuse(const SemFuseArgs& a, hipStream_t s);
 // out[m, n] = sum_u G[u, m] * H[ids[u], n] over u < *n_rows_dev
 struct SemWgradArgs {

@@ -37,8 +37,8 @@
 namespace ngdb {
 namespace {
 
-constexpr float SLACK = 1e-5f;       // of a row's own sums (at most 16 terms a lane, then a tree: 2e-6)
 constexpr int UNBOUNDED = INT_MAX / 4;
+__device__ __forceinline__ int32_t slack_of(int32_t sum) { return sum >= SLACK_CAP ? UNBOUNDED : sum; }
 // relative rounding of an fp32 distance: d additions and d subtractions in sequence
 inline float rounding_of(int d) { return (float)(d + 16) * 6e-8f; }
 constexpr int SAMPLE_SLABS = 16;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(1024) void make_grid_kernel(const float* __restrict
 // Q[w * ld + i]: word w of row i, 32 / BITS consecutive coordinates each, words beyond the row zero (on
 // both sides of a sum: they add nothing).  A wavefront takes 16 rows of the workgroup's 64, one after
 // the other, a float4 per lane; the words pass through LDS so that they leave 64 rows at a time.
-// ENT: slack[i] = the row's error in steps, rounded up (UNBOUNDED where it is not finite).
+// ENT: slack[i] = the row's error in steps, rounded up (SLACK_CAP where it is not finite or larger).
 // !ENT (branch rows, ids): base[i] = excess - err and base[ld + i] = excess + err (for bounds from
 // below and from above), and row_q[i] = the query the row belongs to.
 template <int BITS, bool ENT, int RW>
@@ -147,17 +147,17 @@ __global__ __launch_bounds__(256) void quantise_kernel(const float* __restrict__
             const float4 v4 = X16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(X16 + at)) : *reinterpret_cast<const float4*>(X + at);
             const float v[4] = {v4.x, v4.y, v4.z, v4.w};
             uint32_t w[2] = {0u, 0u};
-            float er = 0.f, ex = 0.f;
+            float er = 0.f, ex = 0.f, dropped = 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float t = (v[j] - l[j]) * inv;
-                const float qf = fminf(fmaxf(rintf(t), 0.f), TOP);       // (a NaN becomes 0; its error stays NaN)
-                const float on = fmaf(qf, step, l[j]);                     // the grid point
+                float qf;
                 if (ENT) {
-                    er += fabsf(v[j] - on) + fabsf(on) * 6e-8f;
+                    qf = to_grid(v[j], l[j], step, inv, TOP, &er);
                 } else {
                     const float cl = fminf(fmaxf(v[j], l[j]), fmaf(TOP, step, l[j]));
                     ex += fabsf(v[j] - cl);
+                    qf = to_grid(v[j], l[j], step, inv, TOP, &dropped);
+                    const float on = fmaf(qf, step, l[j]);
                     er += fabsf(cl - on) + fabsf(on) * 6e-8f + 0.f * v[j];     // (not a number where v is infinite or none)
                 }
                 const uint32_t qi = (uint32_t)qf;
@@ -182,8 +182,7 @@ __global__ __launch_bounds__(256) void quantise_kernel(const float* __restrict__
         const int i = i0 + wave * RW + r;
         if (lane == 0 && i < n_rows) {
             if (ENT) {
-                const float s = e * (1.f + SLACK) * inv + 2.f;
-                slack[i] = s < 1e8f ? (int32_t)s : UNBOUNDED;
+                slack[i] = slack_steps(e, inv);
             } else {
                 base[i] = x * (1.f - SLACK) - e * (1.f + SLACK);
                 base[ld + i] = x * (1.f + SLACK) + e * (1.f + SLACK);
@@ -278,7 +277,7 @@ struct NearArgs {
     const float *base, *grid, *best;
     const int32_t *row_q, *slack;
     uint32_t *found, *found_pair;
-    int ldy, lde, n_rows, n_ent, words, k;
+    int ldy, lde, n_rows, n_ent, words, k, parts;
     float rounding;
 };
 // Pairs that qualify are few (a per cent in the first chunk, one in 10^5 later).  They leave a tile as
@@ -306,7 +305,9 @@ __device__ __forceinline__ void near_tile(const NearArgs& g, int r0, int e0, Nea
     for (int j = 0; j < 8; ++j) {
         const int e = e0 + (j >> 2) * 64 + tx * 4 + (j & 3);
         // the entity's error comes off the sum here; entities past the end never qualify
-        const uint32_t start = e < g.n_ent ? (uint32_t)-g.slack[e] : (uint32_t)(INT_MAX / 2);
+        int32_t sl = 0;
+        for (int p = 0; p < g.parts; ++p) sl += g.slack[(size_t)p * g.lde + min(e, g.n_ent - 1)];
+        const uint32_t start = e < g.n_ent ? (uint32_t)-slack_of(sl) : (uint32_t)(INT_MAX / 2);
 #pragma unroll
         for (int i = 0; i < RPL; ++i) acc[i][j] = start;
     }
@@ -495,7 +496,7 @@ struct MergeArgs {
     int32_t *count, *overflowed;
     float* out_dist;
     int32_t* out_ids;
-    int n_tx, ent_base, d, k, room, ldb;
+    int n_tx, ent_base, d, k, room, ldb, lde, parts;
     float rounding;
 };
 // One workgroup per query: gathers what the tiles left for the query's rows (clearing their words for
@@ -573,7 +574,9 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         float both = 0.f;
         for (int r = r_lo; r < r_hi; ++r) both = fmaxf(both, g.base[g.ldb + r] - g.base[r]);
         auto upper = [&](int x) {
-            const int32_t sl = g.slack[list[x]];
+            int32_t sum = 0;
+            for (int p = 0; p < g.parts; ++p) sum += g.slack[(size_t)p * g.lde + list[x]];
+            const int32_t sl = slack_of(sum);
             return sl == UNBOUNDED || lower[x] == -INFINITY ? INFINITY : (lower[x] + both + (float)(2 * sl + 8) * step) * (1.f + g.rounding);
         };
         for (int x = t; x < n; x += MERGE_T) hi_min = fminf(hi_min, upper(x));
@@ -730,8 +733,9 @@ __global__ __launch_bounds__(64) void answer_distance_kernel(const float* __rest
 // constants; every caller gets the same bits.
 struct Bounds { float lo, hi; };
 __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step, float b_lo, float b_hi, float rounding) {
+    sl = min(sl, SLACK_CAP);
     const float lo = fmaf((float)((int32_t)sum - sl), step, b_lo), hi = fmaf((float)((int32_t)sum + sl), step, b_hi);
-    const bool none = sl == UNBOUNDED;
+    const bool none = sl == SLACK_CAP;
     return {none ? -INFINITY : fmaf(-rounding, fabsf(lo), lo), none ? INFINITY : fmaf(rounding, fabsf(hi), hi)};
 }
 
@@ -746,7 +750,7 @@ __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step
 // the sums takes 60.
 constexpr int EPT = 8, SLAB = EPT * 256, ANS_LDS = 255, ANS_OWN = 15, OPEN_KEPT = 1024;
 static_assert((65536 / SLAB) * EPT < 65536, "own counters of a chunk fit 16 bits");
-__global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restrict__ sums, int ld, const int32_t* __restrict__ slack,
+__global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restrict__ sums, int ld, const int32_t* __restrict__ slack, int parts, int lde,
                                                          const float* __restrict__ base, int ldb, const float* __restrict__ grid,
                                                          const int32_t* __restrict__ root_off, const int32_t* __restrict__ ans_off,
                                                          const float* __restrict__ thr, int n_ent, float rounding,
@@ -795,7 +799,11 @@ __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restr
             for (int h = 0; h < EPT; h += 4) {       // (rows and errors are padded to groups of four)
                 const int e = min(e_lo + h * 256 + t * 4, (e_hi - 1) & ~3);
                 const uint4 sum = *reinterpret_cast<const uint4*>(sums + (size_t)r * ld + e);
-                const int4 sl = *reinterpret_cast<const int4*>(slack + e);
+                int4 sl = *reinterpret_cast<const int4*>(slack + e);
+                for (int p = 1; p < parts; ++p) {
+                    const int4 x = *reinterpret_cast<const int4*>(slack + (size_t)p * lde + e);
+                    sl.x += x.x; sl.y += x.y; sl.z += x.z; sl.w += x.w;
+                }
                 const Bounds b[4] = {bounds_of(sum.x, sl.x, step, b_lo, b_hi, rounding), bounds_of(sum.y, sl.y, step, b_lo, b_hi, rounding),
                                      bounds_of(sum.z, sl.z, step, b_lo, b_hi, rounding), bounds_of(sum.w, sl.w, step, b_lo, b_hi, rounding)};
 #pragma unroll
@@ -894,7 +902,7 @@ __global__ __launch_bounds__(256) void count_open_kernel(const float* __restrict
                                                          const int32_t* __restrict__ root_off, const int32_t* __restrict__ ans_off,
                                                          const float* __restrict__ thr, const float* __restrict__ E,
                                                          const uint16_t* __restrict__ E16, int d, const uint32_t* __restrict__ sums,
-                                                         int ld, const int32_t* __restrict__ slack, const float* __restrict__ base,
+                                                         int ld, const int32_t* __restrict__ slack, int parts, int lde, const float* __restrict__ base,
                                                          int ldb, const float* __restrict__ grid, float rounding,
                                                          const int32_t* __restrict__ list, const int32_t* __restrict__ count, int room,
                                                          int32_t* __restrict__ overflowed, int32_t* __restrict__ chunk_count,
@@ -923,9 +931,11 @@ __global__ __launch_bounds__(256) void count_open_kernel(const float* __restrict
         for (int at = (wave * OPEN_PARTS + part) * 64; at < n; at += 256 * OPEN_PARTS) {
             const bool live = at + lane < n;
             const int32_t e = live ? list[(size_t)q * room + at + lane] : 0;
+            int32_t sl = 0;
+            for (int p = 0; p < parts; ++p) sl += slack[(size_t)p * lde + e];
             float vhi = INFINITY;
             for (int r = r_lo; r < r_hi; ++r)
-                vhi = fminf(vhi, bounds_of(sums[(size_t)r * ld + e], slack[e], step, base[r], base[ldb + r], rounding).hi);
+                vhi = fminf(vhi, bounds_of(sums[(size_t)r * ld + e], sl, step, base[r], base[ldb + r], rounding).hi);
             const float v = exact_distance<B16, 32, 2>(act, row_ids, r_lo, r_hi, E, E16, e, d, slab[wave]);
             for (int a = 0; a < na; ++a) {
                 const float limit = thr[a0 + a];
@@ -982,7 +992,7 @@ hipError_t launch_rank_entities(const RankFilter& f, const float* E, const uint1
 hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const float* best, int k, hipStream_t s) {
     if (n_rows <= 0 || n_ent <= 0) return hipSuccess;
     const NearArgs g{f.Yq, f.Eq, f.base, f.grid, best, f.row_q, f.slack, f.found, f.found_pair,
-                     f.ldy, f.lde, n_rows, n_ent, f.words, k, rounding_of(f.d)};
+                     f.ldy, f.lde, n_rows, n_ent, f.words, k, f.parts, rounding_of(f.d)};
     hipLaunchKernelGGL(near_tile_kernel, dim3((n_ent + 127) / 128, (n_rows + 127) / 128), dim3(256), 0, s, g);
     return hipGetLastError();
 }
@@ -992,7 +1002,7 @@ hipError_t launch_near_merge(const RankFilter& f, int chunk, const float* act, c
                              int32_t* out_ids, hipStream_t s) {
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
     const MergeArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, f.found, f.found_pair, f.count,
-                      f.overflowed + chunk, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, rounding_of(f.d)};
+                      f.overflowed + chunk, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, f.lde, f.parts, rounding_of(f.d)};
     if (E16) hipLaunchKernelGGL((near_merge_kernel<true>), dim3(n_queries), dim3(MERGE_T), 0, s, g);
     else hipLaunchKernelGGL((near_merge_kernel<false>), dim3(n_queries), dim3(MERGE_T), 0, s, g);
     return hipGetLastError();
@@ -1024,7 +1034,7 @@ hipError_t launch_count_sure(const RankFilter& f, const uint32_t* sums, int ld, 
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
     if (n_queries > 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(count_sure_kernel, dim3(std::min((n_ent + SLAB - 1) / SLAB, std::max(1, 4096 / n_queries)), n_queries), dim3(256), 0, s, sums, ld,
-                       (const int32_t*)f.slack, (const float*)f.base, f.ldy, (const float*)f.grid, root_off, ans_off, thr, n_ent,
+                       (const int32_t*)f.slack, f.parts, f.lde, (const float*)f.base, f.ldy, (const float*)f.grid, root_off, ans_off, thr, n_ent,
                        rounding_of(f.d), chunk_count, f.list, f.count, f.room);
     return hipGetLastError();
 }
@@ -1036,7 +1046,7 @@ hipError_t launch_count_open(const RankFilter& f, int chunk, const uint32_t* sum
     if (n_queries > 65535) return hipErrorInvalidValue;
 #define NGDB_OPEN(B16)                                                                                                       \
     hipLaunchKernelGGL((count_open_kernel<B16>), dim3(OPEN_PARTS, n_queries), dim3(256), 0, s, act, row_ids, root_off, ans_off, thr, E, E16, f.d, \
-                       sums, ld, (const int32_t*)f.slack, (const float*)f.base, f.ldy, (const float*)f.grid, rounding_of(f.d),   \
+                       sums, ld, (const int32_t*)f.slack, f.parts, f.lde, (const float*)f.base, f.ldy, (const float*)f.grid, rounding_of(f.d),   \
                        (const int32_t*)f.list, (const int32_t*)f.count, f.room, f.overflowed + chunk, chunk_count, total)
     if (E16) NGDB_OPEN(true);
     else NGDB_OPEN(false);

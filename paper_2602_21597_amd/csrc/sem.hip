@@ -97,6 +97,9 @@ constexpr int SF_BU = 256, SF_N = 208, SF_NBLK = SF_N / 16, SF_KS = 64;
 constexpr int SF_NW = 8;                                      // wavefronts: 32 rows x 208 coordinates each (104 accumulator registers)
 constexpr int SF_HL = SF_BU / 8, SF_WL = 32;                  // loads per stage: feature rows, weight rows (26 used)
 constexpr int SF_STAGE = (SF_HL + SF_WL) * 1024, SF_NB = 2, SF_PER_WAVE = (SF_HL + SF_WL) / SF_NW;
+// BITS: the rows also go onto the integer grid of a ranking, from the accumulators.  For 65 536 rows of 400 coordinates and 1024 feature
+// values 86 -> 99 us; the pass that read the rows again took 27.
+template <int BITS>
 __global__ __launch_bounds__(SF_NW * 64) void sem_fuse_kernel(const SemFuseArgs a) {
     __shared__ __attribute__((aligned(1024))) unsigned char tiles[SF_NB * SF_STAGE];
     const int n_rows = a.n_rows_dev ? min(*a.n_rows_dev, a.n_rows) : a.n_rows;
@@ -194,17 +197,41 @@ __global__ __launch_bounds__(SF_NW * 64) void sem_fuse_kernel(const SemFuseArgs 
         issue(s + 2);
     }
     wait_vm<0>();                            // the loads issued past the end land before the workgroup gives up its LDS
+    const float step = BITS ? a.grid[0] : 0.f, inv = BITS ? a.grid[1] : 0.f;
+    constexpr float TOP = BITS == 8 ? 255.f : 65535.f;
+    float er[2] = {0.f, 0.f};
 #pragma unroll
-    for (int bu = 0; bu < 2; ++bu) {
-        const int u = u0 + wave * 32 + bu * 16 + (lane & 15);
-        if (u >= n_rows) continue;
-        float* orow = a.out + (size_t)u * a.d;
+    for (int bn = 0; bn < SF_NBLK; ++bn) {
+        const int n = n0 + bn * 16 + (lane >> 4) * 4;
+        float4 lo = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (BITS) lo = *reinterpret_cast<const float4*>(a.lo + min(n, a.d - 4));
 #pragma unroll
-        for (int bn = 0; bn < SF_NBLK; ++bn) {
-            const int n = n0 + bn * 16 + (lane >> 4) * 4;
-            if (n >= a.d) continue;
-            *reinterpret_cast<float4*>(orow + n) =
-                make_float4(acc[bu][bn][0], acc[bu][bn][1], acc[bu][bn][2], acc[bu][bn][3]);
+        for (int bu = 0; bu < 2; ++bu) {
+            const int u = u0 + wave * 32 + bu * 16 + (lane & 15);
+            if (u >= n_rows) continue;
+            const float4 v = make_float4(acc[bu][bn][0], acc[bu][bn][1], acc[bu][bn][2], acc[bu][bn][3]);
+            if (n < a.d) *reinterpret_cast<float4*>(a.out + (size_t)u * a.d + n) = v;
+            if (!BITS || n * BITS >= a.words * 32) continue;
+            // (words past the last coordinate are zero)
+            float dropped = 0.f, *e = n < a.d ? &er[bu] : &dropped;
+            uint32_t q[4] = {(uint32_t)to_grid(v.x, lo.x, step, inv, TOP, e), (uint32_t)to_grid(v.y, lo.y, step, inv, TOP, e),
+                             (uint32_t)to_grid(v.z, lo.z, step, inv, TOP, e), (uint32_t)to_grid(v.w, lo.w, step, inv, TOP, e)};
+            if (n >= a.d) q[0] = q[1] = q[2] = q[3] = 0u;
+            if (BITS == 8) {
+                a.Q[(size_t)(n >> 2) * a.ldq + u] = q[0] | q[1] << 8 | q[2] << 16 | q[3] << 24;
+            } else {
+                a.Q[(size_t)(n >> 1) * a.ldq + u] = q[0] | q[1] << 16;
+                a.Q[(size_t)((n >> 1) + 1) * a.ldq + u] = q[2] | q[3] << 16;
+            }
+        }
+    }
+    if (BITS) {
+#pragma unroll
+        for (int bu = 0; bu < 2; ++bu) {
+            const int u = u0 + wave * 32 + bu * 16 + (lane & 15);
+            float e = er[bu] + __shfl_xor(er[bu], 16, 64);
+            e += __shfl_xor(e, 32, 64);
+            if (lane < 16 && u < n_rows) a.err[(size_t)(n0 / SF_N) * a.ldq + u] = slack_steps(e, inv);
         }
     }
 }
@@ -413,14 +440,20 @@ hipError_t launch_translate_refs(const int32_t* in_ref, const int32_t* in_gslot,
     return hipGetLastError();
 }
 
+int sem_fuse_parts(int d) { return (d + SF_N - 1) / SF_N; }
+
 hipError_t launch_sem_fuse(const SemFuseArgs& a, hipStream_t s) {
     if (a.n_rows <= 0) return hipSuccess;
+    if (a.bits && (a.ids || a.n_rows > a.ldq)) return hipErrorInvalidValue;
     if (a.ds <= 0 || a.ds % KS || a.d % 4) return hipErrorInvalidValue;
     const int64_t u_tiles = (a.n_rows + SF_BU - 1) / SF_BU;
     const int64_t n_tiles = (a.d + SF_N - 1) / SF_N;
     const int64_t blocks = ((u_tiles + 7) / 8) * 8 * n_tiles;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(sem_fuse_kernel, dim3((unsigned)blocks), dim3(SF_NW * 64), 0, s, a);
+    const dim3 grid((unsigned)blocks), block(SF_NW * 64);
+    if (a.bits == 8) hipLaunchKernelGGL((sem_fuse_kernel<8>), grid, block, 0, s, a);
+    else if (a.bits == 16) hipLaunchKernelGGL((sem_fuse_kernel<16>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sem_fuse_kernel<0>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

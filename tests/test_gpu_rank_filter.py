@@ -154,6 +154,29 @@ def test_filtered_ranks_by_answers_per_query(N, d, edit):
         np.testing.assert_array_equal(a, b)
 
 
+# text features: rows rounded as they are fused: two words, a column part, two words more, two parts; errors
+# that only a part of a row has or that bound nothing; a second chunk of the filtered ranks: the results of the fp32 pass
+@pytest.mark.parametrize("N,d,edit", [(9001, 8, None), (6001, 208, _outliers), (6001, 216, _shifted), (9001, 400, _far_group(700.0)),
+                                      (70001, 24, _outliers)])
+def test_rows_rounded_as_they_are_fused(N, d, edit):
+    import torch
+    from paper_2602_21597_amd import binding
+    case = par.Case(N, 12, d, 32, 40, 2, 8.0, mix={"1p": 0.5, "2i": 0.3, "2u": 0.2}, seed=79, T=2 * N, d_sem=64, params_edit=edit)
+    off = np.arange(0, 3 * case.B + 1, 3).astype(np.int32)
+    answers = np.random.default_rng(5).integers(0, N, 3 * case.B)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.int32)).cuda()
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb)
+        results = [x for k in (1, 10) for x in eng.rank_all(plan, k)] + list(eng.rank_answers(plan, dev(off), dev(answers)))
+        got.append([x.cpu().numpy() for x in results])
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # the fp32 pass: fewer entities than k, one lane's four, a group of lanes, more than a workgroup's lanes; equal distances
 # beyond the list's room; a second chunk
 @pytest.mark.parametrize("N,d,B,edit", [(5, 8, 9, None), (14, 8, 9, None), (1030, 20, 20, None), (4099, 12, 9, None),
