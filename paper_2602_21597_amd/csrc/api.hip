@@ -94,6 +94,7 @@ struct ngdb_ctx_s {
     int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
     const int32_t* rank_overflowed = nullptr;    // the last ranking's marks per chunk (null: no filter)
     int rank_chunks = 0;
+    int near_most = INT32_MAX;     // entities of a filtered chunk for which there was memory
     // The hidden activations of one depth (forward) or their gradients (backward) once more as bf16
     // pieces in tile order: written by the first launch of a layer pair, read as A operand by the
     // second, then free again.  Only steps whose launches use the small tile get that far.
@@ -1299,6 +1300,12 @@ int presize(ngdb_ctx_t* c) {
 
 // ---- all-entity passes: the entity rows chunk by chunk
 constexpr int RANK_CHUNK = 1 << 16;
+// A filtered top-k takes chunks of up to NEAR_CHUNK: what a chunk costs beside its sums (merging, the launches of an fp32 pass that
+// finds nothing to do) is 50 us whatever its size.  5 million fused entities x 1024 queries 28.5 ms in chunks of 65 536, 27.7 of twice
+// that, 26.6 of four times that; a table of 2.5 million x 512 queries 7.7, 7.06, 6.8.  NEAR_DIST bounds the distances that the fp32 pass
+// of a chunk would write (the memory it has to have at hand).
+constexpr int NEAR_CHUNK = 1 << 18;
+constexpr int64_t NEAR_DIST = 1 << 29;
 constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k); rows the integer grid is made from
 constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filter may leave undecided
 
@@ -1386,15 +1393,22 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const float* act = ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
     const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
-    const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
-    float* dist = nullptr;
-    int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
-    if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, ((size_t)chunk + RANK_SAMPLE) * d * sizeof(float), true);
+    int most = RANK_CHUNK, chunk, ld, rc;
+    while (filtered && most < std::min(NEAR_CHUNK, c->near_most) && 2ll * most * R <= NEAR_DIST) most *= 2;
     RankFilter f{};
-    if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 8, R, B, chunk, &f);
+    for (;; most /= 2) {
+        chunk = std::min(N, most);
+        ld = (chunk + 3) & ~3;
+        rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
+        if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, ((size_t)chunk + RANK_SAMPLE) * d * sizeof(float), true);
+        if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 8, R, B, chunk, &f);
+        if (rc != NGDB_ERR_OOM || most == RANK_CHUNK) break;
+        (void)hipGetLastError();             // smaller chunks need less
+        c->near_most = most / 2;
+    }
     c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
     if (rc != NGDB_OK) return rc;
-    dist = ptr<float>(c->rank_dist);
+    float* dist = ptr<float>(c->rank_dist);
     Overflowed only{f.row_q, f.count, f.room, f.overflowed};
     Timed tm(c, NGDB_TK_SCORE, s);
     // filtered: the sample's k-th distance lets k / sample of the first chunk pass, and chunks grow with what has

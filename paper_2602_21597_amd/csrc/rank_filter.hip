@@ -506,14 +506,15 @@ struct MergeArgs {
 // can lie below that is computed, a tenth.  Nearly all of these turn out farther than the k-th so far;
 // the few that are not are collected and inserted by the first wavefront into the list its lanes
 // hold.  A query with more than ROOM entities, or a crowded tile, is marked (count > room,
-// *overflowed) for the fp32 pass of the chunk.
-constexpr int ROOM = 4096, MERGE_T = 128, BINS = 256;
+// *overflowed) for the fp32 pass of the chunk.  ROOM leaves LDS for four workgroups a compute unit, all of 1024 queries at once.
+constexpr int ROOM = 3584, MERGE_T = 128, BINS = 256;
 template <bool B16>
 __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) {
     __shared__ __attribute__((aligned(16))) float slab[MERGE_T / 64][64 * slab_ld(16)];
-    __shared__ uint16_t list[ROOM];
+    __shared__ int32_t list[ROOM];
     __shared__ float lower[ROOM];
-    __shared__ int32_t hist[BINS];
+    static_assert(BINS * sizeof(int32_t) <= sizeof(slab), "room for the histogram");
+    int32_t* hist = reinterpret_cast<int32_t*>(&slab[0][0]);         // (done with before the first distances)
     __shared__ float sd[MERGE_T], best_hi[MERGE_T / 64];
     __shared__ int32_t si[MERGE_T];
     __shared__ int32_t n_list, n_near, n_new, crowded;
@@ -540,7 +541,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
             const int n = w & 0xFF, from = w >> 8, at = atomicAdd(&n_list, n);
             for (int i = 0; i < n && at + i < ROOM; ++i) {
                 const uint32_t p = pairs[(size_t)x * FOUND + from + i];
-                list[at + i] = (uint16_t)(x * 128 + (p & 127));
+                list[at + i] = (int32_t)(x * 128 + (p & 127));
                 // (a sum that did not fit its bits bounds nothing)
                 lower[at + i] = p >> 7 ? (float)((int32_t)(p >> 7) - SUM_BIAS - 4) * step + b_lo : -INFINITY;
             }
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         for (int base = 0; base < n; base += MERGE_T) {
             const int x = base + t;
             const bool keep = x < n && !(lower[x] > most);
-            const uint16_t e = x < n ? list[x] : 0;
+            const int32_t e = x < n ? list[x] : 0;
             __syncthreads();
             const unsigned long long m = __ballot(keep);
             int at = 0;

@@ -154,6 +154,23 @@ def test_filtered_ranks_by_answers_per_query(N, d, edit):
         np.testing.assert_array_equal(a, b)
 
 
+# chunks of more than 65 536 entities, the last one ragged: their lists, and their fp32 pass where they overflow
+@pytest.mark.parametrize("N,edit,kw", [(320011, None, {}), (288800, _first_rows_far, {}), (290001, None, dict(d_sem=64))])
+def test_large_chunks(N, edit, kw):
+    from paper_2602_21597_amd import binding
+    case = par.Case(N, 12, 8, 32, 24, 2, 8.0, seed=80, T=N, params_edit=edit, **kw)
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb)
+        got.append([x.cpu().numpy() for k in (1, 10) for x in eng.rank_all(plan, k)])
+        assert (binding.lib().ngdb_debug_rank_overflows(eng.ctx) > 0) == (limit == 0 and edit is not None)
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # text features: rows rounded as they are fused: two words, a column part, two words more, two parts; errors
 # that only a part of a row has or that bound nothing; a second chunk of the filtered ranks: the results of the fp32 pass
 @pytest.mark.parametrize("N,d,edit", [(9001, 8, None), (6001, 208, _outliers), (6001, 216, _shifted), (9001, 400, _far_group(700.0)),
