@@ -236,6 +236,189 @@ __global__ __launch_bounds__(SF_NW * 64) void sem_fuse_kernel(const SemFuseArgs 
     }
 }
 
+// The same, for rows that go nowhere else and at least ST_FROM feature values: one workgroup a compute unit takes tile after tile, and
+// the memory is asked for something all the time.  Four wavefronts of 64 rows x 208 coordinates: an operand fetched from LDS feeds twice
+// the products (17 instead of 30 KB a wavefront and 104 products), and with one wavefront a SIMD all of its registers are there, 208
+// for the accumulators and two sets of operands, one being multiplied while the other is fetched.  Feature rows are two stages ahead
+// (they come from HBM; a wavefront fetches and reads its own), weight rows one (from L2); the last stages of a tile request the first
+// ones of the next, and each block of results leaves just before the next tile's structural rows are requested into its registers.
+// 262 144 rows of 400 coordinates and 1024 values 421 -> 366 us (floor at the rate of a copy 281), 20 000 x 128 x 512 25.5 -> 23.5,
+// 65 536 x 632 x 256 108 -> 104; but x 424 x 192 62.2 and 63.6, x 48 x 128 13.8 and 15.0.  Rows that are also put on a
+// ranking's grid stay with the kernel above: this one takes 335 instead of 393 us for 262 144 of them, but the integer sums that
+// follow, at the full rate of the vector units, then run at a lower clock: 1035 instead of 907 us, 28.0 instead of 26.5 ms a pass.
+constexpr int ST_FROM = 256;
+constexpr int ST_NW = 4, ST_RB = SF_BU / ST_NW / 16;          // wavefronts; row blocks of each
+constexpr int ST_HL = SF_BU / 8 / ST_NW, ST_WL = 7;           // loads a wavefront and stage: its own feature rows, a quarter of the weight rows (26 used)
+constexpr int ST_HB = SF_BU * 128, ST_WB = ST_NW * ST_WL * 1024, ST_HS = 3, ST_WS = 2;       // bytes of a stage, stages
+constexpr int ST_WG = 256;
+static_assert(ST_FROM >= ST_HS * SF_KS, "a tile has all the stages that are requested ahead");
+__global__ __launch_bounds__(ST_NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void sem_stream_kernel(const SemFuseArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char tiles[ST_HS * ST_HB + ST_WS * ST_WB];
+    const int n_rows = a.n_rows_dev ? min(*a.n_rows_dev, a.n_rows) : a.n_rows;
+    const int n_tiles = (a.d + SF_N - 1) / SF_N;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // tile t of a die is coordinate tile t % n_tiles of its row tile t / n_tiles (side by side on one die: one L2)
+    const int die = blockIdx.x & 7, t_step = gridDim.x >> 3;
+    auto rows_at = [&](int tile) { return (tile / n_tiles * 8 + die) * SF_BU; };
+    auto cols_at = [&](int tile) { return tile % n_tiles * SF_N; };
+    int t = blockIdx.x >> 3;
+    if (rows_at(t) >= n_rows) return;
+
+    // entities of this lane's rows of a tile (rows past the end: the last row's): feature rows it fetches, rows of its accumulator
+    // blocks.  The row numbers are read unconditionally (from a valid address when the rows are no list).
+    const bool listed = a.ids != nullptr;
+    const int32_t* id_src = listed ? a.ids : reinterpret_cast<const int32_t*>(a.E);
+    auto row_of = [&](int u0, int q) {
+        const int r = q < ST_HL ? q * 8 + (lane >> 3) : (q - ST_HL) * 16 + (lane & 15);
+        return min(u0 + wave * 64 + r, n_rows - 1);
+    };
+    int32_t ent[ST_HL + ST_RB];              // of the tile that is requested next
+    auto read_ids = [&](int u0) {
+#pragma unroll
+        for (int q = 0; q < ST_HL + ST_RB; ++q) ent[q] = id_src[listed ? row_of(u0, q) : 0];
+    };
+    auto take_ids = [&](int u0) {
+#pragma unroll
+        for (int q = 0; q < ST_HL + ST_RB; ++q) {
+            const int r = row_of(u0, q);
+            if (!listed) ent[q] = r < a.n_seq ? (int32_t)a.id_base + r : (r - a.n_seq) * a.spread;
+        }
+    };
+    // sources of this lane's loads at k = 0 (row r of the area = 8 * load + lane / 8, stored column lane % 8)
+    const uint16_t* hsrc[ST_HL];
+    uint32_t wsrc[ST_WL];
+    auto point_h = [&]() {
+#pragma unroll
+        for (int q = 0; q < ST_HL; ++q) hsrc[q] = a.H + (int64_t)ent[q] * a.ds + ((lane & 7) ^ ((q * 4 + (lane >> 4)) & 7)) * 8;
+    };
+    auto point_w = [&](int n0) {
+#pragma unroll
+        for (int q = 0; q < ST_WL; ++q) {
+            const int r = (wave * ST_WL + q) * 8 + (lane >> 3);      // (rows past the tile's 208: padding, the last row again)
+            wsrc[q] = ((uint32_t)min(n0 + min(r, SF_N - 1), a.d - 1) * (uint32_t)a.ds + (uint32_t)((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2;
+        }
+    };
+    // The accumulators start from the structural rows: a lane holds, per block, 4 consecutive coordinates of one row (clamped addresses;
+    // rows and coordinates past the end are never stored).  They are loaded straight into the accumulator registers, behind the
+    // compiler's back, and are there after wait_vm<0>.  Nothing may touch them in between: the loads are in and out operands of the
+    // same registers, all 208 of them are taken by the accumulators, and no branch over single loads parts them.
+    floatx4 acc[ST_RB][SF_NBLK];
+    auto structural = [&](int bu, int n0) {
+        const float* row = a.E + (int64_t)ent[ST_HL + bu] * a.d;
+#pragma unroll
+        for (int bn = 0; bn < SF_NBLK; ++bn) {
+            const float* from = row + min(n0 + bn * 16 + (lane >> 4) * 4, a.d - 4);
+            asm volatile("global_load_dwordx4 %0, %1, off" : "+a"(acc[bu][bn]) : "v"(from) : "memory");
+        }
+    };
+    const uint32_t h_at = lds_addr(tiles) + wave * (ST_HL * 1024), w_at = lds_addr(tiles) + ST_HS * ST_HB + wave * (ST_WL * 1024);
+    const int stages = a.ds / SF_KS;
+    auto issue_h = [&](int k, int buf) {
+#pragma unroll
+        for (int q = 0; q < ST_HL; ++q) lds_load16(hsrc[q] + k * SF_KS, h_at + (uint32_t)(buf * ST_HB + q * 1024));
+    };
+    auto issue_w = [&](int k, int buf) {
+#pragma unroll
+        for (int q = 0; q < ST_WL; ++q) lds_load16_at(a.Wb + k * SF_KS, wsrc[q], w_at + (uint32_t)(buf * ST_WB + q * 1024));
+    };
+    // operand fetch: row R = 16 b + lane % 16 of an area, columns 4 h + lane / 16 (h = which half of the stage's k)
+    const int ri = lane & 15;
+    int frag_at[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        frag_at[h] = (ri >> 3) * 1024 + (ri & 7) * 128 + (((4 * h + (lane >> 4)) ^ ((ri >> 1) & 7))) * 16;
+    constexpr int FETCHES = ST_RB + SF_NBLK, PRODUCTS = ST_RB * SF_NBLK;
+    struct Operands { bf16x8 f[FETCHES]; };
+    auto fetch = [&](Operands& o, int hbuf, int wbuf, int h, int i) {
+        const unsigned char* at = tiles + frag_at[h] + (i < ST_RB ? hbuf * ST_HB + wave * (ST_HL * 1024) + i * 2048 : ST_HS * ST_HB + wbuf * ST_WB + (i - ST_RB) * 2048);
+        o.f[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at));
+    };
+    // (the accumulators stay where they are: with the builtin the compiler copies 200 and more of them about in every stage)
+    auto product = [&](const Operands& o, int m) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[m % ST_RB][m / ST_RB]) : "v"(o.f[ST_RB + m / ST_RB]), "v"(o.f[m % ST_RB]));
+    };
+
+    int u0 = rows_at(t), n0 = cols_at(t), hbuf = 0, wbuf = 0;
+#pragma unroll
+    for (int bu = 0; bu < ST_RB; ++bu)
+#pragma unroll
+        for (int bn = 0; bn < SF_NBLK; ++bn) acc[bu][bn] = floatx4{0.f, 0.f, 0.f, 0.f};
+    read_ids(u0);
+    take_ids(u0);
+#pragma unroll
+    for (int bu = 0; bu < ST_RB; ++bu) structural(bu, n0);
+    point_h();
+    point_w(n0);
+    issue_h(0, 0);
+    issue_w(0, 0);
+    issue_h(1, 1);
+    issue_w(1, 1);
+    issue_h(2, 2);
+    for (;;) {
+        const int t_next = t + t_step, u_next = rows_at(t_next), n_next = cols_at(t_next);
+        const bool more = u_next < n_rows;
+        if (more) read_ids(u_next);
+        wait_vm<0>();
+        if (more) take_ids(u_next);
+        __syncthreads();
+        Operands o0, o1;
+#pragma unroll
+        for (int i = 0; i < FETCHES; ++i) fetch(o0, hbuf, wbuf, 0, i);
+        int hk = min(ST_HS, stages - 1), wk = ST_WS;          // stages to be requested next
+        for (int s = 0; s < stages; ++s) {
+            const int hnext = hbuf == ST_HS - 1 ? 0 : hbuf + 1;
+#pragma unroll
+            for (int m = 0; m < PRODUCTS; ++m) {
+                product(o0, m);
+                if (m % 2 == 0 && m / 2 < FETCHES) fetch(o1, hbuf, wbuf, 1, m / 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // the last stages request the next tile's first ones (without one, the last stage again: nobody reads it)
+            if (more && s + ST_HS == stages) { point_h(); hk = 0; }
+            if (more && s + ST_WS == stages) { point_w(n_next); wk = 0; }
+            wait_vm<ST_HL>();                // all but the rows of the stage after the next: the next one is in LDS
+            wait_lds();                      // ... and this one in registers,
+            __syncthreads();                 // ... every wavefront's part
+            const uint16_t* w_from = a.Wb + wk * SF_KS;
+            const uint32_t w_to = w_at + (uint32_t)(wbuf * ST_WB), h_to = h_at + (uint32_t)(hbuf * ST_HB);
+#pragma unroll
+            for (int m = 0; m < PRODUCTS; ++m) {
+                product(o1, m);
+                if (m % 2 == 0 && m / 2 < FETCHES) fetch(o0, hnext, wbuf ^ 1, 0, m / 2);
+                if (m % 3 == 1 && m / 3 < ST_WL) lds_load16_at(w_from, wsrc[m / 3], w_to + (m / 3) * 1024);
+                if (m % 3 == 1 && m / 3 >= ST_WL && m / 3 < ST_WL + ST_HL) lds_load16(hsrc[m / 3 - ST_WL] + hk * SF_KS, h_to + (m / 3 - ST_WL) * 1024);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            hk = min(hk + 1, stages - 1);
+            wk = min(wk + 1, stages - 1);
+            hbuf = hnext;
+            wbuf ^= 1;
+        }
+        // block of rows by block: results out, the next tile's structural rows in
+#pragma unroll
+        for (int bu = 0; bu < ST_RB; ++bu) {
+            // (a result is read 18 cycles after its product at the earliest; the compiler does not know the products)
+            asm volatile("s_nop 15\n\ts_nop 7" : "+a"(acc[bu][0]), "+a"(acc[bu][1]), "+a"(acc[bu][2]), "+a"(acc[bu][3]), "+a"(acc[bu][4]), "+a"(acc[bu][5]),
+                         "+a"(acc[bu][6]), "+a"(acc[bu][7]), "+a"(acc[bu][8]), "+a"(acc[bu][9]), "+a"(acc[bu][10]), "+a"(acc[bu][11]), "+a"(acc[bu][12]));
+            const int u = u0 + wave * 64 + bu * 16 + (lane & 15);
+            if (u < n_rows) {
+#pragma unroll
+                for (int bn = 0; bn < SF_NBLK; ++bn) {
+                    if (n0 + bn * 16 >= a.d) break;          // uniform
+                    const int n = n0 + bn * 16 + (lane >> 4) * 4;
+                    if (n < a.d) *reinterpret_cast<floatx4*>(a.out + (size_t)u * a.d + n) = acc[bu][bn];
+                }
+            }
+            if (more) structural(bu, n_next);
+        }
+        if (!more) break;
+        t = t_next;
+        u0 = u_next;
+        n0 = n_next;
+    }
+    wait_vm<0>();                            // the loads issued past the end land before the workgroup gives up its LDS
+}
+
 // ------------------------------------------------------------------ gradient of Wp
 constexpr int WG_SEM = 256;     // text-feature coordinates per workgroup tile of the gradient
 
@@ -450,6 +633,10 @@ hipError_t launch_sem_fuse(const SemFuseArgs& a, hipStream_t s) {
     const int64_t n_tiles = (a.d + SF_N - 1) / SF_N;
     const int64_t blocks = ((u_tiles + 7) / 8) * 8 * n_tiles;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    if (!a.bits && a.ds >= ST_FROM) {
+        hipLaunchKernelGGL(sem_stream_kernel, dim3((unsigned)std::min<int64_t>(blocks, ST_WG)), dim3(ST_NW * 64), 0, s, a);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)blocks), block(SF_NW * 64);
     if (a.bits == 8) hipLaunchKernelGGL((sem_fuse_kernel<8>), grid, block, 0, s, a);
     else if (a.bits == 16) hipLaunchKernelGGL((sem_fuse_kernel<16>), grid, block, 0, s, a);

@@ -245,3 +245,25 @@ def test_operators_over_many_rows(d, h, B):
     par.assert_close(eng.score(plan, torch.from_numpy(cand).cuda()).cpu().numpy(),
                      orank.score_candidates(case.qb, cand, om.Model(case.params, case.gamma)), "scores d=%d h=%d" % (d, h))
     plan.free()
+
+
+# rows of text features by list, several tiles a workgroup: a column tile, two of which one holds 8 columns, three; feature stages that
+# leave the ring of stages at another place after every tile; a second launch of fewer rows
+@pytest.mark.parametrize("d,d_sem", [(24, 1024), (216, 256), (432, 320)])
+def test_fused_rows_of_many_tiles(d, d_sem):
+    import torch
+    N, B, A = 3001, 60, 1201
+    par.say("fused rows: d=%d d_sem=%d, %d rows" % (d, d_sem, B * A))
+    case = par.Case(N, 12, d, 32, B, 2, 8.0, seed=5 + d, T=2 * N, d_sem=d_sem)
+    M = case.model()
+    rng = np.random.default_rng(d)
+    answers = np.stack([rng.choice(N, A, replace=False) for _ in range(B)])
+    off = np.arange(0, B * A + 1, A).astype(np.int32)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.int32)).cuda()
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    dist = eng.rank_answers(plan, dev(off), dev(answers.reshape(-1)))[1].cpu().numpy().reshape(B, A)
+    for q in range(B):
+        want = case.distances_all(case.qb, q, M)[answers[q]]
+        np.testing.assert_allclose(dist[q], want, rtol=1e-5)     # (fp32 distances, as in the oracle's band of ranks)
+    plan.free()
