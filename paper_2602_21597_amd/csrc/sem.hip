@@ -84,11 +84,9 @@ __device__ __forceinline__ bf16x8 join8(short4v a, short4v b) {
 // ------------------------------------------------------------------ forward
 // out[u, :] = E[id(u), :] + Wb * H[id(u), :].  Workgroup tile: 256 rows x 208 coordinates (two
 // tiles cover d = 400, so a feature row is brought into LDS twice), k stages of 64 = 128 bytes of
-// every row = one cache line per row and stage.  What bounds the kernel is the number of cache
-// lines a compute unit can have in flight (its L1 miss queue: about 35 GB/s per unit at the
-// latency of an L2 hit under load, whatever the LDS could buffer), so every request is a whole
-// line, the tile is as wide as the accumulators allow, and two stages in LDS (one being multiplied,
-// one landing) are as good as more.
+// every row = one cache line per row and stage.  What bounds the kernel is how much a compute unit has in flight between its
+// barriers (35 GB/s per unit; an L2 hit path that is kept full delivers 122), so every request is a whole line and the tile is as wide
+// as the accumulators allow.
 // A stage is 64 direct loads of 1 KiB, 8 per wavefront: load l of an area covers rows 8l .. 8l+7,
 // 128 bytes each; a lane's 16 bytes land at its lane number, so the lane picks the column that
 // belongs there: column c of row r is stored at c ^ (r / 2 % 8), which spreads the 16 rows x 16
@@ -428,23 +426,23 @@ constexpr int WG_SEM = 256;     // text-feature coordinates per workgroup tile o
 constexpr int WG_KS = 32;                                     // rows per stage = one MFMA step
 constexpr int WG_M = 208, WG_MB = WG_M / 16;                  // embedding coordinates per workgroup tile, MFMA blocks
 constexpr int WG_HP = 544, WG_GP = 2 * WG_M;                  // row pitches, bytes
-constexpr int WG_HL = 19, WG_GL = 13;                         // wave-loads of 1 KiB per stage: H area (17 carry data), G area
+constexpr int WG_HL = 17, WG_GL = 13;                         // wave-loads of 1 KiB per stage: H area, G area
 constexpr int WG_STAGE = (WG_HL + WG_GL) * 1024;
-constexpr int WG_NB = 4;                                      // stages in LDS: one multiplied, three in flight or landing
-constexpr int WG_PER_WAVE = (WG_HL + WG_GL) / 4;              // data loads per wavefront and stage
+constexpr int WG_NB = 5;                                      // stages in LDS: one being fetched from, four in flight or landing
+constexpr int WG_PER_WAVE = (WG_HL + WG_GL + 3) / 4;          // data loads per wavefront and stage (the last two of 32 carry nothing)
 
 // partial[split, m, n] = sum over the split's rows u of G[u, m] * H[id(u), n]
 // Workgroup tile: 208 embedding x 256 feature coordinates (two tiles cover d = 400, so a feature
-// row is brought into LDS twice per step and a gradient row four times; what bounds the kernel is
-// the bytes a compute unit keeps in flight at the latency of a loaded memory system, so the tile
-// is as large as the accumulators allow and LDS is all staging).  Rows travel from global memory straight into LDS
-// (no registers, no transposition on the way): every wavefront issues 8 loads of 1 KiB per
-// stage, up to three stages ahead of the one being multiplied, and one load of the row numbers
-// two stages further; the operands of the MFMA blocks are fetched with transposing reads.
-// One workgroup barrier per stage.
-__global__ __launch_bounds__(256) void sem_wgrad_kernel(const SemWgradArgs a) {
-    __shared__ __attribute__((aligned(1024))) unsigned char tiles[WG_NB * WG_STAGE];
-    __shared__ __attribute__((aligned(256))) int32_t id_ring[4][3][64];     // per wavefront: row numbers of three stages
+// row is brought into LDS twice per step and a gradient row four times; the tile is as large as the accumulators allow and LDS is all
+// staging).  Rows travel from global memory straight into LDS (no registers, no transposition on the way): every wavefront issues 8 loads
+// of 1 KiB per stage, up to five stages ahead of the one being multiplied, and one load of the row numbers three stages further; the
+// operands of the MFMA blocks are fetched with transposing reads, those of the next stage between the products of this one.
+// One workgroup barrier per stage.  What bounds it is the wait for a stage's last rows (3.1 TB/s from HBM, each stage 1830 cycles of which the
+// products take 832): with operands fetched and multiplied in turn and four stages in LDS 2.72 ms for the 2.7 million rows of a step
+// over 5 million entities, 2.46 with the fetches between the products, 2.40 with five stages.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void sem_wgrad_kernel(const SemWgradArgs a) {
+    __shared__ __attribute__((aligned(1024))) unsigned char tiles[WG_NB * WG_STAGE + 2048];       // (the end takes the loads that carry nothing)
+    __shared__ __attribute__((aligned(256))) int32_t id_ring[4][4][64];     // per wavefront: row numbers of four stages
     const int n_rows = min(*a.n_rows_dev, a.n_rows);
     const int m_tiles = (a.d + WG_M - 1) / WG_M, n_tiles = (a.ds + WG_SEM - 1) / WG_SEM;
     const int tiles_mn = m_tiles * n_tiles;
@@ -453,7 +451,7 @@ __global__ __launch_bounds__(256) void sem_wgrad_kernel(const SemWgradArgs a) {
     if (split >= a.n_splits) return;
     const int tile = j % tiles_mn;
     const int m0 = (tile % m_tiles) * WG_M, n0 = (tile / m_tiles) * WG_SEM;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     const int stages = (n_rows + WG_KS - 1) / WG_KS;
     const int per_split = (stages + a.n_splits - 1) / a.n_splits;
@@ -463,93 +461,123 @@ __global__ __launch_bounds__(256) void sem_wgrad_kernel(const SemWgradArgs a) {
 #pragma unroll
     for (int bn = 0; bn < 4; ++bn)
 #pragma unroll
-        for (int bm = 0; bm < WG_MB; ++bm) acc[bn][bm] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int bm = 0; bm < WG_MB; ++bm) {
+            acc[bn][bm] = floatx4{0.f, 0.f, 0.f, 0.f};
+            asm volatile("" : "+a"(acc[bn][bm]));        // (in accumulator registers from here on)
+        }
 
     if (s_lo < s_hi) {
         // What this lane fetches in each of its wavefront's loads of a stage (the same every stage).
         // The H tile is 32 rows x 34 chunks of 16 bytes = 17 loads of 64 chunks (chunk c = row c/34, column
         // c%34; columns 32 and 33 are padding and fetch columns 0 and 1 again), the G tile 32 x 26 = 13 loads.
-        // Loads 0..18 of a stage go to the H area (17 carry the tile, 2 are padding), loads 19..31 are the G tile.
+        // Loads 0..16 of a stage are the H tile, loads 17..29 the G tile.
         constexpr int G_AT = WG_HL;                                       // the G tile starts at this KiB of the stage
-        int row[WG_PER_WAVE], col[WG_PER_WAVE];
-        bool is_h[WG_PER_WAVE];
+        int row[WG_PER_WAVE];
+        const uint16_t* from[WG_PER_WAVE];                                // the lane's column of row 0
 #pragma unroll
         for (int q = 0; q < WG_PER_WAVE; ++q) {
             const int l = wave + 4 * q;                                   // load number within the stage, 0..31
-            is_h[q] = l < G_AT;
-            if (l < G_AT) {                                               // (loads 17, 18: padding, rows past the tile clamp to its last)
+            if (l < G_AT) {
                 const int c = l * 64 + lane;
-                row[q] = min(c / 34, WG_KS - 1);
-                col[q] = min(n0 + ((c % 34) & 31) * 8, a.ds - 8);
+                row[q] = c / 34;
+                from[q] = a.H + min(n0 + ((c % 34) & 31) * 8, a.ds - 8);
             } else {
                 const int c = (l - G_AT) * 64 + lane;
-                row[q] = min(c / (WG_GP / 16), WG_KS - 1);
-                col[q] = min(m0 + (c % (WG_GP / 16)) * 8, a.d - 8);
+                row[q] = min(c / (WG_GP / 16), WG_KS - 1);                // (loads 30, 31: the last row again)
+                from[q] = a.G + min(m0 + (c % (WG_GP / 16)) * 8, a.d - 8);
             }
         }
-        static_assert(WG_HL * 1024 >= WG_KS * WG_HP && WG_GL * 1024 >= WG_KS * WG_GP && (WG_HL + WG_GL) % 4 == 0, "stage layout");
+        static_assert(WG_HL * 1024 >= WG_KS * WG_HP && WG_GL * 1024 >= WG_KS * WG_GP && 4 * WG_PER_WAVE - (WG_HL + WG_GL) == 2, "stage layout");
         const uint32_t tiles_at = lds_addr(tiles), ring_at = lds_addr(&id_ring[wave][0][0]);
         auto issue_ids = [&](int s) {        // row numbers of stage s (rows past the end: the last row's)
-            lds_load4(a.ids + min(s * WG_KS + (lane & (WG_KS - 1)), n_rows - 1), ring_at + (uint32_t)(s % 3) * 256u);
+            lds_load4(a.ids + min(s * WG_KS + (lane & (WG_KS - 1)), n_rows - 1), ring_at + (uint32_t)(s & 3) * 256u);
         };
-        auto issue_data = [&](int s) {       // WG_PER_WAVE loads; needs the row numbers of stage s in the ring
-            const uint32_t base = tiles_at + (uint32_t)(s % WG_NB) * WG_STAGE;
-            const int32_t* ids = id_ring[wave][s % 3];
-            int32_t id[WG_PER_WAVE];
+        // load q of a stage; the row numbers of the stage have to be in the ring
+        auto source_row = [&](int s, int q) { return wave + 4 * q < G_AT ? id_ring[wave][s & 3][row[q]] : min(s * WG_KS + row[q], n_rows - 1); };
+        auto issue_data = [&](int buf, int q, int r) {
+            const int l = wave + 4 * q;
+            const uint16_t* src = from[q] + (size_t)(uint32_t)r * (uint32_t)(l < G_AT ? a.ds : a.d);
+            lds_load16(src, tiles_at + (uint32_t)(l < WG_HL + WG_GL ? buf * WG_STAGE + l * 1024 : WG_NB * WG_STAGE + (l - WG_HL - WG_GL) * 1024));
+        };
+        auto issue_stage = [&](int s, int buf) {
 #pragma unroll
-            for (int q = 0; q < WG_PER_WAVE; ++q) id[q] = ids[row[q]];
+            for (int q = 0; q < WG_PER_WAVE; ++q) issue_data(buf, q, source_row(s, q));
+        };
+        // lane group g = lane / 16 reads rows 4g .. 4g+3 (first read) and 16 + 4g .. (second) of the 32 rows:
+        // the order of the 32 products within an MFMA step is free as long as both operands agree
+        const int row_in = (lane >> 4) * 4 + ((lane & 15) >> 2), col_in = (lane & 3) * 4;
+        const int h_in = row_in * WG_HP + (wave * 64 + col_in) * 2, g_in = G_AT * 1024 + row_in * WG_GP + col_in * 2;
+        constexpr int FETCHES = 2 * (4 + WG_MB), PRODUCTS = 4 * WG_MB;
+        struct Operands { short4v f[FETCHES]; };                          // H blocks, then G blocks, two reads each
+        auto fetch = [&](Operands& o, const unsigned char* buf, int i) {
+            const int b = i >> 1, half = i & 1;
+            o.f[i] = read_tr(reinterpret_cast<const uint16_t*>(b < 4 ? buf + h_in + half * 16 * WG_HP + b * 32 : buf + g_in + half * 16 * WG_GP + (b - 4) * 32));
+        };
+        auto product = [&](const Operands& o, int m) {
+            const int bn = m % 4, bm = m / 4;
+            asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[bn][bm]) : "v"(join8(o.f[2 * bn], o.f[2 * bn + 1])), "v"(join8(o.f[8 + 2 * bm], o.f[9 + 2 * bm])));
+        };
+        // stage s has landed, its last rows may lie past the end: these hold copies of the last row and count as zeros through G
+        auto clear_tail = [&](int s, int buf) {
+            if ((s + 1) * WG_KS <= n_rows || s >= s_hi) return;
+            uint32_t* g = reinterpret_cast<uint32_t*>(tiles + buf * WG_STAGE + G_AT * 1024);
+            for (int i = (n_rows - s * WG_KS) * (WG_GP / 4) + tid; i < WG_KS * (WG_GP / 4); i += 256) g[i] = 0u;
+            __syncthreads();
+        };
+        // Stage s is multiplied from registers while stage s + 1 is fetched from LDS, the stages up to s + 4 are on their way and stage s + 5
+        // is requested into the buffer that stage s was fetched from.
+        int buf = 0;                         // of stage s
+        auto stage = [&](const Operands& now, Operands& next, int s) {
+            // stage s + 1 and the row numbers of stage s + 5 are in LDS: all but the data of stage s + 2 and what follows it
+            wait_vm<3 * WG_PER_WAVE + 2>();
+            wait_lds();                      // (stage s is in this wavefront's registers)
+            __syncthreads();                 // ... those of every wavefront
+            const int next_buf = buf == WG_NB - 1 ? 0 : buf + 1;
+            clear_tail(s + 1, next_buf);
+            int r[WG_PER_WAVE];
 #pragma unroll
-            for (int q = 0; q < WG_PER_WAVE; ++q) {
-                const uint16_t* src = is_h[q] ? a.H + (size_t)id[q] * a.ds + col[q]
-                                              : a.G + (size_t)min(s * WG_KS + row[q], n_rows - 1) * a.d + col[q];
-                lds_load16(src, base + (uint32_t)(wave + 4 * q) * 1024u);
+            for (int q = 0; q < WG_PER_WAVE; ++q) r[q] = source_row(s + 5, q);
+            issue_ids(s + 8);
+#pragma unroll
+            for (int m = 0; m < PRODUCTS; ++m) {
+                product(now, m);
+                if (m < FETCHES) fetch(next, tiles + next_buf * WG_STAGE, m);
+                if (m % 5 == 4 && m / 5 < WG_PER_WAVE) issue_data(buf, m / 5, r[m / 5]);        // (stages past the end fetch valid rows that nobody reads)
+                __builtin_amdgcn_sched_barrier(0);
             }
+            buf = next_buf;
         };
-        // prologue: in flight afterwards, oldest first:
-        // data(s_lo) | ids(s_lo + 3) data(s_lo + 1) | ids(s_lo + 4) data(s_lo + 2)
-        issue_ids(s_lo);
-        issue_ids(s_lo + 1);
-        issue_ids(s_lo + 2);
+        // prologue: in flight afterwards, oldest first: data of the first stage, of the second, then, as in the loop, the row numbers of
+        // stage s + 3 before the data of stage s: ids(5) data(2) | ids(6) data(3) | ids(7) data(4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) issue_ids(s_lo + i);
         wait_vm<0>();
-        issue_data(s_lo);
-        issue_ids(s_lo + 3);
-        issue_data(s_lo + 1);
+        issue_stage(s_lo, 0);
         issue_ids(s_lo + 4);
-        issue_data(s_lo + 2);
-        for (int s = s_lo; s < s_hi; ++s) {
-            // all but the last two stages' loads and the row numbers between them:
-            // stage s and the row numbers of stage s + 3 are in LDS
-            wait_vm<2 * WG_PER_WAVE + 1>();
-            __syncthreads();                 // ... those of every wavefront; and everybody is done with stage s - 1
-            issue_ids(s + 5);
-            issue_data(s + 3);               // into the buffer stage s - 1 was multiplied from (stages past the end fetch valid rows that nobody reads)
-            unsigned char* buf = tiles + (s % WG_NB) * WG_STAGE;
-            if ((s + 1) * WG_KS > n_rows) {  // rows past the end hold copies of the last row: they count as zeros through G
-                uint32_t* g = reinterpret_cast<uint32_t*>(buf + G_AT * 1024);
-                const int first = n_rows - s * WG_KS;
-                for (int i = first * (WG_GP / 4) + tid; i < WG_KS * (WG_GP / 4); i += 256) g[i] = 0u;
-                __syncthreads();
-            }
-            const uint16_t* Hs = reinterpret_cast<const uint16_t*>(buf);
-            const uint16_t* Gs = reinterpret_cast<const uint16_t*>(buf + G_AT * 1024);
-            // lane group g = lane / 16 reads rows 4g .. 4g+3 (first read) and 16 + 4g .. (second) of the 32 rows:
-            // the order of the 32 products within an MFMA step is free as long as both operands agree
-            const int row_in = (lane >> 4) * 4 + ((lane & 15) >> 2), col_in = (lane & 3) * 4;
-            bf16x8 fh[4], fg[WG_MB];
-            const uint16_t* hr = Hs + row_in * (WG_HP / 2) + wave * 64 + col_in;
-            const uint16_t* gr = Gs + row_in * (WG_GP / 2) + col_in;
+        issue_stage(s_lo + 1, 1);
+        wait_vm<WG_PER_WAVE>();              // the first stage and the row numbers of the fifth
 #pragma unroll
-            for (int bn = 0; bn < 4; ++bn) fh[bn] = join8(read_tr(hr + bn * 16), read_tr(hr + 16 * (WG_HP / 2) + bn * 16));
+        for (int i = 2; i < WG_NB; ++i) {
+            issue_ids(s_lo + 3 + i);
+            issue_stage(s_lo + i, i);
+        }
+        __syncthreads();
+        clear_tail(s_lo, 0);
+        Operands o0, o1;
 #pragma unroll
-            for (int bm = 0; bm < WG_MB; ++bm) fg[bm] = join8(read_tr(gr + bm * 16), read_tr(gr + 16 * (WG_GP / 2) + bm * 16));
-#pragma unroll
-            for (int bn = 0; bn < 4; ++bn)
-#pragma unroll
-                for (int bm = 0; bm < WG_MB; ++bm)
-                    acc[bn][bm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh[bn], fg[bm], acc[bn][bm], 0, 0, 0);
+        for (int i = 0; i < FETCHES; ++i) fetch(o0, tiles, i);
+        for (int s = s_lo;;) {
+            stage(o0, o1, s);
+            if (++s == s_hi) break;
+            stage(o1, o0, s);
+            if (++s == s_hi) break;
         }
         wait_vm<0>();                        // the loads issued past the end land before the workgroup gives up its LDS
     }
+#pragma unroll
+    for (int bn = 0; bn < 4; ++bn)           // (a result is read 18 cycles after its product at the earliest; the compiler does not know the products)
+        asm volatile("s_nop 15\n\ts_nop 7" : "+a"(acc[bn][0]), "+a"(acc[bn][1]), "+a"(acc[bn][2]), "+a"(acc[bn][3]), "+a"(acc[bn][4]), "+a"(acc[bn][5]),
+                     "+a"(acc[bn][6]), "+a"(acc[bn][7]), "+a"(acc[bn][8]), "+a"(acc[bn][9]), "+a"(acc[bn][10]), "+a"(acc[bn][11]), "+a"(acc[bn][12]));
     // a lane holds, per block, 4 consecutive feature coordinates n of one embedding coordinate m
 #pragma unroll
     for (int bm = 0; bm < WG_MB; ++bm) {

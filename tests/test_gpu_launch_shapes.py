@@ -267,3 +267,12 @@ def test_fused_rows_of_many_tiles(d, d_sem):
         want = case.distances_all(case.qb, q, M)[answers[q]]
         np.testing.assert_allclose(dist[q], want, rtol=1e-5)     # (fp32 distances, as in the oracle's band of ranks)
     plan.free()
+
+
+# the projection's gradient over nearly all of N rows: a part of a 32-row stage, a whole one, one row more, fewer stages than are requested
+# ahead, as many, several splits of them with a ragged end; coordinates and features of two tiles
+@pytest.mark.parametrize("N,B,K,d,d_sem", [(20, 3, 2, 8, 64), (32, 12, 9, 24, 128), (33, 12, 9, 24, 128), (130, 20, 30, 216, 320),
+                                           (193, 20, 40, 216, 64), (1500, 60, 90, 40, 320)])
+def test_projection_gradient_by_rows(N, B, K, d, d_sem):
+    par.say("projection gradient: N=%d d=%d d_sem=%d" % (N, d, d_sem))
+    par.check_forward_backward(par.Case(N, 6, d, 32, B, K, 8.0, seed=N + d, T=4 * N, d_sem=d_sem))
