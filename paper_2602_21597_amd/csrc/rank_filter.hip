@@ -503,12 +503,15 @@ struct MergeArgs {
 // the next chunk) and merges the distances into the running top-k.  In a first chunk a list holds
 // hundreds of entities against a bound that the chunk itself would improve: the upper bounds of the
 // listed ones give the k-th (a histogram between the smallest and the bound so far), and only what
-// can lie below that is computed, a tenth.  Nearly all of these turn out farther than the k-th so far;
-// the few that are not are collected and inserted by the first wavefront into the list its lanes
-// hold.  A query with more than ROOM entities, or a crowded tile, is marked (count > room,
+// can lie below that is computed, a tenth, 64 of them and one branch a wavefront and turn.  Nearly all of these turn out farther than
+// the k-th so far; the few that are not are collected, and the first wavefront inserts those that still are before the k-th into the
+// list its lanes hold (inserting every one, and a wavefront's branches one after the other: 42 against 28 us for 512 queries x 12 952
+// entities x 400 coordinates, 42.5 against 34.5 for 1024 x 262 144 later on).  A query with more than ROOM entities, or a crowded tile, is marked (count > room,
 // *overflowed) for the fp32 pass of the chunk.  ROOM leaves LDS for four workgroups a compute unit, all of 1024 queries at once.
-constexpr int ROOM = 3584, MERGE_T = 128, BINS = 256;
-template <bool B16>
+// MERGE_T: 128 threads, or 256 where three workgroups a compute unit hold all queries (35.4 and 29.7 us for those 512).  PRUNE_FROM: 64
+// entities are one turn, pruned or not (28.5 against 29.7 us from 128 on).
+constexpr int ROOM = 3584, BINS = 256, MERGE_WIDE_TO = 768, PRUNE_FROM = 64;
+template <bool B16, int MERGE_T>
 __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) {
     __shared__ __attribute__((aligned(16))) float slab[MERGE_T / 64][64 * slab_ld(16)];
     __shared__ int32_t list[ROOM];
@@ -516,6 +519,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
     static_assert(BINS * sizeof(int32_t) <= sizeof(slab), "room for the histogram");
     int32_t* hist = reinterpret_cast<int32_t*>(&slab[0][0]);         // (done with before the first distances)
     __shared__ float sd[MERGE_T], best_hi[MERGE_T / 64];
+    __shared__ uint32_t nearest[MERGE_T];
     __shared__ int32_t si[MERGE_T];
     __shared__ int32_t n_list, n_near, n_new, crowded;
     __shared__ float kth_d, bound;
@@ -570,7 +574,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         return;
     }
     if (n == 0) return;
-    if (n > MERGE_T && kth_d < INFINITY) {
+    if (n > PRUNE_FROM && kth_d < INFINITY) {
         // upper bound of a listed entity: its lower one and twice both errors (the widest branch's)
         float both = 0.f;
         for (int r = r_lo; r < r_hi; ++r) both = fmaxf(both, g.base[g.ldb + r] - g.base[r]);
@@ -643,39 +647,70 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         n = n_near;
     }
     for (int base = 0; base < n; base += MERGE_T) {
-        if (base + wave * 64 < n) {                  // uniform in the wavefront
-            const bool live = base + t < n;
-            const int32_t e = live ? list[base + t] : 0;
-            const float dv = exact_distance<B16, 16, 3>(g.act, g.row_ids, r_lo, r_hi, g.E, g.E16, e, g.d, slab[wave]);
-            if (live && before(dv, g.ent_base + e, kth_d, kth_i)) {
+        // 64 entities and one branch at a time, dealt to the wavefronts (a few entities of a union in one go)
+        const int parts = (min(n - base, MERGE_T) + 63) / 64, units = parts * (r_hi - r_lo);
+        nearest[t] = 0xFFFFFFFFu;
+        __syncthreads();
+        for (int u = wave; u < units; u += MERGE_T / 64) {
+            const int part = u % parts, r = r_lo + u / parts, x = base + part * 64 + lane;
+            const int32_t e = x < n ? list[x] : 0;
+            const float dv = exact_distance<B16, 16, 3>(g.act, g.row_ids, r, r + 1, g.E, g.E16, e, g.d, slab[wave]);
+            atomicMin(&nearest[part * 64 + lane], __builtin_bit_cast(uint32_t, dv));       // (no distance is negative; NaN is above all others)
+        }
+        __syncthreads();
+        if (base + t < n) {
+            const float dv = __builtin_bit_cast(float, nearest[t]);
+            const int32_t id = g.ent_base + list[base + t];
+            if (before(dv, id, kth_d, kth_i)) {
                 const int at = atomicAdd(&n_new, 1);
                 sd[at] = dv;
-                si[at] = g.ent_base + e;
+                si[at] = id;
             }
         }
         __syncthreads();
         if (wave == 0) {
+            // the lanes hold the distances of the round; whatever is no longer before the k-th falls out at once
             const int m = n_new;
-            for (int x = 0; x < m; ++x) {
-                const float dv = sd[x];
-                const int32_t id = si[x];
-                if (__ballot(my_i == id) != 0ull) continue;      // listed by another branch already
-                const bool stays = before(my_d, my_i, dv, id);
-                const float up_d = __shfl_up(my_d, 1, 64);
-                const int32_t up_i = __shfl_up(my_i, 1, 64);
-                const bool up_stays = lane == 0 || before(up_d, up_i, dv, id);
-                if (!stays) {
-                    my_d = up_stays ? dv : up_d;
-                    my_i = up_stays ? id : up_i;
-                }
-                if (lane >= k) {
-                    my_d = INFINITY;
-                    my_i = INT_MAX;
+            float dn[MERGE_T / 64];
+            int32_t in[MERGE_T / 64];
+            bool open[MERGE_T / 64];
+            float kd = kth_d;
+            int32_t ki = kth_i;
+#pragma unroll
+            for (int w = 0; w < MERGE_T / 64; ++w) {
+                open[w] = w * 64 + lane < m;
+                dn[w] = open[w] ? sd[w * 64 + lane] : INFINITY;
+                in[w] = open[w] ? si[w * 64 + lane] : INT_MAX;
+            }
+#pragma unroll
+            for (int w = 0; w < MERGE_T / 64; ++w) {
+                for (;;) {
+                    const unsigned long long left = __ballot(open[w] && before(dn[w], in[w], kd, ki));
+                    if (left == 0ull) break;
+                    const int from = __ffsll(left) - 1;
+                    const float dv = lane_value(dn[w], from);
+                    const int32_t id = lane_value(in[w], from);
+                    open[w] = open[w] && lane > from;
+                    if (__ballot(my_i == id) != 0ull) continue;      // listed by another branch already
+                    const bool stays = before(my_d, my_i, dv, id);
+                    const float up_d = __shfl_up(my_d, 1, 64);
+                    const int32_t up_i = __shfl_up(my_i, 1, 64);
+                    const bool up_stays = lane == 0 || before(up_d, up_i, dv, id);
+                    if (!stays) {
+                        my_d = up_stays ? dv : up_d;
+                        my_i = up_stays ? id : up_i;
+                    }
+                    if (lane >= k) {
+                        my_d = INFINITY;
+                        my_i = INT_MAX;
+                    }
+                    kd = lane_value(my_d, k - 1);
+                    ki = lane_value(my_i, k - 1);
                 }
             }
-            if (lane == k - 1) {
-                kth_d = my_d;
-                kth_i = my_i;
+            if (lane == 0) {
+                kth_d = kd;
+                kth_i = ki;
             }
             if (lane == 0) n_new = 0;
         }
@@ -1004,8 +1039,12 @@ hipError_t launch_near_merge(const RankFilter& f, int chunk, const float* act, c
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
     const MergeArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, f.found, f.found_pair, f.count,
                       f.overflowed + chunk, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, f.lde, f.parts, rounding_of(f.d)};
-    if (E16) hipLaunchKernelGGL((near_merge_kernel<true>), dim3(n_queries), dim3(MERGE_T), 0, s, g);
-    else hipLaunchKernelGGL((near_merge_kernel<false>), dim3(n_queries), dim3(MERGE_T), 0, s, g);
+    const bool wide = n_queries <= MERGE_WIDE_TO;
+    const dim3 grid(n_queries), block(wide ? 256 : 128);
+    if (E16 && wide) hipLaunchKernelGGL((near_merge_kernel<true, 256>), grid, block, 0, s, g);
+    else if (E16) hipLaunchKernelGGL((near_merge_kernel<true, 128>), grid, block, 0, s, g);
+    else if (wide) hipLaunchKernelGGL((near_merge_kernel<false, 256>), grid, block, 0, s, g);
+    else hipLaunchKernelGGL((near_merge_kernel<false, 128>), grid, block, 0, s, g);
     return hipGetLastError();
 }
 

@@ -171,6 +171,22 @@ def test_large_chunks(N, edit, kw):
         np.testing.assert_array_equal(a, b)
 
 
+# the last number of queries that are merged by four wavefronts each, the first by two, few entities and hundreds left after pruning, unions
+@pytest.mark.parametrize("B,edit", [(768, None), (769, None), (769, _outliers), (5, _one_cluster), (800, _one_cluster)])
+def test_merging_by_queries(B, edit):
+    from paper_2602_21597_amd import binding
+    case = par.Case(5003, 12, 16, 32, B, 2, 8.0, mix={"1p": 0.4, "2i": 0.2, "2u": 0.4}, seed=81, T=10000, params_edit=edit)
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb)
+        got.append([x.cpu().numpy() for k in (1, 10, 16) for x in eng.rank_all(plan, k)])
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # text features: rows rounded as they are fused: two words, a column part, two words more, two parts; errors
 # that only a part of a row has or that bound nothing; a second chunk of the filtered ranks: the results of the fp32 pass
 @pytest.mark.parametrize("N,d,edit", [(9001, 8, None), (6001, 208, _outliers), (6001, 216, _shifted), (9001, 400, _far_group(700.0)),
