@@ -1384,7 +1384,6 @@ int rank_filter_begin(ngdb_ctx_t* c, const ngdb_plan_t* pl, const RankFilter& f,
     HIPCHK(c, launch_rank_grid(f, fused_sample ? fused_sample : c->prm.E.p, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr,
                                fused_sample ? 1 : c->cfg.n_entities / RANK_SAMPLE, RANK_SAMPLE, s));
     HIPCHK(c, launch_rank_rows(f, ptr<float>(c->act), roots, pl->hp.n_roots, pl->d_root_off, pl->hp.n_queries, s));
-    if (f.bits == 8) HIPCHK(c, launch_fill_zero_i32(reinterpret_cast<int32_t*>(f.found), f.ldy * (f.lde / 128), s));
     return NGDB_OK;
 }
 

@@ -426,7 +426,7 @@ struct RankFilter {
 };
 int rank_filter_words(int d, int bits);
 size_t rank_found_bytes(int ldy, int lde);
-// the grid of a pass from n_rows rows of a table, row_step apart
+// the grid of a pass from n_rows rows of a table, row_step apart; clears found and the counters
 hipError_t launch_rank_grid(const RankFilter& f, const float* E, const uint16_t* E16, int64_t row_step, int n_rows, hipStream_t s);
 hipError_t launch_rank_rows(const RankFilter& f, const float* act, const int32_t* row_ids, int n_rows, const int32_t* root_off,
                             int n_queries, hipStream_t s);
