@@ -210,7 +210,7 @@ bool gemm_takes_rows(int M, int K);
 constexpr int PIECE_MAX_JOBS = 6;
 struct PieceJob {
     const float* W;
-    uint16_t *out_rk, *out_ck;
+    uint16_t *out_rk, *out_ck;     // (out_ck may be null)
     int R, C;
 };
 struct PieceJobs {

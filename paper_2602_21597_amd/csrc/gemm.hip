@@ -280,6 +280,7 @@ __global__ __launch_bounds__(256) void weight_pieces_kernel(const PieceJobs J) {
         }
     }
     // B[n = column][k = row]: wavefront w writes tile row w / 2, k-tile w % 2 of the block
+    if (!jb.out_ck) return;
     {
         const int nb = c0 / 32 + (wave >> 1), kt = r0 / 16 + (wave & 1), KT = (jb.R + 15) / 16;
         if (nb < (jb.C + 31) / 32 && kt < KT) {

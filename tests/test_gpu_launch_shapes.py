@@ -276,3 +276,13 @@ def test_fused_rows_of_many_tiles(d, d_sem):
 def test_projection_gradient_by_rows(N, B, K, d, d_sem):
     par.say("projection gradient: N=%d d=%d d_sem=%d" % (N, d, d_sem))
     par.check_forward_backward(par.Case(N, 6, d, 32, B, K, 8.0, seed=N + d, T=4 * N, d_sem=d_sem))
+
+
+def test_a_step_after_passes_without_a_backward_half():
+    """Weights are split for the forward half only where nothing else follows: a step on the same context has both."""
+    case = par.Case(1200, 12, 128, 160, 60, 5, 8.0, seed=91, T=2400)
+    eng = case.engine()
+    plan = eng.plan(case.qb)
+    eng.rank_all(plan, 5)
+    plan.free()
+    par.check_forward_backward(case, eng)
