@@ -1212,12 +1212,13 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
 // LDS; fp32 FMAs throughout.  One row: 3.4 us a layer against 6.5 to 7.1 for the tile kernel, and no split weights
 // are needed (9 us a pass).
 constexpr int ROWS_N = 2, ROWS_MAX = 16, ROWS_LDS = 16384;
-template <int MR>
-__global__ __launch_bounds__(256) void rows_kernel(const GemmGroup g) {
+template <int MR, class Group>
+__global__ __launch_bounds__(256) void rows_kernel(const Group g) {
     extern __shared__ __attribute__((aligned(16))) float xs[];      // [M][K]
+    constexpr int MOST = sizeof(g.p) / sizeof(GemmArgs);
     int p = 0;
 #pragma unroll
-    for (int i = 1; i < GEMM_MAX_GROUP; ++i)
+    for (int i = 1; i < MOST; ++i)
         if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) p = i;
     const GemmArgs& a = g.p[p];
     const int block = (int)blockIdx.x - g.tile_start[p];
@@ -1301,6 +1302,7 @@ bool takes_rows_kernel(const GemmArgs& a) {
            !a.addend && !a.a_pieces;
 }
 
+struct GemmOne { int count; int tile_start[2]; GemmArgs p[1]; };
 hipError_t dispatch_rows(GemmGroup& g, hipStream_t s) {
     int blocks = 0, m = 1;
     size_t lds = 0;
@@ -1311,9 +1313,17 @@ hipError_t dispatch_rows(GemmGroup& g, hipStream_t s) {
         lds = std::max(lds, (size_t)g.p[i].M * g.p[i].K * sizeof(float));
     }
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = blocks;
-    if (m <= 2) hipLaunchKernelGGL((rows_kernel<2>), dim3(blocks), dim3(256), lds, s, g);
-    else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8>), dim3(blocks), dim3(256), lds, s, g);
-    else hipLaunchKernelGGL((rows_kernel<16>), dim3(blocks), dim3(256), lds, s, g);
+    // (a single problem without the room for six: 250 bytes of arguments instead of 1520)
+    if (g.count == 1) {
+        const GemmOne one{1, {0, blocks}, {g.p[0]}};
+        if (m <= 2) hipLaunchKernelGGL((rows_kernel<2, GemmOne>), dim3(blocks), dim3(256), lds, s, one);
+        else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8, GemmOne>), dim3(blocks), dim3(256), lds, s, one);
+        else hipLaunchKernelGGL((rows_kernel<16, GemmOne>), dim3(blocks), dim3(256), lds, s, one);
+        return hipGetLastError();
+    }
+    if (m <= 2) hipLaunchKernelGGL((rows_kernel<2, GemmGroup>), dim3(blocks), dim3(256), lds, s, g);
+    else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8, GemmGroup>), dim3(blocks), dim3(256), lds, s, g);
+    else hipLaunchKernelGGL((rows_kernel<16, GemmGroup>), dim3(blocks), dim3(256), lds, s, g);
     return hipGetLastError();
 }
 
