@@ -673,7 +673,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         }
         __syncthreads();
         if (wave == 0) {
-            // the lanes hold the distances of the round; whatever is no longer before the k-th falls out at once
+            // the lanes hold the new distances; whatever is no longer before the k-th falls out at once
             const int m = n_new;
             float dn[MERGE_T / 64];
             int32_t in[MERGE_T / 64];
