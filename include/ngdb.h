@@ -495,6 +495,11 @@ int ngdb_copy_to_host(void* h_dst, const void* d_src, size_t bytes);
  * declared maxima of ngdb_config.                                                              */
 int64_t ngdb_debug_alloc_count(const ngdb_ctx_t* ctx);
 
+/* Bytes of the device buffers that this context holds (those of its plans apart), and a limit for them, beyond which
+ * an allocation fails as if the device had run out of memory (negative: none).  For tests of shortages.       */
+int64_t ngdb_debug_device_bytes(const ngdb_ctx_t* ctx);
+int ngdb_debug_device_limit(ngdb_ctx_t* ctx, int64_t bytes);
+
 /* From how many coordinate differences (branch rows x entities x d) on the rankings of this context go through the
  * integer filter; negative: the library's own choice.  For tests of the filter at sizes below that.   */
 int ngdb_debug_rank_filter_from(ngdb_ctx_t* ctx, int64_t work);

@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -94,7 +95,9 @@ struct ngdb_ctx_s {
     int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
     const int32_t* rank_overflowed = nullptr;    // the last ranking's marks per chunk (null: no filter)
     int rank_chunks = 0;
-    int near_most = INT32_MAX;     // entities of a filtered chunk for which there was memory
+    int near_most = INT32_MAX;     // entities of a filtered chunk for which there was memory, and the memory that was free then
+    size_t near_free = 0;
+    size_t held = 0, held_limit = SIZE_MAX;      // bytes of the buffers below; tests: see ngdb_debug_device_limit
     // The hidden activations of one depth (forward) or their gradients (backward) once more as bf16
     // pieces in tile order: written by the first launch of a layer pair, read as A operand by the
     // second, then free again.  Only steps whose launches use the small tile get that far.
@@ -190,29 +193,52 @@ struct Timed {
 // One grouped contraction launch, bracketed as class `cls`.
 int gemm_timed(ngdb_ctx_t* c, int cls, const GemmArgs* g, int n, hipStream_t s, bool* emitted = nullptr);
 
-// evaluation: a buffer only the ranking calls or ngdb_forward_backward use (allocated on first use
-// also under declared maxima)
-int ensure(ngdb_ctx_t* c, DevBuf& b, size_t bytes, bool evaluation = false) {
+void release(ngdb_ctx_t* c, DevBuf& b) {
+    if (b.p) (void)hipFree(b.p);
+    c->held -= b.cap;
+    b.p = nullptr;
+    b.cap = 0;
+}
+
+// The buffers that the rankings make anew whenever they need them (the device has to be idle).
+bool release_rank_buffers(ngdb_ctx_t* c) {
+    const bool any = c->rank_dist.p || c->rank_ef.p || c->rank_filter.p;
+    release(c, c->rank_dist);
+    release(c, c->rank_ef);
+    release(c, c->rank_filter);
+    c->rank_overflowed = nullptr;
+    return any;
+}
+
+hipError_t device_alloc(ngdb_ctx_t* c, DevBuf& b, size_t bytes) {
+    const hipError_t e = c->held + bytes > c->held_limit ? hipErrorOutOfMemory : hipMalloc(&b.p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();             // (the next launch is not to report it)
+        b.p = nullptr;
+        return e;
+    }
+    ++c->n_alloc;
+    c->held += b.cap = bytes;
+    return e;
+}
+
+// What a buffer is for: every call; evaluation only, i.e. the ranking calls or ngdb_forward_backward (allocated on first use also
+// under declared maxima); or one that release_rank_buffers gives back.
+enum class Use { Any, Evaluation, Ranking };
+int ensure(ngdb_ctx_t* c, DevBuf& b, size_t bytes, Use use = Use::Any) {
     if (bytes <= b.cap) return NGDB_OK;
-    if (c->presized && !evaluation)
+    if (c->presized && use == Use::Any)
         return fail(c, NGDB_ERR_ARG, "the batch needs more workspace than the maxima declared at ngdb_create allow "
                                      "(b_max_queries, k_max, max_nodes_per_query)");
     // growing: nothing may still be using the old allocation
     HIPCHK(c, hipDeviceSynchronize());
-    if (b.p) HIPCHK(c, hipFree(b.p));
-    b.p = nullptr;
-    b.cap = 0;
+    release(c, b);
     const size_t want = bytes + bytes / 4 + 256;
-    HIPCHK(c, hipMalloc(&b.p, want));
-    ++c->n_alloc;
-    b.cap = want;
+    hipError_t e = device_alloc(c, b, want);
+    // (what an earlier ranking has left behind stands in no other call's way; a ranking itself asks for less, see rank_buffers)
+    if (e == hipErrorOutOfMemory && use != Use::Ranking && release_rank_buffers(c)) e = device_alloc(c, b, want);
+    HIPCHK(c, e);
     return NGDB_OK;
-}
-
-void release(DevBuf& b) {
-    if (b.p) (void)hipFree(b.p);
-    b.p = nullptr;
-    b.cap = 0;
 }
 
 template <class T>
@@ -480,9 +506,9 @@ int size_workspace(ngdb_ctx_t* c, const ngdb_plan_t* pl, int K, bool want_table_
     }
     if (want_table_grads) {
         const size_t urows = (size_t)std::min<int64_t>(nk, c->cfg.n_entities);
-        if ((rc = ensure(c, c->gE, urows * d * f, true)) != NGDB_OK) return rc;
-        if ((rc = ensure(c, c->gR, (size_t)std::max<size_t>(hp.r_uniq.size(), 1) * d * f, true)) != NGDB_OK) return rc;
-        if (box && (rc = ensure(c, c->gRo, (size_t)std::max<size_t>(hp.r_uniq.size(), 1) * d * f, true)) != NGDB_OK) return rc;
+        if ((rc = ensure(c, c->gE, urows * d * f, Use::Evaluation)) != NGDB_OK) return rc;
+        if ((rc = ensure(c, c->gR, (size_t)std::max<size_t>(hp.r_uniq.size(), 1) * d * f, Use::Evaluation)) != NGDB_OK) return rc;
+        if (box && (rc = ensure(c, c->gRo, (size_t)std::max<size_t>(hp.r_uniq.size(), 1) * d * f, Use::Evaluation)) != NGDB_OK) return rc;
     }
 #undef ENS
     return NGDB_OK;
@@ -1330,30 +1356,53 @@ int rank_chunk_rows(ngdb_ctx_t* c, int e0, int cnt, bool sample, const RankFilte
     return NGDB_OK;
 }
 
-// Buffers of a filtered pass over R branch rows of B queries.
-int rank_filter_space(ngdb_ctx_t* c, int bits, int R, int B, int chunk, RankFilter* f) {
+// Lays the buffers of a filtered pass over R branch rows of B queries out from `base` (null: only for their size, in bytes).
+size_t rank_filter_layout(const ngdb_ctx_t* c, int bits, int R, int B, int chunk, void* base, RankFilter* f) {
     *f = RankFilter{};
     f->d = c->cfg.d; f->bits = bits; f->words = rank_filter_words(f->d, bits);
     f->ldy = (R + 127) / 128 * 128; f->lde = (chunk + 127) / 128 * 128; f->room = RANK_ROOM;
     f->parts = c->cfg.d_sem > 0 ? sem_fuse_parts(f->d) : 1;
-    size_t at = 0;
-    auto place = [&](size_t words) { const size_t o = at; at += (words + 63) / 64 * 64; return o; };
-    const size_t o_part = place((size_t)32 * f->d), o_lo = place(f->d), o_grid = place(2), o_yq = place((size_t)f->words * f->ldy),
-                 o_base = place(2 * (size_t)f->ldy), o_rq = place(f->ldy), o_eq = place((size_t)f->words * f->lde),
-                 o_slack = place((size_t)f->parts * f->lde), o_list = place(bits == 16 ? (size_t)B * f->room : 0),
-                 o_found = place(bits == 8 ? (size_t)f->ldy * (f->lde / 128) : 0),
-                 o_pair = place(bits == 8 ? rank_found_bytes(f->ldy, f->lde) / 4 : 0);
     f->n_counters = B + c->cfg.n_entities / RANK_CHUNK + 32;
-    const size_t o_count = place(f->n_counters);
-    const int rc = ensure(c, c->rank_filter, at * 4, true);
-    if (rc != NGDB_OK) return rc;
-    uint32_t* p = ptr<uint32_t>(c->rank_filter);
-    f->part = reinterpret_cast<float*>(p + o_part); f->lo = reinterpret_cast<float*>(p + o_lo); f->grid = reinterpret_cast<float*>(p + o_grid);
-    f->Yq = p + o_yq; f->base = reinterpret_cast<float*>(p + o_base); f->row_q = reinterpret_cast<int32_t*>(p + o_rq);
-    f->Eq = p + o_eq; f->slack = reinterpret_cast<int32_t*>(p + o_slack);
-    f->list = reinterpret_cast<int32_t*>(p + o_list); f->found = p + o_found; f->found_pair = p + o_pair; f->count = reinterpret_cast<int32_t*>(p + o_count);
-    f->overflowed = f->count + B;
-    return NGDB_OK;
+    size_t at = 0;
+    auto place = [&](auto*& p, size_t words) {
+        p = base ? reinterpret_cast<std::remove_reference_t<decltype(p)>>(static_cast<uint32_t*>(base) + at) : nullptr;
+        at += (words + 63) / 64 * 64;
+    };
+    place(f->part, (size_t)32 * f->d);
+    place(f->lo, f->d);
+    place(f->grid, 2);
+    place(f->Yq, (size_t)f->words * f->ldy);
+    place(f->base, 2 * (size_t)f->ldy);
+    place(f->row_q, f->ldy);
+    place(f->Eq, (size_t)f->words * f->lde);
+    place(f->slack, (size_t)f->parts * f->lde);
+    place(f->list, bits == 16 ? (size_t)B * f->room : 0);
+    place(f->found, bits == 8 ? (size_t)f->ldy * (f->lde / 128) : 0);
+    place(f->found_pair, bits == 8 ? rank_found_bytes(f->ldy, f->lde) / 4 : 0);
+    place(f->count, f->n_counters);
+    f->overflowed = base ? f->count + B : nullptr;
+    return at * 4;
+}
+
+// Buffers of a ranking: distances [R, ld], fused rows (text features), and those of a filter of `bits` over chunks of `chunk` entities (0: none).
+int rank_buffers(ngdb_ctx_t* c, int R, int B, int ld, int64_t fused_rows, int bits, int chunk, RankFilter* f) {
+    int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), Use::Ranking);
+    if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, ((size_t)fused_rows + RANK_SAMPLE) * c->cfg.d * sizeof(float), Use::Ranking);
+    if (rc == NGDB_OK && bits) {
+        rc = ensure(c, c->rank_filter, rank_filter_layout(c, bits, R, B, chunk, nullptr, f), Use::Ranking);
+        if (rc == NGDB_OK) rank_filter_layout(c, bits, R, B, chunk, c->rank_filter.p, f);
+    }
+    return rc;
+}
+
+// Device memory that an allocation of this context can have.
+size_t device_free(const ngdb_ctx_t* c) {
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return std::min(avail, c->held_limit > c->held ? c->held_limit - c->held : 0);
 }
 
 // The filter serves the plain distance (vector family).  It replaces two operations per coordinate by a quarter (top-k) or a
@@ -1393,18 +1442,32 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const float* act = ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
     const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
-    int most = RANK_CHUNK, chunk, ld, rc;
-    while (filtered && most < std::min(NEAR_CHUNK, c->near_most) && 2ll * most * R <= NEAR_DIST) most *= 2;
     RankFilter f{};
-    for (;; most /= 2) {
+    int most = RANK_CHUNK, chunk, ld, rc;
+    while (filtered && most < NEAR_CHUNK && 2ll * most * R <= NEAR_DIST) most *= 2;
+    if (most > c->near_most) {
+        // There was no memory for such chunks.  They are tried again once as much more is free as one needs (not while the
+        // stream is captured: nothing may be allocated then).
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        const size_t more = (size_t)most * R * sizeof(float) + (c->cfg.d_sem > 0 ? (size_t)most * d * sizeof(float) : 0) + rank_filter_layout(c, 8, R, B, most, nullptr, &f);
+        if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone && device_free(c) >= c->near_free + more + more / 4) c->near_most = INT32_MAX;
+        (void)hipGetLastError();
+        most = std::min(most, c->near_most);
+    }
+    for (bool emptied = false, shorter = false;; emptied = true) {
         chunk = std::min(N, most);
         ld = (chunk + 3) & ~3;
-        rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
-        if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, ((size_t)chunk + RANK_SAMPLE) * d * sizeof(float), true);
-        if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 8, R, B, chunk, &f);
-        if (rc != NGDB_ERR_OOM || most == RANK_CHUNK) break;
-        (void)hipGetLastError();             // smaller chunks need less
-        c->near_most = most / 2;
+        rc = rank_buffers(c, R, B, ld, chunk, filtered ? 8 : 0, chunk, &f);
+        if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
+            if (rc == NGDB_OK && shorter) c->near_free = device_free(c);
+            break;
+        }
+        // a buffer that is larger than the next attempt needs would stay and take the memory from the others
+        release_rank_buffers(c);
+        if (most > RANK_CHUNK) {
+            c->near_most = most /= 2;
+            shorter = true;
+        }
     }
     c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
     if (rc != NGDB_OK) return rc;
@@ -1448,12 +1511,15 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     // (with very many answers per query most entities are undecided for one of them)
     const int chunk = std::min(N, RANK_CHUNK), ld = (chunk + 3) & ~3;
     const bool filtered = rank_filtered(c, R, (double)R * N * (d - 64), 1.4e9 + 3.7e9 * ((N - 1) / chunk)) && n_ans <= 64ll * B;
-    int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), true);
-    if (rc == NGDB_OK) rc = ensure(c, c->rank_count, (size_t)n_ans * 8, true);
-    if (rc == NGDB_OK && !d_ans_dist) rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, true);
-    if (rc == NGDB_OK && sem) rc = ensure(c, c->rank_ef, ((size_t)std::max(chunk, std::min(n_ans, RANK_CHUNK)) + RANK_SAMPLE) * d * sizeof(float), true);
     RankFilter f{};
-    if (rc == NGDB_OK && filtered) rc = rank_filter_space(c, 16, R, B, chunk, &f);
+    int rc = ensure(c, c->rank_count, (size_t)n_ans * 8, Use::Evaluation);
+    if (rc == NGDB_OK && !d_ans_dist) rc = ensure(c, c->rank_thr, (size_t)n_ans * 4, Use::Evaluation);
+    for (bool emptied = false; rc == NGDB_OK; emptied = true) {
+        rc = rank_buffers(c, R, B, ld, std::max(chunk, std::min(n_ans, RANK_CHUNK)), filtered ? 16 : 0, chunk, &f);
+        if (rc != NGDB_ERR_OOM || emptied) break;
+        release_rank_buffers(c);             // (a top-k has left larger ones)
+        rc = NGDB_OK;
+    }
     c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
     c->rank_chunks = (N + chunk - 1) / chunk;
     if (rc != NGDB_OK) return rc;
@@ -1578,7 +1644,7 @@ void ngdb_destroy(ngdb_ctx_t* c) {
                      &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
                      &c->Wb, &c->Ef, &c->Ea, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
                      &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb, &c->later};
-    for (DevBuf* b : all) release(*b);
+    for (DevBuf* b : all) release(c, *b);
     if (c->side[0]) (void)hipStreamDestroy(c->side[0]);
     if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
@@ -1624,7 +1690,7 @@ int ngdb_bind_params(ngdb_ctx_t* c, const ngdb_params* p) {
     if (p->step < 0) return fail(c, NGDB_ERR_ARG, "negative step count");
     if (c->cfg.score_bf16) {   // the bf16 copy of the entity table
         const size_t n = (size_t)c->cfg.n_entities * c->cfg.d;
-        int rc = ensure(c, c->Eb, n * sizeof(uint16_t), true);
+        int rc = ensure(c, c->Eb, n * sizeof(uint16_t), Use::Evaluation);
         if (rc != NGDB_OK) return rc;
         HIPCHK(c, launch_cast_bf16(p->E.p, ptr<uint16_t>(c->Eb), (int64_t)n, nullptr));
         HIPCHK(c, hipDeviceSynchronize());
@@ -2125,6 +2191,14 @@ int ngdb_copy_to_host(void* h_dst, const void* d_src, size_t bytes) {
 }
 
 int64_t ngdb_debug_alloc_count(const ngdb_ctx_t* c) { return c ? c->n_alloc : -1; }
+
+int64_t ngdb_debug_device_bytes(const ngdb_ctx_t* c) { return c ? (int64_t)c->held : -1; }
+
+int ngdb_debug_device_limit(ngdb_ctx_t* c, int64_t bytes) {
+    if (!c) return NGDB_ERR_ARG;
+    c->held_limit = bytes < 0 ? SIZE_MAX : (size_t)bytes;
+    return NGDB_OK;
+}
 
 int ngdb_debug_rank_filter_from(ngdb_ctx_t* c, int64_t work) {
     if (!c) return NGDB_ERR_ARG;

@@ -1,0 +1,87 @@
+"""Rankings, and the calls after them, where device memory is short: a limit on the host side stands for the device's
+(nothing is allocated beyond it), the results are those of a context with all the memory it asks for."""
+import numpy as np
+import pytest
+
+from . import parity as par
+
+pytestmark = pytest.mark.gpu
+
+
+def _engine(case):
+    from paper_2602_21597_amd import binding
+    eng = case.engine()
+    assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, 0) == 0
+    return eng
+
+
+def _held(eng):
+    from paper_2602_21597_amd import binding
+    return binding.lib().ngdb_debug_device_bytes(eng.ctx)
+
+
+def _limit(eng, n):
+    from paper_2602_21597_amd import binding
+    assert binding.lib().ngdb_debug_device_limit(eng.ctx, n) == 0
+
+
+def _ranked(eng, plan):
+    return [x.cpu().numpy() for x in eng.rank_all(plan, 10)]
+
+
+# chunks of 262 144 entities, and without the memory for them half and a quarter of that, each in what its own buffers need; a
+# shortage that has passed is forgotten
+@pytest.mark.parametrize("kw", [{}, dict(d_sem=64)])
+def test_rankings_in_less_memory(kw):
+    from paper_2602_21597_amd.binding import NgdbError, ERR_OOM
+    case = par.Case(290001, 12, 64, 32, 40, 2, 8.0, seed=82, T=290001, **kw)
+    want, held = None, []
+    while len(held) < 9:
+        eng = _engine(case)
+        plan = eng.plan(case.qb)
+        par.say("rank memory: limit %d" % (held[-1] - 1 if held else -1))
+        _limit(eng, held[-1] - 1 if held else -1)
+        try:
+            got = _ranked(eng, plan)
+        except NgdbError as e:
+            assert e.code == ERR_OOM
+            got = None
+        if got is not None:
+            want = want or got
+            for a, b in zip(got, want):
+                np.testing.assert_array_equal(a, b)
+            held.append(_held(eng))
+            assert len(held) == 1 or held[-1] < held[-2]
+        _limit(eng, -1)
+        for a, b in zip(_ranked(eng, plan), want):
+            np.testing.assert_array_equal(a, b)
+        assert _held(eng) == held[0]
+        plan.free()
+        if got is None:
+            break
+    assert len(held) == 3, held
+    if kw:       # (the fused rows of a chunk, a quarter of them spare)
+        assert held[0] - held[2] > 5 * (262144 - 65536) * case.d
+
+
+def test_calls_after_a_ranking_take_its_memory():
+    """Buffers of a top-k over large chunks stand neither in the way of filtered ranks, which need smaller ones, nor of a step."""
+    import torch
+    case = par.Case(290001, 12, 32, 32, 40, 2, 8.0, seed=83, T=290001, d_sem=64)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.int32)).cuda()
+    off, ans = dev(np.arange(0, 3 * case.B + 1, 3)), dev(np.random.default_rng(5).integers(0, case.N, 3 * case.B))
+    neg = dev(np.random.default_rng(6).integers(0, case.N, (case.B, 1000)))
+    got = []
+    for short in (False, True):
+        eng = _engine(case)
+        plan = eng.plan(case.qb)
+        _ranked(eng, plan)
+        if short:
+            _limit(eng, _held(eng))
+        got.append([x.cpu().numpy() for x in eng.rank_answers(plan, off, ans)])
+        if short:
+            _limit(eng, _held(eng))
+        got[-1].append(eng.train_step(plan, neg).cpu().numpy())
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
