@@ -503,8 +503,8 @@ int ngdb_debug_device_limit(ngdb_ctx_t* ctx, int64_t bytes);
 /* From how many coordinate differences (branch rows x entities x d) on the rankings of this context go through the
  * integer filter; negative: the library's own choice.  For tests of the filter at sizes below that.   */
 int ngdb_debug_rank_filter_from(ngdb_ctx_t* ctx, int64_t work);
-/* Chunks of entity rows that the last ranking of this context computed in fp32 for some query although it went through
- * the filter (a list had no room); negative on failure.  Waits for the device.                          */
+/* Pieces of at most 65 536 entity rows that the last ranking of this context computed in fp32 for some query although it
+ * went through the filter (a list had no room); negative on failure.  Waits for the device.                          */
 int ngdb_debug_rank_overflows(ngdb_ctx_t* ctx);
 
 int64_t ngdb_step_count(const ngdb_ctx_t* ctx);

@@ -93,7 +93,7 @@ struct ngdb_ctx_s {
     const uint16_t* wp[3][4]{};     // per type: Wa forward, Wb forward, Wb backward (dH = dY Wb), Wa backward (dZ = dH Wa)
     bool have_pieces = false;
     int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
-    const int32_t* rank_overflowed = nullptr;    // the last ranking's marks per chunk (null: no filter)
+    const int32_t* rank_overflowed = nullptr;    // the last ranking's marks per piece of a chunk (null: no filter)
     int rank_chunks = 0;
     int near_most = INT32_MAX;     // entities of a filtered chunk for which there was memory, and the memory that was free then
     size_t near_free = 0;
@@ -1326,13 +1326,14 @@ int presize(ngdb_ctx_t* c) {
 }
 
 // ---- all-entity passes: the entity rows chunk by chunk
-constexpr int RANK_CHUNK = 1 << 16;
+constexpr int RANK_CHUNK = RANK_PIECE;
 // A filtered top-k takes chunks of up to NEAR_CHUNK: what a chunk costs beside its sums (merging, the launches of an fp32 pass that
 // finds nothing to do) is 50 us whatever its size.  5 million fused entities x 1024 queries 28.5 ms in chunks of 65 536, 27.7 of twice
-// that, 26.6 of four times that; a table of 2.5 million x 512 queries 7.7, 7.06, 6.8.  NEAR_DIST bounds the distances that the fp32 pass
-// of a chunk would write (the memory it has to have at hand).
+// that, 26.6 of four times that; a table of 2.5 million x 512 queries 7.7, 7.06, 6.8.  NEAR_PAIRS bounds the (branch row, entity) pairs of a
+// chunk, for which the tiles need half a byte each to say what they found (256 MiB).  The fp32 pass walks a chunk in pieces of RANK_CHUNK,
+// so that the distances take no more memory than without the filter.
 constexpr int NEAR_CHUNK = 1 << 18;
-constexpr int64_t NEAR_DIST = 1 << 29;
+constexpr int64_t NEAR_PAIRS = 1 << 29;
 constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k); rows the integer grid is made from
 constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filter may leave undecided
 
@@ -1362,7 +1363,8 @@ size_t rank_filter_layout(const ngdb_ctx_t* c, int bits, int R, int B, int chunk
     f->d = c->cfg.d; f->bits = bits; f->words = rank_filter_words(f->d, bits);
     f->ldy = (R + 127) / 128 * 128; f->lde = (chunk + 127) / 128 * 128; f->room = RANK_ROOM;
     f->parts = c->cfg.d_sem > 0 ? sem_fuse_parts(f->d) : 1;
-    f->n_counters = B + c->cfg.n_entities / RANK_CHUNK + 32;
+    const int n_lists = B * (bits == 8 ? (chunk + RANK_CHUNK - 1) / RANK_CHUNK : 1);
+    f->n_counters = n_lists + c->cfg.n_entities / RANK_CHUNK + 32;
     size_t at = 0;
     auto place = [&](auto*& p, size_t words) {
         p = base ? reinterpret_cast<std::remove_reference_t<decltype(p)>>(static_cast<uint32_t*>(base) + at) : nullptr;
@@ -1380,11 +1382,11 @@ size_t rank_filter_layout(const ngdb_ctx_t* c, int bits, int R, int B, int chunk
     place(f->found, bits == 8 ? (size_t)f->ldy * (f->lde / 128) : 0);
     place(f->found_pair, bits == 8 ? rank_found_bytes(f->ldy, f->lde) / 4 : 0);
     place(f->count, f->n_counters);
-    f->overflowed = base ? f->count + B : nullptr;
+    f->overflowed = base ? f->count + n_lists : nullptr;
     return at * 4;
 }
 
-// Buffers of a ranking: distances [R, ld], fused rows (text features), and those of a filter of `bits` over chunks of `chunk` entities (0: none).
+// Buffers of a ranking: distances [R, ld] of a piece, fused rows (text features), and those of a filter of `bits` over chunks of `chunk` entities (0: none).
 int rank_buffers(ngdb_ctx_t* c, int R, int B, int ld, int64_t fused_rows, int bits, int chunk, RankFilter* f) {
     int rc = ensure(c, c->rank_dist, std::max<size_t>((size_t)R * ld * sizeof(float), 256), Use::Ranking);
     if (rc == NGDB_OK && c->cfg.d_sem > 0) rc = ensure(c, c->rank_ef, ((size_t)fused_rows + RANK_SAMPLE) * c->cfg.d * sizeof(float), Use::Ranking);
@@ -1444,19 +1446,19 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
     RankFilter f{};
     int most = RANK_CHUNK, chunk, ld, rc;
-    while (filtered && most < NEAR_CHUNK && 2ll * most * R <= NEAR_DIST) most *= 2;
+    while (filtered && most < NEAR_CHUNK && 2ll * most * R <= NEAR_PAIRS) most *= 2;
     if (most > c->near_most) {
         // There was no memory for such chunks.  They are tried again once as much more is free as one needs (not while the
         // stream is captured: nothing may be allocated then).
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        const size_t more = (size_t)most * R * sizeof(float) + (c->cfg.d_sem > 0 ? (size_t)most * d * sizeof(float) : 0) + rank_filter_layout(c, 8, R, B, most, nullptr, &f);
+        const size_t more = (c->cfg.d_sem > 0 ? (size_t)most * d * sizeof(float) : 0) + rank_filter_layout(c, 8, R, B, most, nullptr, &f);
         if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone && device_free(c) >= c->near_free + more + more / 4) c->near_most = INT32_MAX;
         (void)hipGetLastError();
         most = std::min(most, c->near_most);
     }
     for (bool emptied = false, shorter = false;; emptied = true) {
         chunk = std::min(N, most);
-        ld = (chunk + 3) & ~3;
+        ld = (std::min(chunk, RANK_CHUNK) + 3) & ~3;
         rc = rank_buffers(c, R, B, ld, chunk, filtered ? 8 : 0, chunk, &f);
         if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
             if (rc == NGDB_OK && shorter) c->near_free = device_free(c);
@@ -1477,8 +1479,8 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     // filtered: the sample's k-th distance lets k / sample of the first chunk pass, and chunks grow with what has
     // been ranked (each at most 12 times that), so that a list holds 12 k entities and some that are only near it
     const int sample = std::min(RANK_SAMPLE, std::max(512, 128 * topk));
-    int i_chunk = 0;
-    for (int e0 = 0; e0 < N; ++i_chunk) {
+    int i_piece = 0;
+    for (int e0 = 0; e0 < N;) {
         const int want = !filtered ? chunk : (e0 == 0 ? sample : (int)std::min<int64_t>(chunk, 12ll * e0));
         const int cnt = std::min(want, N - e0);
         ChunkRows er;
@@ -1488,17 +1490,23 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
             HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16));
             HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, s));
             if (filtered && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
+            ++i_piece;
         } else {
             if (c->cfg.d_sem == 0) HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_near_tile(f, R, cnt, d_dist, topk, s));
-            HIPCHK(c, launch_near_merge(f, i_chunk, act, roots, pl->d_root_off, B, er.rows, er.rows16, e0, cnt, topk, d_dist, d_ids, s));
-            only.any = f.overflowed + i_chunk;
-            HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16, &only));
-            HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, false, d_dist, d_ids, s, &only));
+            HIPCHK(c, launch_near_merge(f, i_piece, act, roots, pl->d_root_off, B, er.rows, er.rows16, e0, cnt, topk, d_dist, d_ids, s));
+            for (int p0 = 0; p0 < cnt; p0 += RANK_CHUNK, ++i_piece) {
+                const int n = std::min(RANK_CHUNK, cnt - p0);
+                const size_t at = (size_t)p0 * d;
+                only.count = f.count + (size_t)(p0 / RANK_CHUNK) * B;
+                only.any = f.overflowed + i_piece;
+                HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows + at, n, d, dist, ld, s, er.rows16 ? er.rows16 + at : nullptr, &only));
+                HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0 + p0, n, topk, false, d_dist, d_ids, s, &only));
+            }
         }
         e0 += cnt;
     }
-    c->rank_chunks = i_chunk;
+    c->rank_chunks = i_piece;
     return NGDB_OK;
 }
 

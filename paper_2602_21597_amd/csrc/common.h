@@ -406,6 +406,8 @@ hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off,
                              int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s,
                              const Overflowed* only = nullptr);
 
+// Entities whose distances to every branch row a ranking holds at a time.  The filter takes chunks of several such pieces.
+constexpr int RANK_PIECE = 1 << 16;
 // Ranking with a filter on integer sums (rank_filter.hip): buffers of one pass.  Rows as words of 4
 // (bits = 8) or 2 (bits = 16) coordinates, word-major; leading dimensions are multiples of 128.
 struct RankFilter {
@@ -418,10 +420,10 @@ struct RankFilter {
     int32_t* slack; int parts;       // [parts, lde] error of an entity row, in steps: the sum over the parts
     // top-k: what the tiles of a chunk found, [ldy, tiles] words (zero between chunks) and rank_found_bytes(ldy, lde)
     uint32_t *found, *found_pair;
-    // filtered ranks: per query the entities to be computed in fp32 [queries, room], their number.  Both: a
-    // number above room marks a query for the fp32 pass of the chunk
+    // filtered ranks: per query the entities to be computed in fp32 [queries, room], their number (chunks of one piece).  Both: a
+    // number above room marks a query for the fp32 pass of a piece, count [pieces of a chunk, queries]
     int32_t *list, *count; int room;
-    int32_t* overflowed;             // per chunk: a list had no room (behind count: n_counters in all, cleared with the grid)
+    int32_t* overflowed;             // per piece of the pass: a list had no room (behind count: n_counters in all, cleared with the grid)
     int n_counters;
 };
 int rank_filter_words(int d, int bits);
@@ -433,7 +435,7 @@ hipError_t launch_rank_rows(const RankFilter& f, const float* act, const int32_t
 hipError_t launch_rank_entities(const RankFilter& f, const float* E, const uint16_t* E16, int n_ent, hipStream_t s);
 // lists the chunk's entities that may be among the k nearest (best: running [queries, k] distances), and merges them
 hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const float* best, int k, hipStream_t s);
-hipError_t launch_near_merge(const RankFilter& f, int chunk, const float* act, const int32_t* row_ids, const int32_t* root_off,
+hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, const int32_t* row_ids, const int32_t* root_off,
                              int n_queries, const float* E, const uint16_t* E16, int ent_base, int n_ent, int k, float* out_dist,
                              int32_t* out_ids, hipStream_t s);
 // sums[r * ld + e] of the chunk; chunk_count[a] = entities certainly closer than answer a, the undecided

@@ -183,131 +183,138 @@ __device__ __forceinline__ bool before(float d, int i, float d2, int i2) { retur
 // these in a wavefront is a bound that k entities keep; the second lists what is within the least of these bounds,
 // some ten times k entities, whose places are counted directly.  (Sorted lists of KMAX per lane, merged: 78 us more at
 // 15 000 entities, 290 at 50 000.)  Should the list be too short for ties, the k best are found one after the other.
-constexpr int TOPK_T = 1024, TOPK_LIST = 2048;
+// REST: completes a filtered pass, for the queries that have a mark in count (cleared here), several to a workgroup.
+constexpr int TOPK_T = 1024, TOPK_LIST = 2048, TOPK_FEW = 512;
+template <bool REST>
 __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ dist, int ld, const int32_t* __restrict__ root_off,
-                                                      int ent_base, int n_ent, int k, bool first_chunk,
+                                                      int n_queries, int ent_base, int n_ent, int k, bool first_chunk,
                                                       float* __restrict__ out_dist, int32_t* __restrict__ out_ids,
-                                                      int32_t* __restrict__ count, int room) {
+                                                      int32_t* __restrict__ count, int room, const int32_t* __restrict__ any) {
+    if (REST && *any == 0) return;                         // uniform
     __shared__ float s_d[TOPK_LIST], s_bound[TOPK_T / 64], s_run[KMAX];
     __shared__ int s_i[TOPK_LIST], s_run_i[KMAX], s_n;
-    const int q = blockIdx.x, t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
-    if (count && count[q] <= room) return;          // uniform: the filter has dealt with this query's chunk
-    const int r0 = root_off[q], nb = root_off[q + 1] - r0;
-    const float* row = dist + (size_t)r0 * ld;
-    auto four = [&](int e) {                         // entities e .. e + 3, those past the end not a number
-        float4 v = *reinterpret_cast<const float4*>(row + e);
-        for (int b = 1; b < nb; ++b) {
-            const float4 w = *reinterpret_cast<const float4*>(row + (size_t)b * ld + e);
-            v.x = fminf(v.x, w.x); v.y = fminf(v.y, w.y); v.z = fminf(v.z, w.z); v.w = fminf(v.w, w.w);
-        }
-        if (e + 1 >= n_ent) v.y = NAN;
-        if (e + 2 >= n_ent) v.z = NAN;
-        if (e + 3 >= n_ent) v.w = NAN;
-        return v;
-    };
-    if (t == 0) s_n = 0;
-    if (t < KMAX) {
-        const bool have = !first_chunk && t < k;
-        s_run[t] = have ? out_dist[(size_t)q * k + t] : INFINITY;
-        s_run_i[t] = have ? out_ids[(size_t)q * k + t] : -1;
-    }
-    float least = INFINITY;
-#pragma unroll 4
-    for (int e = 4 * t; e < n_ent; e += 4 * T) {
-        const float4 v = four(e);
-        least = fminf(least, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
-    }
-    int smaller = 0;                                 // lanes before this one
-#pragma unroll
-    for (int j = 0; j < 64; ++j) {
-        const float o = lane_value(least, j);
-        smaller += (o < least || (o == least && j < lane)) ? 1 : 0;
-    }
-    const float bound_w = lane_value(least, __ffsll(__ballot(smaller == k - 1)) - 1);
-    if (lane == 0) s_bound[wave] = bound_w;
-    __syncthreads();
-    float bound = INFINITY;
-    for (int w = 0; w < T / 64; ++w) bound = fminf(bound, s_bound[w]);
-    if (s_run_i[k - 1] >= 0) bound = fminf(bound, s_run[k - 1]);
-    auto list = [&](float d, int id) {
-        const int at = atomicAdd(&s_n, 1);
-        if (at < TOPK_LIST) {
-            s_d[at] = d;
-            s_i[at] = id;
-        }
-    };
-    if (t < k && s_run_i[t] >= 0) list(s_run[t], s_run_i[t]);
-#pragma unroll 4
-    for (int e = 4 * t; e < n_ent; e += 4 * T) {
-        const float4 v = four(e);
-        if (v.x <= bound) list(v.x, ent_base + e);
-        if (v.y <= bound) list(v.y, ent_base + e + 1);
-        if (v.z <= bound) list(v.z, ent_base + e + 2);
-        if (v.w <= bound) list(v.w, ent_base + e + 3);
-    }
-    __syncthreads();
-    const int n = s_n;
-    if (n <= TOPK_LIST) {
-        for (int x = t; x < n; x += T) {
-            const float d = s_d[x];
-            const int id = s_i[x];
-            int place = 0;
-            for (int j = 0; j < n; ++j) place += before(s_d[j], s_i[j], d, id) ? 1 : 0;
-            if (place < k) {
-                out_dist[(size_t)q * k + place] = d;
-                out_ids[(size_t)q * k + place] = id;
+    const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
+    for (int q = blockIdx.x; q < n_queries; q += gridDim.x) {
+        if (REST && count[q] <= room) continue;         // uniform: the filter has dealt with this query's piece
+        const int r0 = root_off[q], nb = root_off[q + 1] - r0;
+        const float* row = dist + (size_t)r0 * ld;
+        auto four = [&](int e) {                         // entities e .. e + 3, those past the end not a number
+            float4 v = *reinterpret_cast<const float4*>(row + e);
+            for (int b = 1; b < nb; ++b) {
+                const float4 w = *reinterpret_cast<const float4*>(row + (size_t)b * ld + e);
+                v.x = fminf(v.x, w.x); v.y = fminf(v.y, w.y); v.z = fminf(v.z, w.z); v.w = fminf(v.w, w.w);
             }
+            if (e + 1 >= n_ent) v.y = NAN;
+            if (e + 2 >= n_ent) v.z = NAN;
+            if (e + 3 >= n_ent) v.w = NAN;
+            return v;
+        };
+        if (t == 0) s_n = 0;
+        if (t < KMAX) {
+            const bool have = !first_chunk && t < k;
+            s_run[t] = have ? out_dist[(size_t)q * k + t] : INFINITY;
+            s_run_i[t] = have ? out_ids[(size_t)q * k + t] : -1;
         }
-        if (t >= n && t < k) {
-            out_dist[(size_t)q * k + t] = INFINITY;
-            out_ids[(size_t)q * k + t] = -1;
+        float least = INFINITY;
+    #pragma unroll 4
+        for (int e = 4 * t; e < n_ent; e += 4 * T) {
+            const float4 v = four(e);
+            least = fminf(least, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
         }
-    } else {
-        float pd = -INFINITY;
-        int pi = -1;
-        for (int r = 0; r < k; ++r) {                // the first one after (pd, pi)
-            float md = INFINITY;
-            int mi = INT_MAX;
-            auto look = [&](float d, int id) {
-                if (before(pd, pi, d, id) && before(d, id, md, mi)) {
-                    md = d;
-                    mi = id;
-                }
-            };
-            if (t < k && s_run_i[t] >= 0) look(s_run[t], s_run_i[t]);
-            for (int e = 4 * t; e < n_ent; e += 4 * T) {
-                const float4 v = four(e);
-                look(v.x, ent_base + e); look(v.y, ent_base + e + 1); look(v.z, ent_base + e + 2); look(v.w, ent_base + e + 3);
+        int smaller = 0;                                 // lanes before this one
+    #pragma unroll
+        for (int j = 0; j < 64; ++j) {
+            const float o = lane_value(least, j);
+            smaller += (o < least || (o == least && j < lane)) ? 1 : 0;
+        }
+        const float bound_w = lane_value(least, __ffsll(__ballot(smaller == k - 1)) - 1);
+        if (lane == 0) s_bound[wave] = bound_w;
+        __syncthreads();
+        float bound = INFINITY;
+        for (int w = 0; w < T / 64; ++w) bound = fminf(bound, s_bound[w]);
+        if (s_run_i[k - 1] >= 0) bound = fminf(bound, s_run[k - 1]);
+        auto list = [&](float d, int id) {
+            const int at = atomicAdd(&s_n, 1);
+            if (at < TOPK_LIST) {
+                s_d[at] = d;
+                s_i[at] = id;
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const float od = __shfl_xor(md, off, 64);
-                const int oi = __shfl_xor(mi, off, 64);
-                if (before(od, oi, md, mi)) {
-                    md = od;
-                    mi = oi;
+        };
+        if (t < k && s_run_i[t] >= 0) list(s_run[t], s_run_i[t]);
+    #pragma unroll 4
+        for (int e = 4 * t; e < n_ent; e += 4 * T) {
+            const float4 v = four(e);
+            if (v.x <= bound) list(v.x, ent_base + e);
+            if (v.y <= bound) list(v.y, ent_base + e + 1);
+            if (v.z <= bound) list(v.z, ent_base + e + 2);
+            if (v.w <= bound) list(v.w, ent_base + e + 3);
+        }
+        __syncthreads();
+        const int n = s_n;
+        if (n <= TOPK_LIST) {
+            for (int x = t; x < n; x += T) {
+                const float d = s_d[x];
+                const int id = s_i[x];
+                int place = 0;
+                for (int j = 0; j < n; ++j) place += before(s_d[j], s_i[j], d, id) ? 1 : 0;
+                if (place < k) {
+                    out_dist[(size_t)q * k + place] = d;
+                    out_ids[(size_t)q * k + place] = id;
                 }
             }
-            __syncthreads();                         // s_d / s_i of the round before have been read
-            if (lane == 0) {
-                s_d[wave] = md;
-                s_i[wave] = mi;
+            if (t >= n && t < k) {
+                out_dist[(size_t)q * k + t] = INFINITY;
+                out_ids[(size_t)q * k + t] = -1;
             }
-            __syncthreads();
-            for (int w = 0; w < T / 64; ++w)
-                if (before(s_d[w], s_i[w], md, mi)) {
-                    md = s_d[w];
-                    mi = s_i[w];
+        } else {
+            float pd = -INFINITY;
+            int pi = -1;
+            for (int r = 0; r < k; ++r) {                // the first one after (pd, pi)
+                float md = INFINITY;
+                int mi = INT_MAX;
+                auto look = [&](float d, int id) {
+                    if (before(pd, pi, d, id) && before(d, id, md, mi)) {
+                        md = d;
+                        mi = id;
+                    }
+                };
+                if (t < k && s_run_i[t] >= 0) look(s_run[t], s_run_i[t]);
+                for (int e = 4 * t; e < n_ent; e += 4 * T) {
+                    const float4 v = four(e);
+                    look(v.x, ent_base + e); look(v.y, ent_base + e + 1); look(v.z, ent_base + e + 2); look(v.w, ent_base + e + 3);
                 }
-            pd = md;
-            pi = mi;
-            if (t == 0) {
-                out_dist[(size_t)q * k + r] = md;
-                out_ids[(size_t)q * k + r] = mi == INT_MAX ? -1 : mi;
+    #pragma unroll
+                for (int off = 32; off > 0; off >>= 1) {
+                    const float od = __shfl_xor(md, off, 64);
+                    const int oi = __shfl_xor(mi, off, 64);
+                    if (before(od, oi, md, mi)) {
+                        md = od;
+                        mi = oi;
+                    }
+                }
+                __syncthreads();                         // s_d / s_i of the round before have been read
+                if (lane == 0) {
+                    s_d[wave] = md;
+                    s_i[wave] = mi;
+                }
+                __syncthreads();
+                for (int w = 0; w < T / 64; ++w)
+                    if (before(s_d[w], s_i[w], md, mi)) {
+                        md = s_d[w];
+                        mi = s_i[w];
+                    }
+                pd = md;
+                pi = mi;
+                if (t == 0) {
+                    out_dist[(size_t)q * k + r] = md;
+                    out_ids[(size_t)q * k + r] = mi == INT_MAX ? -1 : mi;
+                }
             }
         }
+        if (!REST) return;
+        if (t == 0) count[q] = 0;
+        __syncthreads();
     }
-    if (count && t == 0) count[q] = 0;
 }
 
 // ---------------------------------------------------------------- filtered ranks of listed answers
@@ -499,8 +506,13 @@ hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off,
     if (n_queries <= 0) return hipSuccess;
     if (k < 1 || k > KMAX) return hipErrorInvalidValue;
     if (ld & 3) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(topk_kernel, dim3(n_queries), dim3(n_ent > 4096 ? TOPK_T : 256), 0, s, dist, ld, root_off, ent_base, n_ent, k,
-                       first_chunk, out_dist, out_ids, only ? only->count : nullptr, only ? only->room : 0);
+    const dim3 block(n_ent > 4096 ? TOPK_T : 256);
+    if (only)
+        hipLaunchKernelGGL(topk_kernel<true>, dim3(std::min(n_queries, TOPK_FEW)), block, 0, s, dist, ld, root_off, n_queries, ent_base, n_ent, k,
+                           first_chunk, out_dist, out_ids, only->count, only->room, only->any);
+    else
+        hipLaunchKernelGGL(topk_kernel<false>, dim3(n_queries), block, 0, s, dist, ld, root_off, n_queries, ent_base, n_ent, k, first_chunk, out_dist,
+                           out_ids, (int32_t*)nullptr, 0, (const int32_t*)nullptr);
     return hipGetLastError();
 }
 

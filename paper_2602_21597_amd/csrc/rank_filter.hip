@@ -511,9 +511,10 @@ struct MergeArgs {
 // the k-th so far; the few that are not are collected, and the first wavefront inserts those that still are before the k-th into the
 // list its lanes hold (inserting every one, and a wavefront's branches one after the other: 42 against 28 us for 512 queries x 12 952
 // entities x 400 coordinates, 42.5 against 34.5 for 1024 x 262 144 later on).  A query with more than ROOM entities, or a crowded tile, is marked (count > room,
-// *overflowed) for the fp32 pass of the chunk.  ROOM leaves LDS for four workgroups a compute unit, all of 1024 queries at once.
+// overflowed) for the fp32 pass of the chunk's pieces.  ROOM leaves LDS for four workgroups a compute unit, all of 1024 queries at once.
 // MERGE_T: 128 threads, or 256 where three workgroups a compute unit hold all queries (35.4 and 29.7 us for those 512).  PRUNE_FROM: 64
 // entities are one turn, pruned or not (28.5 against 29.7 us from 128 on).
+constexpr int PIECE_TILES = RANK_PIECE / 128;
 constexpr int ROOM = 3584, BINS = 256, MERGE_WIDE_TO = 768, PRUNE_FROM = 64;
 template <bool B16, int MERGE_T>
 __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) {
@@ -571,9 +572,9 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
     __syncthreads();
     int n = n_list;
     if (n > ROOM || crowded) {                       // uniform
-        if (t == 0) {
-            *g.overflowed = 1;
-            g.count[q] = g.room + 1;
+        for (int p = t; p * PIECE_TILES < g.n_tx; p += MERGE_T) {
+            g.overflowed[p] = 1;
+            g.count[(size_t)p * gridDim.x + q] = g.room + 1;
         }
         return;
     }
@@ -1040,12 +1041,12 @@ hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const fl
     return hipGetLastError();
 }
 
-hipError_t launch_near_merge(const RankFilter& f, int chunk, const float* act, const int32_t* row_ids, const int32_t* root_off,
+hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, const int32_t* row_ids, const int32_t* root_off,
                              int n_queries, const float* E, const uint16_t* E16, int ent_base, int n_ent, int k, float* out_dist,
                              int32_t* out_ids, hipStream_t s) {
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
     const MergeArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, f.found, f.found_pair, f.count,
-                      f.overflowed + chunk, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, f.lde, f.parts, rounding_of(f.d)};
+                      f.overflowed + piece, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, f.lde, f.parts, rounding_of(f.d)};
     const bool wide = n_queries <= MERGE_WIDE_TO;
     const dim3 grid(n_queries), block(wide ? 256 : 128);
     if (E16 && wide) hipLaunchKernelGGL((near_merge_kernel<true, 256>), grid, block, 0, s, g);

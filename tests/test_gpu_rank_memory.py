@@ -85,3 +85,14 @@ def test_calls_after_a_ranking_take_its_memory():
         plan.free()
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+def test_distances_are_held_a_piece_at_a_time():
+    """The fp32 pass over a chunk of 262 144 entities takes no more memory for distances than one over 65 536 (a quarter spare)."""
+    case = par.Case(290001, 12, 8, 32, 600, 2, 8.0, seed=84, T=290001)
+    eng = _engine(case)
+    plan = eng.plan(case.qb)
+    rows = plan.export()["n_roots"]
+    _ranked(eng, plan)
+    assert _held(eng) < rows * 262144 * 4 * 0.6
+    plan.free()
