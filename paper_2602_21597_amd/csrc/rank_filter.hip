@@ -510,19 +510,22 @@ struct MergeArgs {
 // can lie below that is computed, a tenth, 64 of them and one branch a wavefront and turn.  Nearly all of these turn out farther than
 // the k-th so far; the few that are not are collected, and the first wavefront inserts those that still are before the k-th into the
 // list its lanes hold (inserting every one, and a wavefront's branches one after the other: 42 against 28 us for 512 queries x 12 952
-// entities x 400 coordinates, 42.5 against 34.5 for 1024 x 262 144 later on).  A query with more than ROOM entities, or a crowded tile, is marked (count > room,
-// overflowed) for the fp32 pass of the chunk's pieces.  ROOM leaves LDS for four workgroups a compute unit, all of 1024 queries at once.
+// entities x 400 coordinates, 42.5 against 34.5 for 1024 x 262 144 later on).
+// What the tiles found goes into one list, or, where that has no room (ROOM entities, or a crowded tile), into one after the other for
+// the pieces of the chunk; a query that has no room for a piece is marked (count > room, overflowed) for the fp32 pass of that piece
+// alone.  (512 queries x 300 000 entities x 400, 5000 of which lie together near one query: 4.05 ms with the whole chunk in fp32, 2.13 so;
+// without such a group 1.06 and 1.08.)  The distances' slabs lie over the lower bounds, which are done with by then: LDS for four
+// workgroups a compute unit, all of 1024 queries at once, or three of 256 threads.
 // MERGE_T: 128 threads, or 256 where three workgroups a compute unit hold all queries (35.4 and 29.7 us for those 512).  PRUNE_FROM: 64
 // entities are one turn, pruned or not (28.5 against 29.7 us from 128 on).
 constexpr int PIECE_TILES = RANK_PIECE / 128;
-constexpr int ROOM = 3584, BINS = 256, MERGE_WIDE_TO = 768, PRUNE_FROM = 64;
+static_assert(PIECE_TILES % 256 == 0, "a thread's words are the same ones by pieces");
+constexpr int ROOM = 4096, BINS = 256, MERGE_WIDE_TO = 768, PRUNE_FROM = 64;
 template <bool B16, int MERGE_T>
 __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) {
-    __shared__ __attribute__((aligned(16))) float slab[MERGE_T / 64][64 * slab_ld(16)];
-    __shared__ int32_t list[ROOM];
-    __shared__ float lower[ROOM];
-    static_assert(BINS * sizeof(int32_t) <= sizeof(slab), "room for the histogram");
-    int32_t* hist = reinterpret_cast<int32_t*>(&slab[0][0]);         // (done with before the first distances)
+    constexpr int SLAB_LDS = 64 * slab_ld(16);
+    __shared__ __attribute__((aligned(16))) float lower[ROOM > MERGE_T / 64 * SLAB_LDS ? ROOM : MERGE_T / 64 * SLAB_LDS];
+    __shared__ int32_t list[ROOM], hist[BINS];
     __shared__ float sd[MERGE_T], best_hi[MERGE_T / 64];
     __shared__ uint32_t nearest[MERGE_T];
     __shared__ int32_t si[MERGE_T];
@@ -534,28 +537,6 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
     __syncthreads();
     const int r_lo = g.root_off[q], r_hi = g.root_off[q + 1];
     const float step = g.grid[0];
-    float hi_min = INFINITY;
-    for (int r = r_lo; r < r_hi; ++r) {
-        uint32_t* words = g.found + (size_t)r * g.n_tx;
-        const uint32_t* pairs = g.found_pair + (size_t)(r >> 7) * g.n_tx * FOUND;
-        const float b_lo = g.base[r];
-        for (int x = t; x < g.n_tx; x += MERGE_T) {
-            const uint32_t w = words[x];
-            if (w == 0u) continue;
-            words[x] = 0u;
-            if (w == CROWDED) {
-                crowded = 1;
-                continue;
-            }
-            const int n = w & 0xFF, from = w >> 8, at = atomicAdd(&n_list, n);
-            for (int i = 0; i < n && at + i < ROOM; ++i) {
-                const uint32_t p = pairs[(size_t)x * FOUND + from + i];
-                list[at + i] = (int32_t)(x * 128 + (p & 127));
-                // (a sum that did not fit its bits bounds nothing)
-                lower[at + i] = p >> 7 ? (float)((int32_t)(p >> 7) - SUM_BIAS - 4) * step + b_lo : -INFINITY;
-            }
-        }
-    }
     float my_d = INFINITY;
     int32_t my_i = INT_MAX;
     if (wave == 0 && lane < k) {
@@ -569,156 +550,207 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
             kth_i = my_i;
         }
     }
-    __syncthreads();
-    int n = n_list;
-    if (n > ROOM || crowded) {                       // uniform
-        for (int p = t; p * PIECE_TILES < g.n_tx; p += MERGE_T) {
-            g.overflowed[p] = 1;
-            g.count[(size_t)p * gridDim.x + q] = g.room + 1;
-        }
-        return;
-    }
-    if (n == 0) return;
-    if (n > PRUNE_FROM && kth_d < INFINITY) {
-        // upper bound of a listed entity: its lower one and twice both errors (the widest branch's)
-        float both = 0.f;
-        for (int r = r_lo; r < r_hi; ++r) both = fmaxf(both, g.base[g.ldb + r] - g.base[r]);
-        auto upper = [&](int x) {
-            int32_t sum = 0;
-            for (int p = 0; p < g.parts; ++p) sum += g.slack[(size_t)p * g.lde + list[x]];
-            const int32_t sl = slack_of(sum);
-            return sl == UNBOUNDED || lower[x] == -INFINITY ? INFINITY : (lower[x] + both + (float)(2 * sl + 8) * step) * (1.f + g.rounding);
-        };
-        for (int x = t; x < n; x += MERGE_T) hi_min = fminf(hi_min, upper(x));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) hi_min = fminf(hi_min, __shfl_xor(hi_min, off, 64));
-        if (lane == 0) best_hi[wave] = hi_min;
-        for (int b = t; b < BINS; b += MERGE_T) hist[b] = 0;
-        __syncthreads();
-        const float top = kth_d;
-        hi_min = best_hi[0];
-#pragma unroll
-        for (int w = 1; w < MERGE_T / 64; ++w) hi_min = fminf(hi_min, best_hi[w]);
-        const float scale = (float)BINS / (top - hi_min);        // (top <= hi_min: nothing falls into a bin)
-        for (int x = t; x < n; x += MERGE_T) {
-            const float b = (upper(x) - hi_min) * scale;
-            if (b >= 0.f && b < (float)BINS) atomicAdd(&hist[(int)b], 1);
-        }
-        __syncthreads();
-        if (wave == 0) {   // the first bin that completes k entities (an entity may be listed by every branch)
-            int32_t c[BINS / 64], sum = 0;
-#pragma unroll
-            for (int i = 0; i < BINS / 64; ++i) {
-                c[i] = hist[lane * (BINS / 64) + i];
-                sum += c[i];
-            }
-            int32_t inc = sum;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int32_t v = __shfl_up(inc, off, 64);
-                if (lane >= off) inc += v;
-            }
-            const int want = k * (r_hi - r_lo);
-            const unsigned long long m = __ballot(inc >= want);
-            if (lane == (m ? __ffsll(m) - 1 : 0)) {
-                int32_t run = inc - sum;
-                int bin = BINS;
-#pragma unroll
-                for (int i = BINS / 64 - 1; i >= 0; --i) {
-                    int32_t upto = run;
-#pragma unroll
-                    for (int i2 = 0; i2 <= i; ++i2) upto += c[i2];
-                    if (upto >= want) bin = lane * (BINS / 64) + i;
+    // every tile column at once, or a piece after the other (a thread looks at the same words either way; seen: which of them, the last
+    // bit for all further ones, are to be cleared)
+    const int per_row = (g.n_tx + MERGE_T - 1) / MERGE_T;
+    uint32_t seen = 0u;
+    auto word_bit = [&](int r, int x) { return 1u << min((r - r_lo) * per_row + x / MERGE_T, 31); };
+    for (int x0 = 0, width = g.n_tx;;) {
+        const int x1 = min(g.n_tx, x0 + width);
+        for (int r = r_lo; r < r_hi; ++r) {
+            const uint32_t* words = g.found + (size_t)r * g.n_tx;
+            const uint32_t* pairs = g.found_pair + (size_t)(r >> 7) * g.n_tx * FOUND;
+            const float b_lo = g.base[r];
+            for (int x = x0 + t; x < x1; x += MERGE_T) {
+                const uint32_t w = words[x];
+                if (w == 0u) continue;
+                seen |= word_bit(r, x);
+                if (w == CROWDED) {
+                    crowded = 1;
+                    continue;
                 }
-                // (one bin of room for the rounding of the bin number)
-                bound = m && bin < BINS - 2 ? fminf(top, hi_min + (float)(bin + 2) / scale) : top;
+                const int n = w & 0xFF, from = w >> 8, at = atomicAdd(&n_list, n);
+                for (int i = 0; i < n && at + i < ROOM; ++i) {
+                    const uint32_t p = pairs[(size_t)x * FOUND + from + i];
+                    list[at + i] = (int32_t)(x * 128 + (p & 127));
+                    // (a sum that did not fit its bits bounds nothing)
+                    lower[at + i] = p >> 7 ? (float)((int32_t)(p >> 7) - SUM_BIAS - 4) * step + b_lo : -INFINITY;
+                }
             }
         }
         __syncthreads();
-        // in place: a slot is written by the round that reads it or a later one
-        const float most = bound * (1.f + g.rounding);
+        int n = n_list;
+        const bool over = n > ROOM || crowded;           // uniform
+        if (over || x1 < g.n_tx) {                       // (there may be another list)
+            __syncthreads();
+            if (t == 0) n_list = crowded = 0;
+        }
+        if (over && width > PIECE_TILES) {
+            width = PIECE_TILES;
+            __syncthreads();
+            continue;
+        }
+        if (x1 == g.n_tx) {                              // no word is looked at again
+            for (int r = r_lo; r < r_hi && seen; ++r)
+                for (int x = t; x < g.n_tx; x += MERGE_T)
+                    if (seen & word_bit(r, x)) g.found[(size_t)r * g.n_tx + x] = 0u;
+            if (n == 0 && !over && width == g.n_tx) return;
+        }
+        if (over) {
+            if (t == 0) {
+                const int p = x0 / PIECE_TILES;
+                g.overflowed[p] = 1;
+                g.count[(size_t)p * gridDim.x + q] = g.room + 1;
+            }
+            n = 0;
+        }
+        if (n > PRUNE_FROM && kth_d < INFINITY) {
+            // upper bound of a listed entity: its lower one and twice both errors (the widest branch's)
+            float both = 0.f;
+            for (int r = r_lo; r < r_hi; ++r) both = fmaxf(both, g.base[g.ldb + r] - g.base[r]);
+            float hi_min = INFINITY;
+            auto upper = [&](int x) {
+                int32_t sum = 0;
+                for (int p = 0; p < g.parts; ++p) sum += g.slack[(size_t)p * g.lde + list[x]];
+                const int32_t sl = slack_of(sum);
+                return sl == UNBOUNDED || lower[x] == -INFINITY ? INFINITY : (lower[x] + both + (float)(2 * sl + 8) * step) * (1.f + g.rounding);
+            };
+            for (int x = t; x < n; x += MERGE_T) hi_min = fminf(hi_min, upper(x));
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) hi_min = fminf(hi_min, __shfl_xor(hi_min, off, 64));
+            if (lane == 0) best_hi[wave] = hi_min;
+            for (int b = t; b < BINS; b += MERGE_T) hist[b] = 0;
+            __syncthreads();
+            const float top = kth_d;
+            hi_min = best_hi[0];
+#pragma unroll
+            for (int w = 1; w < MERGE_T / 64; ++w) hi_min = fminf(hi_min, best_hi[w]);
+            const float scale = (float)BINS / (top - hi_min);        // (top <= hi_min: nothing falls into a bin)
+            for (int x = t; x < n; x += MERGE_T) {
+                const float b = (upper(x) - hi_min) * scale;
+                if (b >= 0.f && b < (float)BINS) atomicAdd(&hist[(int)b], 1);
+            }
+            __syncthreads();
+            if (wave == 0) {   // the first bin that completes k entities (an entity may be listed by every branch)
+                int32_t c[BINS / 64], sum = 0;
+#pragma unroll
+                for (int i = 0; i < BINS / 64; ++i) {
+                    c[i] = hist[lane * (BINS / 64) + i];
+                    sum += c[i];
+                }
+                int32_t inc = sum;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int32_t v = __shfl_up(inc, off, 64);
+                    if (lane >= off) inc += v;
+                }
+                const int want = k * (r_hi - r_lo);
+                const unsigned long long m = __ballot(inc >= want);
+                if (lane == (m ? __ffsll(m) - 1 : 0)) {
+                    int32_t run = inc - sum;
+                    int bin = BINS;
+#pragma unroll
+                    for (int i = BINS / 64 - 1; i >= 0; --i) {
+                        int32_t upto = run;
+#pragma unroll
+                        for (int i2 = 0; i2 <= i; ++i2) upto += c[i2];
+                        if (upto >= want) bin = lane * (BINS / 64) + i;
+                    }
+                    // (one bin of room for the rounding of the bin number)
+                    bound = m && bin < BINS - 2 ? fminf(top, hi_min + (float)(bin + 2) / scale) : top;
+                }
+            }
+            __syncthreads();
+            // in place: a slot is written by the round that reads it or a later one
+            const float most = bound * (1.f + g.rounding);
+            for (int base = 0; base < n; base += MERGE_T) {
+                const int x = base + t;
+                const bool keep = x < n && !(lower[x] > most);
+                const int32_t e = x < n ? list[x] : 0;
+                __syncthreads();
+                const unsigned long long m = __ballot(keep);
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&n_near, __popcll(m));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+                if (keep) list[at] = e;
+                __syncthreads();
+            }
+            n = n_near;
+        }
         for (int base = 0; base < n; base += MERGE_T) {
-            const int x = base + t;
-            const bool keep = x < n && !(lower[x] > most);
-            const int32_t e = x < n ? list[x] : 0;
+            // 64 entities and one branch at a time, dealt to the wavefronts (a few entities of a union in one go)
+            const int parts = (min(n - base, MERGE_T) + 63) / 64, units = parts * (r_hi - r_lo);
+            nearest[t] = 0xFFFFFFFFu;
             __syncthreads();
-            const unsigned long long m = __ballot(keep);
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&n_near, __popcll(m));
-            at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
-            if (keep) list[at] = e;
+            for (int u = wave; u < units; u += MERGE_T / 64) {
+                const int part = u % parts, r = r_lo + u / parts, x = base + part * 64 + lane;
+                const int32_t e = x < n ? list[x] : 0;
+                const float dv = exact_distance<B16, 16, 3>(g.act, g.row_ids, r, r + 1, g.E, g.E16, e, g.d, lower + wave * SLAB_LDS);
+                atomicMin(&nearest[part * 64 + lane], __builtin_bit_cast(uint32_t, dv));       // (no distance is negative; NaN is above all others)
+            }
             __syncthreads();
-        }
-        n = n_near;
-    }
-    for (int base = 0; base < n; base += MERGE_T) {
-        // 64 entities and one branch at a time, dealt to the wavefronts (a few entities of a union in one go)
-        const int parts = (min(n - base, MERGE_T) + 63) / 64, units = parts * (r_hi - r_lo);
-        nearest[t] = 0xFFFFFFFFu;
-        __syncthreads();
-        for (int u = wave; u < units; u += MERGE_T / 64) {
-            const int part = u % parts, r = r_lo + u / parts, x = base + part * 64 + lane;
-            const int32_t e = x < n ? list[x] : 0;
-            const float dv = exact_distance<B16, 16, 3>(g.act, g.row_ids, r, r + 1, g.E, g.E16, e, g.d, slab[wave]);
-            atomicMin(&nearest[part * 64 + lane], __builtin_bit_cast(uint32_t, dv));       // (no distance is negative; NaN is above all others)
-        }
-        __syncthreads();
-        if (base + t < n) {
-            const float dv = __builtin_bit_cast(float, nearest[t]);
-            const int32_t id = g.ent_base + list[base + t];
-            if (before(dv, id, kth_d, kth_i)) {
-                const int at = atomicAdd(&n_new, 1);
-                sd[at] = dv;
-                si[at] = id;
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            // the lanes hold the new distances; whatever is no longer before the k-th falls out at once
-            const int m = n_new;
-            float dn[MERGE_T / 64];
-            int32_t in[MERGE_T / 64];
-            bool open[MERGE_T / 64];
-            float kd = kth_d;
-            int32_t ki = kth_i;
-#pragma unroll
-            for (int w = 0; w < MERGE_T / 64; ++w) {
-                open[w] = w * 64 + lane < m;
-                dn[w] = open[w] ? sd[w * 64 + lane] : INFINITY;
-                in[w] = open[w] ? si[w * 64 + lane] : INT_MAX;
-            }
-#pragma unroll
-            for (int w = 0; w < MERGE_T / 64; ++w) {
-                for (;;) {
-                    const unsigned long long left = __ballot(open[w] && before(dn[w], in[w], kd, ki));
-                    if (left == 0ull) break;
-                    const int from = __ffsll(left) - 1;
-                    const float dv = lane_value(dn[w], from);
-                    const int32_t id = lane_value(in[w], from);
-                    open[w] = open[w] && lane > from;
-                    if (__ballot(my_i == id) != 0ull) continue;      // listed by another branch already
-                    const bool stays = before(my_d, my_i, dv, id);
-                    const float up_d = __shfl_up(my_d, 1, 64);
-                    const int32_t up_i = __shfl_up(my_i, 1, 64);
-                    const bool up_stays = lane == 0 || before(up_d, up_i, dv, id);
-                    if (!stays) {
-                        my_d = up_stays ? dv : up_d;
-                        my_i = up_stays ? id : up_i;
-                    }
-                    if (lane >= k) {
-                        my_d = INFINITY;
-                        my_i = INT_MAX;
-                    }
-                    kd = lane_value(my_d, k - 1);
-                    ki = lane_value(my_i, k - 1);
+            if (base + t < n) {
+                const float dv = __builtin_bit_cast(float, nearest[t]);
+                const int32_t id = g.ent_base + list[base + t];
+                if (before(dv, id, kth_d, kth_i)) {
+                    const int at = atomicAdd(&n_new, 1);
+                    sd[at] = dv;
+                    si[at] = id;
                 }
             }
-            if (lane == 0) {
-                kth_d = kd;
-                kth_i = ki;
+            __syncthreads();
+            if (wave == 0) {
+                // the lanes hold the new distances; whatever is no longer before the k-th falls out at once
+                const int m = n_new;
+                float dn[MERGE_T / 64];
+                int32_t in[MERGE_T / 64];
+                bool open[MERGE_T / 64];
+                float kd = kth_d;
+                int32_t ki = kth_i;
+#pragma unroll
+                for (int w = 0; w < MERGE_T / 64; ++w) {
+                    open[w] = w * 64 + lane < m;
+                    dn[w] = open[w] ? sd[w * 64 + lane] : INFINITY;
+                    in[w] = open[w] ? si[w * 64 + lane] : INT_MAX;
+                }
+#pragma unroll
+                for (int w = 0; w < MERGE_T / 64; ++w) {
+                    for (;;) {
+                        const unsigned long long left = __ballot(open[w] && before(dn[w], in[w], kd, ki));
+                        if (left == 0ull) break;
+                        const int from = __ffsll(left) - 1;
+                        const float dv = lane_value(dn[w], from);
+                        const int32_t id = lane_value(in[w], from);
+                        open[w] = open[w] && lane > from;
+                        if (__ballot(my_i == id) != 0ull) continue;      // listed by another branch already
+                        const bool stays = before(my_d, my_i, dv, id);
+                        const float up_d = __shfl_up(my_d, 1, 64);
+                        const int32_t up_i = __shfl_up(my_i, 1, 64);
+                        const bool up_stays = lane == 0 || before(up_d, up_i, dv, id);
+                        if (!stays) {
+                            my_d = up_stays ? dv : up_d;
+                            my_i = up_stays ? id : up_i;
+                        }
+                        if (lane >= k) {
+                            my_d = INFINITY;
+                            my_i = INT_MAX;
+                        }
+                        kd = lane_value(my_d, k - 1);
+                        ki = lane_value(my_i, k - 1);
+                    }
+                }
+                if (lane == 0) {
+                    kth_d = kd;
+                    kth_i = ki;
+                }
+                if (lane == 0) n_new = 0;
             }
-            if (lane == 0) n_new = 0;
+            __syncthreads();
         }
+        x0 += width;
+        if (x0 >= g.n_tx) break;
+        __syncthreads();
+        if (t == 0) n_near = 0;
         __syncthreads();
     }
     if (wave == 0 && lane < k) {

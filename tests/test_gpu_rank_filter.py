@@ -171,6 +171,30 @@ def test_large_chunks(N, edit, kw):
         np.testing.assert_array_equal(a, b)
 
 
+# thousands of rows that are as near to a query as any lie together in a large chunk: in one of its pieces (too many for a list, of 12
+# queries: no tile has more than it has room for), on either side of the line between two (a list each, then too many), and in one piece
+# for all of 24 equal queries (a list each, but crowded tiles).  Only pieces without room go to fp32, and the results are those of the fp32 pass
+@pytest.mark.parametrize("lo,n,queries,pieces", [(150000, 10000, range(12), 1), (147712 - 2500, 5000, range(12), 0), (147712 - 4500, 9000, range(12), 2),
+                                                 (150000, 3000, [0] * 24, 1)])
+def test_dense_groups_in_large_chunks(lo, n, queries, pieces):
+    from paper_2602_21597_amd import binding
+    par.say("rank filter: %d rows from %d, %d queries" % (n, lo, len(queries)))
+    case = par.Case(320011, 12, 8, 32, 24, 2, 8.0, mix={"1p": 1.0}, seed=85, T=320011)
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb.select(np.array(queries)))
+        E = eng.tensors["E"][0]
+        E[lo:lo + n] = E[eng.rank_all(plan, 1)[0][0, 0].long()]
+        got.append([x.cpu().numpy() for x in eng.rank_all(plan, 10)])
+        if limit == 0:
+            assert binding.lib().ngdb_debug_rank_overflows(eng.ctx) == pieces
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # the last number of queries that are merged by four wavefronts each, the first by two, few entities and hundreds left after pruning, unions
 @pytest.mark.parametrize("B,edit", [(768, None), (769, None), (769, _outliers), (5, _one_cluster), (800, _one_cluster)])
 def test_merging_by_queries(B, edit):
