@@ -234,6 +234,33 @@ def test_rows_rounded_as_they_are_fused(N, d, edit):
         np.testing.assert_array_equal(a, b)
 
 
+# 256 features or more: rows that answers, thresholds and the fp32 pass take come from one fusing kernel, those that are rounded as they are
+# fused from another, and an answer compares equal to itself only if both give the same bits.  Answers in the first chunk of 65 536 and beyond,
+# the nearest entities among them (ranks that one bit would move), rows of one column part, of an uneven part and of two, features of four
+# stages, five and sixteen
+@pytest.mark.parametrize("N,d,d_sem", [(70001, 24, 256), (66001, 216, 320), (67003, 400, 1024)])
+def test_rows_of_both_fusing_kernels(N, d, d_sem):
+    import torch
+    from paper_2602_21597_amd import binding
+    par.say("rank filter: N=%d d=%d d_sem=%d" % (N, d, d_sem))
+    case = par.Case(N, 12, d, 32, 40, 2, 8.0, mix={"1p": 0.5, "2i": 0.3, "2u": 0.2}, seed=86, T=2 * N, d_sem=d_sem)
+    rng = np.random.default_rng(6)
+    off = torch.arange(0, 16 * case.B + 1, 16, dtype=torch.int32, device="cuda")
+    spread = torch.from_numpy(np.concatenate([rng.integers(0, N, (case.B, 3)), rng.integers(65536, N, (case.B, 3))], 1).astype(np.int32)).cuda()
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb)
+        near = eng.rank_all(plan, 10)
+        answers = torch.cat([spread, near[0]], 1).reshape(-1).contiguous()
+        results = [*near, *eng.rank_answers(plan, off, answers)]
+        got.append([x.cpu().numpy() for x in results])
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # the fp32 pass: fewer entities than k, one lane's four, a group of lanes, more than a workgroup's lanes; equal distances
 # beyond the list's room; a second chunk
 @pytest.mark.parametrize("N,d,B,edit", [(5, 8, 9, None), (14, 8, 9, None), (1030, 20, 20, None), (4099, 12, 9, None),
