@@ -242,8 +242,11 @@ __global__ __launch_bounds__(SF_NW * 64) void sem_fuse_kernel(const SemFuseArgs 
 // ones of the next, and each block of results leaves just before the next tile's structural rows are requested into its registers.
 // 262 144 rows of 400 coordinates and 1024 values 421 -> 366 us (floor at the rate of a copy 281), 20 000 x 128 x 512 25.5 -> 23.5,
 // 65 536 x 632 x 256 108 -> 104; but x 424 x 192 62.2 and 63.6, x 48 x 128 13.8 and 15.0.  Rows that are also put on a
-// ranking's grid stay with the kernel above: this one takes 335 instead of 393 us for 262 144 of them, but the integer sums that
-// follow, at the full rate of the vector units, then run at a lower clock: 1035 instead of 907 us, 28.0 instead of 26.5 ms a pass.
+// ranking's grid stay with the kernel above: a form of this one for them took 335 instead of 393 us for 262 144, but the integer sums that
+// follow then took 1035 instead of 907 us, 28.0 instead of 26.5 ms a pass (the cause was not looked for).
+// What the compiler does not know of here (products and accumulator loads) is checked in the listing it makes: tests/test_hand_scheduled_kernels.py.
+// It lets no vector write come just before a product that reads it; a wait in every product would do without the check and costs 1 %
+// of this kernel's time, and 8 % of sem_wgrad_kernel's (2.50 -> 2.70 ms), whose products are issued the same way.
 constexpr int ST_FROM = 256;
 constexpr int ST_NW = 4, ST_RB = SF_BU / ST_NW / 16;          // wavefronts; row blocks of each
 constexpr int ST_HL = SF_BU / 8 / ST_NW, ST_WL = 7;           // loads a wavefront and stage: its own feature rows, a quarter of the weight rows (26 used)
