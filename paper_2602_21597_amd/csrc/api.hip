@@ -355,6 +355,8 @@ bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vecto
 // Splits the weights of the three MLPs for a pass, for its backward half too if it has one (at d = 400, h = 800 scoring 1024 queries takes 415 us instead of 423 without it).
 // Without the buffer (a context
 // that never sized a workspace) the contractions split their B operands themselves.
+// (The box family has always split its own: its two MLPs do not come with pieces, and so its contractions do not reach the kernel for many
+// rows either.  Whether that pays has not been measured.)
 void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, PieceJobs* J) {
     c->have_pieces = false;
     if (c->cfg.family != NGDB_FAMILY_VEC || c->w_pieces.cap < weight_pieces_bytes(c) || !c->w_pieces.p) return;
@@ -1335,7 +1337,7 @@ constexpr int RANK_CHUNK = RANK_PIECE;
 constexpr int NEAR_CHUNK = 1 << 18;
 constexpr int64_t NEAR_PAIRS = 1 << 29;
 constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k); rows the integer grid is made from
-constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filter may leave undecided
+constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filtered ranks may leave undecided (top-k: rank_filter.hip)
 
 // Where a chunk of entity rows lies: in the table (or its bf16 copy), or, with text features, fused
 // into the context's chunk buffer by this call.  sample: there, too, RANK_SAMPLE rows spread over the table (a launch

@@ -23,13 +23,13 @@
 // Top-k: the first rows of the table are ranked in fp32; the k-th distance so far is a bound, and the
 // 8-bit sums of the next chunk leave some tens to hundreds of entities per query that can be below it, which
 // one workgroup per query computes and merges.  Chunks grow with what has been ranked.  1024 queries
-// (1171 branch rows) x 5 M entities x 400: distance tiles 182.6 ms and merges 32.6 became integer sums 17.4 (34 T
-// operations of 4 coordinates a second; the instruction alone reaches 36), rounding 2.1 and merges 2.2.
+// (1171 branch rows) x 5 M entities x 400: distance tiles 182.6 ms and merges 32.6 became integer sums 17.5 (34 T
+// operations of 4 coordinates a second; the instruction alone reaches 36) and merges 1.0.
 // Filtered ranks: the 16-bit sums decide all but about 0.1 % of the (entity, answer) comparisons: 1024
 // queries x 63 000 entities with 8 answers each, tiles 2.78 ms (0.32 of them for the answers' own
-// distances, now computed pair by pair) and counting 0.24 became 0.46 and 0.44.
-// Lists have a fixed room per query; a query whose list overflows in a chunk takes the fp32
-// pass for that chunk (launched always, its workgroups leave at once where nothing overflowed).
+// distances, now computed pair by pair) and counting 0.24 became 0.46 and 0.26.
+// Lists have a fixed room per query; a query whose list overflows takes the fp32 pass for that piece of
+// the table (launched always, its workgroups leave at once where nothing overflowed).
 #include <climits>
 
 #include "common.h"
@@ -816,8 +816,10 @@ __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step
 // some answer of the query is not decided and goes to the query's list.  Grid (parts, queries): a workgroup
 // takes every gridDim.x-th slab of 2048 entities, 8 per lane.  The thresholds of a query lie sorted in LDS: an entity looks
 // up how many are no larger than its upper bound (a search of log2 steps, 3 vector operations each), which places it in a
-// histogram whose running sums are the counts, and it is open if the last of them exceeds its lower bound.  Up to 15 answers every
-// thread has a histogram of its own (lanes that add to one word of LDS take turns); beyond, the workgroup has one.  The list is
+// histogram whose running sums are the counts, and it is open if the last of them exceeds its lower bound.  Up to ANS_OWN answers every
+// thread has a histogram of its own (lanes that add to one word of LDS take turns); beyond, the workgroup has one (us for 1024 queries x
+// 63 000 entities, own and shared: 8 answers 130 and 158, 15 answers 137 and 152; own ones for 31 answers take LDS from all: 8 answers 138, 15
+// 145, 16 151 against 157 shared, 20 153 and 153, 24 159 and 155, 31 162 and 158).  The list is
 // collected in LDS: one device-wide atomic a workgroup as a rule.  1024 queries x 63 000 entities x 8 answers: 217 us with two
 // comparisons per answer whose lanes the scalar unit counts and combines (4 operations at a quarter of the rate), 113 now; reading
 // the sums takes 60.
@@ -967,7 +969,9 @@ __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restr
 // The undecided entities of the chunk in fp32 (for the answers that their upper bound has not counted already), and the
 // chunk's counts added to the running ones.  Grid (OPEN_PARTS, queries): 64 entities at a time, dealt to the parts in turn (queries
 // have up to some hundred entities per answer, and one workgroup per query left the card to those with the longest lists: 198 us
-// against 142 for 1024 queries with 1 to 15 answers, some 440 000 rows of 1600 bytes, which is what is left).  A query whose list overflowed
+// against 142 for 1024 queries with 1 to 15 answers, some 440 000 rows of 1600 bytes, which is what is left).  Four parts, then one and
+// sixteen, us: 1024 queries of 4 answers 98, 97, 294, of 8 143, 166, 297, of 15 256, 294, 319, of 31 491, 565, 472; 64 queries of 8 answers 22,
+// 57, 32, of 15 28, 81, 36, of 40 76, 214, 54, of 60 109, 330, 69.  A query whose list overflowed
 // drops the chunk's counts (the fp32 pass of the chunk counts for it); its list count stays as the mark for that.
 constexpr int OPEN_PARTS = 4;
 template <bool B16>
