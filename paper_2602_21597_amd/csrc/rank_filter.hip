@@ -822,7 +822,8 @@ __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step
 // 145, 16 151 against 157 shared, 20 153 and 153, 24 159 and 155, 31 162 and 158).  The list is
 // collected in LDS: one device-wide atomic a workgroup as a rule.  1024 queries x 63 000 entities x 8 answers: 217 us with two
 // comparisons per answer whose lanes the scalar unit counts and combines (4 operations at a quarter of the rate), 113 now; reading
-// the sums takes 60.
+// the sums takes 60.  Queries of more than ANS_LDS answers are counted that way, the first 256 of them in LDS (128 queries, 20 of them of 256
+// answers: a ranking of 1567 us with a device-wide atomic per answer and slab for all of them, 1517 so).
 constexpr int EPT = 8, SLAB = EPT * 256, ANS_LDS = 255, ANS_OWN = 15, OPEN_KEPT = 1024;
 static_assert((65536 / SLAB) * EPT < 65536, "own counters of a chunk fit 16 bits");
 __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restrict__ sums, int ld, const int32_t* __restrict__ slack, int parts, int lde,
@@ -861,6 +862,7 @@ __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restr
             s_of[at] = t;
         }
     }
+    if (!searched) s_sum[t] = 0;
     if (t == 0) n_open = 0;
     __syncthreads();
     for (int e_lo = blockIdx.x * SLAB; e_lo < n_ent; e_lo += gridDim.x * SLAB) {
@@ -921,7 +923,7 @@ __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restr
                     c += __popcll(sure);
                     some[j] |= sure ^ __ballot(vlo[j] < th);
                 }
-                if (lane == 0 && c) atomicAdd(&closer[a], c);
+                if (lane == 0 && c) atomicAdd(a - a_lo <= ANS_LDS ? &s_sum[a - a_lo] : &closer[a], c);
             }
 #pragma unroll
             for (int j = 0; j < EPT; ++j) open[j] = some[j] >> lane & 1ull;
@@ -948,7 +950,10 @@ __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restr
         }
         __syncthreads();
     }
-    if (!searched) return;
+    if (!searched) {                                 // (at least 256 answers)
+        if (s_sum[t]) atomicAdd(&closer[a_lo + t], s_sum[t]);
+        return;
+    }
     if (own) {
         for (int b = wave; b < n_a; b += 4) {
             const uint32_t x = s_hist[b * 128 + lane], y = s_hist[b * 128 + 64 + lane];
