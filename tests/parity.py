@@ -219,7 +219,10 @@ def assert_rows_close(got, ref, name, tol=1e-3, scale=None):
     err = np.abs(got - ref).max(axis=1)
     big = scale > 1e-30
     worst = (err[big] / scale[big]).max() if big.any() else 0.0
-    assert worst <= tol, "%s: worst row-relative error %.3g" % (name, worst)
+    off = np.abs(got - ref) > tol * scale[:, None]
+    assert worst <= tol, "%s: worst row-relative error %.3g; rows (entries beyond the tolerance, the first of them): %s; errors of all rows: %s" % (
+        name, worst, [(int(i), int(off[i].sum()), np.flatnonzero(off[i])[:8].tolist()) for i in np.flatnonzero(off.any(axis=1) & big)[:8]],
+        ["%.1e" % x for x in err[:64] / np.maximum(scale[:64], 1e-300)])
     assert np.all(err[~big] <= 1e-30), name
 
 
