@@ -237,6 +237,7 @@ int ensure(ngdb_ctx_t* c, DevBuf& b, size_t bytes, Use use = Use::Any) {
     hipError_t e = device_alloc(c, b, want);
     // (what an earlier ranking has left behind stands in no other call's way; a ranking itself asks for less, see rank_buffers)
     if (e == hipErrorOutOfMemory && use != Use::Ranking && release_rank_buffers(c)) e = device_alloc(c, b, want);
+    if (e == hipErrorOutOfMemory && use == Use::Ranking) return NGDB_ERR_OOM;      // (no failure of the call yet, see no_rank_memory)
     HIPCHK(c, e);
     return NGDB_OK;
 }
@@ -1399,6 +1400,8 @@ int rank_buffers(ngdb_ctx_t* c, int R, int B, int ld, int64_t fused_rows, int bi
     return rc;
 }
 
+int no_rank_memory(ngdb_ctx_t* c) { return fail(c, NGDB_ERR_OOM, "no device memory for the buffers of a ranking"); }
+
 // Device memory that an allocation of this context can have.
 size_t device_free(const ngdb_ctx_t* c) {
     size_t avail = 0, total = 0;
@@ -1448,7 +1451,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
     RankFilter f{};
     int most = RANK_CHUNK, chunk, ld, rc;
-    while (filtered && most < NEAR_CHUNK && 2ll * most * R <= NEAR_PAIRS) most *= 2;
+    while (filtered && most < std::min(N, NEAR_CHUNK) && 2ll * most * R <= NEAR_PAIRS) most *= 2;
     if (most > c->near_most) {
         // There was no memory for such chunks.  They are tried again once as much more is free as one needs (not while the
         // stream is captured: nothing may be allocated then).
@@ -1474,7 +1477,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         }
     }
     c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
-    if (rc != NGDB_OK) return rc;
+    if (rc != NGDB_OK) return rc == NGDB_ERR_OOM ? no_rank_memory(c) : rc;
     float* dist = ptr<float>(c->rank_dist);
     Overflowed only{f.row_q, f.count, f.room, f.overflowed};
     Timed tm(c, NGDB_TK_SCORE, s);
@@ -1532,7 +1535,7 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     }
     c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
     c->rank_chunks = (N + chunk - 1) / chunk;
-    if (rc != NGDB_OK) return rc;
+    if (rc != NGDB_OK) return rc == NGDB_ERR_OOM ? no_rank_memory(c) : rc;
     float* dist = ptr<float>(c->rank_dist);
     float* thr = d_ans_dist ? d_ans_dist : ptr<float>(c->rank_thr);
     int32_t* total = ptr<int32_t>(c->rank_count);

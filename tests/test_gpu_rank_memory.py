@@ -25,6 +25,16 @@ def _limit(eng, n):
     assert binding.lib().ngdb_debug_device_limit(eng.ctx, n) == 0
 
 
+def _text(eng):
+    from paper_2602_21597_amd import binding
+    return binding.lib().ngdb_last_error(eng.ctx)
+
+
+def _allocs(eng):
+    from paper_2602_21597_amd import binding
+    return binding.lib().ngdb_debug_alloc_count(eng.ctx)
+
+
 def _ranked(eng, plan):
     return [x.cpu().numpy() for x in eng.rank_all(plan, 10)]
 
@@ -44,9 +54,10 @@ def test_rankings_in_less_memory(kw):
         try:
             got = _ranked(eng, plan)
         except NgdbError as e:
-            assert e.code == ERR_OOM
+            assert e.code == ERR_OOM and b"memory" in _text(eng)
             got = None
         if got is not None:
+            assert _text(eng) == b""         # a call that got by with less has not failed
             want = want or got
             for a, b in zip(got, want):
                 np.testing.assert_array_equal(a, b)
@@ -62,6 +73,31 @@ def test_rankings_in_less_memory(kw):
     assert len(held) == 3, held
     if kw:       # (the fused rows of a chunk, a quarter of them spare)
         assert held[0] - held[2] > 5 * (262144 - 65536) * case.d
+
+
+def test_tables_smaller_than_a_large_chunk_in_less_memory():
+    """Chunks are halved from the table's own size on: 70 000 entities, then 65 536; there is nothing in between to try again."""
+    case = par.Case(70001, 12, 64, 32, 40, 2, 8.0, seed=87, T=70001)
+    eng = _engine(case)
+    plan = eng.plan(case.qb)
+    want, held = _ranked(eng, plan), _held(eng)
+    plan.free()
+    eng = _engine(case)
+    plan = eng.plan(case.qb)
+    _limit(eng, held - 1)
+    allocs = _allocs(eng)
+    for a, b in zip(_ranked(eng, plan), want):
+        np.testing.assert_array_equal(a, b)
+    tried = _allocs(eng) - allocs
+    assert _text(eng) == b""
+    _limit(eng, -1)
+    eng2 = _engine(case)
+    plan2 = eng2.plan(case.qb)
+    allocs = _allocs(eng2)
+    _ranked(eng2, plan2)
+    assert tried == _allocs(eng2) - allocs + 1      # the distances, once for either chunk
+    plan.free()
+    plan2.free()
 
 
 def test_calls_after_a_ranking_take_its_memory():
