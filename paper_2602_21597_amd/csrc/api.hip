@@ -2143,13 +2143,14 @@ int ngdb_debug_mlp(const float* X, const float* W1, const float* b1, const float
         second.B = W1; second.ldb = d; second.b_kcontig = false; second.b_pieces = J.job[0].out_ck; second.b_kt = (h + 15) / 16;
     }
     bool emitted = false;
+    int kernel[2] = {};
     hipError_t e = launch_weight_pieces(J, s);
-    if (e == hipSuccess) e = launch_gemm_group(&first, 1, s, nullptr, &emitted);
+    if (e == hipSuccess) e = launch_gemm_group(&first, 1, s, nullptr, &emitted, &kernel[0]);
     if (e == hipSuccess && emitted) { second.a_pieces = hp; second.a_kt = kt; }
-    if (e == hipSuccess) e = launch_gemm_group(&second, 1, s, nullptr, nullptr);
+    if (e == hipSuccess) e = launch_gemm_group(&second, 1, s, nullptr, nullptr, &kernel[1]);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(buf);
-    if (used) *used = 1 | (emitted ? 2 : 0);
+    if (used) *used = 1 | (emitted ? 2 : 0) | kernel[0] << 2 | kernel[1] << 4;
     return e == hipSuccess ? NGDB_OK : (e == hipErrorInvalidValue ? NGDB_ERR_ARG : NGDB_ERR_HIP);
 }
 

@@ -189,7 +189,9 @@ struct GemmGroup {
 // *route (if given) receives the arithmetic the launch used: GEMM_FP32 or GEMM_SPLIT; *emitted (if
 // given) whether the launch wrote c_pieces (only gemm_kernel does where it reads its B operand as pieces,
 // in launches of few tiles, and only if every problem of the group asks for it).
-hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route = nullptr, bool* emitted = nullptr);
+// *kernel (if given) receives which kernel the launch went to.
+enum GemmKernel { GEMM_K_TILES, GEMM_K_PRODUCT_ONE, GEMM_K_PRODUCT_PAIR, GEMM_K_ROWS };
+hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route = nullptr, bool* emitted = nullptr, int* kernel = nullptr);
 // Weight gradients: C[M,N] = A^T B over the K rows of A [K][lda] and B [K][ldb] (the rows of an operator type),
 // and colsum[m] = sum of column m of A (the gradient of the layer's bias).  M, N and the leading
 // dimensions multiples of 4; K >= 0.  Up to GEMM_MAX_GROUP of them in one launch.

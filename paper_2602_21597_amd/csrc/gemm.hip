@@ -1384,7 +1384,8 @@ hipError_t dispatch_pieces(GemmGroup& g, bool pool, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route, bool* emitted) {
+hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s, int* route, bool* emitted, int* kernel) {
+    if (kernel) *kernel = GEMM_K_TILES;
     if (route) *route = GEMM_FP32;
     if (emitted) *emitted = false;
     GemmGroup g{};
@@ -1414,6 +1415,7 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
     for (int i = 0; i < g.count; ++i) pool = pool || g.p[i].pool_k > 0;
     bool few_rows = true;
     for (int i = 0; i < g.count; ++i) few_rows = few_rows && takes_rows_kernel(g.p[i]);
+    if (few_rows && kernel) *kernel = GEMM_K_ROWS;
     if (few_rows) return pool ? hipErrorNotSupported : dispatch_rows(g, s);
     const int arith = g.p[0].arith;
     const bool auto_split = arith == GEMM_AUTO && g.p[0].a_kcontig && max_k >= 128;
@@ -1430,6 +1432,7 @@ hipError_t launch_gemm_group(const GemmArgs* problems, int count, hipStream_t s,
         if (g.p[i].pool_k == 1 || g.p[i].pool_k > NGDB_MAX_CARD || (g.p[i].pool_k > 0 && g.p[i].M % g.p[i].pool_k)) return hipErrorInvalidValue;
     if (b_ready && (auto_split || arith == GEMM_SPLIT) && blocks_small > product_from(max_k)) {
         if (route) *route = GEMM_SPLIT;
+        if (kernel) *kernel = blocks_small <= PRODUCT_ONE_EACH ? GEMM_K_PRODUCT_ONE : GEMM_K_PRODUCT_PAIR;
         return blocks_small <= PRODUCT_ONE_EACH ? dispatch_product<1, 8>(g, pool, s) : dispatch_product<2, 4>(g, pool, s);
     }
     if (blocks_small >= 2048 && arith != GEMM_SPLIT) {

@@ -203,10 +203,12 @@ def test_box_operators_of_a_depth_in_one_launch(d, h, B):
     pb.check_forward_backward(pb.BoxCase(500, 9, d, h, B, 6, 4.0, alpha=0.2, seed=d + h))
 
 
-# both layers over many rows, one tile more than the two lines of the rule, widths that fill no tile and k that fills no block,
-# fewer blocks of k than groups of wavefronts
-@pytest.mark.parametrize("M,d,h", [(897, 132, 260), (1633, 132, 260), (4100, 148, 68), (4513, 36, 68)])
-def test_layers_of_many_rows(M, d, h):
+# both layers over many rows; the kernel of each (0: few tiles, 1: many rows, k split over eight wavefronts, 2: pairs of them).  Tiles of 32 x 64
+# on both sides of the lines, 140 and 256 (k from 256 on) and 256 (shorter k); widths that fill no tile and k that fills no block, fewer
+# blocks of k than groups of wavefronts
+@pytest.mark.parametrize("M,d,h,kernels", [(4480, 260, 36, (0, 2)), (4481, 260, 36, (1, 2)), (8192, 260, 36, (1, 2)), (8193, 260, 36, (2, 2)), (8192, 132, 36, (0, 2)),
+                                           (8193, 132, 36, (2, 2)), (1633, 132, 260, (2, 1)), (4100, 148, 68, (2, 2)), (4513, 36, 68, (2, 0))])
+def test_layers_of_many_rows(M, d, h, kernels):
     import torch
     from paper_2602_21597_amd import binding
     rng = np.random.default_rng(M)
@@ -215,7 +217,8 @@ def test_layers_of_many_rows(M, d, h):
     dev = [torch.from_numpy(a).cuda() for a in (X, W1, b1, W2, b2)]
     bar = lambda k: 0.1 * 2e-6 * max(1.0, np.sqrt(k) / 8)
     for backward in (False, True):
-        H, Y, _ = binding.debug_mlp(*dev, mask=torch.from_numpy(mask).cuda(), backward=backward)
+        H, Y, used = binding.debug_mlp(*dev, mask=torch.from_numpy(mask).cuda(), backward=backward)
+        assert (used >> 2 & 3, used >> 4 & 3) == kernels
         H, Y = (t.cpu().numpy().astype(np.float64) for t in (H, Y))
         A, B = (W2, W1) if backward else (W1.T, W2.T)
         pre = X.astype(np.float64) @ A + (0 if backward else b1)
