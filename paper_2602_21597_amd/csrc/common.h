@@ -103,7 +103,11 @@ __device__ __forceinline__ float sign_unit(float x) {
 __device__ __forceinline__ float signed_by(float c, float x) { return c * sign_unit(x); }
 // ---- the integer grid of a filtered ranking (rank_filter.hip): a coordinate becomes q = round((x - lo) * inv) within [0, top], the
 // grid point lo + step * q; what the row errs by is summed exactly.
-constexpr float SLACK = 1e-5f;       // of a row's own sums (at most 16 terms a lane, then a tree: 2e-6)
+// SLACK: of a row's own sums.  A lane adds up to 16 terms (quantise_kernel) or 52 (sem_fuse_kernel) one after the other, then a tree of at
+// most six levels follows; a rounding of half a unit each, and some more for the terms themselves: 1.5e-6 and 4e-6.
+constexpr float SLACK = 1e-5f;
+constexpr int SLACK_TERMS = 64;      // a lane may add as many
+static_assert((SLACK_TERMS + 6 + 8) * 6e-8f < SLACK, "the slack covers the sums' rounding");
 constexpr int32_t SLACK_CAP = 100000000;      // an error of this or more bounds nothing (a row's parts are added, each capped)
 __device__ __forceinline__ float to_grid(float x, float lo, float step, float inv, float top, float* err) {
     const float qf = fminf(fmaxf(rintf((x - lo) * inv), 0.f), top);           // (a NaN becomes 0; its error stays NaN)

@@ -216,13 +216,13 @@ __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ 
             s_run_i[t] = have ? out_ids[(size_t)q * k + t] : -1;
         }
         float least = INFINITY;
-    #pragma unroll 4
+#pragma unroll 4
         for (int e = 4 * t; e < n_ent; e += 4 * T) {
             const float4 v = four(e);
             least = fminf(least, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
         }
         int smaller = 0;                                 // lanes before this one
-    #pragma unroll
+#pragma unroll
         for (int j = 0; j < 64; ++j) {
             const float o = lane_value(least, j);
             smaller += (o < least || (o == least && j < lane)) ? 1 : 0;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ 
             }
         };
         if (t < k && s_run_i[t] >= 0) list(s_run[t], s_run_i[t]);
-    #pragma unroll 4
+#pragma unroll 4
         for (int e = 4 * t; e < n_ent; e += 4 * T) {
             const float4 v = four(e);
             if (v.x <= bound) list(v.x, ent_base + e);
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ 
                     const float4 v = four(e);
                     look(v.x, ent_base + e); look(v.y, ent_base + e + 1); look(v.z, ent_base + e + 2); look(v.w, ent_base + e + 3);
                 }
-    #pragma unroll
+#pragma unroll
                 for (int off = 32; off > 0; off >>= 1) {
                     const float od = __shfl_xor(md, off, 64);
                     const int oi = __shfl_xor(mi, off, 64);

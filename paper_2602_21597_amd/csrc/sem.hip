@@ -94,6 +94,7 @@ __device__ __forceinline__ bf16x8 join8(short4v a, short4v b) {
 constexpr int SF_BU = 256, SF_N = 208, SF_NBLK = SF_N / 16, SF_KS = 64;
 constexpr int SF_NW = 8;                                      // wavefronts: 32 rows x 208 coordinates each (104 accumulator registers)
 constexpr int SF_HL = SF_BU / 8, SF_WL = 32;                  // loads per stage: feature rows, weight rows (26 used)
+static_assert(SF_NBLK * 4 <= SLACK_TERMS, "a lane's part of a row's error");
 constexpr int SF_STAGE = (SF_HL + SF_WL) * 1024, SF_NB = 2, SF_PER_WAVE = (SF_HL + SF_WL) / SF_NW;
 // BITS: the rows also go onto the integer grid of a ranking, from the accumulators.  For 65 536 rows of 400 coordinates and 1024 feature
 // values 86 -> 99 us; the pass that read the rows again took 27.
@@ -678,7 +679,7 @@ hipError_t launch_sem_fuse(const SemFuseArgs& a, hipStream_t s) {
 int sem_wgrad_splits(int64_t n_rows_bound, int d, int ds) {
     const int tiles = ((d + WG_M - 1) / WG_M) * ((ds + WG_SEM - 1) / WG_SEM);
     const int64_t stages = (n_rows_bound + WG_KS - 1) / WG_KS;
-    // one resident set of workgroups, no second round: the four stages in LDS leave room for one
+    // one resident set of workgroups, no second round: the five stages in LDS leave room for one
     // workgroup per compute unit; the splits of a launch are dealt to the 8 dies in turn, 32
     // compute units each
     const int cap = std::max(1, 32 / tiles) * 8;
