@@ -923,7 +923,10 @@ __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restr
                     c += __popcll(sure);
                     some[j] |= sure ^ __ballot(vlo[j] < th);
                 }
-                if (lane == 0 && c) atomicAdd(a - a_lo <= ANS_LDS ? &s_sum[a - a_lo] : &closer[a], c);
+                if (lane == 0 && c) {
+                    if (a - a_lo <= ANS_LDS) atomicAdd(&s_sum[a - a_lo], c);
+                    else atomicAdd(&closer[a], c);
+                }
             }
 #pragma unroll
             for (int j = 0; j < EPT; ++j) open[j] = some[j] >> lane & 1ull;
