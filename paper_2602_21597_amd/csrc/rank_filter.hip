@@ -823,7 +823,7 @@ __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step
 // collected in LDS: one device-wide atomic a workgroup as a rule.  1024 queries x 63 000 entities x 8 answers: 217 us with two
 // comparisons per answer whose lanes the scalar unit counts and combines (4 operations at a quarter of the rate), 113 now; reading
 // the sums takes 60.  Queries of more than ANS_LDS answers are counted that way, the first 256 of them in LDS (128 queries, 20 of them of 256
-// answers: a ranking of 1567 us with a device-wide atomic per answer and slab for all of them, 1517 so).
+// answers: a ranking of 1570 us with a device-wide atomic per answer and slab for all of them, 1534 so).
 constexpr int EPT = 8, SLAB = EPT * 256, ANS_LDS = 255, ANS_OWN = 15, OPEN_KEPT = 1024;
 static_assert((65536 / SLAB) * EPT < 65536, "own counters of a chunk fit 16 bits");
 __global__ __launch_bounds__(256) void count_sure_kernel(const uint32_t* __restrict__ sums, int ld, const int32_t* __restrict__ slack, int parts, int lde,
