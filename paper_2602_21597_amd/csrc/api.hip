@@ -1333,10 +1333,11 @@ constexpr int RANK_CHUNK = RANK_PIECE;
 // A filtered top-k takes chunks of up to NEAR_CHUNK: what a chunk costs beside its sums (merging, the launches of an fp32 pass that
 // finds nothing to do) is 50 us whatever its size.  5 million fused entities x 1024 queries 28.5 ms in chunks of 65 536, 27.7 of twice
 // that, 26.6 of four times that; a table of 2.5 million x 512 queries 7.7, 7.06, 6.8.  NEAR_PAIRS bounds the (branch row, entity) pairs of a
-// chunk, for which the tiles need half a byte each to say what they found (256 MiB).  The fp32 pass walks a chunk in pieces of RANK_CHUNK,
-// so that the distances take no more memory than without the filter.
-constexpr int NEAR_CHUNK = 1 << 18;
-constexpr int64_t NEAR_PAIRS = 1 << 29;
+// chunk, for which the tiles need half a byte each to say what they found (256 MiB).  The fp32 pass walks a chunk by as many pieces of RANK_CHUNK
+// as have distances of 256 MiB (NEAR_DIST of them), at least one, so that the distances take no more memory than those of an unfiltered pass of 1024 rows;
+// its launches, which normally find nothing to do, cost 2.2 us each (345 queries x 717 000 entities x 292: 1314 us a piece at a time, 1304 two).
+constexpr int NEAR_CHUNK = RANK_PIECES * RANK_CHUNK;
+constexpr int64_t NEAR_PAIRS = 1 << 29, NEAR_DIST = 1 << 26;
 constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k); rows the integer grid is made from
 constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filtered ranks may leave undecided (top-k: rank_filter.hip)
 
@@ -1450,20 +1451,22 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
     const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
     RankFilter f{};
-    int most = RANK_CHUNK, chunk, ld, rc;
+    int most = RANK_CHUNK, chunk, at_once, ld, rc;
     while (filtered && most < std::min(N, NEAR_CHUNK) && 2ll * most * R <= NEAR_PAIRS) most *= 2;
     if (most > c->near_most) {
         // There was no memory for such chunks.  They are tried again once as much more is free as one needs (not while the
         // stream is captured: nothing may be allocated then).
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        const size_t more = (c->cfg.d_sem > 0 ? (size_t)most * d * sizeof(float) : 0) + rank_filter_layout(c, 8, R, B, most, nullptr, &f);
+        const size_t more = (size_t)NEAR_DIST * sizeof(float) + (c->cfg.d_sem > 0 ? (size_t)most * d * sizeof(float) : 0) + rank_filter_layout(c, 8, R, B, most, nullptr, &f);
         if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone && device_free(c) >= c->near_free + more + more / 4) c->near_most = INT32_MAX;
         (void)hipGetLastError();
         most = std::min(most, c->near_most);
     }
     for (bool emptied = false, shorter = false;; emptied = true) {
         chunk = std::min(N, most);
-        ld = (std::min(chunk, RANK_CHUNK) + 3) & ~3;
+        at_once = RANK_CHUNK;                // (short of memory: a piece)
+        while (!emptied && at_once < chunk && 2ll * at_once * R <= NEAR_DIST) at_once *= 2;
+        ld = (std::min(chunk, at_once) + 3) & ~3;
         rc = rank_buffers(c, R, B, ld, chunk, filtered ? 8 : 0, chunk, &f);
         if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
             if (rc == NGDB_OK && shorter) c->near_free = device_free(c);
@@ -1479,7 +1482,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     c->rank_overflowed = rc == NGDB_OK ? f.overflowed : nullptr;
     if (rc != NGDB_OK) return rc == NGDB_ERR_OOM ? no_rank_memory(c) : rc;
     float* dist = ptr<float>(c->rank_dist);
-    Overflowed only{f.row_q, f.count, f.room, f.overflowed};
+    Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
     Timed tm(c, NGDB_TK_SCORE, s);
     // filtered: the sample's k-th distance lets k / sample of the first chunk pass, and chunks grow with what has
     // been ranked (each at most 12 times that), so that a list holds 12 k entities and some that are only near it
@@ -1500,13 +1503,14 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
             if (c->cfg.d_sem == 0) HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_near_tile(f, R, cnt, d_dist, topk, s));
             HIPCHK(c, launch_near_merge(f, i_piece, act, roots, pl->d_root_off, B, er.rows, er.rows16, e0, cnt, topk, d_dist, d_ids, s));
-            for (int p0 = 0; p0 < cnt; p0 += RANK_CHUNK, ++i_piece) {
-                const int n = std::min(RANK_CHUNK, cnt - p0);
+            for (int p0 = 0; p0 < cnt; p0 += at_once) {
+                const int n = std::min(at_once, cnt - p0);
                 const size_t at = (size_t)p0 * d;
                 only.count = f.count + (size_t)(p0 / RANK_CHUNK) * B;
                 only.any = f.overflowed + i_piece;
                 HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows + at, n, d, dist, ld, s, er.rows16 ? er.rows16 + at : nullptr, &only));
                 HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0 + p0, n, topk, false, d_dist, d_ids, s, &only));
+                i_piece += (n + RANK_CHUNK - 1) / RANK_CHUNK;
             }
         }
         e0 += cnt;
@@ -1540,7 +1544,7 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     float* thr = d_ans_dist ? d_ans_dist : ptr<float>(c->rank_thr);
     int32_t* total = ptr<int32_t>(c->rank_count);
     int32_t* in_chunk = total + n_ans;
-    Overflowed only{f.row_q, f.count, f.room, f.overflowed};
+    Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
     Timed tm(c, NGDB_TK_SCORE, s);
     HIPCHK(c, launch_fill_zero_i32(total, 2 * n_ans, s));
     // distance of every listed answer to its query (the arithmetic of the all-entity pass, so an answer

@@ -381,16 +381,20 @@ struct ScoreArgs {
 hipError_t launch_score(const ScoreArgs& a, bool train, hipStream_t s);
 
 // ---------------------------------------------------------------- ranking (rank.hip)
+// Entities of a piece of the table: an unfiltered ranking takes one at a time, the filter chunks of several (RANK_PIECES at most).
+constexpr int RANK_PIECE = 1 << 16, RANK_PIECES = 4;
 // dist[r*ld + e] = ||act[row_ids[r]] - Emat[e]||_1 for r < n_rows, e < n_ent.
 // With off (box family, 0 <= alpha <= 1): the box distance of (act row, off row) to the entity row.
 // With Emat16 (bf16 bit patterns, same shape as Emat) the entity rows are read from it.
 // With `only` (this call completes a filtered pass): row tiles without a query whose list overflowed
-// are left out, and so are, in the two launches below, the queries whose list did not.
+// are left out, and so are, in the two launches below, the queries whose list did not.  launch_l1_tile and launch_topk_merge
+// take several pieces of RANK_PIECE entities at a time, each with its own lists.
 struct Overflowed {
     const int32_t* row_q;      // query of every branch row
-    int32_t* count;            // [queries] listed entities; more than room: overflowed
+    int32_t* count;            // [pieces, queries] listed entities; more than room: overflowed
     int room;
-    const int32_t* any;        // whether there is such a query
+    const int32_t* any;        // [pieces] whether there is such a query
+    int n_queries;
 };
 hipError_t launch_l1_tile(const float* act, const float* off, float alpha, const int32_t* row_ids, int n_rows,
                           const float* Emat, int n_ent, int d, float* dist, int ld, hipStream_t s,
@@ -412,8 +416,6 @@ hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off,
                              int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s,
                              const Overflowed* only = nullptr);
 
-// Entities whose distances to every branch row a ranking holds at a time.  The filter takes chunks of several such pieces.
-constexpr int RANK_PIECE = 1 << 16;
 // Ranking with a filter on integer sums (rank_filter.hip): buffers of one pass.  Rows as words of 4
 // (bits = 8) or 2 (bits = 16) coordinates, word-major; leading dimensions are multiples of 128.
 struct RankFilter {

@@ -30,10 +30,15 @@ constexpr int DC = 16;
 // contributes relu(a - o) + alpha * min(a, o) = max(alpha * a, a - (1 - alpha) * o), a = |e - c|;
 // the offsets are staged already multiplied by (1 - alpha): five VALU operations per coordinate.
 // Emat16 (if set): the entity rows are read from this bf16 copy of Emat.
-// count (if set): tiles without a row whose query has count > room are left out.
+// count (if set): tiles without a row whose query has count > room for the tile's piece of the table are left out.
 // Three wavefronts per SIMD and two coordinates unrolled: left to itself the compiler unrolled all sixteen, fetched them
 // ahead into 512 registers and ran one wavefront per SIMD, waiting for LDS and copying between register files.  At 603 boxes
 // (737 rows) x 300 000 entities x 316 coordinates 14.4 -> 6.4 ms, at 512 vectors x 200 000 x 256 2.56 -> 1.52 ms.
+__device__ __forceinline__ bool marked_piece(const int32_t* __restrict__ any, int pieces) {
+    int32_t some = 0;
+    for (int p = 0; p < pieces; ++p) some |= any[p];
+    return some != 0;
+}
 template <bool BOX, int RPL, int EPL>
 __global__ __launch_bounds__(256, 3) void l1_tile_kernel(const float* __restrict__ act, const float* __restrict__ off,
                                                       float alpha, const int32_t* __restrict__ row_ids,
@@ -41,8 +46,9 @@ __global__ __launch_bounds__(256, 3) void l1_tile_kernel(const float* __restrict
                                                       const uint16_t* __restrict__ Emat16, int n_ent, int d,
                                                       float* __restrict__ dist, int ld, const int32_t* __restrict__ row_q,
                                                       const int32_t* __restrict__ count, int room,
-                                                      const int32_t* __restrict__ any) {
-    if (any && *any == 0) return;                          // uniform
+                                                      const int32_t* __restrict__ any, int n_queries) {
+    const int pieces = (n_ent + RANK_PIECE - 1) / RANK_PIECE;
+    if (any && !marked_piece(any, pieces)) return;         // uniform
     constexpr int TQ = 16 * RPL, TE = 16 * EPL, LDQ = TQ + 4, LDE = TE + 4;
     constexpr int LQ = (TQ * 4 + 255) / 256, LE = (TE * 4 + 255) / 256;     // float4 per thread and stage
     __shared__ __attribute__((aligned(16))) float Ys[2][DC][LDQ];
@@ -51,12 +57,16 @@ __global__ __launch_bounds__(256, 3) void l1_tile_kernel(const float* __restrict
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
     const int r0 = blockIdx.y * TQ;
+    uint32_t marked = 0u;                                  // pieces for which the rows of this tile are needed
     if (count) {
         const int r = r0 + tid;
-        if (!__syncthreads_or(tid < TQ && r < n_rows && count[row_q[r]] > room)) return;
+        for (int p = 0; p < pieces; ++p)
+            if (__syncthreads_or(tid < TQ && r < n_rows && count[(size_t)p * n_queries + row_q[r]] > room)) marked |= 1u << p;
+        if (marked == 0u) return;                          // uniform
     }
     // (a launch that only completes a filtered pass has few workgroups, each with several entity tiles)
     for (int e0 = blockIdx.x * TE; e0 < n_ent; e0 += gridDim.x * TE) {
+        if (count && !(marked >> (e0 / RANK_PIECE) & 1u)) continue;          // uniform; a piece is a multiple of every tile
 
         const float* yrow[LQ];
         const float* orow[LQ];
@@ -190,15 +200,20 @@ __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ 
                                                       int n_queries, int ent_base, int n_ent, int k, bool first_chunk,
                                                       float* __restrict__ out_dist, int32_t* __restrict__ out_ids,
                                                       int32_t* __restrict__ count, int room, const int32_t* __restrict__ any) {
-    if (REST && *any == 0) return;                         // uniform
+    const int pieces = REST ? (n_ent + RANK_PIECE - 1) / RANK_PIECE : 1;
+    if (REST && !marked_piece(any, pieces)) return;        // uniform
     __shared__ float s_d[TOPK_LIST], s_bound[TOPK_T / 64], s_run[KMAX];
     __shared__ int s_i[TOPK_LIST], s_run_i[KMAX], s_n;
     const int t = threadIdx.x, T = blockDim.x, lane = t & 63, wave = t >> 6;
     for (int q = blockIdx.x; q < n_queries; q += gridDim.x) {
-        if (REST && count[q] <= room) continue;         // uniform: the filter has dealt with this query's piece
+        uint32_t marked = 0u;
+        for (int p = 0; REST && p < pieces; ++p)
+            if (count[(size_t)p * n_queries + q] > room) marked |= 1u << p;
+        if (REST && marked == 0u) continue;              // uniform: the filter has dealt with this query's pieces
         const int r0 = root_off[q], nb = root_off[q + 1] - r0;
         const float* row = dist + (size_t)r0 * ld;
-        auto four = [&](int e) {                         // entities e .. e + 3, those past the end not a number
+        auto four = [&](int e) {                         // entities e .. e + 3, those past the end or dealt with not a number
+            if (REST && !(marked >> (e / RANK_PIECE) & 1u)) return make_float4(NAN, NAN, NAN, NAN);
             float4 v = *reinterpret_cast<const float4*>(row + e);
             for (int b = 1; b < nb; ++b) {
                 const float4 w = *reinterpret_cast<const float4*>(row + (size_t)b * ld + e);
@@ -312,7 +327,7 @@ __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ 
             }
         }
         if (!REST) return;
-        if (t == 0) count[q] = 0;
+        if (t < pieces) count[(size_t)t * n_queries + q] = 0;
         __syncthreads();
     }
 }
@@ -455,11 +470,12 @@ hipError_t launch_l1_tile(const float* act, const float* off, float alpha, const
     const int epl = (long)((n_rows + 16 * rpl - 1) / (16 * rpl)) * ((n_ent + 127) / 128) < 512 ? 4 : 8;
     int tiles_e = (n_ent + 16 * epl - 1) / (16 * epl);
     if (only) tiles_e = std::min(tiles_e, 64);
+    if (only && n_ent > RANK_PIECES * RANK_PIECE) return hipErrorInvalidValue;
     const dim3 grid(tiles_e, (n_rows + 16 * rpl - 1) / (16 * rpl)), block(256);
 #define NGDB_L1(BOX, R, C)                                                                                             \
     hipLaunchKernelGGL((l1_tile_kernel<BOX, R, C>), grid, block, 0, s, act, off, alpha, row_ids, n_rows, Emat, Emat16,   \
                        n_ent, d, dist, ld, only ? only->row_q : nullptr, only ? (const int32_t*)only->count : nullptr,   \
-                       only ? only->room : 0, only ? only->any : nullptr)
+                       only ? only->room : 0, only ? only->any : nullptr, only ? only->n_queries : 0)
 #define NGDB_L1_SIZES(BOX)                                                                  \
     if (rpl == 8) { if (epl == 8) NGDB_L1(BOX, 8, 8); else NGDB_L1(BOX, 8, 4); }             \
     else if (rpl == 4) { if (epl == 8) NGDB_L1(BOX, 4, 8); else NGDB_L1(BOX, 4, 4); }        \

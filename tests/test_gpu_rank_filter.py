@@ -173,9 +173,10 @@ def test_large_chunks(N, edit, kw):
 
 # thousands of rows that are as near to a query as any lie together in a large chunk: in one of its pieces (too many for a list, of 12
 # queries: no tile has more than it has room for), on either side of the line between two (a list each, then too many), and in one piece
-# for all of 24 equal queries (a list each, but crowded tiles).  Only pieces without room go to fp32, and the results are those of the fp32 pass
+# for all of 24 equal queries (a list each, but crowded tiles).  Only pieces without room go to fp32, and the results are those of the fp32 pass,
+# which takes a chunk at once, two pieces at a time (300 queries) or one (600)
 @pytest.mark.parametrize("lo,n,queries,pieces", [(150000, 10000, range(12), 1), (147712 - 2500, 5000, range(12), 0), (147712 - 4500, 9000, range(12), 2),
-                                                 (150000, 3000, [0] * 24, 1)])
+                                                 (150000, 3000, [0] * 24, 1), (147712 - 4500, 9000, [0] * 300, 2), (150000, 3000, [0] * 600, 1)])
 def test_dense_groups_in_large_chunks(lo, n, queries, pieces):
     from paper_2602_21597_amd import binding
     par.say("rank filter: %d rows from %d, %d queries" % (n, lo, len(queries)))
