@@ -1166,14 +1166,22 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
                                  ptr<float>(c->loss_terms), B > 0 ? 1.f / (2.f * B) : 0.f, d_loss, s_tab));
         return NGDB_OK;
     };
+    // who updates the rows resolves for itself: the launch that ends the step, or plain rows' own wavefronts
+    const bool unresolved = (!aside && short_pass) || (!sem && table_takes_once(te, short_pass, max_rows));
+    LossSum loss_sum{};
+    if (unresolved) {
+        te.src = e_src; te.pair_coef = ptr<float>(c->coef); te.pair_win = sem ? nullptr : ptr<int32_t>(c->win);
+        te.n_rowsrc = hp.n_anchor; te.row_base = hp.n_slots; te.B = B; te.K = K;
+        loss_sum = LossSum{ptr<float>(c->loss_terms), B, B > 0 ? 1.f / (2.f * B) : 0.f, d_loss};
+    }
     if (aside) {
         HIPCHK(c, hipEventRecord(c->ev_fork, stream));
         HIPCHK(c, hipStreamWaitEvent(s_tab, c->ev_fork, 0));
-        if ((rc = resolve_records()) != NGDB_OK) return rc;
+        if (!unresolved && (rc = resolve_records()) != NGDB_OK) return rc;
         te.later = ptr<int32_t>(c->later); te.n_later = ptr<int32_t>(c->n_uniq) + 1;
         {
             Timed tm(c, NGDB_TK_TABLE_E, s_tab);
-            HIPCHK(c, launch_table_update(te, ah, short_pass, s_tab));
+            HIPCHK(c, launch_table_update(te, ah, short_pass, max_rows, s_tab));
         }
         HIPCHK(c, hipEventRecord(c->ev_join, s_tab));
         te.pick = te.later; te.n_uniq_dev = te.n_later;
@@ -1189,15 +1197,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     if (rc != NGDB_OK) return rc;
 
     // 6. the other table rows, relation tables, dense Adam
-    const bool unresolved = !aside && short_pass;       // the launch that ends the step resolves for itself
-    LossSum loss_sum{};
-    if (unresolved) {
-        te.src = e_src; te.pair_coef = ptr<float>(c->coef); te.pair_win = sem ? nullptr : ptr<int32_t>(c->win);
-        te.n_rowsrc = hp.n_anchor; te.row_base = hp.n_slots; te.B = B; te.K = K;
-        loss_sum = LossSum{ptr<float>(c->loss_terms), B, B > 0 ? 1.f / (2.f * B) : 0.f, d_loss};
-    } else if (!aside && (rc = resolve_records()) != NGDB_OK) {
-        return rc;
-    }
+    if (!aside && !unresolved && (rc = resolve_records()) != NGDB_OK) return rc;
     tr.g_bf16 = nullptr; tr.mask = nullptr;
     tr.P = c->prm.R.p; tr.Mo = c->prm.R.m; tr.Vo = c->prm.R.v;
     tr.uniq = pl->d_r_uniq; tr.seg_off = pl->d_r_seg_off; tr.n_uniq_dev = pl->d_n_r_uniq;
@@ -1225,7 +1225,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     if (!short_pass) {    // the passes that run long on their own: not in the launch that ends the step
         if (!aside) {
             Timed tm(c, NGDB_TK_TABLE_E, stream);
-            HIPCHK(c, launch_table_update(te, ah, false, stream));
+            HIPCHK(c, launch_table_update(te, ah, false, max_rows, stream));
         }
         Timed tm(c, NGDB_TK_ADAM, stream);
         HIPCHK(c, launch_dense_adam(job, ah, stream));

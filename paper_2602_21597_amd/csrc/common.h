@@ -530,8 +530,10 @@ struct TableArgs {
 hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_base, int B, int K, const float* coef,
                           const int32_t* win, float* rec_coef, int32_t* rec_row, const float* loss_terms,
                           float loss_scale, float* loss, hipStream_t s);
-// few: by one workgroup per compute unit (a pass that has time and should leave the chip to others)
-hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, hipStream_t s);
+// few: by one workgroup per compute unit (a pass that has time and should leave the chip to others); max_rows: at most so many
+// touched rows.  table_takes_once: by a wavefront a row, which may resolve the records of its row (a.src)
+bool table_takes_once(const TableArgs& a, bool few, int64_t max_rows);
+hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, int64_t max_rows, hipStream_t s);
 // The end of a step in one launch: the main table (at most max_rows touched rows; 0: not part of it), up to two small
 // plain tables of the same width (no text features, box weights or bf16 copy: the relation tables, each of at most
 // small_rows touched rows), and the dense tensors.

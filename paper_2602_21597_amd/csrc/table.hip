@@ -117,7 +117,8 @@ __device__ __forceinline__ void row_store(float4* p, float4 v) {
 // With the choice open, the stores of either path count as "maybe issued" for the compiler, and the
 // wait for the next row's parameter rows, requested before them, also waits for the stores.
 // PICK: a.pick may choose the rows; otherwise a.later may leave some out.
-template <int NCH, bool SEM, bool BOX, bool SH, bool NT = false, bool UPD = false, bool PICK = false>
+// ONE: one row to a wavefront, number wave_global; nothing is requested for a next one.
+template <int NCH, bool SEM, bool BOX, bool SH, bool NT = false, bool UPD = false, bool PICK = false, bool ONE = false>
 __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& hp, int wave_global, int n_waves) {
     const int lane = threadIdx.x & 63;
     const int d4 = a.d >> 2;
@@ -157,7 +158,7 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
         t1_n = a.seg_off[u_n + 1];                             \
     } while (0)
 #define NGDB_FETCH_ROWS()                                                                                      \
-    if (!PICK && a.later) first_n = a.rec_row[t0_n];                                                           \
+    if (!PICK && a.later) first_n = ONE && a.src ? a.src[t0_n] - a.n_rowsrc : a.rec_row[t0_n];                                                           \
     _Pragma("unroll") for (int ch = 0; ch < NCH; ++ch) {                                                      \
         if (update || !SEM) p_n[ch] = row_load<NT>(reinterpret_cast<const float4*>(a.P + (size_t)row_n * a.d) + colc[ch]); \
         if (update) {                                                                                          \
@@ -169,7 +170,8 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
         NGDB_FETCH_INDEX(wave_global);
         NGDB_FETCH_ROWS()
     }
-    for (int i = wave_global; i < n_uniq; i += n_waves) {
+    const int i_end = ONE ? min(wave_global + 1, n_uniq) : n_uniq;
+    for (int i = wave_global; i < i_end; i += n_waves) {
         const int u = u_n;
         const bool skip = !PICK && __builtin_amdgcn_readfirstlane(first_n) < 0;     // its gradient rows are not there yet
         if (skip && lane == 0) a.later[atomicAdd(a.n_later, 1)] = u;
@@ -193,7 +195,7 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
             }
             g[ch] = zero4;
         }
-        NGDB_FETCH_INDEX(i + n_waves);
+        if (!ONE) NGDB_FETCH_INDEX(i + n_waves);
         // SH: the row as the scoring pass read it (rounded to bf16)
         float4 psr[SH ? NCH : 1];
         if (SH) {
@@ -209,7 +211,7 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
             const int tl = base + min(lane, n - 1);
             int32_t my_row;
             float my_coef = 0.f;
-            if (PICK && a.src) {
+            if ((PICK || ONE) && a.src) {
                 const Record r = record_of(a.src[tl], a.n_rowsrc, a.row_base, a.B, a.K, a.pair_coef, a.pair_win);
                 my_row = r.row;
                 my_coef = r.coef;
@@ -303,7 +305,7 @@ __device__ __forceinline__ void table_rows(const TableArgs& a, const AdamHyper& 
                     }
             }
         }
-        NGDB_FETCH_ROWS()
+        if (!ONE) { NGDB_FETCH_ROWS() }
         if (SEM) {
             uint2* brow = reinterpret_cast<uint2*>(a.g_bf16 + (size_t)u * a.d);
 #pragma unroll
@@ -369,6 +371,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (BOX && 
                                   (int)((gridDim.x * blockDim.x) >> 6));
 }
 
+// Tables streamed from HBM: a workgroup of four rows, four wavefronts, and the launch has as many as there can be rows (those past
+// the last touched one leave).  A wavefront that walks rows has its requests wait for the stores of the row before, which complete
+// in order with them; here a wavefront ends behind its stores and the next workgroup takes its place, so that the card always has
+// loads to serve, and a launch of another stream finds a place at once.  Bare access pattern (2 M of 2.5 M rows of 400
+// floats, parameter and two moments read and written): 4.77 TB/s walked, 5.10 like this, 5.45 with neighbouring rows on one die; 2, 4
+// or 8 rows to a wavefront lose most of it again.  Step over 2.5 million entities 6.42 -> 5.98 ms, with text features
+// over 5 million 15.05 -> 14.45.
+// Dies take runs of ONCE_RUN workgroups, whose rows share lines of the cache (rows are not a multiple of 128 bytes): runs of 16
+// to 256 and an eighth of the table to a die are alike (5.96 to 6.00 ms; 6.14 without).  Text features, whose pairs read sign codes from
+// all over memory, gain nothing by it (14.3 to 14.45 ms without, 14.45 to 14.6 with runs of 8 to 512).
+// The records of plain rows are resolved here, by the wavefront that needs them (a.src): the launch that resolves them all is
+// 145 us of a step over 2.5 million entities before the first row, this 5.98 -> 5.91 ms.  With text features, where it is half of
+// that, 14.53 -> 14.63 ms: they keep the launch.
+constexpr int ONCE_RUN = 64;
+template <int NCH, bool SEM, bool BOX, bool SH>
+__global__ __launch_bounds__(256) void table_once_kernel(const TableArgs a, const AdamHyper hp) {
+    const int b = (int)blockIdx.x, in = b % (8 * ONCE_RUN);
+    const int group = SEM ? b : b - in + (in & 7) * ONCE_RUN + (in >> 3);
+    // (the wavefront's number is the same in all its lanes: kept in a scalar register)
+    table_rows<NCH, SEM, BOX, SH, true, true, false, true>(a, hp, __builtin_amdgcn_readfirstlane(group * 4 + (int)(threadIdx.x >> 6)), 1);
+}
+
 // The end of a step: the first workgroups walk up to two small plain tables of the same width (the relation tables), the
 // next ones the rows of the main table that are left (in a small step without a second stream: all of them, their records
 // unresolved, a launch less where everything waits for the backward pass anyway), the last
@@ -414,7 +438,7 @@ hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_b
 }
 
 namespace {
-// The number of touched rows is only known on the device: a fixed grid walks them.  Four times as many workgroups as
+// The number of touched rows is only known on the device: a fixed grid walks them, where table_once_kernel does not take them.  Four times as many workgroups as
 // fit at once, so that the launches of the other stream get their turn (6.42, 6.46 and 6.48 ms with 16, 4 and 2 times as
 // many for the step over 2.5 M entities, 15.9 and 16.4 ms with 8 and 2 with text features).  Rows with text features carry
 // twice the traffic: sixteen times as many as fit keep the last round of workgroups short (15.6 ms; 15.8 with 4096 or
@@ -423,6 +447,7 @@ namespace {
 // 2.72, 2048 x 512 at 400 3.93 and 3.89; from 500 000 entities down no difference beyond 1 %.
 constexpr int TABLE_BLOCKS = 256 * 16;
 constexpr int TABLE_BLOCKS_SEM = 4 * TABLE_BLOCKS;
+constexpr int64_t ONCE_MAX_ROWS = 1 << 25;      // (a launch holds less than 2^32 threads)
 
 bool table_args_ok(const TableArgs& a) {
     const bool sem = a.g_bf16 != nullptr, box = a.off != nullptr;
@@ -445,8 +470,20 @@ bool table_args_ok(const TableArgs& a) {
     } while (0)
 }  // namespace
 
-hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, hipStream_t s) {
+bool table_takes_once(const TableArgs& a, bool few, int64_t max_rows) {
+    return a.streaming && !few && !a.g_out && max_rows <= ONCE_MAX_ROWS;
+}
+
+hipError_t launch_table_update(const TableArgs& a, const AdamHyper& hp, bool few, int64_t max_rows, hipStream_t s) {
     if (!table_args_ok(a)) return hipErrorInvalidValue;
+    if (table_takes_once(a, few, max_rows)) {
+        const unsigned groups = (unsigned)((max_rows + 3) / 4 + 8 * ONCE_RUN - 1) / (8 * ONCE_RUN) * (8 * ONCE_RUN);
+        if (groups == 0) return hipSuccess;
+#define NGDB_ONCE(NCH, SEM_, BOX_, SH_) hipLaunchKernelGGL((table_once_kernel<NCH, SEM_, BOX_, SH_>), dim3(groups), dim3(256), 0, s, a, hp)
+        NGDB_TABLE(NGDB_ONCE);
+#undef NGDB_ONCE
+        return hipGetLastError();
+    }
     const int blocks = few ? 256 : a.g_bf16 ? TABLE_BLOCKS_SEM : TABLE_BLOCKS;
 #define NGDB_WALK(NCH, SEM_, BOX_, SH_)                                                                                                   \
     do {                                                                                                                                  \

@@ -130,6 +130,29 @@ def test_tables_beside_the_backward_pass(N, d, B, K, d_sem, bf16):
     assert all(torch.equal(a, b) for a, b in zip(out[0][2], out[1][2]))
 
 
+# tables beyond the caches, a wavefront a row (second stream) against the rows walked at the end of the step (one stream, up to
+# 65 536 rows): rows that fill part of a 256 B piece, of one, two and four pieces; touched rows of less than a window of workgroups
+# and of many; boxes; rows with no pair, with one and with hundreds (the workload's heavy-tailed positives)
+@pytest.mark.parametrize("N,d,B,K,box", [(200000, 120, 70, 700, False), (65000, 384, 61, 1000, False), (24000, 1024, 40, 1200, False),
+                                         (65000, 384, 61, 1000, True), (120000, 200, 65, 900, True)])
+def test_tables_beyond_the_caches_a_wavefront_a_row(N, d, B, K, box):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    names = wl.configs.EPFO9 if box else wl.configs.ALL14
+    qb = wl.make_batch(wl.make_kg(N, 7, 5 * N, 2.1, 1), B, {n: 1.0 for n in names}, 2)
+    negs = torch.from_numpy(wl.make_negatives(N, B, K, 5)).cuda()
+    out = []
+    for streams in (1, 2):
+        eng = Engine(N, 7, d, 520, 12.0, num_streams=streams, family=binding.FAMILY_BOX if box else binding.FAMILY_VEC)
+        eng.bind_numpy((wl.make_box_params if box else wl.make_params)(N, 7, d, 520, 3))
+        plan = eng.plan(qb)
+        losses = [float(eng.train_step(plan, negs)) for _ in range(2)]
+        out.append((losses, [t for name in eng.tensor_names() for t in eng.tensors[name]]))
+        plan.free()
+    assert out[0][0] == out[1][0]
+    assert all(torch.equal(a, b) for a, b in zip(out[0][1], out[1][1]))
+
+
 # operators of a depth in one launch: widths that fill no tile, the widest hidden layer, the limit of weights a layer (for any
 # depth, for depths of few row blocks) and beyond it; one query, row blocks that are nearly empty, intersections of two to eight inputs
 @pytest.mark.parametrize("d,h,B", [(4, 4, 5), (20, 36, 1), (36, 100, 30), (64, 512, 40), (128, 256, 90), (132, 256, 40), (256, 128, 17),
