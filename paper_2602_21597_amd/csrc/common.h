@@ -377,6 +377,7 @@ struct ScoreArgs {
     float alpha = 0.f;
     // candidate rows from a bf16 copy of the table [N, d] (bit patterns) instead of E
     const uint16_t* E16 = nullptr;
+    bool streaming = false;    // E is a table beyond the caches
 };
 hipError_t launch_score(const ScoreArgs& a, bool train, hipStream_t s);
 

@@ -27,7 +27,8 @@ __device__ __forceinline__ int col_of(int ch, int lane) {
     return B16 ? (ch >> 1) * 128 + 2 * lane + (ch & 1) : ch * 64 + lane;
 }
 typedef uint32_t score_u32x4 __attribute__((ext_vector_type(4)));
-template <int NCH, bool B16>
+typedef float score_f32x4 __attribute__((ext_vector_type(4)));
+template <int NCH, bool B16, bool NT>
 __device__ __forceinline__ void load_row(const ScoreArgs& a, int32_t e, int lane, int d4, float4 (&dst)[NCH]) {
     if (B16) {   // the bf16 copy of the table: 16 bytes (8 coordinates) per lane and chunk pair; d % 8 == 0
         const score_u32x4* row = reinterpret_cast<const score_u32x4*>(a.E16 + (size_t)e * a.d);
@@ -39,9 +40,13 @@ __device__ __forceinline__ void load_row(const ScoreArgs& a, int32_t e, int lane
             dst[2 * g + 1] = bf16x4_to_f32(make_uint2(v[2], v[3]));
         }
     } else {
-        const float4* row = reinterpret_cast<const float4*>(a.E + (size_t)e * a.d);
+        const score_f32x4* row = reinterpret_cast<const score_f32x4*>(a.E + (size_t)e * a.d);
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) dst[ch] = row[min(ch * 64 + lane, d4 - 1)];
+        for (int ch = 0; ch < NCH; ++ch) {
+            const score_f32x4* at = row + min(ch * 64 + lane, d4 - 1);
+            const score_f32x4 v = NT ? __builtin_nontemporal_load(at) : *at;
+            dst[ch] = make_float4(v[0], v[1], v[2], v[3]);
+        }
     }
 }
 
@@ -60,7 +65,9 @@ __device__ __forceinline__ void load_row(const ScoreArgs& a, int32_t e, int lane
 // candidate loop.  Stores under a lane condition inside the loop would make every wait in it a wait
 // for everything outstanding (the compiler cannot count requests that may or may not be issued),
 // the row requested ahead included.
-template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16, bool STASH>
+// NT: rows of a table beyond the caches, by non-temporal loads: hardly any is read again before it is gone anyway (1024 x 1000
+// candidates of 2.5 million rows of 400 floats, the whole call 423 -> 400 us; the step of 4096 x 1025 5.85 -> 5.80 ms).
+template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16, bool STASH, bool NT>
 __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int i = blockIdx.x;
@@ -117,9 +124,9 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     float4 cur[NCH], nxt[NCH];
     int c = c_lo + wave;
     int32_t e_nxt = cand_id(a, i, has_pos, min(c + NW, c_hi - 1));
-    if (c < c_hi) load_row<NCH, B16>(a, cand_id(a, i, has_pos, c), lane, d4, cur);
+    if (c < c_hi) load_row<NCH, B16, NT>(a, cand_id(a, i, has_pos, c), lane, d4, cur);
     for (; c < c_hi; c += NW) {
-        load_row<NCH, B16>(a, e_nxt, lane, d4, nxt);
+        load_row<NCH, B16, NT>(a, e_nxt, lane, d4, nxt);
         e_nxt = cand_id(a, i, has_pos, min(c + 2 * NW, c_hi - 1));
         float best = INFINITY;
         int bw = 0;
@@ -316,37 +323,51 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     }
 }
 
+constexpr int SCORE_LONG = 60;             // candidates of a wavefront
 constexpr int STASH_MAX_PAIRS = 4096;     // pairs per query whose results fit the LDS stash (48 KB)
-template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16, bool STASH>
+template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16, bool STASH, bool NT>
 hipError_t launch_stash(const ScoreArgs& a, size_t lds, int parts, hipStream_t s) {
     if (lds > 64 * 1024)
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH, NT>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH>), dim3(a.B, parts), dim3(NW * 64), lds, s, a);
+    hipLaunchKernelGGL((score_kernel<NCH, NW, TRAIN, MASK, BOX, B16, STASH, NT>), dim3(a.B, parts), dim3(NW * 64), lds, s, a);
     return hipGetLastError();
 }
-template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16 = false>
+template <int NCH, int NW, bool TRAIN, bool MASK, bool BOX, bool B16 = false, bool NT = false>
 hipError_t launch_variant(const ScoreArgs& a, size_t lds, hipStream_t s) {
     const int CT = a.C + (a.pos ? 1 : 0);
     // forward only: few queries share their lists over enough workgroups of 4 wavefronts to cover the chip, at least
-    // four candidates a wavefront (one query with 1000 candidates: 24 us in one workgroup, 6 in 63)
-    const int parts = TRAIN ? 1 : std::max(1, std::min((2048 + a.B - 1) / a.B, (CT + 4 * NW - 1) / (4 * NW)));
+    // four candidates a wavefront (one query with 1000 candidates: 24 us in one workgroup, 6 in 63).  Half as many workgroups
+    // as fit at once where that leaves a wavefront SCORE_LONG candidates and more: memory serves fewer wavefronts faster (the whole
+    // call with 1024 x 1000 candidates 388 -> 372 us at d = 400, 1000 x 2000 at 200 400 -> 368, 300 x 1000 at 400 168 -> 160, but 700 x
+    // 300 at 100 115 and 119, 64 x 500 at 512 94 and 98, 32 x 1000 at 400 108 and 113)
+    const int groups = (int64_t)a.B * CT >= (int64_t)1024 * NW * SCORE_LONG ? 1024 : 2048;
+    const int parts = TRAIN ? 1 : std::max(1, std::min((groups + a.B - 1) / a.B, (CT + 4 * NW - 1) / (4 * NW)));
     const int slice = (CT + parts - 1) / parts;
     const size_t stash = (size_t)slice * (TRAIN ? 3 : 1) * sizeof(float);
     if (slice <= STASH_MAX_PAIRS && lds + stash <= 150 * 1024)
-        return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, true>(a, lds + stash, parts, s);
-    return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, false>(a, lds, parts, s);
+        return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, true, NT>(a, lds + stash, parts, s);
+    return launch_stash<NCH, NW, TRAIN, MASK, BOX, B16, false, NT>(a, lds, parts, s);
 }
 
 template <int NCH, int NW>
 hipError_t launch_nw(const ScoreArgs& a, bool train, size_t lds, hipStream_t s) {
-    if (a.off) return train ? launch_variant<NCH, NW, true, false, true>(a, lds, s)
-                            : launch_variant<NCH, NW, false, false, true>(a, lds, s);
-    if (a.E16) return train ? launch_variant<NCH, NW, true, false, false, true>(a, lds, s)
-                            : launch_variant<NCH, NW, false, false, false, true>(a, lds, s);
-    if (train && a.mask) return launch_variant<NCH, NW, true, true, false>(a, lds, s);
-    if (train) return launch_variant<NCH, NW, true, false, false>(a, lds, s);
-    return launch_variant<NCH, NW, false, false, false>(a, lds, s);
+    if constexpr (NW == 4) {                // (forward only: never by more wavefronts)
+        if (!train) {
+            if (a.off && a.streaming) return launch_variant<NCH, NW, false, false, true, false, true>(a, lds, s);
+            if (a.off) return launch_variant<NCH, NW, false, false, true>(a, lds, s);
+            if (a.E16) return launch_variant<NCH, NW, false, false, false, true>(a, lds, s);
+            if (a.streaming) return launch_variant<NCH, NW, false, false, false, false, true>(a, lds, s);
+            return launch_variant<NCH, NW, false, false, false>(a, lds, s);
+        }
+    }
+    if (!train) return hipErrorInvalidValue;
+    if (a.off && a.streaming) return launch_variant<NCH, NW, true, false, true, false, true>(a, lds, s);
+    if (a.off) return launch_variant<NCH, NW, true, false, true>(a, lds, s);
+    if (a.E16) return launch_variant<NCH, NW, true, false, false, true>(a, lds, s);
+    if (a.mask) return launch_variant<NCH, NW, true, true, false>(a, lds, s);
+    if (a.streaming) return launch_variant<NCH, NW, true, false, false, false, true>(a, lds, s);
+    return launch_variant<NCH, NW, true, false, false>(a, lds, s);
 }
 
 template <int NCH>

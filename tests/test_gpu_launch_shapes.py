@@ -65,10 +65,12 @@ def test_weight_gradients_are_as_exact_as_fp32_products(K, hidden):
     assert rms[0] <= 1.05 * rms[1], rms
 
 
-@pytest.mark.parametrize("B,C", [(1, 1), (1, 15), (1, 17), (1, 1000), (3, 4097), (40, 33)])
-def test_candidate_lists_shared_by_workgroups(B, C):
+# (from 245 760 pairs on fewer workgroups; the last: a table beyond the caches)
+@pytest.mark.parametrize("B,C,N", [(1, 1, 3000), (1, 15, 3000), (1, 17, 3000), (1, 1000, 3000), (3, 4097, 3000), (40, 33, 3000),
+                                   (128, 1920, 3000), (128, 1919, 3000), (24, 50, 1200000)])
+def test_candidate_lists_shared_by_workgroups(B, C, N):
     import torch
-    case = par.Case(3000, 10, 60, 40, B, 2, 8.0, seed=17, T=9000)
+    case = par.Case(N, 10, 60, 40, B, 2, 8.0, seed=17, T=3 * N)
     cand = np.random.default_rng(C).integers(0, case.N, (B, C)).astype(np.int32)
     eng = case.engine()
     plan = eng.plan(case.qb)
