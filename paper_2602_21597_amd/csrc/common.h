@@ -463,8 +463,8 @@ hipError_t launch_answer_distance(const float* act, const float* off, float alph
 // ---------------------------------------------------------------- index (index.hip)
 struct IndexBuffers {   // device scratch owned by the context, sized for n_keys
     int32_t *keys_a, *keys_b, *vals_a, *vals_b;   // [n_keys]
-    int32_t* hist;                                // [256 * n_tiles] + scan scratch
-    int32_t* scan_tmp;                            // block sums
+    int32_t* hist;                                // [256 * n_tiles] + totals of the digits
+    int32_t* scan_tmp;                            // heads of a tile
     int32_t *uniq, *seg_off;                      // [n_keys], [n_keys+1]
     int32_t* n_uniq;                              // device scalar
 };

@@ -2,17 +2,19 @@
 // contributions to an embedding table -- anchors, positives, negatives -- are
 // grouped by row id with a stable least-significant-digit radix sort, so that
 // the scatter-add of the backward pass becomes one atomic-free segmented sum per
-// touched row, in a fixed order.  Every pass is three kernels (per-tile digit
-// histogram, exclusive scan of the digit-major histogram, stable scatter); no
-// kernel contains a data-dependent wait.
+// touched row, in a fixed order.  A pass counts the digits of every tile and
+// scatters the tiles, whose places a scan of these counts gives; no kernel
+// contains a data-dependent wait.
 //
 // The build runs beside the forward pass and is bound by its launches, not by its bytes, until there are
 // millions of keys.  Up to SMALL_KEYS keys one workgroup sorts everything in LDS (700 keys of the
 // smallest workload: 14 launches and 32 us became one of 9 us); up to OWN_TILES tiles every workgroup of the
-// scatter adds up the histogram for itself, and up to OWN_KEYS keys the segment heads before it too (five launches
-// for two passes); up to MID_TILES tiles the histogram is
-// scanned by one launch instead of three, each workgroup adding up what lies before its digit (at
-// 66 000 keys 8 launches instead of 14); beyond that this would read the histogram too often.
+// scatter adds up the counts for itself, and up to OWN_KEYS keys the segment heads before it too (five launches
+// for two passes); beyond, a launch scans the tiles of every digit.
+// A tile is put in order in LDS and leaves as runs of equal digits: written from where the keys lie, four bytes at a time all over
+// the output, a pass over 4.2 million keys took 80 to 90 us.  MEASURED
+#include <algorithm>
+#include <type_traits>
 #include "common.h"
 
 namespace ngdb {
@@ -20,12 +22,18 @@ namespace {
 
 constexpr int RADIX_BITS = 8;
 constexpr int RADIX = 1 << RADIX_BITS;
-constexpr int SORT_THREADS = 256;
-constexpr int SORT_ITEMS = 4;                        // keys per thread
-constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS; // keys per workgroup
-constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
+constexpr int SORT_THREADS = 512, SORT_WAVES = SORT_THREADS / 64;
+// Keys of a thread; a tile is SORT_THREADS x ITEMS keys, SORT_WAVES pieces of ITEMS rounds of 64 in their order.
+constexpr int FEW_ITEMS = 4, MID_ITEMS = 8, MANY_ITEMS = 16;
+constexpr int OWN_TILES = 64;            // most tiles whose counts a workgroup adds up for itself
+constexpr int64_t FEW_KEYS = 80000, MID_KEYS = (int64_t)OWN_TILES * SORT_THREADS * MID_ITEMS;
+static_assert((FEW_KEYS + SORT_THREADS * FEW_ITEMS - 1) / (SORT_THREADS * FEW_ITEMS) <= OWN_TILES, "short arrays have few tiles");
+constexpr int64_t OWN_KEYS = FEW_KEYS;   // most keys whose heads a workgroup counts for itself
+inline int items_of(int64_t n) { return n <= FEW_KEYS ? FEW_ITEMS : n <= MID_KEYS ? MID_ITEMS : MANY_ITEMS; }
+inline int tiles_of(int64_t n) {
+    const int64_t tile = (int64_t)SORT_THREADS * items_of(n);
+    return (int)((n + tile - 1) / tile);
+}
 
 // The keys of a pass: the sorted ones of the pass before, or (FIRST) head and tail one after the other, the
 // value then being the position.
@@ -41,24 +49,27 @@ struct KeySource {
 };
 
 // hist[digit * n_tiles + tile] = number of keys of the tile with that digit
-template <bool FIRST>
+template <bool FIRST, int ITEMS>
 __global__ __launch_bounds__(SORT_THREADS) void hist_kernel(const KeySource<FIRST> src, int64_t n, int shift, int n_tiles,
                                                             int32_t* __restrict__ hist) {
     __shared__ int32_t h[RADIX];
-    h[threadIdx.x] = 0;
+    const int64_t base = (int64_t)blockIdx.x * (SORT_THREADS * ITEMS) + threadIdx.x;
+    int32_t key[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) key[r] = src.key(min(base + r * SORT_THREADS, n - 1));
+    if (threadIdx.x < RADIX) h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
-    for (int r = 0; r < SORT_ITEMS; ++r) {
-        const int64_t i = base + (int64_t)r * SORT_THREADS + threadIdx.x;
-        if (i < n) atomicAdd(&h[(src.key(i) >> shift) & (RADIX - 1)], 1);
-    }
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+        if (base + r * SORT_THREADS < n) atomicAdd(&h[(key[r] >> shift) & (RADIX - 1)], 1);
     __syncthreads();
-    hist[(size_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < RADIX) hist[(size_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
 }
 
-// ---- exclusive scan of int32 in three steps: tile sums, scan of the sums, tile scan
+// exclusive scan over the threads of a workgroup of WAVES wavefronts, *total the sum
+template <int WAVES>
 __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t* total) {
-    __shared__ int32_t wsum[SCAN_THREADS / 64];
+    __shared__ int32_t wsum[WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t inc = v;
 #pragma unroll
@@ -71,7 +82,7 @@ __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t* tota
     __syncthreads();
     int32_t woff = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         if (w < wave) woff += wsum[w];
         tot += wsum[w];
     }
@@ -79,146 +90,127 @@ __device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t* tota
     return woff + inc - v;
 }
 
-template <bool HEADS>
-__device__ __forceinline__ int32_t scan_input(const int32_t* __restrict__ in, int64_t i) {
-    if (!HEADS) return in[i];
-    return (i == 0 || in[i] != in[i - 1]) ? 1 : 0;   // segment head flag over sorted keys
-}
-
-template <bool HEADS>
-__global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(const int32_t* __restrict__ in, int64_t n,
-                                                                 int32_t* __restrict__ sums) {
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    int32_t s = 0;
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (base + k < n) s += scan_input<HEADS>(in, base + k);
-    int32_t tot;
-    block_exclusive_scan(s, &tot);
-    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-}
-
-// one workgroup: exclusive scan of sums[0..m) in place, grand total to *total
-__global__ __launch_bounds__(SCAN_THREADS) void scan_top_kernel(int32_t* __restrict__ sums, int m,
-                                                                int32_t* __restrict__ total) {
+// Exclusive scan of every digit's row of hist, in place, its sum to totals: a workgroup a digit.
+__global__ __launch_bounds__(256) void scan_rows_kernel(int32_t* __restrict__ hist, int n_tiles, int32_t* __restrict__ totals) {
+    int32_t* row = hist + (size_t)blockIdx.x * n_tiles;
     int32_t carry = 0;
-    for (int base = 0; base < m; base += SCAN_THREADS) {
-        const int i = base + threadIdx.x;
-        const int32_t v = i < m ? sums[i] : 0;
-        int32_t tot;
-        const int32_t ex = block_exclusive_scan(v, &tot);
-        if (i < m) sums[i] = carry + ex;
-        carry += tot;
-    }
-    if (threadIdx.x == 0 && total) total[0] = carry, total[1] = 0;
-}
-
-// HEADS=false: out[i] = exclusive prefix.  HEADS=true: for every head position i
-// with rank u: uniq[u] = keys[i], seg_off[u] = i; the last workgroup closes seg_off.
-template <bool HEADS>
-__global__ __launch_bounds__(SCAN_THREADS) void scan_apply_kernel(const int32_t* __restrict__ in, int64_t n,
-                                                                  const int32_t* __restrict__ sums,
-                                                                  int32_t* __restrict__ out,
-                                                                  int32_t* __restrict__ seg_off,
-                                                                  const int32_t* __restrict__ total) {
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    int32_t v[SCAN_ITEMS];
-    int32_t s = 0;
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        v[k] = base + k < n ? scan_input<HEADS>(in, base + k) : 0;
-        s += v[k];
-    }
-    int32_t tot;
-    int32_t run = sums[blockIdx.x] + block_exclusive_scan(s, &tot);
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        if (base + k < n) {
-            if (!HEADS) {
-                out[base + k] = run;
-            } else if (v[k]) {
-                out[run] = in[base + k];
-                seg_off[run] = (int32_t)(base + k);
-            }
+    for (int base = 0; base < n_tiles; base += 1024) {
+        int32_t x[4], sum = 0, all;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = base + (int)threadIdx.x * 4 + j;
+            x[j] = i < n_tiles ? row[i] : 0;
+            sum += x[j];
         }
-        run += v[k];
+        int32_t run = carry + block_exclusive_scan<4>(sum, &all);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = base + (int)threadIdx.x * 4 + j;
+            if (i < n_tiles) row[i] = run;
+            run += x[j];
+        }
+        carry += all;
     }
-    if (HEADS && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) seg_off[*total] = (int32_t)n;
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-// Exclusive scan of a short digit-major histogram in one launch: workgroup `digit` adds up the rows before its own
-// and scans its own (n_tiles <= MID_TILES <= SCAN_THREADS), out of place.
-constexpr int MID_TILES = 256;
-__global__ __launch_bounds__(SCAN_THREADS) void scan_rows_kernel(const int32_t* __restrict__ hist, int n_tiles,
-                                                                 int32_t* __restrict__ offs) {
-    const int digit = blockIdx.x, t = threadIdx.x;
-    // 16 bytes a lane, eight loads on the way (one 4-byte load after the other: 18 us at 66 tiles, 33 at 128)
-    int32_t before = 0;
-    const int n_before = digit * n_tiles, n4 = n_before >> 2;
-    const int4* h4 = reinterpret_cast<const int4*>(hist);
-    for (int i = t; i < n4; i += 8 * SCAN_THREADS) {
-        int4 x[8];
+// The heads of a tile's segments: bit l of heads[r] = key r * 64 + l of this wavefront's piece starts one.
+template <int ITEMS>
+__device__ __forceinline__ int32_t tile_heads(const int32_t* __restrict__ keys, int64_t n, int64_t piece, int32_t (&key)[ITEMS],
+                                              unsigned long long (&heads)[ITEMS]) {
+    const int lane = threadIdx.x & 63;
+    int32_t last = keys[max((int64_t)0, min(piece, n) - 1)], count = 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = h4[min(i + j * SCAN_THREADS, n4 - 1)];
+    for (int r = 0; r < ITEMS; ++r) key[r] = keys[min(piece + r * 64 + lane, n - 1)];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) before += i + j * SCAN_THREADS < n4 ? (x[j].x + x[j].y) + (x[j].z + x[j].w) : 0;
+    for (int r = 0; r < ITEMS; ++r) {
+        const int64_t i = piece + r * 64 + lane;
+        int32_t before = __shfl_up(key[r], 1, 64);
+        if (lane == 0) before = last;
+        last = lane_value(key[r], 63);
+        heads[r] = __ballot(i < n && (i == 0 || key[r] != before));
+        count += __popcll(heads[r]);
     }
-    if (t < (n_before & 3)) before += hist[n4 * 4 + t];
-    int32_t base, row;
-    block_exclusive_scan(before, &base);
-    const int32_t v = t < n_tiles ? hist[(size_t)digit * n_tiles + t] : 0;
-    const int32_t ex = block_exclusive_scan(v, &row);
-    if (t < n_tiles) offs[(size_t)digit * n_tiles + t] = base + ex;
+    return count;
 }
 
-// Segment heads of a short sorted array in one launch after the tile sums: like scan_apply_kernel<true>, each workgroup
-// adding up the sums of the tiles before it (at most MID_TILES of them).
-// OWN: without sums, each counting the heads before it (at most OWN_KEYS keys).
-constexpr int OWN_KEYS = 16384;
-template <bool OWN>
-__global__ __launch_bounds__(SCAN_THREADS) void heads_kernel(const int32_t* __restrict__ keys, int64_t n,
+// sums[tile] = number of its heads
+template <int ITEMS>
+__global__ __launch_bounds__(SORT_THREADS) void head_sums_kernel(const int32_t* __restrict__ keys, int64_t n, int32_t* __restrict__ sums) {
+    __shared__ int32_t wsum[SORT_WAVES];
+    const int wave = threadIdx.x >> 6;
+    int32_t key[ITEMS];
+    unsigned long long heads[ITEMS];
+    const int32_t count = tile_heads<ITEMS>(keys, n, ((int64_t)blockIdx.x * SORT_WAVES + wave) * (64 * ITEMS), key, heads);
+    if ((threadIdx.x & 63) == 0) wsum[wave] = count;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t all = 0;
+        for (int w = 0; w < SORT_WAVES; ++w) all += wsum[w];
+        sums[blockIdx.x] = all;
+    }
+}
+
+// For every head i with rank u: uniq[u] = keys[i], seg_off[u] = i; the last workgroup closes seg_off.  A workgroup adds up the
+// sums of the tiles before its own.  OWN: without sums, each counting the heads before it (at most OWN_KEYS keys).
+template <bool OWN, int ITEMS>
+__global__ __launch_bounds__(SORT_THREADS) void heads_kernel(const int32_t* __restrict__ keys, int64_t n,
                                                              const int32_t* __restrict__ sums, int32_t* __restrict__ uniq,
                                                              int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) {
-    int32_t base, all, tot;
-    int32_t mine = 0;
+    __shared__ int32_t wsum[SORT_WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t piece = ((int64_t)blockIdx.x * SORT_WAVES + wave) * (64 * ITEMS);
+    int32_t key[ITEMS], mine = 0, base;
+    unsigned long long heads[ITEMS];
+    const int32_t count = tile_heads<ITEMS>(keys, n, piece, key, heads);
     if (OWN) {
-        const int n4 = (int)blockIdx.x * (SCAN_TILE / 4);
-        for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * SCAN_THREADS) {
-            int4 k[4];
-            int32_t last[4];
+        // (16 bytes a lane, eight requests on the way; the key before a group of four by a request of its own)
+        const int n4 = (int)blockIdx.x * (SORT_THREADS * ITEMS / 4);
+        for (int i0 = threadIdx.x; i0 < n4; i0 += 8 * SORT_THREADS) {
+            int4 k[8];
+            int32_t last[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = min(i0 + j * SCAN_THREADS, n4 - 1);
+            for (int j = 0; j < 8; ++j) {
+                const int i = min(i0 + j * SORT_THREADS, n4 - 1);
                 k[j] = reinterpret_cast<const int4*>(keys)[i];
                 last[j] = keys[max(4 * i - 1, 0)];
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = i0 + j * SCAN_THREADS;
-                if (i >= n4) break;
-                mine += (i == 0 || k[j].x != last[j] ? 1 : 0) + (k[j].y != k[j].x ? 1 : 0) + (k[j].z != k[j].y ? 1 : 0) + (k[j].w != k[j].z ? 1 : 0);
+            for (int j = 0; j < 8; ++j) {
+                const int i = i0 + j * SORT_THREADS;
+                if (i < n4)
+                    mine += (i == 0 || k[j].x != last[j] ? 1 : 0) + (k[j].y != k[j].x ? 1 : 0) + (k[j].z != k[j].y ? 1 : 0) + (k[j].w != k[j].z ? 1 : 0);
             }
         }
     } else {
-        mine = (int)threadIdx.x < (int)blockIdx.x ? sums[threadIdx.x] : 0;
+        for (int i = threadIdx.x; i < (int)blockIdx.x; i += SORT_THREADS) mine += sums[i];
     }
-    block_exclusive_scan(mine, &base);
-    const int64_t first = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    int32_t v[SCAN_ITEMS], s = 0;
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        v[k] = first + k < n ? scan_input<true>(keys, first + k) : 0;
-        s += v[k];
+    block_exclusive_scan<SORT_WAVES>(mine, &base);
+    if (lane == 0) wsum[wave] = count;
+    __syncthreads();
+    int32_t run = base, all = base;
+#pragma unroll
+    for (int w = 0; w < SORT_WAVES; ++w) {
+        run += w < wave ? wsum[w] : 0;
+        all += wsum[w];
     }
-    int32_t run = base + block_exclusive_scan(s, &tot);
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (v[k]) {
-            uniq[run] = keys[first + k];
-            seg_off[run++] = (int32_t)(first + k);
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        if ((heads[r] >> lane) & 1) {
+            const int32_t u = run + __popcll(heads[r] & ((1ull << lane) - 1ull));
+            uniq[u] = key[r];
+            seg_off[u] = (int32_t)(piece + r * 64 + lane);
         }
-    all = base + tot;
+        run += __popcll(heads[r]);
+    }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
         seg_off[all] = (int32_t)n;
         n_uniq[0] = all;
         n_uniq[1] = 0;
     }
 }
+
+__global__ void no_segments_kernel(int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) { seg_off[0] = n_uniq[0] = n_uniq[1] = 0; }
 
 // Lanes of the wavefront that hold a valid key with the lane's digit
 __device__ __forceinline__ unsigned long long digit_peers(bool valid, int digit) {
@@ -231,77 +223,90 @@ __device__ __forceinline__ unsigned long long digit_peers(bool valid, int digit)
     return peers;
 }
 
-// Stable scatter of one radix pass.  The tile is walked in rounds of 256
-// consecutive keys (thread t takes key round*256 + t), so the order inside the
-// tile is (round, wavefront, lane); the rank of a key among equal digits is
-// running count of earlier rounds + counts of lower wavefronts + lower lanes.
-// OWN: offs is the histogram itself (at most OWN_TILES tiles), scanned by every workgroup.
-constexpr int OWN_TILES = 32;
-template <bool FIRST, bool OWN>
+// Stable scatter of one radix pass.  Every wavefront walks its piece of the tile in rounds of 64 keys and counts the digits of its own
+// as it goes: a key's place among equal digits is the count so far + the lower lanes of the round.  With the counts of the
+// wavefronts before it and of the smaller digits that is its place in the tile, where it is put in LDS; the tile is then written from
+// there, neighbours next to one another.
+// OWN: offs is the histogram itself (at most OWN_TILES tiles), scanned by every workgroup; else the scan of its rows and totals.
+template <bool FIRST, bool OWN, int ITEMS>
 __global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const KeySource<FIRST> src, int64_t n, int shift, int n_tiles,
-                                                               const int32_t* __restrict__ offs,
-                                                               int32_t* __restrict__ keys_out,
-                                                               int32_t* __restrict__ vals_out) {
-    __shared__ int32_t running[RADIX];                    // global position of the next key per digit
-    __shared__ int32_t wcnt[SORT_THREADS / 64][RADIX];    // per wavefront counts of the current round
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                                               const int32_t* __restrict__ offs, const int32_t* __restrict__ totals,
+                                                               int32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out) {
+    constexpr int TILE = SORT_THREADS * ITEMS;
+    __shared__ int32_t sk[TILE], sv[TILE];
+    __shared__ int32_t cnt[SORT_WAVES][RADIX];            // of a wavefront; then the place of its first key of the digit in the tile
+    __shared__ int32_t to[RADIX];                         // what is added to a place in the tile
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t base = (int64_t)blockIdx.x * TILE, piece = base + wave * (64 * ITEMS);
+    int32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int64_t i = min(piece + r * 64 + lane, n - 1);
+        key[r] = src.key(i);
+        val[r] = src.val(i);
+    }
+    // of digit t: keys of all tiles and of those before this one
+    int32_t before = 0, total = 0, all;
     if (OWN) {
-        int32_t before = 0, total = 0, all;
+        if (t < RADIX)
 #pragma unroll
-        for (int i0 = 0; i0 < OWN_TILES; i0 += 8) {
-            if (i0 >= n_tiles) break;
-            int32_t x[8];
+            for (int i0 = 0; i0 < OWN_TILES; i0 += 8) {
+                if (i0 >= n_tiles) break;
+                int32_t x[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = offs[threadIdx.x * n_tiles + min(i0 + i, n_tiles - 1)];
+                for (int i = 0; i < 8; ++i) x[i] = offs[t * n_tiles + min(i0 + i, n_tiles - 1)];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                before += i0 + i < (int)blockIdx.x ? x[i] : 0;
-                total += i0 + i < n_tiles ? x[i] : 0;
+                for (int i = 0; i < 8; ++i) {
+                    before += i0 + i < (int)blockIdx.x ? x[i] : 0;
+                    total += i0 + i < n_tiles ? x[i] : 0;
+                }
             }
-        }
-        running[threadIdx.x] = block_exclusive_scan(total, &all) + before;
-    } else {
-        running[threadIdx.x] = offs[(size_t)threadIdx.x * n_tiles + blockIdx.x];
+    } else if (t < RADIX) {
+        before = offs[(size_t)t * n_tiles + blockIdx.x];
+        total = totals[t];
     }
-    for (int w = 0; w < SORT_THREADS / 64; ++w) wcnt[w][threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * SORT_TILE;
-    int32_t key[SORT_ITEMS], val[SORT_ITEMS];
+    for (int i = t; i < SORT_WAVES * RADIX; i += SORT_THREADS) (&cnt[0][0])[i] = 0;
+    const int32_t global = block_exclusive_scan<SORT_WAVES>(total, &all) + before;     // (behind its barriers the counts are zero)
+    volatile int32_t* mine = cnt[wave];
 #pragma unroll
-    for (int r = 0; r < SORT_ITEMS; ++r) {
-        const int64_t i = base + (int64_t)r * SORT_THREADS + threadIdx.x;
-        key[r] = i < n ? src.key(i) : 0;
-        val[r] = i < n ? src.val(i) : 0;
-    }
-#pragma unroll
-    for (int r = 0; r < SORT_ITEMS; ++r) {
-        const int64_t i = base + (int64_t)r * SORT_THREADS + threadIdx.x;
-        const bool valid = i < n;
+    for (int r = 0; r < ITEMS; ++r) {
+        const bool valid = piece + r * 64 + lane < n;
         const int digit = (key[r] >> shift) & (RADIX - 1);
-        const unsigned long long peers = digit_peers(valid, digit);
-        const unsigned long long lower = peers & ((1ull << lane) - 1ull);
-        const int rank_in_wave = __popcll(lower);
-        if (valid && lower == 0ull) wcnt[wave][digit] = __popcll(peers);   // one writer per digit
-        __syncthreads();
-        int32_t pos = 0;
-        if (valid) {
-            pos = running[digit] + rank_in_wave;
-            for (int w = 0; w < wave; ++w) pos += wcnt[w][digit];
+        const unsigned long long peers = digit_peers(valid, digit), lower = peers & ((1ull << lane) - 1ull);
+        const int32_t so_far = mine[digit];               // (the LDS operations of a wavefront stay in order)
+        rank[r] = so_far + __popcll(lower);
+        if (valid && lower == 0ull) mine[digit] = so_far + __popcll(peers);      // one writer per digit
+    }
+    __syncthreads();
+    int32_t here = 0;
+    if (t < RADIX) {
+#pragma unroll
+        for (int w = 0; w < SORT_WAVES; ++w) {
+            const int32_t c = cnt[w][t];
+            cnt[w][t] = here;
+            here += c;
         }
-        __syncthreads();
-        {   // thread t owns digit t: advance the running position, clear the round's counts
-            int32_t add = 0;
-            for (int w = 0; w < SORT_THREADS / 64; ++w) {
-                add += wcnt[w][threadIdx.x];
-                wcnt[w][threadIdx.x] = 0;
-            }
-            running[threadIdx.x] += add;
+    }
+    const int32_t first = block_exclusive_scan<SORT_WAVES>(here, &all);
+    if (t < RADIX) {
+#pragma unroll
+        for (int w = 0; w < SORT_WAVES; ++w) cnt[w][t] += first;
+        to[t] = global - first;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+        if (piece + r * 64 + lane < n) {
+            const int32_t at = cnt[wave][(key[r] >> shift) & (RADIX - 1)] + rank[r];
+            sk[at] = key[r];
+            sv[at] = val[r];
         }
-        if (valid) {
-            keys_out[pos] = key[r];
-            vals_out[pos] = val[r];
-        }
-        __syncthreads();
+    __syncthreads();
+    const int count = (int)min((int64_t)TILE, n - base);
+    for (int i = t; i < count; i += SORT_THREADS) {
+        const int32_t k = sk[i], pos = to[(k >> shift) & (RADIX - 1)] + i;
+        keys_out[pos] = k;
+        vals_out[pos] = sv[i];
     }
 }
 
@@ -405,40 +410,55 @@ __global__ __launch_bounds__(SMALL_THREADS) void small_index_kernel(const int32_
     }
 }
 
-inline int tiles_of(int64_t n, int tile) { return (int)((n + tile - 1) / tile); }
-
-// exclusive scan of in[0..n) into out (may alias), scratch `sums` of ceil(n/SCAN_TILE) ints
-hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* sums, hipStream_t s) {
-    const int nt = tiles_of(n, SCAN_TILE);
-    hipLaunchKernelGGL((scan_sums_kernel<false>), dim3(nt), dim3(SCAN_THREADS), 0, s, in, n, sums);
-    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, sums, nt, (int32_t*)nullptr);
-    hipLaunchKernelGGL((scan_apply_kernel<false>), dim3(nt), dim3(SCAN_THREADS), 0, s, in, n,
-                       (const int32_t*)sums, out, (int32_t*)nullptr, (const int32_t*)nullptr);
+// launches of ITEMS keys a thread
+template <int ITEMS>
+hipError_t build_tiled(const int32_t* head, int n_head, const int32_t* tail, int64_t n, int bits, const IndexBuffers& buf, int32_t** src_out,
+                       hipStream_t s) {
+    const int n_tiles = tiles_of(n);
+    const bool own = n_tiles <= OWN_TILES;
+    int32_t* totals = buf.hist + (size_t)RADIX * n_tiles;
+    int32_t *kin = buf.keys_a, *kout = buf.keys_b, *vin = buf.vals_a, *vout = buf.vals_b;
+    const dim3 grid(n_tiles), block(SORT_THREADS);
+    auto pass = [&](auto src, int shift) {
+        constexpr bool FIRST = std::is_same<decltype(src), KeySource<true>>::value;
+        hipLaunchKernelGGL((hist_kernel<FIRST, ITEMS>), grid, block, 0, s, src, n, shift, n_tiles, buf.hist);
+        if (own) {
+            hipLaunchKernelGGL((scatter_kernel<FIRST, true, ITEMS>), grid, block, 0, s, src, n, shift, n_tiles, (const int32_t*)buf.hist,
+                               (const int32_t*)nullptr, kout, vout);
+        } else {
+            hipLaunchKernelGGL(scan_rows_kernel, dim3(RADIX), dim3(256), 0, s, buf.hist, n_tiles, totals);
+            hipLaunchKernelGGL((scatter_kernel<FIRST, false, ITEMS>), grid, block, 0, s, src, n, shift, n_tiles, (const int32_t*)buf.hist,
+                               (const int32_t*)totals, kout, vout);
+        }
+        std::swap(kin, kout);
+        std::swap(vin, vout);
+    };
+    pass(KeySource<true>{head, tail, n_head}, 0);
+    for (int shift = RADIX_BITS; shift < bits; shift += RADIX_BITS) pass(KeySource<false>{kin, vin, 0}, shift);
+    *src_out = vin;
+    // segment heads over the sorted keys
+    if (n <= OWN_KEYS) {
+        hipLaunchKernelGGL((heads_kernel<true, ITEMS>), grid, block, 0, s, (const int32_t*)kin, n, (const int32_t*)nullptr, buf.uniq, buf.seg_off,
+                           buf.n_uniq);
+    } else {
+        hipLaunchKernelGGL((head_sums_kernel<ITEMS>), grid, block, 0, s, (const int32_t*)kin, n, buf.scan_tmp);
+        hipLaunchKernelGGL((heads_kernel<false, ITEMS>), grid, block, 0, s, (const int32_t*)kin, n, (const int32_t*)buf.scan_tmp, buf.uniq,
+                           buf.seg_off, buf.n_uniq);
+    }
     return hipGetLastError();
 }
 
 }  // namespace
 
-size_t index_hist_elems(int64_t n_keys) {
-    const size_t tiles = tiles_of(std::max<int64_t>(n_keys, 1), SORT_TILE);
-    return (size_t)RADIX * std::max(tiles, 2 * std::min<size_t>(tiles, MID_TILES));     // (the short scan is out of place)
-}
-
-size_t index_scan_tmp_elems(int64_t n_keys) {
-    const int64_t a = tiles_of((int64_t)index_hist_elems(n_keys), SCAN_TILE);
-    const int64_t b = tiles_of(std::max<int64_t>(n_keys, 1), SCAN_TILE);
-    return (size_t)std::max(a, b) + 1;
-}
+// (shorter arrays may have more tiles, but at most OWN_TILES)
+size_t index_scan_tmp_elems(int64_t n_keys) { return (size_t)std::max(OWN_TILES, tiles_of(std::max<int64_t>(n_keys, 1))); }
+size_t index_hist_elems(int64_t n_keys) { return RADIX * (index_scan_tmp_elems(n_keys) + 1); }
 
 hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* tail, int64_t n_tail,
                                int32_t key_bound, const IndexBuffers& buf, int32_t** src_out, hipStream_t s) {
     const int64_t n = (int64_t)n_head + n_tail;
     if (n <= 0) {
-        // empty index: n_uniq = 0, seg_off[0] = 0
-        hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, buf.seg_off, 0, buf.n_uniq);
-        hipLaunchKernelGGL((scan_apply_kernel<true>), dim3(1), dim3(SCAN_THREADS), 0, s,
-                           (const int32_t*)buf.keys_a, (int64_t)0, (const int32_t*)buf.scan_tmp, buf.uniq,
-                           buf.seg_off, (const int32_t*)buf.n_uniq);
+        hipLaunchKernelGGL(no_segments_kernel, dim3(1), dim3(1), 0, s, buf.seg_off, buf.n_uniq);
         *src_out = buf.vals_a;
         return hipGetLastError();
     }
@@ -450,54 +470,11 @@ hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* t
         *src_out = buf.vals_a;
         return hipGetLastError();
     }
-    const int n_tiles = tiles_of(n, SORT_TILE);
-    const bool own = n_tiles <= OWN_TILES, mid = !own && n_tiles <= MID_TILES;
-    int32_t* offs = mid ? buf.hist + (size_t)RADIX * n_tiles : buf.hist;
-    int32_t *kin = buf.keys_a, *kout = buf.keys_b, *vin = buf.vals_a, *vout = buf.vals_b;
-    for (int shift = 0; shift < bits; shift += RADIX_BITS) {
-        const KeySource<true> first{head, tail, n_head};
-        const KeySource<false> sorted{kin, vin, 0};
-        if (shift == 0)
-            hipLaunchKernelGGL((hist_kernel<true>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, first, n, shift, n_tiles, buf.hist);
-        else
-            hipLaunchKernelGGL((hist_kernel<false>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, sorted, n, shift, n_tiles, buf.hist);
-        if (own) {
-        } else if (mid) {
-            hipLaunchKernelGGL(scan_rows_kernel, dim3(RADIX), dim3(SCAN_THREADS), 0, s, (const int32_t*)buf.hist, n_tiles, offs);
-        } else {
-            hipError_t e = scan_exclusive(buf.hist, buf.hist, (int64_t)RADIX * n_tiles, buf.scan_tmp, s);
-            if (e != hipSuccess) return e;
-        }
-#define NGDB_SCATTER(FIRST, OWN, SRC)                                                                                                  \
-    hipLaunchKernelGGL((scatter_kernel<FIRST, OWN>), dim3(n_tiles), dim3(SORT_THREADS), 0, s, SRC, n, shift, n_tiles, (const int32_t*)offs, kout, vout)
-        if (shift == 0 && own) NGDB_SCATTER(true, true, first);
-        else if (shift == 0) NGDB_SCATTER(true, false, first);
-        else if (own) NGDB_SCATTER(false, true, sorted);
-        else NGDB_SCATTER(false, false, sorted);
-#undef NGDB_SCATTER
-        std::swap(kin, kout);
-        std::swap(vin, vout);
+    switch (items_of(n)) {
+        case FEW_ITEMS: return build_tiled<FEW_ITEMS>(head, n_head, tail, n, bits, buf, src_out, s);
+        case MID_ITEMS: return build_tiled<MID_ITEMS>(head, n_head, tail, n, bits, buf, src_out, s);
+        default: return build_tiled<MANY_ITEMS>(head, n_head, tail, n, bits, buf, src_out, s);
     }
-    // segment heads over the sorted keys
-    const int nt = tiles_of(n, SCAN_TILE);
-    if (n <= OWN_KEYS) {
-        hipLaunchKernelGGL((heads_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n, (const int32_t*)nullptr, buf.uniq,
-                           buf.seg_off, buf.n_uniq);
-        *src_out = vin;
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((scan_sums_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n,
-                       buf.scan_tmp);
-    if (nt <= MID_TILES) {
-        hipLaunchKernelGGL((heads_kernel<false>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n, (const int32_t*)buf.scan_tmp,
-                           buf.uniq, buf.seg_off, buf.n_uniq);
-    } else {
-        hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, buf.scan_tmp, nt, buf.n_uniq);
-        hipLaunchKernelGGL((scan_apply_kernel<true>), dim3(nt), dim3(SCAN_THREADS), 0, s, (const int32_t*)kin, n,
-                           (const int32_t*)buf.scan_tmp, buf.uniq, buf.seg_off, (const int32_t*)buf.n_uniq);
-    }
-    *src_out = vin;
-    return hipGetLastError();
 }
 
 }  // namespace ngdb

@@ -79,11 +79,13 @@ def test_candidate_lists_shared_by_workgroups(B, C, N):
     plan.free()
 
 
-# keys: one; 4096 and more (one workgroup / tiles); 16 384 and more (heads counted by every workgroup / scanned); 32 768 and more
-# (histogram scanned by every workgroup / once); 262 144 and more (short / long histogram); a bound of one digit, of two and of three
+# keys: one; 4096 and more (one workgroup / tiles); 80 000 and more (tiles of 2048 and 4096 keys, heads counted by every workgroup / from
+# sums); 262 144 and more (tiles of 8192 keys); 524 288 and more (histogram scanned by every workgroup / once); a bound of one digit, of
+# two and of three; a few keys all of the time
 @pytest.mark.parametrize("N,B,n_keys", [(50, 1, 3), (200, 8, 4096), (200, 8, 4104), (200, 8, 16384), (70000, 8, 16392),
                                         (70000, 8, 32768), (3000, 8, 32776), (70000, 64, 4096), (70000, 64, 262144),
-                                        (300, 64, 262208), (1000, 700, 300000)])
+                                        (300, 64, 262208), (1000, 700, 300000), (70000, 64, 79936), (70000, 64, 80064), (5000, 64, 131136),
+                                        (70000, 64, 524288), (70000, 64, 524352), (20, 64, 600000)])
 def test_gradient_index_by_size(N, B, n_keys):
     import torch
     from paper_2602_21597_amd import Engine
