@@ -6,6 +6,7 @@ and back.  PyTorch is used for device memory and streams.  If the library is
 missing the import fails loudly -- there is no fallback path.
 """
 import ctypes as C
+import operator
 import os
 
 import numpy as np
@@ -307,7 +308,9 @@ class SampledBatch:
         self.in_idx = take(c.in_idx, int(self.in_off[-1]), np.int32)
         self.pos = take(c.pos, B, np.int32)
         self.negs = take(neg_ptr, (B, K), np.int32)
-        self.names = list(map(names.__getitem__, take(tmpl_ptr, B, np.uint8).tobytes()))
+        kinds = take(tmpl_ptr, B, np.uint8).tobytes()
+        # (one call for all of them: half of the time of a call each)
+        self.names = list(operator.itemgetter(*kinds)(names)) if B > 1 else [names[k] for k in kinds]
 
     def query_nodes(self, i):
         """Nodes of query i as a list of (op, arg, [local input indices]), root last."""

@@ -146,3 +146,21 @@ def test_sampler_errors():
     with pytest.raises(NgdbError) as e:
         s.next(4, 1)
     assert e.value.code == binding.ERR_UNSUPPORTED and "2p" in str(e.value)
+
+
+def test_negatives_drawn_several_at_a_time_are_those_drawn_one_by_one():
+    # rows of a query begin alike whatever their length, and their last pairs (up to seven) are drawn one by one; of 2^32 values
+    # 6 700 416 are redrawn here, one pair in 320
+    N = 6700417
+    assert 2 ** 32 % N == N - 1
+    rng = np.random.default_rng(2)
+    head, tail, rel = rng.integers(0, N, 500), rng.integers(0, N, 500), rng.integers(0, 3, 500)
+    rows = {}
+    for K in [1, 2, 14, 15] + list(range(30, 192, 16)) + [31, 191, 200]:
+        s = Sampler(N, 3, head, rel, tail, ["1p"], seed=9, n_threads=2)
+        rows[K] = s.next(48, K).negs
+        s.close()
+    for K, row in rows.items():
+        even = K // 2 * 2
+        assert row.shape == (48, K) and row.min() >= 0 and row.max() < N
+        assert np.array_equal(row[:, :even], rows[200][:, :even]), K
