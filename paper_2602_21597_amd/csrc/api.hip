@@ -90,6 +90,8 @@ struct ngdb_ctx_s {
     // kernel (bf16 pieces in MFMA lane order), in both orientations: rebuilt at the start of every
     // forward pass, so they are never older than the weights the pass reads.
     DevBuf w_pieces;
+    SmallIndex index_waits{};      // a small gradient index that a launch of the forward pass may take along (n: 0 without one)
+    DevBuf sync;        // counts of the launches of several depths, zero between them
     const uint16_t* wp[3][4]{};     // per type: Wa forward, Wb forward, Wb backward (dH = dY Wb), Wa backward (dZ = dH Wa)
     bool have_pieces = false;
     int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
@@ -338,7 +340,7 @@ bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vecto
         for (int g = sg.g_lo; box && g < sg.g_hi; ++g)      // the offsets of the same inputs through the second MLP
             if (!level_add(*a, T_NEG, LEVEL_GATE, hp.g_n[g], hp.g_nin[g], sg.ref_off + hp.g_mlp_base[g] - sg.mlp_base, -1, hp.g_mlp_base[g], hp.g_out_base[g])) return false;
     }
-    if (!level_fits(c->cfg.d, c->cfg.h, box) && a->tile_start[a->count] > LEVEL_FEW) return false;
+    if (!level_fits(c->cfg.d, c->cfg.h, box) && a->t.tile_start[a->t.count] > LEVEL_FEW) return false;
     if (box) {
         a->act = ptr<float>(c->act); a->off = ptr<float>(c->off); a->dact = ptr<float>(c->dact); a->doff = ptr<float>(c->doff);
         a->Att = ptr<float>(c->Att); a->Gate = ptr<float>(c->Gate); a->dAtt = ptr<float>(c->dAtt); a->dGate = ptr<float>(c->dGate);
@@ -350,6 +352,31 @@ bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vecto
         const MlpRefs W = mlp_of(c->prm, t);
         a->mlp[t] = LevelMlp{W.Wa, W.ba, W.Wb, W.bb, ptr<float>(c->Z[t]), ptr<float>(c->H[t]), ptr<float>(c->dH[t])};
     }
+    return true;
+}
+
+// All depths of a direction in one launch, where each would take one and they are few enough.  fill() adds to a depth what the pass knows.
+template <class Fill>
+bool enqueue_levels(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Fill fill, int32_t* sync, hipStream_t s, int* rc) {
+    const int n = pl->hp.n_levels;
+    if (n < 2 || n > LEVEL_CHAIN || !sync) return false;
+    LevelArgs la[LEVEL_CHAIN];
+    double flop = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const std::vector<Segment>& segs = pl->levels[backward ? n - i : i + 1];
+        if (!level_problems(c, pl, segs, &la[i])) return false;
+        fill(la[i]);
+        flop += level_flop(c, segs);
+    }
+    if (!levels_chain(la, n)) return false;
+    auto launch = [&]() -> int {
+        Timed tm(c, backward ? NGDB_TK_GEMM_BWD : NGDB_TK_GEMM_FWD, s);
+        HIPCHK(c, launch_levels(la, n, backward, sync, backward ? nullptr : &c->index_waits, s));
+        if (!backward) c->index_waits.n = 0;
+        tm.work(GEMM_FP32, flop);
+        return NGDB_OK;
+    };
+    *rc = launch();
     return true;
 }
 
@@ -649,6 +676,8 @@ const Segment* riding_projection(const std::vector<Segment>& segs) {
 // into one launch per layer, then the two pooling kernels.
 int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     const int d = c->cfg.d, h = c->cfg.h;
+    int rc_l = NGDB_OK;
+    if (enqueue_levels(c, pl, false, [](LevelArgs&) {}, ptr<int32_t>(c->sync), s, &rc_l)) return rc_l;
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         LevelArgs la;
@@ -721,10 +750,11 @@ struct FwdSpace {
     float* H[3];
     float* Att;
     bool reclaim;
+    int32_t* sync;             // (the context's; null: depths in launches of their own)
 };
 FwdSpace ctx_space(const ngdb_ctx_t* c, bool reclaim = false) {
     return FwdSpace{ptr<float>(c->act), {ptr<float>(c->Z[0]), ptr<float>(c->Z[1]), ptr<float>(c->Z[2])},
-                    {ptr<float>(c->H[0]), ptr<float>(c->H[1]), ptr<float>(c->H[2])}, ptr<float>(c->Att), reclaim};
+                    {ptr<float>(c->H[0]), ptr<float>(c->H[1]), ptr<float>(c->H[2])}, ptr<float>(c->Att), reclaim, ptr<int32_t>(c->sync)};
 }
 // Bytes of the buffers of a forward-only pass, in the order act, Att, then Z and H per type.
 struct FwdBytes { size_t act, att, z[3], h[3]; };
@@ -786,13 +816,18 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
 int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hipStream_t s, const FwdSpace& w) {
     if (c->cfg.family == NGDB_FAMILY_BOX) return enqueue_forward_box(c, pl, s);   // (always on the context's buffers)
     const int d = c->cfg.d, h = c->cfg.h;
+    auto forward_level = [&](LevelArgs& la) {
+        la.refs = er.refs; la.rel = pl->d_rel; la.E = er.rows; la.R = c->prm.R.p;
+        la.act = w.act; la.Att = w.Att; la.out_row = w.reclaim ? pl->d_f_row : nullptr;
+        la.keep = !w.reclaim;
+    };
+    int rc_l = NGDB_OK;
+    if (w.sync && enqueue_levels(c, pl, false, forward_level, w.sync, s, &rc_l)) return rc_l;
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
-            la.refs = er.refs; la.rel = pl->d_rel; la.E = er.rows; la.R = c->prm.R.p;
-            la.act = w.act; la.Att = w.Att; la.out_row = w.reclaim ? pl->d_f_row : nullptr;
-            la.keep = !w.reclaim;
+            forward_level(la);
             Timed tm(c, NGDB_TK_GEMM_FWD, s);
             HIPCHK(c, launch_level(la, false, s));
             tm.work(GEMM_FP32, level_flop(c, segs));
@@ -927,11 +962,17 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     const int d = c->cfg.d, h = c->cfg.h;
     const HostPlan& hp = pl->hp;
     float* dact = ptr<float>(c->dact);
-    for (int l = hp.n_levels; l >= 1; --l) {
+    auto backward_level = [&](LevelArgs& la) {
+        la.dst_row = pl->d_in_gslot; la.Att = ptr<float>(c->Att); la.dact = dact; la.dAtt = ptr<float>(c->dAtt);
+    };
+    int rc_l = NGDB_OK;
+    const bool chained = enqueue_levels(c, pl, true, backward_level, ptr<int32_t>(c->sync), s, &rc_l);
+    if (rc_l != NGDB_OK) return rc_l;
+    for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
-            la.dst_row = pl->d_in_gslot; la.Att = ptr<float>(c->Att); la.dact = dact; la.dAtt = ptr<float>(c->dAtt);
+            backward_level(la);
             Timed tm(c, NGDB_TK_GEMM_BWD, s);
             HIPCHK(c, launch_level(la, true, s));
             tm.work(GEMM_FP32, level_flop(c, segs));
@@ -999,7 +1040,10 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
 int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJob* wj) {
     const int d = c->cfg.d, h = c->cfg.h;
     const HostPlan& hp = pl->hp;
-    for (int l = hp.n_levels; l >= 1; --l) {
+    int rc_l = NGDB_OK;
+    const bool chained = enqueue_levels(c, pl, true, [](LevelArgs&) {}, ptr<int32_t>(c->sync), s, &rc_l);
+    if (rc_l != NGDB_OK) return rc_l;
+    for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1108,7 +1152,12 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         end.forked = true;
     }
     EntRows er{c->prm.E.p, pl->d_in_ref, pl->d_pos, d_neg}, scored = er;
-    if ((rc = build_index(c, pl, d_neg, (int64_t)B * K, s_idx, &e_src)) != NGDB_OK) return rc;
+    // (a small index on the caller's stream: the launch of a small forward pass takes it along, or it follows)
+    c->index_waits.n = 0;
+    const bool index_rides = !aside && !sem && small_index_job(pl->d_ekeys_head, hp.n_anchor + B, d_neg, (int64_t)B * K, c->cfg.n_entities,
+                                                               index_buffers(c), &c->index_waits);
+    if (index_rides) e_src = c->index_waits.vals_out;
+    else if ((rc = build_index(c, pl, d_neg, (int64_t)B * K, s_idx, &e_src)) != NGDB_OK) return rc;
     if (sem) {
         if ((rc = fuse_indexed(c, pl, e_src, (int64_t)B * K, s_idx, &scored)) != NGDB_OK) return rc;
         if (aside) HIPCHK(c, hipEventRecord(c->ev_join, s_idx));
@@ -1117,7 +1166,10 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
 
     // 2. forward frontiers
     rc = enqueue_forward(c, pl, er, stream, ctx_space(c));
+    const bool index_left = c->index_waits.n > 0;
+    c->index_waits.n = 0;
     if (rc != NGDB_OK) return rc;
+    if (index_left && (rc = build_index(c, pl, d_neg, (int64_t)B * K, stream, &e_src)) != NGDB_OK) return rc;
 
     // 3. scores, loss terms, dL/ds, gradients of the branch embeddings
     if (sem && aside) HIPCHK(c, hipStreamWaitEvent(stream, c->ev_join, 0));
@@ -1643,6 +1695,8 @@ int ngdb_create(const ngdb_config* cfg, ngdb_ctx_t** out) {
     ok = ok && hipStreamCreateWithFlags(&c->upload, hipStreamNonBlocking) == hipSuccess;
     unsigned char* sp = nullptr;
     ok = ok && noalloc_scratch(&sp) == hipSuccess;     // address of the static scratch on this GPU
+    const int32_t zeros[LEVEL_SYNC] = {};
+    ok = ok && device_alloc(c, c->sync, sizeof(zeros)) == hipSuccess && hipMemcpy(c->sync.p, zeros, sizeof(zeros), hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) {
         ngdb_destroy(c);
         return NGDB_ERR_HIP;
@@ -1664,7 +1718,7 @@ void ngdb_destroy(ngdb_ctx_t* c) {
     DevBuf* all[] = {&c->act, &c->dact, &c->Z[0], &c->Z[1], &c->Z[2], &c->H[0], &c->H[1], &c->H[2], &c->dH[0],
                      &c->dH[1], &c->dH[2], &c->Att, &c->dAtt, &c->Dx, &c->score, &c->coef, &c->win, &c->mask,
                      &c->loss_terms, &c->rec_coef, &c->rec_row, &c->keys_a, &c->keys_b, &c->vals_a, &c->vals_b, &c->hist, &c->scan_tmp,
-                     &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->h_pieces, &c->gE, &c->gR, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
+                     &c->uniq, &c->seg_off, &c->n_uniq, &c->gW, &c->w_pieces, &c->sync, &c->h_pieces, &c->gE, &c->gR, &c->rank_dist, &c->rank_thr, &c->rank_count, &c->rank_filter,
                      &c->Wb, &c->Ef, &c->Ea, &c->inv, &c->refs_sem, &c->g_bf16, &c->wp_partial, &c->gWp, &c->rank_ef,
                      &c->off, &c->doff, &c->Gate, &c->dGate, &c->DxO, &c->gRo, &c->Eb, &c->later};
     for (DevBuf* b : all) release(c, *b);

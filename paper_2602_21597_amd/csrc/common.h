@@ -333,11 +333,15 @@ constexpr long LEVEL_WORK = 512l * LEVEL_WEIGHTS_BOX;
 constexpr int LEVEL_GATE = 2, LEVEL_PROJECTION = 3;      // box family (off set): pooling of offsets, projection without MLP
 struct LevelProblem { int type, pool, n, k, ref_off, rel_off, row0, out0; };
 struct LevelMlp { const float *Wa, *ba, *Wb, *bb; float *Z, *H, *dH; };
-struct LevelArgs {
-    int count, d, h;
-    bool keep;                      // forward: inputs, hidden rows and logits are kept for a backward pass
+struct LevelTiles {                 // the problems of a depth and the first of their workgroups
+    int count;
     int tile_start[LEVEL_MAX + 1];
     LevelProblem p[LEVEL_MAX];
+};
+struct LevelArgs {
+    int d, h;
+    bool keep;                      // forward: inputs, hidden rows and logits are kept for a backward pass
+    LevelTiles t;
     LevelMlp mlp[3];
     const int32_t *refs, *rel, *out_row, *dst_row;   // out_row: row of act per output (null: itself); dst_row: of dact per reference
     const float *E, *R;
@@ -349,6 +353,13 @@ bool level_fits(int d, int h, bool box);
 // adds a problem; false if the launch has no room for it
 bool level_add(LevelArgs& a, int type, int pool, int n, int k, int ref_off, int rel_off, int row0, int out0);
 hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s);
+// All depths of a pass in one launch, in the order of their dependence; alike but for their tiles.  Taken for at most LEVEL_CHAIN
+// depths of at most LEVEL_CHAIN_TILES workgroups together.  sync: LEVEL_SYNC words, zero, and zero again behind the launch.
+// index: a small gradient index built beside them, by one more workgroup (null: none).
+struct SmallIndex;
+constexpr int LEVEL_CHAIN = 4, LEVEL_CHAIN_TILES = 256, LEVEL_SYNC = 2 + LEVEL_CHAIN;
+bool levels_chain(const LevelArgs* a, int n);
+hipError_t launch_levels(const LevelArgs* a, int n, bool backward, int32_t* sync, const SmallIndex* index, hipStream_t s);
 
 // ---------------------------------------------------------------- scoring (score.hip)
 struct ScoreArgs {
@@ -470,6 +481,14 @@ struct IndexBuffers {   // device scratch owned by the context, sized for n_keys
 };
 size_t index_hist_elems(int64_t n_keys);
 size_t index_scan_tmp_elems(int64_t n_keys);
+// Up to SMALL_KEYS keys: the build as a job for one workgroup of 1024 threads (false: not so few, or none).  The order lands in vals_a.
+constexpr int SMALL_KEYS = 4096;
+struct SmallIndex {
+    const int32_t *head, *tail;
+    int n_head, n, bits;
+    int32_t *vals_out, *uniq, *seg_off, *n_uniq;
+};
+bool small_index_job(const int32_t* head, int n_head, const int32_t* tail, int64_t n_tail, int32_t key_bound, const IndexBuffers& buf, SmallIndex* job);
 // keys = [head[0..n_head) | tail[0..n_tail)], values < key_bound.  On return
 // (stream order) uniq/seg_off/n_uniq are filled and the contribution order is in
 // *src_out (one of vals_a / vals_b).

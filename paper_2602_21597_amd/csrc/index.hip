@@ -8,20 +8,18 @@
 //
 // The build runs beside the forward pass and is bound by its launches, not by its bytes, until there are
 // millions of keys.  Up to SMALL_KEYS keys one workgroup sorts everything in LDS (700 keys of the
-// smallest workload: 14 launches and 32 us became one of 9 us); up to OWN_TILES tiles every workgroup of the
+// smallest workload: 14 launches and 32 us became one of 9 us; in small models a launch of the forward pass takes it along); up to OWN_TILES tiles every workgroup of the
 // scatter adds up the counts for itself, and up to OWN_KEYS keys the segment heads before it too (five launches
 // for two passes); beyond, a launch scans the tiles of every digit.
 // A tile is put in order in LDS and leaves as runs of equal digits: written from where the keys lie, four bytes at a time all over
-// the output, a pass over 4.2 million keys took 80 to 90 us.  MEASURED
+// the output, a pass over 4.2 million keys took 80 to 90 us, in this way 30 to 40, beside the forward pass (the whole build 460 -> 210 us).
 #include <algorithm>
 #include <type_traits>
-#include "common.h"
+#include "small_index.h"
 
 namespace ngdb {
 namespace {
 
-constexpr int RADIX_BITS = 8;
-constexpr int RADIX = 1 << RADIX_BITS;
 constexpr int SORT_THREADS = 512, SORT_WAVES = SORT_THREADS / 64;
 // Keys of a thread; a tile is SORT_THREADS x ITEMS keys, SORT_WAVES pieces of ITEMS rounds of 64 in their order.
 constexpr int FEW_ITEMS = 4, MID_ITEMS = 8, MANY_ITEMS = 16;
@@ -212,17 +210,6 @@ __global__ __launch_bounds__(SORT_THREADS) void heads_kernel(const int32_t* __re
 
 __global__ void no_segments_kernel(int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) { seg_off[0] = n_uniq[0] = n_uniq[1] = 0; }
 
-// Lanes of the wavefront that hold a valid key with the lane's digit
-__device__ __forceinline__ unsigned long long digit_peers(bool valid, int digit) {
-    unsigned long long peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < RADIX_BITS; ++b) {
-        const unsigned long long bal = __ballot((digit >> b) & 1);
-        peers &= ((digit >> b) & 1) ? bal : ~bal;
-    }
-    return peers;
-}
-
 // Stable scatter of one radix pass.  Every wavefront walks its piece of the tile in rounds of 64 keys and counts the digits of its own
 // as it goes: a key's place among equal digits is the count so far + the lower lanes of the round.  With the counts of the
 // wavefronts before it and of the smaller digits that is its place in the tile, where it is put in LDS; the tile is then written from
@@ -310,104 +297,9 @@ __global__ __launch_bounds__(SORT_THREADS) void scatter_kernel(const KeySource<F
     }
 }
 
-// The whole index of at most SMALL_KEYS keys by one workgroup, keys and values in LDS: the same stable
-// radix passes (rounds of 1024 keys), then the segment heads.
-constexpr int SMALL_KEYS = 4096, SMALL_THREADS = 1024, SMALL_WAVES = SMALL_THREADS / 64;
-__global__ __launch_bounds__(SMALL_THREADS) void small_index_kernel(const int32_t* __restrict__ head, int n_head,
-                                                                    const int32_t* __restrict__ tail, int n, int bits,
-                                                                    int32_t* __restrict__ vals_out, int32_t* __restrict__ uniq,
-                                                                    int32_t* __restrict__ seg_off, int32_t* __restrict__ n_uniq) {
-    __shared__ int32_t ks[2][SMALL_KEYS], vs[2][SMALL_KEYS];
-    __shared__ int32_t running[RADIX], wcnt[SMALL_WAVES][RADIX], wsum[SMALL_WAVES];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    for (int i = t; i < n; i += SMALL_THREADS) {
-        ks[0][i] = i < n_head ? head[i] : tail[i - n_head];
-        vs[0][i] = i;
-    }
-    int cur = 0;
-    for (int shift = 0; shift < bits; shift += RADIX_BITS) {
-        if (t < RADIX) running[t] = 0;
-        for (int i = t; i < SMALL_WAVES * RADIX; i += SMALL_THREADS) (&wcnt[0][0])[i] = 0;
-        __syncthreads();
-        for (int i = t; i < n; i += SMALL_THREADS) atomicAdd(&running[(ks[cur][i] >> shift) & (RADIX - 1)], 1);
-        __syncthreads();
-        if (wave == 0) {          // exclusive scan of the 256 counts, four per lane
-            int32_t c[4], sum = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                c[j] = running[lane * 4 + j];
-                sum += c[j];
-            }
-            int32_t inc = sum;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int32_t v = __shfl_up(inc, off, 64);
-                if (lane >= off) inc += v;
-            }
-            int32_t run = inc - sum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                running[lane * 4 + j] = run;
-                run += c[j];
-            }
-        }
-        __syncthreads();
-        for (int base = 0; base < n; base += SMALL_THREADS) {
-            const int i = base + t;
-            const bool valid = i < n;
-            const int32_t key = valid ? ks[cur][i] : 0, val = valid ? vs[cur][i] : 0;
-            const int digit = (key >> shift) & (RADIX - 1);
-            const unsigned long long peers = digit_peers(valid, digit);
-            const unsigned long long lower = peers & ((1ull << lane) - 1ull);
-            if (valid && lower == 0ull) wcnt[wave][digit] = __popcll(peers);
-            __syncthreads();
-            if (t < RADIX) {      // counts of a digit -> its position in every wavefront
-                int32_t run = running[t];
-                for (int w = 0; w < SMALL_WAVES; ++w) {
-                    const int32_t c = wcnt[w][t];
-                    wcnt[w][t] = run;
-                    run += c;
-                }
-                running[t] = run;
-            }
-            __syncthreads();
-            if (valid) {
-                const int pos = wcnt[wave][digit] + __popcll(lower);
-                ks[cur ^ 1][pos] = key;
-                vs[cur ^ 1][pos] = val;
-            }
-            __syncthreads();
-            for (int x = t; x < SMALL_WAVES * RADIX; x += SMALL_THREADS) (&wcnt[0][0])[x] = 0;
-            __syncthreads();
-        }
-        cur ^= 1;
-    }
-    int32_t done = 0;             // heads before the round (the same in all threads)
-    for (int base = 0; base < n; base += SMALL_THREADS) {
-        const int i = base + t;
-        const bool valid = i < n;
-        const bool is_head = valid && (i == 0 || ks[cur][i] != ks[cur][i - 1]);
-        const unsigned long long m = __ballot(is_head);
-        __syncthreads();
-        if (lane == 0) wsum[wave] = __popcll(m);
-        __syncthreads();
-        int32_t at = done + __popcll(m & ((1ull << lane) - 1ull));
-#pragma unroll
-        for (int w = 0; w < SMALL_WAVES; ++w) {
-            at += w < wave ? wsum[w] : 0;
-            done += wsum[w];
-        }
-        if (is_head) {
-            uniq[at] = ks[cur][i];
-            seg_off[at] = i;
-        }
-        if (valid) vals_out[i] = vs[cur][i];
-    }
-    if (t == 0) {
-        seg_off[done] = n;
-        n_uniq[0] = done;
-        n_uniq[1] = 0;
-    }
+__global__ __launch_bounds__(SMALL_THREADS) void small_index_kernel(const SmallIndex job) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[SMALL_INDEX_LDS];
+    small_index(job, lds);
 }
 
 // launches of ITEMS keys a thread
@@ -454,6 +346,18 @@ hipError_t build_tiled(const int32_t* head, int n_head, const int32_t* tail, int
 size_t index_scan_tmp_elems(int64_t n_keys) { return (size_t)std::max(OWN_TILES, tiles_of(std::max<int64_t>(n_keys, 1))); }
 size_t index_hist_elems(int64_t n_keys) { return RADIX * (index_scan_tmp_elems(n_keys) + 1); }
 
+inline int bits_below(int32_t bound) {
+    int bits = 1;
+    while (bits < 31 && (1ll << bits) < (long long)bound) ++bits;
+    return bits;
+}
+bool small_index_job(const int32_t* head, int n_head, const int32_t* tail, int64_t n_tail, int32_t key_bound, const IndexBuffers& buf, SmallIndex* job) {
+    const int64_t n = (int64_t)n_head + n_tail;
+    if (n <= 0 || n > SMALL_KEYS) return false;
+    *job = SmallIndex{head, tail, n_head, (int)n, bits_below(key_bound), buf.vals_a, buf.uniq, buf.seg_off, buf.n_uniq};
+    return true;
+}
+
 hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* tail, int64_t n_tail,
                                int32_t key_bound, const IndexBuffers& buf, int32_t** src_out, hipStream_t s) {
     const int64_t n = (int64_t)n_head + n_tail;
@@ -462,14 +366,13 @@ hipError_t build_segment_index(const int32_t* head, int n_head, const int32_t* t
         *src_out = buf.vals_a;
         return hipGetLastError();
     }
-    int bits = 1;
-    while (bits < 31 && (1ll << bits) < (long long)key_bound) ++bits;
-    if (n <= SMALL_KEYS) {
-        hipLaunchKernelGGL(small_index_kernel, dim3(1), dim3(SMALL_THREADS), 0, s, head, n_head, tail, (int)n, bits, buf.vals_a,
-                           buf.uniq, buf.seg_off, buf.n_uniq);
+    SmallIndex job;
+    if (small_index_job(head, n_head, tail, n_tail, key_bound, buf, &job)) {
+        hipLaunchKernelGGL(small_index_kernel, dim3(1), dim3(SMALL_THREADS), 0, s, job);
         *src_out = buf.vals_a;
         return hipGetLastError();
     }
+    const int bits = bits_below(key_bound);
     switch (items_of(n)) {
         case FEW_ITEMS: return build_tiled<FEW_ITEMS>(head, n_head, tail, n, bits, buf, src_out, s);
         case MID_ITEMS: return build_tiled<MID_ITEMS>(head, n_head, tail, n, bits, buf, src_out, s);

@@ -13,7 +13,7 @@
 // Boxes (more launches apart): 128, 128: 46 -> 39, 112 -> 106; 128, 256: 48 -> 46, 116 -> 123; 64, 512: 49 -> 49, 117 -> 132,
 // and with 16 queries 56 -> 47 and 100 -> 104.
 #include <algorithm>
-#include "common.h"
+#include "small_index.h"
 
 namespace ngdb {
 namespace {
@@ -98,9 +98,49 @@ struct Layer {
     }
 };
 
+// Several depths in one launch (CHAIN): a workgroup takes the next number, and with it the next tile of the depths in their
+// order, requests its weights, waits until all tiles of the depth before are through, and counts itself when its rows are stored.  Numbers are
+// handed out in the order of dependence, so whoever is waited for has its number and runs, whatever part of the launch is resident and whoever
+// else is on the card.  What one depth hands to the next (rows of act, or of dact) is stored and loaded at the scope of the card, past
+// the L2s of the dies: a store is where everybody finds it when its wavefront's wait is over, and no cache has to be written
+// back or dropped.  The launch between two depths that this replaces costs 4 us of host time and 2 to 3 of the card's beyond
+// the wait: steps of 64 queries x 8 negatives at d = 32, h = 64 73.0 -> 68.0 us, 256 x 32 at 64, 128 135 -> 123, 64 x 16 at 100, 200 142 -> 130,
+// boxes of 200 x 32 at 128, 128 116 -> 105.
+template <bool CHAIN>
+__device__ __forceinline__ float4 row_get(const float* p) {
+    if (!CHAIN) return *reinterpret_cast<const float4*>(p);
+    const unsigned long long* q = reinterpret_cast<const unsigned long long*>(p);
+    const unsigned long long lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float4(__uint_as_float((uint32_t)lo), __uint_as_float((uint32_t)(lo >> 32)), __uint_as_float((uint32_t)hi),
+                       __uint_as_float((uint32_t)(hi >> 32)));
+}
+template <bool CHAIN>
+__device__ __forceinline__ float row_get1(const float* p) {
+    return CHAIN ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <bool CHAIN>
+__device__ __forceinline__ void row_put1(float* p, float v) {
+    if (CHAIN) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+template <bool CHAIN>
+__device__ __forceinline__ void row_put(float* p, float4 v) {
+    if (!CHAIN) { *reinterpret_cast<float4*>(p) = v; return; }
+    row_put1<true>(p, v.x); row_put1<true>(p + 1, v.y); row_put1<true>(p + 2, v.z); row_put1<true>(p + 3, v.w);
+}
+// sync[0]: numbers handed out, sync[1]: tiles through, sync[2 + l]: tiles of depth l through
+constexpr int CHAIN_SPINS = 1 << 22;          // (seconds: a wait that no working card comes near ends all the same)
+__device__ __forceinline__ void wait_for_depth(const int32_t* through, int tiles) {
+    if (threadIdx.x == 0)
+        for (int i = 0; i < CHAIN_SPINS && __hip_atomic_load(through, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tiles; ++i) __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
+    __syncthreads();
+}
+
 // Box family: projections have no MLP (16 members a workgroup: centre plus, offset plus relu of the relation's rows); the
 // offset side of an intersection pools by the least input times the gate of the mean logit.
-template <bool BWD>
+template <bool BWD, bool CHAIN>
 __device__ __forceinline__ void box_projection(const LevelArgs& a, const LevelProblem& p, int i0) {
     const int d4 = a.d >> 2;
     const int n = min(LV_ROWS, p.n - i0) * d4;
@@ -109,43 +149,40 @@ __device__ __forceinline__ void box_projection(const LevelArgs& a, const LevelPr
         const size_t out = (size_t)(p.out0 + i) * a.d + c;
         if (BWD) {
             const size_t in = (size_t)a.dst_row[p.ref_off + i] * a.d + c;
-            *reinterpret_cast<float4*>(a.dact + in) = *reinterpret_cast<const float4*>(a.dact + out);
-            *reinterpret_cast<float4*>(a.doff + in) = *reinterpret_cast<const float4*>(a.doff + out);
+            row_put<CHAIN>(a.dact + in, row_get<CHAIN>(a.dact + out));
+            row_put<CHAIN>(a.doff + in, row_get<CHAIN>(a.doff + out));
             continue;
         }
         const int32_t ref = a.refs[p.ref_off + i];
         const size_t r = (size_t)a.rel[p.rel_off + i] * a.d + c;
         float4 x, o = make_float4(0.f, 0.f, 0.f, 0.f);
         if (ref >= 0) {
-            x = *reinterpret_cast<const float4*>(a.act + (size_t)ref * a.d + c);
-            o = *reinterpret_cast<const float4*>(a.off + (size_t)ref * a.d + c);
+            x = row_get<CHAIN>(a.act + (size_t)ref * a.d + c);
+            o = row_get<CHAIN>(a.off + (size_t)ref * a.d + c);
         } else {
             x = *reinterpret_cast<const float4*>(a.E + (size_t)(-1 - ref) * a.d + c);
         }
         const float4 rc = *reinterpret_cast<const float4*>(a.R + r), ro = *reinterpret_cast<const float4*>(a.Ro + r);
         x.x += rc.x; x.y += rc.y; x.z += rc.z; x.w += rc.w;
         o.x += fmaxf(ro.x, 0.f); o.y += fmaxf(ro.y, 0.f); o.z += fmaxf(ro.z, 0.f); o.w += fmaxf(ro.w, 0.f);
-        *reinterpret_cast<float4*>(a.act + out) = x;
-        *reinterpret_cast<float4*>(a.off + out) = o;
+        row_put<CHAIN>(a.act + out, x);
+        row_put<CHAIN>(a.off + out, o);
     }
 }
 
-template <bool BWD, bool BOX>
-__global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
-    extern __shared__ __attribute__((aligned(16))) float lds[];
+// tile `block` of problem p; before(): what it reads of other depths is there
+template <bool BWD, bool BOX, bool CHAIN, class Before>
+__device__ __forceinline__ void level_tile(const LevelArgs& a, const LevelProblem& p, int block, float* lds, Before before) {
     __shared__ int row_of[LV_ROWS], out_of[LV_ROWS], in_of[LV_ROWS];     // MLP row / output row / input reference of a tile row
-    int q = 0;
-    for (int i = 1; i < a.count; ++i)
-        if ((int)blockIdx.x >= a.tile_start[i]) q = i;
-    const LevelProblem p = a.p[q];
     const LevelMlp w = a.mlp[p.type];
     const int d = a.d, h = a.h, xp = lv_pitch(d), hp = lv_pitch(h);
     float *Xs = lds, *Ls = Xs + LV_ROWS * xp, *Hs = Ls + LV_ROWS * xp, *bias = Hs + LV_ROWS * hp;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int m = LV_ROWS / p.k, i0 = ((int)blockIdx.x - a.tile_start[q]) * m;
+    const int m = LV_ROWS / p.k, i0 = block * m;
     const bool inter = p.pool != 0;
     if (BOX && p.pool == LEVEL_PROJECTION) {
-        box_projection<BWD>(a, p, i0);
+        before();
+        box_projection<BWD, CHAIN>(a, p, i0);
         return;
     }
     const bool gate = BOX && p.pool == LEVEL_GATE;
@@ -173,6 +210,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
     }
     if (!BWD)
         for (int i = tid; i < h + d; i += LV_T) bias[i] = i < h ? w.ba[i] : w.bb[i - h];
+    before();
     // rows of the tile that are no rows, and the columns that fill up the last k-step, count as zeros
     if (!BWD) {
         const int c4 = (xp - 4) >> 2;
@@ -183,7 +221,8 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
             if (j < p.k && i < p.n && c < d) {
                 const int r = j * p.n + i;
                 const int32_t ref = a.refs[p.ref_off + r];
-                v = *reinterpret_cast<const float4*>((ref >= 0 ? act + (size_t)ref * d : a.E + (size_t)(-1 - ref) * d) + c);
+                if (ref >= 0) v = row_get<CHAIN>(act + (size_t)ref * d + c);
+                else v = *reinterpret_cast<const float4*>(a.E + (size_t)(-1 - ref) * d + c);
                 if (p.rel_off >= 0) {
                     const float4 t = *reinterpret_cast<const float4*>(a.R + (size_t)a.rel[p.rel_off + r] * d + c);
                     v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
@@ -214,7 +253,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                     Ls[lr * xp + n] = y;
                     if (a.keep && r >= 0) Att[(size_t)r * d + n] = y;
                 } else if (r >= 0) {
-                    act[(size_t)out_of[lr] * d + n] = y;
+                    row_put1<CHAIN>(act + (size_t)out_of[lr] * d + n, y);
                 }
             }
         });
@@ -229,7 +268,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                     mean += Ls[(j * m + ii) * xp + c];
                     mn = fminf(mn, Xs[(j * m + ii) * xp + c]);
                 }
-                act[(size_t)out_of[ii] * d + c] = mn * sigmoid_f(mean / (float)p.k);
+                row_put1<CHAIN>(act + (size_t)out_of[ii] * d + c, mn * sigmoid_f(mean / (float)p.k));
                 continue;
             }
             float e[NGDB_MAX_CARD], mx = -INFINITY, den = 0.f, y = 0.f;
@@ -246,7 +285,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
             const float inv = 1.f / den;
 #pragma unroll
             for (int j = 0; j < NGDB_MAX_CARD; ++j) y += e[j] * inv * Xs[(min(j, p.k - 1) * m + ii) * xp + c];
-            act[(size_t)out_of[ii] * d + c] = y;
+            row_put1<CHAIN>(act + (size_t)out_of[ii] * d + c, y);
         }
         return;
     }
@@ -258,7 +297,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
             const int lr = idx / c4, c = (idx - lr * c4) * 4;
             const int j = lr / m, i = i0 + lr - j * m;
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!inter && j < p.k && i < p.n && c < d) v = *reinterpret_cast<const float4*>(dact + (size_t)(p.out0 + i) * d + c);
+            if (!inter && j < p.k && i < p.n && c < d) v = row_get<CHAIN>(dact + (size_t)(p.out0 + i) * d + c);
             *reinterpret_cast<float4*>(Xs + lr * xp + c) = v;
         }
         for (int idx = tid; idx < LV_ROWS * e4; idx += LV_T) {
@@ -281,7 +320,7 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
                     x[j] = w.Z[at];
                     if (j < p.k) mx = fmaxf(mx, e[j]);
                 }
-                const float dy = dact[(size_t)(p.out0 + i0 + ii) * d + c];
+                const float dy = row_get1<CHAIN>(dact + (size_t)(p.out0 + i0 + ii) * d + c);
                 if (gate) {
                     float mean = 0.f, mn = INFINITY;
                     int arg = 0;
@@ -338,10 +377,62 @@ __global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int lr = (lane >> 4) * 4 + e;
-                if (row_of[lr] >= 0) dact[(size_t)in_of[lr] * d + n] = v[e] + (inter ? Ls[lr * xp + n] : 0.f);
+                if (row_of[lr] >= 0) row_put1<CHAIN>(dact + (size_t)in_of[lr] * d + n, v[e] + (inter ? Ls[lr * xp + n] : 0.f));
             }
         });
     }
+}
+
+__device__ __forceinline__ int problem_of(const LevelTiles& t, int tile) {
+    int q = 0;
+    for (int i = 1; i < t.count; ++i)
+        if (tile >= t.tile_start[i]) q = i;
+    return q;
+}
+
+template <bool BWD, bool BOX>
+__global__ __launch_bounds__(LV_T) void level_kernel(const LevelArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int q = problem_of(a.t, (int)blockIdx.x);
+    level_tile<BWD, BOX, false>(a, a.t.p[q], (int)blockIdx.x - a.t.tile_start[q], lds, [] {});
+}
+
+struct LevelRun {                   // the first depth's tiles stand in a
+    LevelArgs a;
+    LevelTiles more[LEVEL_CHAIN - 1];
+    int n, first[LEVEL_CHAIN + 1];      // depths, the first tile of each
+    int32_t* sync;
+    SmallIndex index;               // (n: 0 without one)
+};
+static_assert(LV_T == SMALL_THREADS, "the index of few keys is a workgroup's job here too");
+// INDEX: the first workgroup builds the gradient index meanwhile, which nothing here reads.  A launch of its own for it was 5 to 10 us
+// of a small step (64 x 8 at 32, 64 68.0 -> 62.6 us, 64 x 16 at 100, 200 130 -> 120, 16 x 4 boxes at 64, 64 66 -> 56).
+template <bool BWD, bool BOX, bool INDEX>
+__global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ int number;
+    if (INDEX && blockIdx.x == 0) {
+        small_index(r.index, lds);
+        return;
+    }
+    if (threadIdx.x == 0) number = __hip_atomic_fetch_add(r.sync, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int at = __builtin_amdgcn_readfirstlane(number);
+    int l = 0;
+    for (int i = 1; i < r.n; ++i)
+        if (at >= r.first[i]) l = i;
+    const LevelTiles& t = l == 0 ? r.a.t : r.more[l - 1];
+    const int tile = at - r.first[l], q = problem_of(t, tile);
+    level_tile<BWD, BOX, true>(r.a, t.p[q], tile - t.tile_start[q], lds, [&] {
+        if (l > 0) wait_for_depth(r.sync + 1 + l, r.first[l] - r.first[l - 1]);
+    });
+    wait_vm<0>();                   // this wavefront's rows are where the next depth finds them,
+    __syncthreads();                // ... and everybody's
+    if (threadIdx.x != 0) return;
+    __hip_atomic_fetch_add(r.sync + 2 + l, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the last one through (nobody waits any more) leaves the counts as they were found
+    if (__hip_atomic_fetch_add(r.sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r.first[r.n] - 1)
+        for (int i = 0; i < LEVEL_SYNC; ++i) __hip_atomic_store(r.sync + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 size_t lv_lds(int d, int h) { return ((size_t)LV_ROWS * (2 * lv_pitch(d) + lv_pitch(h)) + d + h) * sizeof(float); }
@@ -350,24 +441,65 @@ size_t lv_lds(int d, int h) { return ((size_t)LV_ROWS * (2 * lv_pitch(d) + lv_pi
 
 bool level_add(LevelArgs& a, int type, int pool, int n, int k, int ref_off, int rel_off, int row0, int out0) {
     if (n <= 0) return true;
-    if (a.count == LEVEL_MAX || k < 1 || k > NGDB_MAX_CARD) return false;
-    a.p[a.count] = LevelProblem{type, pool, n, k, ref_off, rel_off, row0, out0};
+    LevelTiles& t = a.t;
+    if (t.count == LEVEL_MAX || k < 1 || k > NGDB_MAX_CARD) return false;
+    t.p[t.count] = LevelProblem{type, pool, n, k, ref_off, rel_off, row0, out0};
     const int m = LV_ROWS / k;
-    a.tile_start[a.count + 1] = a.tile_start[a.count] + (n + m - 1) / m;
-    return (long)a.tile_start[++a.count] * a.d * a.h <= LEVEL_WORK;
+    t.tile_start[t.count + 1] = t.tile_start[t.count] + (n + m - 1) / m;
+    return (long)t.tile_start[++t.count] * a.d * a.h <= LEVEL_WORK;
 }
 
 bool level_fits(int d, int h, bool box) { return d <= 256 && h <= 512 && d * h <= (box ? LEVEL_WEIGHTS_BOX : LEVEL_WEIGHTS); }
 
 hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
-    if (a.count == 0) return hipSuccess;
+    if (a.t.count == 0) return hipSuccess;
     if (!level_fits(a.d, a.h, true) || (a.d & 3) || (a.h & 3)) return hipErrorInvalidValue;
-    const dim3 grid(a.tile_start[a.count]);
+    const dim3 grid(a.t.tile_start[a.t.count]);
     const size_t lds = lv_lds(a.d, a.h);
     if (a.off && backward) hipLaunchKernelGGL((level_kernel<true, true>), grid, dim3(LV_T), lds, s, a);
     else if (a.off) hipLaunchKernelGGL((level_kernel<false, true>), grid, dim3(LV_T), lds, s, a);
     else if (backward) hipLaunchKernelGGL((level_kernel<true, false>), grid, dim3(LV_T), lds, s, a);
     else hipLaunchKernelGGL((level_kernel<false, false>), grid, dim3(LV_T), lds, s, a);
+    return hipGetLastError();
+}
+
+bool levels_chain(const LevelArgs* a, int n) {
+    int tiles = 0;
+    for (int l = 0; l < n; ++l) {
+        if (a[l].t.count == 0) return false;
+        tiles += a[l].t.tile_start[a[l].t.count];
+    }
+    return n > 1 && n <= LEVEL_CHAIN && tiles <= LEVEL_CHAIN_TILES;
+}
+
+hipError_t launch_levels(const LevelArgs* a, int n, bool backward, int32_t* sync, const SmallIndex* index, hipStream_t s) {
+    if (!levels_chain(a, n) || !sync || !level_fits(a[0].d, a[0].h, true) || (a[0].d & 3) || (a[0].h & 3)) return hipErrorInvalidValue;
+    LevelRun r{};
+    r.a = a[0];
+    r.n = n;
+    r.sync = sync;
+    for (int l = 0; l < n; ++l) {
+        if (l > 0) r.more[l - 1] = a[l].t;
+        r.first[l + 1] = r.first[l] + a[l].t.tile_start[a[l].t.count];
+    }
+    const bool with_index = index && index->n > 0;
+    if (with_index && backward) return hipErrorInvalidValue;
+    if (with_index) r.index = *index;
+    const dim3 grid(r.first[n] + (with_index ? 1 : 0));
+    const size_t lds = std::max(lv_lds(r.a.d, r.a.h), with_index ? SMALL_INDEX_LDS : 0);
+#define NGDB_LEVELS(...)                                                                                                                    \
+    do {                                                                                                                                    \
+        if (lds > 64 * 1024)                                                                                                                \
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(levels_kernel<__VA_ARGS__>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+        hipLaunchKernelGGL((levels_kernel<__VA_ARGS__>), grid, dim3(LV_T), lds, s, r);                                                      \
+    } while (0)
+    if (r.a.off && backward) NGDB_LEVELS(true, true, false);
+    else if (r.a.off && with_index) NGDB_LEVELS(false, true, true);
+    else if (r.a.off) NGDB_LEVELS(false, true, false);
+    else if (backward) NGDB_LEVELS(true, false, false);
+    else if (with_index) NGDB_LEVELS(false, false, true);
+    else NGDB_LEVELS(false, false, false);
+#undef NGDB_LEVELS
     return hipGetLastError();
 }
 

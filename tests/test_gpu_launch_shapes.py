@@ -181,6 +181,43 @@ def test_operators_of_a_depth_in_one_launch(d, h, B):
     plan.free()
 
 
+# all depths of a pass in one launch against a launch each (the entry point without allocations): nearly empty tiles, up to 256
+# workgroups and beyond, calls in a row; and with the gradient index taken along, up to 4096 keys and beyond
+@pytest.mark.parametrize("B,d,h", [(1, 36, 52), (64, 36, 52), (300, 128, 160), (1200, 36, 52), (1900, 36, 52)])
+def test_depths_of_a_pass_in_one_launch(B, d, h):
+    import torch
+    case = par.Case(900, 9, d, h, B, 2, 6.0, seed=B)
+    eng = case.engine()
+    cand = torch.from_numpy(np.random.default_rng(B).integers(0, 900, (B, 5)).astype(np.int32)).cuda()
+    for n in (B, max(1, B // 3), B):
+        plan = eng.plan(case.qb.select(np.arange(n)))
+        want = eng.score_noalloc(plan, cand[:n].contiguous(), torch.empty((n, 5), dtype=torch.float32, device="cuda")).clone()
+        for _ in range(3):
+            assert torch.equal(eng.score(plan, cand[:n].contiguous()), want)
+        plan.free()
+
+
+@pytest.mark.parametrize("box", [False, True])
+@pytest.mark.parametrize("B,n_keys", [(2, 40), (30, 4096), (30, 4126)])
+def test_index_taken_along_by_a_forward_pass(B, n_keys, box):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N = 700
+    qb = wl.make_batch(wl.make_kg(N, 5, 4 * N, 2.1, 3), B, {"2i": 1.0}, 4)                  # two anchors a query, two depths
+    K = (n_keys - 3 * B) // B
+    negs = wl.make_negatives(N, B, K, 5)
+    eng = Engine(N, 5, 20, 36, 8.0, family=binding.FAMILY_BOX if box else binding.FAMILY_VEC)
+    eng.bind_numpy((wl.make_box_params if box else wl.make_params)(N, 5, 20, 36, 6))
+    plan = eng.plan(qb)
+    u, off, src = oplan.entity_index(plan.export(), qb.pos, negs)
+    for _ in range(2):
+        eng.forward_backward(plan, torch.from_numpy(negs).cuda())
+        g = eng.grads()
+        for name, want in (("e_uniq", u), ("e_seg_off", off), ("e_src", src)):
+            assert np.array_equal(g[name], want), name
+    plan.free()
+
+
 # Rounding errors of a layer over k: chains of 16 products, four of them as a tree, these sums one after the other.  In units of
 # the variance of one relative rounding (at most 2^-48 / 3), for products of random sign: 8.5 + 2 + (k / 64 + 1) / 2.  (Two
 # chains over all of k have k / 4.)  The errors of both layers add up in quadrature.
