@@ -147,34 +147,31 @@ struct GemmArgs {
     const float* A = nullptr;
     const float* B = nullptr;
     float* C = nullptr;
-    int M = 0, N = 0, K = 0;
-    int lda = 0, ldb = 0, ldc = 0;
-    bool a_kcontig = true, b_kcontig = true;
     const float* bias = nullptr;
-    bool relu = false;
     const float* mask = nullptr;
-    int ldmask = 0;
     const float* addend = nullptr;
-    int ldadd = 0;
     const int32_t* dst_row = nullptr;
-    int arith = 0;                 // GEMM_AUTO / GEMM_FP32 / GEMM_SPLIT: how the products are formed
     const uint16_t* b_pieces = nullptr;
-    int b_kt = 0;
     // The same for A (rows of A in blocks of 32: tile (m / 32, k / 16), a_kt tiles per block row), and
     // for the output, written once more in that form where c_pieces is given (c_kt tiles per block
     // row, at least 2 * ceil(N / 32); no dst_row) for the launch that reads it as its A operand.
     const uint16_t* a_pieces = nullptr;
-    int a_kt = 0;
     uint16_t* c_pieces = nullptr;
-    int c_kt = 0;
-    int a_row0 = 0;                // row 0 of A is row a_row0 of a_pieces (with pool_k only)
     // The output rows are the logits of intersections of pool_k inputs (row j * n + i: input j of member i, M = n * pool_k):
     // row i of pool_out, or row pool_row[i], receives sum_j softmax_j(C[j * n + i]) * pool_X[j * n + i] (leading dimension ldc).
     // C may be null then.  Only launches of split weights do this; others return hipErrorNotSupported.
-    int pool_k = 0;
     const float* pool_X = nullptr;
     float* pool_out = nullptr;
     const int32_t* pool_row = nullptr;
+    int pool_k = 0;
+    int M = 0, N = 0, K = 0;
+    int lda = 0, ldb = 0, ldc = 0;
+    int ldmask = 0, ldadd = 0;
+    int b_kt = 0, a_kt = 0, c_kt = 0;
+    int a_row0 = 0;                // row 0 of A is row a_row0 of a_pieces (with pool_k only)
+    int arith = 0;                 // GEMM_AUTO / GEMM_FP32 / GEMM_SPLIT: how the products are formed
+    bool a_kcontig = true, b_kcontig = true;
+    bool relu = false;
 };
 // GEMM_FP32: fp32 MFMA.  GEMM_SPLIT: every fp32 operand value as the exact sum of three bf16
 // values, the six largest of the nine partial products on the bf16 MFMA with fp32 accumulation
@@ -185,11 +182,14 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // Up to GEMM_MAX_GROUP independent contractions with the same operand layout in one
 // launch (the operator groups of one depth, or the weight gradients of all types).
 constexpr int GEMM_MAX_GROUP = 6;
-struct GemmGroup {
+template <int MOST_>
+struct GemmGroupOf {
+    static constexpr int MOST = MOST_;
     int count;
-    int tile_start[GEMM_MAX_GROUP + 1];   // first workgroup of every problem
-    GemmArgs p[GEMM_MAX_GROUP];
+    int tile_start[MOST + 1];             // first workgroup of every problem
+    GemmArgs p[MOST];
 };
+using GemmGroup = GemmGroupOf<GEMM_MAX_GROUP>;
 // *route (if given) receives the arithmetic the launch used: GEMM_FP32 or GEMM_SPLIT; *emitted (if
 // given) whether the launch wrote c_pieces (only gemm_kernel does where it reads its B operand as pieces,
 // in launches of few tiles, and only if every problem of the group asks for it).

@@ -21,6 +21,7 @@
 // weights, once per pass, by weight_pieces_kernel; AP: the hidden rows, by the epilogue of
 // the launch that produced them): such pieces lie in global memory tile by tile in the lane
 // order of the MFMA and go from there straight into its operand registers.
+#include <type_traits>
 #include "common.h"
 
 namespace ngdb {
@@ -303,8 +304,8 @@ __device__ __forceinline__ bf16x8 piece_at(const uint16_t* at, int q) {
 
 // POOL: problems with pool_k set take whole intersections: a tile is all inputs of 32 / pool_k members, and the pooling
 // is the end of the epilogue (a launch of its own cost 3 to 5 us at each depth).
-template <int BM, int BN, int NW, bool AK, bool BKC, bool SPLIT = false, int PF = 1, bool BP = false, bool AP = false, bool POOL = false>
-__global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
+template <int BM, int BN, int NW, bool AK, bool BKC, bool SPLIT = false, int PF = 1, bool BP = false, bool AP = false, bool POOL = false, class Group = GemmGroup>
+__global__ __launch_bounds__(NW * 64) void gemm_kernel(const Group g) {
     static_assert(!BP || (SPLIT && AK), "B operand from split pieces: split route with k-contiguous A only");
     static_assert(!AP || (BP && BM == 32), "A operand from split pieces: with B from pieces, one block of rows");
     static_assert(!SPLIT || BK == 16, "split path: one 32x32x16 MFMA step per staged tile");
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_kernel(const GemmGroup g) {
     // which problem of the group this workgroup works on (uniform, stays in scalar registers)
     int p = 0, first = g.tile_start[0], last = g.tile_start[1];
 #pragma unroll
-    for (int i = 1; i < GEMM_MAX_GROUP; ++i)
+    for (int i = 1; i < Group::MOST; ++i)
         if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) {
             p = i;
             first = g.tile_start[i];
@@ -907,8 +908,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradGroup g) {
 constexpr int FIRST = 3;      // products ahead of the wait for a block's reads
 constexpr int PN = 64, PN_LD = PN + 4;      // columns of a tile
 __device__ __forceinline__ int tile_swizzle(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
-template <int WM, int WK, bool ADD, bool POOL>
-__global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(const GemmGroup g) {
+template <int WM, int WK, bool ADD, bool POOL, class Group>
+__global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(const Group g) {
     constexpr int NW = WM * WK, BM = 32 * WM;
     constexpr int AB = 2048, BB = 2 * WTILE * 2;             // bytes of 32 rows of a block, of two tiles of pieces
     constexpr int ROWS = (ADD ? 2 : 1) * AB, GROUP = 2 * BB + WM * ROWS;
@@ -921,7 +922,7 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = wave / WM, wm = wave % WM;      // (in scalar registers)
     int p = 0;
 #pragma unroll
-    for (int i = 1; i < GEMM_MAX_GROUP; ++i)
+    for (int i = 1; i < Group::MOST; ++i)
         if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) p = i;
     const GemmArgs& a = g.p[p];
     // (all of the arguments that are used late are requested here: one by one each costs a round trip to the argument segment)
@@ -1215,10 +1216,9 @@ constexpr int ROWS_N = 2, ROWS_MAX = 16, ROWS_LDS = 16384;
 template <int MR, class Group>
 __global__ __launch_bounds__(256) void rows_kernel(const Group g) {
     extern __shared__ __attribute__((aligned(16))) float xs[];      // [M][K]
-    constexpr int MOST = sizeof(g.p) / sizeof(GemmArgs);
     int p = 0;
 #pragma unroll
-    for (int i = 1; i < MOST; ++i)
+    for (int i = 1; i < Group::MOST; ++i)
         if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) p = i;
     const GemmArgs& a = g.p[p];
     const int block = (int)blockIdx.x - g.tile_start[p];
@@ -1302,7 +1302,24 @@ bool takes_rows_kernel(const GemmArgs& a) {
            !a.addend && !a.a_pieces;
 }
 
-struct GemmOne { int count; int tile_start[2]; GemmArgs p[1]; };
+// Launches of few problems are given the room of a smaller group: a launch costs the host 1 us for every KB of its arguments (a group
+// of six takes 1.3 KB, of three 0.7; launch_with(f) calls f with the smallest that holds g).
+template <int MOST>
+GemmGroupOf<MOST> smaller(const GemmGroup& g) {
+    GemmGroupOf<MOST> s;
+    s.count = g.count;
+    for (int i = 0; i <= MOST; ++i) s.tile_start[i] = g.tile_start[i];
+    for (int i = 0; i < MOST; ++i) s.p[i] = g.p[i];
+    return s;
+}
+template <class Launch>
+hipError_t launch_with(const GemmGroup& g, Launch launch) {
+    if (g.count == 1) launch(smaller<1>(g));
+    else if (g.count <= 3) launch(smaller<3>(g));
+    else launch(g);
+    return hipGetLastError();
+}
+
 hipError_t dispatch_rows(GemmGroup& g, hipStream_t s) {
     int blocks = 0, m = 1;
     size_t lds = 0;
@@ -1313,18 +1330,12 @@ hipError_t dispatch_rows(GemmGroup& g, hipStream_t s) {
         lds = std::max(lds, (size_t)g.p[i].M * g.p[i].K * sizeof(float));
     }
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = blocks;
-    // (a single problem without the room for six: 250 bytes of arguments instead of 1520)
-    if (g.count == 1) {
-        const GemmOne one{1, {0, blocks}, {g.p[0]}};
-        if (m <= 2) hipLaunchKernelGGL((rows_kernel<2, GemmOne>), dim3(blocks), dim3(256), lds, s, one);
-        else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8, GemmOne>), dim3(blocks), dim3(256), lds, s, one);
-        else hipLaunchKernelGGL((rows_kernel<16, GemmOne>), dim3(blocks), dim3(256), lds, s, one);
-        return hipGetLastError();
-    }
-    if (m <= 2) hipLaunchKernelGGL((rows_kernel<2, GemmGroup>), dim3(blocks), dim3(256), lds, s, g);
-    else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8, GemmGroup>), dim3(blocks), dim3(256), lds, s, g);
-    else hipLaunchKernelGGL((rows_kernel<16, GemmGroup>), dim3(blocks), dim3(256), lds, s, g);
-    return hipGetLastError();
+    return launch_with(g, [&](const auto& f) {
+        using Group = std::decay_t<decltype(f)>;
+        if (m <= 2) hipLaunchKernelGGL((rows_kernel<2, Group>), dim3(blocks), dim3(256), lds, s, f);
+        else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8, Group>), dim3(blocks), dim3(256), lds, s, f);
+        else hipLaunchKernelGGL((rows_kernel<16, Group>), dim3(blocks), dim3(256), lds, s, f);
+    });
 }
 
 template <int BM, int BN, int NW, bool SPLIT = false>
@@ -1337,15 +1348,16 @@ hipError_t dispatch_layout(GemmGroup& g, hipStream_t s) {
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = tiles;
     dim3 grid(tiles), block(NW * 64);
     const GemmArgs& a = g.p[0];
-    if (a.a_kcontig && a.b_kcontig)
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, SPLIT>), grid, block, 0, s, g);
-    else if (a.a_kcontig && !a.b_kcontig)
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, false, SPLIT>), grid, block, 0, s, g);
-    else if (!a.a_kcontig && !a.b_kcontig && (!SPLIT || BM == 32))     // (the large tile: fp32 only)
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, false, false, SPLIT && BM == 32>), grid, block, 0, s, g);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (!a.a_kcontig && (a.b_kcontig || (SPLIT && BM != 32))) return hipErrorInvalidValue;     // (both row-contiguous: the large tile in fp32 only)
+    return launch_with(g, [&](const auto& f) {
+        using Group = std::decay_t<decltype(f)>;
+        if (a.a_kcontig && a.b_kcontig)
+            hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, SPLIT, 1, false, false, false, Group>), grid, block, 0, s, f);
+        else if (a.a_kcontig)
+            hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, false, SPLIT, 1, false, false, false, Group>), grid, block, 0, s, f);
+        else
+            hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, false, false, SPLIT && BM == 32, 1, false, false, false, Group>), grid, block, 0, s, f);
+    });
 }
 
 template <int WM, int WK>
@@ -1361,10 +1373,12 @@ hipError_t dispatch_product(GemmGroup& g, bool pool, hipStream_t s) {
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = tiles;
     const dim3 grid(tiles), block(WM * WK * 64);
     if (pool && add) return hipErrorInvalidValue;
-    if (pool) hipLaunchKernelGGL((product_kernel<WM, WK, false, true>), grid, block, 0, s, g);
-    else if (add) hipLaunchKernelGGL((product_kernel<WM, WK, true, false>), grid, block, 0, s, g);
-    else hipLaunchKernelGGL((product_kernel<WM, WK, false, false>), grid, block, 0, s, g);
-    return hipGetLastError();
+    return launch_with(g, [&](const auto& f) {
+        using Group = std::decay_t<decltype(f)>;
+        if (pool) hipLaunchKernelGGL((product_kernel<WM, WK, false, true, Group>), grid, block, 0, s, f);
+        else if (add) hipLaunchKernelGGL((product_kernel<WM, WK, true, false, Group>), grid, block, 0, s, f);
+        else hipLaunchKernelGGL((product_kernel<WM, WK, false, false, Group>), grid, block, 0, s, f);
+    });
 }
 
 template <bool AP, int PF>
@@ -1377,9 +1391,11 @@ hipError_t dispatch_pieces(GemmGroup& g, bool pool, hipStream_t s) {
         tiles += (((n + rows - 1) / rows) * ((g.p[i].N + BN - 1) / BN) + 7) / 8 * 8;
     }
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = tiles;
-    if (pool) hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP, true>), dim3(tiles), dim3(NW * 64), 0, s, g);
-    else hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP>), dim3(tiles), dim3(NW * 64), 0, s, g);
-    return hipGetLastError();
+    return launch_with(g, [&](const auto& f) {
+        using Group = std::decay_t<decltype(f)>;
+        if (pool) hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP, true, Group>), dim3(tiles), dim3(NW * 64), 0, s, f);
+        else hipLaunchKernelGGL((gemm_kernel<BM, BN, NW, true, true, true, PF, true, AP, false, Group>), dim3(tiles), dim3(NW * 64), 0, s, f);
+    });
 }
 
 }  // namespace
