@@ -1212,40 +1212,77 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
 // their weight rows (k-contiguous, a float4 per lane) and multiplies them with up to MR assembled rows held in
 // LDS; fp32 FMAs throughout.  One row: 3.4 us a layer against 6.5 to 7.1 for the tile kernel, and no split weights
 // are needed (9 us a pass).
-constexpr int ROWS_N = 2, ROWS_MAX = 16, ROWS_LDS = 16384;
+// Rows go to workgroups of four, two where there are no more.  (A workgroup that took all rows assembled, multiplied and reduced them one
+// after the other on a card that was nearly empty.  1, 2, 3, 4 and 16 rows of 400 into 800 columns 2.7, 3.2, 4.5, 4.9 and 11.0 us, now 2.7,
+// 2.9, 3.4, 3.5 and 4.2; of 800 into 400 3.1, 3.7, 5.8, 6.4 and 14.9, now 3.1, 3.3, 4.1, 4.2 and 4.3.)  From 17 rows on the tiles pool
+// intersections in their epilogues, which costs a launch here: up to 32 rows here 40 queries of all structures score in 89 against 81 us at
+// d = 512, h = 1024, 12 without intersections in 53 against 57 at 400, 800.
+constexpr int ROWS_N = 2, ROWS_M = 4, ROWS_MAX = 16, ROWS_LDS = 16384;
 template <int MR, class Group>
 __global__ __launch_bounds__(256) void rows_kernel(const Group g) {
-    extern __shared__ __attribute__((aligned(16))) float xs[];      // [M][K]
+    extern __shared__ __attribute__((aligned(16))) float xs[];      // [MR][K]
     int p = 0;
 #pragma unroll
     for (int i = 1; i < Group::MOST; ++i)
         if (i < g.count && (int)blockIdx.x >= g.tile_start[i]) p = i;
     const GemmArgs& a = g.p[p];
-    const int block = (int)blockIdx.x - g.tile_start[p];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k4 = a.K >> 2;
-    const int n0 = (block * 4 + wave) * ROWS_N;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (the arguments in one request and what they point to in another: one by one each costs a round trip, which is most of what a
+    // launch of one row takes)
+    const int32_t *a_ref = a.a_ref, *a_add_idx = a.a_add_idx, *dst_row = a.dst_row;
+    const float *A = a.A, *base0 = a.a_base0, *base1 = a.a_base1, *a_add = a.a_add, *B = a.B, *a_bias = a.bias;
+    float *C = a.C, *a_copy = a.a_copy;
+    const int rows = a.M, N = a.N, K = a.K, lda = a.lda, ldb = a.ldb, ldc = a.ldc, relu = a.relu;
+    asm volatile("" ::"s"(a_ref), "s"(a_add_idx), "s"(dst_row), "s"(A), "s"(base0), "s"(base1), "s"(a_add), "s"(B), "s"(a_bias), "s"(C), "s"(a_copy));
+    asm volatile("" ::"s"(rows), "s"(N), "s"(K), "s"(lda), "s"(ldb), "s"(ldc), "s"(relu));
+    const int groups_n = (N + 4 * ROWS_N - 1) / (4 * ROWS_N), block = (int)blockIdx.x - g.tile_start[p];
+    const int m0 = MR == 2 ? 0 : block / groups_n * MR, nb = MR == 2 ? block : block % groups_n, M = min(MR, rows - m0);      // (two rows: all there are)
+    const int k4 = K >> 2;
+    const int n0 = (nb * 4 + wave) * ROWS_N;
     // the first piece of the weight rows is on its way while the inputs are assembled
     const float* wrow[ROWS_N];
 #pragma unroll
-    for (int j = 0; j < ROWS_N; ++j) wrow[j] = a.B + (size_t)min(n0 + j, a.N - 1) * a.ldb;
+    for (int j = 0; j < ROWS_N; ++j) wrow[j] = B + (size_t)min(n0 + j, N - 1) * ldb;
     float4 w[ROWS_N];
 #pragma unroll
     for (int j = 0; j < ROWS_N; ++j) w[j] = load_global4(wrow[j] + min(lane, k4 - 1) * 4);
-    for (int idx = tid; idx < a.M * k4; idx += 256) {
-        const int m = idx / k4, c = (idx - m * k4) * 4;
-        const float* row = a.A + (size_t)m * a.lda;
-        if (a.a_ref) {
-            const int32_t r = a.a_ref[m];
-            row = r >= 0 ? a.a_base0 + (size_t)r * a.lda : a.a_base1 + (size_t)(-1 - r) * a.lda;
+    // a wavefront takes an input row (the last one again where there are fewer); a bias a column, a place a row.  (What is not
+    // given is read from the weights, and not used.)
+    const int mine = m0 + min(wave, M - 1);
+    const int32_t* none = reinterpret_cast<const int32_t*>(B);
+    const int32_t ref = (a_ref ? a_ref : none)[a_ref ? mine : 0], add_at = (a_add_idx ? a_add_idx : none)[a_add_idx ? mine : 0];
+    float bias[ROWS_N];
+    int to[MR];
+#pragma unroll
+    for (int j = 0; j < ROWS_N; ++j) bias[j] = (a_bias ? a_bias : B)[a_bias ? min(n0 + j, N - 1) : 0];
+#pragma unroll
+    for (int m = 0; m < MR; ++m) to[m] = (dst_row ? dst_row : none)[dst_row ? m0 + min(m, M - 1) : 0];
+    asm volatile("" ::"s"(ref), "s"(add_at), "s"(bias[0]), "s"(bias[1]), "s"(to[0]), "s"(to[MR - 1]));
+    static_assert(ROWS_N == 2, "biases named above");
+#pragma unroll
+    for (int j = 0; j < ROWS_N; ++j) bias[j] = a_bias ? bias[j] : 0.f;
+#pragma unroll
+    for (int m = 0; m < MR; ++m) to[m] = dst_row ? to[m] : m0 + m;
+    const float* row = !a_ref ? A + (size_t)mine * lda : ref >= 0 ? base0 + (size_t)ref * lda : base1 + (size_t)(-1 - ref) * lda;
+    const bool has_add = a_ref && a_add_idx;
+    const float* add = has_add ? a_add + (size_t)add_at * lda : row;
+    for (int c0 = lane * 4; wave < M && c0 < K; c0 += 1024) {
+        float4 x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = min(c0 + u * 256, K - 4);
+            x[u] = load_global4(row + c);
+            if (has_add) y[u] = load_global4(add + c);
         }
-        float4 v = load_global4(row + c);
-        if (a.a_ref && a.a_add_idx) {
-            const float4 t = load_global4(a.a_add + (size_t)a.a_add_idx[m] * a.lda + c);
-            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = c0 + u * 256;
+            if (c >= K) break;
+            float4 v = x[u];
+            if (has_add) { v.x += y[u].x; v.y += y[u].y; v.z += y[u].z; v.w += y[u].w; }
+            *reinterpret_cast<float4*>(xs + wave * K + c) = v;
+            if (nb == 0 && a_copy) *reinterpret_cast<float4*>(a_copy + (size_t)mine * lda + c) = v;
         }
-        *reinterpret_cast<float4*>(xs + m * a.K + c) = v;
-        if (block == 0 && a.a_copy) *reinterpret_cast<float4*>(a.a_copy + (size_t)m * a.lda + c) = v;
     }
     __syncthreads();
     float acc[MR][ROWS_N];
@@ -1261,7 +1298,7 @@ __global__ __launch_bounds__(256) void rows_kernel(const Group g) {
         if (q < k4) {
 #pragma unroll
             for (int m = 0; m < MR; ++m) {
-                const float4 x = *reinterpret_cast<const float4*>(xs + min(m, a.M - 1) * a.K + q * 4);
+                const float4 x = *reinterpret_cast<const float4*>(xs + min(m, M - 1) * K + q * 4);
 #pragma unroll
                 for (int j = 0; j < ROWS_N; ++j)
                     acc[m][j] += (x.x * w[j].x + x.y * w[j].y) + (x.z * w[j].z + x.w * w[j].w);
@@ -1272,17 +1309,12 @@ __global__ __launch_bounds__(256) void rows_kernel(const Group g) {
     }
 #pragma unroll
     for (int m = 0; m < MR; ++m) {
-        if (m < a.M) {       // uniform
+        if (MR == 2 && m >= M) break;        // uniform
 #pragma unroll
-            for (int j = 0; j < ROWS_N; ++j) {
-                float v = wave_sum_dpp(acc[m][j]);
-                const int n = n0 + j;
-                if (n < a.N) {
-                    if (a.bias) v += a.bias[n];
-                    if (a.relu) v = fmaxf(v, 0.f);
-                    if (lane == 0) a.C[(size_t)(a.dst_row ? a.dst_row[m] : m) * a.ldc + n] = v;
-                }
-            }
+        for (int j = 0; j < ROWS_N; ++j) {
+            float v = wave_sum_dpp(acc[m][j]) + bias[j];
+            if (relu) v = fmaxf(v, 0.f);
+            if (lane == 0 && m < M && n0 + j < N) C[(size_t)to[m] * ldc + n0 + j] = v;
         }
     }
 }
@@ -1321,20 +1353,22 @@ hipError_t launch_with(const GemmGroup& g, Launch launch) {
 }
 
 hipError_t dispatch_rows(GemmGroup& g, hipStream_t s) {
-    int blocks = 0, m = 1;
-    size_t lds = 0;
+    int blocks = 0, most = 1, k = 4;
+    for (int i = 0; i < g.count; ++i) {
+        most = std::max(most, g.p[i].M);
+        k = std::max(k, g.p[i].K);
+    }
+    const int mr = most <= 2 ? 2 : ROWS_M;
     for (int i = 0; i < g.count; ++i) {
         g.tile_start[i] = blocks;
-        blocks += (g.p[i].N + 4 * ROWS_N - 1) / (4 * ROWS_N);
-        m = std::max(m, g.p[i].M);
-        lds = std::max(lds, (size_t)g.p[i].M * g.p[i].K * sizeof(float));
+        blocks += (g.p[i].M + mr - 1) / mr * ((g.p[i].N + 4 * ROWS_N - 1) / (4 * ROWS_N));
     }
     for (int i = g.count; i <= GEMM_MAX_GROUP; ++i) g.tile_start[i] = blocks;
+    const size_t lds = (size_t)std::min(mr, most) * k * sizeof(float);
     return launch_with(g, [&](const auto& f) {
         using Group = std::decay_t<decltype(f)>;
-        if (m <= 2) hipLaunchKernelGGL((rows_kernel<2, Group>), dim3(blocks), dim3(256), lds, s, f);
-        else if (m <= 8) hipLaunchKernelGGL((rows_kernel<8, Group>), dim3(blocks), dim3(256), lds, s, f);
-        else hipLaunchKernelGGL((rows_kernel<16, Group>), dim3(blocks), dim3(256), lds, s, f);
+        if (mr == 2) hipLaunchKernelGGL((rows_kernel<2, Group>), dim3(blocks), dim3(256), lds, s, f);
+        else hipLaunchKernelGGL((rows_kernel<ROWS_M, Group>), dim3(blocks), dim3(256), lds, s, f);
     });
 }
 

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 5, 4), (1, 800, 400), (2, 401, 260), (3, 36, 1024), (8, 17, 800), (9, 72, 100),
-                                   (16, 33, 1024), (17, 33, 64)])
+                                   (16, 33, 1024), (17, 33, 64), (1, 9, 16384), (3, 8, 5460), (4, 16, 1028), (5, 12, 400)])
 def test_forward_layers_of_few_rows(M, N, K):
     import torch
     from paper_2602_21597_amd import binding
