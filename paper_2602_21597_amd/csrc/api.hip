@@ -1396,7 +1396,7 @@ constexpr int RANK_CHUNK = RANK_PIECE;
 // its launches, which normally find nothing to do, cost 2.2 us each (345 queries x 717 000 entities x 292: 1314 us a piece at a time, 1304 two).
 constexpr int NEAR_CHUNK = RANK_PIECES * RANK_CHUNK;
 constexpr int64_t NEAR_PAIRS = 1 << 29, NEAR_DIST = 1 << 26;
-constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k); rows the integer grid is made from
+constexpr int RANK_SAMPLE = 2048;      // most rows ranked in fp32 first (top-k of several pieces); rows the integer grid is made from
 constexpr int RANK_ROOM = 4096;        // entities per query and chunk that the filtered ranks may leave undecided (top-k: rank_filter.hip)
 
 // Where a chunk of entity rows lies: in the table (or its bf16 copy), or, with text features, fused
@@ -1482,7 +1482,11 @@ size_t device_free(const ngdb_ctx_t* c) {
 // Answers: the filter's counting takes as long per pair as 64 coordinates save, and each chunk has launches of its own:
 // 502 us in fp32 and 602 with the filter at 200 000 x 585 x 64, 250 and 230 at 15 000 x 585 x 256, 439 and 586 at 200 000 x 114 x
 // 256 (four chunks), 1357 and 1180 at 200 000 x 585 x 256.
-constexpr double NEAR_FROM = 3.3e9;
+// A table of one piece needs no fp32 rows, lists or chunks (pick_kernel), and the filter pays from less on, in the same units and order:
+// 8000 x 228 x 400 (0.67) 130 and 137, 30 000 x 114 x 400 (0.96) 160 and 147, 15 000 x 585 x 128 (1.1) 157 and 131, 5000 x 585 x 400 (1.2) 168 and
+// 157, 60 000 x 114 x 400 (1.9) 228 and 177, 65 000 x 1171 x 400 (32) 1402 and 447; with chunks from a sample of 2048 rows on the filter took
+// 184, 261, 151, 192, 291 and 540.  60 000 x 28 x 400 (below 0) 127 and 143.
+constexpr double NEAR_FROM = 3.3e9, WHOLE_FROM = 0.8e9;
 double near_work(const ngdb_ctx_t* c, int n_rows) {
     const int tile_rows = n_rows <= 32 ? 32 : (n_rows <= 64 ? 64 : (n_rows + 127) / 128 * 128);
     return (double)(tile_rows - 48) * c->cfg.n_entities * c->cfg.d;
@@ -1507,7 +1511,9 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
     const float* act = ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
-    const bool filtered = rank_filtered(c, R, near_work(c, R), NEAR_FROM);
+    const bool whole = N <= RANK_CHUNK;
+    bool filtered = rank_filtered(c, R, near_work(c, R), whole ? WHOLE_FROM : NEAR_FROM);
+    const bool needed = c->rank_filter_from >= 0 || near_work(c, R) >= NEAR_FROM;
     RankFilter f{};
     int most = RANK_CHUNK, chunk, at_once, ld, rc;
     while (filtered && most < std::min(N, NEAR_CHUNK) && 2ll * most * R <= NEAR_PAIRS) most *= 2;
@@ -1526,7 +1532,8 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         while (!emptied && at_once < chunk && 2ll * at_once * R <= NEAR_DIST) at_once *= 2;
         ld = (std::min(chunk, at_once) + 3) & ~3;
         rc = rank_buffers(c, R, B, ld, chunk, filtered ? 8 : 0, chunk, &f);
-        if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
+        if (rc == NGDB_ERR_OOM && emptied && filtered && !needed) filtered = false;      // (fp32 takes little longer, and the distances only)
+        else if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
             if (rc == NGDB_OK && shorter) c->near_free = device_free(c);
             break;
         }
@@ -1542,6 +1549,21 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     float* dist = ptr<float>(c->rank_dist);
     Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
     Timed tm(c, NGDB_TK_SCORE, s);
+    if (filtered && whole) {                 // the sums of all entities, the nearest of these, and what had no room in fp32
+        ChunkRows er;
+        if ((rc = rank_chunk_rows(c, 0, N, true, nullptr, s, &er)) != NGDB_OK) return rc;
+        if ((rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
+        f.parts = 1;                         // (the rows are fused with those of the sample, and rounded after them)
+        uint32_t* sums = reinterpret_cast<uint32_t*>(dist);
+        HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, N, s));
+        HIPCHK(c, launch_sum_tile(f, R, N, sums, ld, s));
+        HIPCHK(c, launch_pick(f, sums, ld, act, roots, pl->d_root_off, B, er.rows, er.rows16, N, topk, d_dist, d_ids, s));
+        only.any = f.overflowed;
+        HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, N, d, dist, ld, s, er.rows16, &only));
+        HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, 0, N, topk, false, d_dist, d_ids, s, &only));
+        c->rank_chunks = 1;
+        return NGDB_OK;
+    }
     // filtered: the sample's k-th distance lets k / sample of the first chunk pass, and chunks grow with what has
     // been ranked (each at most 12 times that), so that a list holds 12 k entities and some that are only near it
     const int sample = std::min(RANK_SAMPLE, std::max(512, 128 * topk));

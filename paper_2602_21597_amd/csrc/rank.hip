@@ -7,9 +7,9 @@
 // matrix cores cannot help): a workgroup owns a tile of (branch rows x entities),
 // 128 x 128 where both sides fill it, stages both operands k-major in LDS 16
 // coordinates at a time, and every lane accumulates an 8 x 8 block of distances in
-// registers, so that one 16-byte LDS read feeds 32 accumulations.  Large tables in
-// the vector family go through these kernels for a first sample only, and for what
-// the filter of rank_filter.hip cannot take.
+// registers, so that one 16-byte LDS read feeds 32 accumulations.  Vector
+// families with enough to do go through these kernels for a first sample at most, and
+// for what the filter of rank_filter.hip cannot take.
 //
 // The selection pass looks for a bound, lists what is within it and places that with the running result of
 // earlier chunks.  Order is (distance, entity id), so equal distances rank the lower id first.

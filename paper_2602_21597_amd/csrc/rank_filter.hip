@@ -25,6 +25,8 @@
 // one workgroup per query computes and merges.  Chunks grow with what has been ranked.  1024 queries
 // (1171 branch rows) x 5 M entities x 400: distance tiles 182.6 ms and merges 32.6 became integer sums 17.5 (34 T
 // operations of 4 coordinates a second; the instruction alone reaches 36) and merges 1.0.
+// Top-k of a table of one piece (65 536 rows): the 8-bit sums of all entities go to memory, and one workgroup per query takes its nearest
+// from them (pick_kernel).  512 queries x 15 000 x 400: fp32 rows 43 us, tiles of the rest 56 and merges 29 became sums 42 and 27.
 // Filtered ranks: the 16-bit sums decide all but about 0.1 % of the (entity, answer) comparisons: 1024
 // queries x 63 000 entities with 8 answers each, tiles 2.78 ms (0.32 of them for the answers' own
 // distances, now computed pair by pair) and counting 0.24 became 0.46 and 0.26.
@@ -274,7 +276,7 @@ __device__ __forceinline__ void sad_tile(const uint32_t* __restrict__ Yq, int ld
     }
 }
 // rows of the last tile row: 128, 64 or 32
-__device__ __forceinline__ int tail_rows(int n_rows, int r0) { return n_rows - r0 > 64 ? 128 : (n_rows - r0 > 32 ? 64 : 32); }
+__host__ __device__ __forceinline__ int tail_rows(int n_rows, int r0) { return n_rows - r0 > 64 ? 128 : (n_rows - r0 > 32 ? 64 : 32); }
 
 struct NearArgs {
     const uint32_t *Yq, *Eq;
@@ -385,18 +387,47 @@ __global__ __launch_bounds__(256) void near_tile_kernel(const NearArgs g) {
     else near_tile<2>(g, r0, e0, L);
 }
 
-// Filtered ranks: the sums themselves, sums[r * ld + e] = SAD
-template <int RPL>
+// Filtered ranks, and the top-k of tables of one piece: the sums themselves, sums[r * ld + e] = SAD
+// (15 000 entities x 585 rows x 400 coordinates by tiles of 64 rows 42 us, of 128 48; 60 000 x 228 x 400 the other way round, 272 and 241 us a ranking.)
+// Top-k (8 bits): also edge[r * tiles + tile] = the least of the tile's sums less the entities' errors, and with them
+__device__ __forceinline__ int32_t least_of_16(int32_t v) {        // over lanes 16 i .. 16 i + 15, rotated by 8, 4, 2, 1
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true));
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, true));
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x122, 0xF, 0xF, true));
+    return min(v, __builtin_amdgcn_mov_dpp(v, 0x121, 0xF, 0xF, true));
+}
+template <int BITS, int RPL>
 __device__ __forceinline__ void sum_tile(const uint32_t* __restrict__ Yq, int ldy, int n_rows, const uint32_t* __restrict__ Eq,
                                          int lde, int n_ent, int words, uint32_t* __restrict__ sums, int ld, int r0, int e0,
-                                         uint32_t* lds) {
+                                         const int32_t* __restrict__ slack, int2* __restrict__ edge, uint32_t* lds) {
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     uint32_t acc[RPL][8];
 #pragma unroll
     for (int i = 0; i < RPL; ++i)
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[i][j] = 0u;
-    sad_tile<16, RPL>(Yq, ldy, r0, Eq, lde, e0, words, acc, lds);
+    sad_tile<BITS, RPL>(Yq, ldy, r0, Eq, lde, e0, words, acc, lds);
+    if (BITS == 8) {
+        int32_t sl[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int e = e0 + (j >> 2) * 64 + tx * 4 + (j & 3);
+            sl[j] = e < n_ent ? slack_of(slack[e]) : -1;
+        }
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {
+            int32_t lo = UNBOUNDED, hi = UNBOUNDED;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                lo = min(lo, sl[j] >= 0 ? (int32_t)acc[i][j] - sl[j] : UNBOUNDED);
+                hi = min(hi, sl[j] >= 0 ? (int32_t)acc[i][j] + sl[j] : UNBOUNDED);
+            }
+            lo = least_of_16(lo);
+            hi = least_of_16(hi);
+            const int r = r0 + ty * RPL + i;
+            if (tx == 0 && r < n_rows) edge[(size_t)r * gridDim.x + blockIdx.x] = make_int2(lo, hi);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < RPL; ++i) {
         const int r = r0 + ty * RPL + i;
@@ -415,15 +446,17 @@ __device__ __forceinline__ void sum_tile(const uint32_t* __restrict__ Yq, int ld
         }
     }
 }
+template <int BITS>
 __global__ __launch_bounds__(256) void sum_tile_kernel(const uint32_t* __restrict__ Yq, int ldy, int n_rows,
                                                        const uint32_t* __restrict__ Eq, int lde, int n_ent, int words,
-                                                       uint32_t* __restrict__ sums, int ld) {
+                                                       uint32_t* __restrict__ sums, int ld, int tile_rows,
+                                                       const int32_t* __restrict__ slack, int2* __restrict__ edge) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[TILE_LDS];
-    const int r0 = blockIdx.y * 128, e0 = blockIdx.x * 128;
-    const int rows = tail_rows(n_rows, r0);
-    if (rows == 128) sum_tile<8>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, lds);
-    else if (rows == 64) sum_tile<4>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, lds);
-    else sum_tile<2>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, lds);
+    const int r0 = blockIdx.y * tile_rows, e0 = blockIdx.x * 128;
+    const int rows = min(tile_rows, tail_rows(n_rows, r0));
+    if (rows == 128) sum_tile<BITS, 8>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, slack, edge, lds);
+    else if (rows == 64) sum_tile<BITS, 4>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, slack, edge, lds);
+    else sum_tile<BITS, 2>(Yq, ldy, n_rows, Eq, lde, n_ent, words, sums, ld, r0, e0, slack, edge, lds);
 }
 
 // ---------------------------------------------------------------- fp32 distances of a list
@@ -812,6 +845,159 @@ __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step
     return {none ? -INFINITY : fmaf(-rounding, fabsf(lo), lo), none ? INFINITY : fmaf(rounding, fabsf(hi), hi)};
 }
 
+// Top-k of a table of one piece: the sums of all its entities are in memory, and one workgroup per query takes its k nearest from them.
+// The tiles have left the least upper and lower bound of every row: the k-th smallest upper one of 64 groups of tiles is a bound that k
+// entities keep, hardly more than k of them.  Tiles that reach below it are looked through, and whatever may lie within it, some two or
+// three times k, is computed; what lies within the same bound on these distances is placed by counting.  Lists without room go
+// to the fp32 pass, with no result yet.  512 queries x 15 000 entities x 400: 42 us looking through all sums twice, 27 through the tiles.  128 registers a lane: four workgroups a compute unit (158, two rounds of 512 queries: 59 us against 42).
+constexpr int PICK_T = 256, PICK_ROOM = 2048, PICK_SLABS = 4, PICK_AHEAD = 4, PICK_WALK = 4;
+static_assert(PICK_ROOM <= 32 * PICK_T, "a thread's places in the list are bits of a word");
+struct PickArgs {
+    const float *act, *E, *base, *grid;
+    const uint16_t* E16;
+    const int32_t *row_ids, *root_off, *slack;
+    const uint32_t* sums;
+    const int2* edge;
+    int32_t *count, *overflowed;
+    float* out_dist;
+    int32_t* out_ids;
+    int ld, n_ent, d, k, room, ldb;
+    float rounding;
+};
+template <bool B16>
+__global__ __launch_bounds__(PICK_T, 4) void pick_kernel(const PickArgs g) {
+    __shared__ __attribute__((aligned(16))) float slab[PICK_SLABS][64 * slab_ld(16)];
+    __shared__ uint32_t nearest[PICK_ROOM];
+    __shared__ int32_t list[PICK_ROOM];
+    __shared__ float s_least[PICK_T], s_bound[2];
+    __shared__ int32_t n_list, n_valid;
+    const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6, k = g.k;
+    const int r_lo = g.root_off[q], r_hi = g.root_off[q + 1];
+    const float step = g.grid[0];
+    if (t == 0) n_list = n_valid = 0;
+    auto bound_of = [&](float v, float* out) {           // the k-th smallest of the 64 groups' smallest values
+        s_least[t] = v;
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int w = 1; w < PICK_T / 64; ++w) v = fminf(v, s_least[w * 64 + lane]);
+            int smaller = 0;
+#pragma unroll
+            for (int j = 0; j < 64; ++j) {
+                const float o = lane_value(v, j);
+                smaller += (o < v || (o == v && j < lane)) ? 1 : 0;
+            }
+            if (smaller == k - 1) *out = v;
+        }
+        __syncthreads();
+        return *out;
+    };
+    const int n_tx = (g.n_ent + 127) / 128;
+    float least = INFINITY;
+    for (int r = r_lo; r < r_hi; ++r) {
+        int32_t sum_least = UNBOUNDED;
+        for (int x = t; x < n_tx; x += PICK_T) sum_least = min(sum_least, g.edge[(size_t)r * n_tx + x].y);
+        const float hi = fmaf((float)sum_least, step, g.base[g.ldb + r]);
+        if (sum_least < UNBOUNDED) least = fminf(least, fmaf(g.rounding, fabsf(hi), hi));
+    }
+    const float most = bound_of(least, &s_bound[0]);
+    for (int r = r_lo; r < r_hi; ++r) {
+        const float bound = (most * (1.f + g.rounding) - g.base[r]) * g.grid[1] + 4.f;
+        // (no bound, or not a number: everything qualifies; entities of unbounded error always do)
+        const int32_t sum_most = bound < 5e8f ? (int32_t)fmaxf(bound, -(float)(UNBOUNDED - SUM_BIAS)) : INT_MAX / 2 - 1;
+        for (int x0 = 0; x0 < n_tx; x0 += PICK_T) {      // (neighbouring tiles go to different wavefronts)
+            const int mine = x0 + lane * (PICK_T / 64) + wave;
+            unsigned long long m = __ballot(mine < n_tx && g.edge[(size_t)r * n_tx + min(mine, n_tx - 1)].x <= sum_most);
+            while (m != 0ull) {
+                int e[PICK_WALK];
+                uint2 sum[PICK_WALK];
+                int2 sl[PICK_WALK];
+#pragma unroll
+                for (int i = 0; i < PICK_WALK; ++i) {
+                    const int from = m ? __ffsll(m) - 1 : 0;
+                    e[i] = m ? (x0 + from * (PICK_T / 64) + wave) * 128 + 2 * lane : g.n_ent;
+                    m &= m - 1ull;
+                    const int at = min(e[i], (g.n_ent - 1) & ~1);
+                    sum[i] = *reinterpret_cast<const uint2*>(g.sums + (size_t)r * g.ld + at);
+                    sl[i] = *reinterpret_cast<const int2*>(g.slack + at);
+                }
+#pragma unroll
+                for (int i = 0; i < PICK_WALK; ++i) {
+                    auto look = [&](int id, uint32_t v, int32_t err) {
+                        if (id >= g.n_ent || (int32_t)v - slack_of(err) > sum_most) return;
+                        const int at = atomicAdd(&n_list, 1);
+                        if (at < PICK_ROOM) {
+                            list[at] = id;
+                            nearest[at] = 0xFFFFFFFFu;
+                        }
+                    };
+                    look(e[i], sum[i].x, sl[i].x);
+                    look(e[i] + 1, sum[i].y, sl[i].y);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int n = n_list;
+    float* out_d = g.out_dist + (size_t)q * k;
+    int32_t* out_i = g.out_ids + (size_t)q * k;
+    if (n > PICK_ROOM) {                                 // uniform
+        if (t < k) {
+            out_d[t] = INFINITY;
+            out_i[t] = -1;
+        }
+        if (t == 0) {
+            g.count[q] = g.room + 1;
+            *g.overflowed = 1;
+        }
+        return;
+    }
+    const int parts = (n + 63) / 64, units = parts * (r_hi - r_lo);
+    if (wave < PICK_SLABS) {
+        for (int u = wave; u < units; u += PICK_SLABS) {
+            const int r = r_lo + u / parts, x = (u % parts) * 64 + lane;
+            const int32_t e = x < n ? list[x] : list[0];
+            const float dv = exact_distance<B16, 16, PICK_AHEAD>(g.act, g.row_ids, r, r + 1, g.E, g.E16, e, g.d, slab[wave]);
+            if (x < n) atomicMin(&nearest[x], __builtin_bit_cast(uint32_t, dv));       // (no distance is negative; NaN is above all others)
+        }
+    }
+    __syncthreads();
+    if (r_hi - r_lo > 1) {                               // an entity that several branches have listed stays once
+        uint32_t twice = 0u;
+        for (int x = t, i = 0; x < n; x += PICK_T, ++i)
+#pragma unroll 8
+            for (int j = 0; j < x; ++j) twice |= list[j] == list[x] ? 1u << i : 0u;
+        __syncthreads();
+        for (int x = t, i = 0; x < n; x += PICK_T, ++i)
+            if (twice >> i & 1u) nearest[x] = 0xFFFFFFFFu;
+        __syncthreads();
+    }
+    least = INFINITY;
+    for (int x = t; x < n; x += PICK_T) {
+        const float v = __builtin_bit_cast(float, nearest[x]);
+        least = fminf(least, v);
+        const unsigned long long m = __ballot(v == v);
+        if (lane == __ffsll(m) - 1) atomicAdd(&n_valid, __popcll(m));
+    }
+    const float within = bound_of(least, &s_bound[1]);
+    for (int x = t; x < n; x += PICK_T) {
+        const float v = __builtin_bit_cast(float, nearest[x]);
+        if (!(v <= within)) continue;
+        const int32_t id = list[x];
+        int place = 0;
+#pragma unroll 8
+        for (int j = 0; j < n; ++j) place += before(__builtin_bit_cast(float, nearest[j]), list[j], v, id) ? 1 : 0;
+        if (place < k) {
+            out_d[place] = v;
+            out_i[place] = id;
+        }
+    }
+    if (t >= n_valid && t < k) {
+        out_d[t] = INFINITY;
+        out_i[t] = -1;
+    }
+}
+
 // closer[a] += entities that are certainly closer than answer a; an entity that may lie between its bounds from
 // some answer of the query is not decided and goes to the query's list.  Grid (parts, queries): a workgroup
 // takes every gridDim.x-th slab of 2048 entities, 8 per lane.  The thresholds of a query lie sorted in LDS: an entity looks
@@ -1100,10 +1286,34 @@ hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, c
     return hipGetLastError();
 }
 
+hipError_t launch_pick(const RankFilter& f, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
+                       int n_queries, const float* E, const uint16_t* E16, int n_ent, int k, float* out_dist, int32_t* out_ids, hipStream_t s) {
+    if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
+    if (k < 1 || k > NGDB_MAX_TOPK || f.parts != 1 || (ld & 3) || n_ent > RANK_PIECE) return hipErrorInvalidValue;
+    const PickArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, sums, reinterpret_cast<const int2*>(f.found_pair), f.count, f.overflowed, out_dist, out_ids,
+                     ld, n_ent, f.d, k, f.room, f.ldy, rounding_of(f.d)};
+    if (E16) hipLaunchKernelGGL(pick_kernel<true>, dim3(n_queries), dim3(PICK_T), 0, s, g);
+    else hipLaunchKernelGGL(pick_kernel<false>, dim3(n_queries), dim3(PICK_T), 0, s, g);
+    return hipGetLastError();
+}
+
 hipError_t launch_sum_tile(const RankFilter& f, int n_rows, int n_ent, uint32_t* sums, int ld, hipStream_t s) {
     if (n_rows <= 0 || n_ent <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sum_tile_kernel, dim3((n_ent + 127) / 128, (n_rows + 127) / 128), dim3(256), 0, s, (const uint32_t*)f.Yq,
-                       f.ldy, n_rows, (const uint32_t*)f.Eq, f.lde, n_ent, f.words, sums, ld);
+    // Tiles of 64 rows take more time for the same pairs, but go round 256 compute units with less left over: sixths of a
+    // tile of 128 that the busiest one has, either way.
+    const int tiles_e = (n_ent + 127) / 128;
+    auto turns = [&](int tr, int cost) {
+        const int rest = n_rows % tr, quarters = n_rows / tr * (tr / 32) + (rest == 0 ? 0 : std::min(tr, tail_rows(rest, 0)) / 32);
+        return (int)(((int64_t)tiles_e * quarters / (tr / 32) + 255) / 256) * cost;
+    };
+    const int tile_rows = turns(64, 4) < turns(128, 7) ? 64 : 128;
+    const dim3 grid(tiles_e, (n_rows + tile_rows - 1) / tile_rows), block(256);
+    if (f.bits == 8)
+        hipLaunchKernelGGL(sum_tile_kernel<8>, grid, block, 0, s, (const uint32_t*)f.Yq, f.ldy, n_rows, (const uint32_t*)f.Eq, f.lde, n_ent,
+                           f.words, sums, ld, tile_rows, (const int32_t*)f.slack, reinterpret_cast<int2*>(f.found_pair));
+    else
+        hipLaunchKernelGGL(sum_tile_kernel<16>, grid, block, 0, s, (const uint32_t*)f.Yq, f.ldy, n_rows, (const uint32_t*)f.Eq, f.lde, n_ent,
+                           f.words, sums, ld, tile_rows, (const int32_t*)f.slack, reinterpret_cast<int2*>(f.found_pair));
     return hipGetLastError();
 }
 

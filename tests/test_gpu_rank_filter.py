@@ -212,6 +212,39 @@ def test_merging_by_queries(B, edit):
         np.testing.assert_array_equal(a, b)
 
 
+def _no_numbers(rows):
+    def edit(P):
+        P["E"][rows[0]] = np.nan
+        P["E"][rows[1]] = np.inf
+    edit.__name__ = "_no_numbers(%s)" % (rows,)
+    return edit
+
+
+# tables of one piece: 33 tiles of entities (fewer than groups), all of 512, ragged ends; row tiles of 64 and of 128 with every remainder;
+# rows that are no numbers, of the grid's sample (every fourth) and not; more copies of the nearest entity than a list has room for, and fewer
+@pytest.mark.parametrize("N,d,B,copies,edit", [(4097, 8, 5, 0, None), (65536, 4, 40, 0, None), (65535, 8, 300, 0, None), (8190, 400, 130, 0, None),
+                                               (15000, 36, 512, 0, None), (9001, 20, 77, 0, _no_numbers((7, 4001))),
+                                               (9001, 20, 77, 0, _no_numbers((8, 4000))), (9000, 16, 24, 1900, None), (9000, 16, 24, 2100, None)])
+def test_tables_of_one_piece(N, d, B, copies, edit):
+    from paper_2602_21597_amd import binding
+    par.say("rank filter: N=%d d=%d B=%d, %d copies %s" % (N, d, B, copies, edit.__name__ if edit else ""))
+    case = par.Case(N, 12, d, 32, B, 2, 8.0, mix={"1p": 1.0} if copies else {"1p": 0.4, "2i": 0.2, "2u": 0.4}, seed=87, T=2 * N,
+                    params_edit=edit)
+    got = []
+    for limit in (0, 1 << 60):
+        eng = case.engine()
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, limit) == 0
+        plan = eng.plan(case.qb.select(np.zeros(B, int)) if copies else case.qb)
+        E = eng.tensors["E"][0]
+        E[100:100 + copies] = E[eng.rank_all(plan, 1)[0][0, 0].long()]
+        got.append([x.cpu().numpy() for k in (1, 10, 16) for x in eng.rank_all(plan, k)])
+        if limit == 0 and edit is None:
+            assert binding.lib().ngdb_debug_rank_overflows(eng.ctx) == (1 if copies > 2048 else 0)
+        plan.free()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 # text features: rows rounded as they are fused: two words, a column part, two words more, two parts; errors
 # that only a part of a row has or that bound nothing; a second chunk of the filtered ranks: the results of the fp32 pass
 @pytest.mark.parametrize("N,d,edit", [(9001, 8, None), (6001, 208, _outliers), (6001, 216, _shifted), (9001, 400, _far_group(700.0)),
