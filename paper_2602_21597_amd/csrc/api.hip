@@ -1626,21 +1626,20 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     int32_t* in_chunk = total + n_ans;
     Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
     Timed tm(c, NGDB_TK_SCORE, s);
-    HIPCHK(c, launch_fill_zero_i32(total, 2 * n_ans, s));
     // distance of every listed answer to its query (the arithmetic of the all-entity pass, so an answer
     // compares equal to itself there)
     for (int a0 = 0; a0 < n_ans; a0 += RANK_CHUNK) {
         const int cnt = std::min(RANK_CHUNK, n_ans - a0);
-        const float* rows = c->prm.E.p;
+        const float* ans_rows = c->prm.E.p;
         if (sem) {
             SemFuseArgs fa{};
             fa.H = c->prm.H_sem; fa.Wb = ptr<uint16_t>(c->Wb); fa.E = c->prm.E.p; fa.ids = d_ans + a0; fa.n_rows = cnt;
             fa.d = d; fa.ds = c->cfg.d_sem; fa.out = ptr<float>(c->rank_ef);
             HIPCHK(c, launch_sem_fuse(fa, s));
-            rows = ptr<float>(c->rank_ef);
+            ans_rows = ptr<float>(c->rank_ef);
         }
         HIPCHK(c, launch_answer_distance(act, box_off, c->cfg.box_alpha, roots, pl->d_root_off, d_ans_off, B, sem ? nullptr : d_ans, a0, cnt,
-                                         rows, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr, d, thr, s));
+                                         ans_rows, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr, d, thr, total, n_ans, s));
     }
     // entities strictly closer than each answer, chunk by chunk
     for (int e0 = 0; e0 < N; e0 += chunk) {

@@ -469,10 +469,11 @@ hipError_t launch_count_sure(const RankFilter& f, const uint32_t* sums, int ld, 
 hipError_t launch_count_open(const RankFilter& f, int chunk, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
                              const int32_t* ans_off, const float* thr, int n_queries, const float* E, const uint16_t* E16,
                              int32_t* chunk_count, int32_t* total, hipStream_t s);
-// thr[a] = fp32 distance of answer a to its query, a0 <= a < a0 + cnt (row ans[a] of E, or row a - a0 where ans is null)
+// thr[a] = fp32 distance of answer a to its query, a0 <= a < a0 + cnt (row ans[a] of E, or row a - a0 where ans is null);
+// counters[a] = counters[n_ans + a] = 0 for them
 hipError_t launch_answer_distance(const float* act, const float* off, float alpha, const int32_t* row_ids, const int32_t* root_off,
                                   const int32_t* ans_off, int n_queries, const int32_t* ans, int a0, int cnt, const float* E,
-                                  const uint16_t* E16, int d, float* thr, hipStream_t s);
+                                  const uint16_t* E16, int d, float* thr, int32_t* counters, int n_ans, hipStream_t s);
 
 // ---------------------------------------------------------------- index (index.hip)
 struct IndexBuffers {   // device scratch owned by the context, sized for n_keys

@@ -419,29 +419,44 @@ __global__ __launch_bounds__(256) void finish_rank_kernel(const int32_t* __restr
 
 // out[0] = mean reciprocal rank, out[1..3] = Hit@1, @3, @10: per query the mean over its first
 // n_take[q] listed answers (all if n_take is null), then the mean over the queries that have one.
-// One workgroup, fixed summation order.
-__global__ __launch_bounds__(256) void rank_metrics_kernel(const int32_t* __restrict__ rank,
-                                                           const int32_t* __restrict__ ans_off,
-                                                           const int32_t* __restrict__ n_take, int n_queries,
-                                                           float* __restrict__ out) {
-    __shared__ float part[256][5];
+// One workgroup, fixed summation order: the queries of 1024 threads at a time, then 256 sums of every 256th query, then these
+// (a thread per sum for all of its queries: 1024 queries of 8 answers 12 us, 5.6 so).
+constexpr int METRIC_T = 1024;
+__global__ __launch_bounds__(METRIC_T) void rank_metrics_kernel(const int32_t* __restrict__ rank,
+                                                                const int32_t* __restrict__ ans_off,
+                                                                const int32_t* __restrict__ n_take, int n_queries,
+                                                                float* __restrict__ out) {
+    __shared__ float per[METRIC_T][5], part[256][5];
     float acc[5] = {0.f, 0.f, 0.f, 0.f, 0.f};      // MRR, H@1, H@3, H@10, queries counted
-    for (int q = threadIdx.x; q < n_queries; q += 256) {
-        const int lo = ans_off[q];
-        const int n = n_take ? min(n_take[q], ans_off[q + 1] - lo) : ans_off[q + 1] - lo;
-        if (n <= 0) continue;
-        float rr = 0.f, h1 = 0.f, h3 = 0.f, h10 = 0.f;
-        for (int j = 0; j < n; ++j) {
-            const int r = rank[lo + j];
-            rr += 1.f / (float)r;
-            h1 += r <= 1 ? 1.f : 0.f;
-            h3 += r <= 3 ? 1.f : 0.f;
-            h10 += r <= 10 ? 1.f : 0.f;
+    for (int q0 = 0; q0 < n_queries; q0 += METRIC_T) {
+        const int q = q0 + threadIdx.x;
+        float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+        if (q < n_queries) {
+            const int lo = ans_off[q];
+            const int n = n_take ? min(n_take[q], ans_off[q + 1] - lo) : ans_off[q + 1] - lo;
+            float rr = 0.f, h1 = 0.f, h3 = 0.f, h10 = 0.f;
+#pragma unroll 4
+            for (int j = 0; j < n; ++j) {
+                const int r = rank[lo + j];
+                rr += 1.f / (float)r;
+                h1 += r <= 1 ? 1.f : 0.f;
+                h3 += r <= 3 ? 1.f : 0.f;
+                h10 += r <= 10 ? 1.f : 0.f;
+            }
+            if (n > 0) {
+                const float inv = 1.f / (float)n;
+                v[0] = rr * inv; v[1] = h1 * inv; v[2] = h3 * inv; v[3] = h10 * inv; v[4] = 1.f;
+            }
         }
-        const float inv = 1.f / (float)n;
-        acc[0] += rr * inv; acc[1] += h1 * inv; acc[2] += h3 * inv; acc[3] += h10 * inv; acc[4] += 1.f;
+        __syncthreads();                               // the round before has been read
+        for (int k = 0; k < 5; ++k) per[threadIdx.x][k] = v[k];
+        __syncthreads();
+        if (threadIdx.x < 256)
+            for (int i = 0; i < METRIC_T; i += 256)
+                for (int k = 0; k < 5; ++k) acc[k] += per[i + threadIdx.x][k];
     }
-    for (int k = 0; k < 5; ++k) part[threadIdx.x][k] = acc[k];
+    if (threadIdx.x < 256)
+        for (int k = 0; k < 5; ++k) part[threadIdx.x][k] = acc[k];
     __syncthreads();
     for (int off = 128; off > 0; off >>= 1) {
         if ((int)threadIdx.x < off)
@@ -506,7 +521,7 @@ hipError_t launch_finish_rank(const int32_t* count, const float* thr, const int3
 
 hipError_t launch_rank_metrics(const int32_t* rank, const int32_t* ans_off, const int32_t* n_take, int n_queries,
                                float* out, hipStream_t s) {
-    hipLaunchKernelGGL(rank_metrics_kernel, dim3(1), dim3(256), 0, s, rank, ans_off, n_take, n_queries, out);
+    hipLaunchKernelGGL(rank_metrics_kernel, dim3(1), dim3(METRIC_T), 0, s, rank, ans_off, n_take, n_queries, out);
     return hipGetLastError();
 }
 
