@@ -1498,12 +1498,10 @@ bool rank_filtered(const ngdb_ctx_t* c, int n_rows, double work, double from) {
 }
 
 // The grid of a filtered pass, from rows spread over the table (the first rows alone would leave a table that is ordered
-// by kind with most of its rows off the grid, every list overflowing and every chunk paid twice), and the branch rows on it.
-int rank_filter_begin(ngdb_ctx_t* c, const ngdb_plan_t* pl, const RankFilter& f, const int32_t* roots, const float* fused_sample,
-                      hipStream_t s) {
+// by kind with most of its rows off the grid, every list overflowing and every chunk paid twice).
+int rank_filter_begin(ngdb_ctx_t* c, const RankFilter& f, const float* fused_sample, hipStream_t s) {
     HIPCHK(c, launch_rank_grid(f, fused_sample ? fused_sample : c->prm.E.p, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr,
                                fused_sample ? 1 : c->cfg.n_entities / RANK_SAMPLE, RANK_SAMPLE, s));
-    HIPCHK(c, launch_rank_rows(f, ptr<float>(c->act), roots, pl->hp.n_roots, pl->d_root_off, pl->hp.n_queries, s));
     return NGDB_OK;
 }
 
@@ -1548,14 +1546,15 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     if (rc != NGDB_OK) return rc == NGDB_ERR_OOM ? no_rank_memory(c) : rc;
     float* dist = ptr<float>(c->rank_dist);
     Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
+    const RankRows rows{act, roots, R, pl->d_root_off, B};
     Timed tm(c, NGDB_TK_SCORE, s);
     if (filtered && whole) {                 // the sums of all entities, the nearest of these, and what had no room in fp32
         ChunkRows er;
         if ((rc = rank_chunk_rows(c, 0, N, true, nullptr, s, &er)) != NGDB_OK) return rc;
-        if ((rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
+        if ((rc = rank_filter_begin(c, f, er.sample, s)) != NGDB_OK) return rc;
         f.parts = 1;                         // (the rows are fused with those of the sample, and rounded after them)
         uint32_t* sums = reinterpret_cast<uint32_t*>(dist);
-        HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, N, s));
+        HIPCHK(c, launch_quantise(f, &rows, er.rows, er.rows16, N, s));
         HIPCHK(c, launch_sum_tile(f, R, N, sums, ld, s));
         HIPCHK(c, launch_pick(f, sums, ld, act, roots, pl->d_root_off, B, er.rows, er.rows16, N, topk, d_dist, d_ids, s));
         only.any = f.overflowed;
@@ -1577,10 +1576,11 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         if (!rounded) {
             HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16));
             HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, s));
-            if (filtered && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
+            if (filtered && (rc = rank_filter_begin(c, f, er.sample, s)) != NGDB_OK) return rc;
             ++i_piece;
         } else {
-            if (c->cfg.d_sem == 0) HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
+            const bool fused = c->cfg.d_sem > 0;
+            if (!fused || e0 == sample) HIPCHK(c, launch_quantise(f, e0 == sample ? &rows : nullptr, er.rows, er.rows16, fused ? 0 : cnt, s));
             HIPCHK(c, launch_near_tile(f, R, cnt, d_dist, topk, s));
             HIPCHK(c, launch_near_merge(f, i_piece, act, roots, pl->d_root_off, B, er.rows, er.rows16, e0, cnt, topk, d_dist, d_ids, s));
             for (int p0 = 0; p0 < cnt; p0 += at_once) {
@@ -1624,6 +1624,7 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
     float* thr = d_ans_dist ? d_ans_dist : ptr<float>(c->rank_thr);
     int32_t* total = ptr<int32_t>(c->rank_count);
     int32_t* in_chunk = total + n_ans;
+    const RankRows rows{act, roots, R, pl->d_root_off, B};
     Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
     Timed tm(c, NGDB_TK_SCORE, s);
     // distance of every listed answer to its query (the arithmetic of the all-entity pass, so an answer
@@ -1648,9 +1649,9 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
         const bool rounded = filtered && sem && e0 > 0;      // (the first chunk's rows hold the sample that the grid comes from)
         if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, rounded ? &f : nullptr, s, &er)) != NGDB_OK) return rc;
         if (filtered) {
-            if (e0 == 0 && (rc = rank_filter_begin(c, pl, f, roots, er.sample, s)) != NGDB_OK) return rc;
+            if (e0 == 0 && (rc = rank_filter_begin(c, f, er.sample, s)) != NGDB_OK) return rc;
             f.parts = rounded ? sem_fuse_parts(d) : 1;
-            if (!rounded) HIPCHK(c, launch_rank_entities(f, er.rows, er.rows16, cnt, s));
+            if (!rounded) HIPCHK(c, launch_quantise(f, e0 == 0 ? &rows : nullptr, er.rows, er.rows16, cnt, s));
             HIPCHK(c, launch_sum_tile(f, R, cnt, reinterpret_cast<uint32_t*>(dist), ld, s));
             HIPCHK(c, launch_count_sure(f, reinterpret_cast<const uint32_t*>(dist), ld, pl->d_root_off, d_ans_off, thr, B, cnt, in_chunk, s));
             HIPCHK(c, launch_count_open(f, e0 / chunk, reinterpret_cast<const uint32_t*>(dist), ld, act, roots, pl->d_root_off, d_ans_off, thr, B, er.rows, er.rows16, in_chunk, total, s));

@@ -450,9 +450,10 @@ int rank_filter_words(int d, int bits);
 size_t rank_found_bytes(int ldy, int lde);
 // the grid of a pass from n_rows rows of a table, row_step apart; clears found and the counters
 hipError_t launch_rank_grid(const RankFilter& f, const float* E, const uint16_t* E16, int64_t row_step, int n_rows, hipStream_t s);
-hipError_t launch_rank_rows(const RankFilter& f, const float* act, const int32_t* row_ids, int n_rows, const int32_t* root_off,
-                            int n_queries, hipStream_t s);
-hipError_t launch_rank_entities(const RankFilter& f, const float* E, const uint16_t* E16, int n_ent, hipStream_t s);
+// the branch rows of a pass, and the entity rows of a chunk, on the grid: both in one launch (8 us of one's own for the few branch rows), or
+// either (rows null; n_ent 0)
+struct RankRows { const float* act; const int32_t* ids; int n; const int32_t* root_off; int n_queries; };
+hipError_t launch_quantise(const RankFilter& f, const RankRows* rows, const float* E, const uint16_t* E16, int n_ent, hipStream_t s);
 // lists the chunk's entities that may be among the k nearest (best: running [queries, k] distances), and merges them
 hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const float* best, int k, hipStream_t s);
 hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, const int32_t* row_ids, const int32_t* root_off,

@@ -126,17 +126,18 @@ __global__ __launch_bounds__(1024) void make_grid_kernel(const float* __restrict
 // !ENT (branch rows, ids): base[i] = excess - err and base[ld + i] = excess + err (for bounds from
 // below and from above), and row_q[i] = the query the row belongs to.
 template <int BITS, bool ENT, int RW>
-__global__ __launch_bounds__(256) void quantise_kernel(const float* __restrict__ X, const uint16_t* __restrict__ X16,
-                                                       const int32_t* __restrict__ ids, int n_rows, int d, int words,
-                                                       const float* __restrict__ lo, const float* __restrict__ grid,
-                                                       uint32_t* __restrict__ Q, int ld, int32_t* __restrict__ slack,
-                                                       float* __restrict__ base, const int32_t* __restrict__ root_off,
-                                                       int n_queries, int32_t* __restrict__ row_q) {
+__device__ __forceinline__ void quantise(int block, const float* __restrict__ X, const uint16_t* __restrict__ X16,
+                                         const int32_t* __restrict__ ids, int n_rows, int d, int words,
+                                         const float* __restrict__ lo, const float* __restrict__ grid,
+                                         uint32_t* __restrict__ Q, int ld, int32_t* __restrict__ slack,
+                                         float* __restrict__ base, const int32_t* __restrict__ root_off,
+                                         int n_queries, int32_t* __restrict__ row_q, uint32_t* lds) {
     constexpr int WPQ = BITS == 8 ? 1 : 2;       // words of four coordinates
     constexpr float TOP = BITS == 8 ? 255.f : 65535.f;
-    __shared__ uint32_t tile[64 * WPQ][4 * RW + 1];      // 64 float4 columns of 4 * RW rows
+    constexpr int LD = 4 * RW + 1;
+    uint32_t (*tile)[LD] = reinterpret_cast<uint32_t (*)[LD]>(lds);      // [64 * WPQ]: 64 float4 columns of 4 * RW rows
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = blockIdx.x * 4 * RW;
+    const int i0 = block * 4 * RW;
     const float step = grid[0], inv = grid[1];
     float err[RW], excess[RW];
 #pragma unroll
@@ -201,6 +202,26 @@ __global__ __launch_bounds__(256) void quantise_kernel(const float* __restrict__
             }
         }
     }
+}
+struct QuantiseArgs {
+    const float *act, *E, *lo, *grid;
+    const uint16_t* E16;
+    const int32_t *row_ids, *root_off;
+    uint32_t *Yq, *Eq;
+    int32_t *slack, *row_q;
+    float* base;
+    int n_rows, n_ent, n_queries, d, words, ldy, lde, row_blocks;      // row_blocks: workgroups that take branch rows, before those of the entities
+};
+constexpr int QUANTISE_ROWS = 2;
+template <int BITS, int RW>
+__global__ __launch_bounds__(256) void quantise_kernel(const QuantiseArgs g) {
+    __shared__ uint32_t lds[(BITS == 8 ? 64 : 128) * (4 * (RW > QUANTISE_ROWS ? RW : QUANTISE_ROWS) + 1)];
+    if ((int)blockIdx.x < g.row_blocks)                    // uniform
+        quantise<BITS, false, QUANTISE_ROWS>(blockIdx.x, g.act, nullptr, g.row_ids, g.n_rows, g.d, g.words, g.lo, g.grid, g.Yq, g.ldy, nullptr, g.base,
+                                             g.root_off, g.n_queries, g.row_q, lds);
+    else
+        quantise<BITS, true, RW>(blockIdx.x - g.row_blocks, g.E, g.E16, nullptr, g.n_ent, g.d, g.words, g.lo, g.grid, g.Eq, g.lde, g.slack, nullptr, nullptr,
+                                 0, nullptr, lds);
 }
 
 // ---------------------------------------------------------------- integer sums of a tile
@@ -806,6 +827,7 @@ __global__ __launch_bounds__(64) void answer_distance_kernel(const float* __rest
                                                              float* __restrict__ thr, int32_t* __restrict__ counters, int n_ans) {
     const int i = blockIdx.x * 64 + threadIdx.x, a = a0 + i;
     if (i >= cnt) return;
+    counters[a] = counters[n_ans + a] = 0;
     int lo = 0, hi = n_queries;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -827,7 +849,6 @@ __global__ __launch_bounds__(64) void answer_distance_kernel(const float* __rest
             const float4 x = E16 ? bf16x4_to_f32(*reinterpret_cast<const uint2*>(E16 + e * d + c)) : *reinterpret_cast<const float4*>(E + e * d + c);
             const float4 y = *reinterpret_cast<const float4*>(act + yrow + c);
             const float4 o = BOX ? *reinterpret_cast<const float4*>(off + yrow + c) : x;
-    counters[a] = counters[n_ans + a] = 0;
             add(y.x, x.x, o.x);
             add(y.y, x.y, o.y);
             add(y.z, x.z, o.z);
@@ -844,6 +865,7 @@ __global__ __launch_bounds__(64) void answer_distance_kernel(const float* __rest
 // no larger than lo's, of any D no larger than that of hi and its relative slack.  (d + 16) 2^-24 of the distance itself left 440 000 entities of 1024
 // queries x 63 000 x 400 with 8 answers each undecided: 147 us in count_open_kernel, 131 now.
 struct Bounds { float lo, hi; };
+__device__ __forceinline__ float power_of_two(float x) { return __uint_as_float(__float_as_uint(x) & 0x7F800000u); }     // of |x|, the largest within
 __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step, float b_lo, float b_hi, float rounding) {
     sl = min(sl, SLACK_CAP);
     const float lo = fmaf((float)((int32_t)sum - sl), step, b_lo), hi = fmaf((float)((int32_t)sum + sl), step, b_hi);
@@ -865,7 +887,6 @@ struct PickArgs {
     const uint32_t* sums;
     const int2* edge;
     int32_t *count, *overflowed;
-__device__ __forceinline__ float power_of_two(float x) { return __uint_as_float(__float_as_uint(x) & 0x7F800000u); }     // of |x|, the largest within
     float* out_dist;
     int32_t* out_ids;
     int ld, n_ent, d, k, room, ldb;
@@ -1242,31 +1263,26 @@ hipError_t launch_rank_grid(const RankFilter& f, const float* E, const uint16_t*
     return hipGetLastError();
 }
 
-hipError_t launch_rank_rows(const RankFilter& f, const float* act, const int32_t* row_ids, int n_rows, const int32_t* root_off,
-                            int n_queries, hipStream_t s) {
-    if (n_rows <= 0) return hipSuccess;
-    // (padding rows of the last tile are copies of the last row)
-    const dim3 grid((f.ldy + 7) / 8), block(256);
-    if (f.bits == 8)
-        hipLaunchKernelGGL((quantise_kernel<8, false, 2>), grid, block, 0, s, act, (const uint16_t*)nullptr, row_ids, n_rows, f.d, f.words,
-                           f.lo, f.grid, f.Yq, f.ldy, (int32_t*)nullptr, f.base, root_off, n_queries, f.row_q);
-    else
-        hipLaunchKernelGGL((quantise_kernel<16, false, 2>), grid, block, 0, s, act, (const uint16_t*)nullptr, row_ids, n_rows, f.d, f.words,
-                           f.lo, f.grid, f.Yq, f.ldy, (int32_t*)nullptr, f.base, root_off, n_queries, f.row_q);
-    return hipGetLastError();
-}
-
-hipError_t launch_rank_entities(const RankFilter& f, const float* E, const uint16_t* E16, int n_ent, hipStream_t s) {
-    if (n_ent <= 0) return hipSuccess;
+hipError_t launch_quantise(const RankFilter& f, const RankRows* rows, const float* E, const uint16_t* E16, int n_ent, hipStream_t s) {
+    QuantiseArgs g{};
+    g.lo = f.lo; g.grid = f.grid; g.d = f.d; g.words = f.words; g.ldy = f.ldy; g.lde = f.lde;
+    if (rows && rows->n > 0) {
+        g.act = rows->act; g.row_ids = rows->ids; g.n_rows = rows->n; g.root_off = rows->root_off; g.n_queries = rows->n_queries;
+        g.Yq = f.Yq; g.base = f.base; g.row_q = f.row_q;
+        g.row_blocks = (f.ldy + 4 * QUANTISE_ROWS - 1) / (4 * QUANTISE_ROWS);      // (padding rows of the last tile are copies of the last row)
+    }
+    g.E = E; g.E16 = E16; g.n_ent = n_ent; g.Eq = f.Eq; g.slack = f.slack;
     // 64 rows a workgroup, or 16 where these would be fewer than two a compute unit (12 952 rows of 400 coordinates: 20 and 9.6 us)
     const bool few = n_ent < 32768;
-    const dim3 grid((n_ent + 127) / 128 * (few ? 8 : 2)), block(256);
-#define NGDB_QUANTISE(BITS, RW)                                                                                                      \
-    hipLaunchKernelGGL((quantise_kernel<BITS, true, RW>), grid, block, 0, s, E, E16, (const int32_t*)nullptr, n_ent, f.d, f.words,  \
-                       f.lo, f.grid, f.Eq, f.lde, f.slack, (float*)nullptr, (const int32_t*)nullptr, 0, (int32_t*)nullptr)
-    if (f.bits == 8) { if (few) NGDB_QUANTISE(8, 4); else NGDB_QUANTISE(8, 16); }
-    else { if (few) NGDB_QUANTISE(16, 4); else NGDB_QUANTISE(16, 16); }
-#undef NGDB_QUANTISE
+    const dim3 grid(g.row_blocks + (n_ent + 127) / 128 * (few ? 8 : 2)), block(256);
+    if (grid.x == 0) return hipSuccess;
+    if (f.bits == 8) {
+        if (few) hipLaunchKernelGGL((quantise_kernel<8, 4>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((quantise_kernel<8, 16>), grid, block, 0, s, g);
+    } else {
+        if (few) hipLaunchKernelGGL((quantise_kernel<16, 4>), grid, block, 0, s, g);
+        else hipLaunchKernelGGL((quantise_kernel<16, 16>), grid, block, 0, s, g);
+    }
     return hipGetLastError();
 }
 
