@@ -272,17 +272,23 @@ int gslot_of(int t) { return t == T_PROJ ? 0 : (t == T_NEG ? 4 : 8); }
 struct FwdBytes;
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim);
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
-// bytes of the split weights: per type two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
-size_t weight_pieces_bytes(const ngdb_ctx_t* c) {
-    if (c->cfg.family != NGDB_FAMILY_VEC) return 0;
-    return 3 * 2 * (pieces_elems(c->cfg.h, c->cfg.d) + pieces_elems(c->cfg.d, c->cfg.h)) * sizeof(uint16_t);
+// Whether the weights are split once for a pass.  The two MLPs of the box family: from as many inputs of intersections on as some 800 queries have (a
+// step of 4096 boxes at d = 400, h = 800 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; a step of 512 takes the host as
+// long as the device, with and without, and its first pass two more allocations).
+constexpr int BOX_PIECES_FROM = 768;
+bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows >= BOX_PIECES_FROM; }
+// bytes of the split weights: per MLP two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
+size_t weight_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
+    if (!weights_split(c, hp)) return 0;
+    return (c->cfg.family == NGDB_FAMILY_BOX ? 2 : 3) * 2 * (pieces_elems(c->cfg.h, c->cfg.d) + pieces_elems(c->cfg.d, c->cfg.h)) * sizeof(uint16_t);
 }
 // Room for the hidden rows of one depth as pieces: blocks of 32 rows per segment, k-tiles in pairs.
 constexpr size_t H_PIECES_MAX_ROWS = 2048;      // launches over more rows do not write pieces
 int h_pieces_kt(const ngdb_ctx_t* c) { return 2 * ((c->cfg.h + 31) / 32); }
 size_t h_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
-    if (c->cfg.family != NGDB_FAMILY_VEC) return 0;
-    const size_t rows = std::min<size_t>((size_t)hp.n_proj + hp.n_int_rows + hp.n_neg, H_PIECES_MAX_ROWS);
+    if (!weights_split(c, hp)) return 0;
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;       // centres and offsets of the intersections' inputs
+    const size_t rows = std::min<size_t>(box ? 2 * (size_t)hp.n_int_rows : (size_t)hp.n_proj + hp.n_int_rows + hp.n_neg, H_PIECES_MAX_ROWS);
     return (rows / 32 + 3) * h_pieces_kt(c) * 1536 * sizeof(uint16_t);
 }
 // Hands the segments of one depth their places in h_pieces (as output of `first`, as A operand of
@@ -293,7 +299,7 @@ struct HiddenPieces {
 };
 HiddenPieces place_hidden_pieces(ngdb_ctx_t* c, GemmArgs* first, int n) {
     HiddenPieces hpc;
-    if (!c->have_pieces || !c->h_pieces.p) return hpc;
+    if (!c->have_pieces || !c->h_pieces.p || n > 3) return hpc;
     hpc.kt = h_pieces_kt(c);
     const size_t tile_row = (size_t)hpc.kt * 1536;
     size_t blocks = 0;
@@ -380,14 +386,13 @@ bool enqueue_levels(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Fill fi
     return true;
 }
 
-// Splits the weights of the three MLPs for a pass, for its backward half too if it has one (at d = 400, h = 800 scoring 1024 queries takes 415 us instead of 423 without it).
+// Splits the weights of the MLPs for a pass, for its backward half too if it has one (at d = 400, h = 800 scoring 1024 queries takes 415 us instead of 423 without it).
 // Without the buffer (a context
 // that never sized a workspace) the contractions split their B operands themselves.
-// (The box family has always split its own: its two MLPs do not come with pieces, and so its contractions do not reach the kernel for many
-// rows either.  Whether that pays has not been measured.)
 void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, PieceJobs* J) {
     c->have_pieces = false;
-    if (c->cfg.family != NGDB_FAMILY_VEC || c->w_pieces.cap < weight_pieces_bytes(c) || !c->w_pieces.p) return;
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    if (!weights_split(c, pl->hp) || c->w_pieces.cap < weight_pieces_bytes(c, pl->hp) || !c->w_pieces.p) return;
     const int d = c->cfg.d, h = c->cfg.h;
     if ((d & 3) || (h & 3)) return;   // the split reads rows as float4
     if (d < 128 && h < 128) return;   // no contraction of these widths takes the split route
@@ -395,11 +400,12 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
     LevelArgs la;
     for (const std::vector<Segment>& segs : pl->levels) {
         if (level_problems(c, pl, segs, &la)) continue;
-        for (const Segment& sg : segs) narrow = narrow && gemm_takes_rows(sg.rows, std::max(d, h));
+        for (const Segment& sg : segs) narrow = narrow && ((box && sg.type == T_PROJ) || gemm_takes_rows(sg.rows, std::max(d, h)));
     }
     if (narrow) return;
     uint16_t* at = ptr<uint16_t>(c->w_pieces);
     for (int t = 0; t < 3; ++t) {
+        if (box && t == T_PROJ) continue;
         const MlpRefs W = mlp_of(c->prm, t);
         // Wa [h][d]: rows as n = forward operand of H = X Wa^T; columns as n = backward operand of dZ = dH Wa
         PieceJob& ja = J->job[J->count++];
@@ -465,7 +471,7 @@ int size_workspace(ngdb_ctx_t* c, const ngdb_plan_t* pl, int K, bool want_table_
     const size_t rows[3] = {(size_t)hp.n_proj, (size_t)hp.n_int_rows, (size_t)hp.n_neg};
     int rc;
 #define ENS(buf, bytes) if ((rc = ensure(c, buf, std::max<size_t>((bytes), 256))) != NGDB_OK) return rc
-    ENS(c->w_pieces, weight_pieces_bytes(c));
+    ENS(c->w_pieces, weight_pieces_bytes(c, hp));
     ENS(c->h_pieces, h_pieces_bytes(c, hp));
     ENS(c->act, (size_t)hp.n_slots * d * f);
     ENS(c->dact, ((size_t)hp.n_slots + hp.n_anchor) * d * f);
@@ -710,12 +716,19 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
                 GemmArgs& b = g2[n];
                 b.A = Hh; b.lda = h; b.B = W.Wb; b.ldb = h; b.M = sg.rows; b.N = d; b.K = h; b.bias = W.bb; b.ldc = d;
                 b.C = ptr<float>(part ? c->Gate : c->Att) + (size_t)sg.mlp_base * d;
+                if (c->have_pieces) {
+                    a.b_pieces = c->wp[t][0]; a.b_kt = (d + 15) / 16;
+                    b.b_pieces = c->wp[t][1]; b.b_kt = (h + 15) / 16;
+                }
                 ++n;
             }
         }
         if (n == 0) continue;
         int rc_g;
-        if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_FWD, g1, n, s)) != NGDB_OK) return rc_g;
+        const HiddenPieces hpc = place_hidden_pieces(c, g1, n);
+        bool emitted = false;
+        if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_FWD, g1, n, s, &emitted)) != NGDB_OK) return rc_g;
+        if (emitted) take_hidden_pieces(hpc, g2, n);
         if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_FWD, g2, n, s)) != NGDB_OK) return rc_g;
         for (const Segment& sg : segs) {
             if (sg.type != T_INTER) continue;
@@ -780,7 +793,7 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
     const FwdBytes fb = forward_bytes(c, pl, true);
     int rc;
 #define ENS(buf, bytes) if ((rc = ensure(c, buf, std::max<size_t>((bytes), 256))) != NGDB_OK) return rc
-    ENS(c->w_pieces, weight_pieces_bytes(c));
+    ENS(c->w_pieces, weight_pieces_bytes(c, hp));
     ENS(c->h_pieces, h_pieces_bytes(c, hp));
     ENS(c->act, fb.act);
     ENS(c->Att, fb.att);
@@ -1093,12 +1106,19 @@ int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, Wg
                 y.A = dHh; y.lda = h; y.B = W.Wa; y.ldb = d; y.b_kcontig = false;
                 y.C = ptr<float>(part ? c->doff : c->dact); y.ldc = d; y.M = sg.rows; y.N = d; y.K = h;
                 y.addend = ptr<float>(part ? c->DxO : c->Dx) + mb * d; y.ldadd = d; y.dst_row = pl->d_in_gslot + sg.ref_off;
+                if (c->have_pieces) {
+                    x.b_pieces = c->wp[t][2]; x.b_kt = (d + 15) / 16;
+                    y.b_pieces = c->wp[t][3]; y.b_kt = (h + 15) / 16;
+                }
                 ++n;
             }
         }
         if (n == 0) continue;
         int rc_g;
-        if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_BWD, b2, n, s)) != NGDB_OK) return rc_g;
+        const HiddenPieces hpc = place_hidden_pieces(c, b2, n);
+        bool emitted = false;
+        if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_BWD, b2, n, s, &emitted)) != NGDB_OK) return rc_g;
+        if (emitted) take_hidden_pieces(hpc, b1, n);
         if ((rc_g = gemm_timed(c, NGDB_TK_GEMM_BWD, b1, n, s)) != NGDB_OK) return rc_g;
     }
     wj->nt = 2;

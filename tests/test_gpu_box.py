@@ -31,6 +31,14 @@ def test_box_workload_widths_ragged_sizes():
     pb.check_train_steps(case, steps=2)
 
 
+# on either side of the rows (2.4 a query) from which on the weights are split once per pass: the kernel for few rows, tiles of 32 (hidden rows as
+# pieces between the layers), the kernel for many rows by one block of rows and by two; widths that fill no tile
+@pytest.mark.parametrize("B,d,h", [(5, 136, 264), (300, 136, 264), (340, 136, 264), (480, 132, 260), (400, 60, 140)])
+def test_box_layers_by_rows(B, d, h):
+    _say("box family, layers by rows: B=%d d=%d h=%d" % (B, d, h))
+    pb.check_forward_backward(pb.BoxCase(2000, 20, d, h, B, 3, 12.0, alpha=0.1, mix={"2i": 0.4, "3i": 0.4, "pi": 0.2}, seed=9))
+
+
 def test_box_odd_width_and_streams():
     _say("box family, d=100 h=72, streams 1 vs 4")
     case = pb.BoxCase(2000, 20, 100, 72, 90, 7, 6.0, alpha=0.1, seed=4)
