@@ -1502,10 +1502,12 @@ size_t device_free(const ngdb_ctx_t* c) {
 // Answers: the filter's counting takes as long per pair as 64 coordinates save, and each chunk has launches of its own:
 // 502 us in fp32 and 602 with the filter at 200 000 x 585 x 64, 250 and 230 at 15 000 x 585 x 256, 439 and 586 at 200 000 x 114 x
 // 256 (four chunks), 1357 and 1180 at 200 000 x 585 x 256.
-// A table of one piece needs no fp32 rows, lists or chunks (pick_kernel), and the filter pays from less on, in the same units and order:
+// A table of one piece, or of up to four whose sums fit 256 MiB, needs no fp32 rows, lists or chunks (pick_kernel), and the filter pays from less on, in the same units and order:
 // 8000 x 228 x 400 (0.67) 130 and 137, 30 000 x 114 x 400 (0.96) 160 and 147, 15 000 x 585 x 128 (1.1) 157 and 131, 5000 x 585 x 400 (1.2) 168 and
 // 157, 60 000 x 114 x 400 (1.9) 228 and 177, 65 000 x 1171 x 400 (32) 1402 and 447; with chunks from a sample of 2048 rows on the filter took
-// 184, 261, 151, 192, 291 and 540.  60 000 x 28 x 400 (below 0) 127 and 143.
+// 184, 261, 151, 192, 291 and 540.  60 000 x 28 x 400 (below 0) 127 and 143.  Several pieces, from a sample on and as a whole: 70 000 x 585 x 400 396 and
+// 309, 100 000 x 114 x 400 301 and 217, 200 000 x 57 x 400 352 and 266, 262 144 x 228 x 400 602 and 477 (not with text features, whose rows are rounded as they
+// are fused in the chunks, and here would be by a launch that reads them again).
 constexpr double NEAR_FROM = 3.3e9, WHOLE_FROM = 0.8e9;
 double near_work(const ngdb_ctx_t* c, int n_rows) {
     const int tile_rows = n_rows <= 32 ? 32 : (n_rows <= 64 ? 64 : (n_rows + 127) / 128 * 128);
@@ -1529,7 +1531,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
     const float* act = ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
-    const bool whole = N <= RANK_CHUNK;
+    const bool whole = N <= RANK_CHUNK || (c->cfg.d_sem == 0 && N <= NEAR_CHUNK && (int64_t)R * N <= NEAR_DIST);
     bool filtered = rank_filtered(c, R, near_work(c, R), whole ? WHOLE_FROM : NEAR_FROM);
     const bool needed = c->rank_filter_from >= 0 || near_work(c, R) >= NEAR_FROM;
     RankFilter f{};
@@ -1547,11 +1549,13 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     for (bool emptied = false, shorter = false;; emptied = true) {
         chunk = std::min(N, most);
         at_once = RANK_CHUNK;                // (short of memory: a piece)
-        while (!emptied && at_once < chunk && 2ll * at_once * R <= NEAR_DIST) at_once *= 2;
+        while (!emptied && at_once < chunk && (2ll * at_once * R <= NEAR_DIST || (whole && filtered))) at_once *= 2;
         ld = (std::min(chunk, at_once) + 3) & ~3;
         rc = rank_buffers(c, R, B, ld, chunk, filtered ? 8 : 0, chunk, &f);
-        if (rc == NGDB_ERR_OOM && emptied && filtered && !needed) filtered = false;      // (fp32 takes little longer, and the distances only)
-        else if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
+        if (rc == NGDB_ERR_OOM && emptied && filtered && !needed) {      // (fp32 takes little longer, and the distances only)
+            filtered = false;
+            most = RANK_CHUNK;
+        } else if (rc != NGDB_ERR_OOM || (emptied && most == RANK_CHUNK)) {
             if (rc == NGDB_OK && shorter) c->near_free = device_free(c);
             break;
         }
@@ -1568,7 +1572,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
     Overflowed only{f.row_q, f.count, f.room, f.overflowed, B};
     const RankRows rows{act, roots, R, pl->d_root_off, B};
     Timed tm(c, NGDB_TK_SCORE, s);
-    if (filtered && whole) {                 // the sums of all entities, the nearest of these, and what had no room in fp32
+    if (filtered && whole && ld >= N) {      // (a table of several pieces: unless short of memory) the sums of all entities, the nearest of these, and what had no room in fp32
         ChunkRows er;
         if ((rc = rank_chunk_rows(c, 0, N, true, nullptr, s, &er)) != NGDB_OK) return rc;
         if ((rc = rank_filter_begin(c, f, er.sample, s)) != NGDB_OK) return rc;
@@ -1580,7 +1584,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         only.any = f.overflowed;
         HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, N, d, dist, ld, s, er.rows16, &only));
         HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, 0, N, topk, false, d_dist, d_ids, s, &only));
-        c->rank_chunks = 1;
+        c->rank_chunks = (N + RANK_CHUNK - 1) / RANK_CHUNK;
         return NGDB_OK;
     }
     // filtered: the sample's k-th distance lets k / sample of the first chunk pass, and chunks grow with what has

@@ -459,7 +459,7 @@ hipError_t launch_near_tile(const RankFilter& f, int n_rows, int n_ent, const fl
 hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, const int32_t* row_ids, const int32_t* root_off,
                              int n_queries, const float* E, const uint16_t* E16, int ent_base, int n_ent, int k, float* out_dist,
                              int32_t* out_ids, hipStream_t s);
-// the k nearest of a table of one piece from its sums (ld >= n_ent rounded up to 4); queries whose list has no room get no result and a mark
+// the k nearest of a table (RANK_PIECES pieces at most) from its sums (ld >= n_ent rounded up to 4); queries whose list has no room get no result and a mark
 hipError_t launch_pick(const RankFilter& f, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
                        int n_queries, const float* E, const uint16_t* E16, int n_ent, int k, float* out_dist, int32_t* out_ids, hipStream_t s);
 // sums[r * ld + e] of the chunk; chunk_count[a] = entities certainly closer than answer a, the undecided

@@ -25,7 +25,7 @@
 // one workgroup per query computes and merges.  Chunks grow with what has been ranked.  1024 queries
 // (1171 branch rows) x 5 M entities x 400: distance tiles 182.6 ms and merges 32.6 became integer sums 17.5 (34 T
 // operations of 4 coordinates a second; the instruction alone reaches 36) and merges 1.0.
-// Top-k of a table of one piece (65 536 rows): the 8-bit sums of all entities go to memory, and one workgroup per query takes its nearest
+// Top-k of a table of one piece (65 536 rows) or few: the 8-bit sums of all entities go to memory, and one workgroup per query takes its nearest
 // from them (pick_kernel).  512 queries x 15 000 x 400: fp32 rows 43 us, tiles of the rest 56 and merges 29 became sums 42 and 27.
 // Filtered ranks: the 16-bit sums decide all but about 0.1 % of the (entity, answer) comparisons: 1024
 // queries x 63 000 entities with 8 answers each, tiles 2.78 ms (0.32 of them for the answers' own
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void near_tile_kernel(const NearArgs g) {
     else near_tile<2>(g, r0, e0, L);
 }
 
-// Filtered ranks, and the top-k of tables of one piece: the sums themselves, sums[r * ld + e] = SAD
+// Filtered ranks, and the top-k of tables taken as a whole: the sums themselves, sums[r * ld + e] = SAD
 // (15 000 entities x 585 rows x 400 coordinates by tiles of 64 rows 42 us, of 128 48; 60 000 x 228 x 400 the other way round, 272 and 241 us a ranking.)
 // Top-k (8 bits): also edge[r * tiles + tile] = the least of the tile's sums less the entities' errors, and with them
 __device__ __forceinline__ int32_t least_of_16(int32_t v) {        // over lanes 16 i .. 16 i + 15, rotated by 8, 4, 2, 1
@@ -873,7 +873,7 @@ __device__ __forceinline__ Bounds bounds_of(uint32_t sum, int32_t sl, float step
     return {none ? -INFINITY : fmaf(-rounding, power_of_two(lo), lo), none ? INFINITY : fmaf(rounding, power_of_two(fmaf(rounding, fabsf(hi), hi)), hi)};
 }
 
-// Top-k of a table of one piece: the sums of all its entities are in memory, and one workgroup per query takes its k nearest from them.
+// Top-k of a table as a whole: the sums of all its entities are in memory, and one workgroup per query takes its k nearest from them.
 // The tiles have left the least upper and lower bound of every row: the k-th smallest upper one of 64 groups of tiles is a bound that k
 // entities keep, hardly more than k of them.  Tiles that reach below it are looked through, and whatever may lie within it, some two or
 // three times k, is computed; what lies within the same bound on these distances is placed by counting.  Lists without room go
@@ -974,9 +974,9 @@ __global__ __launch_bounds__(PICK_T, 4) void pick_kernel(const PickArgs g) {
             out_d[t] = INFINITY;
             out_i[t] = -1;
         }
-        if (t == 0) {
-            g.count[q] = g.room + 1;
-            *g.overflowed = 1;
+        if (t * RANK_PIECE < g.n_ent) {
+            g.count[(size_t)t * gridDim.x + q] = g.room + 1;
+            g.overflowed[t] = 1;
         }
         return;
     }
@@ -1312,7 +1312,7 @@ hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, c
 hipError_t launch_pick(const RankFilter& f, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
                        int n_queries, const float* E, const uint16_t* E16, int n_ent, int k, float* out_dist, int32_t* out_ids, hipStream_t s) {
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
-    if (k < 1 || k > NGDB_MAX_TOPK || f.parts != 1 || (ld & 3) || n_ent > RANK_PIECE) return hipErrorInvalidValue;
+    if (k < 1 || k > NGDB_MAX_TOPK || f.parts != 1 || (ld & 3) || n_ent > RANK_PIECES * RANK_PIECE) return hipErrorInvalidValue;
     const PickArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, sums, reinterpret_cast<const int2*>(f.found_pair), f.count, f.overflowed, out_dist, out_ids,
                      ld, n_ent, f.d, k, f.room, f.ldy, rounding_of(f.d)};
     if (E16) hipLaunchKernelGGL(pick_kernel<true>, dim3(n_queries), dim3(PICK_T), 0, s, g);

@@ -220,11 +220,12 @@ def _no_numbers(rows):
     return edit
 
 
-# tables of one piece: 33 tiles of entities (fewer than groups), all of 512, ragged ends; row tiles of 64 and of 128 with every remainder;
+# tables of one piece, and of few where the sums fit: 33 tiles of entities (fewer than groups), all of 512, ragged ends; row tiles of 64 and of 128 with every remainder;
 # rows that are no numbers, of the grid's sample (every fourth) and not; more copies of the nearest entity than a list has room for, and fewer
 @pytest.mark.parametrize("N,d,B,copies,edit", [(4097, 8, 5, 0, None), (65536, 4, 40, 0, None), (65535, 8, 300, 0, None), (8190, 400, 130, 0, None),
                                                (15000, 36, 512, 0, None), (9001, 20, 77, 0, _no_numbers((7, 4001))),
-                                               (9001, 20, 77, 0, _no_numbers((8, 4000))), (9000, 16, 24, 1900, None), (9000, 16, 24, 2100, None)])
+                                               (9001, 20, 77, 0, _no_numbers((8, 4000))), (9000, 16, 24, 1900, None), (9000, 16, 24, 2100, None),
+                                               (131075, 8, 40, 0, None), (262144, 4, 9, 1900, None), (200001, 4, 9, 2100, None)])
 def test_tables_of_one_piece(N, d, B, copies, edit):
     from paper_2602_21597_amd import binding
     par.say("rank filter: N=%d d=%d B=%d, %d copies %s" % (N, d, B, copies, edit.__name__ if edit else ""))
@@ -239,7 +240,7 @@ def test_tables_of_one_piece(N, d, B, copies, edit):
         E[100:100 + copies] = E[eng.rank_all(plan, 1)[0][0, 0].long()]
         got.append([x.cpu().numpy() for k in (1, 10, 16) for x in eng.rank_all(plan, k)])
         if limit == 0 and edit is None:
-            assert binding.lib().ngdb_debug_rank_overflows(eng.ctx) == (1 if copies > 2048 else 0)
+            assert binding.lib().ngdb_debug_rank_overflows(eng.ctx) == (-(-N // 65536) if copies > 2048 else 0)
         plan.free()
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
