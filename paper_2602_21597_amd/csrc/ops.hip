@@ -2,57 +2,15 @@
 // precomputed references, Sec. 4.2 "Efficient Tensor Indexing", are fused into the
 // contraction kernel's operand loads): the attention
 // pooling of the intersection classes C_k (Sec. 4.3), dense Adam (Alg. 1, OptimizerStep) and the final loss reduction.
-#include "common.h"
+#include "pool.h"
 
 namespace ngdb {
 namespace {
 
-// y_i = sum_j softmax_j(att_j)_c * x_j,c : one thread per (member, coordinate); the cardinality
-// classes of one level are the jobs of one launch (blockIdx.y).  The loops over inputs run to
-// the compile-time maximum under a predicate, so the per-input values stay in registers.
+// the cardinality classes of one level are the jobs of one launch (blockIdx.y)
 template <bool BWD>
-__global__ __launch_bounds__(256) void inter_kernel(const InterJobs jobs) {
-    const InterJob jb = jobs.job[blockIdx.y];
-    const int d = jobs.d, n = jb.n, k = jb.k;
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)n * d) return;
-    const int i = (int)(t / d), c = (int)(t % d);
-    float a[NGDB_MAX_CARD], x[NGDB_MAX_CARD];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < NGDB_MAX_CARD; ++j) {
-        const size_t row = (size_t)min(j, k - 1) * n + i;
-        a[j] = jb.Att[row * d + c];
-        x[j] = jb.X[row * d + c];
-        if (j < k) mx = fmaxf(mx, a[j]);
-    }
-    float den = 0.f;
-#pragma unroll
-    for (int j = 0; j < NGDB_MAX_CARD; ++j) {
-        a[j] = j < k ? expf(a[j] - mx) : 0.f;
-        den += a[j];
-    }
-    const float inv = 1.f / den;
-    if (!BWD) {
-        float y = 0.f;
-#pragma unroll
-        for (int j = 0; j < NGDB_MAX_CARD; ++j) y += a[j] * inv * x[j];
-        jb.out[(size_t)(jb.out_row ? jb.out_row[i] : i) * d + c] = y;
-    } else {
-        const float dy = jb.dY[(size_t)i * d + c];
-        float tall = 0.f;
-#pragma unroll
-        for (int j = 0; j < NGDB_MAX_CARD; ++j) tall += a[j] * inv * x[j] * dy;
-#pragma unroll
-        for (int j = 0; j < NGDB_MAX_CARD; ++j) {
-            if (j < k) {
-                const size_t row = (size_t)j * n + i;
-                const float w = a[j] * inv;
-                jb.dAtt[row * d + c] = w * (dy * x[j] - tall);
-                jb.Dx[row * d + c] = w * dy;
-            }
-        }
-    }
+__global__ __launch_bounds__(pool::THREADS) void inter_kernel(const InterJobs jobs) {
+    pool::member<BWD, false>(jobs.job[blockIdx.y], jobs.d, (size_t)blockIdx.x * pool::THREADS + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* p, size_t n) {
@@ -178,11 +136,12 @@ hipError_t launch_inter(const InterJobs& jobs, bool backward, hipStream_t s) {
     size_t most = 0;
     for (int i = 0; i < jobs.count; ++i) {
         if (jobs.job[i].n <= 0 || jobs.job[i].k < 1 || jobs.job[i].k > NGDB_MAX_CARD) return hipErrorInvalidValue;
-        most = std::max(most, (size_t)jobs.job[i].n * jobs.d);
+        most = std::max(most, (size_t)jobs.job[i].n * (jobs.d >> 2));
     }
-    const dim3 grid((unsigned)((most + 255) / 256), jobs.count);
-    if (backward) hipLaunchKernelGGL((inter_kernel<true>), grid, dim3(256), 0, s, jobs);
-    else hipLaunchKernelGGL((inter_kernel<false>), grid, dim3(256), 0, s, jobs);
+    if (jobs.d & 3) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((most + pool::THREADS - 1) / pool::THREADS), jobs.count), block(pool::THREADS);
+    if (backward) hipLaunchKernelGGL((inter_kernel<true>), grid, block, 0, s, jobs);
+    else hipLaunchKernelGGL((inter_kernel<false>), grid, block, 0, s, jobs);
     return hipGetLastError();
 }
 
