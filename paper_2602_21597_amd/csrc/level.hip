@@ -129,7 +129,7 @@ __device__ __forceinline__ void row_put(float* p, float4 v) {
     if (!CHAIN) { *reinterpret_cast<float4*>(p) = v; return; }
     row_put1<true>(p, v.x); row_put1<true>(p + 1, v.y); row_put1<true>(p + 2, v.z); row_put1<true>(p + 3, v.w);
 }
-// sync[0]: numbers handed out, sync[1]: tiles through, sync[2 + l]: tiles of depth l through
+// sync[0]: numbers handed out, sync[1]: tiles through, sync[2 + l]: tiles of depth l through (but the last)
 constexpr int CHAIN_SPINS = 1 << 22;          // (seconds: a wait that no working card comes near ends all the same)
 __device__ __forceinline__ void wait_for_depth(const int32_t* through, int tiles) {
     if (threadIdx.x == 0)
@@ -429,8 +429,10 @@ __global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
     wait_vm<0>();                   // this wavefront's rows are where the next depth finds them,
     __syncthreads();                // ... and everybody's
     if (threadIdx.x != 0) return;
-    __hip_atomic_fetch_add(r.sync + 2 + l, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the last one through (nobody waits any more) leaves the counts as they were found
+    // (nobody waits for the last depth; the counts of the others were seen in full by whoever gets there, so none of them can
+    // still be on its way when they are cleared)
+    if (l + 1 < r.n) __hip_atomic_fetch_add(r.sync + 2 + l, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the last one through leaves the counts as they were found
     if (__hip_atomic_fetch_add(r.sync + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r.first[r.n] - 1)
         for (int i = 0; i < LEVEL_SYNC; ++i) __hip_atomic_store(r.sync + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
