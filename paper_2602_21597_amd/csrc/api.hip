@@ -94,6 +94,7 @@ struct ngdb_ctx_s {
     // forward pass, so they are never older than the weights the pass reads.
     DevBuf w_pieces;
     bool chained = false;          // the pass under way has a launch of several depths
+    bool rows_chained = false;     // ... its first, which is all of its forward pass (rows_chain)
     SmallIndex index_waits{};      // a small gradient index that a launch of the forward pass may take along (n: 0 without one)
     DevBuf sync;        // of the launches of several depths (LevelSync), in device memory
     int32_t* gave_up = nullptr;    // and in pinned host memory: one of them has given up waiting, for good
@@ -254,6 +255,9 @@ int ensure(ngdb_ctx_t* c, DevBuf& b, size_t bytes, Use use = Use::Any) {
 template <class T>
 T* ptr(const DevBuf& b) { return static_cast<T*>(b.p); }
 
+// Words of c->sync: LevelSync's counts and the mark of a launch that gave up, then those of rows_chain_kernel.
+constexpr int CHAIN_AT = 64, SYNC_WORDS = CHAIN_AT + CHAIN_SYNC;
+static_assert(LEVEL_SYNC + 1 <= CHAIN_AT, "lines of their own");
 LevelSync level_sync(const ngdb_ctx_t* c) {
     LevelSync y;
     if (c->chain_polls < 0) return y;            // (a launch per depth)
@@ -443,15 +447,86 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
     c->have_pieces = true;
 }
 
+// All layers of a forward pass in one launch (rows_chain_kernel), where each would be one of a few rows: the same sums in the same order.
+// Only passes that keep no rows for others (outputs reclaimed), of the vector family without text features (whose references are made on the
+// device).  False: not such a pass.
+bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
+    const HostPlan& hp = pl->hp;
+    const int d = c->cfg.d, h = c->cfg.h;
+    const LevelSync sync = level_sync(c);
+    if (c->cfg.family != NGDB_FAMILY_VEC || c->cfg.d_sem > 0 || !sync.counts || hp.n_levels < 1 || hp.n_levels > LEVEL_CHAIN || std::max(d, h) > CHAIN_WIDTH ||
+        level_fits(d, h, true))
+        return false;
+    r->d = d; r->h = h; r->depths = hp.n_levels; r->sync = sync; r->chain = sync.counts + CHAIN_AT;
+    auto word = [&](int32_t v) { r->words[r->n_words++] = v; };
+    for (int l = 1; l <= hp.n_levels; ++l) {
+        int& count = r->count[l - 1];
+        count = 0;
+        for (const Segment& sg : pl->levels[l]) {
+            if (sg.rows <= 0) continue;
+            if (!gemm_takes_rows(sg.rows, std::max(d, h))) return false;
+            const int classes = sg.type == T_INTER ? sg.g_hi - sg.g_lo : 1;
+            for (int i = 0; i < classes; ++i) {
+                const int g = sg.g_lo + i;
+                const bool inter = sg.type == T_INTER;
+                RowsProblem p{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, r->n_words, inter ? hp.g_mlp_base[g] - sg.mlp_base : 0};
+                if (count == CHAIN_PROBLEMS || p.k > CHAIN_CARD || (inter && p.k < 2) || r->n_words + p.n * (p.k + 2) > CHAIN_WORDS) return false;
+                const int ref0 = sg.ref_off + p.row0, out0 = inter ? hp.g_out_base[g] : sg.out_base;
+                for (int x = 0; x < p.n * p.k; ++x) {
+                    const int32_t ref = hp.in_ref[ref0 + x];
+                    word(ref >= 0 ? hp.f_row[ref] : ref);
+                }
+                for (int x = 0; sg.type == T_PROJ && x < p.n; ++x) word(hp.rel[sg.rel_off + x]);
+                for (int x = 0; x < p.n; ++x) word(hp.f_row[out0 + x]);
+                r->p[l - 1][count++] = p;
+            }
+        }
+        if (count == 0) return false;
+    }
+    for (int t = 0; t < 3; ++t) {
+        const MlpRefs W = mlp_of(c->prm, t);
+        r->Wa[t] = W.Wa; r->ba[t] = W.ba; r->Wb[t] = W.Wb; r->bb[t] = W.bb;
+        r->H[t] = ptr<float>(c->H[t]);
+    }
+    r->E = c->prm.E.p; r->R = c->prm.R.p; r->act = ptr<float>(c->act); r->Z = ptr<float>(c->Z[T_INTER]);
+    return true;
+}
+
 // The first launch of a pass: the plan to the device and the weights as pieces.
 // A plan of ordinary size reaches the device with the first call that uses it: workgroups of this launch
 // read the staging buffer (120 KB: 5 us as a launch of its own), which needs neither a wait on the host (10 us) nor an
 // event between streams (9 us of host time).  Large ones are copied when they are planned.
 constexpr size_t PLAN_INLINE_BYTES = 256 << 10;
-int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t s) {
+int plan_uploaded(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
+    if (pl->uploaded) return NGDB_OK;
+    // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIPCHK(c, hipStreamIsCapturing(s, &st));
+    if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
+    return NGDB_OK;
+}
+int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t s, bool chain = false) {
     const int waited = check_waits(c);
     if (waited != NGDB_OK) return waited;
-    c->chained = false;
+    c->chained = c->rows_chained = false;
+    RowsChain r;
+    if (chain && rows_chain(c, pl, &r)) {
+        if (!pl->uploaded) {
+            r.copy_dst = reinterpret_cast<float4*>(pl->blob.dev);
+            r.copy_src = reinterpret_cast<const float4*>(pl->blob.pinned);
+            r.copy_n = (int)(pl->blob_bytes / 16);
+        }
+        Timed tm(c, NGDB_TK_GEMM_FWD, s);
+        const hipError_t e = launch_rows_chain(r, s);
+        if (e == hipSuccess) {
+            double flop = 0.0;
+            for (const std::vector<Segment>& segs : pl->levels) flop += level_flop(c, segs);
+            tm.work(GEMM_FP32, flop);
+            c->chained = c->rows_chained = true;
+            return plan_uploaded(c, pl, s);
+        }
+        if (e != hipErrorInvalidValue) HIPCHK(c, e);
+    }
     PieceJobs J{};
     if (!pl->uploaded) {
         J.copy_dst = reinterpret_cast<float4*>(pl->blob.dev);
@@ -463,13 +538,7 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
         HIPCHK(c, launch_weight_pieces(J, s));
     }
-    if (!pl->uploaded) {
-        // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        HIPCHK(c, hipStreamIsCapturing(s, &st));
-        if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
-    }
-    return NGDB_OK;
+    return plan_uploaded(c, pl, s);
 }
 
 // The end of a pass, also of one that is refused or fails half way: what it enqueued still reads the plan, whose buffer
@@ -853,6 +922,7 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
 // depth are independent: they share one grouped launch per MLP layer.
 int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hipStream_t s, const FwdSpace& w) {
     if (c->cfg.family == NGDB_FAMILY_BOX) return enqueue_forward_box(c, pl, s);   // (always on the context's buffers)
+    if (c->rows_chained) return NGDB_OK;       // (the launch that began the pass)
     const int d = c->cfg.d, h = c->cfg.h;
     auto forward_level = [&](LevelArgs& la) {
         la.refs = er.refs; la.rel = pl->d_rel; la.E = er.rows; la.R = c->prm.R.p;
@@ -1770,7 +1840,7 @@ int ngdb_create(const ngdb_config* cfg, ngdb_ctx_t** out) {
     ok = ok && hipStreamCreateWithFlags(&c->upload, hipStreamNonBlocking) == hipSuccess;
     unsigned char* sp = nullptr;
     ok = ok && noalloc_scratch(&sp) == hipSuccess;     // address of the static scratch on this GPU
-    const int32_t zeros[LEVEL_SYNC + 1] = {};
+    static const int32_t zeros[SYNC_WORDS] = {};
     ok = ok && device_alloc(c, c->sync, sizeof(zeros)) == hipSuccess && hipMemcpy(c->sync.p, zeros, sizeof(zeros), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&c->gave_up, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
     if (ok) {
@@ -2109,7 +2179,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     int rc = reclaim ? size_forward_only(c, pl, n_tail) : size_workspace(c, pl, d_cand ? C : 0, false);
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, s};
-    if ((rc = begin_pass(c, pl, false, s)) != NGDB_OK) return rc;
+    if ((rc = begin_pass(c, pl, false, s, reclaim)) != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, d_cand, n_tail, s, &er, reclaim);
@@ -2221,7 +2291,7 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     int rc = reclaim ? size_forward_only(c, pl, 0) : size_workspace(c, pl, 0, false);
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, s};
-    if ((rc = begin_pass(c, pl, false, s)) != NGDB_OK) return rc;
+    if ((rc = begin_pass(c, pl, false, s, reclaim)) != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, nullptr, 0, s, &er, reclaim);
@@ -2379,7 +2449,7 @@ int ngdb_debug_device_limit(ngdb_ctx_t* c, int64_t bytes) {
 int ngdb_debug_chain_polls(ngdb_ctx_t* c, int32_t polls) {
     if (!c) return NGDB_ERR_ARG;
     HIPCHK(c, hipDeviceSynchronize());
-    const int32_t zeros[LEVEL_SYNC + 1] = {};
+    static const int32_t zeros[SYNC_WORDS] = {};
     HIPCHK(c, hipMemcpy(c->sync.p, zeros, sizeof(zeros), hipMemcpyHostToDevice));
     *c->gave_up = 0;
     c->chain_polls = polls;

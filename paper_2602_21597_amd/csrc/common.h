@@ -367,6 +367,28 @@ struct LevelSync {
     int32_t* host_gave_up = nullptr;        // the same in pinned host memory, for the next call
     int32_t polls = 0;              // looks at a count before a wait gives up (0: it does at once)
 };
+// A forward pass of a handful of queries, all layers of all depths in one launch (level.hip: rows_chain_kernel).  A problem is a projection or
+// negation group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its depth's buffers; words[at ..] holds
+// its n k references, the relations of a projection and its n output rows, so that nothing waits for the plan to reach the device.
+// Limits: words of all problems, inputs of an intersection, values of a row.
+constexpr int CHAIN_SYNC = (2 * LEVEL_CHAIN * 8 + 1) * 32;      // words that such launches share, zero, and zero again behind each of them
+constexpr int CHAIN_PROBLEMS = 5, CHAIN_WORDS = 160, CHAIN_CARD = 4, CHAIN_WIDTH = 1024;
+struct RowsProblem { int type, k, n, at, row0; };
+struct RowsChain {
+    int d, h, depths = 0, n_words = 0;
+    int count[LEVEL_CHAIN] = {}, first[2 * LEVEL_CHAIN + 1] = {};    // problems of a depth; tiles before each layer (filled in by the launch)
+    RowsProblem p[LEVEL_CHAIN][CHAIN_PROBLEMS];
+    const float *Wa[3], *ba[3], *Wb[3], *bb[3];     // by type: projection, intersection, negation
+    const float *E, *R;
+    float *act, *Z, *H[3];                          // outputs; inputs of intersections; hidden rows by type
+    LevelSync sync;                                 // (its counts are not used)
+    int32_t* chain;                                 // CHAIN_SYNC words
+    const float4* copy_src = nullptr;               // the plan, copied for the launches that follow by one more workgroup
+    float4* copy_dst = nullptr;
+    int copy_n = 0;
+    int32_t words[CHAIN_WORDS];
+};
+hipError_t launch_rows_chain(RowsChain& r, hipStream_t s);
 bool levels_chain(const LevelArgs* a, int n);
 hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, hipStream_t s);
 

@@ -469,6 +469,183 @@ __global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
     if (!BWD && (before >= GAVE_UP || !there)) no_rows(r);
 }
 
+// The forward pass of a handful of queries (every layer has a few rows only: gemm.hip's rows_kernel, whose sums these are): all layers of
+// all depths in one launch.  As a launch a layer such a pass is bound by the host, 4 us each, and the first of them, which copies the plan,
+// is spared too: the references travel as arguments and one more workgroup copies the plan for whoever follows.  A tile requests its weights,
+// all of them, before it waits for the layer before; what an intersection pools are its tile's own columns.  Rows and values of one layer
+// reach the next as in levels_kernel, and a wait ends like there; a tile that gave up leaves NaN, and so does then every tile of the layers behind it.
+// Tiles are dealt by workgroup number: a die starts its workgroups in order, so that a tile waits only for tiles that started
+// before it on its own die or need nothing of that die.  What is counted are the tiles through of a layer, in CHAIN_LINES words on lines
+// of their own: tickets from one word and counts in another, taken by a few hundred workgroups one after the other, were 14 us a layer.
+// A layer's first tile clears the words of the layer but one before (whoever waited for those is through); those of the last but one are
+// cleared by whoever is the last to get past its wait for them.  Scoring at d = 400, h = 800, a launch a layer and like this, us a call (the host of
+// the machine between 38 and 50 us for the former): one query 38 to 50 and 32, of it 24 this launch for three depths, four 40 to 50 and 38, eight 44 to 54
+// and 42; one at 512, 1024 37 to 50 and 33, eight at 132, 260 41 to 53 and 32.
+constexpr int CHAIN_ROWS = 4, CHAIN_COLS = 4, CHAIN_T = 256, CHAIN_LINES = 8, CHAIN_STRIDE = 32;
+constexpr int CHAIN_TILES = 2048;
+static_assert(CHAIN_CARD <= CHAIN_ROWS && CHAIN_ROWS * CHAIN_COLS <= 64 && CHAIN_TILES < GAVE_UP, "an intersection is a tile, its sums a lane each");
+static_assert(CHAIN_SYNC == (2 * LEVEL_CHAIN * CHAIN_LINES + 1) * CHAIN_STRIDE, "the words of all layers and of those past the last wait");
+__host__ __device__ inline int chain_row_groups(const RowsProblem& p, bool second) {
+    return second && p.k > 1 ? p.n : (p.n * p.k + CHAIN_ROWS - 1) / CHAIN_ROWS;
+}
+__host__ __device__ inline int chain_col_groups(int n) { return (n + 4 * CHAIN_COLS - 1) / (4 * CHAIN_COLS); }
+__global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];      // [CHAIN_ROWS][K]
+    __shared__ int waited;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int layers = 2 * r.depths, at = (int)blockIdx.x;
+    if (at == r.first[layers]) {                  // (only where there is something to copy)
+        for (int i = threadIdx.x; i < r.copy_n; i += CHAIN_T) r.copy_dst[i] = r.copy_src[i];
+        return;
+    }
+    int32_t* const counts = r.chain;
+    const int polls = r.sync.polls;
+    asm volatile("" ::"s"(counts), "s"(polls));
+    int l = 0;                       // layer: 2 * depth, and one more for the second of the depth
+    for (int i = 1; i < layers; ++i)
+        if (at >= r.first[i]) l = i;
+    const bool second = l & 1;
+    const int K = second ? r.h : r.d, N = second ? r.d : r.h, cols = chain_col_groups(N), in_layer = at - r.first[l];
+    int tile = in_layer, q = 0;
+    for (; q + 1 < r.count[l >> 1]; ++q) {
+        const int n = chain_row_groups(r.p[l >> 1][q], second) * cols;
+        if (tile < n) break;
+        tile -= n;
+    }
+    const RowsProblem p = r.p[l >> 1][q];
+    const int rg = tile / cols, nb = tile - rg * cols;
+    const bool pooled = second && p.k > 1;
+    const int M = pooled ? p.k : min(CHAIN_ROWS, p.n * p.k - rg * CHAIN_ROWS), row_lo = pooled ? rg : rg * CHAIN_ROWS, row_step = pooled ? p.n : 1;
+    const int n0 = (nb * 4 + wave) * CHAIN_COLS, k4 = K >> 2;
+    const float* W = second ? r.Wb[p.type] : r.Wa[p.type];
+    const float* bias_of = second ? r.bb[p.type] : r.ba[p.type];
+    float4 w[CHAIN_COLS][CHAIN_WIDTH / 256];
+#pragma unroll
+    for (int c = 0; c < CHAIN_WIDTH / 256; ++c)
+#pragma unroll
+        for (int j = 0; j < CHAIN_COLS; ++j)
+            if (c * 64 < k4) w[j][c] = *reinterpret_cast<const float4*>(W + (size_t)min(n0 + j, N - 1) * K + min(c * 64 + lane, k4 - 1) * 4);
+    float bias[CHAIN_COLS];
+#pragma unroll
+    for (int j = 0; j < CHAIN_COLS; ++j) bias[j] = bias_of[min(n0 + j, N - 1)];
+    // a wavefront takes an input row (the last one again where there are fewer)
+    const int mine = row_lo + min(wave, M - 1) * row_step;
+    const int32_t ref = second ? 0 : r.words[p.at + mine];
+    const bool related = !second && p.type == 0;
+    const float* rel = r.R + (related ? (size_t)r.words[p.at + p.n + mine] * K : 0);
+    // (lane CHAIN_COLS m + j stores column n0 + j of row m, and has that of input m of an intersection)
+    const int m_out = pooled ? 0 : min(lane / CHAIN_COLS, M - 1), col = n0 + lane % CHAIN_COLS;
+    const int out_row = second ? r.words[p.at + p.n * p.k + (p.type == 0 ? p.n : 0) + row_lo + m_out] : p.row0 + row_lo + m_out;
+    float* const to = (second ? r.act : r.H[p.type]) + (size_t)out_row * N + col;
+    float4 x[CHAIN_WIDTH / 256], y[CHAIN_WIDTH / 256];
+#pragma unroll
+    for (int c = 0; c < CHAIN_WIDTH / 256; ++c) {
+        const int k = min(c * 64 + lane, k4 - 1) * 4;
+        if (related && c * 64 < k4) y[c] = *reinterpret_cast<const float4*>(rel + k);
+        if (ref < 0 && c * 64 < k4) x[c] = *reinterpret_cast<const float4*>(r.E + (size_t)(-1 - ref) * K + k);
+    }
+    bool there = true;
+    if (l > 0) {
+        if (wave == 0) {
+            const int tiles = r.first[l] - r.first[l - 1], want = (tiles - lane + CHAIN_LINES - 1) / CHAIN_LINES;       // of this lane's word
+            const int32_t* word = counts + ((l - 1) * CHAIN_LINES + min(lane, CHAIN_LINES - 1)) * CHAIN_STRIDE;
+            bool all = false;
+            for (int i = 0; i < polls; ++i) {
+                const int n = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                all = __ballot(lane < CHAIN_LINES && n != want) == 0ull;
+                if (all || __ballot(lane < CHAIN_LINES && n > want) != 0ull) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (lane == 0) waited = all;
+        }
+        asm volatile("" ::: "memory");
+        __syncthreads();
+        there = waited != 0;
+    }
+    if (ref >= 0) {
+        const float* row = second ? r.H[p.type] + (size_t)(p.row0 + mine) * K : r.act + (size_t)ref * K;
+#pragma unroll
+        for (int c = 0; c < CHAIN_WIDTH / 256; ++c)
+            if (c * 64 < k4) x[c] = row_get<true>(row + min(c * 64 + lane, k4 - 1) * 4);
+    }
+    float input = 0.f;
+    if (pooled) input = row_get1<true>(r.Z + (size_t)(p.row0 + row_lo + min(lane / CHAIN_COLS, p.k - 1) * row_step) * r.d + min(col, N - 1));
+    // (the clearing, beside the loads)
+    if (there && l >= 2 && in_layer == 0 && threadIdx.x < CHAIN_LINES)
+        __hip_atomic_store(counts + ((l - 2) * CHAIN_LINES + threadIdx.x) * CHAIN_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (there && l + 1 == layers && threadIdx.x == CHAIN_T - 1) {
+        int32_t* past = counts + 2 * LEVEL_CHAIN * CHAIN_LINES * CHAIN_STRIDE;
+        if (__hip_atomic_fetch_add(past, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r.first[layers] - r.first[l] - 1) {
+            __hip_atomic_store(past, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int i = 0; i < CHAIN_LINES; ++i)
+                __hip_atomic_store(counts + ((l - 1) * CHAIN_LINES + i) * CHAIN_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (wave < M) {
+#pragma unroll
+        for (int c = 0; c < CHAIN_WIDTH / 256; ++c) {
+            if (c * 64 + lane >= k4) break;
+            float4 v = x[c];
+            if (related) { v.x += y[c].x; v.y += y[c].y; v.z += y[c].z; v.w += y[c].w; }
+            *reinterpret_cast<float4*>(lds + wave * K + (c * 64 + lane) * 4) = v;
+            if (nb == 0 && !second && p.k > 1) row_put<true>(r.Z + (size_t)(p.row0 + mine) * K + (c * 64 + lane) * 4, v);
+        }
+    }
+    __syncthreads();
+    float out = 0.f, sum[CHAIN_ROWS][CHAIN_COLS];
+#pragma unroll
+    for (int m = 0; m < CHAIN_ROWS; ++m) {
+        if (m >= M) continue;        // uniform
+        float acc[CHAIN_COLS];
+#pragma unroll
+        for (int j = 0; j < CHAIN_COLS; ++j) acc[j] = 0.f;
+#pragma unroll
+        for (int c = 0; c < CHAIN_WIDTH / 256; ++c) {
+            if (c * 64 + lane >= k4) break;
+            const float4 v = *reinterpret_cast<const float4*>(lds + m * K + (c * 64 + lane) * 4);
+#pragma unroll
+            for (int j = 0; j < CHAIN_COLS; ++j) acc[j] += (v.x * w[j][c].x + v.y * w[j][c].y) + (v.z * w[j][c].z + v.w * w[j][c].w);
+        }
+#pragma unroll
+        for (int j = 0; j < CHAIN_COLS; ++j) {
+            float v = wave_sum_dpp(acc[j]) + bias[j];
+            if (!second) v = fmaxf(v, 0.f);
+            sum[m][j] = v;
+            if (lane == m * CHAIN_COLS + j) out = v;
+        }
+    }
+    if (pooled) {
+#pragma unroll
+        for (int j = 0; j < CHAIN_COLS; ++j) {
+            float mx = -INFINITY, den = 0.f, v = 0.f;
+#pragma unroll
+            for (int m = 0; m < CHAIN_ROWS; ++m)
+                if (m < M) mx = fmaxf(mx, sum[m][j]);
+#pragma unroll
+            for (int m = 0; m < CHAIN_ROWS; ++m) {
+                sum[m][j] = m < M ? expf(sum[m][j] - mx) : 0.f;
+                den += sum[m][j];
+            }
+            const float inv = 1.f / den;
+#pragma unroll
+            for (int m = 0; m < CHAIN_ROWS; ++m)
+                if (m < M) v += sum[m][j] * inv * lane_value(input, m * CHAIN_COLS + j);
+            if (lane == j) out = v;
+        }
+    }
+    if (!there) out = NAN;
+    if (lane < (pooled ? 1 : M) * CHAIN_COLS && col < N) row_put1<true>(to, out);
+    wait_vm<0>();                    // this wavefront's values are where the next layer finds them,
+    __syncthreads();                 // ... and everybody's
+    if (threadIdx.x != 0) return;
+    if (!there) {
+        __hip_atomic_store(r.sync.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(r.sync.host_gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (l + 1 < layers)
+        __hip_atomic_fetch_add(counts + (l * CHAIN_LINES + in_layer % CHAIN_LINES) * CHAIN_STRIDE, there ? 1 : GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 size_t lv_lds(int d, int h) { return ((size_t)LV_ROWS * (2 * lv_pitch(d) + lv_pitch(h)) + d + h) * sizeof(float); }
 
 }  // namespace
@@ -494,6 +671,27 @@ hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
     else if (a.off) hipLaunchKernelGGL((level_kernel<false, true>), grid, dim3(LV_T), lds, s, a);
     else if (backward) hipLaunchKernelGGL((level_kernel<true, false>), grid, dim3(LV_T), lds, s, a);
     else hipLaunchKernelGGL((level_kernel<false, false>), grid, dim3(LV_T), lds, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_rows_chain(RowsChain& r, hipStream_t s) {
+    if (r.depths < 1 || r.depths > LEVEL_CHAIN || r.d < 4 || r.h < 4 || (r.d & 3) || (r.h & 3) || std::max(r.d, r.h) > CHAIN_WIDTH || r.n_words > CHAIN_WORDS ||
+        !r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.copy_n < 0 || (r.copy_n > 0 && (!r.copy_src || !r.copy_dst)))
+        return hipErrorInvalidValue;
+    int tiles = 0;
+    for (int l = 0; l < 2 * r.depths; ++l) {
+        r.first[l] = tiles;
+        if (r.count[l >> 1] < 1 || r.count[l >> 1] > CHAIN_PROBLEMS) return hipErrorInvalidValue;
+        for (int q = 0; q < r.count[l >> 1]; ++q) {
+            const RowsProblem& p = r.p[l >> 1][q];
+            if (p.n < 1 || p.k < 1 || p.k > CHAIN_CARD || p.type < 0 || p.type > 2 || p.at < 0 || p.at + p.n * (p.k + 1 + (p.type == 0 ? 1 : 0)) > r.n_words) return hipErrorInvalidValue;
+            tiles += chain_row_groups(p, l & 1) * chain_col_groups(l & 1 ? r.d : r.h);
+        }
+    }
+    for (int l = 2 * r.depths; l <= 2 * LEVEL_CHAIN; ++l) r.first[l] = tiles;
+    if (tiles > CHAIN_TILES) return hipErrorInvalidValue;
+    const size_t bytes = (size_t)CHAIN_ROWS * std::max(r.d, r.h) * sizeof(float);
+    hipLaunchKernelGGL(rows_chain_kernel, dim3(tiles + (r.copy_n > 0 ? 1 : 0)), dim3(CHAIN_T), bytes, s, r);
     return hipGetLastError();
 }
 

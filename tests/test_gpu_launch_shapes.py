@@ -265,6 +265,97 @@ def test_depths_of_a_pass_in_one_launch(B, d, h):
         plan.free()
 
 
+# A pass of a handful of queries, all layers in one launch against a launch each, bit for bit: one row and rows that fill no tile, widths
+# that fill no chunk of a wavefront up to the widest, every cardinality it pools and one more, as many depths as it takes and one more, more
+# words than its arguments hold; from a plan that it brings to the device itself, and for what reads that plan afterwards; on context after another
+@pytest.mark.parametrize("d,h,B", [(400, 800, 1), (400, 800, 5), (132, 260, 3), (260, 1024, 7), (1024, 36, 4), (516, 132, 16), (400, 800, 40)])
+def test_layers_of_a_few_rows_in_one_launch(d, h, B):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    rng = np.random.default_rng(d + B)
+    N, R = 900, 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    inter = lambda k: ("i",) + tuple(proj() for _ in range(k))
+    kinds = [lambda: proj(), lambda: inter(2), lambda: proj(inter(3)), lambda: ("i", proj(), ("n", proj(proj()))), lambda: ("u", proj(), proj(proj())),
+             lambda: proj(("i", proj(), ("n", proj()))), lambda: inter(4), lambda: inter(5), lambda: proj(proj(proj(proj(proj()))))]
+    batches = [[kinds[(first + i) % len(kinds)]() for i in range(B)] for first in range(len(kinds))]
+    eng = Engine(N, R, d, h, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, d, h, 6))
+    cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    ans = cand[:, :2].contiguous().view(-1)
+    off = torch.arange(0, 2 * B + 1, 2, dtype=torch.int32, device="cuda")
+    for trees in batches:
+        qb = wl.batch_from_trees(trees, [0] * B)
+        out = []
+        for polls in (-1, 1 << 22):
+            assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
+            got = []
+            for call in (lambda p: [eng.score(p, cand)], lambda p: list(eng.rank_all(p, 3)), lambda p: list(eng.rank_answers(p, off, ans))):
+                plan = eng.plan(qb)
+                got += [t.clone() for _ in range(2) for t in call(plan)]
+                plan.free()
+            plan = eng.plan(qb)
+            got.append(eng.score(plan, cand).clone())
+            got.append(eng.score_noalloc(plan, cand, torch.empty_like(got[0])).clone())
+            got.append(eng.forward_backward(plan, cand).clone())
+            plan.free()
+            out.append(got)
+        assert all(torch.equal(a, b) for a, b in zip(*out)), trees
+
+
+# ... one that gives up waiting (here at once): nobody can take what it leaves for results, the next call is refused, and what is computed
+# after that is as if nothing had been
+def test_layers_of_a_few_rows_that_give_up_waiting():
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R, B = 900, 9, 3
+    eng = Engine(N, R, 400, 800, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, 400, 800, 6))
+    qb = wl.batch_from_trees([("p", 1, ("e", 5)), ("i", ("p", 2, ("e", 7)), ("p", 3, ("e", 9))), ("p", 4, ("p", 5, ("e", 6)))], [0] * B)
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9)
+    off = torch.arange(0, 2 * B + 1, 2, dtype=torch.int32, device="cuda")
+    calls = [lambda p: [eng.score(p, cand)], lambda p: list(eng.rank_all(p, 3)), lambda p: list(eng.rank_answers(p, off, cand[:, :2].contiguous().view(-1)))]
+    invalid = [lambda out: bool((out[0] == -np.inf).all()), lambda out: bool((out[0] == -1).all()), lambda out: bool((out[0] == 0).all())]
+    polls = lambda n: binding.lib().ngdb_debug_chain_polls(eng.ctx, n)
+    plan = eng.plan(qb)
+    want = [[t.clone() for t in call(plan)] for call in calls]
+    for call, ok in zip(calls, invalid):
+        assert polls(0) == 0
+        assert ok(call(plan))
+        torch.cuda.synchronize()
+        with pytest.raises(binding.NgdbError) as e:
+            eng.score(plan, cand)
+        assert e.value.code == binding.ERR_HIP, str(e.value)
+    assert polls(1 << 22) == 0
+    for call, ok in zip(calls, want):
+        assert all(torch.equal(a, b) for a, b in zip(call(plan), ok))
+    plan.free()
+
+
+# ... captured: every replay as the call
+def test_layers_of_a_few_rows_captured():
+    import torch
+    from paper_2602_21597_amd import Engine
+    N, R, B = 900, 9, 3
+    eng = Engine(N, R, 400, 800, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, 400, 800, 6))
+    qb = wl.batch_from_trees([("p", 1, ("e", 5)), ("i", ("p", 2, ("e", 7)), ("p", 3, ("e", 9))), ("p", 4, ("p", 5, ("e", 6)))], [0] * B)
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9)
+    plan, other = eng.plan(qb), eng.plan(qb.select(np.arange(2)))
+    want = eng.score(plan, cand).clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = eng.score(plan, cand)
+    for _ in range(4):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        eng.score(other, cand[:2].contiguous())
+    plan.free()
+    other.free()
+
+
 # both directions of both families, all depths in one launch against a launch each
 @pytest.mark.parametrize("box", [False, True])
 @pytest.mark.parametrize("B,d,h", [(1, 36, 52), (64, 32, 64), (300, 128, 160), (700, 64, 128), (1900, 36, 52)])
