@@ -95,6 +95,7 @@ struct ngdb_ctx_s {
     DevBuf w_pieces;
     bool chained = false;          // the pass under way has a launch of several depths
     bool rows_chained = false;     // ... its first, which is all of its forward pass (rows_chain)
+    bool plan_rides = false;       // the plan comes to the device with the launch of all depths of the forward pass, which reads it where it is
     SmallIndex index_waits{};      // a small gradient index that a launch of the forward pass may take along (n: 0 without one)
     DevBuf sync;        // of the launches of several depths (LevelSync), in device memory
     int32_t* gave_up = nullptr;    // and in pinned host memory: one of them has given up waiting, for good
@@ -386,6 +387,18 @@ bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vecto
     return true;
 }
 
+int plan_uploaded(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
+    if (pl->uploaded) return NGDB_OK;
+    // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIPCHK(c, hipStreamIsCapturing(s, &st));
+    if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
+    return NGDB_OK;
+}
+PlanCopy plan_copy(const ngdb_plan_t* pl) {
+    return PlanCopy{reinterpret_cast<const float4*>(pl->blob.pinned), reinterpret_cast<float4*>(pl->blob.dev), (int)(pl->blob_bytes / 16)};
+}
+
 // All depths of a direction in one launch, where each would take one and they are few enough.  fill() adds to a depth what the pass knows.
 template <class Fill>
 bool enqueue_levels(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Fill fill, const LevelSync& sync, hipStream_t s, int* rc) {
@@ -400,16 +413,37 @@ bool enqueue_levels(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Fill fi
         flop += level_flop(c, segs);
     }
     if (!levels_chain(la, n)) return false;
+    PlanCopy copy;
+    if (!backward && c->plan_rides) {
+        copy = plan_copy(pl);
+        auto there = [&](const int32_t*& p) { if (p) p = pl->blob.pinned + (p - pl->d_blob); };
+        for (int i = 0; i < n; ++i) {
+            there(la[i].refs); there(la[i].rel); there(la[i].out_row);
+        }
+        if (c->index_waits.n > 0) there(c->index_waits.head);
+    }
     auto launch = [&]() -> int {
         Timed tm(c, backward ? NGDB_TK_GEMM_BWD : NGDB_TK_GEMM_FWD, s);
-        HIPCHK(c, launch_levels(la, n, backward, sync, backward ? nullptr : &c->index_waits, s));
+        HIPCHK(c, launch_levels(la, n, backward, sync, backward ? nullptr : &c->index_waits, copy, s));
         if (!backward) c->index_waits.n = 0;
         c->chained = true;
         tm.work(GEMM_FP32, flop);
-        return NGDB_OK;
+        if (!copy.n) return NGDB_OK;
+        c->plan_rides = false;
+        return plan_uploaded(c, pl, s);
     };
     *rc = launch();
     return true;
+}
+
+// Whether enqueue_levels will take the forward pass.
+bool forward_chained(const ngdb_ctx_t* c, const ngdb_plan_t* pl) {
+    const int n = pl->hp.n_levels;
+    if (n < 2 || n > LEVEL_CHAIN || !level_sync(c).counts) return false;
+    LevelArgs la[LEVEL_CHAIN];
+    for (int i = 0; i < n; ++i)
+        if (!level_problems(c, pl, pl->levels[i + 1], &la[i])) return false;
+    return levels_chain(la, n);
 }
 
 // Splits the weights of the MLPs for a pass, for its backward half too if it has one (at d = 400, h = 800 scoring 1024 queries takes 415 us instead of 423 without it).
@@ -497,24 +531,15 @@ bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
 // read the staging buffer (120 KB: 5 us as a launch of its own), which needs neither a wait on the host (10 us) nor an
 // event between streams (9 us of host time).  Large ones are copied when they are planned.
 constexpr size_t PLAN_INLINE_BYTES = 256 << 10;
-int plan_uploaded(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
-    if (pl->uploaded) return NGDB_OK;
-    // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    HIPCHK(c, hipStreamIsCapturing(s, &st));
-    if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
-    return NGDB_OK;
-}
-int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t s, bool chain = false) {
+// chain: a forward pass that rows_chain may take; ride: nothing but that pass (and an index it takes along) reads the plan before it is through.
+int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t s, bool chain = false, bool ride = false) {
     const int waited = check_waits(c);
     if (waited != NGDB_OK) return waited;
-    c->chained = c->rows_chained = false;
+    c->chained = c->rows_chained = c->plan_rides = false;
     RowsChain r;
     if (chain && rows_chain(c, pl, &r)) {
         if (!pl->uploaded) {
-            r.copy_dst = reinterpret_cast<float4*>(pl->blob.dev);
-            r.copy_src = reinterpret_cast<const float4*>(pl->blob.pinned);
-            r.copy_n = (int)(pl->blob_bytes / 16);
+            r.copy = plan_copy(pl);
         }
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
         const hipError_t e = launch_rows_chain(r, s);
@@ -534,6 +559,11 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
         J.copy_n = (int)(pl->blob_bytes / 16);
     }
     add_weight_pieces(c, pl, backward, &J);
+    // (a launch of the plan alone is 4 of the 62 us of a step of 64 queries x 8 negatives at d = 32, h = 64)
+    if (ride && !pl->uploaded && J.count == 0 && forward_chained(c, pl)) {
+        c->plan_rides = true;
+        return NGDB_OK;
+    }
     {
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
         HIPCHK(c, launch_weight_pieces(J, s));
@@ -1246,7 +1276,6 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     int rc = size_workspace(c, pl, K, !apply);
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, stream};
-    if ((rc = begin_pass(c, pl, true, stream)) != NGDB_OK) return rc;
 
     // 1. entity gradient index (depends only on the plan and the negatives).  With a library stream the index build, and with
     // text features the fusion of all rows that are scored, run beside the forward pass, which needs the anchors' rows only.
@@ -1262,6 +1291,14 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
                                                           n_contrib <= 70000 && max_rows * d <= 2000000));
     const bool aside = c->n_side > 0 && !host_bound;
     hipStream_t s_idx = aside ? c->side[0] : stream;
+    // (a small index on the caller's stream: the launch of a small forward pass takes it along, or it follows)
+    c->index_waits.n = 0;
+    const bool index_rides = !aside && !sem && small_index_job(pl->d_ekeys_head, hp.n_anchor + B, d_neg, (int64_t)B * K, c->cfg.n_entities,
+                                                               index_buffers(c), &c->index_waits);
+    if ((rc = begin_pass(c, pl, true, stream, false, index_rides)) != NGDB_OK) {
+        c->index_waits.n = 0;
+        return rc;
+    }
     if (sem && (rc = cast_projection(c, stream)) != NGDB_OK) return rc;
     if (aside) {
         HIPCHK(c, hipEventRecord(c->ev_fork, stream));
@@ -1269,10 +1306,6 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         end.forked = true;
     }
     EntRows er{c->prm.E.p, pl->d_in_ref, pl->d_pos, d_neg}, scored = er;
-    // (a small index on the caller's stream: the launch of a small forward pass takes it along, or it follows)
-    c->index_waits.n = 0;
-    const bool index_rides = !aside && !sem && small_index_job(pl->d_ekeys_head, hp.n_anchor + B, d_neg, (int64_t)B * K, c->cfg.n_entities,
-                                                               index_buffers(c), &c->index_waits);
     if (index_rides) e_src = c->index_waits.vals_out;
     else if ((rc = build_index(c, pl, d_neg, (int64_t)B * K, s_idx, &e_src)) != NGDB_OK) return rc;
     if (sem) {
@@ -2179,7 +2212,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     int rc = reclaim ? size_forward_only(c, pl, n_tail) : size_workspace(c, pl, d_cand ? C : 0, false);
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, s};
-    if ((rc = begin_pass(c, pl, false, s, reclaim)) != NGDB_OK) return rc;
+    if ((rc = begin_pass(c, pl, false, s, reclaim, c->cfg.d_sem == 0)) != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, d_cand, n_tail, s, &er, reclaim);
@@ -2291,7 +2324,7 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     int rc = reclaim ? size_forward_only(c, pl, 0) : size_workspace(c, pl, 0, false);
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, s};
-    if ((rc = begin_pass(c, pl, false, s, reclaim)) != NGDB_OK) return rc;
+    if ((rc = begin_pass(c, pl, false, s, reclaim, c->cfg.d_sem == 0)) != NGDB_OK) return rc;
     const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, nullptr, 0, s, &er, reclaim);

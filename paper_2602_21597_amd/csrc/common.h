@@ -367,6 +367,12 @@ struct LevelSync {
     int32_t* host_gave_up = nullptr;        // the same in pinned host memory, for the next call
     int32_t polls = 0;              // looks at a count before a wait gives up (0: it does at once)
 };
+// The plan, copied from pinned memory for the launches that follow, by one more workgroup (n: 16-byte units, 0: nothing to copy).
+struct PlanCopy {
+    const float4* src = nullptr;
+    float4* dst = nullptr;
+    int n = 0;
+};
 // A forward pass of a handful of queries, all layers of all depths in one launch (level.hip: rows_chain_kernel).  A problem is a projection or
 // negation group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its depth's buffers; words[at ..] holds
 // its n k references, the relations of a projection and its n output rows, so that nothing waits for the plan to reach the device.
@@ -383,14 +389,12 @@ struct RowsChain {
     float *act, *Z, *H[3];                          // outputs; inputs of intersections; hidden rows by type
     LevelSync sync;                                 // (its counts are not used)
     int32_t* chain;                                 // CHAIN_SYNC words
-    const float4* copy_src = nullptr;               // the plan, copied for the launches that follow by one more workgroup
-    float4* copy_dst = nullptr;
-    int copy_n = 0;
+    PlanCopy copy;
     int32_t words[CHAIN_WORDS];
 };
 hipError_t launch_rows_chain(RowsChain& r, hipStream_t s);
 bool levels_chain(const LevelArgs* a, int n);
-hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, hipStream_t s);
+hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, const PlanCopy& copy, hipStream_t s);
 
 // ---------------------------------------------------------------- scoring (score.hip)
 struct ScoreArgs {

@@ -179,7 +179,7 @@ __device__ __forceinline__ void box_projection(const LevelArgs& a, const LevelPr
 // tile `block` of problem p; before(): what it reads of other depths is there
 template <bool BWD, bool BOX, bool CHAIN, class Before>
 __device__ __forceinline__ void level_tile(const LevelArgs& a, const LevelProblem& p, int block, float* lds, Before before) {
-    __shared__ int row_of[LV_ROWS], out_of[LV_ROWS], in_of[LV_ROWS];     // MLP row / output row / input reference of a tile row
+    __shared__ int row_of[LV_ROWS], out_of[LV_ROWS], in_of[LV_ROWS], rel_of[LV_ROWS];     // MLP row / output row / input reference / relation of a tile row
     const LevelMlp w = a.mlp[p.type];
     const int d = a.d, h = a.h, xp = lv_pitch(d), hp = lv_pitch(h);
     float *Xs = lds, *Ls = Xs + LV_ROWS * xp, *Hs = Ls + LV_ROWS * xp, *bias = Hs + LV_ROWS * hp;
@@ -212,6 +212,8 @@ __device__ __forceinline__ void level_tile(const LevelArgs& a, const LevelProble
         } else {
             const int o = p.out0 + min(i, p.n - 1);
             out_of[tid] = a.out_row ? a.out_row[o] : o;
+            in_of[tid] = ok ? a.refs[p.ref_off + r] : 0;
+            rel_of[tid] = ok && p.rel_off >= 0 ? a.rel[p.rel_off + r] : 0;
         }
     }
     if (!BWD)
@@ -219,6 +221,7 @@ __device__ __forceinline__ void level_tile(const LevelArgs& a, const LevelProble
     before();
     // rows of the tile that are no rows, and the columns that fill up the last k-step, count as zeros
     if (!BWD) {
+        __syncthreads();
         const int c4 = (xp - 4) >> 2;
         for (int idx = tid; idx < LV_ROWS * c4; idx += LV_T) {
             const int lr = idx / c4, c = (idx - lr * c4) * 4;
@@ -226,11 +229,11 @@ __device__ __forceinline__ void level_tile(const LevelArgs& a, const LevelProble
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
             if (j < p.k && i < p.n && c < d) {
                 const int r = j * p.n + i;
-                const int32_t ref = a.refs[p.ref_off + r];
+                const int32_t ref = in_of[lr];
                 if (ref >= 0) v = row_get<CHAIN>(act + (size_t)ref * d + c);
                 else v = *reinterpret_cast<const float4*>(a.E + (size_t)(-1 - ref) * d + c);
                 if (p.rel_off >= 0) {
-                    const float4 t = *reinterpret_cast<const float4*>(a.R + (size_t)a.rel[p.rel_off + r] * d + c);
+                    const float4 t = *reinterpret_cast<const float4*>(a.R + (size_t)rel_of[lr] * d + c);
                     v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
                 }
                 if (a.keep) *reinterpret_cast<float4*>(w.Z + (size_t)(p.row0 + r) * d + c) = v;
@@ -409,6 +412,7 @@ struct LevelRun {                   // the first depth's tiles stand in a
     int n, first[LEVEL_CHAIN + 1];      // depths, the first tile of each
     LevelSync sync;
     SmallIndex index;               // (n: 0 without one)
+    PlanCopy copy;                  // (n: 0 without one)
 };
 static_assert(LV_T == SMALL_THREADS, "the index of few keys is a workgroup's job here too");
 // Every output row of all depths becomes NaN, centres of boxes and offsets alike (one thread: a pass that gave up waiting)
@@ -433,6 +437,10 @@ __global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
     __shared__ int number;
     if (INDEX && blockIdx.x == 0) {
         small_index(r.index, lds);
+        return;
+    }
+    if (!BWD && r.copy.n > 0 && blockIdx.x == gridDim.x - 1) {
+        for (int i = threadIdx.x; i < r.copy.n; i += LV_T) r.copy.dst[i] = r.copy.src[i];
         return;
     }
     // (requested here: where it is needed it would cost a round trip to the argument segment)
@@ -495,7 +503,7 @@ __global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int layers = 2 * r.depths, at = (int)blockIdx.x;
     if (at == r.first[layers]) {                  // (only where there is something to copy)
-        for (int i = threadIdx.x; i < r.copy_n; i += CHAIN_T) r.copy_dst[i] = r.copy_src[i];
+        for (int i = threadIdx.x; i < r.copy.n; i += CHAIN_T) r.copy.dst[i] = r.copy.src[i];
         return;
     }
     int32_t* const counts = r.chain;
@@ -676,7 +684,7 @@ hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
 
 hipError_t launch_rows_chain(RowsChain& r, hipStream_t s) {
     if (r.depths < 1 || r.depths > LEVEL_CHAIN || r.d < 4 || r.h < 4 || (r.d & 3) || (r.h & 3) || std::max(r.d, r.h) > CHAIN_WIDTH || r.n_words > CHAIN_WORDS ||
-        !r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.copy_n < 0 || (r.copy_n > 0 && (!r.copy_src || !r.copy_dst)))
+        !r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.copy.n < 0 || (r.copy.n > 0 && (!r.copy.src || !r.copy.dst)))
         return hipErrorInvalidValue;
     int tiles = 0;
     for (int l = 0; l < 2 * r.depths; ++l) {
@@ -691,7 +699,7 @@ hipError_t launch_rows_chain(RowsChain& r, hipStream_t s) {
     for (int l = 2 * r.depths; l <= 2 * LEVEL_CHAIN; ++l) r.first[l] = tiles;
     if (tiles > CHAIN_TILES) return hipErrorInvalidValue;
     const size_t bytes = (size_t)CHAIN_ROWS * std::max(r.d, r.h) * sizeof(float);
-    hipLaunchKernelGGL(rows_chain_kernel, dim3(tiles + (r.copy_n > 0 ? 1 : 0)), dim3(CHAIN_T), bytes, s, r);
+    hipLaunchKernelGGL(rows_chain_kernel, dim3(tiles + (r.copy.n > 0 ? 1 : 0)), dim3(CHAIN_T), bytes, s, r);
     return hipGetLastError();
 }
 
@@ -704,7 +712,7 @@ bool levels_chain(const LevelArgs* a, int n) {
     return n > 1 && n <= LEVEL_CHAIN && tiles <= LEVEL_CHAIN_TILES;
 }
 
-hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, hipStream_t s) {
+hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, const PlanCopy& copy, hipStream_t s) {
     if (!levels_chain(a, n) || !sync.counts || !sync.gave_up || !sync.host_gave_up || !level_fits(a[0].d, a[0].h, true) || (a[0].d & 3) || (a[0].h & 3)) return hipErrorInvalidValue;
     LevelRun r{};
     r.a = a[0];
@@ -717,7 +725,9 @@ hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSy
     const bool with_index = index && index->n > 0;
     if (with_index && backward) return hipErrorInvalidValue;
     if (with_index) r.index = *index;
-    const dim3 grid(r.first[n] + (with_index ? 1 : 0));
+    if (copy.n < 0 || (copy.n > 0 && (backward || !copy.src || !copy.dst))) return hipErrorInvalidValue;
+    r.copy = copy;
+    const dim3 grid(r.first[n] + (with_index ? 1 : 0) + (copy.n > 0 ? 1 : 0));
     const size_t lds = std::max(lv_lds(r.a.d, r.a.h), with_index ? SMALL_INDEX_LDS : 0);
 #define NGDB_LEVELS(...)                                                                                                                    \
     do {                                                                                                                                    \

@@ -332,13 +332,14 @@ def test_layers_of_a_few_rows_that_give_up_waiting():
     plan.free()
 
 
-# ... captured: every replay as the call
-def test_layers_of_a_few_rows_captured():
+# ... captured, and so the launch of all depths of a small model, which copies the plan too: every replay as the call
+@pytest.mark.parametrize("d,h", [(400, 800), (36, 52)])
+def test_layers_of_a_few_rows_captured(d, h):
     import torch
     from paper_2602_21597_amd import Engine
     N, R, B = 900, 9, 3
-    eng = Engine(N, R, 400, 800, 8.0)
-    eng.bind_numpy(wl.make_params(N, R, 400, 800, 6))
+    eng = Engine(N, R, d, h, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, d, h, 6))
     qb = wl.batch_from_trees([("p", 1, ("e", 5)), ("i", ("p", 2, ("e", 7)), ("p", 3, ("e", 9))), ("p", 4, ("p", 5, ("e", 6)))], [0] * B)
     cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9)
     plan, other = eng.plan(qb), eng.plan(qb.select(np.arange(2)))
