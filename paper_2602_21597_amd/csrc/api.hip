@@ -256,8 +256,8 @@ int ensure(ngdb_ctx_t* c, DevBuf& b, size_t bytes, Use use = Use::Any) {
 template <class T>
 T* ptr(const DevBuf& b) { return static_cast<T*>(b.p); }
 
-// Words of c->sync: LevelSync's counts and the mark of a launch that gave up, then those of rows_chain_kernel.
-constexpr int CHAIN_AT = 64, SYNC_WORDS = CHAIN_AT + CHAIN_SYNC;
+// Words of c->sync: LevelSync's counts and the mark of a launch that gave up, then those of rows_chain_kernel and of tile_chain_kernel.
+constexpr int CHAIN_AT = 64, TILE_AT = CHAIN_AT + CHAIN_SYNC, SYNC_WORDS = TILE_AT + TILE_SYNC;
 static_assert(LEVEL_SYNC + 1 <= CHAIN_AT, "lines of their own");
 LevelSync level_sync(const ngdb_ctx_t* c) {
     LevelSync y;
@@ -479,6 +479,8 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
         c->wp[t][2] = jw.out_ck = backward ? at : nullptr; at += pieces_elems(h, d);
     }
     c->have_pieces = true;
+    J->clear = ptr<int32_t>(c->sync) + TILE_AT;
+    J->clear_n = TILE_SYNC;
 }
 
 // All layers of a forward pass in one launch (rows_chain_kernel), where each would be one of a few rows: the same sums in the same order.
@@ -948,6 +950,76 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
     return NGDB_OK;
 }
 
+// The operators of a depth as problems of one launch of tiles.  row0: of the type's buffers.  False: too many, or others.
+template <class Row0>
+bool tile_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, Row0 row0, bool backward, TileProblem* p, int* count) {
+    const HostPlan& hp = pl->hp;
+    LevelArgs la;
+    *count = 0;
+    if (level_problems(c, pl, segs, &la)) return false;
+    // (forward layers of a few rows are summed in another order: such a depth stays with its launches)
+    bool few[2] = {!backward, !backward};
+    for (const Segment& sg : segs) {
+        few[0] = few[0] && gemm_takes_rows(sg.rows, c->cfg.d);
+        few[1] = few[1] && gemm_takes_rows(sg.rows, c->cfg.h);
+    }
+    if (few[0] || few[1]) return false;
+    for (const Segment& sg : segs) {
+        const bool inter = sg.type == T_INTER;
+        if (sg.rows <= 0) continue;
+        for (int i = 0; i < (inter ? sg.g_hi - sg.g_lo : 1); ++i) {
+            if (*count == TILE_PROBLEMS) return false;
+            const int g = sg.g_lo + i, at = inter ? hp.g_mlp_base[g] - sg.mlp_base : 0;
+            if (inter && (hp.g_nin[g] < 2 || hp.g_nin[g] > TILE_CARD)) return false;
+            p[(*count)++] = TileProblem{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, row0(sg) + at, sg.ref_off + at, sg.rel_off,
+                                        inter ? hp.g_out_base[g] : sg.out_base};
+        }
+    }
+    return true;
+}
+// All layers of the depths l0 .. l1 in one launch (tile_chain_kernel), where their launches would be small ones: the same sums in the same order.  False: not
+// such depths.
+bool tile_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, const FwdSpace& w, int l0, int l1, TileChain* r) {
+    const int n = l1 - l0 + 1;
+    if (!w.sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
+    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
+    int counts[LEVEL_CHAIN];
+    for (int i = 0; i < n; ++i)
+        if (!tile_problems(c, pl, pl->levels[l0 + i], [&](const Segment& sg) { return w.reclaim ? 0 : sg.mlp_base; }, false, problems[i], &counts[i])) return false;
+    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = w.reclaim ? 0 : 1;
+    if (!tile_chain_fits(*r, problems, counts, n, false)) return false;
+    for (int t = 0; t < 3; ++t) {
+        const MlpRefs W = mlp_of(c->prm, t);
+        r->W[0][t] = c->wp[t][0]; r->W[1][t] = c->wp[t][1]; r->bias[0][t] = W.ba; r->bias[1][t] = W.bb;
+        r->Z[t] = w.Z[t]; r->H[t] = w.H[t]; r->dH[t] = nullptr;
+    }
+    r->E = er.rows; r->R = c->prm.R.p; r->refs = er.refs; r->rel = pl->d_rel; r->out_row = w.reclaim ? pl->d_f_row : nullptr;
+    r->act = w.act; r->Att = w.Att; r->dact = r->dAtt = r->Dx = nullptr;
+    r->sync = w.sync; r->chain = w.sync.counts + TILE_AT;
+    return true;
+}
+// ... of the backward pass, the deepest first.
+bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, int l0, TileChain* r) {
+    const HostPlan& hp = pl->hp;
+    const LevelSync sync = level_sync(c);
+    const int n = hp.n_levels - l0 + 1;
+    if (!sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
+    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
+    int counts[LEVEL_CHAIN];
+    for (int i = 0; i < n; ++i)
+        if (!tile_problems(c, pl, pl->levels[hp.n_levels - i], [](const Segment& sg) { return sg.mlp_base; }, true, problems[i], &counts[i])) return false;
+    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = 0;
+    if (!tile_chain_fits(*r, problems, counts, n, true)) return false;
+    for (int t = 0; t < 3; ++t) {
+        r->W[0][t] = c->wp[t][2]; r->W[1][t] = c->wp[t][3]; r->bias[0][t] = r->bias[1][t] = nullptr;
+        r->Z[t] = ptr<float>(c->Z[t]); r->H[t] = ptr<float>(c->H[t]); r->dH[t] = ptr<float>(c->dH[t]);
+    }
+    r->E = r->R = nullptr; r->refs = pl->d_in_gslot; r->rel = r->out_row = nullptr;
+    r->act = nullptr; r->Att = ptr<float>(c->Att); r->dact = ptr<float>(c->dact); r->dAtt = ptr<float>(c->dAtt); r->Dx = ptr<float>(c->Dx);
+    r->sync = sync; r->chain = sync.counts + TILE_AT + TILE_LAYERS * TILE_LAYER;
+    return true;
+}
+
 // forward over the plan's frontiers; results in w.act.  The type segments of one
 // depth are independent: they share one grouped launch per MLP layer.
 int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hipStream_t s, const FwdSpace& w) {
@@ -961,8 +1033,25 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
     };
     int rc_l = NGDB_OK;
     if (enqueue_levels(c, pl, false, forward_level, w.sync, s, &rc_l)) return rc_l;
+    TileChain chain;
+    // (depths have fewer rows the deeper they are, as a rule: the last that it can take, and those before it)
+    int chain_to = pl->hp.n_levels;
+    while (chain_to > 0 && !tile_chain(c, pl, er, w, chain_to, chain_to, &chain)) --chain_to;
+    int chain_from = std::max(1, chain_to - LEVEL_CHAIN + 1);
+    while (chain_from < chain_to && !tile_chain(c, pl, er, w, chain_from, chain_to, &chain)) ++chain_from;
+    if (chain_to > 0 && chain_from == chain_to) (void)tile_chain(c, pl, er, w, chain_to, chain_to, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        if (chain_to > 0 && l == chain_from) {
+            Timed tm(c, NGDB_TK_GEMM_FWD, s);
+            HIPCHK(c, launch_tile_chain(chain, false, s));
+            double flop = 0.0;
+            for (; l <= chain_to; ++l) flop += level_flop(c, pl->levels[l]);
+            tm.work(GEMM_SPLIT, flop);
+            c->chained = true;
+            --l;
+            continue;
+        }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
             forward_level(la);
@@ -1106,7 +1195,19 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     int rc_l = NGDB_OK;
     const bool chained = enqueue_levels(c, pl, true, backward_level, level_sync(c), s, &rc_l);
     if (rc_l != NGDB_OK) return rc_l;
-    for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
+    int l_next = chained ? 0 : hp.n_levels;
+    TileChain chain;
+    int chain_from = std::max(1, hp.n_levels - LEVEL_CHAIN + 1);
+    while (l_next && chain_from <= hp.n_levels && !tile_chain_backward(c, pl, chain_from, &chain)) ++chain_from;
+    if (l_next && chain_from <= hp.n_levels) {
+        Timed tm(c, NGDB_TK_GEMM_BWD, s);
+        HIPCHK(c, launch_tile_chain(chain, true, s));
+        double flop = 0.0;
+        for (; l_next >= chain_from; --l_next) flop += level_flop(c, pl->levels[l_next]);
+        tm.work(GEMM_SPLIT, flop);
+        c->chained = true;
+    }
+    for (int l = l_next; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {

@@ -72,6 +72,18 @@ __device__ __forceinline__ void lds_load16_at(const void* base, uint32_t offset,
 __device__ __forceinline__ void lds_load4(const void* gptr, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
 }
+// What workgroups of one launch hand to each other across the dies: loads and stores past the L2s, at the scope of the card.
+__device__ __forceinline__ void lds_load16_card(const void* gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off sc1" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory");
+}
+__device__ __forceinline__ float2 card_get2(const float* p) {          // (8-byte aligned, like the next)
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+__device__ __forceinline__ void card_put2(float* p, float x, float y) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__float_as_uint(y) << 32 | __float_as_uint(x), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
 // at most n vector-memory operations of this wavefront still in flight (they complete in order)
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -227,6 +239,9 @@ struct PieceJobs {
     float4* copy_dst;
     const float4* copy_src;
     int copy_n, copy_blocks;
+    // and clear_n words from clear on are zero afterwards (those that launches of several layers count in)
+    int32_t* clear;
+    int clear_n;
 };
 inline size_t pieces_elems(int N, int K) { return (size_t)((N + 31) / 32) * ((K + 15) / 16) * 1536; }
 hipError_t launch_weight_pieces(PieceJobs& jobs, hipStream_t s);
@@ -367,6 +382,7 @@ struct LevelSync {
     int32_t* host_gave_up = nullptr;        // the same in pinned host memory, for the next call
     int32_t polls = 0;              // looks at a count before a wait gives up (0: it does at once)
 };
+constexpr int32_t GAVE_UP = 1 << 16;      // what a tile that gave up adds to a count of tiles
 // The plan, copied from pinned memory for the launches that follow, by one more workgroup (n: 16-byte units, 0: nothing to copy).
 struct PlanCopy {
     const float4* src = nullptr;
@@ -393,6 +409,40 @@ struct RowsChain {
     int32_t words[CHAIN_WORDS];
 };
 hipError_t launch_rows_chain(RowsChain& r, hipStream_t s);
+// All layers of a pass over up to some hundred rows a depth in one launch (gemm.hip: tile_chain_kernel).  A problem is a projection or negation
+// group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its type's buffers, references ref0 + ... (and
+// relations rel0 + ..., -1: none), outputs out0 + i.  Limits: inputs of an intersection, input values and hidden values of a row, problems of a depth.
+constexpr int TILE_CARD = 4, TILE_D = 512, TILE_H = 1024, TILE_PROBLEMS = 6, TILE_PARTS = 32;
+// words of counts, zero before the launch: of the layers of a forward pass (two a depth), then of a backward one (up to three a depth)
+constexpr int TILE_LINES = 16, TILE_STRIDE = 32, TILE_LAYER = TILE_LINES * TILE_STRIDE;
+constexpr int TILE_LAYERS = 2 * LEVEL_CHAIN, TILE_LAYERS_BWD = 3 * LEVEL_CHAIN, TILE_SYNC = (TILE_LAYERS + TILE_LAYERS_BWD) * TILE_LAYER;
+struct TileProblem { int type, k, n, row0, ref0, rel0, out0; };
+// What the tiles of a part do.  Backward: the gradient of the hidden rows (from that of the outputs), of the inputs (from that of the
+// hidden rows), and before both the pooling of a class.
+enum TileKind { TILE_FIRST = 0, TILE_SECOND = 1, TILE_POOLED = 3, TILE_POOL_BWD = 2 };
+// The tiles of a problem in one layer: mt = quotient of a tile's number by `by` (the row tile) or its remainder, mem members each; number: of its first tile
+// in the layer.  inv_*: what a product's upper half divides by.
+struct TilePart { int M, row0, ref0, rel0, out0, number, tiles, by; uint32_t inv_by; int m_major, mem, inv_mem, n_mem, cls, pools; };
+struct TileChain {
+    int d, h, layers = 0, parts = 0;
+    int keep = 0;                                   // forward: inputs, hidden rows and logits are kept for a backward pass
+    int tiles[TILE_LAYERS_BWD] = {};                // of a layer
+    uint32_t start[TILE_PARTS];                     // of a part: its first workgroup << 8 | layer << 4 | type << 2 | kind
+    TilePart part[TILE_PARTS];
+    const uint16_t* W[2][3];                        // by layer of the MLP (backward: in the order they are taken) and type: pieces of the weights, biases,
+    const float* bias[2][3];                        // ... inputs of the second layer and outputs of the first
+    float *Z[3], *H[3];
+    const float *E, *R;
+    const int32_t *refs, *rel, *out_row;            // out_row: row of act per output (null: itself); backward: refs = row of dact per reference
+    float *act, *Att;
+    float *dact, *dAtt, *Dx, *dH[3];                // backward
+    LevelSync sync;                                 // (its counts are not used)
+    int32_t* chain;                                 // a word of TILE_LINES on lines of their own per layer
+    int blocks = 0;
+};
+// Lays out the tiles of n depths in the order given (count[l] problems each).  False: no such launch, or so many tiles that one is not the better way.
+bool tile_chain_fits(TileChain& r, const TileProblem (*p)[TILE_PROBLEMS], const int* count, int n, bool backward);
+hipError_t launch_tile_chain(const TileChain& r, bool backward, hipStream_t s);
 bool levels_chain(const LevelArgs* a, int n);
 hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, const PlanCopy& copy, hipStream_t s);
 

@@ -240,6 +240,7 @@ constexpr int WTILE = 3 * 512;            // bf16 values of one tile
 // (four tiles along k) and B[n = column][k = row] (two tile rows x two k-tiles).
 __global__ __launch_bounds__(256) void weight_pieces_kernel(const PieceJobs J) {
     __shared__ float blk[32][65];
+    for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < J.clear_n; i += gridDim.x * 256) J.clear[i] = 0;
     if ((int)blockIdx.x < J.copy_blocks) {
         for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < J.copy_n; i += J.copy_blocks * 256) J.copy_dst[i] = J.copy_src[i];
         return;
@@ -1207,6 +1208,335 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
     }
 }
 
+// A pass over up to some hundred rows a depth, all layers of all depths in one launch a direction (or of the deep ones, where the first have more rows).
+// As launches such layers take 6 to 10 us and a gap of 2 before each; what bounds them is the chain from the arguments over references, rows and weights to the
+// sums, not the 1 to 2 us of the matrix unit.  Here a workgroup has one tile of 32 rows x 32 columns, requests its first weights and
+// relations and looks its rows up before it waits for the layer before, and then brings its rows into LDS at once; the weights go from
+// global memory into the registers they are multiplied from.  k is dealt to the eight wavefronts in blocks of 16, four of them on the way; 64 KB
+// of LDS and 128 registers leave room for two workgroups a compute unit.  Rows handed from layer to layer are stored and loaded at
+// the scope of the card (level.hip: levels_kernel).  Tiles are dealt by workgroup number as in rows_chain_kernel, whose waits and
+// giving up these are; the counts are cleared by the launch that splits the weights.  Sums are formed as in product_kernel with eight partial sums.
+// What a workgroup has to know first comes in two round trips to the argument segment, its part of the layer, then that part's values
+// and pointers (looked up one by one, with divisions, the start of a tile took 2 to 6 us instead of 1.0 to 2.5).  A layer takes 4.3 us at k = 400 and 5.3 at
+// 800: 0.9 until a count is seen, 0.7 for the rows, 1.3 and 2.3 for the products, 0.5 to 1 for sums and pooling, 0.5 for the stores.
+// Scoring and training with 8 negatives, by launches and like this, us: 40 queries at d = 400, h = 800 75 and 162 against 64 and 137, 160
+// queries 84 and 186 against 76 and 175, 320 95 and 222 against 91 and 216; 40 at 208, 416 63 and 141 against 50 and 108, 160 70 and 155 against 52 and 123, 512 76
+// and 181 against 66 and 171; 40 at 512, 1024 77 and 177 against 69 and 157.
+constexpr int TC_WAVES = 8, TC_T = TC_WAVES * 64, TC_AHEAD = 4, TC_LD = 36;
+static_assert(TC_AHEAD * TC_WAVES * 16 >= TILE_D && 2 * TC_AHEAD * TC_WAVES * 16 >= TILE_H, "relations in registers; two chunks at most");
+// Waits until all tiles of the layer before are through (each counts on one of its words); every thread learns whether they are.
+__device__ __forceinline__ bool tc_wait(const int32_t* words, int tiles, int polls, int* waited) {
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x, want = (tiles - lane + TILE_LINES - 1) / TILE_LINES;       // of this lane's word
+        const int32_t* word = words + min(lane, TILE_LINES - 1) * TILE_STRIDE;
+        bool all = false;
+        for (int i = 0; i < polls; ++i) {
+            const int n = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            all = __ballot(lane < TILE_LINES && n != want) == 0ull;
+            if (all || __ballot(lane < TILE_LINES && n > want) != 0ull) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        if (lane == 0) *waited = all;
+    }
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    return *waited != 0;
+}
+// The end of a tile that others wait for (number: in its layer; counts: null where nobody does)
+__device__ __forceinline__ void tc_through(const TileChain& r, int32_t* counts, int number, bool there) {
+    if (!counts && there) return;
+    wait_vm<0>();                    // this wavefront's values are where the next layer finds them,
+    __syncthreads();                 // ... and everybody's
+    if (threadIdx.x != 0) return;
+    if (!there) {
+        __hip_atomic_store(r.sync.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(r.sync.host_gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (counts) __hip_atomic_fetch_add(counts + number % TILE_LINES * TILE_STRIDE, there ? 1 : GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// A tile of a class's pooling, backward (pool.h: attention<true>): a thread takes four coordinates of a member.
+__device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TilePart& p, int tile, const int32_t* before_counts, int before_tiles, int polls,
+                                                 int32_t* counts, int* waited) {
+    if (tile >= p.tiles) return;
+    const int d = r.d, d4 = d >> 2, k = p.cls, t = tile * TC_T + (int)threadIdx.x;
+    const bool inside = t < p.n_mem * d4;
+    const int i = min((int)__umulhi((uint32_t)t, p.inv_by), p.n_mem - 1), c = min(t - i * d4, d4 - 1) * 4;      // (inv_by: by d4)
+    float4 a[TILE_CARD], x[TILE_CARD];
+#pragma unroll
+    for (int j = 0; j < TILE_CARD; ++j) {
+        const size_t at = (size_t)(p.row0 + min(j, k - 1) * p.n_mem + i) * d + c;
+        a[j] = load_global4(r.Att + at);
+        x[j] = load_global4(r.Z[1] + at);
+    }
+    const bool there = before_counts ? tc_wait(before_counts, before_tiles, polls, waited) : true;
+    const float* from = r.dact + (size_t)(p.out0 + i) * d + c;
+    const float2 g0 = card_get2(from), g1 = card_get2(from + 2);
+    auto one = [&](float g, auto of) {
+        float mx = -INFINITY, den = 0.f, tall = 0.f;
+#pragma unroll
+        for (int j = 0; j < TILE_CARD; ++j)
+            if (j < k) mx = fmaxf(mx, of(a[j]));
+#pragma unroll
+        for (int j = 0; j < TILE_CARD; ++j) {
+            of(a[j]) = j < k ? expf(of(a[j]) - mx) : 0.f;
+            den += of(a[j]);
+        }
+        const float inv = 1.f / den;
+#pragma unroll
+        for (int j = 0; j < TILE_CARD; ++j) tall += of(a[j]) * inv * of(x[j]) * g;
+#pragma unroll
+        for (int j = 0; j < TILE_CARD; ++j) {
+            const float w = of(a[j]) * inv;
+            of(a[j]) = there ? w * (g * of(x[j]) - tall) : NAN;
+            of(x[j]) = w * g;
+        }
+    };
+    one(g0.x, [](float4& f) -> float& { return f.x; });
+    one(g0.y, [](float4& f) -> float& { return f.y; });
+    one(g1.x, [](float4& f) -> float& { return f.z; });
+    one(g1.y, [](float4& f) -> float& { return f.w; });
+#pragma unroll
+    for (int j = 0; j < TILE_CARD; ++j) {
+        if (j >= k || !inside) break;
+        const size_t at = (size_t)(p.row0 + j * p.n_mem + i) * d + c;
+        card_put2(r.dAtt + at, a[j].x, a[j].y);
+        card_put2(r.dAtt + at + 2, a[j].z, a[j].w);
+        card_put2(r.Dx + at, x[j].x, x[j].y);
+        card_put2(r.Dx + at + 2, x[j].z, x[j].w);
+    }
+    tc_through(r, counts, p.number + tile, there);
+}
+// BWD: the reverse.  An intersection's pooling is a layer of its own, four coordinates of a member a thread, ahead of its depth's other two.
+template <bool BWD>
+__global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[TC_WAVES * TC_AHEAD * 2048];
+    __shared__ int waited;
+    static_assert(sizeof(lds) >= TC_WAVES * 32 * TC_LD * sizeof(float), "partial sums lie over the rows");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int layers = r.layers;
+    const uint32_t at = blockIdx.x;
+    int32_t* const counts = r.chain;
+    const int polls = r.sync.polls, d = r.d, h = r.h;
+    float *const act = BWD ? r.dact : r.act, *const Dx = r.Dx;
+    const float *const E = r.E, *const R = r.R;
+    const int32_t *const refs = r.refs, *const rels = r.rel, *const out_row = r.out_row;
+    const int keep = r.keep;
+    asm volatile("" ::"s"(counts), "s"(polls), "s"(d), "s"(h), "s"(act), "s"(refs), "s"(layers));
+    if (BWD) asm volatile("" ::"s"(Dx));
+    else asm volatile("" ::"s"(E), "s"(R), "s"(rels), "s"(out_row), "s"(keep));
+    int e = 0;
+    uint32_t start = r.start[0];
+#pragma unroll
+    for (int i = 1; i < TILE_PARTS; ++i)
+        if (at >= r.start[i] >> 8) { e = i; start = r.start[i]; }
+    const int l = start >> 4 & 15, type = start >> 2 & 3, kind = start & 3;
+    const bool second = kind & 1, pooled = !BWD && kind == TILE_POOLED;
+    const TilePart p = r.part[e];
+    const uint16_t* W = r.W[kind & 1][type];
+    const float* bias_of = r.bias[kind & 1][type];
+    float *const H = r.H[type], *const Z = r.Z[type], *const dH = r.dH[type];
+    const int before_tiles = r.tiles[l > 0 ? l - 1 : 0];
+    asm volatile("" ::"s"(p.M), "s"(p.row0), "s"(p.out0), "s"(p.inv_mem), "s"(W), "s"(H), "s"(before_tiles));
+    if (BWD) asm volatile("" ::"s"(dH));
+    else asm volatile("" ::"s"(bias_of), "s"(Z));
+    int32_t* const my_counts = l + 1 < layers ? counts + l * TILE_LAYER : nullptr;
+    const int32_t* const before_counts = counts + (l - 1) * TILE_LAYER;
+    if (BWD && kind == TILE_POOL_BWD) {
+        tc_pool_backward(r, p, (int)(at - (start >> 8)), l > 0 ? before_counts : nullptr, before_tiles, polls, my_counts, &waited);
+        return;
+    }
+    const int K = second ? h : d, N = second ? d : h, tiles_n = (N + 31) >> 5;
+    const int local = (int)(at - (start >> 8)), tile = (local & 7) * ((p.tiles + 7) >> 3) + (local >> 3);
+    if (tile >= p.tiles) return;
+    const int M = p.M, number = p.number + tile;
+    const int quo = p.by == 1 ? tile : (int)__umulhi((uint32_t)tile, p.inv_by), rem = tile - quo * p.by;
+    const int mt = p.m_major ? quo : rem, nt = p.m_major ? rem : quo, n0 = nt * 32;
+    // (a tile is mem members of a class that pools, with all their inputs, else 32 rows)
+    const int mem = p.mem, n_mem = p.n_mem, cls = p.cls;
+    auto row_of = [&](int lr, bool* ok) {          // row of the problem that row lr of the tile is (past the end: the last one)
+        const int j = lr * p.inv_mem >> 16, i = mt * mem + lr - j * mem;
+        *ok = j < cls && i < n_mem;
+        return *ok ? j * n_mem + i : M - 1;
+    };
+    const int nk = (K + 15) >> 4;
+    const bool two = nk > TC_AHEAD * TC_WAVES;      // chunks of k
+    auto block_of = [&](int c, int j) { return (c * TC_AHEAD + j) * TC_WAVES + wave; };
+    W += (size_t)nt * nk * WTILE + lane * 8;
+    bf16x8 b[TC_AHEAD][3];
+    auto issue_b = [&](int blk, int j) {
+        const uint16_t* from = W + (size_t)blk * WTILE;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) b[j][i] = piece_at(from, i);
+    };
+    // a lane fetches 16 bytes of rows lane / 4 and 16 + lane / 4 of a block, and multiplies 8 values of row lane % 32; a thread ends with two
+    // columns of a row
+    const bool related = !BWD && !second && p.rel0 >= 0, mapped = !BWD && second && out_row != nullptr;        // uniform
+    bool ok, mine_ok, inside;
+    const int m0 = row_of(lane >> 2, &ok), m1 = row_of(16 + (lane >> 2), &ok), mine = row_of(lane & 31, &mine_ok), k_in = (lane >> 5) * 8;
+    const int erow = tid >> 4, lc = (tid & 15) * 2, col = min(n0 + lc, N - 2);
+    const int em = row_of(erow, &inside), out_i = pooled ? min(mt * mem + erow, n_mem - 1) : em;
+    inside = inside && n0 + lc < N;
+    // (numbers of rows are read whether or not this layer has a use for them: all at once, from where there are some)
+    const int32_t *ref_of = refs + p.ref0, *rel_of = related ? rels + p.rel0 : ref_of, *out_of = mapped ? out_row + p.out0 : ref_of;
+    const int32_t ref0 = BWD ? 0 : ref_of[m0], ref1 = BWD ? 0 : ref_of[m1], my_rel = BWD ? 0 : rel_of[mine], my_out = out_of[mapped ? out_i : em];
+    // (added in the end; backward: a hidden value that the relu cut off has no gradient)
+    float2 bias = make_float2(0.f, 0.f), mask = make_float2(1.f, 1.f);
+    if (!BWD) bias = make_float2(bias_of[col], bias_of[col + 1]);
+    else if (!second) mask = *reinterpret_cast<const float2*>(H + (size_t)(p.row0 + em) * h + col);
+    // (blocks past the end: the last one again, not multiplied)
+#pragma unroll
+    for (int j = 0; j < TC_AHEAD; ++j) issue_b(min(block_of(0, j), nk - 1), j);
+    const float* arow[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int32_t ref = i ? ref1 : ref0, m = i ? m1 : m0;
+        if (BWD) {
+            arow[i] = second ? dH + (size_t)(p.row0 + m) * h : (p.pools ? r.dAtt + (size_t)(p.row0 + m) * d : act + (size_t)(p.out0 + m) * d);
+        } else {
+            const float* of_depths = ref >= 0 ? act + (size_t)ref * d : E + (size_t)(-1 - ref) * d;
+            arow[i] = second ? H + (size_t)(p.row0 + m) * h : of_depths;
+        }
+    }
+    const int orow = !second ? p.row0 + em : (BWD || mapped ? my_out : p.out0 + out_i);
+    // first layer: the relations' values; second: the inputs that a thread pools, once they are there
+    float4 rel[TC_AHEAD][2];
+    if (related) {
+        const float* row = R + (size_t)my_rel * d;
+#pragma unroll
+        for (int j = 0; j < TC_AHEAD; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) rel[j][i] = load_global4(row + min(min(block_of(0, j), nk - 1) * 16 + k_in + i * 4, K - 4));
+    }
+
+    const bool there = l > 0 ? tc_wait(before_counts, before_tiles, polls, &waited) : true;
+    const uint32_t at_a = lds_addr(lds) + wave * (TC_AHEAD * 2048);
+    const int unit = ((lane & 3) ^ tile_swizzle(lane >> 2)) * 4;
+    auto issue_a = [&](int blk, int j) {
+        const int k = min(blk * 16 + unit, K - 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) lds_load16_card(arow[i] + k, at_a + j * 2048 + i * 1024);
+    };
+#pragma unroll
+    for (int j = 0; j < TC_AHEAD; ++j)
+        if (block_of(0, j) < nk) issue_a(block_of(0, j), j);
+    if (pooled) {
+#pragma unroll
+        for (int j = 0; j < TILE_CARD; ++j) {
+            const float2 x = card_get2(Z + (size_t)(p.row0 + min(j, cls - 1) * n_mem + out_i) * d + col);
+            rel[j][0].x = x.x; rel[j][0].y = x.y;
+        }
+    }
+    if (BWD && second && p.pools) bias = card_get2(Dx + (size_t)(p.row0 + em) * d + col);       // what the pooling passes on directly
+    const bool copies = !BWD && !second && (keep || p.pools);        // uniform
+    floatx16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    const int f = tile_swizzle(lane & 15), u0 = (lane >> 5) * 2;
+    const unsigned char* rows = lds + wave * (TC_AHEAD * 2048) + (lane & 31) * 64;
+    auto chunk = [&](auto which, bool more) {
+        constexpr int c = decltype(which)::value;
+        asm volatile("" ::: "memory");
+        wait_vm<0>();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < TC_AHEAD; ++j) {
+            const int blk = block_of(c, j);
+            if (blk >= nk) break;                            // uniform
+            float4 v[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                v[i] = *reinterpret_cast<const float4*>(rows + j * 2048 + ((u0 + i) ^ f) * 16);
+                if (c == 0 && related) { v[i].x += rel[j][i].x; v[i].y += rel[j][i].y; v[i].z += rel[j][i].z; v[i].w += rel[j][i].w; }
+            }
+            // the rows as gathered, for who reads them later: a block of k by the tile whose turn it is
+            if (c == 0 && copies && (unsigned)blk % (unsigned)tiles_n == (unsigned)nt) {
+                float* to = Z + (size_t)(p.row0 + mine) * d + blk * 16 + k_in;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (mine_ok && blk * 16 + k_in + i * 4 < K) {
+                        if (p.pools) {
+                            card_put2(to + i * 4, v[i].x, v[i].y);
+                            card_put2(to + i * 4 + 2, v[i].z, v[i].w);
+                        } else {
+                            *reinterpret_cast<float4*>(to + i * 4) = v[i];
+                        }
+                    }
+            }
+            u32x4 hi, mi, lo;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                uint32_t w0, w1, w2;
+                split2(v[i].x, v[i].y, w0, w1, w2);
+                hi[2 * i] = w0; mi[2 * i] = w1; lo[2 * i] = w2;
+                split2(v[i].z, v[i].w, w0, w1, w2);
+                hi[2 * i + 1] = w0; mi[2 * i + 1] = w1; lo[2 * i + 1] = w2;
+            }
+            if (c == 0 && more && block_of(1, j) < nk) {     // (the values are read: their place is this wavefront's own)
+                asm volatile("" ::: "memory");
+                wait_lds();
+                issue_a(block_of(1, j), j);
+            }
+            const bf16x8 a[3] = {__builtin_bit_cast(bf16x8, hi), __builtin_bit_cast(bf16x8, mi), __builtin_bit_cast(bf16x8, lo)};
+            constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};      // smallest products first
+#pragma unroll
+            for (int t = 0; t < 6; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j][PB[t]], a[PA[t]], acc, 0, 0, 0);
+            if (c == 0 && more && block_of(1, j) < nk) issue_b(block_of(1, j), j);
+        }
+    };
+    chunk(std::integral_constant<int, 0>(), two);
+    if (two) chunk(std::integral_constant<int, 1>(), false);
+    __syncthreads();
+    float* all = reinterpret_cast<float*>(lds);
+    float* part = all + (wave * 32 + (lane & 31)) * TC_LD;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(part + i * 8 + (lane >> 5) * 4) = make_float4(acc[i * 4], acc[i * 4 + 1], acc[i * 4 + 2], acc[i * 4 + 3]);
+    __syncthreads();
+    float* own = all + erow * TC_LD + lc;
+    float o0 = 0.f, o1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < TC_WAVES; ++w) {
+        const float2 v = *reinterpret_cast<const float2*>(own + w * 32 * TC_LD);
+        o0 += v.x; o1 += v.y;
+    }
+    o0 += bias.x; o1 += bias.y;
+    if (BWD) {
+        o0 = mask.x > 0.f ? o0 : 0.f; o1 = mask.y > 0.f ? o1 : 0.f;
+    } else if (!second) {
+        o0 = fmaxf(o0, 0.f); o1 = fmaxf(o1, 0.f);
+    }
+    if (pooled) {
+        if (inside && keep) *reinterpret_cast<float2*>(r.Att + (size_t)(p.row0 + em) * d + n0 + lc) = make_float2(o0, o1);
+        *reinterpret_cast<float2*>(own) = make_float2(o0, o1);           // (read before by this thread only)
+        __syncthreads();
+        inside = erow < mem && mt * mem + erow < n_mem && n0 + lc < N;
+        float2 z[TILE_CARD];
+#pragma unroll
+        for (int j = 0; j < TILE_CARD; ++j) z[j] = *reinterpret_cast<const float2*>(all + (min(j, cls - 1) * mem + min(erow, mem - 1)) * TC_LD + lc);
+        auto pool = [&](auto logit, auto input) {
+            float mx = -INFINITY, den = 0.f, w[TILE_CARD], y = 0.f;
+#pragma unroll
+            for (int j = 0; j < TILE_CARD; ++j)
+                if (j < cls) mx = fmaxf(mx, logit(j));
+#pragma unroll
+            for (int j = 0; j < TILE_CARD; ++j)
+                if (j < cls) { w[j] = expf(logit(j) - mx); den += w[j]; }
+            const float inv = 1.f / den;
+#pragma unroll
+            for (int j = 0; j < TILE_CARD; ++j)
+                if (j < cls) y += w[j] * inv * input(j);
+            return y;
+        };
+        o0 = pool([&](int j) { return z[j].x; }, [&](int j) { return rel[j][0].x; });
+        o1 = pool([&](int j) { return z[j].y; }, [&](int j) { return rel[j][0].y; });
+    }
+    if (!there) o0 = o1 = NAN;
+    float* const rows_out = BWD ? dH : H;
+    if (inside) card_put2((second ? act + (size_t)orow * d : rows_out + (size_t)orow * h) + n0 + lc, o0, o1);
+    tc_through(r, my_counts, number, there);
+}
+
 // Forward layers of very few rows (a handful of queries): a matrix-vector product per row.  The time is reading
 // the weights once, 1.3 MB at d=400, h=800, spread over the chip: a wavefront takes ROWS_N output columns, reads
 // their weight rows (k-contiguous, a float4 per lane) and multiplies them with up to MR assembled rows held in
@@ -1544,6 +1874,61 @@ hipError_t launch_wgrad_group(const WgradArgs* problems, int count, hipStream_t 
     return hipGetLastError();
 }
 
+// The card holds 512 such tiles at a time, and what exceeds them starts a layer late; a launch a layer has larger tiles then, which the longer k is the sooner
+// pays.  Scoring and training, us, by launches and with at most 400, 512 and 800 tiles a layer here: 512 queries at d = 208, h = 416 76 and 181
+// against 66 and 171, 72 and 181, 73 and 182; at 400, 800 100 and 245 against 97 and 243, 102 and 246, 108 and 255.  With 400 and 260 (by
+// TILE_CHAIN_WORK): 320 at 512, 1024 99 and 245 against 103 and 252, 99 and 242; 160 at 512, 1024 90 and 204 against 87 and 206, 85 and 196.
+constexpr int TILE_CHAIN_MOST = 400, TILE_CHAIN_WORK = 400000;
+static_assert(TILE_CHAIN_MOST < GAVE_UP, "counts of tiles and of those that gave up in one word");
+bool tile_chain_fits(TileChain& r, const TileProblem (*problems)[TILE_PROBLEMS], const int* count, int n, bool backward) {
+    if (n < 1 || n > LEVEL_CHAIN || (r.d & 3) || (r.h & 3) || r.d < 128 || r.h < 128 || r.d > TILE_D || r.h > TILE_H) return false;
+    const auto up = [](int by) { return by == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + by - 1) / by); };
+    int blocks = 0, most = 0;
+    r.parts = r.layers = 0;
+    for (int l = 0; l < n; ++l) {
+        if (count[l] < 1) return false;
+        for (const int kind : {(int)TILE_POOL_BWD, (int)TILE_FIRST, (int)TILE_SECOND}) {
+            const bool pool_bwd = kind == TILE_POOL_BWD, second = kind == TILE_SECOND;
+            if (pool_bwd && !backward) continue;
+            const int N = second ? r.d : r.h, tiles_n = (N + 31) / 32, layer = r.layers;
+            int tiles = 0;
+            for (int q = 0; q < count[l]; ++q) {
+                const TileProblem& p = problems[l][q];
+                if (p.n < 1 || p.k < 1 || p.k > TILE_CARD || p.type < 0 || p.type > 2 || (long)p.n * p.k > 1 << 16) return false;
+                if (pool_bwd && p.k == 1) continue;
+                if (r.parts == TILE_PARTS) return false;
+                const bool pooled = second && !backward && p.k > 1;
+                TilePart& t = r.part[r.parts];
+                t.M = p.n * p.k; t.row0 = p.row0; t.ref0 = p.ref0; t.rel0 = p.rel0; t.out0 = p.out0; t.pools = p.k > 1;
+                t.cls = pooled || pool_bwd ? p.k : 1; t.mem = 32 / t.cls; t.n_mem = t.M / t.cls; t.inv_mem = (65535 + t.mem) / t.mem;
+                const int tiles_m = (t.n_mem + t.mem - 1) / t.mem;
+                t.m_major = t.M >= N;
+                t.by = pool_bwd ? r.d / 4 : (t.m_major ? tiles_n : tiles_m);
+                t.inv_by = up(t.by);
+                t.tiles = pool_bwd ? (t.n_mem * (r.d / 4) + TC_T - 1) / TC_T : tiles_m * tiles_n;
+                t.number = tiles;
+                r.start[r.parts++] = (uint32_t)blocks << 8 | layer << 4 | p.type << 2 | (pooled ? (int)TILE_POOLED : kind);
+                tiles += t.tiles;
+                blocks += (t.tiles + 7) / 8 * 8;
+                if (blocks >= 1 << 20) return false;
+            }
+            if (tiles == 0) continue;                // (a depth without intersections)
+            r.tiles[r.layers++] = tiles;
+            most = std::max(most, tiles);
+        }
+    }
+    for (int i = r.parts; i < TILE_PARTS; ++i) r.start[i] = 0xFFFFFFFFu;
+    r.blocks = blocks;
+    return most <= std::min(TILE_CHAIN_MOST, TILE_CHAIN_WORK / (r.d + r.h));
+}
+
+hipError_t launch_tile_chain(const TileChain& r, bool backward, hipStream_t s) {
+    if (!r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.blocks < 1 || r.parts < 1) return hipErrorInvalidValue;
+    if (backward) hipLaunchKernelGGL(tile_chain_kernel<true>, dim3(r.blocks), dim3(TC_T), 0, s, r);
+    else hipLaunchKernelGGL(tile_chain_kernel<false>, dim3(r.blocks), dim3(TC_T), 0, s, r);
+    return hipGetLastError();
+}
+
 bool gemm_takes_rows(int M, int K) {
     GemmArgs a;
     a.M = M; a.K = K;
@@ -1554,7 +1939,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) { return launch_gemm_gr
 
 hipError_t launch_weight_pieces(PieceJobs& J, hipStream_t s) {
     if (J.count <= 0 && J.copy_n <= 0) return hipSuccess;
-    if (J.count > PIECE_MAX_JOBS || J.copy_n < 0) return hipErrorInvalidValue;
+    if (J.count > PIECE_MAX_JOBS || J.copy_n < 0 || J.clear_n < 0 || (J.clear_n > 0 && !J.clear)) return hipErrorInvalidValue;
     int blocks = 0;
     for (int i = 0; i < J.count; ++i) {
         if ((J.job[i].C & 3) || J.job[i].R <= 0 || J.job[i].C <= 0) return hipErrorInvalidValue;

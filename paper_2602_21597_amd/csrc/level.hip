@@ -132,7 +132,6 @@ __device__ __forceinline__ void row_put(float* p, float4 v) {
 // counts[0]: numbers handed out, counts[1]: tiles through, counts[2 + l]: tiles of depth l through (but the last).  A wait that no
 // working card comes near ends all the same, after so many looks that they take seconds: the rows of its tile are not valid then, and its
 // depth's count goes past all tiles there are by GAVE_UP, so that whoever waits for that depth gives up at once too.
-constexpr int32_t GAVE_UP = 1 << 16;
 static_assert(LEVEL_CHAIN_TILES < GAVE_UP && (long)LEVEL_CHAIN_TILES * (GAVE_UP + 1) < INT32_MAX, "counts of tiles and of those that gave up in one word");
 // whether all tiles of that depth have their rows stored (known to the first thread, which looks)
 __device__ __forceinline__ bool wait_for_depth(const int32_t* through, int tiles, int polls) {

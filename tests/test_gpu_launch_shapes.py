@@ -332,6 +332,94 @@ def test_layers_of_a_few_rows_that_give_up_waiting():
     plan.free()
 
 
+# Passes of more rows, the layers of their depths in one launch of tiles a direction against a launch each, bit for bit: rows that fill no tile, widths that
+# fill no block of k and no column tile, one chunk of k and two, the widest and one more, classes of two to four inputs and one more, as many
+# depths as it takes and one more, depths of too many rows before those it takes and of too few behind them
+@pytest.mark.parametrize("d,h,B", [(400, 800, 40), (132, 260, 33), (512, 1024, 50), (128, 1024, 70), (404, 132, 90), (400, 800, 300), (208, 416, 900), (400, 800, 140),
+                                   (256, 512, 170), (516, 132, 60)])
+def test_layers_of_some_rows_in_one_launch(d, h, B):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    rng = np.random.default_rng(d + B)
+    N, R = 900, 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    inter = lambda k: ("i",) + tuple(proj() for _ in range(k))
+    kinds = [lambda: proj(), lambda: inter(2), lambda: proj(inter(3)), lambda: ("i", proj(), ("n", proj(proj()))), lambda: ("u", proj(), proj(proj())),
+             lambda: proj(("i", proj(), ("n", proj()))), lambda: inter(4)]
+    batches = [kinds[:6], kinds, kinds + [lambda: inter(5)], kinds[:2] + [lambda: proj(proj(proj(proj(proj()))))], kinds[2:4], [lambda: proj(proj())]]
+    eng = Engine(N, R, d, h, 8.0)
+    params = wl.make_params(N, R, d, h, 6)
+    cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    for some in batches:
+        qb = wl.batch_from_trees([some[i % len(some)]() for i in range(B)], [int(x) for x in rng.integers(0, N, B)])
+        out = []
+        for polls in (-1, 1 << 22):
+            assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
+            eng.bind_numpy(params)
+            plan = eng.plan(qb)
+            got = [eng.score(plan, cand).clone() for _ in range(3)]
+            assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+            got += [eng.forward_backward(plan, cand).clone()] + [eng.train_step(plan, cand).clone() for _ in range(2)]
+            got += [t[0].clone() for t in eng.tensors.values()] + [t[2].clone() for t in eng.tensors.values()]
+            plan.free()
+            out.append(got[2:])
+        assert all(torch.equal(a, b) for a, b in zip(*out)), [i for i, (a, b) in enumerate(zip(*out)) if not torch.equal(a, b)]
+
+
+# ... one that gives up waiting (here at once): the rows of its depths are nobody's results, parameters stay as they were, and the next call is refused
+def test_layers_of_some_rows_that_give_up_waiting():
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R, B = 900, 9, 60
+    rng = np.random.default_rng(3)
+    eng = Engine(N, R, 400, 800, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, 400, 800, 6))
+    qb = wl.batch_from_trees([("p", int(rng.integers(R)), ("p", 1, ("e", int(rng.integers(N))))) for _ in range(B)], [0] * B)
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
+    polls = lambda n: binding.lib().ngdb_debug_chain_polls(eng.ctx, n)
+    plan = eng.plan(qb)
+    want = eng.score(plan, cand).clone()
+    before = {k: t[0].clone() for k, t in eng.tensors.items()}
+    for call in (lambda: eng.score(plan, cand), lambda: eng.train_step(plan, cand)):
+        assert polls(0) == 0
+        got = call()
+        torch.cuda.synchronize()
+        assert got.numel() == 1 or bool((got == -np.inf).all())
+        with pytest.raises(binding.NgdbError) as e:
+            eng.score(plan, cand)
+        assert e.value.code == binding.ERR_HIP, str(e.value)
+        assert all(torch.equal(before[k], eng.tensors[k][0]) for k in before)
+    assert polls(1 << 22) == 0
+    assert torch.equal(eng.score(plan, cand), want)
+    plan.free()
+
+
+# ... captured: every replay as the call, with other launches of the kind in between
+def test_layers_of_some_rows_captured():
+    import torch
+    from paper_2602_21597_amd import Engine
+    N, R, B = 900, 9, 60
+    rng = np.random.default_rng(4)
+    eng = Engine(N, R, 260, 516, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, 260, 516, 6))
+    e = lambda: ("e", int(rng.integers(N)))
+    qb = wl.batch_from_trees([("p", 3, ("i", ("p", 1, e()), ("p", 2, e()))) for _ in range(B)], [0] * B)
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
+    plan, other = eng.plan(qb), eng.plan(qb.select(np.arange(25)))
+    want = eng.score(plan, cand).clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = eng.score(plan, cand)
+    for _ in range(4):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        eng.score(other, cand[:25].contiguous())
+    plan.free()
+    other.free()
+
+
 # ... captured, and so the launch of all depths of a small model, which copies the plan too: every replay as the call
 @pytest.mark.parametrize("d,h", [(400, 800), (36, 52)])
 def test_layers_of_a_few_rows_captured(d, h):
