@@ -298,11 +298,9 @@ int gslot_of(int t) { return t == T_PROJ ? 0 : (t == T_NEG ? 4 : 8); }
 struct FwdBytes;
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim);
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
-// Whether the weights are split once for a pass.  The two MLPs of the box family: from as many inputs of intersections on as some 800 queries have (a
-// step of 4096 boxes at d = 400, h = 800 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; a step of 512 takes the host as
-// long as the device, with and without, and its first pass two more allocations).
-constexpr int BOX_PIECES_FROM = 768;
-bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows >= BOX_PIECES_FROM; }
+// Whether the weights are split once for a pass.  The two MLPs of the box family: where there are intersections (a step of 4096 boxes at d = 400, h = 800
+// 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; few of them pass in one launch, tile_chain, which needs it).
+bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows > 0; }
 // bytes of the split weights: per MLP two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
 size_t weight_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
     if (!weights_split(c, hp)) return 0;
@@ -803,6 +801,127 @@ const Segment* riding_projection(const std::vector<Segment>& segs) {
     return joint ? proj : nullptr;
 }
 
+// Device memory the forward pass of the vector family writes: operator outputs by slot, and per
+// type the gathered first-layer inputs, the hidden rows and (intersections) the logits.
+// reclaim (forward-only passes, Sec. 4.3 eager reference counting): an output is kept only until
+// its consumer has run -- act holds n_f_rows storage rows addressed through the plan's f_row map,
+// and Z / H / Att hold the rows of one step at a time (sizes: forward_bytes).
+struct FwdSpace {
+    float* act;
+    float* Z[3];
+    float* H[3];
+    float* Att;
+    bool reclaim;
+    LevelSync sync;            // (the context's; without: depths in launches of their own)
+};
+FwdSpace ctx_space(const ngdb_ctx_t* c, bool reclaim = false) {
+    return FwdSpace{ptr<float>(c->act), {ptr<float>(c->Z[0]), ptr<float>(c->Z[1]), ptr<float>(c->Z[2])},
+                    {ptr<float>(c->H[0]), ptr<float>(c->H[1]), ptr<float>(c->H[2])}, ptr<float>(c->Att), reclaim, level_sync(c)};
+}
+// The operators of a depth as problems of one launch of tiles.  row0: of the type's buffers.  False: too many, or others.
+template <class Row0>
+bool tile_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, Row0 row0, bool backward, TileProblem* p, int* count) {
+    const HostPlan& hp = pl->hp;
+    LevelArgs la;
+    *count = 0;
+    if (level_problems(c, pl, segs, &la)) return false;
+    // (forward layers of a few rows are summed in another order: such a depth stays with its launches)
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    bool few[2] = {!backward, !backward}, any = false;
+    for (const Segment& sg : segs) {
+        if (box && sg.type == T_PROJ) continue;              // (has no MLP)
+        any = true;
+        few[0] = few[0] && gemm_takes_rows(sg.rows, c->cfg.d);
+        few[1] = few[1] && gemm_takes_rows(sg.rows, c->cfg.h);
+    }
+    if (any && (few[0] || few[1])) return false;
+    for (const Segment& sg : segs) {
+        const bool inter = sg.type == T_INTER;
+        if (sg.rows <= 0) continue;
+        for (int i = 0; i < (inter ? sg.g_hi - sg.g_lo : 1); ++i) {
+            if (*count == TILE_PROBLEMS) return false;
+            const int g = sg.g_lo + i, at = inter ? hp.g_mlp_base[g] - sg.mlp_base : 0;
+            if (inter && (hp.g_nin[g] < 2 || hp.g_nin[g] > TILE_CARD)) return false;
+            p[(*count)++] = TileProblem{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, row0(sg) + at, sg.ref_off + at, sg.rel_off,
+                                        inter ? hp.g_out_base[g] : sg.out_base};
+            if (!box || !inter) continue;
+            if (*count == TILE_PROBLEMS) return false;
+            p[*count] = p[*count - 1];                       // (the offsets of the same inputs through the second MLP)
+            p[(*count)++].type = T_NEG;
+        }
+    }
+    return true;
+}
+// (the box family's own buffers; null with vectors)
+void chain_boxes(const ngdb_ctx_t* c, TileChain* r) {
+    r->Ro = c->prm.Ro.p; r->off = ptr<float>(c->off); r->Gate = ptr<float>(c->Gate);
+    r->doff = ptr<float>(c->doff); r->dGate = ptr<float>(c->dGate); r->DxO = ptr<float>(c->DxO);
+}
+// All layers of the depths l0 .. l1 in one launch (tile_chain_kernel), where their launches would be small ones: the same sums in the same order.  False: not
+// such depths.
+bool tile_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, const FwdSpace& w, int l0, int l1, TileChain* r) {
+    const int n = l1 - l0 + 1;
+    if (!w.sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
+    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
+    int counts[LEVEL_CHAIN];
+    for (int i = 0; i < n; ++i)
+        if (!tile_problems(c, pl, pl->levels[l0 + i], [&](const Segment& sg) { return w.reclaim ? 0 : sg.mlp_base; }, false, problems[i], &counts[i])) return false;
+    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = w.reclaim ? 0 : 1;
+    if (!tile_chain_fits(*r, problems, counts, n, false, c->cfg.family == NGDB_FAMILY_BOX)) return false;
+    for (int t = 0; t < 3; ++t) {
+        const MlpRefs W = mlp_of(c->prm, t);
+        r->W[0][t] = c->wp[t][0]; r->W[1][t] = c->wp[t][1]; r->bias[0][t] = W.ba; r->bias[1][t] = W.bb;
+        r->Z[t] = w.Z[t]; r->H[t] = w.H[t]; r->dH[t] = nullptr;
+    }
+    r->E = er.rows; r->R = c->prm.R.p; r->refs = er.refs; r->rel = pl->d_rel; r->out_row = w.reclaim ? pl->d_f_row : nullptr;
+    r->act = w.act; r->Att = w.Att; r->dact = r->dAtt = r->Dx = nullptr;
+    chain_boxes(c, r);
+    r->sync = w.sync; r->chain = w.sync.counts + TILE_AT;
+    return true;
+}
+// ... of the backward pass, the deepest first.
+bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, int l0, int l1, TileChain* r) {
+    const LevelSync sync = level_sync(c);
+    const int n = l1 - l0 + 1;
+    if (!sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
+    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
+    int counts[LEVEL_CHAIN];
+    for (int i = 0; i < n; ++i)
+        if (!tile_problems(c, pl, pl->levels[l1 - i], [](const Segment& sg) { return sg.mlp_base; }, true, problems[i], &counts[i])) return false;
+    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = 0;
+    if (!tile_chain_fits(*r, problems, counts, n, true, c->cfg.family == NGDB_FAMILY_BOX)) return false;
+    for (int t = 0; t < 3; ++t) {
+        r->W[0][t] = c->wp[t][2]; r->W[1][t] = c->wp[t][3]; r->bias[0][t] = r->bias[1][t] = nullptr;
+        r->Z[t] = ptr<float>(c->Z[t]); r->H[t] = ptr<float>(c->H[t]); r->dH[t] = ptr<float>(c->dH[t]);
+    }
+    r->E = r->R = nullptr; r->refs = pl->d_in_gslot; r->rel = r->out_row = nullptr;
+    chain_boxes(c, r);
+    r->act = nullptr; r->Att = ptr<float>(c->Att); r->dact = ptr<float>(c->dact); r->dAtt = ptr<float>(c->dAtt); r->Dx = ptr<float>(c->Dx);
+    r->sync = sync; r->chain = sync.counts + TILE_AT + TILE_LAYERS * TILE_LAYER;
+    return true;
+}
+
+// The depths that one launch takes: the last that it can take (depths have fewer rows the deeper they are, as a rule) and those before it.
+// try_chain(l0, l1, r) lays r out.  False: none.
+struct ChainDepths { int from = 0, to = 0; };
+template <class Try>
+bool chain_depths(int n_levels, Try try_chain, TileChain* r, ChainDepths* out) {
+    for (out->to = n_levels; out->to > 0 && !try_chain(out->to, out->to, r);) --out->to;
+    if (out->to == 0) return false;
+    for (out->from = std::max(1, out->to - LEVEL_CHAIN + 1); out->from < out->to; ++out->from)
+        if (try_chain(out->from, out->to, r)) return true;
+    return try_chain(out->to, out->to, r);
+}
+int enqueue_chain(ngdb_ctx_t* c, const ngdb_plan_t* pl, const TileChain& chain, const ChainDepths& depths, bool backward, hipStream_t s) {
+    Timed tm(c, backward ? NGDB_TK_GEMM_BWD : NGDB_TK_GEMM_FWD, s);
+    HIPCHK(c, launch_tile_chain(chain, backward, c->cfg.family == NGDB_FAMILY_BOX, s));
+    double flop = 0.0;
+    for (int l = depths.from; l <= depths.to; ++l) flop += level_flop(c, pl->levels[l]);
+    tm.work(GEMM_SPLIT, flop);
+    c->chained = true;
+    return NGDB_OK;
+}
+
 // Box family, forward: projections are one elementwise launch per group; an intersection runs two
 // MLPs over its inputs (attention logits from the centres, gate inputs from the offsets), grouped
 // into one launch per layer, then the two pooling kernels.
@@ -810,8 +929,18 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     const int d = c->cfg.d, h = c->cfg.h;
     int rc_l = NGDB_OK;
     if (enqueue_levels(c, pl, false, [](LevelArgs&) {}, level_sync(c), s, &rc_l)) return rc_l;
+    TileChain chain;
+    ChainDepths depths;
+    const EntRows er{c->prm.E.p, pl->d_in_ref, nullptr, nullptr};
+    const FwdSpace w = ctx_space(c);
+    const bool in_one = chain_depths(pl->hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain(c, pl, er, w, l0, l1, r); }, &chain, &depths);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        if (in_one && l == depths.from) {
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s)) != NGDB_OK) return rc_l;
+            l = depths.to;
+            continue;
+        }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
             Timed tm(c, NGDB_TK_GEMM_FWD, s);
@@ -878,23 +1007,6 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     return NGDB_OK;
 }
 
-// Device memory the forward pass of the vector family writes: operator outputs by slot, and per
-// type the gathered first-layer inputs, the hidden rows and (intersections) the logits.
-// reclaim (forward-only passes, Sec. 4.3 eager reference counting): an output is kept only until
-// its consumer has run -- act holds n_f_rows storage rows addressed through the plan's f_row map,
-// and Z / H / Att hold the rows of one step at a time (sizes: forward_bytes).
-struct FwdSpace {
-    float* act;
-    float* Z[3];
-    float* H[3];
-    float* Att;
-    bool reclaim;
-    LevelSync sync;            // (the context's; without: depths in launches of their own)
-};
-FwdSpace ctx_space(const ngdb_ctx_t* c, bool reclaim = false) {
-    return FwdSpace{ptr<float>(c->act), {ptr<float>(c->Z[0]), ptr<float>(c->Z[1]), ptr<float>(c->Z[2])},
-                    {ptr<float>(c->H[0]), ptr<float>(c->H[1]), ptr<float>(c->H[2])}, ptr<float>(c->Att), reclaim, level_sync(c)};
-}
 // Bytes of the buffers of a forward-only pass, in the order act, Att, then Z and H per type.
 struct FwdBytes { size_t act, att, z[3], h[3]; };
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim) {
@@ -950,76 +1062,6 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
     return NGDB_OK;
 }
 
-// The operators of a depth as problems of one launch of tiles.  row0: of the type's buffers.  False: too many, or others.
-template <class Row0>
-bool tile_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, Row0 row0, bool backward, TileProblem* p, int* count) {
-    const HostPlan& hp = pl->hp;
-    LevelArgs la;
-    *count = 0;
-    if (level_problems(c, pl, segs, &la)) return false;
-    // (forward layers of a few rows are summed in another order: such a depth stays with its launches)
-    bool few[2] = {!backward, !backward};
-    for (const Segment& sg : segs) {
-        few[0] = few[0] && gemm_takes_rows(sg.rows, c->cfg.d);
-        few[1] = few[1] && gemm_takes_rows(sg.rows, c->cfg.h);
-    }
-    if (few[0] || few[1]) return false;
-    for (const Segment& sg : segs) {
-        const bool inter = sg.type == T_INTER;
-        if (sg.rows <= 0) continue;
-        for (int i = 0; i < (inter ? sg.g_hi - sg.g_lo : 1); ++i) {
-            if (*count == TILE_PROBLEMS) return false;
-            const int g = sg.g_lo + i, at = inter ? hp.g_mlp_base[g] - sg.mlp_base : 0;
-            if (inter && (hp.g_nin[g] < 2 || hp.g_nin[g] > TILE_CARD)) return false;
-            p[(*count)++] = TileProblem{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, row0(sg) + at, sg.ref_off + at, sg.rel_off,
-                                        inter ? hp.g_out_base[g] : sg.out_base};
-        }
-    }
-    return true;
-}
-// All layers of the depths l0 .. l1 in one launch (tile_chain_kernel), where their launches would be small ones: the same sums in the same order.  False: not
-// such depths.
-bool tile_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, const FwdSpace& w, int l0, int l1, TileChain* r) {
-    const int n = l1 - l0 + 1;
-    if (!w.sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
-    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
-    int counts[LEVEL_CHAIN];
-    for (int i = 0; i < n; ++i)
-        if (!tile_problems(c, pl, pl->levels[l0 + i], [&](const Segment& sg) { return w.reclaim ? 0 : sg.mlp_base; }, false, problems[i], &counts[i])) return false;
-    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = w.reclaim ? 0 : 1;
-    if (!tile_chain_fits(*r, problems, counts, n, false)) return false;
-    for (int t = 0; t < 3; ++t) {
-        const MlpRefs W = mlp_of(c->prm, t);
-        r->W[0][t] = c->wp[t][0]; r->W[1][t] = c->wp[t][1]; r->bias[0][t] = W.ba; r->bias[1][t] = W.bb;
-        r->Z[t] = w.Z[t]; r->H[t] = w.H[t]; r->dH[t] = nullptr;
-    }
-    r->E = er.rows; r->R = c->prm.R.p; r->refs = er.refs; r->rel = pl->d_rel; r->out_row = w.reclaim ? pl->d_f_row : nullptr;
-    r->act = w.act; r->Att = w.Att; r->dact = r->dAtt = r->Dx = nullptr;
-    r->sync = w.sync; r->chain = w.sync.counts + TILE_AT;
-    return true;
-}
-// ... of the backward pass, the deepest first.
-bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, int l0, TileChain* r) {
-    const HostPlan& hp = pl->hp;
-    const LevelSync sync = level_sync(c);
-    const int n = hp.n_levels - l0 + 1;
-    if (!sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
-    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
-    int counts[LEVEL_CHAIN];
-    for (int i = 0; i < n; ++i)
-        if (!tile_problems(c, pl, pl->levels[hp.n_levels - i], [](const Segment& sg) { return sg.mlp_base; }, true, problems[i], &counts[i])) return false;
-    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = 0;
-    if (!tile_chain_fits(*r, problems, counts, n, true)) return false;
-    for (int t = 0; t < 3; ++t) {
-        r->W[0][t] = c->wp[t][2]; r->W[1][t] = c->wp[t][3]; r->bias[0][t] = r->bias[1][t] = nullptr;
-        r->Z[t] = ptr<float>(c->Z[t]); r->H[t] = ptr<float>(c->H[t]); r->dH[t] = ptr<float>(c->dH[t]);
-    }
-    r->E = r->R = nullptr; r->refs = pl->d_in_gslot; r->rel = r->out_row = nullptr;
-    r->act = nullptr; r->Att = ptr<float>(c->Att); r->dact = ptr<float>(c->dact); r->dAtt = ptr<float>(c->dAtt); r->Dx = ptr<float>(c->Dx);
-    r->sync = sync; r->chain = sync.counts + TILE_AT + TILE_LAYERS * TILE_LAYER;
-    return true;
-}
-
 // forward over the plan's frontiers; results in w.act.  The type segments of one
 // depth are independent: they share one grouped launch per MLP layer.
 int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hipStream_t s, const FwdSpace& w) {
@@ -1034,22 +1076,13 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
     int rc_l = NGDB_OK;
     if (enqueue_levels(c, pl, false, forward_level, w.sync, s, &rc_l)) return rc_l;
     TileChain chain;
-    // (depths have fewer rows the deeper they are, as a rule: the last that it can take, and those before it)
-    int chain_to = pl->hp.n_levels;
-    while (chain_to > 0 && !tile_chain(c, pl, er, w, chain_to, chain_to, &chain)) --chain_to;
-    int chain_from = std::max(1, chain_to - LEVEL_CHAIN + 1);
-    while (chain_from < chain_to && !tile_chain(c, pl, er, w, chain_from, chain_to, &chain)) ++chain_from;
-    if (chain_to > 0 && chain_from == chain_to) (void)tile_chain(c, pl, er, w, chain_to, chain_to, &chain);
+    ChainDepths depths;
+    const bool in_one = chain_depths(pl->hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain(c, pl, er, w, l0, l1, r); }, &chain, &depths);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
-        if (chain_to > 0 && l == chain_from) {
-            Timed tm(c, NGDB_TK_GEMM_FWD, s);
-            HIPCHK(c, launch_tile_chain(chain, false, s));
-            double flop = 0.0;
-            for (; l <= chain_to; ++l) flop += level_flop(c, pl->levels[l]);
-            tm.work(GEMM_SPLIT, flop);
-            c->chained = true;
-            --l;
+        if (in_one && l == depths.from) {
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s)) != NGDB_OK) return rc_l;
+            l = depths.to;
             continue;
         }
         LevelArgs la;
@@ -1195,20 +1228,16 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     int rc_l = NGDB_OK;
     const bool chained = enqueue_levels(c, pl, true, backward_level, level_sync(c), s, &rc_l);
     if (rc_l != NGDB_OK) return rc_l;
-    int l_next = chained ? 0 : hp.n_levels;
     TileChain chain;
-    int chain_from = std::max(1, hp.n_levels - LEVEL_CHAIN + 1);
-    while (l_next && chain_from <= hp.n_levels && !tile_chain_backward(c, pl, chain_from, &chain)) ++chain_from;
-    if (l_next && chain_from <= hp.n_levels) {
-        Timed tm(c, NGDB_TK_GEMM_BWD, s);
-        HIPCHK(c, launch_tile_chain(chain, true, s));
-        double flop = 0.0;
-        for (; l_next >= chain_from; --l_next) flop += level_flop(c, pl->levels[l_next]);
-        tm.work(GEMM_SPLIT, flop);
-        c->chained = true;
-    }
-    for (int l = l_next; l >= 1; --l) {
+    ChainDepths depths;
+    const bool in_one = !chained && chain_depths(hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain_backward(c, pl, l0, l1, r); }, &chain, &depths);
+    for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        if (in_one && l == depths.to) {
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s)) != NGDB_OK) return rc_l;
+            l = depths.from;
+            continue;
+        }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
             backward_level(la);
@@ -1282,8 +1311,16 @@ int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, Wg
     int rc_l = NGDB_OK;
     const bool chained = enqueue_levels(c, pl, true, [](LevelArgs&) {}, level_sync(c), s, &rc_l);
     if (rc_l != NGDB_OK) return rc_l;
+    TileChain chain;
+    ChainDepths depths;
+    const bool in_one = !chained && chain_depths(hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain_backward(c, pl, l0, l1, r); }, &chain, &depths);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
+        if (in_one && l == depths.to) {
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s)) != NGDB_OK) return rc_l;
+            l = depths.from;
+            continue;
+        }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
             Timed tm(c, NGDB_TK_GEMM_BWD, s);

@@ -412,14 +412,15 @@ hipError_t launch_rows_chain(RowsChain& r, hipStream_t s);
 // All layers of a pass over up to some hundred rows a depth in one launch (gemm.hip: tile_chain_kernel).  A problem is a projection or negation
 // group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its type's buffers, references ref0 + ... (and
 // relations rel0 + ..., -1: none), outputs out0 + i.  Limits: inputs of an intersection, input values and hidden values of a row, problems of a depth.
-constexpr int TILE_CARD = 4, TILE_D = 512, TILE_H = 1024, TILE_PROBLEMS = 6, TILE_PARTS = 32;
+constexpr int TILE_CARD = 4, TILE_D = 512, TILE_H = 1024, TILE_PROBLEMS = 8, TILE_PARTS = 32;
 // words of counts, zero before the launch: of the layers of a forward pass (two a depth), then of a backward one (up to three a depth)
 constexpr int TILE_LINES = 16, TILE_STRIDE = 32, TILE_LAYER = TILE_LINES * TILE_STRIDE;
 constexpr int TILE_LAYERS = 2 * LEVEL_CHAIN, TILE_LAYERS_BWD = 3 * LEVEL_CHAIN, TILE_SYNC = (TILE_LAYERS + TILE_LAYERS_BWD) * TILE_LAYER;
 struct TileProblem { int type, k, n, row0, ref0, rel0, out0; };
 // What the tiles of a part do.  Backward: the gradient of the hidden rows (from that of the outputs), of the inputs (from that of the
-// hidden rows), and before both the pooling of a class.
-enum TileKind { TILE_FIRST = 0, TILE_SECOND = 1, TILE_POOLED = 3, TILE_POOL_BWD = 2 };
+// hidden rows), and before both the pooling of a class.  Boxes: intersections once for the centres (type 1) and once for the offsets (type 2: pooled by the
+// least input times the gate), projections (type 0) coordinate by coordinate, in the first layer of their depth.
+enum TileKind { TILE_FIRST = 0, TILE_SECOND = 1, TILE_POOLED = 3, TILE_PLAIN = 2 };
 // The tiles of a problem in one layer: mt = quotient of a tile's number by `by` (the row tile) or its remainder, mem members each; number: of its first tile
 // in the layer.  inv_*: what a product's upper half divides by.
 struct TilePart { int M, row0, ref0, rel0, out0, number, tiles, by; uint32_t inv_by; int m_major, mem, inv_mem, n_mem, cls, pools; };
@@ -436,13 +437,15 @@ struct TileChain {
     const int32_t *refs, *rel, *out_row;            // out_row: row of act per output (null: itself); backward: refs = row of dact per reference
     float *act, *Att;
     float *dact, *dAtt, *Dx, *dH[3];                // backward
+    const float* Ro;                                // boxes: relations and the same buffers for the offsets
+    float *off, *Gate, *doff, *dGate, *DxO;
     LevelSync sync;                                 // (its counts are not used)
     int32_t* chain;                                 // a word of TILE_LINES on lines of their own per layer
     int blocks = 0;
 };
 // Lays out the tiles of n depths in the order given (count[l] problems each).  False: no such launch, or so many tiles that one is not the better way.
-bool tile_chain_fits(TileChain& r, const TileProblem (*p)[TILE_PROBLEMS], const int* count, int n, bool backward);
-hipError_t launch_tile_chain(const TileChain& r, bool backward, hipStream_t s);
+bool tile_chain_fits(TileChain& r, const TileProblem (*p)[TILE_PROBLEMS], const int* count, int n, bool backward, bool box);
+hipError_t launch_tile_chain(const TileChain& r, bool backward, bool box, hipStream_t s);
 bool levels_chain(const LevelArgs* a, int n);
 hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, const PlanCopy& copy, hipStream_t s);
 

@@ -1222,6 +1222,8 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
 // Scoring and training with 8 negatives, by launches and like this, us: 40 queries at d = 400, h = 800 75 and 162 against 64 and 137, 160
 // queries 84 and 186 against 76 and 175, 320 95 and 222 against 91 and 216; 40 at 208, 416 63 and 141 against 50 and 108, 160 70 and 155 against 52 and 123, 512 76
 // and 181 against 66 and 171; 40 at 512, 1024 77 and 177 against 69 and 157.
+// Boxes, whose projections are parts of their own: 40 queries at d = 300, h = 500 49 and 108 against 40 and 90, 160 56 and 118 against 43 and 102, 80 at 400, 800 58 and
+// 120 against 44 and 101, 160 at 160, 320 56 and 109 against 34 and 87.
 constexpr int TC_WAVES = 8, TC_T = TC_WAVES * 64, TC_AHEAD = 4, TC_LD = 36;
 static_assert(TC_AHEAD * TC_WAVES * 16 >= TILE_D && 2 * TC_AHEAD * TC_WAVES * 16 >= TILE_H, "relations in registers; two chunks at most");
 // Waits until all tiles of the layer before are through (each counts on one of its words); every thread learns whether they are.
@@ -1254,7 +1256,8 @@ __device__ __forceinline__ void tc_through(const TileChain& r, int32_t* counts, 
     }
     if (counts) __hip_atomic_fetch_add(counts + number % TILE_LINES * TILE_STRIDE, there ? 1 : GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A tile of a class's pooling, backward (pool.h: attention<true>): a thread takes four coordinates of a member.
+// A tile of a class's pooling, backward (pool.h: attention<true>, and smallest<true> for the offsets of boxes): a thread takes four coordinates of a member.
+template <bool OFFSETS>
 __device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TilePart& p, int tile, const int32_t* before_counts, int before_tiles, int polls,
                                                  int32_t* counts, int* waited) {
     if (tile >= p.tiles) return;
@@ -1265,13 +1268,33 @@ __device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TileP
 #pragma unroll
     for (int j = 0; j < TILE_CARD; ++j) {
         const size_t at = (size_t)(p.row0 + min(j, k - 1) * p.n_mem + i) * d + c;
-        a[j] = load_global4(r.Att + at);
-        x[j] = load_global4(r.Z[1] + at);
+        a[j] = load_global4((OFFSETS ? r.Gate : r.Att) + at);
+        x[j] = load_global4(r.Z[OFFSETS ? 2 : 1] + at);
     }
     const bool there = before_counts ? tc_wait(before_counts, before_tiles, polls, waited) : true;
-    const float* from = r.dact + (size_t)(p.out0 + i) * d + c;
+    const float* from = (OFFSETS ? r.doff : r.dact) + (size_t)(p.out0 + i) * d + c;
     const float2 g0 = card_get2(from), g1 = card_get2(from + 2);
     auto one = [&](float g, auto of) {
+        if (OFFSETS) {
+            float mean = 0.f, mn = INFINITY;
+            int arg = 0;
+#pragma unroll
+            for (int j = 0; j < TILE_CARD; ++j) {
+                if (j >= k) break;
+                mean += of(a[j]);
+                if (of(x[j]) < mn) {                         // strict: equal offsets keep the lower input
+                    mn = of(x[j]);
+                    arg = j;
+                }
+            }
+            const float gate = sigmoid_f(mean / (float)k), dpre = g * mn * gate * (1.f - gate) / (float)k;
+#pragma unroll
+            for (int j = 0; j < TILE_CARD; ++j) {
+                of(a[j]) = there ? dpre : NAN;
+                of(x[j]) = j == arg ? g * gate : 0.f;
+            }
+            return;
+        }
         float mx = -INFINITY, den = 0.f, tall = 0.f;
 #pragma unroll
         for (int j = 0; j < TILE_CARD; ++j)
@@ -1299,15 +1322,64 @@ __device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TileP
     for (int j = 0; j < TILE_CARD; ++j) {
         if (j >= k || !inside) break;
         const size_t at = (size_t)(p.row0 + j * p.n_mem + i) * d + c;
-        card_put2(r.dAtt + at, a[j].x, a[j].y);
-        card_put2(r.dAtt + at + 2, a[j].z, a[j].w);
-        card_put2(r.Dx + at, x[j].x, x[j].y);
-        card_put2(r.Dx + at + 2, x[j].z, x[j].w);
+        float *const da = (OFFSETS ? r.dGate : r.dAtt) + at, *const dx = (OFFSETS ? r.DxO : r.Dx) + at;
+        card_put2(da, a[j].x, a[j].y);
+        card_put2(da + 2, a[j].z, a[j].w);
+        card_put2(dx, x[j].x, x[j].y);
+        card_put2(dx + 2, x[j].z, x[j].w);
+    }
+    tc_through(r, counts, p.number + tile, there);
+}
+// A tile of the projections of boxes (box.hip: proj_body), likewise.
+template <bool BWD>
+__device__ __forceinline__ void tc_box_projection(const TileChain& r, const TilePart& p, int tile, const int32_t* before_counts, int before_tiles, int polls,
+                                                  int32_t* counts, int* waited) {
+    if (tile >= p.tiles) return;
+    const int d = r.d, d4 = d >> 2, t = tile * TC_T + (int)threadIdx.x;
+    const bool inside = t < p.n_mem * d4;
+    const int i = min((int)__umulhi((uint32_t)t, p.inv_by), p.n_mem - 1), c = min(t - i * d4, d4 - 1) * 4;
+    const int32_t ref = r.refs[p.ref0 + i];                  // (backward: the row of the input's gradient)
+    const size_t out = (size_t)(p.out0 + i) * d + c;
+    auto get = [](const float* from) {
+        const float2 a = card_get2(from), b = card_get2(from + 2);
+        return make_float4(a.x, a.y, b.x, b.y);
+    };
+    float4 x, o = make_float4(0.f, 0.f, 0.f, 0.f), rc = o, ro = o;
+    if (!BWD) {
+        const size_t rel = (size_t)r.rel[p.rel0 + i] * d + c;
+        rc = load_global4(r.R + rel);
+        ro = load_global4(r.Ro + rel);
+    }
+    const bool there = before_counts ? tc_wait(before_counts, before_tiles, polls, waited) : true;
+    float *to_x, *to_o;
+    if (BWD) {
+        x = get(r.dact + out);
+        o = get(r.doff + out);
+        to_x = r.dact + (size_t)ref * d + c;
+        to_o = r.doff + (size_t)ref * d + c;
+    } else {
+        if (ref >= 0) {
+            x = get(r.act + (size_t)ref * d + c);
+            o = get(r.off + (size_t)ref * d + c);
+        } else {
+            x = load_global4(r.E + (size_t)(-1 - ref) * d + c);
+        }
+        x.x += rc.x; x.y += rc.y; x.z += rc.z; x.w += rc.w;
+        o.x += fmaxf(ro.x, 0.f); o.y += fmaxf(ro.y, 0.f); o.z += fmaxf(ro.z, 0.f); o.w += fmaxf(ro.w, 0.f);
+        to_x = r.act + out;
+        to_o = r.off + out;
+    }
+    if (!there) x = o = make_float4(NAN, NAN, NAN, NAN);
+    if (inside) {
+        card_put2(to_x, x.x, x.y);
+        card_put2(to_x + 2, x.z, x.w);
+        card_put2(to_o, o.x, o.y);
+        card_put2(to_o + 2, o.z, o.w);
     }
     tc_through(r, counts, p.number + tile, there);
 }
 // BWD: the reverse.  An intersection's pooling is a layer of its own, four coordinates of a member a thread, ahead of its depth's other two.
-template <bool BWD>
+template <bool BWD, bool BOX>
 __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[TC_WAVES * TC_AHEAD * 2048];
     __shared__ int waited;
@@ -1317,12 +1389,13 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
     const uint32_t at = blockIdx.x;
     int32_t* const counts = r.chain;
     const int polls = r.sync.polls, d = r.d, h = r.h;
-    float *const act = BWD ? r.dact : r.act, *const Dx = r.Dx;
+    float *const act1 = BWD ? r.dact : r.act, *const Dx1 = r.Dx, *const act2 = BWD ? r.doff : r.off, *const Dx2 = r.DxO;
     const float *const E = r.E, *const R = r.R;
     const int32_t *const refs = r.refs, *const rels = r.rel, *const out_row = r.out_row;
     const int keep = r.keep;
-    asm volatile("" ::"s"(counts), "s"(polls), "s"(d), "s"(h), "s"(act), "s"(refs), "s"(layers));
-    if (BWD) asm volatile("" ::"s"(Dx));
+    asm volatile("" ::"s"(counts), "s"(polls), "s"(d), "s"(h), "s"(act1), "s"(refs), "s"(layers));
+    if (BOX) asm volatile("" ::"s"(act2), "s"(Dx2));
+    if (BWD) asm volatile("" ::"s"(Dx1));
     else asm volatile("" ::"s"(E), "s"(R), "s"(rels), "s"(out_row), "s"(keep));
     int e = 0;
     uint32_t start = r.start[0];
@@ -1341,10 +1414,16 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
     else asm volatile("" ::"s"(bias_of), "s"(Z));
     int32_t* const my_counts = l + 1 < layers ? counts + l * TILE_LAYER : nullptr;
     const int32_t* const before_counts = counts + (l - 1) * TILE_LAYER;
-    if (BWD && kind == TILE_POOL_BWD) {
-        tc_pool_backward(r, p, (int)(at - (start >> 8)), l > 0 ? before_counts : nullptr, before_tiles, polls, my_counts, &waited);
+    if ((BWD || BOX) && kind == TILE_PLAIN) {
+        const int tile = (int)(at - (start >> 8));
+        const int32_t* const words = l > 0 ? before_counts : nullptr;
+        if (BOX && type == 0) tc_box_projection<BWD>(r, p, tile, words, before_tiles, polls, my_counts, &waited);
+        else if (BOX && type == 2) tc_pool_backward<true>(r, p, tile, words, before_tiles, polls, my_counts, &waited);
+        else if (BWD) tc_pool_backward<false>(r, p, tile, words, before_tiles, polls, my_counts, &waited);
         return;
     }
+    const bool offsets = BOX && type == 2;
+    float *const act = offsets ? act2 : act1, *const Dx = offsets ? Dx2 : Dx1;
     const int K = second ? h : d, N = second ? d : h, tiles_n = (N + 31) >> 5;
     const int local = (int)(at - (start >> 8)), tile = (local & 7) * ((p.tiles + 7) >> 3) + (local >> 3);
     if (tile >= p.tiles) return;
@@ -1391,7 +1470,7 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
     for (int i = 0; i < 2; ++i) {
         const int32_t ref = i ? ref1 : ref0, m = i ? m1 : m0;
         if (BWD) {
-            arow[i] = second ? dH + (size_t)(p.row0 + m) * h : (p.pools ? r.dAtt + (size_t)(p.row0 + m) * d : act + (size_t)(p.out0 + m) * d);
+            arow[i] = second ? dH + (size_t)(p.row0 + m) * h : (p.pools ? (offsets ? r.dGate : r.dAtt) + (size_t)(p.row0 + m) * d : act + (size_t)(p.out0 + m) * d);
         } else {
             const float* of_depths = ref >= 0 ? act + (size_t)ref * d : E + (size_t)(-1 - ref) * d;
             arow[i] = second ? H + (size_t)(p.row0 + m) * h : of_depths;
@@ -1507,7 +1586,7 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
         o0 = fmaxf(o0, 0.f); o1 = fmaxf(o1, 0.f);
     }
     if (pooled) {
-        if (inside && keep) *reinterpret_cast<float2*>(r.Att + (size_t)(p.row0 + em) * d + n0 + lc) = make_float2(o0, o1);
+        if (inside && keep) *reinterpret_cast<float2*>((offsets ? r.Gate : r.Att) + (size_t)(p.row0 + em) * d + n0 + lc) = make_float2(o0, o1);
         *reinterpret_cast<float2*>(own) = make_float2(o0, o1);           // (read before by this thread only)
         __syncthreads();
         inside = erow < mem && mt * mem + erow < n_mem && n0 + lc < N;
@@ -1515,6 +1594,16 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
 #pragma unroll
         for (int j = 0; j < TILE_CARD; ++j) z[j] = *reinterpret_cast<const float2*>(all + (min(j, cls - 1) * mem + min(erow, mem - 1)) * TC_LD + lc);
         auto pool = [&](auto logit, auto input) {
+            if (offsets) {
+                float mean = 0.f, mn = INFINITY;
+#pragma unroll
+                for (int j = 0; j < TILE_CARD; ++j)
+                    if (j < cls) {
+                        mean += logit(j);
+                        if (input(j) < mn) mn = input(j);
+                    }
+                return mn * sigmoid_f(mean / (float)cls);
+            }
             float mx = -INFINITY, den = 0.f, w[TILE_CARD], y = 0.f;
 #pragma unroll
             for (int j = 0; j < TILE_CARD; ++j)
@@ -1878,36 +1967,40 @@ hipError_t launch_wgrad_group(const WgradArgs* problems, int count, hipStream_t 
 // pays.  Scoring and training, us, by launches and with at most 400, 512 and 800 tiles a layer here: 512 queries at d = 208, h = 416 76 and 181
 // against 66 and 171, 72 and 181, 73 and 182; at 400, 800 100 and 245 against 97 and 243, 102 and 246, 108 and 255.  With 400 and 260 (by
 // TILE_CHAIN_WORK): 320 at 512, 1024 99 and 245 against 103 and 252, 99 and 242; 160 at 512, 1024 90 and 204 against 87 and 206, 85 and 196.
-constexpr int TILE_CHAIN_MOST = 400, TILE_CHAIN_WORK = 400000;
+// Boxes (scoring and training at 300, 500): 512 of them with at most 300 to 400 tiles 64 and 149 against 61 and 145, with 500 151; 1024, whose layer of 306
+// tiles 400 lets in, 79 and 170.5 against 74 and 174.
+constexpr int TILE_CHAIN_MOST = 400, TILE_CHAIN_MOST_BOX = 300, TILE_CHAIN_WORK = 400000;
 static_assert(TILE_CHAIN_MOST < GAVE_UP, "counts of tiles and of those that gave up in one word");
-bool tile_chain_fits(TileChain& r, const TileProblem (*problems)[TILE_PROBLEMS], const int* count, int n, bool backward) {
+bool tile_chain_fits(TileChain& r, const TileProblem (*problems)[TILE_PROBLEMS], const int* count, int n, bool backward, bool box) {
     if (n < 1 || n > LEVEL_CHAIN || (r.d & 3) || (r.h & 3) || r.d < 128 || r.h < 128 || r.d > TILE_D || r.h > TILE_H) return false;
     const auto up = [](int by) { return by == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + by - 1) / by); };
     int blocks = 0, most = 0;
     r.parts = r.layers = 0;
     for (int l = 0; l < n; ++l) {
         if (count[l] < 1) return false;
-        for (const int kind : {(int)TILE_POOL_BWD, (int)TILE_FIRST, (int)TILE_SECOND}) {
-            const bool pool_bwd = kind == TILE_POOL_BWD, second = kind == TILE_SECOND;
-            if (pool_bwd && !backward) continue;
+        // layers of a depth: forward first and second, backward pooling, gradient of the hidden rows, of the inputs
+        for (int layer_of = backward ? 0 : 1; layer_of < 3; ++layer_of) {
+            const bool second = layer_of == 2, plain_turn = layer_of == (backward ? 0 : 1);
             const int N = second ? r.d : r.h, tiles_n = (N + 31) / 32, layer = r.layers;
             int tiles = 0;
             for (int q = 0; q < count[l]; ++q) {
                 const TileProblem& p = problems[l][q];
                 if (p.n < 1 || p.k < 1 || p.k > TILE_CARD || p.type < 0 || p.type > 2 || (long)p.n * p.k > 1 << 16) return false;
-                if (pool_bwd && p.k == 1) continue;
+                const bool projection = box && p.type == 0, plain = projection || layer_of == 0;
+                if (projection ? !plain_turn : layer_of == 0 && p.k == 1) continue;
                 if (r.parts == TILE_PARTS) return false;
                 const bool pooled = second && !backward && p.k > 1;
                 TilePart& t = r.part[r.parts];
                 t.M = p.n * p.k; t.row0 = p.row0; t.ref0 = p.ref0; t.rel0 = p.rel0; t.out0 = p.out0; t.pools = p.k > 1;
-                t.cls = pooled || pool_bwd ? p.k : 1; t.mem = 32 / t.cls; t.n_mem = t.M / t.cls; t.inv_mem = (65535 + t.mem) / t.mem;
+                t.cls = pooled || plain ? p.k : 1; t.mem = 32 / t.cls; t.n_mem = t.M / t.cls; t.inv_mem = (65535 + t.mem) / t.mem;
                 const int tiles_m = (t.n_mem + t.mem - 1) / t.mem;
                 t.m_major = t.M >= N;
-                t.by = pool_bwd ? r.d / 4 : (t.m_major ? tiles_n : tiles_m);
+                t.by = plain ? r.d / 4 : (t.m_major ? tiles_n : tiles_m);
                 t.inv_by = up(t.by);
-                t.tiles = pool_bwd ? (t.n_mem * (r.d / 4) + TC_T - 1) / TC_T : tiles_m * tiles_n;
+                t.tiles = plain ? (t.n_mem * (r.d / 4) + TC_T - 1) / TC_T : tiles_m * tiles_n;
                 t.number = tiles;
-                r.start[r.parts++] = (uint32_t)blocks << 8 | layer << 4 | p.type << 2 | (pooled ? (int)TILE_POOLED : kind);
+                const int kind = plain ? TILE_PLAIN : (pooled ? TILE_POOLED : (second ? TILE_SECOND : TILE_FIRST));
+                r.start[r.parts++] = (uint32_t)blocks << 8 | layer << 4 | p.type << 2 | kind;
                 tiles += t.tiles;
                 blocks += (t.tiles + 7) / 8 * 8;
                 if (blocks >= 1 << 20) return false;
@@ -1919,13 +2012,16 @@ bool tile_chain_fits(TileChain& r, const TileProblem (*problems)[TILE_PROBLEMS],
     }
     for (int i = r.parts; i < TILE_PARTS; ++i) r.start[i] = 0xFFFFFFFFu;
     r.blocks = blocks;
-    return most <= std::min(TILE_CHAIN_MOST, TILE_CHAIN_WORK / (r.d + r.h));
+    return most <= std::min(box ? TILE_CHAIN_MOST_BOX : TILE_CHAIN_MOST, TILE_CHAIN_WORK / (r.d + r.h));
 }
 
-hipError_t launch_tile_chain(const TileChain& r, bool backward, hipStream_t s) {
+hipError_t launch_tile_chain(const TileChain& r, bool backward, bool box, hipStream_t s) {
     if (!r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.blocks < 1 || r.parts < 1) return hipErrorInvalidValue;
-    if (backward) hipLaunchKernelGGL(tile_chain_kernel<true>, dim3(r.blocks), dim3(TC_T), 0, s, r);
-    else hipLaunchKernelGGL(tile_chain_kernel<false>, dim3(r.blocks), dim3(TC_T), 0, s, r);
+    const dim3 grid(r.blocks), block(TC_T);
+    if (box && backward) hipLaunchKernelGGL((tile_chain_kernel<true, true>), grid, block, 0, s, r);
+    else if (box) hipLaunchKernelGGL((tile_chain_kernel<false, true>), grid, block, 0, s, r);
+    else if (backward) hipLaunchKernelGGL((tile_chain_kernel<true, false>), grid, block, 0, s, r);
+    else hipLaunchKernelGGL((tile_chain_kernel<false, false>), grid, block, 0, s, r);
     return hipGetLastError();
 }
 

@@ -366,6 +366,36 @@ def test_layers_of_some_rows_in_one_launch(d, h, B):
         assert all(torch.equal(a, b) for a, b in zip(*out)), [i for i, (a, b) in enumerate(zip(*out)) if not torch.equal(a, b)]
 
 
+# ... of boxes: projections and both sides of intersections, classes of two to four inputs and one more, depths without intersections, of too few
+# rows and of too many
+@pytest.mark.parametrize("d,h,B", [(300, 500, 40), (400, 800, 130), (132, 260, 33), (512, 1024, 50), (160, 320, 700), (404, 132, 90)])
+def test_layers_of_some_boxes_in_one_launch(d, h, B):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    rng = np.random.default_rng(d + B)
+    N, R = 900, 9
+    params = wl.make_box_params(N, R, d, h, 5)
+    eng = Engine(N, R, d, h, 8.0, family=binding.FAMILY_BOX)
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    inter = lambda k: ("i",) + tuple(proj() for _ in range(k))
+    kinds = [lambda: proj(), lambda: inter(2), lambda: proj(inter(3)), lambda: ("i", proj(), proj(proj())), lambda: ("u", proj(), proj(proj())), lambda: inter(4)]
+    cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    for some in (kinds, kinds[:4], kinds + [lambda: inter(5)], kinds[:2] + [lambda: proj(proj(proj(proj(proj()))))], kinds[:1] + kinds[4:5], kinds[2:4]):
+        qb = wl.batch_from_trees([some[i % len(some)]() for i in range(B)], [int(x) for x in rng.integers(0, N, B)])
+        out = []
+        for polls in (-1, 1 << 22):
+            assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
+            eng.bind_numpy(params)
+            plan = eng.plan(qb)
+            got = [eng.score(plan, cand).clone() for _ in range(3)]
+            assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+            got += [eng.forward_backward(plan, cand).clone()] + [eng.train_step(plan, cand).clone() for _ in range(2)]
+            got += [t[0].clone() for t in eng.tensors.values()] + [t[2].clone() for t in eng.tensors.values()]
+            plan.free()
+            out.append(got[2:])
+        assert all(torch.equal(a, b) for a, b in zip(*out)), [i for i, (a, b) in enumerate(zip(*out)) if not torch.equal(a, b)]
+
+
 # ... one that gives up waiting (here at once): the rows of its depths are nobody's results, parameters stay as they were, and the next call is refused
 def test_layers_of_some_rows_that_give_up_waiting():
     import torch
