@@ -94,6 +94,8 @@ struct ngdb_ctx_s {
     // forward pass, so they are never older than the weights the pass reads.
     DevBuf w_pieces;
     bool chained = false;          // the pass under way has a launch of several depths
+    bool trains = false;           // ... has a backward half
+    bool fuses_beside = false;     // ... fuses many rows beside its forward half, which takes all compute units that are free
     bool rows_chained = false;     // ... its first, which is all of its forward pass (rows_chain)
     bool plan_rides = false;       // the plan comes to the device with the launch of all depths of the forward pass, which reads it where it is
     SmallIndex index_waits{};      // a small gradient index that a launch of the forward pass may take along (n: 0 without one)
@@ -298,8 +300,10 @@ int gslot_of(int t) { return t == T_PROJ ? 0 : (t == T_NEG ? 4 : 8); }
 struct FwdBytes;
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim);
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
-// Whether the weights are split once for a pass.  The two MLPs of the box family: where there are intersections (a step of 4096 boxes at d = 400, h = 800
-// 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; few of them pass in one launch, tile_chain, which needs it).
+// Whether there is room for the weights split once for a pass.  The two MLPs of the box family are split from as many inputs of intersections on as some 800 queries have (a
+// step of 4096 boxes at d = 400, h = 800 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; a step of 512 takes the host as
+// long as the device, with and without), and where a launch of several layers needs it.
+constexpr int BOX_PIECES_FROM = 768;
 bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows > 0; }
 // bytes of the split weights: per MLP two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
 size_t weight_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
@@ -444,6 +448,69 @@ bool forward_chained(const ngdb_ctx_t* c, const ngdb_plan_t* pl) {
     return levels_chain(la, n);
 }
 
+// Tiles of the largest layer of a depth in a launch of several (tile_chain_kernel).  0: not a depth that such a launch takes.
+int depth_tiles(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, bool backward) {
+    const HostPlan& hp = pl->hp;
+    const int d = c->cfg.d, h = c->cfg.h;
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    // (forward layers of a few rows are summed in another order: such a depth stays with its launches)
+    bool few[2] = {!backward, !backward}, any = false;
+    int first = 0, second = 0, plain = 0;
+    for (const Segment& sg : segs) {
+        if (sg.rows <= 0) continue;
+        if (box && sg.type == T_PROJ) {                      // (has no MLP)
+            plain += tile_chain_plain(sg.rows, d);
+            continue;
+        }
+        any = true;
+        few[0] = few[0] && gemm_takes_rows(sg.rows, d);
+        few[1] = few[1] && gemm_takes_rows(sg.rows, h);
+        const int sides = box ? 2 : 1;
+        for (int g = sg.g_lo; sg.type == T_INTER && g < sg.g_hi; ++g) {
+            if (hp.g_nin[g] < 2 || hp.g_nin[g] > TILE_CARD) return 0;
+            first += sides * tile_chain_tiles(hp.g_n[g] * hp.g_nin[g], 1, h);
+            second += sides * tile_chain_tiles(hp.g_n[g], backward ? 1 : hp.g_nin[g], d);
+            if (backward) plain += sides * tile_chain_plain(hp.g_n[g], d);
+        }
+        if (sg.type == T_INTER) continue;
+        first += tile_chain_tiles(sg.rows, 1, h);
+        second += tile_chain_tiles(sg.rows, 1, d);
+    }
+    if (any && (few[0] || few[1])) return 0;
+    return std::max(std::max(backward ? first : first + plain, second), plain);
+}
+// The depths that one launch takes: the last that it can take (depths have fewer rows the deeper they are, as a rule) and those before it.  Looked
+// for in every pass, also in those of a few queries, which the host bounds: nothing is laid out here.
+// CHAIN_LAUNCHES: what it has to take the place of, two launches a depth with MLPs, three with the pooling of boxes, one of their projections (scoring
+// 16 queries at d = 320, h = 836 in one launch for the one depth of more than a few rows 68 against 61 us; a training step is the faster for one depth already).
+struct ChainDepths { int from = 0, to = 0; };
+constexpr int CHAIN_LAUNCHES_TRAIN = 2, CHAIN_LAUNCHES = 4;
+// Tiles that wait hold the places of those that fuse rows beside them: forward passes beside more than so many contributions keep their launches (31 000 of them at 288, 224,
+// 896 features 343 against 379 us; up to 20 000 the launch of several layers is 1.00 to 1.25 times as fast).
+constexpr int64_t CHAIN_FUSED = 20000;
+bool chain_depths(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, ChainDepths* out) {
+    const bool box = c->cfg.family == NGDB_FAMILY_BOX;
+    const int n = pl->hp.n_levels, most = tile_chain_most(c->cfg.d, c->cfg.h, box, c->trains);
+    if (most == 0 || level_fits(c->cfg.d, c->cfg.h, box) || (!backward && c->fuses_beside)) return false;
+    auto takes = [&](int l) {
+        const int tiles = depth_tiles(c, pl, pl->levels[l], backward);
+        LevelArgs la;
+        return tiles > 0 && tiles <= most && !(level_fits(c->cfg.d, c->cfg.h, true) && level_problems(c, pl, pl->levels[l], &la));
+    };
+    int l = n;
+    while (l > 0 && !takes(l)) --l;
+    if (l == 0) return false;
+    out->to = l;
+    while (l > 1 && out->to - l + 1 < LEVEL_CHAIN && takes(l - 1)) --l;
+    out->from = l;
+    int launches = 0;
+    for (; l <= out->to; ++l) {
+        bool mlp = !box;
+        for (const Segment& sg : pl->levels[l]) mlp = mlp || sg.type == T_INTER;
+        launches += !mlp ? 1 : (box ? 3 : 2);
+    }
+    return launches >= (c->trains ? CHAIN_LAUNCHES_TRAIN : CHAIN_LAUNCHES);
+}
 // Splits the weights of the MLPs for a pass, for its backward half too if it has one (at d = 400, h = 800 scoring 1024 queries takes 415 us instead of 423 without it).
 // Without the buffer (a context
 // that never sized a workspace) the contractions split their B operands themselves.
@@ -460,7 +527,8 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
         if (level_problems(c, pl, segs, &la)) continue;
         for (const Segment& sg : segs) narrow = narrow && ((box && sg.type == T_PROJ) || gemm_takes_rows(sg.rows, std::max(d, h)));
     }
-    if (narrow) return;
+    ChainDepths depths;
+    if (narrow || (box && pl->hp.n_int_rows < BOX_PIECES_FROM && !chain_depths(c, pl, backward, &depths))) return;
     uint16_t* at = ptr<uint16_t>(c->w_pieces);
     for (int t = 0; t < 3; ++t) {
         if (box && t == T_PROJ) continue;
@@ -536,6 +604,8 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
     const int waited = check_waits(c);
     if (waited != NGDB_OK) return waited;
     c->chained = c->rows_chained = c->plan_rides = false;
+    c->trains = backward;
+    c->fuses_beside = false;
     RowsChain r;
     if (chain && rows_chain(c, pl, &r)) {
         if (!pl->uploaded) {
@@ -818,56 +888,47 @@ FwdSpace ctx_space(const ngdb_ctx_t* c, bool reclaim = false) {
     return FwdSpace{ptr<float>(c->act), {ptr<float>(c->Z[0]), ptr<float>(c->Z[1]), ptr<float>(c->Z[2])},
                     {ptr<float>(c->H[0]), ptr<float>(c->H[1]), ptr<float>(c->H[2])}, ptr<float>(c->Att), reclaim, level_sync(c)};
 }
-// The operators of a depth as problems of one launch of tiles.  row0: of the type's buffers.  False: too many, or others.
+// Their operators as problems, depth by depth in the order they are computed.  row0: of the type's buffers.  False: too many.
 template <class Row0>
-bool tile_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Segment>& segs, Row0 row0, bool backward, TileProblem* p, int* count) {
+bool tile_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const ChainDepths& depths, bool backward, Row0 row0, TileChain* r) {
     const HostPlan& hp = pl->hp;
-    LevelArgs la;
-    *count = 0;
-    if (level_problems(c, pl, segs, &la)) return false;
-    // (forward layers of a few rows are summed in another order: such a depth stays with its launches)
     const bool box = c->cfg.family == NGDB_FAMILY_BOX;
-    bool few[2] = {!backward, !backward}, any = false;
-    for (const Segment& sg : segs) {
-        if (box && sg.type == T_PROJ) continue;              // (has no MLP)
-        any = true;
-        few[0] = few[0] && gemm_takes_rows(sg.rows, c->cfg.d);
-        few[1] = few[1] && gemm_takes_rows(sg.rows, c->cfg.h);
-    }
-    if (any && (few[0] || few[1])) return false;
-    for (const Segment& sg : segs) {
-        const bool inter = sg.type == T_INTER;
-        if (sg.rows <= 0) continue;
-        for (int i = 0; i < (inter ? sg.g_hi - sg.g_lo : 1); ++i) {
-            if (*count == TILE_PROBLEMS) return false;
-            const int g = sg.g_lo + i, at = inter ? hp.g_mlp_base[g] - sg.mlp_base : 0;
-            if (inter && (hp.g_nin[g] < 2 || hp.g_nin[g] > TILE_CARD)) return false;
-            p[(*count)++] = TileProblem{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, row0(sg) + at, sg.ref_off + at, sg.rel_off,
-                                        inter ? hp.g_out_base[g] : sg.out_base};
-            if (!box || !inter) continue;
-            if (*count == TILE_PROBLEMS) return false;
-            p[*count] = p[*count - 1];                       // (the offsets of the same inputs through the second MLP)
-            p[(*count)++].type = T_NEG;
+    const int n = depths.to - depths.from + 1;
+    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
+    int counts[LEVEL_CHAIN];
+    for (int i = 0; i < n; ++i) {
+        int& count = counts[i];
+        count = 0;
+        for (const Segment& sg : pl->levels[backward ? depths.to - i : depths.from + i]) {
+            const bool inter = sg.type == T_INTER;
+            if (sg.rows <= 0) continue;
+            for (int k = 0; k < (inter ? sg.g_hi - sg.g_lo : 1); ++k) {
+                const int g = sg.g_lo + k, at = inter ? hp.g_mlp_base[g] - sg.mlp_base : 0;
+                const TileProblem p{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, row0(sg) + at, sg.ref_off + at, sg.rel_off,
+                                    inter ? hp.g_out_base[g] : sg.out_base};
+                for (int side = 0; side < (box && inter ? 2 : 1); ++side) {
+                    if (count == TILE_PROBLEMS) return false;
+                    problems[i][count] = p;
+                    if (side) problems[i][count].type = T_NEG;      // (the offsets of the same inputs through the second MLP)
+                    ++count;
+                }
+            }
         }
     }
-    return true;
+    r->d = c->cfg.d; r->h = c->cfg.h;
+    return tile_chain_lay_out(*r, problems, counts, n, backward, box);
 }
 // (the box family's own buffers; null with vectors)
 void chain_boxes(const ngdb_ctx_t* c, TileChain* r) {
     r->Ro = c->prm.Ro.p; r->off = ptr<float>(c->off); r->Gate = ptr<float>(c->Gate);
     r->doff = ptr<float>(c->doff); r->dGate = ptr<float>(c->dGate); r->DxO = ptr<float>(c->DxO);
 }
-// All layers of the depths l0 .. l1 in one launch (tile_chain_kernel), where their launches would be small ones: the same sums in the same order.  False: not
-// such depths.
-bool tile_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, const FwdSpace& w, int l0, int l1, TileChain* r) {
-    const int n = l1 - l0 + 1;
-    if (!w.sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
-    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
-    int counts[LEVEL_CHAIN];
-    for (int i = 0; i < n; ++i)
-        if (!tile_problems(c, pl, pl->levels[l0 + i], [&](const Segment& sg) { return w.reclaim ? 0 : sg.mlp_base; }, false, problems[i], &counts[i])) return false;
-    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = w.reclaim ? 0 : 1;
-    if (!tile_chain_fits(*r, problems, counts, n, false, c->cfg.family == NGDB_FAMILY_BOX)) return false;
+// All layers of some depths in one launch (tile_chain_kernel), where their launches would be small ones: the same sums in the same order.  False: no such depths.
+bool tile_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, const FwdSpace& w, ChainDepths* depths, TileChain* r) {
+    if (!w.sync.counts || !c->have_pieces || !chain_depths(c, pl, false, depths) ||
+        !tile_problems(c, pl, *depths, false, [&](const Segment& sg) { return w.reclaim ? 0 : sg.mlp_base; }, r))
+        return false;
+    r->keep = w.reclaim ? 0 : 1;
     for (int t = 0; t < 3; ++t) {
         const MlpRefs W = mlp_of(c->prm, t);
         r->W[0][t] = c->wp[t][0]; r->W[1][t] = c->wp[t][1]; r->bias[0][t] = W.ba; r->bias[1][t] = W.bb;
@@ -880,16 +941,12 @@ bool tile_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, c
     return true;
 }
 // ... of the backward pass, the deepest first.
-bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, int l0, int l1, TileChain* r) {
+bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, ChainDepths* depths, TileChain* r) {
     const LevelSync sync = level_sync(c);
-    const int n = l1 - l0 + 1;
-    if (!sync.counts || !c->have_pieces || n < 1 || n > LEVEL_CHAIN) return false;
-    TileProblem problems[LEVEL_CHAIN][TILE_PROBLEMS];
-    int counts[LEVEL_CHAIN];
-    for (int i = 0; i < n; ++i)
-        if (!tile_problems(c, pl, pl->levels[l1 - i], [](const Segment& sg) { return sg.mlp_base; }, true, problems[i], &counts[i])) return false;
-    r->d = c->cfg.d; r->h = c->cfg.h; r->keep = 0;
-    if (!tile_chain_fits(*r, problems, counts, n, true, c->cfg.family == NGDB_FAMILY_BOX)) return false;
+    if (!sync.counts || !c->have_pieces || !chain_depths(c, pl, true, depths) ||
+        !tile_problems(c, pl, *depths, true, [](const Segment& sg) { return sg.mlp_base; }, r))
+        return false;
+    r->keep = 0;
     for (int t = 0; t < 3; ++t) {
         r->W[0][t] = c->wp[t][2]; r->W[1][t] = c->wp[t][3]; r->bias[0][t] = r->bias[1][t] = nullptr;
         r->Z[t] = ptr<float>(c->Z[t]); r->H[t] = ptr<float>(c->H[t]); r->dH[t] = ptr<float>(c->dH[t]);
@@ -899,18 +956,6 @@ bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, int l0, int
     r->act = nullptr; r->Att = ptr<float>(c->Att); r->dact = ptr<float>(c->dact); r->dAtt = ptr<float>(c->dAtt); r->Dx = ptr<float>(c->Dx);
     r->sync = sync; r->chain = sync.counts + TILE_AT + TILE_LAYERS * TILE_LAYER;
     return true;
-}
-
-// The depths that one launch takes: the last that it can take (depths have fewer rows the deeper they are, as a rule) and those before it.
-// try_chain(l0, l1, r) lays r out.  False: none.
-struct ChainDepths { int from = 0, to = 0; };
-template <class Try>
-bool chain_depths(int n_levels, Try try_chain, TileChain* r, ChainDepths* out) {
-    for (out->to = n_levels; out->to > 0 && !try_chain(out->to, out->to, r);) --out->to;
-    if (out->to == 0) return false;
-    for (out->from = std::max(1, out->to - LEVEL_CHAIN + 1); out->from < out->to; ++out->from)
-        if (try_chain(out->from, out->to, r)) return true;
-    return try_chain(out->to, out->to, r);
 }
 int enqueue_chain(ngdb_ctx_t* c, const ngdb_plan_t* pl, const TileChain& chain, const ChainDepths& depths, bool backward, hipStream_t s) {
     Timed tm(c, backward ? NGDB_TK_GEMM_BWD : NGDB_TK_GEMM_FWD, s);
@@ -933,7 +978,7 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     ChainDepths depths;
     const EntRows er{c->prm.E.p, pl->d_in_ref, nullptr, nullptr};
     const FwdSpace w = ctx_space(c);
-    const bool in_one = chain_depths(pl->hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain(c, pl, er, w, l0, l1, r); }, &chain, &depths);
+    const bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.from) {
@@ -1077,7 +1122,7 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
     if (enqueue_levels(c, pl, false, forward_level, w.sync, s, &rc_l)) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    const bool in_one = chain_depths(pl->hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain(c, pl, er, w, l0, l1, r); }, &chain, &depths);
+    const bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.from) {
@@ -1230,7 +1275,7 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     if (rc_l != NGDB_OK) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    const bool in_one = !chained && chain_depths(hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain_backward(c, pl, l0, l1, r); }, &chain, &depths);
+    const bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.to) {
@@ -1313,7 +1358,7 @@ int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, Wg
     if (rc_l != NGDB_OK) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    const bool in_one = !chained && chain_depths(hp.n_levels, [&](int l0, int l1, TileChain* r) { return tile_chain_backward(c, pl, l0, l1, r); }, &chain, &depths);
+    const bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.to) {
@@ -1437,6 +1482,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
         c->index_waits.n = 0;
         return rc;
     }
+    c->fuses_beside = aside && sem && n_contrib > CHAIN_FUSED;
     if (sem && (rc = cast_projection(c, stream)) != NGDB_OK) return rc;
     if (aside) {
         HIPCHK(c, hipEventRecord(c->ev_fork, stream));

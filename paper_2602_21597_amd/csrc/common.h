@@ -443,8 +443,13 @@ struct TileChain {
     int32_t* chain;                                 // a word of TILE_LINES on lines of their own per layer
     int blocks = 0;
 };
-// Lays out the tiles of n depths in the order given (count[l] problems each).  False: no such launch, or so many tiles that one is not the better way.
-bool tile_chain_fits(TileChain& r, const TileProblem (*p)[TILE_PROBLEMS], const int* count, int n, bool backward, bool box);
+// Tiles of a layer of n columns over members of k rows each that belong together, and of what is done coordinate by coordinate; the most that
+// a layer may have for such a launch to be the better way (0: widths it does not take).
+int tile_chain_tiles(int members, int k, int n);
+int tile_chain_plain(int members, int d);
+int tile_chain_most(int d, int h, bool box, bool trains);
+// Lays out the tiles of n depths in the order given (count[l] problems each).  False: more parts than one launch has room for.
+bool tile_chain_lay_out(TileChain& r, const TileProblem (*p)[TILE_PROBLEMS], const int* count, int n, bool backward, bool box);
 hipError_t launch_tile_chain(const TileChain& r, bool backward, bool box, hipStream_t s);
 bool levels_chain(const LevelArgs* a, int n);
 hipError_t launch_levels(const LevelArgs* a, int n, bool backward, const LevelSync& sync, const SmallIndex* index, const PlanCopy& copy, hipStream_t s);
