@@ -261,6 +261,28 @@ T* ptr(const DevBuf& b) { return static_cast<T*>(b.p); }
 // Words of c->sync: LevelSync's counts and the mark of a launch that gave up, then those of rows_chain_kernel and of tile_chain_kernel.
 constexpr int CHAIN_AT = 64, TILE_AT = CHAIN_AT + CHAIN_SYNC, SYNC_WORDS = TILE_AT + TILE_SYNC;
 static_assert(LEVEL_SYNC + 1 <= CHAIN_AT, "lines of their own");
+// Launches of several layers whose tiles are dealt by workgroup number may hold each other up for good where two of them run at a time: the tiles of one that wait on one die
+// keep out those that the other waits for.  So only one stream's are under way: launch() is called, and true returned, if no other stream
+// of the process may still run one; else, and in a capture, whose replays are not known here, the pass keeps a launch a layer (the same sums).
+struct ChainStream { hipStream_t s; bool any; };
+std::mutex g_chain_mu;
+ChainStream g_chain_stream[NOALLOC_MAX_DEVICES] = {};
+template <class Launch>
+bool chain_turn(hipStream_t s, Launch launch) {
+    int dev = -1;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= NOALLOC_MAX_DEVICES || hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) return false;
+    std::lock_guard<std::mutex> lk(g_chain_mu);
+    ChainStream& last = g_chain_stream[dev];
+    if (last.any && last.s != s) {
+        const hipError_t e = hipStreamQuery(last.s);      // (a stream that is gone runs nothing)
+        if (e != hipSuccess) (void)hipGetLastError();
+        if (e == hipErrorNotReady) return false;
+    }
+    last = ChainStream{s, true};
+    launch();
+    return true;
+}
 LevelSync level_sync(const ngdb_ctx_t* c) {
     LevelSync y;
     if (c->chain_polls < 0) return y;            // (a launch per depth)
@@ -612,7 +634,8 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
             r.copy = plan_copy(pl);
         }
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
-        const hipError_t e = launch_rows_chain(r, s);
+        hipError_t e = hipErrorInvalidValue;
+        chain_turn(s, [&] { e = launch_rows_chain(r, s); });
         if (e == hipSuccess) {
             double flop = 0.0;
             for (const std::vector<Segment>& segs : pl->levels) flop += level_flop(c, segs);
@@ -957,9 +980,13 @@ bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, ChainDepths
     r->sync = sync; r->chain = sync.counts + TILE_AT + TILE_LAYERS * TILE_LAYER;
     return true;
 }
-int enqueue_chain(ngdb_ctx_t* c, const ngdb_plan_t* pl, const TileChain& chain, const ChainDepths& depths, bool backward, hipStream_t s) {
+// *done: whether it was enqueued
+int enqueue_chain(ngdb_ctx_t* c, const ngdb_plan_t* pl, const TileChain& chain, const ChainDepths& depths, bool backward, hipStream_t s, bool* done) {
     Timed tm(c, backward ? NGDB_TK_GEMM_BWD : NGDB_TK_GEMM_FWD, s);
-    HIPCHK(c, launch_tile_chain(chain, backward, c->cfg.family == NGDB_FAMILY_BOX, s));
+    hipError_t e = hipSuccess;
+    *done = chain_turn(s, [&] { e = launch_tile_chain(chain, backward, c->cfg.family == NGDB_FAMILY_BOX, s); });
+    if (!*done) return NGDB_OK;
+    HIPCHK(c, e);
     double flop = 0.0;
     for (int l = depths.from; l <= depths.to; ++l) flop += level_flop(c, pl->levels[l]);
     tm.work(GEMM_SPLIT, flop);
@@ -978,13 +1005,15 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     ChainDepths depths;
     const EntRows er{c->prm.E.p, pl->d_in_ref, nullptr, nullptr};
     const FwdSpace w = ctx_space(c);
-    const bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
+    bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.from) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s)) != NGDB_OK) return rc_l;
-            l = depths.to;
-            continue;
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s, &in_one)) != NGDB_OK) return rc_l;
+            if (in_one) {
+                l = depths.to;
+                continue;
+            }
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1122,13 +1151,15 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
     if (enqueue_levels(c, pl, false, forward_level, w.sync, s, &rc_l)) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    const bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
+    bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.from) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s)) != NGDB_OK) return rc_l;
-            l = depths.to;
-            continue;
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s, &in_one)) != NGDB_OK) return rc_l;
+            if (in_one) {
+                l = depths.to;
+                continue;
+            }
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1275,13 +1306,15 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     if (rc_l != NGDB_OK) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    const bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
+    bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.to) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s)) != NGDB_OK) return rc_l;
-            l = depths.from;
-            continue;
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s, &in_one)) != NGDB_OK) return rc_l;
+            if (in_one) {
+                l = depths.from;
+                continue;
+            }
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1358,13 +1391,15 @@ int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, Wg
     if (rc_l != NGDB_OK) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    const bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
+    bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.to) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s)) != NGDB_OK) return rc_l;
-            l = depths.from;
-            continue;
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s, &in_one)) != NGDB_OK) return rc_l;
+            if (in_one) {
+                l = depths.from;
+                continue;
+            }
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {

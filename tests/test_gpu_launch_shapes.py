@@ -424,6 +424,32 @@ def test_layers_of_some_rows_that_give_up_waiting():
     plan.free()
 
 
+# ... two contexts on two streams, calls of both under way at a time: each as it is alone
+def test_layers_of_some_rows_on_two_streams():
+    import torch
+    from paper_2602_21597_amd import Engine
+    N, R, B = 900, 9, 60
+    rng = np.random.default_rng(6)
+    proj = lambda: ("p", int(rng.integers(R)), ("p", int(rng.integers(R)), ("e", int(rng.integers(N)))))
+    cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    sides = []
+    for d, h in ((260, 516), (300, 400)):
+        eng = Engine(N, R, d, h, 8.0)
+        eng.bind_numpy(wl.make_params(N, R, d, h, 6))
+        plan = eng.plan(wl.batch_from_trees([("i", proj(), proj()) for _ in range(B)], [0] * B))
+        sides.append((eng, plan, torch.cuda.Stream(), eng.score(plan, cand).clone()))
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(20):
+        for eng, plan, stream, want in sides:
+            with torch.cuda.stream(stream):
+                got.append((eng.score(plan, cand), want))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in got)
+    for eng, plan, _, _ in sides:
+        plan.free()
+
+
 # ... captured: every replay as the call, with other launches of the kind in between
 def test_layers_of_some_rows_captured():
     import torch
