@@ -517,6 +517,13 @@ int ngdb_debug_device_limit(ngdb_ctx_t* ctx, int64_t bytes);
  * of the context returns NGDB_ERR_HIP.  For tests.                                                                      */
 int ngdb_debug_chain_polls(ngdb_ctx_t* ctx, int32_t polls);
 
+/* How often a workgroup of a launch of several layers looks at the counts of the layer before until it takes a tile of the earlier layers that no workgroup has.
+ * Negative: it does so at once, and every eighth workgroup looks so often, some 2 us apart, whether another has its tile before it takes it.  For tests. */
+int ngdb_debug_chain_patience(ngdb_ctx_t* ctx, int32_t looks);
+/* Launches of several layers that this context has made: kind 0: forward passes of a handful of queries, 1 and 2: forward and backward passes of more rows; kind 3:
+ * their tiles that a workgroup with another tile computed (waits for the device).  Negative on failure.  For tests. */
+int64_t ngdb_debug_chain_launches(ngdb_ctx_t* ctx, int32_t kind);
+
 /* From how many coordinate differences (branch rows x entities x d) on the rankings of this context go through the
  * integer filter; negative: the library's own choice.  For tests of the filter at sizes below that.   */
 int ngdb_debug_rank_filter_from(ngdb_ctx_t* ctx, int64_t work);

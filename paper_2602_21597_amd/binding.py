@@ -123,6 +123,8 @@ def load_library(path=LIB_PATH):
         "ngdb_debug_device_bytes": (i64, [vp]),
         "ngdb_debug_device_limit": (C.c_int, [vp, i64]),
         "ngdb_debug_chain_polls": (C.c_int, [vp, i32]),
+        "ngdb_debug_chain_patience": (C.c_int, [vp, i32]),
+        "ngdb_debug_chain_launches": (i64, [vp, i32]),
         "ngdb_debug_rank_filter_from": (C.c_int, [vp, i64]),
         "ngdb_debug_rank_by_chunks": (C.c_int, [vp, i32]),
         "ngdb_debug_rank_overflows": (C.c_int, [vp]),

@@ -102,6 +102,11 @@ struct ngdb_ctx_s {
     DevBuf sync;        // of the launches of several depths (LevelSync), in device memory
     int32_t* gave_up = nullptr;    // and in pinned host memory: one of them has given up waiting, for good
     int chain_polls = CHAIN_POLLS;       // tests: see ngdb_debug_chain_polls
+    int chain_patience = TILE_PATIENCE; // tests: see ngdb_debug_chain_patience
+    unsigned long long chain_launch = 0; // number of the last launch whose tiles are taken
+    bool chain_odd = false;        // which of two sets of bits the next launch of a few rows finds cleared
+    int64_t chain_count[3]{};            // tests: see ngdb_debug_chain_launches
+    bool captured = false;         // the pass under way is recorded into a graph: replays have no launch numbers of their own
     const uint16_t* wp[3][4]{};     // per type: Wa forward, Wb forward, Wb backward (dH = dY Wb), Wa backward (dZ = dH Wa)
     bool have_pieces = false;
     int64_t rank_filter_from = -1;       // tests: see ngdb_debug_rank_filter_from
@@ -258,36 +263,20 @@ int ensure(ngdb_ctx_t* c, DevBuf& b, size_t bytes, Use use = Use::Any) {
 template <class T>
 T* ptr(const DevBuf& b) { return static_cast<T*>(b.p); }
 
-// Words of c->sync: LevelSync's counts and the mark of a launch that gave up, then those of rows_chain_kernel and of tile_chain_kernel.
-constexpr int CHAIN_AT = 64, TILE_AT = CHAIN_AT + CHAIN_SYNC, SYNC_WORDS = TILE_AT + TILE_SYNC;
-static_assert(LEVEL_SYNC + 1 <= CHAIN_AT, "lines of their own");
-// Launches of several layers whose tiles are dealt by workgroup number may hold each other up for good where two of them run at a time: the tiles of one that wait on one die
-// keep out those that the other waits for.  So only one stream's are under way: launch() is called, and true returned, if no other stream
-// of the process may still run one; else, and in a capture, whose replays are not known here, the pass keeps a launch a layer (the same sums).
-struct ChainStream { hipStream_t s; bool any; };
-std::mutex g_chain_mu;
-ChainStream g_chain_stream[NOALLOC_MAX_DEVICES] = {};
-template <class Launch>
-bool chain_turn(hipStream_t s, Launch launch) {
-    int dev = -1;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= NOALLOC_MAX_DEVICES || hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) return false;
-    std::lock_guard<std::mutex> lk(g_chain_mu);
-    ChainStream& last = g_chain_stream[dev];
-    if (last.any && last.s != s) {
-        const hipError_t e = hipStreamQuery(last.s);      // (a stream that is gone runs nothing)
-        if (e != hipSuccess) (void)hipGetLastError();
-        if (e == hipErrorNotReady) return false;
-    }
-    last = ChainStream{s, true};
-    launch();
-    return true;
-}
+// Words of c->sync: LevelSync's counts and the mark of a launch that gave up, the count of tiles that another workgroup computed, then what rows_chain_kernel and
+// tile_chain_kernel wait by: bits twice, whose tiles are taken, counts.
+constexpr int HELPED_AT = 32, CHAIN_AT = 64, TAKEN_AT = CHAIN_AT + 2 * 2 * CHAIN_SYNC, TILE_AT = TAKEN_AT + 2 * TILE_WORDS, SYNC_WORDS = TILE_AT + TILE_SYNC;
+static_assert(LEVEL_SYNC + 1 <= HELPED_AT && CHAIN_AT % 32 == 0 && TAKEN_AT % 32 == 0, "lines of their own");
 LevelSync level_sync(const ngdb_ctx_t* c) {
     LevelSync y;
     if (c->chain_polls < 0) return y;            // (a launch per depth)
     y.counts = ptr<int32_t>(c->sync); y.gave_up = y.counts + LEVEL_SYNC; y.host_gave_up = c->gave_up; y.polls = c->chain_polls;
     return y;
+}
+TileHelp tile_help(const ngdb_ctx_t* c) {
+    TileHelp t;
+    t.helped = ptr<int32_t>(c->sync) + HELPED_AT; t.patience = c->chain_patience;
+    return t;
 }
 // A launch of an earlier call gave up waiting for a depth: nothing is computed on this context any more.
 int check_waits(ngdb_ctx_t* c) {
@@ -411,14 +400,8 @@ bool level_problems(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vecto
     return true;
 }
 
-int plan_uploaded(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
-    if (pl->uploaded) return NGDB_OK;
-    // (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    HIPCHK(c, hipStreamIsCapturing(s, &st));
-    if (st == hipStreamCaptureStatusNone) pl->uploaded = true;
-    return NGDB_OK;
-}
+// (in a stream capture nothing has run yet: whoever uses the plan outside of it copies again)
+void plan_uploaded(const ngdb_ctx_t* c, const ngdb_plan_t* pl) { pl->uploaded = pl->uploaded || !c->captured; }
 PlanCopy plan_copy(const ngdb_plan_t* pl) {
     return PlanCopy{reinterpret_cast<const float4*>(pl->blob.pinned), reinterpret_cast<float4*>(pl->blob.dev), (int)(pl->blob_bytes / 16)};
 }
@@ -454,7 +437,8 @@ bool enqueue_levels(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Fill fi
         tm.work(GEMM_FP32, flop);
         if (!copy.n) return NGDB_OK;
         c->plan_rides = false;
-        return plan_uploaded(c, pl, s);
+        plan_uploaded(c, pl);
+        return NGDB_OK;
     };
     *rc = launch();
     return true;
@@ -513,7 +497,7 @@ constexpr int64_t CHAIN_FUSED = 20000;
 bool chain_depths(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, ChainDepths* out) {
     const bool box = c->cfg.family == NGDB_FAMILY_BOX;
     const int n = pl->hp.n_levels, most = tile_chain_most(c->cfg.d, c->cfg.h, box, c->trains);
-    if (most == 0 || level_fits(c->cfg.d, c->cfg.h, box) || (!backward && c->fuses_beside)) return false;
+    if (most == 0 || c->captured || level_fits(c->cfg.d, c->cfg.h, box) || (!backward && c->fuses_beside)) return false;
     auto takes = [&](int l) {
         const int tiles = depth_tiles(c, pl, pl->levels[l], backward);
         LevelArgs la;
@@ -572,16 +556,16 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
 }
 
 // All layers of a forward pass in one launch (rows_chain_kernel), where each would be one of a few rows: the same sums in the same order.
-// Only passes that keep no rows for others (outputs reclaimed), of the vector family without text features (whose references are made on the
-// device).  False: not such a pass.
+// Only passes that keep no rows for others, of the vector family without text features (whose references are made on the device).  Outputs keep a row
+// each, by slot, and every depth has rows of its own (TileWords): roots are those of passes that keep everything.  False: not such a pass.
 bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
     const HostPlan& hp = pl->hp;
     const int d = c->cfg.d, h = c->cfg.h;
     const LevelSync sync = level_sync(c);
-    if (c->cfg.family != NGDB_FAMILY_VEC || c->cfg.d_sem > 0 || !sync.counts || hp.n_levels < 1 || hp.n_levels > LEVEL_CHAIN || std::max(d, h) > CHAIN_WIDTH ||
+    if (c->cfg.family != NGDB_FAMILY_VEC || c->cfg.d_sem > 0 || !sync.counts || c->captured || hp.n_levels < 1 || hp.n_levels > LEVEL_CHAIN || std::max(d, h) > CHAIN_WIDTH ||
         level_fits(d, h, true))
         return false;
-    r->d = d; r->h = h; r->depths = hp.n_levels; r->sync = sync; r->chain = sync.counts + CHAIN_AT;
+    r->d = d; r->h = h; r->depths = hp.n_levels; r->sync = sync;
     auto word = [&](int32_t v) { r->words[r->n_words++] = v; };
     for (int l = 1; l <= hp.n_levels; ++l) {
         int& count = r->count[l - 1];
@@ -593,15 +577,12 @@ bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
             for (int i = 0; i < classes; ++i) {
                 const int g = sg.g_lo + i;
                 const bool inter = sg.type == T_INTER;
-                RowsProblem p{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, r->n_words, inter ? hp.g_mlp_base[g] - sg.mlp_base : 0};
+                RowsProblem p{sg.type, inter ? hp.g_nin[g] : 1, inter ? hp.g_n[g] : sg.rows, r->n_words, inter ? hp.g_mlp_base[g] : sg.mlp_base};
                 if (count == CHAIN_PROBLEMS || p.k > CHAIN_CARD || (inter && p.k < 2) || r->n_words + p.n * (p.k + 2) > CHAIN_WORDS) return false;
-                const int ref0 = sg.ref_off + p.row0, out0 = inter ? hp.g_out_base[g] : sg.out_base;
-                for (int x = 0; x < p.n * p.k; ++x) {
-                    const int32_t ref = hp.in_ref[ref0 + x];
-                    word(ref >= 0 ? hp.f_row[ref] : ref);
-                }
+                const int ref0 = sg.ref_off + p.row0 - sg.mlp_base, out0 = inter ? hp.g_out_base[g] : sg.out_base;
+                for (int x = 0; x < p.n * p.k; ++x) word(hp.in_ref[ref0 + x]);
                 for (int x = 0; sg.type == T_PROJ && x < p.n; ++x) word(hp.rel[sg.rel_off + x]);
-                for (int x = 0; x < p.n; ++x) word(hp.f_row[out0 + x]);
+                for (int x = 0; x < p.n; ++x) word(out0 + x);
                 r->p[l - 1][count++] = p;
             }
         }
@@ -625,6 +606,9 @@ constexpr size_t PLAN_INLINE_BYTES = 256 << 10;
 int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t s, bool chain = false, bool ride = false) {
     const int waited = check_waits(c);
     if (waited != NGDB_OK) return waited;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIPCHK(c, hipStreamIsCapturing(s, &capture));
+    c->captured = capture != hipStreamCaptureStatusNone;
     c->chained = c->rows_chained = c->plan_rides = false;
     c->trains = backward;
     c->fuses_beside = false;
@@ -633,15 +617,21 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
         if (!pl->uploaded) {
             r.copy = plan_copy(pl);
         }
+        unsigned long long* bits = reinterpret_cast<unsigned long long*>(ptr<int32_t>(c->sync) + CHAIN_AT);
+        r.through = bits + (c->chain_odd ? CHAIN_SYNC : 0);
+        r.clear = bits + (c->chain_odd ? 0 : CHAIN_SYNC);
+        r.help = tile_help(c);
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
-        hipError_t e = hipErrorInvalidValue;
-        chain_turn(s, [&] { e = launch_rows_chain(r, s); });
+        const hipError_t e = launch_rows_chain(r, s);
         if (e == hipSuccess) {
+            ++c->chain_count[0];
+            c->chain_odd = !c->chain_odd;
             double flop = 0.0;
             for (const std::vector<Segment>& segs : pl->levels) flop += level_flop(c, segs);
             tm.work(GEMM_FP32, flop);
             c->chained = c->rows_chained = true;
-            return plan_uploaded(c, pl, s);
+            plan_uploaded(c, pl);
+            return NGDB_OK;
         }
         if (e != hipErrorInvalidValue) HIPCHK(c, e);
     }
@@ -661,7 +651,8 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
         HIPCHK(c, launch_weight_pieces(J, s));
     }
-    return plan_uploaded(c, pl, s);
+    plan_uploaded(c, pl);
+    return NGDB_OK;
 }
 
 // The end of a pass, also of one that is refused or fails half way: what it enqueued still reads the plan, whose buffer
@@ -980,13 +971,13 @@ bool tile_chain_backward(const ngdb_ctx_t* c, const ngdb_plan_t* pl, ChainDepths
     r->sync = sync; r->chain = sync.counts + TILE_AT + TILE_LAYERS * TILE_LAYER;
     return true;
 }
-// *done: whether it was enqueued
-int enqueue_chain(ngdb_ctx_t* c, const ngdb_plan_t* pl, const TileChain& chain, const ChainDepths& depths, bool backward, hipStream_t s, bool* done) {
+int enqueue_chain(ngdb_ctx_t* c, const ngdb_plan_t* pl, TileChain& chain, const ChainDepths& depths, bool backward, hipStream_t s) {
+    chain.taken = reinterpret_cast<unsigned long long*>(ptr<int32_t>(c->sync) + TAKEN_AT);
+    chain.launch = ++c->chain_launch;
+    chain.help = tile_help(c);
     Timed tm(c, backward ? NGDB_TK_GEMM_BWD : NGDB_TK_GEMM_FWD, s);
-    hipError_t e = hipSuccess;
-    *done = chain_turn(s, [&] { e = launch_tile_chain(chain, backward, c->cfg.family == NGDB_FAMILY_BOX, s); });
-    if (!*done) return NGDB_OK;
-    HIPCHK(c, e);
+    HIPCHK(c, launch_tile_chain(chain, backward, c->cfg.family == NGDB_FAMILY_BOX, s));
+    ++c->chain_count[backward ? 2 : 1];
     double flop = 0.0;
     for (int l = depths.from; l <= depths.to; ++l) flop += level_flop(c, pl->levels[l]);
     tm.work(GEMM_SPLIT, flop);
@@ -1005,15 +996,13 @@ int enqueue_forward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s) {
     ChainDepths depths;
     const EntRows er{c->prm.E.p, pl->d_in_ref, nullptr, nullptr};
     const FwdSpace w = ctx_space(c);
-    bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
+    const bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.from) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s, &in_one)) != NGDB_OK) return rc_l;
-            if (in_one) {
-                l = depths.to;
-                continue;
-            }
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s)) != NGDB_OK) return rc_l;
+            l = depths.to;
+            continue;
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1102,7 +1091,7 @@ FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim)
 // reclaimed sizes; with text features also the index over [anchors | tail] and the fused rows.
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
     const HostPlan& hp = pl->hp;
-    const FwdBytes fb = forward_bytes(c, pl, true);
+    const FwdBytes fb = forward_bytes(c, pl, hp.n_slots > CHAIN_WORDS);     // (nothing used twice where rows_chain may take the pass)
     int rc;
 #define ENS(buf, bytes) if ((rc = ensure(c, buf, std::max<size_t>((bytes), 256))) != NGDB_OK) return rc
     ENS(c->w_pieces, weight_pieces_bytes(c, hp));
@@ -1151,15 +1140,13 @@ int enqueue_forward(ngdb_ctx_t* c, const ngdb_plan_t* pl, const EntRows& er, hip
     if (enqueue_levels(c, pl, false, forward_level, w.sync, s, &rc_l)) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
+    const bool in_one = tile_chain(c, pl, er, w, &depths, &chain);
     for (int l = 1; l <= pl->hp.n_levels; ++l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.from) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s, &in_one)) != NGDB_OK) return rc_l;
-            if (in_one) {
-                l = depths.to;
-                continue;
-            }
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, false, s)) != NGDB_OK) return rc_l;
+            l = depths.to;
+            continue;
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1306,15 +1293,13 @@ int enqueue_backward(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, WgradJ
     if (rc_l != NGDB_OK) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
+    const bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.to) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s, &in_one)) != NGDB_OK) return rc_l;
-            if (in_one) {
-                l = depths.from;
-                continue;
-            }
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s)) != NGDB_OK) return rc_l;
+            l = depths.from;
+            continue;
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -1391,15 +1376,13 @@ int enqueue_backward_box(ngdb_ctx_t* c, const ngdb_plan_t* pl, hipStream_t s, Wg
     if (rc_l != NGDB_OK) return rc_l;
     TileChain chain;
     ChainDepths depths;
-    bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
+    const bool in_one = !chained && tile_chain_backward(c, pl, &depths, &chain);
     for (int l = chained ? 0 : hp.n_levels; l >= 1; --l) {
         const std::vector<Segment>& segs = pl->levels[l];
         if (in_one && l == depths.to) {
-            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s, &in_one)) != NGDB_OK) return rc_l;
-            if (in_one) {
-                l = depths.from;
-                continue;
-            }
+            if ((rc_l = enqueue_chain(c, pl, chain, depths, true, s)) != NGDB_OK) return rc_l;
+            l = depths.from;
+            continue;
         }
         LevelArgs la;
         if (level_problems(c, pl, segs, &la)) {
@@ -2432,7 +2415,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, s};
     if ((rc = begin_pass(c, pl, false, s, reclaim, c->cfg.d_sem == 0)) != NGDB_OK) return rc;
-    const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
+    const int32_t* roots = reclaim && !c->rows_chained ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, d_cand, n_tail, s, &er, reclaim);
     if (rc != NGDB_OK) return rc;
@@ -2544,7 +2527,7 @@ int ngdb_rank_answers(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ans
     if (rc != NGDB_OK) return rc;
     PassEnd end{c, pl, s};
     if ((rc = begin_pass(c, pl, false, s, reclaim, c->cfg.d_sem == 0)) != NGDB_OK) return rc;
-    const int32_t* roots = reclaim ? pl->d_f_root : pl->d_root_slot;
+    const int32_t* roots = reclaim && !c->rows_chained ? pl->d_f_root : pl->d_root_slot;
     EntRows er{};
     rc = prepare_entities(c, pl, nullptr, 0, s, &er, reclaim);
     if (rc != NGDB_OK) return rc;
@@ -2706,6 +2689,20 @@ int ngdb_debug_chain_polls(ngdb_ctx_t* c, int32_t polls) {
     *c->gave_up = 0;
     c->chain_polls = polls;
     return NGDB_OK;
+}
+
+int ngdb_debug_chain_patience(ngdb_ctx_t* c, int32_t looks) {
+    if (!c) return NGDB_ERR_ARG;
+    c->chain_patience = looks;
+    return NGDB_OK;
+}
+
+int64_t ngdb_debug_chain_launches(ngdb_ctx_t* c, int32_t kind) {
+    if (!c || kind < 0 || kind > 3) return -1;
+    if (kind < 3) return c->chain_count[kind];
+    int32_t helped = 0;
+    if (hipDeviceSynchronize() != hipSuccess || hipMemcpy(&helped, ptr<int32_t>(c->sync) + HELPED_AT, sizeof(helped), hipMemcpyDeviceToHost) != hipSuccess) return -1;
+    return helped;
 }
 
 int ngdb_debug_rank_filter_from(ngdb_ctx_t* c, int64_t work) {

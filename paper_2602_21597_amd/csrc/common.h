@@ -383,6 +383,28 @@ struct LevelSync {
     int32_t polls = 0;              // looks at a count before a wait gives up (0: it does at once)
 };
 constexpr int32_t GAVE_UP = 1 << 16;      // what a tile that gave up adds to a count of tiles
+// A launch whose tiles, dealt by workgroup number, wait for one another has to come to its end whatever else holds places on the card, other
+// launches of its kind among them, on other streams or of other processes: nobody may wait for good for a workgroup that has not started.  So a
+// workgroup that has looked `patience` times for the layer before computes another one's tile, and then begins its own again.  Of the layers that are not through
+// the first is always worked on, then: its tiles wait for nothing.
+// rows_chain_kernel: a bit is set when its tile is through, and whoever helps computes one of the first layer that is not, which its own workgroup or others may do as
+// well: they write the same values, to rows that nothing else of the launch is written to, and set the same bit.
+// tile_chain_kernel, whose rows may be used again by a later depth: a workgroup takes its tile before it works on it, by setting the tile's word, and whoever helps takes
+// the first tile that nobody has (what it works on lies before everything that is not taken, so that it never waits for such a tile itself, and
+// whoever has a tile of the first layer that is not through works on that one).  Tiles of the last layer, which nobody waits for, are not taken.
+// patience < 0, for tests: waiting workgroups help at once, and every eighth one looks -patience times whether its tile is done or taken before it begins itself.
+struct TileHelp {
+    int32_t* helped = nullptr;              // counts the tiles that another workgroup computed
+    int32_t patience = 0;
+};
+constexpr int TILE_PATIENCE = 1024, TILE_AGAIN = 64;       // (looks of 0.3 us and more; a launch takes up to 60 us)
+// What a workgroup learns before it needs the layer before: goes on; goes on, but its rows are not valid; has no tile any more.  Else: whose tile to compute first.
+constexpr int TILE_GO = -1, TILE_GAVE_UP = -2, TILE_TAKEN = -3;
+template <class Over>
+__device__ __forceinline__ void tile_late(const TileHelp& c, int at, Over over) {
+    if (__builtin_expect(c.patience < 0 && (at & 7) == 7, 0))
+        for (int i = 0; i < -c.patience && !over(); ++i) __builtin_amdgcn_s_sleep(64);
+}
 // The plan, copied from pinned memory for the launches that follow, by one more workgroup (n: 16-byte units, 0: nothing to copy).
 struct PlanCopy {
     const float4* src = nullptr;
@@ -390,21 +412,24 @@ struct PlanCopy {
     int n = 0;
 };
 // A forward pass of a handful of queries, all layers of all depths in one launch (level.hip: rows_chain_kernel).  A problem is a projection or
-// negation group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its depth's buffers; words[at ..] holds
+// negation group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its type's buffers, which no other depth uses; words[at ..] holds
 // its n k references, the relations of a projection and its n output rows, so that nothing waits for the plan to reach the device.
 // Limits: words of all problems, inputs of an intersection, values of a row.
-constexpr int CHAIN_SYNC = (2 * LEVEL_CHAIN * 8 + 1) * 32;      // words that such launches share, zero, and zero again behind each of them
 constexpr int CHAIN_PROBLEMS = 5, CHAIN_WORDS = 160, CHAIN_CARD = 4, CHAIN_WIDTH = 1024;
+// Tiles of a layer by bits of CHAIN_LINES words on lines of their own, the highest bit of each for a tile that gave up.  A launch clears the words of the next one.
+constexpr int CHAIN_LINES = 16, CHAIN_STRIDE = 16, CHAIN_LAYER = CHAIN_LINES * CHAIN_STRIDE, CHAIN_BITS = 63, CHAIN_SYNC = 2 * LEVEL_CHAIN * CHAIN_LAYER;
+constexpr unsigned long long CHAIN_GAVE_UP = 1ull << CHAIN_BITS;
 struct RowsProblem { int type, k, n, at, row0; };
-struct RowsChain {
+struct RowsChain {                                  // (what every tile needs first stands together)
     int d, h, depths = 0, n_words = 0;
+    unsigned long long *through, *clear;            // CHAIN_SYNC words each: zero at first; zero at last
+    TileHelp help;
+    LevelSync sync;                                 // (its counts are not used)
     int count[LEVEL_CHAIN] = {}, first[2 * LEVEL_CHAIN + 1] = {};    // problems of a depth; tiles before each layer (filled in by the launch)
     RowsProblem p[LEVEL_CHAIN][CHAIN_PROBLEMS];
     const float *Wa[3], *ba[3], *Wb[3], *bb[3];     // by type: projection, intersection, negation
     const float *E, *R;
     float *act, *Z, *H[3];                          // outputs; inputs of intersections; hidden rows by type
-    LevelSync sync;                                 // (its counts are not used)
-    int32_t* chain;                                 // CHAIN_SYNC words
     PlanCopy copy;
     int32_t words[CHAIN_WORDS];
 };
@@ -412,7 +437,7 @@ hipError_t launch_rows_chain(RowsChain& r, hipStream_t s);
 // All layers of a pass over up to some hundred rows a depth in one launch (gemm.hip: tile_chain_kernel).  A problem is a projection or negation
 // group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its type's buffers, references ref0 + ... (and
 // relations rel0 + ..., -1: none), outputs out0 + i.  Limits: inputs of an intersection, input values and hidden values of a row, problems of a depth.
-constexpr int TILE_CARD = 4, TILE_D = 512, TILE_H = 1024, TILE_PROBLEMS = 8, TILE_PARTS = 32;
+constexpr int TILE_CARD = 4, TILE_D = 512, TILE_H = 1024, TILE_PROBLEMS = 8, TILE_PARTS = 32, TILE_WORDS = 8192;
 // words of counts, zero before the launch: of the layers of a forward pass (two a depth), then of a backward one (up to three a depth)
 constexpr int TILE_LINES = 16, TILE_STRIDE = 32, TILE_LAYER = TILE_LINES * TILE_STRIDE;
 constexpr int TILE_LAYERS = 2 * LEVEL_CHAIN, TILE_LAYERS_BWD = 3 * LEVEL_CHAIN, TILE_SYNC = (TILE_LAYERS + TILE_LAYERS_BWD) * TILE_LAYER;
@@ -441,6 +466,9 @@ struct TileChain {
     float *off, *Gate, *doff, *dGate, *DxO;
     LevelSync sync;                                 // (its counts are not used)
     int32_t* chain;                                 // a word of TILE_LINES on lines of their own per layer
+    unsigned long long* taken;                      // TILE_WORDS, by workgroup number: the number of the last launch that took it, ...
+    unsigned long long launch = 0;                  // ... which no other launch of the context has, so that nothing is cleared between them
+    TileHelp help;
     int blocks = 0;
 };
 // Tiles of a layer of n columns over members of k rows each that belong together, and of what is done coordinate by coordinate; the most that

@@ -1214,8 +1214,8 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
 // relations and looks its rows up before it waits for the layer before, and then brings its rows into LDS at once; the weights go from
 // global memory into the registers they are multiplied from.  k is dealt to the eight wavefronts in blocks of 16, four of them on the way; 64 KB
 // of LDS and 128 registers leave room for two workgroups a compute unit.  Rows handed from layer to layer are stored and loaded at
-// the scope of the card (level.hip: levels_kernel).  Tiles are dealt by workgroup number as in rows_chain_kernel, whose waits and
-// giving up these are; the counts are cleared by the launch that splits the weights.  Sums are formed as in product_kernel with eight partial sums.
+// the scope of the card (level.hip: levels_kernel).  Tiles are dealt by workgroup number (TileHelp), waits and
+// giving up are those of rows_chain_kernel; the counts are cleared by the launch that splits the weights.  Sums are formed as in product_kernel with eight partial sums.
 // What a workgroup has to know first comes in two round trips to the argument segment, its part of the layer, then that part's values
 // and pointers (looked up one by one, with divisions, the start of a tile took 2 to 6 us instead of 1.0 to 2.5).  A layer takes 4.3 us at k = 400 and 5.3 at
 // 800: 0.9 until a count is seen, 0.7 for the rows, 1.3 and 2.3 for the products, 0.5 to 1 for sums and pooling, 0.5 for the stores.
@@ -1226,23 +1226,62 @@ __global__ __launch_bounds__(WM * WK * 64, WM > 1 ? 4 : 2) void product_kernel(c
 // 120 against 44 and 101, 160 at 160, 320 56 and 109 against 34 and 87.
 constexpr int TC_WAVES = 8, TC_T = TC_WAVES * 64, TC_AHEAD = 4, TC_LD = 36;
 static_assert(TC_AHEAD * TC_WAVES * 16 >= TILE_D && 2 * TC_AHEAD * TC_WAVES * 16 >= TILE_H, "relations in registers; two chunks at most");
-// Waits until all tiles of the layer before are through (each counts on one of its words); every thread learns whether they are.
-__device__ __forceinline__ bool tc_wait(const int32_t* words, int tiles, int polls, int* waited) {
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x, want = (tiles - lane + TILE_LINES - 1) / TILE_LINES;       // of this lane's word
-        const int32_t* word = words + min(lane, TILE_LINES - 1) * TILE_STRIDE;
-        bool all = false;
-        for (int i = 0; i < polls; ++i) {
-            const int n = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            all = __ballot(lane < TILE_LINES && n != want) == 0ull;
-            if (all || __ballot(lane < TILE_LINES && n > want) != 0ull) break;
-            __builtin_amdgcn_s_sleep(1);
+// (the number of the launch that had taken it before)
+__device__ __forceinline__ unsigned long long tc_take(const TileChain& r, int at) {
+    return __hip_atomic_exchange(r.taken + at, r.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool tc_taken(const TileChain& r, int at) {
+    return __hip_atomic_load(r.taken + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r.launch;
+}
+// The first tile of the workgroups before `end` that nobody has, taken; TILE_GO: there is none.  By one wavefront.
+__device__ __forceinline__ int tc_take_first(const TileChain& r, int end) {
+    const int lane = threadIdx.x & 63;
+    for (int base = 0; base < end; base += 64) {
+        unsigned long long open = __ballot(base + lane < end && !tc_taken(r, min(base + lane, end - 1)));
+        for (; open != 0ull; open &= open - 1ull) {
+            const int at = base + __ffsll(open) - 1;
+            if (__ballot(lane == 0 && tc_take(r, at) != r.launch) == 0ull) continue;
+            if (lane == 0) __hip_atomic_fetch_add(r.help.helped, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return at;
         }
-        if (lane == 0) *waited = all;
+    }
+    return TILE_GO;
+}
+// Waits until all tiles of the layer before are through, each counted in one of its words; of every thread: what to do (TILE_*).  taken: (of the first
+// thread) what tc_take said of its tile, looked at only here, as the answer is slow; helps: may take another tile meanwhile.
+__device__ __forceinline__ int tc_wait(const TileChain& r, int l, const int32_t* before_counts, int before_tiles, int polls, unsigned long long taken, bool helps, int* state) {
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x, want = (before_tiles - lane + TILE_LINES - 1) / TILE_LINES;       // of this lane's word
+        const int32_t* word = before_counts + min(lane, TILE_LINES - 1) * TILE_STRIDE;
+        asm volatile("" : "+v"(taken));
+        int got = __builtin_amdgcn_readfirstlane((int)(taken != r.launch)) ? TILE_GO : TILE_TAKEN, again = max(r.help.patience, 0);
+        if (got == TILE_GO && l > 0) {
+            got = TILE_GAVE_UP;
+            for (int i = 0; i < polls; ++i) {
+                const int n = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__ballot(lane < TILE_LINES && n != want) == 0ull) {
+                    got = TILE_GO;
+                    break;
+                }
+                if (__ballot(lane < TILE_LINES && n > want) != 0ull) break;
+                if (__builtin_expect(helps && i >= again, 0)) {
+                    int part = 0;                          // (the first of this layer)
+                    while (part + 1 < r.parts && (int)(r.start[part] >> 4 & 15) < l) ++part;
+                    const int at = tc_take_first(r, (int)(r.start[part] >> 8));
+                    if (at >= 0) {
+                        got = at;
+                        break;
+                    }
+                    again = i + TILE_AGAIN;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        if (lane == 0) *state = got;
     }
     asm volatile("" ::: "memory");
     __syncthreads();
-    return *waited != 0;
+    return __builtin_amdgcn_readfirstlane(*state);
 }
 // The end of a tile that others wait for (number: in its layer; counts: null where nobody does)
 __device__ __forceinline__ void tc_through(const TileChain& r, int32_t* counts, int number, bool there) {
@@ -1258,9 +1297,8 @@ __device__ __forceinline__ void tc_through(const TileChain& r, int32_t* counts, 
 }
 // A tile of a class's pooling, backward (pool.h: attention<true>, and smallest<true> for the offsets of boxes): a thread takes four coordinates of a member.
 template <bool OFFSETS>
-__device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TilePart& p, int tile, const int32_t* before_counts, int before_tiles, int polls,
-                                                 int32_t* counts, int* waited) {
-    if (tile >= p.tiles) return;
+__device__ __forceinline__ int tc_pool_backward(const TileChain& r, const TilePart& p, int tile, int l, const int32_t* before_counts, int before_tiles, int polls,
+                                                int32_t* counts, unsigned long long taken, bool helps, int* state) {
     const int d = r.d, d4 = d >> 2, k = p.cls, t = tile * TC_T + (int)threadIdx.x;
     const bool inside = t < p.n_mem * d4;
     const int i = min((int)__umulhi((uint32_t)t, p.inv_by), p.n_mem - 1), c = min(t - i * d4, d4 - 1) * 4;      // (inv_by: by d4)
@@ -1271,7 +1309,9 @@ __device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TileP
         a[j] = load_global4((OFFSETS ? r.Gate : r.Att) + at);
         x[j] = load_global4(r.Z[OFFSETS ? 2 : 1] + at);
     }
-    const bool there = before_counts ? tc_wait(before_counts, before_tiles, polls, waited) : true;
+    const int got = tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
+    if (got >= 0 || got == TILE_TAKEN) return got;
+    const bool there = got == TILE_GO;
     const float* from = (OFFSETS ? r.doff : r.dact) + (size_t)(p.out0 + i) * d + c;
     const float2 g0 = card_get2(from), g1 = card_get2(from + 2);
     auto one = [&](float g, auto of) {
@@ -1329,12 +1369,12 @@ __device__ __forceinline__ void tc_pool_backward(const TileChain& r, const TileP
         card_put2(dx + 2, x[j].z, x[j].w);
     }
     tc_through(r, counts, p.number + tile, there);
+    return TILE_GO;
 }
 // A tile of the projections of boxes (box.hip: proj_body), likewise.
 template <bool BWD>
-__device__ __forceinline__ void tc_box_projection(const TileChain& r, const TilePart& p, int tile, const int32_t* before_counts, int before_tiles, int polls,
-                                                  int32_t* counts, int* waited) {
-    if (tile >= p.tiles) return;
+__device__ __forceinline__ int tc_box_projection(const TileChain& r, const TilePart& p, int tile, int l, const int32_t* before_counts, int before_tiles, int polls,
+                                                 int32_t* counts, unsigned long long taken, bool helps, int* state) {
     const int d = r.d, d4 = d >> 2, t = tile * TC_T + (int)threadIdx.x;
     const bool inside = t < p.n_mem * d4;
     const int i = min((int)__umulhi((uint32_t)t, p.inv_by), p.n_mem - 1), c = min(t - i * d4, d4 - 1) * 4;
@@ -1350,7 +1390,9 @@ __device__ __forceinline__ void tc_box_projection(const TileChain& r, const Tile
         rc = load_global4(r.R + rel);
         ro = load_global4(r.Ro + rel);
     }
-    const bool there = before_counts ? tc_wait(before_counts, before_tiles, polls, waited) : true;
+    const int got = tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
+    if (got >= 0 || got == TILE_TAKEN) return got;
+    const bool there = got == TILE_GO;
     float *to_x, *to_o;
     if (BWD) {
         x = get(r.dact + out);
@@ -1377,23 +1419,27 @@ __device__ __forceinline__ void tc_box_projection(const TileChain& r, const Tile
         card_put2(to_o + 2, o.z, o.w);
     }
     tc_through(r, counts, p.number + tile, there);
+    return TILE_GO;
 }
 // BWD: the reverse.  An intersection's pooling is a layer of its own, four coordinates of a member a thread, ahead of its depth's other two.
+// The tile of workgroup `at`.  takes: the workgroup that runs it still has to take it; helps: may take another one while it waits.  Returns whose tile to
+// compute first (>= 0), or that this one is done with (TILE_GO) or somebody else's (TILE_TAKEN).
 template <bool BWD, bool BOX>
-__global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[TC_WAVES * TC_AHEAD * 2048];
-    __shared__ int waited;
-    static_assert(sizeof(lds) >= TC_WAVES * 32 * TC_LD * sizeof(float), "partial sums lie over the rows");
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+__device__ __forceinline__ int tc_tile(const TileChain& r, uint32_t at, bool helps, bool takes, unsigned char* lds, int* state) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));        // (where tiles are computed in a loop nothing that follows from it is kept from one to the next)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int layers = r.layers;
-    const uint32_t at = blockIdx.x;
     int32_t* const counts = r.chain;
     const int polls = r.sync.polls, d = r.d, h = r.h;
     float *const act1 = BWD ? r.dact : r.act, *const Dx1 = r.Dx, *const act2 = BWD ? r.doff : r.off, *const Dx2 = r.DxO;
     const float *const E = r.E, *const R = r.R;
     const int32_t *const refs = r.refs, *const rels = r.rel, *const out_row = r.out_row;
     const int keep = r.keep;
-    asm volatile("" ::"s"(counts), "s"(polls), "s"(d), "s"(h), "s"(act1), "s"(refs), "s"(layers));
+    unsigned long long* const words = r.taken;
+    const unsigned long long launch = r.launch;
+    const int patience = r.help.patience;
+    asm volatile("" ::"s"(counts), "s"(polls), "s"(d), "s"(h), "s"(act1), "s"(refs), "s"(layers), "s"(words), "s"(launch), "s"(patience));
     if (BOX) asm volatile("" ::"s"(act2), "s"(Dx2));
     if (BWD) asm volatile("" ::"s"(Dx1));
     else asm volatile("" ::"s"(E), "s"(R), "s"(rels), "s"(out_row), "s"(keep));
@@ -1414,19 +1460,21 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
     else asm volatile("" ::"s"(bias_of), "s"(Z));
     int32_t* const my_counts = l + 1 < layers ? counts + l * TILE_LAYER : nullptr;
     const int32_t* const before_counts = counts + (l - 1) * TILE_LAYER;
+    const int local = (int)(at - (start >> 8)), tile = (BWD || BOX) && kind == TILE_PLAIN ? local : (local & 7) * ((p.tiles + 7) >> 3) + (local >> 3);
+    unsigned long long taken = 0;
+    if (takes && my_counts && tid == 0) {
+        tile_late(r.help, (int)at, [&] { return tc_taken(r, (int)at); });
+        taken = tc_take(r, (int)at);
+    }
+    if (tile >= p.tiles) return TILE_GO;
     if ((BWD || BOX) && kind == TILE_PLAIN) {
-        const int tile = (int)(at - (start >> 8));
-        const int32_t* const words = l > 0 ? before_counts : nullptr;
-        if (BOX && type == 0) tc_box_projection<BWD>(r, p, tile, words, before_tiles, polls, my_counts, &waited);
-        else if (BOX && type == 2) tc_pool_backward<true>(r, p, tile, words, before_tiles, polls, my_counts, &waited);
-        else if (BWD) tc_pool_backward<false>(r, p, tile, words, before_tiles, polls, my_counts, &waited);
-        return;
+        if (BOX && type == 0) return tc_box_projection<BWD>(r, p, tile, l, before_counts, before_tiles, polls, my_counts, taken, helps, state);
+        if (BOX && type == 2) return tc_pool_backward<true>(r, p, tile, l, before_counts, before_tiles, polls, my_counts, taken, helps, state);
+        if (BWD) return tc_pool_backward<false>(r, p, tile, l, before_counts, before_tiles, polls, my_counts, taken, helps, state);
     }
     const bool offsets = BOX && type == 2;
     float *const act = offsets ? act2 : act1, *const Dx = offsets ? Dx2 : Dx1;
     const int K = second ? h : d, N = second ? d : h, tiles_n = (N + 31) >> 5;
-    const int local = (int)(at - (start >> 8)), tile = (local & 7) * ((p.tiles + 7) >> 3) + (local >> 3);
-    if (tile >= p.tiles) return;
     const int M = p.M, number = p.number + tile;
     const int quo = p.by == 1 ? tile : (int)__umulhi((uint32_t)tile, p.inv_by), rem = tile - quo * p.by;
     const int mt = p.m_major ? quo : rem, nt = p.m_major ? rem : quo, n0 = nt * 32;
@@ -1487,7 +1535,6 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
             for (int i = 0; i < 2; ++i) rel[j][i] = load_global4(row + min(min(block_of(0, j), nk - 1) * 16 + k_in + i * 4, K - 4));
     }
 
-    const bool there = l > 0 ? tc_wait(before_counts, before_tiles, polls, &waited) : true;
     const uint32_t at_a = lds_addr(lds) + wave * (TC_AHEAD * 2048);
     const int unit = ((lane & 3) ^ tile_swizzle(lane >> 2)) * 4;
     auto issue_a = [&](int blk, int j) {
@@ -1495,9 +1542,19 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
 #pragma unroll
         for (int i = 0; i < 2; ++i) lds_load16_card(arow[i] + k, at_a + j * 2048 + i * 1024);
     };
+    auto first_rows = [&] {
 #pragma unroll
-    for (int j = 0; j < TC_AHEAD; ++j)
-        if (block_of(0, j) < nk) issue_a(block_of(0, j), j);
+        for (int j = 0; j < TC_AHEAD; ++j)
+            if (block_of(0, j) < nk) issue_a(block_of(0, j), j);
+    };
+    if (l == 0) first_rows();        // (wait for no layer)
+    const int got = tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
+    if (got >= 0 || got == TILE_TAKEN) {
+        wait_vm<0>();
+        return got;
+    }
+    const bool there = got == TILE_GO;
+    if (l > 0) first_rows();
     if (pooled) {
 #pragma unroll
         for (int j = 0; j < TILE_CARD; ++j) {
@@ -1624,6 +1681,25 @@ __global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) 
     float* const rows_out = BWD ? dH : H;
     if (inside) card_put2((second ? act + (size_t)orow * d : rows_out + (size_t)orow * h) + n0 + lc, o0, o1);
     tc_through(r, my_counts, number, there);
+    return TILE_GO;
+}
+template <bool BWD, bool BOX>
+__global__ __launch_bounds__(TC_T, 4) void tile_chain_kernel(const TileChain r) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[TC_WAVES * TC_AHEAD * 2048];
+    __shared__ int state;
+    static_assert(sizeof(lds) >= TC_WAVES * 32 * TC_LD * sizeof(float), "partial sums lie over the rows");
+    int other = tc_tile<BWD, BOX>(r, blockIdx.x, true, true, lds, &state);
+    if (__builtin_expect(other < 0, 1)) return;
+    // (code of its own: around the tile above this loop would cost it 20 vector registers more than there are)
+#pragma clang loop unroll(disable)
+    for (;;) {
+        __syncthreads();
+        int again = 0;               // (and no argument is kept from tile to tile)
+        asm volatile("" : "+s"(again));
+        const bool own = other < 0;
+        other = tc_tile<BWD, BOX>((&r)[again], own ? blockIdx.x : (uint32_t)other, own, false, lds, &state);
+        if (own && other < 0) return;
+    }
 }
 
 // Forward layers of very few rows (a handful of queries): a matrix-vector product per row.  The time is reading
@@ -2011,7 +2087,7 @@ bool tile_chain_lay_out(TileChain& r, const TileProblem (*problems)[TILE_PROBLEM
                 r.start[r.parts++] = (uint32_t)blocks << 8 | layer << 4 | p.type << 2 | kind;
                 tiles += t.tiles;
                 blocks += (t.tiles + 7) / 8 * 8;
-                if (blocks >= 1 << 20) return false;
+                if (blocks > TILE_WORDS) return false;
             }
             if (tiles == 0) continue;                // (a depth without intersections)
             r.tiles[r.layers++] = tiles;
@@ -2023,7 +2099,7 @@ bool tile_chain_lay_out(TileChain& r, const TileProblem (*problems)[TILE_PROBLEM
 }
 
 hipError_t launch_tile_chain(const TileChain& r, bool backward, bool box, hipStream_t s) {
-    if (!r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.blocks < 1 || r.parts < 1) return hipErrorInvalidValue;
+    if (!r.chain || !r.taken || !r.help.helped || !r.sync.gave_up || !r.sync.host_gave_up || r.blocks < 1 || r.blocks > TILE_WORDS || r.parts < 1) return hipErrorInvalidValue;
     const dim3 grid(r.blocks), block(TC_T);
     if (box && backward) hipLaunchKernelGGL((tile_chain_kernel<true, true>), grid, block, 0, s, r);
     else if (box) hipLaunchKernelGGL((tile_chain_kernel<false, true>), grid, block, 0, s, r);

@@ -481,38 +481,68 @@ __global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
 // is spared too: the references travel as arguments and one more workgroup copies the plan for whoever follows.  A tile requests its weights,
 // all of them, before it waits for the layer before; what an intersection pools are its tile's own columns.  Rows and values of one layer
 // reach the next as in levels_kernel, and a wait ends like there; a tile that gave up leaves NaN, and so does then every tile of the layers behind it.
-// Tiles are dealt by workgroup number: a die starts its workgroups in order, so that a tile waits only for tiles that started
-// before it on its own die or need nothing of that die.  What is counted are the tiles through of a layer, in CHAIN_LINES words on lines
-// of their own: tickets from one word and counts in another, taken by a few hundred workgroups one after the other, were 14 us a layer.
-// A layer's first tile clears the words of the layer but one before (whoever waited for those is through); those of the last but one are
-// cleared by whoever is the last to get past its wait for them.  Scoring at d = 400, h = 800, a launch a layer and like this, us a call (the host of
+// Tiles are dealt by workgroup number (TileHelp), and a tile that is through says so by a bit of a word that few others share: tickets and counts, each in one word taken by a few
+// hundred workgroups one after the other, were 14 us a layer; a tile that is taken before it is worked on costs the launch 3 us, a word a tile 1.
+// Scoring at d = 400, h = 800, a launch a layer and like this, us a call (the host of
 // the machine between 38 and 50 us for the former): one query 38 to 50 and 32, of it 24 this launch for three depths, four 40 to 50 and 38, eight 44 to 54
 // and 42; one at 512, 1024 37 to 50 and 33, eight at 132, 260 41 to 53 and 32.
-constexpr int CHAIN_ROWS = 4, CHAIN_COLS = 4, CHAIN_T = 256, CHAIN_LINES = 8, CHAIN_STRIDE = 32;
+constexpr int CHAIN_ROWS = 4, CHAIN_COLS = 4, CHAIN_T = 256;
 constexpr int CHAIN_TILES = 2048;
-static_assert(CHAIN_CARD <= CHAIN_ROWS && CHAIN_ROWS * CHAIN_COLS <= 64 && CHAIN_TILES < GAVE_UP, "an intersection is a tile, its sums a lane each");
-static_assert(CHAIN_SYNC == (2 * LEVEL_CHAIN * CHAIN_LINES + 1) * CHAIN_STRIDE, "the words of all layers and of those past the last wait");
+static_assert(CHAIN_CARD <= CHAIN_ROWS && CHAIN_ROWS * CHAIN_COLS <= 64, "an intersection is a tile, its sums a lane each");
 __host__ __device__ inline int chain_row_groups(const RowsProblem& p, bool second) {
     return second && p.k > 1 ? p.n : (p.n * p.k + CHAIN_ROWS - 1) / CHAIN_ROWS;
 }
 __host__ __device__ inline int chain_col_groups(int n) { return (n + 4 * CHAIN_COLS - 1) / (4 * CHAIN_COLS); }
-__global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) {
-    extern __shared__ __attribute__((aligned(16))) float lds[];      // [CHAIN_ROWS][K]
-    __shared__ int waited;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int layers = 2 * r.depths, at = (int)blockIdx.x;
-    if (at == r.first[layers]) {                  // (only where there is something to copy)
-        for (int i = threadIdx.x; i < r.copy.n; i += CHAIN_T) r.copy.dst[i] = r.copy.src[i];
-        return;
+// The bits of a lane's word once all `tiles` of a layer are through
+__device__ __forceinline__ unsigned long long rows_all(int tiles, int lane) {
+    return lane < CHAIN_LINES && lane < tiles ? (CHAIN_GAVE_UP - 1ull) >> (CHAIN_BITS - (tiles - lane + CHAIN_LINES - 1) / CHAIN_LINES) : 0ull;
+}
+__device__ __forceinline__ unsigned long long rows_word(const unsigned long long* layer, int line) {
+    return __hip_atomic_load(layer + min(line, CHAIN_LINES - 1) * CHAIN_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Waits until all tiles of the layer before l are through (helps: or there is one to compute meanwhile): TILE_GO, TILE_GAVE_UP or whose tile that is.  By one
+// wavefront.
+__device__ __forceinline__ int rows_wait(const RowsChain& r, const unsigned long long* through, int l, int polls, bool helps) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long want = rows_all(r.first[l] - r.first[l - 1], lane);
+    int again = max(r.help.patience, 0);
+    for (int i = 0; i < polls; ++i) {
+        const unsigned long long now = rows_word(through + (l - 1) * CHAIN_LAYER, lane);
+        if (__ballot(lane < CHAIN_LINES && now != want) == 0ull) return TILE_GO;
+        if (__ballot(now >= CHAIN_GAVE_UP) != 0ull) break;
+        if (__builtin_expect(helps && i >= again, 0)) {
+            for (int m = 0; m < l; ++m) {        // (the first layer that is not through: it waits for nothing)
+                const unsigned long long open = rows_all(r.first[m + 1] - r.first[m], lane) & ~rows_word(through + m * CHAIN_LAYER, lane);
+                unsigned long long lines = __ballot(open != 0ull);
+                if (lines == 0ull) continue;
+                for (int skip = (int)blockIdx.x % __popcll(lines); skip > 0; --skip) lines &= lines - 1ull;       // (not all the same one)
+                const int line = __ffsll(lines) - 1, bit = __builtin_amdgcn_readlane(__ffsll(open) - 1, line);
+                if (lane == 0) __hip_atomic_fetch_add(r.help.helped, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return r.first[m] + bit * CHAIN_LINES + line;
+            }
+            again = i + TILE_AGAIN;
+        }
+        __builtin_amdgcn_s_sleep(1);
     }
-    int32_t* const counts = r.chain;
+    return TILE_GAVE_UP;
+}
+// The tile of workgroup `at`.  first: the workgroup that runs it begins with it; helps: may leave it for another one while it waits.  Returns whose tile to
+// compute first (>= 0), or TILE_GO: done.
+__device__ __forceinline__ int rows_tile(const RowsChain& r, int at, bool helps, bool first, float* lds, int* state) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));        // (where tiles are computed in a loop nothing that follows from it is kept from one to the next)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int layers = 2 * r.depths;
     const int polls = r.sync.polls;
-    asm volatile("" ::"s"(counts), "s"(polls));
+    unsigned long long* const through = r.through;
+    asm volatile("" ::"s"(polls), "s"(through));
     int l = 0;                       // layer: 2 * depth, and one more for the second of the depth
     for (int i = 1; i < layers; ++i)
         if (at >= r.first[i]) l = i;
     const bool second = l & 1;
     const int K = second ? r.h : r.d, N = second ? r.d : r.h, cols = chain_col_groups(N), in_layer = at - r.first[l];
+    if (first && l + 1 < layers)
+        tile_late(r.help, at, [&] { return (rows_word(through + l * CHAIN_LAYER, in_layer % CHAIN_LINES) >> (in_layer / CHAIN_LINES) & 1ull) != 0ull; });
     int tile = in_layer, q = 0;
     for (; q + 1 < r.count[l >> 1]; ++q) {
         const int n = chain_row_groups(r.p[l >> 1][q], second) * cols;
@@ -551,23 +581,14 @@ __global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) 
         if (related && c * 64 < k4) y[c] = *reinterpret_cast<const float4*>(rel + k);
         if (ref < 0 && c * 64 < k4) x[c] = *reinterpret_cast<const float4*>(r.E + (size_t)(-1 - ref) * K + k);
     }
-    bool there = true;
+    int got = TILE_GO;
     if (l > 0) {
         if (wave == 0) {
-            const int tiles = r.first[l] - r.first[l - 1], want = (tiles - lane + CHAIN_LINES - 1) / CHAIN_LINES;       // of this lane's word
-            const int32_t* word = counts + ((l - 1) * CHAIN_LINES + min(lane, CHAIN_LINES - 1)) * CHAIN_STRIDE;
-            bool all = false;
-            for (int i = 0; i < polls; ++i) {
-                const int n = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                all = __ballot(lane < CHAIN_LINES && n != want) == 0ull;
-                if (all || __ballot(lane < CHAIN_LINES && n > want) != 0ull) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-            if (lane == 0) waited = all;
+            got = rows_wait(r, through, l, polls, helps);
+            if (lane == 0) *state = got;
         }
         asm volatile("" ::: "memory");
         __syncthreads();
-        there = waited != 0;
     }
     if (ref >= 0) {
         const float* row = second ? r.H[p.type] + (size_t)(p.row0 + mine) * K : r.act + (size_t)ref * K;
@@ -577,17 +598,11 @@ __global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) 
     }
     float input = 0.f;
     if (pooled) input = row_get1<true>(r.Z + (size_t)(p.row0 + row_lo + min(lane / CHAIN_COLS, p.k - 1) * row_step) * r.d + min(col, N - 1));
-    // (the clearing, beside the loads)
-    if (there && l >= 2 && in_layer == 0 && threadIdx.x < CHAIN_LINES)
-        __hip_atomic_store(counts + ((l - 2) * CHAIN_LINES + threadIdx.x) * CHAIN_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (there && l + 1 == layers && threadIdx.x == CHAIN_T - 1) {
-        int32_t* past = counts + 2 * LEVEL_CHAIN * CHAIN_LINES * CHAIN_STRIDE;
-        if (__hip_atomic_fetch_add(past, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == r.first[layers] - r.first[l] - 1) {
-            __hip_atomic_store(past, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (int i = 0; i < CHAIN_LINES; ++i)
-                __hip_atomic_store(counts + ((l - 1) * CHAIN_LINES + i) * CHAIN_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    if (l > 0) {                     // (looked at when the rows are requested)
+        got = __builtin_amdgcn_readfirstlane(*state);
+        if (got >= 0) return got;
     }
+    const bool there = got == TILE_GO;
     if (wave < M) {
 #pragma unroll
         for (int c = 0; c < CHAIN_WIDTH / 256; ++c) {
@@ -644,13 +659,39 @@ __global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) 
     if (lane < (pooled ? 1 : M) * CHAIN_COLS && col < N) row_put1<true>(to, out);
     wait_vm<0>();                    // this wavefront's values are where the next layer finds them,
     __syncthreads();                 // ... and everybody's
-    if (threadIdx.x != 0) return;
-    if (!there) {
-        __hip_atomic_store(r.sync.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(r.sync.host_gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (tid == 0) {
+        if (!there) {
+            __hip_atomic_store(r.sync.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(r.sync.host_gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        if (l + 1 < layers)
+            __hip_atomic_fetch_or(through + l * CHAIN_LAYER + in_layer % CHAIN_LINES * CHAIN_STRIDE, there ? 1ull << (in_layer / CHAIN_LINES) : CHAIN_GAVE_UP, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (l + 1 < layers)
-        __hip_atomic_fetch_add(counts + (l * CHAIN_LINES + in_layer % CHAIN_LINES) * CHAIN_STRIDE, there ? 1 : GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return TILE_GO;
+}
+__global__ __launch_bounds__(CHAIN_T) void rows_chain_kernel(const RowsChain r) {
+    extern __shared__ __attribute__((aligned(16))) float lds[];      // [CHAIN_ROWS][K]
+    __shared__ int state;
+    const int own = (int)blockIdx.x;
+    if (own == r.first[2 * r.depths]) {           // (only where there is something to copy)
+        for (int i = threadIdx.x; i < r.copy.n; i += CHAIN_T) r.copy.dst[i] = r.copy.src[i];
+        return;
+    }
+    if (own + 1 == r.first[2 * r.depths])         // (a tile that has time)
+        for (int i = threadIdx.x; i < 2 * LEVEL_CHAIN * CHAIN_LINES; i += CHAIN_T) r.clear[i * CHAIN_STRIDE] = 0ull;
+    int other = rows_tile(r, own, true, true, lds, &state);
+    if (__builtin_expect(other < 0, 1)) return;
+    // (code of its own: around the tile above this loop would cost it registers)
+#pragma clang loop unroll(disable)
+    for (;;) {
+        __syncthreads();
+        int again = 0;               // (and no argument is kept from tile to tile)
+        asm volatile("" : "+s"(again));
+        const bool home = other < 0;
+        other = rows_tile((&r)[again], home ? own : other, home, false, lds, &state);
+        if (home && other < 0) return;
+    }
 }
 
 size_t lv_lds(int d, int h) { return ((size_t)LV_ROWS * (2 * lv_pitch(d) + lv_pitch(h)) + d + h) * sizeof(float); }
@@ -683,10 +724,11 @@ hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
 
 hipError_t launch_rows_chain(RowsChain& r, hipStream_t s) {
     if (r.depths < 1 || r.depths > LEVEL_CHAIN || r.d < 4 || r.h < 4 || (r.d & 3) || (r.h & 3) || std::max(r.d, r.h) > CHAIN_WIDTH || r.n_words > CHAIN_WORDS ||
-        !r.chain || !r.sync.gave_up || !r.sync.host_gave_up || r.copy.n < 0 || (r.copy.n > 0 && (!r.copy.src || !r.copy.dst)))
+        !r.through || !r.clear || !r.help.helped || !r.sync.gave_up || !r.sync.host_gave_up || r.copy.n < 0 || (r.copy.n > 0 && (!r.copy.src || !r.copy.dst)))
         return hipErrorInvalidValue;
     int tiles = 0;
     for (int l = 0; l < 2 * r.depths; ++l) {
+        if (l > 0 && tiles - r.first[l - 1] > CHAIN_LINES * CHAIN_BITS) return hipErrorInvalidValue;
         r.first[l] = tiles;
         if (r.count[l >> 1] < 1 || r.count[l >> 1] > CHAIN_PROBLEMS) return hipErrorInvalidValue;
         for (int q = 0; q < r.count[l >> 1]; ++q) {

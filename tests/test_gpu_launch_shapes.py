@@ -424,11 +424,57 @@ def test_layers_of_some_rows_that_give_up_waiting():
     plan.free()
 
 
-# ... two contexts on two streams, calls of both under way at a time: each as it is alone
-def test_layers_of_some_rows_on_two_streams():
+def chain_launches(eng):
+    """Launches of several layers so far (few rows, forward, backward), and their tiles that were computed by a workgroup with another one."""
+    from paper_2602_21597_amd import binding
+    n = [binding.lib().ngdb_debug_chain_launches(eng.ctx, kind) for kind in range(4)]
+    assert min(n) >= 0
+    return np.array(n)
+
+
+# ... every eighth workgroup late (some milliseconds, or until its tile is taken): the others compute its tiles, each once, and the results are the same bits.  A
+# handful of queries and more, both families and directions, launches of more workgroups than the card holds; and as it is by default, calls in a row
+@pytest.mark.parametrize("box,d,h,B", [(False, 400, 800, 3), (False, 132, 260, 5), (False, 400, 800, 40), (False, 260, 516, 170), (False, 512, 1024, 50),
+                                       (True, 300, 500, 40), (True, 160, 320, 130)])
+def test_tiles_of_workgroups_that_start_late(box, d, h, B):
     import torch
-    from paper_2602_21597_amd import Engine
-    N, R, B = 900, 9, 60
+    from paper_2602_21597_amd import Engine, binding
+    rng = np.random.default_rng(d + B)
+    N, R = 900, 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    kinds = [lambda: proj(proj()), lambda: proj(("i", proj(), proj())), lambda: ("i", proj(), proj(proj()), proj()), lambda: ("u", proj(), proj(proj()))]
+    qb = wl.batch_from_trees([kinds[i % 4]() for i in range(B)], [int(x) for x in rng.integers(0, N, B)])
+    cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    params = (wl.make_box_params if box else wl.make_params)(N, R, d, h, 6)
+    eng = Engine(N, R, d, h, 8.0, family=binding.FAMILY_BOX if box else binding.FAMILY_VEC)
+    few = not box and B <= 16
+    out, helped = [], []
+    for polls, patience in ((-1, 1024), (1 << 22, -4096), (1 << 22, 0), (1 << 22, 1024)):
+        assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
+        assert binding.lib().ngdb_debug_chain_patience(eng.ctx, patience) == 0
+        eng.bind_numpy(params)
+        plan = eng.plan(qb)
+        before = chain_launches(eng)
+        got = [eng.score(plan, cand).clone() for _ in range(3)]
+        if not few:
+            got += [eng.train_step(plan, cand).clone() for _ in range(2)] + [t[0].clone() for t in eng.tensors.values()]
+        torch.cuda.synchronize()
+        plan.free()
+        out.append(got)
+        new = chain_launches(eng) - before
+        assert list(new[:3]) == ([0, 0, 0] if polls < 0 else [3, 0, 0] if few else [0, 5, 2])
+        helped.append(new[3])
+    assert all(torch.equal(a, b) for got in out[1:] for a, b in zip(got, out[0]))
+    assert helped[0] == 0 and helped[1] > 0
+
+
+# ... two contexts on two streams, calls of both under way at a time: each as it is alone, in launches of several layers all the same
+@pytest.mark.parametrize("patience", [1024, 0])
+@pytest.mark.parametrize("B", [60, 2])
+def test_layers_of_some_rows_on_two_streams(B, patience):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R = 900, 9
     rng = np.random.default_rng(6)
     proj = lambda: ("p", int(rng.integers(R)), ("p", int(rng.integers(R)), ("e", int(rng.integers(N)))))
     cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
@@ -436,9 +482,11 @@ def test_layers_of_some_rows_on_two_streams():
     for d, h in ((260, 516), (300, 400)):
         eng = Engine(N, R, d, h, 8.0)
         eng.bind_numpy(wl.make_params(N, R, d, h, 6))
+        assert binding.lib().ngdb_debug_chain_patience(eng.ctx, patience) == 0
         plan = eng.plan(wl.batch_from_trees([("i", proj(), proj()) for _ in range(B)], [0] * B))
         sides.append((eng, plan, torch.cuda.Stream(), eng.score(plan, cand).clone()))
     torch.cuda.synchronize()
+    before = [chain_launches(eng)[:2].sum() for eng, _, _, _ in sides]
     got = []
     for _ in range(20):
         for eng, plan, stream, want in sides:
@@ -446,6 +494,7 @@ def test_layers_of_some_rows_on_two_streams():
                 got.append((eng.score(plan, cand), want))
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in got)
+    assert [chain_launches(eng)[:2].sum() - n for (eng, _, _, _), n in zip(sides, before)] == [20, 20]
     for eng, plan, _, _ in sides:
         plan.free()
 
@@ -463,9 +512,11 @@ def test_layers_of_some_rows_captured():
     cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
     plan, other = eng.plan(qb), eng.plan(qb.select(np.arange(25)))
     want = eng.score(plan, cand).clone()
+    before = chain_launches(eng)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         out = eng.score(plan, cand)
+    assert (chain_launches(eng) == before).all()           # (replays have no launch numbers of their own)
     for _ in range(4):
         out.zero_()
         graph.replay()
