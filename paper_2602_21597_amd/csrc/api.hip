@@ -273,6 +273,7 @@ LevelSync level_sync(const ngdb_ctx_t* c) {
     y.counts = ptr<int32_t>(c->sync); y.gave_up = y.counts + LEVEL_SYNC; y.host_gave_up = c->gave_up; y.polls = c->chain_polls;
     return y;
 }
+const int32_t* gave_up_mark(const ngdb_ctx_t* c) { return ptr<int32_t>(c->sync) + LEVEL_SYNC; }
 TileHelp tile_help(const ngdb_ctx_t* c) {
     TileHelp t;
     t.helped = ptr<int32_t>(c->sync) + HELPED_AT; t.patience = c->chain_patience;
@@ -1529,7 +1530,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     sa.act = ptr<float>(c->act); sa.E = scored.rows; candidate_table(c, &sa);
     sa.root_off = pl->d_root_off; sa.root_slot = pl->d_root_slot;
     sa.pos = scored.pos; sa.cand = scored.cand; sa.B = B; sa.C = K; sa.d = d; sa.max_branch = std::max(1, hp.max_branch);
-    sa.gamma = c->cfg.gamma; sa.score = ptr<float>(c->score); sa.coef = ptr<float>(c->coef);
+    sa.gave_up = gave_up_mark(c); sa.gamma = c->cfg.gamma; sa.score = ptr<float>(c->score); sa.coef = ptr<float>(c->coef);
     sa.win = sem ? nullptr : ptr<int32_t>(c->win); sa.mask = sem ? c->mask.p : nullptr; sa.dact = ptr<float>(c->dact); sa.loss_terms = ptr<float>(c->loss_terms);
     if (box) { sa.off = ptr<float>(c->off); sa.doff = ptr<float>(c->doff); sa.alpha = c->cfg.box_alpha; }
     if (c->cfg.score_bf16) sa.E16 = ptr<uint16_t>(c->Eb);
@@ -1556,7 +1557,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     AdamHyper ah{c->cfg.lr, c->cfg.beta1, c->cfg.beta2, c->cfg.eps,
                  (float)(1.0 - std::pow((double)c->cfg.beta1, (double)t)),
                  (float)(1.0 - std::pow((double)c->cfg.beta2, (double)t))};
-    if (c->chained) ah.gave_up = level_sync(c).gave_up;
+    if (c->chained) ah.gave_up = gave_up_mark(c);
     TableArgs te{};
     te.P = c->prm.E.p; te.Mo = c->prm.E.m; te.Vo = c->prm.E.v;
     te.uniq = ptr<int32_t>(c->uniq); te.seg_off = ptr<int32_t>(c->seg_off);
@@ -1603,7 +1604,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     WgradJob wj;
     rc = enqueue_backward(c, pl, stream, &wj);
     if (rc != NGDB_OK) return rc;
-    if (c->chained) ah.gave_up = level_sync(c).gave_up;
+    if (c->chained) ah.gave_up = gave_up_mark(c);
 
     rc = enqueue_weight_grads(c, wj, stream, aside && !short_pass);
     if (rc != NGDB_OK) return rc;
@@ -1799,6 +1800,7 @@ size_t rank_filter_layout(const ngdb_ctx_t* c, int bits, int R, int B, int chunk
     place(f->found_pair, bits == 8 ? rank_found_bytes(f->ldy, f->lde) / 4 : 0);
     place(f->count, f->n_counters);
     f->overflowed = base ? f->count + n_lists : nullptr;
+    f->gave_up = gave_up_mark(c);
     return at * 4;
 }
 
@@ -1917,7 +1919,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         HIPCHK(c, launch_pick(f, sums, ld, act, roots, pl->d_root_off, B, er.rows, er.rows16, N, topk, d_dist, d_ids, s));
         only.any = f.overflowed;
         HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, N, d, dist, ld, s, er.rows16, &only));
-        HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, 0, N, topk, false, d_dist, d_ids, s, &only));
+        HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, 0, N, topk, false, d_dist, d_ids, gave_up_mark(c), s, &only));
         c->rank_chunks = (N + RANK_CHUNK - 1) / RANK_CHUNK;
         return NGDB_OK;
     }
@@ -1933,7 +1935,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
         if ((rc = rank_chunk_rows(c, e0, cnt, filtered && e0 == 0, rounded ? &f : nullptr, s, &er)) != NGDB_OK) return rc;
         if (!rounded) {
             HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows, cnt, d, dist, ld, s, er.rows16));
-            HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, s));
+            HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0, cnt, topk, e0 == 0, d_dist, d_ids, gave_up_mark(c), s));
             if (filtered && (rc = rank_filter_begin(c, f, er.sample, s)) != NGDB_OK) return rc;
             ++i_piece;
         } else {
@@ -1947,7 +1949,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
                 only.count = f.count + (size_t)(p0 / RANK_CHUNK) * B;
                 only.any = f.overflowed + i_piece;
                 HIPCHK(c, launch_l1_tile(act, box_off, c->cfg.box_alpha, roots, R, er.rows + at, n, d, dist, ld, s, er.rows16 ? er.rows16 + at : nullptr, &only));
-                HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0 + p0, n, topk, false, d_dist, d_ids, s, &only));
+                HIPCHK(c, launch_topk_merge(dist, ld, pl->d_root_off, B, e0 + p0, n, topk, false, d_dist, d_ids, gave_up_mark(c), s, &only));
                 i_piece += (n + RANK_CHUNK - 1) / RANK_CHUNK;
             }
         }
@@ -1998,7 +2000,7 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
             ans_rows = ptr<float>(c->rank_ef);
         }
         HIPCHK(c, launch_answer_distance(act, box_off, c->cfg.box_alpha, roots, pl->d_root_off, d_ans_off, B, sem ? nullptr : d_ans, a0, cnt,
-                                         ans_rows, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr, d, thr, total, n_ans, s));
+                                         ans_rows, c->cfg.score_bf16 ? ptr<uint16_t>(c->Eb) : nullptr, d, gave_up_mark(c), thr, total, n_ans, s));
     }
     // entities strictly closer than each answer, chunk by chunk
     for (int e0 = 0; e0 < N; e0 += chunk) {
@@ -2019,7 +2021,7 @@ int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, cons
         HIPCHK(c, launch_count_less(dist, ld, pl->d_root_off, d_ans_off, thr, B, cnt, total, s, filtered ? &only : nullptr));
         if (filtered && e0 + cnt < N) HIPCHK(c, launch_fill_zero_i32(f.count, B, s));
     }
-    HIPCHK(c, launch_finish_rank(total, thr, d_ans_off, B, n_ans, c->chained ? level_sync(c).gave_up : nullptr, d_rank, s));
+    HIPCHK(c, launch_finish_rank(total, thr, d_ans_off, B, n_ans, gave_up_mark(c), d_rank, s));
     return NGDB_OK;
 }
 
@@ -2426,7 +2428,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
         sa.act = ptr<float>(c->act); sa.E = er.rows; candidate_table(c, &sa);
         sa.root_off = pl->d_root_off; sa.root_slot = roots;
         sa.pos = nullptr; sa.cand = er.cand; sa.B = pl->hp.n_queries; sa.C = C; sa.d = c->cfg.d;
-        sa.max_branch = std::max(1, pl->hp.max_branch); sa.gamma = c->cfg.gamma; sa.score = d_scores;
+        sa.max_branch = std::max(1, pl->hp.max_branch); sa.gave_up = gave_up_mark(c); sa.gamma = c->cfg.gamma; sa.score = d_scores;
         if (c->cfg.family == NGDB_FAMILY_BOX) { sa.off = ptr<float>(c->off); sa.alpha = c->cfg.box_alpha; }
         if (c->cfg.score_bf16) sa.E16 = ptr<uint16_t>(c->Eb);
         hipError_t e;
@@ -2499,7 +2501,7 @@ int ngdb_score_noalloc(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_ca
         sa.act = w.act; sa.E = er.rows; candidate_table(c, &sa);
         sa.root_off = pl->d_root_off; sa.root_slot = pl->d_f_root;
         sa.pos = nullptr; sa.cand = d_cand; sa.B = hp.n_queries; sa.C = C; sa.d = c->cfg.d;
-        sa.max_branch = std::max(1, hp.max_branch); sa.gamma = c->cfg.gamma; sa.score = d_scores;
+        sa.max_branch = std::max(1, hp.max_branch); sa.gave_up = gave_up_mark(c); sa.gamma = c->cfg.gamma; sa.score = d_scores;
         if (c->cfg.score_bf16) sa.E16 = ptr<uint16_t>(c->Eb);
         const hipError_t e = launch_score(sa, false, s);
         if (e == hipErrorInvalidValue) rc = fail(c, NGDB_ERR_UNSUPPORTED, "embedding width / union branch count too large for the scoring kernel");

@@ -375,7 +375,7 @@ hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s);
 struct SmallIndex;
 constexpr int LEVEL_CHAIN = 4, LEVEL_CHAIN_TILES = 256, LEVEL_SYNC = 2 + LEVEL_CHAIN;
 // What such launches share: counts, zero, and zero again behind each of them, and what is set for good once one of them has given up
-// waiting for a depth (its results are not valid then: forward passes leave rows of NaN in the end).
+// waiting for a depth: rows are not valid then, whatever is computed from them, and launches that hand out results look at the mark instead.
 struct LevelSync {
     int32_t* counts = nullptr;      // LEVEL_SYNC words
     int32_t* gave_up = nullptr;     // a word on the device, for the launches that follow
@@ -510,6 +510,7 @@ struct ScoreArgs {
     // candidate rows from a bf16 copy of the table [N, d] (bit patterns) instead of E
     const uint16_t* E16 = nullptr;
     bool streaming = false;    // E is a table beyond the caches
+    const int32_t* gave_up = nullptr;      // as LevelSync: scores are minus infinity if it is set
     size_t table_bytes = 0;    // of the candidates' rows
 };
 hipError_t launch_score(const ScoreArgs& a, bool train, hipStream_t s);
@@ -537,7 +538,7 @@ hipError_t launch_l1_tile(const float* act, const float* off, float alpha, const
 hipError_t launch_count_less(const float* dist, int ld, const int32_t* root_off, const int32_t* ans_off,
                              const float* thr, int n_queries, int n_ent, int32_t* count, hipStream_t s,
                              const Overflowed* only = nullptr);
-// rank[a] = 1 + count[a] - #{listed answers b of a's query: thr[b] < thr[a]}; 0 if *gave_up (null: none) is set
+// rank[a] = 1 + count[a] - #{listed answers b of a's query: thr[b] < thr[a]}; 0 if *gave_up is set
 hipError_t launch_finish_rank(const int32_t* count, const float* thr, const int32_t* ans_off, int n_queries, int n_ans,
                               const int32_t* gave_up, int32_t* rank, hipStream_t s);
 // out[0..3] = MRR, Hit@1, Hit@3, Hit@10 over the first n_take[q] (null: all) answers of every query
@@ -547,7 +548,7 @@ hipError_t launch_fill_zero_i32(int32_t* p, int n, hipStream_t s);
 // per query q: entity value = min over rows root_off[q]..root_off[q+1]-1 of dist; merges the
 // k best (value, ent_base + e) of this chunk into out_dist/out_ids [n_queries, k]
 hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off, int n_queries, int ent_base, int n_ent,
-                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s,
+                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, const int32_t* gave_up, hipStream_t s,
                              const Overflowed* only = nullptr);
 
 // Ranking with a filter on integer sums (rank_filter.hip): buffers of one pass.  Rows as words of 4
@@ -567,6 +568,7 @@ struct RankFilter {
     int32_t *list, *count; int room;
     int32_t* overflowed;             // per piece of the pass: a list had no room (behind count: n_counters in all, cleared with the grid)
     int n_counters;
+    const int32_t* gave_up;          // nobody is near if this word is set
 };
 int rank_filter_words(int d, int bits);
 size_t rank_found_bytes(int ldy, int lde);
@@ -596,7 +598,7 @@ hipError_t launch_count_open(const RankFilter& f, int chunk, const uint32_t* sum
 // counters[a] = counters[n_ans + a] = 0 for them
 hipError_t launch_answer_distance(const float* act, const float* off, float alpha, const int32_t* row_ids, const int32_t* root_off,
                                   const int32_t* ans_off, int n_queries, const int32_t* ans, int a0, int cnt, const float* E,
-                                  const uint16_t* E16, int d, float* thr, int32_t* counters, int n_ans, hipStream_t s);
+                                  const uint16_t* E16, int d, const int32_t* gave_up, float* thr, int32_t* counters, int n_ans, hipStream_t s);
 
 // ---------------------------------------------------------------- index (index.hip)
 struct IndexBuffers {   // device scratch owned by the context, sized for n_keys

@@ -414,20 +414,6 @@ struct LevelRun {                   // the first depth's tiles stand in a
     PlanCopy copy;                  // (n: 0 without one)
 };
 static_assert(LV_T == SMALL_THREADS, "the index of few keys is a workgroup's job here too");
-// Every output row of all depths becomes NaN, centres of boxes and offsets alike (one thread: a pass that gave up waiting)
-__device__ void no_rows(const LevelRun& r) {
-    for (int l = 0; l < r.n; ++l) {
-        const LevelTiles& t = l == 0 ? r.a.t : r.more[l - 1];
-        for (int q = 0; q < t.count; ++q)
-            for (int i = 0; i < t.p[q].n; ++i) {
-                const size_t o = r.a.out_row ? r.a.out_row[t.p[q].out0 + i] : t.p[q].out0 + i;
-                for (int c = 0; c < r.a.d; ++c) {
-                    r.a.act[o * r.a.d + c] = NAN;
-                    if (r.a.off) r.a.off[o * r.a.d + c] = NAN;
-                }
-            }
-    }
-}
 // INDEX: the first workgroup builds the gradient index meanwhile, which nothing here reads.  A launch of its own for it was 5 to 10 us
 // of a small step (64 x 8 at 32, 64 68.0 -> 62.6 us, 64 x 16 at 100, 200 130 -> 120, 16 x 4 boxes at 64, 64 66 -> 56).
 template <bool BWD, bool BOX, bool INDEX>
@@ -470,10 +456,8 @@ __global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
     // still be on its way when they are cleared.  In a pass that gave up one can: nothing is launched on these counts any more)
     if (l + 1 < r.n) __hip_atomic_fetch_add(counts + 2 + l, there ? 1 : GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // the last one through leaves the counts as they were found
-    const int32_t before = __hip_atomic_fetch_add(counts + 1, there ? 1 : GAVE_UP + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((before & (GAVE_UP - 1)) != r.first[r.n] - 1) return;
+    if (__hip_atomic_fetch_add(counts + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != r.first[r.n] - 1) return;
     for (int i = 0; i < LEVEL_SYNC; ++i) __hip_atomic_store(counts + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!BWD && (before >= GAVE_UP || !there)) no_rows(r);
 }
 
 // The forward pass of a handful of queries (every layer has a few rows only: gemm.hip's rows_kernel, whose sums these are): all layers of

@@ -199,8 +199,10 @@ template <bool REST>
 __global__ __launch_bounds__(TOPK_T) void topk_kernel(const float* __restrict__ dist, int ld, const int32_t* __restrict__ root_off,
                                                       int n_queries, int ent_base, int n_ent, int k, bool first_chunk,
                                                       float* __restrict__ out_dist, int32_t* __restrict__ out_ids,
-                                                      int32_t* __restrict__ count, int room, const int32_t* __restrict__ any) {
+                                                      const int32_t* __restrict__ gave_up, int32_t* __restrict__ count, int room,
+                                                      const int32_t* __restrict__ any) {
     const int pieces = REST ? (n_ent + RANK_PIECE - 1) / RANK_PIECE : 1;
+    if (*gave_up) n_ent = 0;             // (uniform)
     if (REST && !marked_piece(any, pieces)) return;        // uniform
     __shared__ float s_d[TOPK_LIST], s_bound[TOPK_T / 64], s_run[KMAX];
     __shared__ int s_i[TOPK_LIST], s_run_i[KMAX], s_n;
@@ -410,7 +412,7 @@ __global__ __launch_bounds__(256) void finish_rank_kernel(const int32_t* __restr
                                                           int n_ans, const int32_t* __restrict__ gave_up, int32_t* __restrict__ rank) {
     const int a = blockIdx.x * blockDim.x + threadIdx.x;
     if (a >= n_ans) return;
-    if (gave_up && *gave_up) {           // (uniform: no entity is closer than an answer at no distance, which would be rank 1)
+    if (*gave_up) {                      // (uniform: no entity is closer than an answer at no distance, which would be rank 1)
         rank[a] = 0;
         return;
     }
@@ -536,18 +538,19 @@ hipError_t launch_fill_zero_i32(int32_t* p, int n, hipStream_t s) {
 }
 
 hipError_t launch_topk_merge(const float* dist, int ld, const int32_t* root_off, int n_queries, int ent_base, int n_ent,
-                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, hipStream_t s,
+                             int k, bool first_chunk, float* out_dist, int32_t* out_ids, const int32_t* gave_up, hipStream_t s,
                              const Overflowed* only) {
     if (n_queries <= 0) return hipSuccess;
+    if (!gave_up) return hipErrorInvalidValue;
     if (k < 1 || k > KMAX) return hipErrorInvalidValue;
     if (ld & 3) return hipErrorInvalidValue;
     const dim3 block(n_ent > 4096 ? TOPK_T : 256);
     if (only)
         hipLaunchKernelGGL(topk_kernel<true>, dim3(std::min(n_queries, TOPK_FEW)), block, 0, s, dist, ld, root_off, n_queries, ent_base, n_ent, k,
-                           first_chunk, out_dist, out_ids, only->count, only->room, only->any);
+                           first_chunk, out_dist, out_ids, gave_up, only->count, only->room, only->any);
     else
         hipLaunchKernelGGL(topk_kernel<false>, dim3(n_queries), block, 0, s, dist, ld, root_off, n_queries, ent_base, n_ent, k, first_chunk, out_dist,
-                           out_ids, (int32_t*)nullptr, 0, (const int32_t*)nullptr);
+                           out_ids, gave_up, (int32_t*)nullptr, 0, (const int32_t*)nullptr);
     return hipGetLastError();
 }
 

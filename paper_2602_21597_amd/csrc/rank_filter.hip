@@ -556,6 +556,7 @@ struct MergeArgs {
     int32_t* out_ids;
     int n_tx, ent_base, d, k, room, ldb, lde, parts;
     float rounding;
+    const int32_t* gave_up;
 };
 // One workgroup per query: gathers what the tiles left for the query's rows (clearing their words for
 // the next chunk) and merges the distances into the running top-k.  In a first chunk a list holds
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(MERGE_T) void near_merge_kernel(const MergeArgs g) 
         if (t == 0) n_near = 0;
         __syncthreads();
     }
-    if (wave == 0 && lane < k) {
+    if (wave == 0 && lane < k && !*g.gave_up) {          // (of a pass that gave up there is none from the first chunk on)
         g.out_dist[(size_t)q * k + lane] = my_d;
         g.out_ids[(size_t)q * k + lane] = my_i == INT_MAX ? -1 : my_i;
     }
@@ -824,7 +825,7 @@ __global__ __launch_bounds__(64) void answer_distance_kernel(const float* __rest
                                                              const int32_t* __restrict__ ans_off, int n_queries,
                                                              const int32_t* __restrict__ ans, int a0, int cnt,
                                                              const float* __restrict__ E, const uint16_t* __restrict__ E16, int d,
-                                                             float* __restrict__ thr, int32_t* __restrict__ counters, int n_ans) {
+                                                             const int32_t* __restrict__ gave_up, float* __restrict__ thr, int32_t* __restrict__ counters, int n_ans) {
     const int i = blockIdx.x * 64 + threadIdx.x, a = a0 + i;
     if (i >= cnt) return;
     counters[a] = counters[n_ans + a] = 0;
@@ -856,7 +857,7 @@ __global__ __launch_bounds__(64) void answer_distance_kernel(const float* __rest
         }
         best = fminf(best, acc);
     }
-    thr[a] = best;
+    thr[a] = *gave_up ? INFINITY : best;
 }
 
 // Bounds of the distance of a (row, entity) pair from its sum, the entity's error in steps and the row's
@@ -902,6 +903,7 @@ struct PickArgs {
     int32_t* out_ids;
     int ld, n_ent, d, k, room, ldb;
     float rounding;
+    const int32_t* gave_up;
 };
 template <bool B16>
 __global__ __launch_bounds__(PICK_T, 4) void pick_kernel(const PickArgs g) {
@@ -1052,7 +1054,7 @@ __global__ __launch_bounds__(PICK_T, 4) void pick_kernel(const PickArgs g) {
     }
     __syncthreads();
     if (t < k) {
-        const uint64_t key = s_run[t];
+        const uint64_t key = *g.gave_up ? NONE : s_run[t];
         g.out_dist[(size_t)q * k + t] = key == NONE ? INFINITY : __builtin_bit_cast(float, (uint32_t)(key >> 32));
         g.out_ids[(size_t)q * k + t] = key == NONE ? -1 : (int32_t)(uint32_t)key;
     }
@@ -1330,8 +1332,9 @@ hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, c
                              int n_queries, const float* E, const uint16_t* E16, int ent_base, int n_ent, int k, float* out_dist,
                              int32_t* out_ids, hipStream_t s) {
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
+    if (!f.gave_up) return hipErrorInvalidValue;
     const MergeArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, f.found, f.found_pair, f.count,
-                      f.overflowed + piece, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, f.lde, f.parts, rounding_of(f.d)};
+                      f.overflowed + piece, out_dist, out_ids, (n_ent + 127) / 128, ent_base, f.d, k, f.room, f.ldy, f.lde, f.parts, rounding_of(f.d), f.gave_up};
     const bool wide = n_queries <= MERGE_WIDE_TO;
     const dim3 grid(n_queries), block(wide ? 256 : 128);
     if (E16 && wide) hipLaunchKernelGGL((near_merge_kernel<true, 256>), grid, block, 0, s, g);
@@ -1344,9 +1347,9 @@ hipError_t launch_near_merge(const RankFilter& f, int piece, const float* act, c
 hipError_t launch_pick(const RankFilter& f, const uint32_t* sums, int ld, const float* act, const int32_t* row_ids, const int32_t* root_off,
                        int n_queries, const float* E, const uint16_t* E16, int n_ent, int k, float* out_dist, int32_t* out_ids, hipStream_t s) {
     if (n_queries <= 0 || n_ent <= 0) return hipSuccess;
-    if (k < 1 || k > NGDB_MAX_TOPK || f.parts != 1 || (ld & 3) || n_ent > RANK_PIECES * RANK_PIECE) return hipErrorInvalidValue;      // (NGDB_MAX_BRANCH rows a query: the planner's)
+    if (k < 1 || k > NGDB_MAX_TOPK || f.parts != 1 || !f.gave_up || (ld & 3) || n_ent > RANK_PIECES * RANK_PIECE) return hipErrorInvalidValue;      // (NGDB_MAX_BRANCH rows a query: the planner's)
     const PickArgs g{act, E, f.base, f.grid, E16, row_ids, root_off, f.slack, sums, reinterpret_cast<const int2*>(f.found_pair), f.count, f.overflowed, out_dist, out_ids,
-                     ld, n_ent, f.d, k, f.room, f.ldy, rounding_of(f.d)};
+                     ld, n_ent, f.d, k, f.room, f.ldy, rounding_of(f.d), f.gave_up};
     if (E16) hipLaunchKernelGGL(pick_kernel<true>, dim3(n_queries), dim3(PICK_T), 0, s, g);
     else hipLaunchKernelGGL(pick_kernel<false>, dim3(n_queries), dim3(PICK_T), 0, s, g);
     return hipGetLastError();
@@ -1375,15 +1378,16 @@ hipError_t launch_sum_tile(const RankFilter& f, int n_rows, int n_ent, uint32_t*
 
 hipError_t launch_answer_distance(const float* act, const float* off, float alpha, const int32_t* row_ids, const int32_t* root_off,
                                   const int32_t* ans_off, int n_queries, const int32_t* ans, int a0, int cnt, const float* E,
-                                  const uint16_t* E16, int d, float* thr, int32_t* counters, int n_ans, hipStream_t s) {
+                                  const uint16_t* E16, int d, const int32_t* gave_up, float* thr, int32_t* counters, int n_ans, hipStream_t s) {
     if (cnt <= 0) return hipSuccess;
+    if (!gave_up) return hipErrorInvalidValue;
     const dim3 grid((cnt + 63) / 64), block(64);
     if (off)
         hipLaunchKernelGGL((answer_distance_kernel<true>), grid, block, 0, s, act, off, alpha, row_ids, root_off, ans_off, n_queries, ans,
-                           a0, cnt, E, E16, d, thr, counters, n_ans);
+                           a0, cnt, E, E16, d, gave_up, thr, counters, n_ans);
     else
         hipLaunchKernelGGL((answer_distance_kernel<false>), grid, block, 0, s, act, off, alpha, row_ids, root_off, ans_off, n_queries, ans,
-                           a0, cnt, E, E16, d, thr, counters, n_ans);
+                           a0, cnt, E, E16, d, gave_up, thr, counters, n_ans);
     return hipGetLastError();
 }
 

@@ -424,6 +424,54 @@ def test_layers_of_some_rows_that_give_up_waiting():
     plan.free()
 
 
+# ... nothing of such a pass can be taken for a result, whatever follows it: deeper depths of few rows in launches of their own, whose relu makes a number of what is none, unions
+# one branch of which is valid, the filter of rankings, in chunks and as a whole; passes of a few rows, of more and of small models; both families
+@pytest.mark.parametrize("box,d,h,B,N", [(False, 400, 800, 60, 900), (False, 400, 800, 60, 5000), (False, 400, 800, 60, 70000), (False, 400, 800, 4, 900), (False, 36, 52, 60, 900),
+                                         (False, 36, 52, 60, 5000), (True, 300, 500, 60, 900), (True, 36, 52, 60, 900)])
+def test_nothing_of_a_pass_that_gave_up_is_a_result(box, d, h, B, N):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    rng = np.random.default_rng(B)
+    R = 9
+    proj = lambda t=None: ("p", int(rng.integers(R)), t or ("e", int(rng.integers(N))))
+    trees = [(proj(), proj(proj()), ("i", proj(), proj(proj())), ("u", proj(), proj(proj())))[i % 4] for i in range(B - 2)] + [proj(proj(proj())), ("u", proj(), proj(proj(proj())))]
+    eng = Engine(N, R, d, h, 8.0, family=binding.FAMILY_BOX if box else binding.FAMILY_VEC)
+    eng.bind_numpy((wl.make_box_params if box else wl.make_params)(N, R, d, h, 6))
+    if N > 900:
+        assert binding.lib().ngdb_debug_rank_filter_from(eng.ctx, 0) == 0
+    cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    off = torch.arange(0, 2 * B + 1, 2, dtype=torch.int32, device="cuda")
+    ans = cand[:, :2].contiguous().view(-1)
+    polls = lambda n: binding.lib().ngdb_debug_chain_polls(eng.ctx, n)
+    chunks = lambda on: binding.lib().ngdb_debug_rank_by_chunks(eng.ctx, on)
+    plan = eng.plan(wl.batch_from_trees(trees, [0] * B))
+
+    def ranked(on):
+        assert chunks(on) == 0
+        return eng.rank_all(plan, 3)
+
+    calls = [(lambda: eng.score(plan, cand), lambda s: bool((s == -np.inf).all())),
+             (lambda: ranked(0), lambda r: bool((r[0] == -1).all()) and bool((r[1] == np.inf).all())),
+             (lambda: ranked(1), lambda r: bool((r[0] == -1).all()) and bool((r[1] == np.inf).all())),
+             (lambda: eng.rank_answers(plan, off, ans), lambda r: bool((r[0] == 0).all()) and bool((r[1] == np.inf).all()))]
+    if B > 16 or box or d < 128:
+        calls.append((lambda: eng.train_step(plan, cand), lambda loss: float(loss) == np.inf))
+    before = {k: t[0].clone() for k, t in eng.tensors.items()}
+    want = eng.score(plan, cand).clone()
+    for call, nothing in calls:
+        assert polls(0) == 0
+        got = call()
+        assert nothing(got), got
+        torch.cuda.synchronize()
+        with pytest.raises(binding.NgdbError) as e:
+            eng.score(plan, cand)
+        assert e.value.code == binding.ERR_HIP, str(e.value)
+    assert all(torch.equal(before[k], eng.tensors[k][0]) for k in before)
+    assert polls(1 << 22) == 0
+    assert torch.equal(eng.score(plan, cand), want)
+    plan.free()
+
+
 def chain_launches(eng):
     """Launches of several layers so far (few rows, forward, backward), and their tiles that were computed by a workgroup with another one."""
     from paper_2602_21597_amd import binding
