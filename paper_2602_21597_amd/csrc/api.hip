@@ -312,11 +312,15 @@ int gslot_of(int t) { return t == T_PROJ ? 0 : (t == T_NEG ? 4 : 8); }
 struct FwdBytes;
 FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim);
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
-// Whether there is room for the weights split once for a pass.  The two MLPs of the box family are split from as many inputs of intersections on as some 800 queries have (a
-// step of 4096 boxes at d = 400, h = 800 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; a step of 512 takes the host as
-// long as the device, with and without), and where a launch of several layers needs it.
+// Whether the weights are split once for a pass, and hidden rows handed on as pieces: with vectors always; the two MLPs of the box family from as many inputs of intersections on as
+// some 800 queries have (a step of 4096 boxes at d = 400, h = 800 619 us without and 528 with, of 1024 246 and 226, scoring 1024 108 and 102; a step of 512 takes the host as
+// long as the device, with and without; its first pass at d = 300, h = 500 takes 530 to 580 us, with room for both, 18 MB in two allocations, up to 1930).
 constexpr int BOX_PIECES_FROM = 768;
-bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows > 0; }
+bool all_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows >= BOX_PIECES_FROM; }
+// ... or the weights alone, for a launch of several layers (tile_chain_kernel) that the pass may have (first passes 545 to 560 us).
+bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) {
+    return all_split(c, hp) || (hp.n_int_rows > 0 && !level_fits(c->cfg.d, c->cfg.h, true) && tile_chain_most(c->cfg.d, c->cfg.h, true, true) > 0);
+}
 // bytes of the split weights: per MLP two operands of ceil(h/32) x ceil(d/16) tiles and two of ceil(d/32) x ceil(h/16)
 size_t weight_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
     if (!weights_split(c, hp)) return 0;
@@ -326,7 +330,7 @@ size_t weight_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
 constexpr size_t H_PIECES_MAX_ROWS = 2048;      // launches over more rows do not write pieces
 int h_pieces_kt(const ngdb_ctx_t* c) { return 2 * ((c->cfg.h + 31) / 32); }
 size_t h_pieces_bytes(const ngdb_ctx_t* c, const HostPlan& hp) {
-    if (!weights_split(c, hp)) return 0;
+    if (!all_split(c, hp)) return 0;
     const bool box = c->cfg.family == NGDB_FAMILY_BOX;       // centres and offsets of the intersections' inputs
     const size_t rows = std::min<size_t>(box ? 2 * (size_t)hp.n_int_rows : (size_t)hp.n_proj + hp.n_int_rows + hp.n_neg, H_PIECES_MAX_ROWS);
     return (rows / 32 + 3) * h_pieces_kt(c) * 1536 * sizeof(uint16_t);
@@ -535,7 +539,7 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
         for (const Segment& sg : segs) narrow = narrow && ((box && sg.type == T_PROJ) || gemm_takes_rows(sg.rows, std::max(d, h)));
     }
     ChainDepths depths;
-    if (narrow || (box && pl->hp.n_int_rows < BOX_PIECES_FROM && !chain_depths(c, pl, backward, &depths))) return;
+    if (narrow || (!all_split(c, pl->hp) && !chain_depths(c, pl, backward, &depths))) return;
     uint16_t* at = ptr<uint16_t>(c->w_pieces);
     for (int t = 0; t < 3; ++t) {
         if (box && t == T_PROJ) continue;

@@ -396,6 +396,28 @@ def test_layers_of_some_boxes_in_one_launch(d, h, B):
         assert all(torch.equal(a, b) for a, b in zip(*out)), [i for i, (a, b) in enumerate(zip(*out)) if not torch.equal(a, b)]
 
 
+# Memory of contexts of few boxes: room for split weights where a launch of several layers may read them (both widths from 128 on), and for nothing else of that kind
+def test_few_boxes_hold_what_their_passes_read():
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R, B, h = 200, 5, 40, 600
+    qb = wl.batch_from_trees([("p", 1, ("i", ("p", 2, ("e", i)), ("p", 3, ("e", i + 1)))) for i in range(B)], [0] * B)
+    cand = torch.arange(B * 3, dtype=torch.int32, device="cuda").view(B, 3)
+    held = {}
+    for d in (124, 128):
+        eng = Engine(N, R, d, h, 8.0, family=binding.FAMILY_BOX)
+        eng.bind_numpy(wl.make_box_params(N, R, d, h, 5))
+        plan = eng.plan(qb)
+        eng.train_step(plan, cand)
+        torch.cuda.synchronize()
+        held[d] = binding.lib().ngdb_debug_device_bytes(eng.ctx)
+        plan.free()
+    tiles = lambda n, k: -(-n // 32) * -(-k // 16) * 1536
+    pieces = 2 * 2 * 2 * (tiles(h, 128) + tiles(128, h))        # two MLPs, both orientations of both layers, two bytes a value
+    without = held[124] * 128 / 124                              # (buffers have a quarter more than is needed)
+    assert without + pieces < held[128] < without + 1.25 * pieces + (1 << 18), (held, pieces)
+
+
 # ... one that gives up waiting (here at once): the rows of its depths are nobody's results, parameters stay as they were, and the next call is refused
 def test_layers_of_some_rows_that_give_up_waiting():
     import torch
