@@ -538,6 +538,28 @@ def test_tiles_of_workgroups_that_start_late(box, d, h, B):
     assert helped[0] == 0 and helped[1] > 0
 
 
+# ... the first ones of a context, whose memory an earlier context's launches have left their marks in
+def test_first_layers_of_a_context():
+    import torch
+    from paper_2602_21597_amd import Engine
+    N, R, d, h = 900, 9, 260, 516
+    params = wl.make_params(N, R, d, h, 6)
+    qb = wl.batch_from_trees([("p", 1, ("i", ("p", 2, ("e", i)), ("p", 3, ("e", i + 1)))) for i in range(60)], [0] * 60)
+    cand = torch.arange(60 * 9, dtype=torch.int32, device="cuda").view(60, 9)
+    got = []
+    for first in (60, 2, 60, 2):
+        eng = Engine(N, R, d, h, 8.0)
+        eng.bind_numpy(params)
+        for n in (first, 62 - first, 60, 2):
+            plan = eng.plan(qb.select(np.arange(n)))
+            got.append((n, eng.score(plan, cand[:n].contiguous()).clone()))
+            plan.free()
+        assert list(chain_launches(eng)[:2]) == [2, 2]
+        del eng
+    want = {n: s for n, s in got[:2]}
+    assert all(torch.equal(s, want[n]) for n, s in got)
+
+
 # ... two contexts on two streams, calls of both under way at a time: each as it is alone, in launches of several layers all the same
 @pytest.mark.parametrize("patience", [1024, 0])
 @pytest.mark.parametrize("B", [60, 2])
