@@ -603,7 +603,7 @@ bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
         r->H[t] = ptr<float>(c->H[t]);
     }
     r->E = c->prm.E.p; r->R = c->prm.R.p; r->act = ptr<float>(c->act); r->Z = ptr<float>(c->Z[T_INTER]);
-    return true;
+    return rows_chain_lay_out(*r);
 }
 
 // The first launch of a pass: the plan to the device and the weights as pieces.
@@ -633,18 +633,15 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
         r.clear = bits + (c->chain_odd ? 0 : CHAIN_SYNC);
         r.help = tile_help(c);
         Timed tm(c, NGDB_TK_GEMM_FWD, s);
-        const hipError_t e = launch_rows_chain(r, s);
-        if (e == hipSuccess) {
-            ++c->chain_count[0];
-            c->chain_odd = !c->chain_odd;
-            double flop = 0.0;
-            for (const std::vector<Segment>& segs : pl->levels) flop += level_flop(c, segs);
-            tm.work(GEMM_FP32, flop);
-            c->chained = c->rows_chained = true;
-            plan_uploaded(c, pl);
-            return NGDB_OK;
-        }
-        if (e != hipErrorInvalidValue) HIPCHK(c, e);
+        HIPCHK(c, launch_rows_chain(r, s));
+        ++c->chain_count[0];
+        c->chain_odd = !c->chain_odd;
+        double flop = 0.0;
+        for (const std::vector<Segment>& segs : pl->levels) flop += level_flop(c, segs);
+        tm.work(GEMM_FP32, flop);
+        c->chained = c->rows_chained = true;
+        plan_uploaded(c, pl);
+        return NGDB_OK;
     }
     PieceJobs J{};
     if (!pl->uploaded) {

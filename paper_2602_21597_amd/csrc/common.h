@@ -425,7 +425,7 @@ struct RowsChain {                                  // (what every tile needs fi
     unsigned long long *through, *clear;            // CHAIN_SYNC words each: zero at first; zero at last
     TileHelp help;
     LevelSync sync;                                 // (its counts are not used)
-    int count[LEVEL_CHAIN] = {}, first[2 * LEVEL_CHAIN + 1] = {};    // problems of a depth; tiles before each layer (filled in by the launch)
+    int count[LEVEL_CHAIN] = {}, first[2 * LEVEL_CHAIN + 1] = {};    // problems of a depth; tiles before each layer (rows_chain_lay_out)
     RowsProblem p[LEVEL_CHAIN][CHAIN_PROBLEMS];
     const float *Wa[3], *ba[3], *Wb[3], *bb[3];     // by type: projection, intersection, negation
     const float *E, *R;
@@ -433,7 +433,9 @@ struct RowsChain {                                  // (what every tile needs fi
     PlanCopy copy;
     int32_t words[CHAIN_WORDS];
 };
-hipError_t launch_rows_chain(RowsChain& r, hipStream_t s);
+// Counts its tiles.  False: too many for one launch, or not such a pass.
+bool rows_chain_lay_out(RowsChain& r);
+hipError_t launch_rows_chain(const RowsChain& r, hipStream_t s);
 // All layers of a pass over up to some hundred rows a depth in one launch (gemm.hip: tile_chain_kernel).  A problem is a projection or negation
 // group (k = 1) or one class of intersections (k inputs each): rows row0 + j * n + i of its type's buffers, references ref0 + ... (and
 // relations rel0 + ..., -1: none), outputs out0 + i.  Limits: inputs of an intersection, input values and hidden values of a row, problems of a depth.

@@ -706,23 +706,28 @@ hipError_t launch_level(const LevelArgs& a, bool backward, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_rows_chain(RowsChain& r, hipStream_t s) {
-    if (r.depths < 1 || r.depths > LEVEL_CHAIN || r.d < 4 || r.h < 4 || (r.d & 3) || (r.h & 3) || std::max(r.d, r.h) > CHAIN_WIDTH || r.n_words > CHAIN_WORDS ||
-        !r.through || !r.clear || !r.help.helped || !r.sync.gave_up || !r.sync.host_gave_up || r.copy.n < 0 || (r.copy.n > 0 && (!r.copy.src || !r.copy.dst)))
-        return hipErrorInvalidValue;
+bool rows_chain_lay_out(RowsChain& r) {
+    if (r.depths < 1 || r.depths > LEVEL_CHAIN || r.d < 4 || r.h < 4 || (r.d & 3) || (r.h & 3) || std::max(r.d, r.h) > CHAIN_WIDTH || r.n_words > CHAIN_WORDS) return false;
     int tiles = 0;
     for (int l = 0; l < 2 * r.depths; ++l) {
-        if (l > 0 && tiles - r.first[l - 1] > CHAIN_LINES * CHAIN_BITS) return hipErrorInvalidValue;
+        if (l > 0 && tiles - r.first[l - 1] > CHAIN_LINES * CHAIN_BITS) return false;
         r.first[l] = tiles;
-        if (r.count[l >> 1] < 1 || r.count[l >> 1] > CHAIN_PROBLEMS) return hipErrorInvalidValue;
+        if (r.count[l >> 1] < 1 || r.count[l >> 1] > CHAIN_PROBLEMS) return false;
         for (int q = 0; q < r.count[l >> 1]; ++q) {
             const RowsProblem& p = r.p[l >> 1][q];
-            if (p.n < 1 || p.k < 1 || p.k > CHAIN_CARD || p.type < 0 || p.type > 2 || p.at < 0 || p.at + p.n * (p.k + 1 + (p.type == 0 ? 1 : 0)) > r.n_words) return hipErrorInvalidValue;
+            if (p.n < 1 || p.k < 1 || p.k > CHAIN_CARD || p.type < 0 || p.type > 2 || p.at < 0 || p.at + p.n * (p.k + 1 + (p.type == 0 ? 1 : 0)) > r.n_words) return false;
             tiles += chain_row_groups(p, l & 1) * chain_col_groups(l & 1 ? r.d : r.h);
         }
     }
     for (int l = 2 * r.depths; l <= 2 * LEVEL_CHAIN; ++l) r.first[l] = tiles;
-    if (tiles > CHAIN_TILES) return hipErrorInvalidValue;
+    return tiles <= CHAIN_TILES;
+}
+
+hipError_t launch_rows_chain(const RowsChain& r, hipStream_t s) {
+    const int tiles = r.first[2 * LEVEL_CHAIN];
+    if (tiles < 1 || tiles > CHAIN_TILES || !r.through || !r.clear || !r.help.helped || !r.sync.gave_up || !r.sync.host_gave_up || r.copy.n < 0 ||
+        (r.copy.n > 0 && (!r.copy.src || !r.copy.dst)))
+        return hipErrorInvalidValue;
     const size_t bytes = (size_t)CHAIN_ROWS * std::max(r.d, r.h) * sizeof(float);
     hipLaunchKernelGGL(rows_chain_kernel, dim3(tiles + (r.copy.n > 0 ? 1 : 0)), dim3(CHAIN_T), bytes, s, r);
     return hipGetLastError();

@@ -538,6 +538,44 @@ def test_tiles_of_workgroups_that_start_late(box, d, h, B):
     assert helped[0] == 0 and helped[1] > 0
 
 
+# ... passes that keep a launch a layer: more tiles than one launch takes, captures; nothing is counted that was not launched
+@pytest.mark.parametrize("box,d,h,B,captured", [(False, 1024, 1024, 24, False), (False, 400, 800, 3, True), (True, 300, 500, 40, True)])
+def test_passes_that_keep_a_launch_a_layer(box, d, h, B, captured):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R = 200, 5
+    eng = Engine(N, R, d, h, 8.0, family=binding.FAMILY_BOX if box else binding.FAMILY_VEC)
+    eng.bind_numpy((wl.make_box_params if box else wl.make_params)(N, R, d, h, 5))
+    p = lambda t: ("p", 1, t)
+    e = lambda i: ("e", i % N)
+    # (24: few rows a layer, but 2304 tiles in all)
+    kinds = [lambda i: p(("i", p(e(i)), p(e(i + 1))))] if box or B < 16 else [lambda i: p(("n", ("i", e(i), e(i + 1)))), lambda i: p(("n", ("n", e(i)))), lambda i: p(p(e(i)))]
+    plan = eng.plan(wl.batch_from_trees([kinds[i * len(kinds) // B](i) for i in range(B)], [0] * B))
+    cand = torch.arange(B * 3, dtype=torch.int32, device="cuda").view(B, 3) % N
+    counts, out = [], []
+    for polls in (-1, 1 << 22):
+        assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
+        eng.score(plan, cand)
+        before = chain_launches(eng)
+        if captured:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                got = eng.score(plan, cand)
+            counts.append(None)
+            graph.replay()
+            torch.cuda.synchronize()
+            out.append(got.clone())
+        else:
+            eng.set_timing(("gemm_fwd", "inter"))
+            eng.get_timing(reset=True)
+            out.append(eng.score(plan, cand).clone())
+            counts.append({k: v[1] for k, v in eng.get_timing(reset=True).items()})
+            eng.set_timing(())
+        assert (chain_launches(eng) == before).all()
+    assert counts[0] == counts[1] and torch.equal(out[0], out[1]), counts
+    plan.free()
+
+
 # ... the first ones of a context, whose memory an earlier context's launches have left their marks in
 def test_first_layers_of_a_context():
     import torch
