@@ -12,6 +12,14 @@ from . import parity as par
 pytestmark = pytest.mark.gpu
 
 
+def chain_launches(eng):
+    """Launches of several layers so far (few rows, forward, backward), and their tiles that were computed by a workgroup with another one."""
+    from paper_2602_21597_amd import binding
+    n = [binding.lib().ngdb_debug_chain_launches(eng.ctx, kind) for kind in range(4)]
+    assert min(n) >= 0
+    return np.array(n)
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 5, 4), (1, 800, 400), (2, 401, 260), (3, 36, 1024), (8, 17, 800), (9, 72, 100),
                                    (16, 33, 1024), (17, 33, 64), (1, 9, 16384), (3, 8, 5460), (4, 16, 1028), (5, 12, 400)])
 def test_forward_layers_of_few_rows(M, N, K):
@@ -284,10 +292,12 @@ def test_layers_of_a_few_rows_in_one_launch(d, h, B):
     cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
     ans = cand[:, :2].contiguous().view(-1)
     off = torch.arange(0, 2 * B + 1, 2, dtype=torch.int32, device="cuda")
+    taken = {}
     for trees in batches:
         qb = wl.batch_from_trees(trees, [0] * B)
         out = []
         for polls in (-1, 1 << 22):
+            before = chain_launches(eng)
             assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
             got = []
             for call in (lambda p: [eng.score(p, cand)], lambda p: list(eng.rank_all(p, 3)), lambda p: list(eng.rank_answers(p, off, ans))):
@@ -300,7 +310,10 @@ def test_layers_of_a_few_rows_in_one_launch(d, h, B):
             got.append(eng.forward_backward(plan, cand).clone())
             plan.free()
             out.append(got)
+            taken[polls] = taken.get(polls, 0) + (chain_launches(eng) - before)[0]
         assert all(torch.equal(a, b) for a, b in zip(*out)), trees
+    # (seven calls without allocations or gradients, for the batches of which no query is of the last two kinds)
+    assert taken == {-1: 0, 1 << 22: 7 * max(0, 8 - B)}
 
 
 # ... one that gives up waiting (here at once): nobody can take what it leaves for results, the next call is refused, and what is computed
@@ -350,6 +363,7 @@ def test_layers_of_some_rows_in_one_launch(d, h, B):
     eng = Engine(N, R, d, h, 8.0)
     params = wl.make_params(N, R, d, h, 6)
     cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    count = np.zeros(4, int)
     for some in batches:
         qb = wl.batch_from_trees([some[i % len(some)]() for i in range(B)], [int(x) for x in rng.integers(0, N, B)])
         out = []
@@ -363,7 +377,12 @@ def test_layers_of_some_rows_in_one_launch(d, h, B):
             got += [t[0].clone() for t in eng.tensors.values()] + [t[2].clone() for t in eng.tensors.values()]
             plan.free()
             out.append(got[2:])
+            if polls < 0:
+                assert (chain_launches(eng) == count).all()
         assert all(torch.equal(a, b) for a, b in zip(*out)), [i for i, (a, b) in enumerate(zip(*out)) if not torch.equal(a, b)]
+        count = chain_launches(eng)
+    # (forward and backward passes of most batches, where the widths are taken)
+    assert (count[0], count[1] >= 12, count[2] >= 12) == (0, d <= 512, d <= 512), count
 
 
 # ... of boxes: projections and both sides of intersections, classes of two to four inputs and one more, depths without intersections, of too few
@@ -380,6 +399,7 @@ def test_layers_of_some_boxes_in_one_launch(d, h, B):
     inter = lambda k: ("i",) + tuple(proj() for _ in range(k))
     kinds = [lambda: proj(), lambda: inter(2), lambda: proj(inter(3)), lambda: ("i", proj(), proj(proj())), lambda: ("u", proj(), proj(proj())), lambda: inter(4)]
     cand = torch.from_numpy(rng.integers(0, N, (B, 9)).astype(np.int32)).cuda()
+    count = np.zeros(4, int)
     for some in (kinds, kinds[:4], kinds + [lambda: inter(5)], kinds[:2] + [lambda: proj(proj(proj(proj(proj()))))], kinds[:1] + kinds[4:5], kinds[2:4]):
         qb = wl.batch_from_trees([some[i % len(some)]() for i in range(B)], [int(x) for x in rng.integers(0, N, B)])
         out = []
@@ -393,7 +413,12 @@ def test_layers_of_some_boxes_in_one_launch(d, h, B):
             got += [t[0].clone() for t in eng.tensors.values()] + [t[2].clone() for t in eng.tensors.values()]
             plan.free()
             out.append(got[2:])
+            if polls < 0:
+                assert (chain_launches(eng) == count).all()
         assert all(torch.equal(a, b) for a, b in zip(*out)), [i for i, (a, b) in enumerate(zip(*out)) if not torch.equal(a, b)]
+        count = chain_launches(eng)
+    # (forward and backward passes of most batches, where the widths are taken)
+    assert (count[0], count[1] >= 12, count[2] >= 12) == (0, d <= 512, d <= 512), count
 
 
 # Memory of contexts of few boxes: room for split weights where a launch of several layers may read them (both widths from 128 on), and for nothing else of that kind
@@ -416,6 +441,31 @@ def test_few_boxes_hold_what_their_passes_read():
     pieces = 2 * 2 * 2 * (tiles(h, 128) + tiles(128, h))        # two MLPs, both orientations of both layers, two bytes a value
     without = held[124] * 128 / 124                              # (buffers have a quarter more than is needed)
     assert without + pieces < held[128] < without + 1.25 * pieces + (1 << 18), (held, pieces)
+
+
+# ... with text features, whose anchors' rows are fused by the pass itself; and beside many rows that are fused on the library's stream, where forward passes keep their launches
+@pytest.mark.parametrize("K,beside", [(9, False), (400, True)])
+def test_layers_of_some_rows_with_text_features(K, beside):
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R, d, h, ds, B = 30000, 9, 128, 256, 64, 60
+    rng = np.random.default_rng(8)
+    e = lambda: ("e", int(rng.integers(N)))
+    qb = wl.batch_from_trees([("p", 1, ("i", ("p", 2, e()), ("p", 3, e()))) for _ in range(B)], [int(x) for x in rng.integers(0, N, B)])
+    cand = torch.from_numpy(rng.integers(0, N, (B, K)).astype(np.int32)).cuda()
+    params = wl.make_params(N, R, d, h, 6, ds)
+    eng = Engine(N, R, d, h, 8.0, d_sem=ds, num_streams=2)
+    out = []
+    for polls in (-1, 1 << 22):
+        assert binding.lib().ngdb_debug_chain_polls(eng.ctx, polls) == 0
+        eng.bind_numpy(params, sem_bits=wl.make_sem_features(N, ds, 7))
+        before = chain_launches(eng)
+        plan = eng.plan(qb)
+        got = [eng.score(plan, cand).clone()] + [eng.train_step(plan, cand).clone() for _ in range(2)] + [t[0].clone() for t in eng.tensors.values()]
+        plan.free()
+        out.append(got)
+        assert list((chain_launches(eng) - before)[:3]) == ([0, 0, 0] if polls < 0 else [0, 1 if beside else 3, 2])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
 
 
 # ... one that gives up waiting (here at once): the rows of its depths are nobody's results, parameters stay as they were, and the next call is refused
@@ -492,14 +542,6 @@ def test_nothing_of_a_pass_that_gave_up_is_a_result(box, d, h, B, N):
     assert polls(1 << 22) == 0
     assert torch.equal(eng.score(plan, cand), want)
     plan.free()
-
-
-def chain_launches(eng):
-    """Launches of several layers so far (few rows, forward, backward), and their tiles that were computed by a workgroup with another one."""
-    from paper_2602_21597_amd import binding
-    n = [binding.lib().ngdb_debug_chain_launches(eng.ctx, kind) for kind in range(4)]
-    assert min(n) >= 0
-    return np.array(n)
 
 
 # ... every eighth workgroup late (some milliseconds, or until its tile is taken): the others compute its tiles, each once, and the results are the same bits.  A
@@ -629,6 +671,38 @@ def test_layers_of_some_rows_on_two_streams(B, patience):
         plan.free()
 
 
+# ... two processes on the card, both with such launches: each as it is by launches of a layer
+_PROCESS = """
+import sys
+import numpy as np, torch
+import workloads as wl
+from paper_2602_21597_amd import Engine, binding
+B, N, R = int(sys.argv[1]), 900, 9
+eng = Engine(N, R, 300, 400, 8.0)
+eng.bind_numpy(wl.make_params(N, R, 300, 400, 6))
+plan = eng.plan(wl.batch_from_trees([("p", 1, ("i", ("p", 2, ("e", i)), ("p", 3, ("e", i + 1)))) for i in range(B)], [0] * B))
+cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
+assert binding.lib().ngdb_debug_chain_polls(eng.ctx, -1) == 0
+want = eng.score(plan, cand).clone()
+assert binding.lib().ngdb_debug_chain_polls(eng.ctx, 1 << 22) == 0
+for _ in range(150):
+    got = [eng.score(plan, cand) for _ in range(20)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(g, want) for g in got)
+assert sum(binding.lib().ngdb_debug_chain_launches(eng.ctx, kind) for kind in (0, 1)) == 3000
+"""
+
+
+def test_layers_of_some_rows_in_two_processes():
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    children = [subprocess.Popen([sys.executable, "-c", _PROCESS, str(B)], cwd=root, stderr=subprocess.PIPE, text=True) for B in (160, 2)]
+    ends = [child.communicate(timeout=100)[1][-2000:] for child in children]
+    assert [child.returncode for child in children] == [0, 0], ends
+
+
 # ... captured: every replay as the call, with other launches of the kind in between
 def test_layers_of_some_rows_captured():
     import torch
@@ -655,6 +729,40 @@ def test_layers_of_some_rows_captured():
         eng.score(other, cand[:25].contiguous())
     plan.free()
     other.free()
+
+
+# ... a stream that has run such a launch is captured while another context has one on a stream of its own: neither notices the other
+def test_layers_of_some_rows_beside_a_capture():
+    import torch
+    from paper_2602_21597_amd import Engine
+    N, R, B = 900, 9, 60
+    rng = np.random.default_rng(4)
+    e = lambda: ("e", int(rng.integers(N)))
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
+    sides = []
+    for seed in (6, 7):
+        eng, stream = Engine(N, R, 260, 516, 8.0), torch.cuda.Stream()
+        eng.bind_numpy(wl.make_params(N, R, 260, 516, seed))
+        plan = eng.plan(wl.batch_from_trees([("p", 3, ("i", ("p", 1, e()), ("p", 2, e()))) for _ in range(B)], [0] * B))
+        with torch.cuda.stream(stream):
+            sides.append((eng, plan, stream, eng.score(plan, cand).clone()))
+    torch.cuda.synchronize()
+    (a, plan_a, stream_a, want_a), (b, plan_b, stream_b, want_b) = sides
+    with torch.cuda.stream(stream_a):
+        a.score(plan_a, cand)
+    before = chain_launches(b)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream_a, capture_error_mode="relaxed"):
+        out = a.score(plan_a, cand)
+        with torch.cuda.stream(stream_b):
+            got = b.score(plan_b, cand)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want_a) and torch.equal(got, want_b)
+    assert list((chain_launches(b) - before)[:3]) == [0, 1, 0]
+    for _, plan, _, _ in sides:
+        plan.free()
 
 
 # ... captured, and so the launch of all depths of a small model, which copies the plan too: every replay as the call
