@@ -1247,9 +1247,9 @@ __device__ __forceinline__ int tc_take_first(const TileChain& r, int end) {
     }
     return TILE_GO;
 }
-// Waits until all tiles of the layer before are through, each counted in one of its words; of every thread: what to do (TILE_*).  taken: (of the first
+// Waits until all tiles of the layer before are through, each counted in one of its words; *state: what to do (TILE_*), for all threads.  taken: (of the first
 // thread) what tc_take said of its tile, looked at only here, as the answer is slow; helps: may take another tile meanwhile.
-__device__ __forceinline__ int tc_wait(const TileChain& r, int l, const int32_t* before_counts, int before_tiles, int polls, unsigned long long taken, bool helps, int* state) {
+__device__ __forceinline__ void tc_wait(const TileChain& r, int l, const int32_t* before_counts, int before_tiles, int polls, unsigned long long taken, bool helps, int* state) {
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x, want = (before_tiles - lane + TILE_LINES - 1) / TILE_LINES;       // of this lane's word
         const int32_t* word = before_counts + min(lane, TILE_LINES - 1) * TILE_STRIDE;
@@ -1281,7 +1281,6 @@ __device__ __forceinline__ int tc_wait(const TileChain& r, int l, const int32_t*
     }
     asm volatile("" ::: "memory");
     __syncthreads();
-    return __builtin_amdgcn_readfirstlane(*state);
 }
 // The end of a tile that others wait for (number: in its layer; counts: null where nobody does)
 __device__ __forceinline__ void tc_through(const TileChain& r, int32_t* counts, int number, bool there) {
@@ -1309,11 +1308,12 @@ __device__ __forceinline__ int tc_pool_backward(const TileChain& r, const TilePa
         a[j] = load_global4((OFFSETS ? r.Gate : r.Att) + at);
         x[j] = load_global4(r.Z[OFFSETS ? 2 : 1] + at);
     }
-    const int got = tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
-    if (got >= 0 || got == TILE_TAKEN) return got;
-    const bool there = got == TILE_GO;
+    tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
     const float* from = (OFFSETS ? r.doff : r.dact) + (size_t)(p.out0 + i) * d + c;
     const float2 g0 = card_get2(from), g1 = card_get2(from + 2);
+    const int got = __builtin_amdgcn_readfirstlane(*state);      // (looked at when the values are requested)
+    if (got >= 0 || got == TILE_TAKEN) return got;
+    const bool there = got == TILE_GO;
     auto one = [&](float g, auto of) {
         if (OFFSETS) {
             float mean = 0.f, mn = INFINITY;
@@ -1390,9 +1390,7 @@ __device__ __forceinline__ int tc_box_projection(const TileChain& r, const TileP
         rc = load_global4(r.R + rel);
         ro = load_global4(r.Ro + rel);
     }
-    const int got = tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
-    if (got >= 0 || got == TILE_TAKEN) return got;
-    const bool there = got == TILE_GO;
+    tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
     float *to_x, *to_o;
     if (BWD) {
         x = get(r.dact + out);
@@ -1411,6 +1409,9 @@ __device__ __forceinline__ int tc_box_projection(const TileChain& r, const TileP
         to_x = r.act + out;
         to_o = r.off + out;
     }
+    const int got = __builtin_amdgcn_readfirstlane(*state);
+    if (got >= 0 || got == TILE_TAKEN) return got;
+    const bool there = got == TILE_GO;
     if (!there) x = o = make_float4(NAN, NAN, NAN, NAN);
     if (inside) {
         card_put2(to_x, x.x, x.y);
@@ -1548,13 +1549,14 @@ __device__ __forceinline__ int tc_tile(const TileChain& r, uint32_t at, bool hel
             if (block_of(0, j) < nk) issue_a(block_of(0, j), j);
     };
     if (l == 0) first_rows();        // (wait for no layer)
-    const int got = tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
+    tc_wait(r, l, before_counts, before_tiles, polls, taken, helps, state);
+    if (l > 0) first_rows();
+    const int got = __builtin_amdgcn_readfirstlane(*state);      // (looked at when the rows are requested)
     if (got >= 0 || got == TILE_TAKEN) {
         wait_vm<0>();
         return got;
     }
     const bool there = got == TILE_GO;
-    if (l > 0) first_rows();
     if (pooled) {
 #pragma unroll
         for (int j = 0; j < TILE_CARD; ++j) {
