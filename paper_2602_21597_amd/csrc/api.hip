@@ -1537,7 +1537,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     sa.act = ptr<float>(c->act); sa.E = scored.rows; candidate_table(c, &sa);
     sa.root_off = pl->d_root_off; sa.root_slot = pl->d_root_slot;
     sa.pos = scored.pos; sa.cand = scored.cand; sa.B = B; sa.C = K; sa.d = d; sa.max_branch = std::max(1, hp.max_branch);
-    sa.gave_up = gave_up_mark(c); sa.gamma = c->cfg.gamma; sa.score = ptr<float>(c->score); sa.coef = ptr<float>(c->coef);
+    sa.gamma = c->cfg.gamma; sa.score = ptr<float>(c->score); sa.coef = ptr<float>(c->coef);
     sa.win = sem ? nullptr : ptr<int32_t>(c->win); sa.mask = sem ? c->mask.p : nullptr; sa.dact = ptr<float>(c->dact); sa.loss_terms = ptr<float>(c->loss_terms);
     if (box) { sa.off = ptr<float>(c->off); sa.doff = ptr<float>(c->doff); sa.alpha = c->cfg.box_alpha; }
     if (c->cfg.score_bf16) sa.E16 = ptr<uint16_t>(c->Eb);
@@ -1582,7 +1582,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     auto resolve_records = [&]() -> int {
         HIPCHK(c, launch_resolve(e_src, n_contrib, hp.n_anchor, hp.n_slots, B, K, ptr<float>(c->coef),
                                  sem ? nullptr : ptr<int32_t>(c->win), ptr<float>(c->rec_coef), ptr<int32_t>(c->rec_row),
-                                 ptr<float>(c->loss_terms), B > 0 ? 1.f / (2.f * B) : 0.f, d_loss, s_tab));
+                                 ptr<float>(c->loss_terms), B > 0 ? 1.f / (2.f * B) : 0.f, d_loss, gave_up_mark(c), s_tab));
         return NGDB_OK;
     };
     // who updates the rows resolves for itself: the launch that ends the step, or plain rows' own wavefronts
@@ -1591,7 +1591,7 @@ int run_step(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_neg, int K, 
     if (unresolved) {
         te.src = e_src; te.pair_coef = ptr<float>(c->coef); te.pair_win = sem ? nullptr : ptr<int32_t>(c->win);
         te.n_rowsrc = hp.n_anchor; te.row_base = hp.n_slots; te.B = B; te.K = K;
-        loss_sum = LossSum{ptr<float>(c->loss_terms), B, B > 0 ? 1.f / (2.f * B) : 0.f, d_loss};
+        loss_sum = LossSum{ptr<float>(c->loss_terms), B, B > 0 ? 1.f / (2.f * B) : 0.f, d_loss, gave_up_mark(c)};
     }
     if (aside) {
         HIPCHK(c, hipEventRecord(c->ev_fork, stream));

@@ -512,7 +512,7 @@ struct ScoreArgs {
     // candidate rows from a bf16 copy of the table [N, d] (bit patterns) instead of E
     const uint16_t* E16 = nullptr;
     bool streaming = false;    // E is a table beyond the caches
-    const int32_t* gave_up = nullptr;      // as LevelSync: scores are minus infinity if it is set
+    const int32_t* gave_up = nullptr;      // as LevelSync: scores are minus infinity if it is set (not in training)
     size_t table_bytes = 0;    // of the candidates' rows
 };
 hipError_t launch_score(const ScoreArgs& a, bool train, hipStream_t s);
@@ -677,10 +677,10 @@ struct TableArgs {
 // sorted contribution numbers -> records: c < n_rowsrc is gradient row row_base + c,
 // otherwise a (query, candidate) pair in the order [B positives | B*K negatives]
 // (win: winning rows per pair -> records carry act rows; null -> records carry pair numbers).
-// With loss_terms [B] the same launch also writes loss[0] = loss_scale * sum of the terms.
+// With loss_terms [B] the same launch also writes loss[0] = loss_scale * sum of the terms (infinite if *gave_up is set).
 hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_base, int B, int K, const float* coef,
                           const int32_t* win, float* rec_coef, int32_t* rec_row, const float* loss_terms,
-                          float loss_scale, float* loss, hipStream_t s);
+                          float loss_scale, float* loss, const int32_t* gave_up, hipStream_t s);
 // few: by one workgroup per compute unit (a pass that has time and should leave the chip to others); max_rows: at most so many
 // touched rows.  table_takes_once: by a wavefront a row, which may resolve the records of its row (a.src)
 bool table_takes_once(const TableArgs& a, bool few, int64_t max_rows);
@@ -698,8 +698,9 @@ struct TableTail {
     int n_loss;
     float loss_scale;
     float* loss;
+    const int32_t* gave_up;
 };
-struct LossSum { const float* terms; int n; float scale; float* loss; };
+struct LossSum { const float* terms; int n; float scale; float* loss; const int32_t* gave_up; };       // gave_up: the loss is infinite if it is set
 hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArgs* small, int n_small, int small_rows,
                             const DenseAdamJob& dense, const LossSum& loss, const AdamHyper& hp, hipStream_t s);
 

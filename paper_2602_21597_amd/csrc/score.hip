@@ -74,7 +74,7 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const ScoreArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int d4 = a.d >> 2;
     const int r0 = a.root_off[i];
-    const int nb = *a.gave_up ? 0 : a.root_off[i + 1] - r0;          // (no branch: nothing is near)
+    const int nb = !TRAIN && *a.gave_up ? 0 : a.root_off[i + 1] - r0;          // (no branch: nothing is near.  Training: the sum of the loss looks at the mark)
     const int has_pos = a.pos ? 1 : 0;
     const int CT = a.C + has_pos;
     // (forward only: the list may be shared by gridDim.y workgroups, equal slices of it each)
@@ -402,7 +402,7 @@ hipError_t launch_nch(const ScoreArgs& a, bool train, hipStream_t s) {
 
 hipError_t launch_score(const ScoreArgs& a, bool train, hipStream_t s) {
     if (a.B <= 0) return hipSuccess;
-    if (!a.gave_up) return hipErrorInvalidValue;
+    if (!train && !a.gave_up) return hipErrorInvalidValue;
     if (a.C + (a.pos ? 1 : 0) <= 0) return hipErrorInvalidValue;   // the kernel clamps into a non-empty candidate list
     if (train && (a.win == nullptr) == (a.mask == nullptr)) return hipErrorInvalidValue;   // exactly one of the two
     if (a.off && (a.mask || (train && !a.doff))) return hipErrorInvalidValue;

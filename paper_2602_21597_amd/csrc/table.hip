@@ -43,14 +43,14 @@ __device__ __forceinline__ Record record_of(int32_t c, int n_rowsrc, int row_bas
 }
 
 // one workgroup of 256 threads
-__device__ __forceinline__ void sum_loss(const float* __restrict__ terms, int n, float scale, float* __restrict__ loss) {
+__device__ __forceinline__ void sum_loss(const float* __restrict__ terms, int n, float scale, const int32_t* gave_up, float* __restrict__ loss) {
     __shared__ float part[4];
     float s = 0.f;
     for (int i = threadIdx.x; i < n; i += 256) s += terms[i];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) loss[0] = scale * ((part[0] + part[1]) + (part[2] + part[3]));
+    if (threadIdx.x == 0) loss[0] = *gave_up ? INFINITY : scale * ((part[0] + part[1]) + (part[2] + part[3]));
 }
 
 // rec_row[t] >= 0: pair contribution (rec_coef[t] = dL/ds): the row of act of the pair's
@@ -62,10 +62,10 @@ __global__ __launch_bounds__(256) void resolve_kernel(const int32_t* __restrict_
                                                       const int32_t* __restrict__ win, float* __restrict__ rec_coef,
                                                       int32_t* __restrict__ rec_row,
                                                       const float* __restrict__ loss_terms, float loss_scale,
-                                                      float* __restrict__ loss) {
+                                                      float* __restrict__ loss, const int32_t* __restrict__ gave_up) {
     const int walkers = (int)gridDim.x - (loss_terms ? 1 : 0);
     if ((int)blockIdx.x == walkers) {      // (only with loss_terms)
-        sum_loss(loss_terms, B, loss_scale, loss);
+        sum_loss(loss_terms, B, loss_scale, gave_up, loss);
         return;
     }
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)walkers * blockDim.x) {
@@ -409,7 +409,7 @@ void step_tail_kernel(const TableArgs a, const TableTail tail, const AdamHyper h
     if (mb >= tail.main_blocks) {
         const int db = mb - tail.main_blocks;
         if (db == tail.dense.count * tail.dense_blocks) {
-            sum_loss(tail.loss_terms, tail.n_loss, tail.loss_scale, tail.loss);
+            sum_loss(tail.loss_terms, tail.n_loss, tail.loss_scale, tail.gave_up, tail.loss);
             return;
         }
         dense_adam(tail.dense, db / tail.dense_blocks, hp, (int64_t)(db % tail.dense_blocks) * 256 + threadIdx.x,
@@ -433,11 +433,12 @@ void step_tail_kernel(const TableArgs a, const TableTail tail, const AdamHyper h
 
 hipError_t launch_resolve(const int32_t* src, int64_t n, int n_rowsrc, int row_base, int B, int K, const float* coef,
                           const int32_t* win, float* rec_coef, int32_t* rec_row, const float* loss_terms,
-                          float loss_scale, float* loss, hipStream_t s) {
+                          float loss_scale, float* loss, const int32_t* gave_up, hipStream_t s) {
+    if (loss_terms && !gave_up) return hipErrorInvalidValue;
     if (n <= 0) return loss_terms ? launch_loss_reduce(loss_terms, B, loss_scale, loss, s) : hipSuccess;
     const unsigned blocks = (unsigned)std::min<int64_t>((n + 255) / 256, 4096) + (loss_terms ? 1 : 0);
     hipLaunchKernelGGL(resolve_kernel, dim3(blocks), dim3(256), 0, s, src, n, n_rowsrc, row_base, B, K, coef, win,
-                       rec_coef, rec_row, loss_terms, loss_scale, loss);
+                       rec_coef, rec_row, loss_terms, loss_scale, loss, gave_up);
     return hipGetLastError();
 }
 
@@ -514,7 +515,7 @@ hipError_t launch_step_tail(const TableArgs& a, int64_t max_rows, const TableArg
     int64_t longest = 0;
     for (int t = 0; t < dense.count; ++t) longest = std::max(longest, dense.n[t]);
     tail.dense_blocks = (int)std::max<int64_t>(1, std::min<int64_t>((longest + 255) / 256, 512));
-    tail.loss_terms = loss.terms; tail.n_loss = loss.n; tail.loss_scale = loss.scale; tail.loss = loss.loss;
+    tail.loss_terms = loss.terms; tail.n_loss = loss.n; tail.loss_scale = loss.scale; tail.loss = loss.loss; tail.gave_up = loss.gave_up;
     const int blocks = tail.blocks[0] + tail.blocks[1] + tail.main_blocks + dense.count * tail.dense_blocks + (loss.terms ? 1 : 0);
     if (blocks == 0) return hipSuccess;
 #define NGDB_TAIL(NCH, SEM_, BOX_, SH_)                                                                                          \
