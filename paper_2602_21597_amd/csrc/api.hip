@@ -104,7 +104,6 @@ struct ngdb_ctx_s {
     int chain_polls = CHAIN_POLLS;       // tests: see ngdb_debug_chain_polls
     int chain_patience = TILE_PATIENCE; // tests: see ngdb_debug_chain_patience
     unsigned long long chain_launch = 0; // number of the last launch whose tiles are taken
-    bool chain_ready = false;      // the words that such launches wait by have been cleared (with the first of them: 139 KB, which ngdb_create would wait for)
     bool chain_odd = false;        // which of two sets of bits the next launch of a few rows finds cleared
     int64_t chain_count[3]{};            // tests: see ngdb_debug_chain_launches
     bool captured = false;         // the pass under way is recorded into a graph: replays have no launch numbers of their own
@@ -557,11 +556,8 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
         c->wp[t][2] = jw.out_ck = backward ? at : nullptr; at += pieces_elems(h, d);
     }
     c->have_pieces = true;
-    // (counts are zero before each of the launches that follow, the words before them at first)
-    const int from = c->chain_ready || c->captured ? TILE_AT : CHAIN_AT;
-    J->clear = ptr<int32_t>(c->sync) + from;
-    J->clear_n = SYNC_WORDS - from;
-    c->chain_ready = c->chain_ready || !c->captured;
+    J->clear = ptr<int32_t>(c->sync) + TILE_AT;
+    J->clear_n = TILE_SYNC;
 }
 
 // All layers of a forward pass in one launch (rows_chain_kernel), where each would be one of a few rows: the same sums in the same order.
@@ -626,8 +622,6 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
         if (!pl->uploaded) {
             r.copy = plan_copy(pl);
         }
-        if (!c->chain_ready) HIPCHK(c, launch_fill_zero_i32(ptr<int32_t>(c->sync) + CHAIN_AT, SYNC_WORDS - CHAIN_AT, s));
-        c->chain_ready = true;
         unsigned long long* bits = reinterpret_cast<unsigned long long*>(ptr<int32_t>(c->sync) + CHAIN_AT);
         r.through = bits + (c->chain_odd ? CHAIN_SYNC : 0);
         r.clear = bits + (c->chain_odd ? 0 : CHAIN_SYNC);
@@ -2084,8 +2078,8 @@ int ngdb_create(const ngdb_config* cfg, ngdb_ctx_t** out) {
     ok = ok && hipStreamCreateWithFlags(&c->upload, hipStreamNonBlocking) == hipSuccess;
     unsigned char* sp = nullptr;
     ok = ok && noalloc_scratch(&sp) == hipSuccess;     // address of the static scratch on this GPU
-    const int32_t zeros[CHAIN_AT] = {};                // (the words behind them: chain_ready)
-    ok = ok && device_alloc(c, c->sync, SYNC_WORDS * sizeof(int32_t)) == hipSuccess && hipMemcpy(c->sync.p, zeros, sizeof(zeros), hipMemcpyHostToDevice) == hipSuccess;
+    ok = ok && device_alloc(c, c->sync, SYNC_WORDS * sizeof(int32_t)) == hipSuccess && launch_fill_zero_i32(ptr<int32_t>(c->sync), SYNC_WORDS, nullptr) == hipSuccess &&
+         hipStreamSynchronize(nullptr) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&c->gave_up, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
     if (ok) {
         *c->gave_up = 0;
@@ -2693,9 +2687,8 @@ int ngdb_debug_device_limit(ngdb_ctx_t* c, int64_t bytes) {
 int ngdb_debug_chain_polls(ngdb_ctx_t* c, int32_t polls) {
     if (!c) return NGDB_ERR_ARG;
     HIPCHK(c, hipDeviceSynchronize());
-    const int32_t zeros[CHAIN_AT] = {};
-    HIPCHK(c, hipMemcpy(c->sync.p, zeros, sizeof(zeros), hipMemcpyHostToDevice));
-    c->chain_ready = false;
+    HIPCHK(c, launch_fill_zero_i32(ptr<int32_t>(c->sync), SYNC_WORDS, nullptr));
+    HIPCHK(c, hipDeviceSynchronize());
     *c->gave_up = 0;
     c->chain_polls = polls;
     return NGDB_OK;
