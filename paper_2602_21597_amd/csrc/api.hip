@@ -492,12 +492,14 @@ int depth_tiles(const ngdb_ctx_t* c, const ngdb_plan_t* pl, const std::vector<Se
 }
 // The depths that one launch takes: the last that it can take (depths have fewer rows the deeper they are, as a rule) and those before it.  Looked
 // for in every pass, also in those of a few queries, which the host bounds: nothing is laid out here.
-// CHAIN_LAUNCHES: what it has to take the place of, two launches a depth with MLPs, three with the pooling of boxes, one of their projections (scoring
-// 16 queries at d = 320, h = 836 in one launch for the one depth of more than a few rows 68 against 61 us; a training step is the faster for one depth already).
+// CHAIN_LAUNCHES: what it has to take the place of, two launches a depth with MLPs, three with the pooling of boxes, one of their projections.  One depth of vectors
+// alone (1p, 17 to 256 queries), whose time in two launches is 24 to 31 us: at 320, 836, 400, 800 and 512, 1024 0.82 to 1.01 times as fast in one, at 208, 416 and 400, 132
+// 0.99 to 1.03, at 128, 256 0.88 to 1.04; two depths of boxes' projections (2p, 26 to 34 us) 1.00 to 1.1.  A training step is the faster for one depth already.
 struct ChainDepths { int from = 0, to = 0; };
 constexpr int CHAIN_LAUNCHES_TRAIN = 2, CHAIN_LAUNCHES = 4;
-// Tiles that wait hold the places of those that fuse rows beside them: forward passes beside more than so many contributions keep their launches (31 000 of them at 288, 224,
-// 896 features 343 against 379 us; up to 20 000 the launch of several layers is 1.00 to 1.25 times as fast).
+// Tiles that wait hold the places of those that fuse rows beside them: forward passes beside more than so many contributions keep their launches.  In one launch, steps of
+// 64 to 256 queries at 400, 800 with 1024 and 256 features, 288, 224 with 896, 208, 416 with 512 and 128, 256 with 128 were, with 2600 to 11 000 contributions, 0.98 to 1.07
+// times as fast, with 20 000 to 42 000 0.96 to 1.01, with 65 000 to 130 000 0.98 to 1.03; and one of 31 000 at 288, 224 343 us against 379.
 constexpr int64_t CHAIN_FUSED = 20000;
 bool chain_depths(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, ChainDepths* out) {
     const bool box = c->cfg.family == NGDB_FAMILY_BOX;

@@ -467,9 +467,9 @@ __global__ __launch_bounds__(LV_T) void levels_kernel(const LevelRun r) {
 // reach the next as in levels_kernel, and a wait ends like there; a tile that gave up leaves NaN, and so does then every tile of the layers behind it.
 // Tiles are dealt by workgroup number (TileHelp), and a tile that is through says so by a bit of a word that few others share: tickets and counts, each in one word taken by a few
 // hundred workgroups one after the other, were 14 us a layer; a tile that is taken before it is worked on costs the launch 3 us, a word a tile 1.
-// Scoring at d = 400, h = 800, a launch a layer and like this, us a call (the host of
-// the machine between 38 and 50 us for the former): one query 38 to 50 and 32, of it 24 this launch for three depths, four 40 to 50 and 38, eight 44 to 54
-// and 42; one at 512, 1024 37 to 50 and 33, eight at 132, 260 41 to 53 and 32.
+// Scoring against 1000 candidates, a launch a layer and like this, us a call with its plan, on average over six batches of all structures (those with an inner
+// depth of too many words keep their launches): one query at d = 400, h = 800 41.3 and 26.7 (35 to 55 and 21 to 35), four 50.3 and 37.3, eight 60 and 52; one at 512, 1024 41.3
+// and 27.0, eight at 132, 260 58 and 43.  Of a call of one query with three depths 23.4 are this launch.
 constexpr int CHAIN_ROWS = 4, CHAIN_COLS = 4, CHAIN_T = 256;
 constexpr int CHAIN_TILES = 2048;
 static_assert(CHAIN_CARD <= CHAIN_ROWS && CHAIN_ROWS * CHAIN_COLS <= 64, "an intersection is a tile, its sums a lane each");
