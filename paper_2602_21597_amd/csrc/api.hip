@@ -317,7 +317,7 @@ int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail);
 // long as the device, with and without; its first pass at d = 300, h = 500 takes 530 to 580 us, with room for both, 18 MB in two allocations, up to 1930).
 constexpr int BOX_PIECES_FROM = 768;
 bool all_split(const ngdb_ctx_t* c, const HostPlan& hp) { return c->cfg.family == NGDB_FAMILY_VEC || hp.n_int_rows >= BOX_PIECES_FROM; }
-// ... or the weights alone, for a launch of several layers (tile_chain_kernel) that the pass may have (first passes 545 to 560 us).
+// ... or the weights alone, for a launch of several layers (tile_chain_kernel) that the pass may have (first passes 515 to 630 us).
 bool weights_split(const ngdb_ctx_t* c, const HostPlan& hp) {
     return all_split(c, hp) || (hp.n_int_rows > 0 && !level_fits(c->cfg.d, c->cfg.h, true) && tile_chain_most(c->cfg.d, c->cfg.h, true, true) > 0);
 }
