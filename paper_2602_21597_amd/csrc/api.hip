@@ -614,8 +614,12 @@ int begin_pass(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, hipStream_t 
     const int waited = check_waits(c);
     if (waited != NGDB_OK) return waited;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    HIPCHK(c, hipStreamIsCapturing(s, &capture));
-    c->captured = capture != hipStreamCaptureStatusNone;
+    const hipError_t asked = hipStreamIsCapturing(s, &capture);
+    if (asked != hipSuccess) {       // (the default stream, while a stream that waits for it is captured)
+        if (!pl->uploaded) HIPCHK(c, asked);
+        (void)hipGetLastError();
+    }
+    c->captured = asked != hipSuccess || capture != hipStreamCaptureStatusNone;
     c->chained = c->rows_chained = c->plan_rides = false;
     c->trains = backward;
     c->fuses_beside = false;

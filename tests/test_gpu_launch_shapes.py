@@ -765,6 +765,37 @@ def test_layers_of_some_rows_beside_a_capture():
         plan.free()
 
 
+# ... a call on the default stream, whose state cannot be asked for while a stream that waits for it is captured, and whose plan is on the device
+def test_layers_of_some_rows_beside_a_capture_of_a_blocking_stream():
+    import ctypes
+    import torch
+    from paper_2602_21597_amd import Engine
+    N, R, B = 900, 9, 60
+    rng = np.random.default_rng(4)
+    e = lambda: ("e", int(rng.integers(N)))
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
+    eng = Engine(N, R, 260, 516, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, 260, 516, 6))
+    plan = eng.plan(wl.batch_from_trees([("p", 3, ("i", ("p", 1, e()), ("p", 2, e()))) for _ in range(B)], [0] * B))
+    want = eng.score(plan, cand).clone()
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(stream)) == 0
+    assert hip.hipStreamBeginCapture(stream, 2) == 0               # (2: relaxed)
+    try:
+        got = eng.score(plan, cand)
+    finally:
+        ended = hip.hipStreamEndCapture(stream, ctypes.byref(graph))
+    torch.cuda.synchronize()
+    assert ended == 0 and torch.equal(got, want)
+    assert torch.equal(eng.score(plan, cand), want)
+    if graph.value:
+        assert hip.hipGraphDestroy(graph) == 0
+    assert hip.hipStreamDestroy(stream) == 0
+    plan.free()
+
+
 # ... captured, and so the launch of all depths of a small model, which copies the plan too: every replay as the call
 @pytest.mark.parametrize("d,h", [(400, 800), (36, 52)])
 def test_layers_of_a_few_rows_captured(d, h):
