@@ -266,7 +266,14 @@ T* ptr(const DevBuf& b) { return static_cast<T*>(b.p); }
 // Words of c->sync: LevelSync's counts and the mark of a launch that gave up, the count of tiles that another workgroup computed, then what rows_chain_kernel and
 // tile_chain_kernel wait by: bits twice, whose tiles are taken, counts.
 constexpr int HELPED_AT = 32, CHAIN_AT = 64, TAKEN_AT = CHAIN_AT + 2 * 2 * CHAIN_SYNC, TILE_AT = TAKEN_AT + 2 * TILE_WORDS, SYNC_WORDS = TILE_AT + TILE_SYNC;
-static_assert(LEVEL_SYNC + 1 <= HELPED_AT && CHAIN_AT % 32 == 0 && TAKEN_AT % 32 == 0, "lines of their own");
+static_assert(LEVEL_SYNC + 1 <= HELPED_AT && CHAIN_AT % 32 == 0 && TAKEN_AT % 32 == 0 && SYNC_WORDS % 32 == 0, "lines of their own");
+// ... and behind them the rows of rows_chain_kernel, none of which is used twice: outputs and inputs of intersections, together no more than its words, then hidden
+// rows.  They are there from the start, so that no pass has to make the buffers grow that a captured graph may go on using.
+bool rows_chain_model(const ngdb_ctx_t* c) {
+    return c->cfg.family == NGDB_FAMILY_VEC && c->cfg.d_sem == 0 && std::max(c->cfg.d, c->cfg.h) <= CHAIN_WIDTH && !level_fits(c->cfg.d, c->cfg.h, true);
+}
+size_t rows_chain_bytes(const ngdb_ctx_t* c) { return rows_chain_model(c) ? (size_t)CHAIN_WORDS * (c->cfg.d + c->cfg.h) * sizeof(float) : 0; }
+float* rows_chain_act(const ngdb_ctx_t* c) { return ptr<float>(c->sync) + SYNC_WORDS; }
 LevelSync level_sync(const ngdb_ctx_t* c) {
     LevelSync y;
     if (c->chain_polls < 0) return y;            // (a launch per depth)
@@ -564,13 +571,13 @@ void add_weight_pieces(ngdb_ctx_t* c, const ngdb_plan_t* pl, bool backward, Piec
 
 // All layers of a forward pass in one launch (rows_chain_kernel), where each would be one of a few rows: the same sums in the same order.
 // Only passes that keep no rows for others, of the vector family without text features (whose references are made on the device).  Outputs keep a row
-// each, by slot, and every depth has rows of its own (TileWords): roots are those of passes that keep everything.  False: not such a pass.
+// each, by slot, and every depth has rows of its own (TileHelp), in memory that only these launches use: roots are those of passes that keep everything.  False: not such a pass.
 bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
     const HostPlan& hp = pl->hp;
     const int d = c->cfg.d, h = c->cfg.h;
     const LevelSync sync = level_sync(c);
-    if (c->cfg.family != NGDB_FAMILY_VEC || c->cfg.d_sem > 0 || !sync.counts || c->captured || hp.n_levels < 1 || hp.n_levels > LEVEL_CHAIN || std::max(d, h) > CHAIN_WIDTH ||
-        level_fits(d, h, true))
+    if (!rows_chain_model(c) || !sync.counts || c->captured || hp.n_levels < 1 || hp.n_levels > LEVEL_CHAIN || hp.n_slots + (int64_t)hp.n_int_rows > CHAIN_WORDS ||
+        (int64_t)hp.n_proj + hp.n_int_rows + hp.n_neg > CHAIN_WORDS)
         return false;
     r->d = d; r->h = h; r->depths = hp.n_levels; r->sync = sync;
     auto word = [&](int32_t v) { r->words[r->n_words++] = v; };
@@ -595,12 +602,15 @@ bool rows_chain(const ngdb_ctx_t* c, const ngdb_plan_t* pl, RowsChain* r) {
         }
         if (count == 0) return false;
     }
+    const int32_t hidden[3] = {hp.n_proj, hp.n_int_rows, hp.n_neg};
+    float* H = rows_chain_act(c) + (size_t)CHAIN_WORDS * d;
     for (int t = 0; t < 3; ++t) {
         const MlpRefs W = mlp_of(c->prm, t);
         r->Wa[t] = W.Wa; r->ba[t] = W.ba; r->Wb[t] = W.Wb; r->bb[t] = W.bb;
-        r->H[t] = ptr<float>(c->H[t]);
+        r->H[t] = H;
+        H += (size_t)hidden[t] * h;
     }
-    r->E = c->prm.E.p; r->R = c->prm.R.p; r->act = ptr<float>(c->act); r->Z = ptr<float>(c->Z[T_INTER]);
+    r->E = c->prm.E.p; r->R = c->prm.R.p; r->act = rows_chain_act(c); r->Z = r->act + (size_t)hp.n_slots * d;
     return rows_chain_lay_out(*r);
 }
 
@@ -1099,7 +1109,7 @@ FwdBytes forward_bytes(const ngdb_ctx_t* c, const ngdb_plan_t* pl, bool reclaim)
 // reclaimed sizes; with text features also the index over [anchors | tail] and the fused rows.
 int size_forward_only(ngdb_ctx_t* c, const ngdb_plan_t* pl, int64_t n_tail) {
     const HostPlan& hp = pl->hp;
-    const FwdBytes fb = forward_bytes(c, pl, hp.n_slots > CHAIN_WORDS);     // (nothing used twice where rows_chain may take the pass)
+    const FwdBytes fb = forward_bytes(c, pl, true);
     int rc;
 #define ENS(buf, bytes) if ((rc = ensure(c, buf, std::max<size_t>((bytes), 256))) != NGDB_OK) return rc
     ENS(c->w_pieces, weight_pieces_bytes(c, hp));
@@ -1872,7 +1882,7 @@ int rank_filter_begin(ngdb_ctx_t* c, const RankFilter& f, const float* fused_sam
 
 int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int topk, int32_t* d_ids, float* d_dist, hipStream_t s) {
     const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
-    const float* act = ptr<float>(c->act);
+    const float* act = c->rows_chained ? rows_chain_act(c) : ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
     const bool whole = !c->rank_by_chunks && (N <= RANK_CHUNK || (c->cfg.d_sem == 0 && N <= NEAR_CHUNK && (int64_t)R * N <= NEAR_DIST));
     bool filtered = rank_filtered(c, R, near_work(c, R), whole ? WHOLE_FROM : NEAR_FROM);
@@ -1969,7 +1979,7 @@ int rank_nearest(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, int
 int rank_listed(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* roots, const int32_t* d_ans_off, const int32_t* d_ans, int n_ans,
                 int32_t* d_rank, float* d_ans_dist, hipStream_t s) {
     const int N = c->cfg.n_entities, d = c->cfg.d, R = pl->hp.n_roots, B = pl->hp.n_queries;
-    const float* act = ptr<float>(c->act);
+    const float* act = c->rows_chained ? rows_chain_act(c) : ptr<float>(c->act);
     const float* box_off = c->cfg.family == NGDB_FAMILY_BOX ? ptr<float>(c->off) : nullptr;
     const bool sem = c->cfg.d_sem > 0;
     // (with very many answers per query most entities are undecided for one of them)
@@ -2084,7 +2094,7 @@ int ngdb_create(const ngdb_config* cfg, ngdb_ctx_t** out) {
     ok = ok && hipStreamCreateWithFlags(&c->upload, hipStreamNonBlocking) == hipSuccess;
     unsigned char* sp = nullptr;
     ok = ok && noalloc_scratch(&sp) == hipSuccess;     // address of the static scratch on this GPU
-    ok = ok && device_alloc(c, c->sync, SYNC_WORDS * sizeof(int32_t)) == hipSuccess && launch_fill_zero_i32(ptr<int32_t>(c->sync), SYNC_WORDS, nullptr) == hipSuccess &&
+    ok = ok && device_alloc(c, c->sync, SYNC_WORDS * sizeof(int32_t) + rows_chain_bytes(c)) == hipSuccess && launch_fill_zero_i32(ptr<int32_t>(c->sync), SYNC_WORDS, nullptr) == hipSuccess &&
          hipStreamSynchronize(nullptr) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&c->gave_up, sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
     if (ok) {
@@ -2432,7 +2442,7 @@ int ngdb_score(ngdb_ctx_t* c, const ngdb_plan_t* pl, const int32_t* d_cand, int3
     if (rc != NGDB_OK) return rc;
     if (d_cand) {
         ScoreArgs sa{};
-        sa.act = ptr<float>(c->act); sa.E = er.rows; candidate_table(c, &sa);
+        sa.act = c->rows_chained ? rows_chain_act(c) : ptr<float>(c->act); sa.E = er.rows; candidate_table(c, &sa);
         sa.root_off = pl->d_root_off; sa.root_slot = roots;
         sa.pos = nullptr; sa.cand = er.cand; sa.B = pl->hp.n_queries; sa.C = C; sa.d = c->cfg.d;
         sa.max_branch = std::max(1, pl->hp.max_branch); sa.gave_up = gave_up_mark(c); sa.gamma = c->cfg.gamma; sa.score = d_scores;

@@ -765,6 +765,37 @@ def test_layers_of_some_rows_beside_a_capture():
         plan.free()
 
 
+# ... a pass over some of its queries, or over a handful, makes no buffer grow that the graph uses
+def test_fewer_queries_after_a_capture():
+    import torch
+    from paper_2602_21597_amd import Engine, binding
+    N, R, B = 900, 9, 60
+    rng = np.random.default_rng(4)
+    eng = Engine(N, R, 260, 516, 8.0)
+    eng.bind_numpy(wl.make_params(N, R, 260, 516, 6))
+    qb = wl.batch_from_trees([("p", 3, ("p", 1, ("p", 2, ("e", int(rng.integers(N)))))) for _ in range(B)], [0] * B)
+    cand = torch.arange(B * 9, dtype=torch.int32, device="cuda").view(B, 9) % N
+    plan = eng.plan(qb)
+    want = eng.score(plan, cand).clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = eng.score(plan, cand)
+    few = [(n, eng.plan(qb.select(np.arange(n)))) for n in (53, 16, 2)]
+    allocs = binding.lib().ngdb_debug_alloc_count(eng.ctx)
+    for n, some in few:
+        got = eng.score(some, cand[:n].contiguous())
+        assert binding.lib().ngdb_debug_alloc_count(eng.ctx) == allocs, n
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert binding.lib().ngdb_debug_chain_polls(eng.ctx, -1) == 0
+        assert torch.equal(got, eng.score(some, cand[:n].contiguous()))
+        assert binding.lib().ngdb_debug_chain_polls(eng.ctx, 1 << 22) == 0
+        some.free()
+    plan.free()
+
+
 # ... a call on the default stream, whose state cannot be asked for while a stream that waits for it is captured, and whose plan is on the device
 def test_layers_of_some_rows_beside_a_capture_of_a_blocking_stream():
     import ctypes
